@@ -1,9 +1,15 @@
 // gr_item_mask_build: valid-item mask blob from the sorted item table (paper Section 6.1).
 //
-// The table is scanned once.  A row that starts a new first token contributes a level-0 bit and the
-// row offsets of that token; a row that starts a new (t1,t2) pair contributes a level-1 bit and one
-// entry of the sparse pair list (the CSR form of level 1, which is also the row index of level 2).
-// Pair positions come from a three-kernel exclusive scan (block counts, scan of counts, scatter).
+// A row that starts a new first token contributes the row offsets of that token; a row that starts a new
+// (t1,t2) pair contributes one entry of the sparse pair list (the CSR form of level 1, which is also the
+// row index of level 2).  The first pass over the table counts the pairs of every block of rows, the
+// second one places them; the two bit levels are then made from the finished pair list, one workgroup per first token.
+//
+// Bound: memory (the table twice, the second time mostly from the Infinity Cache, and what is written once): 10 M items at
+// V = 8192 take 25 us (count: 4.7 TB/s) + 35 us (scatter: 230 MB) + 11 us (bits), against 44 + 5 (scan) + 222 us with rows
+// taken in runs per thread (96-byte strides between lanes) and bits set by atomics in memory.
+// Both passes bring a block's rows in with whole-line 16-byte loads through LDS and take rows lane by lane, so
+// that every store is contiguous over the wavefront; a row's place in the pair list is a ballot rank.
 #include "gr_internal.hpp"
 
 namespace {
@@ -11,20 +17,59 @@ namespace {
 constexpr int kBuildThreads = 256;
 constexpr int kRowsPerThread = 8;
 constexpr int kRowsPerBlock = kBuildThreads * kRowsPerThread;
+constexpr int kBuildWaves = kBuildThreads / 64;
+constexpr int kBitThreads = 256;
+// With more blocks of rows than this their counts are scanned by a kernel of its own (5 us and a launch at any size);
+// below, every workgroup of the second pass adds up the counts in front of it (at most 32 KB of L2 reads, about 2 us).
+constexpr int kSumBlocks = 8192;
 
-__global__ void k_fill_u32(uint32_t* p, size_t n, uint32_t v) {
-  size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  size_t stride = (size_t)gridDim.x * blockDim.x;
-  for (; i < n; i += stride) p[i] = v;
+// where the parts of the blob lie
+struct MaskParts {
+  gr_mask_header* head;
+  uint32_t* l0;
+  uint32_t* l1;
+  int32_t* off1;
+  int32_t* pair_off;
+  int32_t* pair_t2;
+  int32_t* pair_row;
+  int32_t* t3;
+};
+
+// The block's rows as they lie in the table: s_rows[3 + 3 r + c] = column c of the block's row r; s_rows[0..2] = the row in
+// front of the block (of the first block: tokens -1, which no valid row equals and every valid row follows).
+__device__ __forceinline__ int stage_rows(const int32_t* items, int64_t n, int32_t* s_rows) {
+  const int64_t first = (int64_t)blockIdx.x * kRowsPerBlock;
+  const int rows = (int)(n - first < kRowsPerBlock ? n - first : kRowsPerBlock);
+  const int32_t* src = items + 3 * first;
+  const int ints = 3 * rows, t = threadIdx.x;
+  if (((uintptr_t)src & 15) == 0) {                       // (blocks start at multiples of 24 KiB of the table)
+    const int quads = ints >> 2;
+    int4 q[3 * kRowsPerBlock / 4 / kBuildThreads];
+#pragma unroll
+    for (int k = 0; k < 3 * kRowsPerBlock / 4 / kBuildThreads; k++)
+      if (t + k * kBuildThreads < quads) q[k] = ((const int4*)src)[t + k * kBuildThreads];
+#pragma unroll
+    for (int k = 0; k < 3 * kRowsPerBlock / 4 / kBuildThreads; k++) {
+      const int i = t + k * kBuildThreads;
+      if (i < quads) { int32_t* d = s_rows + 3 + 4 * i; d[0] = q[k].x; d[1] = q[k].y; d[2] = q[k].z; d[3] = q[k].w; }
+    }
+    const int i = 4 * quads + t;
+    if (i < ints) s_rows[3 + i] = src[i];
+  } else {
+    for (int i = t; i < ints; i += kBuildThreads) s_rows[3 + i] = src[i];
+  }
+  if (t < 3) s_rows[t] = first > 0 ? src[t - 3] : -1;
+  __syncthreads();
+  return rows;
 }
 
-__device__ __forceinline__ bool row_ok_and_flags(const int32_t* items, int64_t i, int V, bool* new_t1, bool* new_pair) {
-  const int32_t a = items[3 * i], b = items[3 * i + 1], c = items[3 * i + 2];
-  bool ok = (a >= 0 && a < V && b >= 0 && b < V && c >= 0 && c < V);
-  if (i == 0) { *new_t1 = true; *new_pair = true; return ok; }
-  const int32_t pa = items[3 * i - 3], pb = items[3 * i - 2], pc = items[3 * i - 1];
+// row r of the block against the row in front of it; false when the table is not valid there
+__device__ __forceinline__ bool row_ok_and_flags(const int32_t* s_rows, int r, int V, bool* new_t1, bool* new_pair) {
+  const int32_t* p = s_rows + 3 * r;
+  const int32_t pa = p[0], pb = p[1], pc = p[2], a = p[3], b = p[4], c = p[5];
+  const bool ok = a >= 0 && a < V && b >= 0 && b < V && c >= 0 && c < V;
   // strictly increasing lexicographic order
-  bool gt = (a > pa) || (a == pa && (b > pb || (b == pb && c > pc)));
+  const bool gt = (a > pa) || (a == pa && (b > pb || (b == pb && c > pc)));
   *new_t1 = (a != pa);
   *new_pair = (a != pa) || (b != pb);
   return ok && gt;
@@ -32,32 +77,35 @@ __device__ __forceinline__ bool row_ok_and_flags(const int32_t* items, int64_t i
 
 // pass 1: validate rows, count pair starts per block
 __global__ void __launch_bounds__(kBuildThreads) k_mask_count(const int32_t* items, int64_t n, int V, int32_t* block_counts, int32_t* err) {
-  __shared__ int s_cnt;
-  if (threadIdx.x == 0) s_cnt = 0;
-  __syncthreads();
-  int64_t base = (int64_t)blockIdx.x * kRowsPerBlock;
+  __shared__ int32_t s_rows[3 * kRowsPerBlock + 3];
+  __shared__ int s_cnt[kBuildWaves];
+  const int rows = stage_rows(items, n, s_rows);
   int cnt = 0;
   bool bad = false;
+#pragma unroll
   for (int k = 0; k < kRowsPerThread; k++) {
-    int64_t i = base + (int64_t)k * kBuildThreads + threadIdx.x;
-    if (i < n) {
-      bool t1, pr;
-      if (!row_ok_and_flags(items, i, V, &t1, &pr)) bad = true;
-      cnt += pr ? 1 : 0;
-    }
+    const int r = k * kBuildThreads + (int)threadIdx.x;
+    bool t1 = false, pr = false;
+    if (r < rows && !row_ok_and_flags(s_rows, r, V, &t1, &pr)) bad = true;
+    cnt += __popcll(__ballot(pr));
   }
   if (bad) atomicOr(err, 1);
-  atomicAdd(&s_cnt, cnt);
+  if ((threadIdx.x & 63) == 0) s_cnt[threadIdx.x >> 6] = cnt;
   __syncthreads();
-  if (threadIdx.x == 0) block_counts[blockIdx.x] = s_cnt;
+  if (threadIdx.x == 0) {
+    int sum = 0;
+#pragma unroll
+    for (int w = 0; w < kBuildWaves; w++) sum += s_cnt[w];
+    block_counts[blockIdx.x] = sum;
+  }
 }
 
-// pass 2: exclusive scan of the per-block counts by a single block; total -> counts[nblocks]
+// Exclusive scan of the per-block counts by a single workgroup (large tables only, see kSumBlocks).
 __global__ void __launch_bounds__(1024) k_mask_scan(int32_t* counts, int nblocks) {
   __shared__ int s_part[1024];
   const int t = threadIdx.x;
   const int per = (nblocks + 1023) / 1024;
-  const int lo = t * per, hi = min(nblocks, lo + per);
+  const int lo = min(nblocks, t * per), hi = min(nblocks, lo + per);
   int sum = 0;
   for (int i = lo; i < hi; i++) sum += counts[i];
   s_part[t] = sum;
@@ -70,69 +118,128 @@ __global__ void __launch_bounds__(1024) k_mask_scan(int32_t* counts, int nblocks
   }
   int run = s_part[t] - sum;
   for (int i = lo; i < hi; i++) { int c = counts[i]; counts[i] = run; run += c; }
-  if (t == 1023) counts[nblocks] = s_part[1023];
 }
 
-// pass 3: scatter pairs, set bits, fill offsets, copy the third column
-__global__ void __launch_bounds__(kBuildThreads) k_mask_scatter(const int32_t* items, int64_t n, int V, const int32_t* block_base,
-                                                                int nblocks, char* blob, const int32_t* err) {
+// pass 2: scatter pairs, fill offsets, copy the third column
+__global__ void __launch_bounds__(kBuildThreads) k_mask_scatter(const int32_t* items, int64_t n, int V, const int32_t* block_counts,
+                                                                bool scanned, MaskParts m, const int32_t* err) {
+  __shared__ int32_t s_rows[3 * kRowsPerBlock + 3];
+  __shared__ int s_base[kBuildWaves];
+  __shared__ int s_cnt[kRowsPerThread * kBuildWaves + 1];  // pair starts of every 64 consecutive rows, then their exclusive prefix and sum
   if (*err) return;   // a bad table could index out of bounds; the host reports GR_ERR_BAD_TABLE
-  const gr_mask_header* h = (const gr_mask_header*)blob;
-  uint32_t* l0 = (uint32_t*)(blob + h->off_l0);
-  uint32_t* l1 = (uint32_t*)(blob + h->off_l1);
-  int32_t* off1 = (int32_t*)(blob + h->off_off1);
-  int32_t* pair_off = (int32_t*)(blob + h->off_pair_off);
-  int32_t* pair_t2 = (int32_t*)(blob + h->off_pair_t2);
-  int32_t* pair_row = (int32_t*)(blob + h->off_pair_row);
-  int32_t* t3 = (int32_t*)(blob + h->off_t3);
-  const int words = h->words;
-
-  // rows are taken in contiguous runs per thread so that a serial in-thread count gives table order
-  __shared__ int s_scan[kBuildThreads];
-  const int t = threadIdx.x;
-  const int64_t first = (int64_t)blockIdx.x * kRowsPerBlock + (int64_t)t * kRowsPerThread;
-  bool nt1[kRowsPerThread], npr[kRowsPerThread];
-  int cnt = 0;
-  for (int k = 0; k < kRowsPerThread; k++) {
-    int64_t i = first + k;
-    nt1[k] = npr[k] = false;
-    if (i < n) { row_ok_and_flags(items, i, V, &nt1[k], &npr[k]); cnt += npr[k] ? 1 : 0; }
-  }
-  s_scan[t] = cnt;
-  __syncthreads();
-  for (int o = 1; o < kBuildThreads; o <<= 1) {
-    int v = (t >= o) ? s_scan[t - o] : 0;
-    __syncthreads();
-    s_scan[t] += v;
-    __syncthreads();
-  }
-  int p = block_base[blockIdx.x] + s_scan[t] - cnt;   // pair index of this thread's first pair start
-  const int total_pairs = block_base[nblocks];
-  for (int k = 0; k < kRowsPerThread; k++) {
-    int64_t i = first + k;
-    if (i >= n) break;
-    const int32_t a = items[3 * i], b = items[3 * i + 1];
-    t3[i] = items[3 * i + 2];
-    if (npr[k]) {
-      pair_t2[p] = b;
-      pair_row[p] = (int32_t)i;
-      atomicOr(&l1[(size_t)a * words + (b >> 5)], 1u << (b & 31));
-      if (nt1[k]) {
-        atomicOr(&l0[a >> 5], 1u << (a & 31));
-        const int prev = (i == 0) ? -1 : items[3 * i - 3];
-        for (int tok = prev + 1; tok <= a; tok++) { off1[tok] = (int32_t)i; pair_off[tok] = p; }
-      }
-      p++;
+  const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
+  // pairs of all blocks in front of this one
+  int part = 0;
+  if (scanned) part = t == 0 ? block_counts[blockIdx.x] : 0;
+  else
+    for (int i = 4 * t; i < (int)blockIdx.x; i += 4 * kBuildThreads) {
+      const int4 q = *(const int4*)(block_counts + i);     // (reads at most three counts past the last: inside the workspace)
+      const int left = (int)blockIdx.x - i;
+      part += q.x + (left > 1 ? q.y : 0) + (left > 2 ? q.z : 0) + (left > 3 ? q.w : 0);
     }
-    if (i == n - 1) {
-      for (int tok = a + 1; tok <= V; tok++) { off1[tok] = (int32_t)n; pair_off[tok] = total_pairs; }
-      pair_row[total_pairs] = (int32_t)n;
-      ((gr_mask_header*)blob)->n_pairs = total_pairs;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) part += __shfl_xor(part, o, 64);
+  if (lane == 0) s_base[wave] = part;
+  const int rows = stage_rows(items, n, s_rows);           // (its barrier publishes s_base)
+  int base = 0;
+#pragma unroll
+  for (int w = 0; w < kBuildWaves; w++) base += s_base[w];
+  const int64_t first = (int64_t)blockIdx.x * kRowsPerBlock;
+  bool nt1[kRowsPerThread], npr[kRowsPerThread];
+  int rank[kRowsPerThread];
+#pragma unroll
+  for (int k = 0; k < kRowsPerThread; k++) {
+    const int r = k * kBuildThreads + t;
+    nt1[k] = npr[k] = false;
+    if (r < rows) row_ok_and_flags(s_rows, r, V, &nt1[k], &npr[k]);
+    const uint64_t starts = __ballot(npr[k]);
+    rank[k] = __popcll(starts & (((uint64_t)1 << lane) - 1));
+    if (lane == 0) s_cnt[k * kBuildWaves + wave] = __popcll(starts);
+  }
+  __syncthreads();
+  if (wave == 0) {
+    constexpr int N = kRowsPerThread * kBuildWaves;
+    const int v = lane < N ? s_cnt[lane] : 0;
+    int incl = v;
+#pragma unroll
+    for (int o = 1; o < N; o <<= 1) { const int x = __shfl_up(incl, o, 64); if (lane >= o) incl += x; }
+    if (lane < N) s_cnt[lane] = incl - v;
+    if (lane == N - 1) s_cnt[N] = incl;
+  }
+  __syncthreads();
+  auto fill = [&](int tok0, int tok1, int from, int step, int row, int p) {
+    for (int tok = tok0 + from; tok <= tok1; tok += step) { m.off1[tok] = row; m.pair_off[tok] = p; }
+  };
+#pragma unroll
+  for (int k = 0; k < kRowsPerThread; k++) {
+    const int r = k * kBuildThreads + t;
+    const int p = base + s_cnt[k * kBuildWaves + wave] + rank[k];
+    const int i = (int)(first + r);
+    int tok0 = 0, tok1 = -1;                               // first tokens whose rows begin here
+    if (r < rows) {
+      m.t3[i] = s_rows[3 + 3 * r + 2];
+      if (npr[k]) { m.pair_t2[p] = s_rows[3 + 3 * r + 1]; m.pair_row[p] = i; }
+      if (nt1[k]) { tok0 = s_rows[3 * r] + 1; tok1 = s_rows[3 + 3 * r]; }
+    }
+    // few tokens are skipped as a rule; where many are, the wavefront writes them together
+    const bool many = tok1 - tok0 >= 8;
+    if (!many) fill(tok0, tok1, 0, 1, i, p);
+    for (uint64_t todo = __ballot(many); todo; todo &= todo - 1) {
+      const int l = __ffsll((unsigned long long)todo) - 1;
+      fill(__shfl(tok0, l, 64), __shfl(tok1, l, 64), lane, 64, __shfl(i, l, 64), __shfl(p, l, 64));
+    }
+  }
+  if (first + rows == n) {                                 // the last block closes the offsets
+    const int total_pairs = base + s_cnt[kRowsPerThread * kBuildWaves];
+    fill(s_rows[3 * rows] + 1, V, t, kBuildThreads, (int)n, total_pairs);
+    if (t == 0) {
+      m.pair_row[total_pairs] = (int32_t)n;
+      m.head->n_pairs = total_pairs;
     }
   }
 }
 
-__global__ void k_mask_write_header(char* blob, gr_mask_header h) { *(gr_mask_header*)blob = h; }
+// pass 3: the bits.  The workgroup of first token t1 marks its second tokens in LDS, one byte each, and writes the row of
+// level 1 once, whole (so the levels need no clearing, and no bit is set by an atomic operation: neighbours of the sorted list
+// fall in one word, where the LDS would take them one after another).  Every 32nd workgroup also writes the word of level 0
+// that its token begins.
+__global__ void __launch_bounds__(kBitThreads) k_mask_bits(int V, MaskParts m, const int32_t* err) {
+  extern __shared__ __attribute__((aligned(16))) uint4 s_mark[];        // a byte per token, `words` x 32
+  const int words = (V + 31) >> 5, t1 = blockIdx.x, t = threadIdx.x;
+  const int bad = *err, lo = m.pair_off[t1], hi = m.pair_off[t1 + 1];
+  if (bad) return;
+  constexpr int U = 4;
+  int v[U];
+  auto request = [&](int i0) {
+#pragma unroll
+    for (int k = 0; k < U; k++) v[k] = m.pair_t2[min(i0 + k * kBitThreads, hi - 1)];      // (a pair marked twice is marked)
+  };
+  if (lo + t < hi) request(lo + t);
+  for (int i = t; i < 2 * words; i += kBitThreads) s_mark[i] = make_uint4(0, 0, 0, 0);
+  __syncthreads();
+  for (int i0 = lo + t; i0 < hi; i0 += U * kBitThreads) {
+#pragma unroll
+    for (int k = 0; k < U; k++) ((uint8_t*)s_mark)[v[k]] = 1;
+    if (i0 + U * kBitThreads < hi) request(i0 + U * kBitThreads);
+  }
+  __syncthreads();
+  uint32_t* row = m.l1 + (size_t)t1 * words;
+  for (int i = t; i < words; i += kBitThreads) {
+    const uint4 a = s_mark[2 * i], b = s_mark[2 * i + 1];
+    const uint32_t q[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+    uint32_t bits = 0;
+#pragma unroll
+    for (int k = 0; k < 8; k++) bits |= ((q[k] * 0x10204080u) >> 28) << (4 * k);     // bytes 0..3 of q -> bits 0..3
+    row[i] = bits;
+  }
+  if ((t1 & 31) == 0 && t < 64) {
+    const int tok = min(t1 + t, V - 1);
+    const uint64_t some = __ballot(t < 32 && t1 + t < V && m.pair_off[tok + 1] > m.pair_off[tok]);
+    if (t == 0) m.l0[t1 >> 5] = (uint32_t)some;
+  }
+}
+
+__global__ void k_mask_begin(gr_mask_header* head, gr_mask_header h, int32_t* err) { *head = h; *err = 0; }
 
 }  // namespace
 
@@ -145,8 +252,7 @@ extern "C" size_t gr_item_mask_bytes(int64_t n_items, int32_t depth, int32_t V) 
 
 extern "C" size_t gr_item_mask_build_workspace_bytes(int64_t n_items, int32_t depth, int32_t V) {
   if (n_items <= 0 || depth != 3 || V <= 0) return 0;
-  int64_t nblocks = (n_items + kRowsPerBlock - 1) / kRowsPerBlock;
-  return 256 + gr_align256((size_t)(nblocks + 1) * 4);
+  return 256 + gr_align256((size_t)((n_items + kRowsPerBlock - 1) / kRowsPerBlock) * 4);
 }
 
 extern "C" gr_status gr_item_mask_build(const int32_t* items_sorted, int64_t n_items, int32_t depth, int32_t V, void* mask_out,
@@ -164,15 +270,22 @@ extern "C" gr_status gr_item_mask_build(const int32_t* items_sorted, int64_t n_i
   int32_t* err = (int32_t*)workspace;
   int32_t* counts = (int32_t*)((char*)workspace + 256);
   const int nblocks = (int)((n_items + kRowsPerBlock - 1) / kRowsPerBlock);
+  const bool scanned = nblocks > kSumBlocks;
+  MaskParts m;
+  m.head = (gr_mask_header*)blob;
+  m.l0 = (uint32_t*)(blob + h.off_l0);
+  m.l1 = (uint32_t*)(blob + h.off_l1);
+  m.off1 = (int32_t*)(blob + h.off_off1);
+  m.pair_off = (int32_t*)(blob + h.off_pair_off);
+  m.pair_t2 = (int32_t*)(blob + h.off_pair_t2);
+  m.pair_row = (int32_t*)(blob + h.off_pair_row);
+  m.t3 = (int32_t*)(blob + h.off_t3);
 
-  hipLaunchKernelGGL(k_mask_write_header, dim3(1), dim3(1), 0, stream, blob, h);
-  hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, stream, (uint32_t*)err, (size_t)64, 0u);
-  // zero the two bitmask levels (they are contiguous in the layout)
-  const size_t bit_words = (size_t)(h.off_off1 - h.off_l0) / 4;
-  hipLaunchKernelGGL(k_fill_u32, dim3(1024), dim3(256), 0, stream, (uint32_t*)(blob + h.off_l0), bit_words, 0u);
+  hipLaunchKernelGGL(k_mask_begin, dim3(1), dim3(1), 0, stream, m.head, h, err);
   hipLaunchKernelGGL(k_mask_count, dim3(nblocks), dim3(kBuildThreads), 0, stream, items_sorted, n_items, V, counts, err);
-  hipLaunchKernelGGL(k_mask_scan, dim3(1), dim3(1024), 0, stream, counts, nblocks);
-  hipLaunchKernelGGL(k_mask_scatter, dim3(nblocks), dim3(kBuildThreads), 0, stream, items_sorted, n_items, V, counts, nblocks, blob, err);
+  if (scanned) hipLaunchKernelGGL(k_mask_scan, dim3(1), dim3(1024), 0, stream, counts, nblocks);
+  hipLaunchKernelGGL(k_mask_scatter, dim3(nblocks), dim3(kBuildThreads), 0, stream, items_sorted, n_items, V, counts, scanned, m, err);
+  hipLaunchKernelGGL(k_mask_bits, dim3(V), dim3(kBitThreads), (size_t)h.words * 32, stream, V, m, err);
   GR_HIP_TRY(hipGetLastError());
   int32_t host_err = 0;
   GR_HIP_TRY(hipMemcpyAsync(&host_err, err, sizeof(int32_t), hipMemcpyDeviceToHost, stream));
