@@ -1,21 +1,18 @@
 // gr_beam_select: beam item step (paper Sections 6.1-6.3) on gfx950.
 //
 // Two kernels per call (no host synchronisation, no allocation; everything lives in caller buffers):
-//   k_rows         both kinds of beam row in one launch:
-//                  streamed rows, one workgroup each: validity bits staged in LDS (dense level-0 /
-//                  level-1 mask rows, or the row's sparse last-level positions set in an empty mask),
-//                  logits read ONCE with 16-byte loads and kept in registers for the max, the fp64
-//                  sum-exp and the per-chunk maxima; the validity bits come straight from the mask row in
-//                  memory, and a thinly populated row packs its valid logits before exponentiating them;
-//                  gathered rows (few valid children), one wavefront each: only those logits are read.
-//   k_select       one workgroup per request: top-W of the request's candidates by (score descending,
-//                  flat index ascending).  It never sorts the W*V candidates: the rows kernels leave
-//                  one "chunk key" (best candidate score) per 1/256th of a row; a histogram of those
-//                  keys yields a threshold that at least W candidates reach, only the chunks that
-//                  reach it are re-read, and only their candidates above the threshold are sorted
-//                  (the early-termination idea of Section 6.2: stop as soon as the survivors are
-//                  fixed).  If the survivors do not fit in LDS (massive ties) an exact MSB radix
-//                  select over all candidates takes over.
+//   k_rows         one pass over the logits.  A streamed row is read ONCE by a workgroup with 16-byte loads and kept in
+//                  registers for the max, the fp64 sum-exp and the keys; the validity bits come straight from the mask
+//                  row in memory.  A row with few valid children is gathered by one wavefront, which leaves all of its
+//                  candidate scores.
+//   k_select       one workgroup per request: top-W of the request's candidates by (score descending, flat index
+//                  ascending).  It never sorts the W*V candidates: k_rows leaves the best candidate score of every 16th of a
+//                  row; a histogram of these yields a threshold that at least W candidates reach, only what reaches
+//                  it is read again (by finer keys that k_rows left too), and a second histogram over that yields the few
+//                  candidates that are sorted (the early-termination idea of Section 6.2: stop as soon as the
+//                  survivors are fixed).  One CU draws some 40 GB/s from memory it has not seen, so what counts
+//                  is how few cache lines it has to touch.  If the survivors do not fit in LDS
+//                  (massive ties) an exact MSB radix select over all candidates takes over.
 //
 // Arithmetic that decides beam order is fixed: m = fp32 max over valid logits, S = fp64 sum of
 // exp(x - m), lse = fp32(m + log S), bias = score_in - lse (fp32), cand = bias + x (fp32), with no
@@ -24,25 +21,34 @@
 
 namespace {
 
-constexpr int kRowThreads = 256;
-constexpr int kChunksPerRow = 256;  // chunk keys stored per row (dense rows use all, sparse rows the first 64)
+constexpr int kGroups = 16;         // groups of a row's candidates; the best score of each is kept
+// and, per row, this many floats of finer data behind them:
+//   streamed row: 256 keys of 16 bits, one for every line of 32 consecutive logits of a block (the best score, rounded up);
+//   gathered row with at most kScoreMax children: all of their scores;
+//   gathered row with more: 64 keys (children k, k + 64, ...).
+constexpr int kRowFloats = 240;
+constexpr int kLines = 256;
+constexpr int kKeys = 64;
+constexpr int kScoreMax = kRowFloats;
+constexpr int kWaveMax = 1024;      // a row with at most this many children is gathered by one wavefront, one with more by a workgroup
 constexpr int kSelThreads = 1024;
-constexpr int kSparseMax = 256;     // rows with at most this many valid children are gathered, not streamed
-constexpr int kSparseKeys = 64;     // chunk keys of a gathered row (chunk k = children k, k+64, ...)
 constexpr int kListCap = 8192;      // survivors that fit in LDS
-constexpr int kChunkCap = 2048;     // chunks re-read by the fast path
+constexpr int kChunkCap = 6144;     // keys whose candidates are looked at again by the fast path
+constexpr int kUnitSpan = 256;      // children that one unit of four, 64 apart, reaches over
+constexpr int kUnitCap = 8192;      // units of four candidates that are
 constexpr int kHistBins = 2048;
 constexpr int kMaxMaskWords = 1024; // V <= 32768
-constexpr int kRegV4 = 8;           // float4 per thread kept in registers (V <= 8192)
+constexpr int kBlockV = 8192;       // logits of a row that a workgroup holds in registers at a time
 constexpr int kMaxW = 2048;
-constexpr size_t kSelLdsBytes = (size_t)kListCap * 8 + (size_t)kHistBins * 4 + (size_t)kChunkCap * 4 + (size_t)kMaxW * 20;
+constexpr int kGroupCap = 2 * kListCap;  // key groups (floats in the list's place)
+constexpr size_t kSelLdsBytes = (size_t)kListCap * 8 + (size_t)kUnitCap * 4 + (size_t)kHistBins * 4 + (size_t)kChunkCap * 4 + (size_t)kMaxW * 12;
 
-enum { ROW_DEAD = 0, ROW_DENSE = 1, ROW_SPARSE = 2 };
+enum { ROW_DEAD = 0, ROW_DENSE = 1, ROW_SPARSE = 2 };      // low bits of row_info; the child count of a gathered row above them
 
 struct SelCtx {
   int B, W, V, depth, step, flags;
-  int vec4;                  // V % 4 == 0: rows are 16-byte aligned, chunks interleave float4 groups
-  int epc;                   // element slots per chunk of a dense row
+  int row_threads;           // threads that stream a row: thread t holds tokens 4 (t + row_threads i) .. + 3 for all i
+  int unit_shift;            // log2 of the units (float4 of logits) behind a key of a streamed row: 8 per block of kBlockV logits, to a power of two
   const char* blob;          // mask blob or nullptr
   const float* logits;
   const float* scores_in;
@@ -55,10 +61,15 @@ struct SelCtx {
   int32_t* range_out;
   int32_t* item_index_out;
   float* row_bias;           // workspace [B*W]
-  int32_t* row_mode;         // workspace [B*W]
-  float* row_top;            // workspace [B*W]: best candidate score of the row (= its largest chunk key)
-  float* chunk_key;          // workspace [B*W*kChunksPerRow]
+  int32_t* row_info;         // workspace [B*W]
+  int32_t* row_start;        // workspace [B*W]: first child of a gathered row in the pair list (level 1) or in the table (level 2)
+  float* row_group;          // workspace [B*W*kGroups]
+  float* row_data;           // workspace [B*W*kRowFloats]
 };
+
+// four consecutive logits; a row begins at any multiple of 4 bytes
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u32x4u __attribute__((ext_vector_type(4), aligned(4)));
 
 struct MaskView {
   const uint32_t* l0;
@@ -89,33 +100,20 @@ __device__ __forceinline__ MaskView mask_view(const char* blob, int V, int depth
   return m;
 }
 
-// The valid children of a beam row as a sorted token list (steps 1 and 2).  A prefix or range that
-// this mask could not have produced yields an empty list instead of an out-of-bounds read.
-__device__ __forceinline__ void row_children(const SelCtx& c, const MaskView& mv, int row, const int32_t** list, int* n) {
-  if (!mv.ok) { *list = nullptr; *n = 0; return; }
+// The valid children of a beam row (steps 1 and 2): entries [start, start + n) of the pair list or of the table.  A prefix
+// or range that this mask could not have produced yields none instead of an out-of-bounds read.
+__device__ __forceinline__ void row_children(const SelCtx& c, const MaskView& mv, int row, int* start, int* n) {
+  *start = 0; *n = 0;
+  if (!mv.ok) return;
   if (c.step == 1) {
     const int t1 = c.prefix_in[(size_t)row * c.depth];
-    const bool ok = t1 >= 0 && t1 < c.V;
-    const int p0 = ok ? mv.pair_off[t1] : 0, p1 = ok ? mv.pair_off[t1 + 1] : 0;
-    *list = mv.pair_t2 + p0;
-    *n = p1 - p0;
+    if (t1 >= 0 && t1 < c.V) { *start = mv.pair_off[t1]; *n = mv.pair_off[t1 + 1] - *start; }
   } else {
-    int lo = c.range_in[2 * (size_t)row], hi = c.range_in[2 * (size_t)row + 1];
-    if (lo < 0 || hi < lo || (int64_t)hi > mv.n_items) { lo = 0; hi = 0; }
-    *list = mv.t3 + lo;
-    *n = hi - lo;
+    const int lo = c.range_in[2 * (size_t)row], hi = c.range_in[2 * (size_t)row + 1];
+    if (lo >= 0 && hi >= lo && (int64_t)hi <= mv.n_items) { *start = lo; *n = hi - lo; }
   }
 }
-
-// Does this row get gathered (true) or streamed (false)?  Same decision in every kernel.
-__device__ __forceinline__ bool row_is_sparse(const SelCtx& c, int n_children) {
-  return c.blob && c.step >= 1 && !(c.flags & GR_SELECT_FORCE_DENSE) && n_children <= kSparseMax;
-}
-
-// Token held by element slot e of chunk k of a dense row (or >= V when the slot is empty).
-__device__ __forceinline__ int dense_slot_token(const SelCtx& c, int k, int e) {
-  return c.vec4 ? 4 * (k + kChunksPerRow * (e >> 2)) + (e & 3) : k + kChunksPerRow * e;
-}
+__device__ __forceinline__ const int32_t* child_list(const SelCtx& c, const MaskView& mv) { return c.step == 1 ? mv.pair_t2 : mv.t3; }
 
 __device__ __forceinline__ int lower_bound_i32(const int32_t* a, int n, int key) {
   int lo = 0, hi = n;
@@ -123,20 +121,21 @@ __device__ __forceinline__ int lower_bound_i32(const int32_t* a, int n, int key)
   return lo;
 }
 
-// e^(x - ref) in fp64 for fp32 x <= ref (and not more than ~700 below it), about 1e-14 relative:
-//   t = (x - ref) * 64/ln2 = n + f with n = rint(t), |f| <= 1/2, both from one addition of 1.5 * 2^52 (the sum's
-//   low word then holds n); e^(x-ref) = 2^(n>>6) * 2^((n&63)/64) * 2^(f/64) with
-//   2^(f/64) - 1 = f (c1 + f (c2 + f (c3 + f c4))), c_k = (ln2/64)^k / k!  (truncation < 4e-14), the middle factor
-//   from a 64-entry table in LDS and the power of two added to the exponent field.  Eleven fp64 and four integer
-//   operations, all at the full rate (no rounding, conversion-to-integer or ldexp instruction).  The error is far
-//   below what the single fp32 rounding of lse = m + log S can see.
+// e^(x - ref) in fp64 for fp32 x <= ref (and not more than ~700 below it), about 2e-14 relative:
+//   t = (x - ref) * 256/ln2 = n + f with n = rint(t), |f| <= 1/2, both from one addition of 1.5 * 2^52 (the sum's
+//   low word then holds n); e^(x-ref) = 2^(n>>8) * 2^((n&255)/256) * 2^(f/256) with 2^(f/256) = c0 + f (c1 + f (c2 + f c3)):
+//   the Taylor terms c_k = (ln2/256)^k / k! with the fourth one spread over c0 and c2 as its Chebyshev expansion on |f| <= 1/2
+//   says (f^4 = f^2/4 - 1/128 + T_4(2 f)/128: what is left is below 2e-14).  The middle factor comes from a 256-entry table in
+//   LDS whose high words have their index subtracted, so that one shift-and-add of n makes both factors at once.
+//   Nine fp64 and three integer operations, all at the full rate (no rounding, conversion-to-integer or ldexp instruction);
+//   the exponentials are what a streamed row costs beside its bytes.  The error is far below what the single fp32 rounding
+//   of lse = m + log S can see.
 // The constants live in scalar registers (set up once per kernel): left to itself the compiler
 // re-materialises each 64-bit literal with vector moves next to every use.
-struct ExpK { double c, magic, c1, c2, c3, c4; };
+struct ExpK { double c, magic, c0, c1, c2, c3; };
 __device__ __forceinline__ ExpK exp_consts() {
-  ExpK k = {0x1.71547652b82fep+6, 0x1.8p+52, 0x1.62e42fefa39efp-7, 0x1.ebfbdff82c58fp-15, 0x1.c6b08d704a0c0p-23,
-            0x1.3b2ab6fba4e77p-31};
-  asm volatile("" : "+s"(k.c), "+s"(k.magic), "+s"(k.c1), "+s"(k.c2), "+s"(k.c3), "+s"(k.c4));
+  ExpK k = {0x1.71547652b82fep+8, 0x1.8p+52, 0x1.fffffffffff62p-1, 0x1.62e42fefa39efp-9, 0x1.ebfbe4e4d734ep-19, 0x1.c6b08d704a0c0p-29};
+  asm volatile("" : "+s"(k.c), "+s"(k.magic), "+s"(k.c0), "+s"(k.c1), "+s"(k.c2), "+s"(k.c3));
   return k;
 }
 __constant__ double c_exp_tab[64] = {        // 2^(j/64), correctly rounded
@@ -156,20 +155,27 @@ __constant__ double c_exp_tab[64] = {        // 2^(j/64), correctly rounded
     0x1.c199bdd85529cp+0, 0x1.c67f12e57d14bp+0, 0x1.cb720dcef9069p+0, 0x1.d072d4a07897cp+0,
     0x1.d5818dcfba487p+0, 0x1.da9e603db3285p+0, 0x1.dfc97337b9b5fp+0, 0x1.e502ee78b3ff6p+0,
     0x1.ea4afa2a490dap+0, 0x1.efa1bee615a27p+0, 0x1.f50765b6e4540p+0, 0x1.fa7c1819e90d8p+0};
-// rc = -(double)ref * k.c; x must be >= ref - 600 (callers clamp: what is cut off is below 1e-260 of the sum)
-__device__ __forceinline__ double exp_rel(float x, double rc, const double* tab, const ExpK& k) {
+constexpr int kExpTab = 256;
+__device__ __forceinline__ void fill_exp_tab(double* tab, int threads) {      // (the caller's barrier publishes it)
+  for (int j = threadIdx.x; j < kExpTab; j += threads) {
+    const double q = (j & 1) ? ((j & 2) ? 0x1.02168143b0281p+0 : 0x1.00b1afa5abcbfp+0) : ((j & 2) ? 0x1.0163da9fb3335p+0 : 1.0);    // 2^((j & 3)/256)
+    const double v = c_exp_tab[j >> 2] * q;
+    tab[j] = __hiloint2double(__double2hiint(v) - (j << 12), __double2loint(v));
+  }
+}
+// S + e^(x - ref); rc = -(double)ref * k.c; x must be >= ref - 600 (callers clamp: what is cut off is below 1e-260 of the sum)
+__device__ __forceinline__ double exp_add(double S, float x, double rc, const double* tab, const ExpK& k) {
   const double t = fma((double)x, k.c, rc);
   const double u = t + k.magic;
-  const int n = __double2loint(u);
+  const uint32_t n = (uint32_t)__double2loint(u);
   const double f = t - (u - k.magic);
-  double p = fma(f, k.c4, k.c3);
-  p = fma(p, f, k.c2);
+  double p = fma(f, k.c3, k.c2);
   p = fma(p, f, k.c1);
-  p = p * f;
-  const double tj = tab[n & 63];
-  const double r = fma(tj, p, tj);
-  return __hiloint2double(__double2hiint(r) + ((n >> 6) << 20), __double2loint(r));
+  p = fma(p, f, k.c0);
+  const double tj = tab[n & (kExpTab - 1)];
+  return fma(__hiloint2double(__double2hiint(tj) + (int)(n << 12), __double2loint(tj)), p, S);
 }
+__device__ __forceinline__ double exp_rel(float x, double rc, const double* tab, const ExpK& k) { return exp_add(0.0, x, rc, tab, k); }
 // max without the NaN-quieting instructions fmaxf() drags in (NaN inputs are outside the contract)
 __device__ __forceinline__ float max_raw(float a, float b) {
   float r;
@@ -177,54 +183,68 @@ __device__ __forceinline__ float max_raw(float a, float b) {
   return r;
 }
 
+// Wavefront reductions: within rows of 16 lanes by DPP, across the four rows by lane reads (the result is wave-uniform).
+template <int CTRL>
+__device__ __forceinline__ float dpp_f32(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kHalfMirror = 0x141, kMirror = 0x140;
+__device__ __forceinline__ float quad_max(float v) {
+  v = max_raw(v, dpp_f32<kXor1>(v));
+  return max_raw(v, dpp_f32<kXor2>(v));
+}
+__device__ __forceinline__ float lane_f32(float v, int l) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l)); }
+__device__ __forceinline__ float wave_max(float v) {
+  v = quad_max(v);
+  v = max_raw(v, dpp_f32<kHalfMirror>(v));
+  v = max_raw(v, dpp_f32<kMirror>(v));
+  return max_raw(max_raw(lane_f32(v, 0), lane_f32(v, 16)), max_raw(lane_f32(v, 32), lane_f32(v, 48)));
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double v) {
+  return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true),
+                          __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ double lane_f64(double v, int l) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l), __builtin_amdgcn_readlane(__double2loint(v), l));
+}
+__device__ __forceinline__ double wave_sum(double v) {
+  v += dpp_f64<kXor1>(v);
+  v += dpp_f64<kXor2>(v);
+  v += dpp_f64<kHalfMirror>(v);
+  v += dpp_f64<kMirror>(v);
+  return (lane_f64(v, 0) + lane_f64(v, 16)) + (lane_f64(v, 32) + lane_f64(v, 48));
+}
+// inclusive prefix sum over the lanes
+__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false);       // row_shr:1
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false);       // row_shr:2
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false);       // row_shr:4
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false);       // row_shr:8
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);       // lane 15 of rows 0, 2 to rows 1, 3
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);       // lane 31 to rows 2, 3
+  return v;
+}
+
 // Workgroup reductions with ONE barrier each: the per-wavefront partials go to one of two slot sets, used
 // alternately (every thread makes the same sequence of calls: `par` counts them), so a wavefront that is
 // already writing the next reduction's partials cannot disturb a slower one that still reads this one's; the
 // set after that is only written behind the next reduction's barrier.  s_red holds 2 * NWAVES entries.
 template <int NWAVES>
-__device__ __forceinline__ float block_max(float v, float* s_red, int& par) {
-  v = gr_wave_max(v);
-  float* slot = s_red + (par++ & 1) * NWAVES;
-  if (gr_lane() == 0) slot[threadIdx.x >> 6] = v;
+__device__ __forceinline__ void block_max_min(float& mx, float& mn, float2* s_red, int& par) {
+  mx = wave_max(mx);
+  mn = -wave_max(-mn);
+  float2* slot = s_red + (par++ & 1) * NWAVES;
+  if (gr_lane() == 0) slot[threadIdx.x >> 6] = make_float2(mx, mn);
   __syncthreads();
-  float r = slot[0];
 #pragma unroll
-  for (int i = 1; i < NWAVES; i++) r = fmaxf(r, slot[i]);
-  return r;
-}
-template <int NWAVES>
-__device__ __forceinline__ double block_sum(double v, double* s_red, int& par) {
-  v = gr_wave_sum(v);
-  double* slot = s_red + (par++ & 1) * NWAVES;
-  if (gr_lane() == 0) slot[threadIdx.x >> 6] = v;
-  __syncthreads();
-  double r = slot[0];
-#pragma unroll
-  for (int i = 1; i < NWAVES; i++) r += slot[i];
-  return r;
-}
-// The same with a barrier in front as well (for callers that rely on it to publish other LDS writes).
-template <int NWAVES>
-__device__ __forceinline__ float block_max2(float v, float* s_red) {
-  v = gr_wave_max(v);
-  __syncthreads();
-  if (gr_lane() == 0) s_red[threadIdx.x >> 6] = v;
-  __syncthreads();
-  float r = s_red[0];
-#pragma unroll
-  for (int i = 1; i < NWAVES; i++) r = fmaxf(r, s_red[i]);
-  return r;
+  for (int i = 0; i < NWAVES; i++) { const float2 r = slot[i]; mx = fmaxf(mx, r.x); mn = fminf(mn, r.y); }
 }
 // exclusive prefix of v over the workgroup's threads (thread order), and the total
 template <int NWAVES>
 __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* total, uint32_t* s_red, int& par) {
   const int lane = gr_lane(), wave = threadIdx.x >> 6;
-  uint32_t incl = v;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const uint32_t t = __shfl_up(incl, o, 64);
-    if (lane >= o) incl += t;
-  }
+  const uint32_t incl = wave_incl_scan(v);
   uint32_t* slot = s_red + (par++ & 1) * NWAVES;
   if (lane == 63) slot[wave] = incl;
   __syncthreads();
@@ -236,267 +256,414 @@ __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* total,
 }
 
 // ------------------------------------------------------------------------------------------------
-// Rows that are streamed in full.
+// Rows that are streamed in full: one workgroup per row.
 // ------------------------------------------------------------------------------------------------
-constexpr int kQueueMax = 2048;      // valid logits of a thinly populated streamed row that are packed before exponentiation
-__device__ __forceinline__ void row_dense(const SelCtx& c, int owns_dead, int row) {
-  __shared__ uint32_t s_mask[kMaxMaskWords];     // (general shapes and long last-level lists only)
-  __shared__ float s_q[kQueueMax];
-  __shared__ float s_redf[2 * (kRowThreads / 64)];
-  __shared__ double s_redd[2 * (kRowThreads / 64)];
-  __shared__ uint32_t s_redu[2 * (kRowThreads / 64)];
-  __shared__ double s_tab[64];
-  constexpr int NW = kRowThreads / 64;
-  int par = 0;
-  const int tid = threadIdx.x;
-  const float s_in = c.scores_in[row];
-  // (the first token of the prefix picks the level-1 mask row: asked for together with the score)
-  const int t1 = (c.blob && c.step == 1) ? c.prefix_in[(size_t)row * c.depth] : -1;
-  if (!(s_in > -INFINITY)) {
-    if (owns_dead && tid == 0) { c.row_mode[row] = ROW_DEAD; c.row_bias[row] = -INFINITY; c.row_top[row] = -INFINITY; }
-    return;                                        // the keys of a dead row are never read
-  }
-  const int V = c.V;
-  const float* x = c.logits + (size_t)row * V;
-  const bool reg = c.vec4 && V <= kRegV4 * 4 * kRowThreads;
-  // ---- the row is requested as early as it is known to be streamed (one HBM read: it stays in registers): at
-  // once when no child count can turn it into a gathered row, else after the look-up of its children
-  const int nv4 = V >> 2;
-  float4 xr[kRegV4];
-  auto request_row = [&]() {
-#pragma unroll
-    for (int i = 0; i < kRegV4; i++) {
-      const int p = tid + i * kRowThreads;
-      xr[i] = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
-      if (p < nv4) xr[i] = *(const float4*)(x + 4 * (size_t)p);
-    }
-  };
-  const bool surely_streamed = !c.blob || c.step == 0 || (c.flags & GR_SELECT_FORCE_DENSE);
-  const int32_t* list = nullptr;
-  int n_list = 0;                                  // number of valid children, where it is looked up
-  MaskView mv;
-  mv.ok = true;
-  const int words = (V + 31) >> 5;
-  // the dense mask row of this beam (levels 0 and 1), or nothing (no mask, last level, mismatched blob); a row that
-  // is streamed whatever its child count asks for the mask words and the logits at once
-  const uint32_t* mrow = nullptr;
-  uint32_t mw[kRegV4];
-#pragma unroll
-  for (int i = 0; i < kRegV4; i++) mw[i] = 0u;
-  if (c.blob) {
-    mv = mask_view(c.blob, c.V, c.depth);
-    if (mv.ok) {
-      if (c.step == 0) mrow = mv.l0;
-      else if (c.step == 1 && t1 >= 0 && t1 < V) mrow = mv.l1 + (size_t)t1 * mv.words;
-    }
-    auto request_mask = [&]() {
-#pragma unroll
-      for (int i = 0; i < kRegV4; i++) {
-        const int wi = (tid >> 3) + 32 * i;        // float4 p = tid + i * kRowThreads has its nibble in word p >> 3
-        if (wi < words) mw[i] = mrow[wi];
-      }
-    };
-    if (reg && surely_streamed) {
-      if (mrow) request_mask();
-      request_row();
-    }
-    // a level-1 row that is streamed whatever its child count needs no look-up: its mask row says what is valid
-    if (c.step >= 1 && !(c.step == 1 && (c.flags & GR_SELECT_FORCE_DENSE))) {
-      row_children(c, mv, row, &list, &n_list);
-      if (row_is_sparse(c, n_list)) return;      // a gathered row: rows_sparse owns it
-    }
-    if (reg && !surely_streamed) {
-      request_row();
-      if (mrow) request_mask();
-    }
-  } else if (reg) request_row();
-  // validity bits from the mask words: bit 4 i + j <-> token 4 (tid + i * kRowThreads) + j
-  uint32_t mbits = 0;
-#pragma unroll
-  for (int i = 0; i < kRegV4; i++) mbits |= ((mw[i] >> (4 * (tid & 7))) & 0xfu) << (4 * i);
-  if (tid < 64) s_tab[tid] = c_exp_tab[tid];
-  const ExpK ek = exp_consts();
-  // the last level has no dense mask: a long child list is set position by position in an empty LDS mask
-  // (Section 6.1's sparse form applied to an existing mask); a short one is matched against directly below
-  const bool lds_mask = !reg || (c.blob && c.step == 2 && n_list > 64);
-  if (lds_mask) {
-    if (!c.blob) {
-      for (int i = tid; i < words; i += kRowThreads) s_mask[i] = 0xffffffffu;
-    } else if (c.step == 2) {
-      for (int i = tid; i < words; i += kRowThreads) s_mask[i] = 0u;
-      __syncthreads();
-      for (int i = tid; i < n_list; i += kRowThreads) { const int v = list[i]; atomicOr(&s_mask[v >> 5], 1u << (v & 31)); }
-    } else {
-      for (int i = tid; i < words; i += kRowThreads) s_mask[i] = mrow ? mrow[i] : 0u;
-    }
-  }
-  __syncthreads();                                 // (s_tab, s_mask)
+template <int NT>
+struct RowLds {
+  float q[NT / 64][kBlockV / (NT / 64) / 4];     // valid logits of a thinly populated block, per wavefront
+  double tab[kExpTab];
+  double s[2][NT / 64];                // per-wavefront sums and maxima, and the best logit behind every key; two sets, used in turn
+  float m[2][NT / 64];                 // by successive rows
+  float key[2][kLines];
+  uint32_t mask[kMaxMaskWords];        // validity bits of a last-level row with many children
+};
 
-  float lmax = -INFINITY;     // this thread's chunk: best valid logit
-  double S = 0.0;
-  float m;
-  if (reg) {
-    // ---- validity bits straight from the mask row: bit 4 i + j <-> token 4 (tid + i * kRowThreads) + j.
-    // Invalid entries become -inf: they lose every max and add nothing to the sum.
-    uint32_t vbits = 0;
-    if (!c.blob) {
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* p, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, bytes, 0x00020000);
+}
+__device__ __forceinline__ float keep_if_bit(float x, uint32_t bits, int k) {        // x where bit k is set, else -inf
+  const uint32_t mask = (uint32_t)((int32_t)(bits << (31 - k)) >> 31);
+  return __uint_as_float((mask & __float_as_uint(x)) | (~mask & 0xff800000u));
+}
+
+// A score to 16 bits that order as scores do, rounded up; and a bound rounded down: key16_up(s) >= key16_down(t) wherever s >= t.
+__device__ __forceinline__ uint32_t key16_up(float f) { return (gr_ordkey(f) + 0xffffu) >> 16; }
+__device__ __forceinline__ uint32_t key16_down(float f) { return gr_ordkey(f) >> 16; }
+
+__device__ __forceinline__ void mark_dead(const SelCtx& c, int row) { c.row_info[row] = ROW_DEAD; }
+
+// Bound: HBM and, close behind, the fp64 exponentials: 8192 rows of 8192 logits take 53 us = 5.1 TB/s, of which the vector
+// instructions alone are 34 us (650 a wavefront; with the 64-entry table, a polynomial term and an addition more per exponential, a
+// barrier per reduction and a compare per validity bit it was 68 us).  Six workgroups a CU: 80 registers, no spills (seven: 66 us).
+//
+// `row` is live; t1 = first token of its prefix (level 1), [start, start + n_list) = its children where they were looked up
+// (all wave-uniform).  Every wavefront works relative to its own maximum and the workgroup meets once: the first wavefront then joins
+// the (max, sum) pairs and writes the row's results, while the others are free for the next row (or gone).
+template <int NT>
+__device__ __forceinline__ void row_dense(const SelCtx& c, const MaskView& mv, RowLds<NT>& L, int row, float s_in, int t1, int start, int n_list, int set) {
+  constexpr int NV4 = kBlockV / 4 / NT, NWV = NT / 64;        // float4 per thread; wavefronts
+  const int tid = threadIdx.x, wave = tid >> 6, V = c.V;
+  const float* x = c.logits + (size_t)row * V;
+  const int words = (V + 31) >> 5;
+  const uint32_t* mrow = nullptr;                  // the row's validity bits: levels 0 and 1 from the mask, else made in LDS
+  const bool all_valid = !c.blob;
+  if (c.blob) {
+    if (c.step == 0) mrow = mv.ok ? mv.l0 : nullptr;
+    else if (c.step == 1) mrow = (mv.ok && t1 >= 0 && t1 < V) ? mv.l1 + (size_t)t1 * mv.words : nullptr;
+    else {
+      // the last level has no dense mask: the child list is set position by position in an empty LDS mask
+      // (Section 6.1's sparse form applied to an existing mask)
+      __syncthreads();
+      for (int i = tid; i < words; i += NT) L.mask[i] = 0u;
+      __syncthreads();
+      for (int i = tid; i < n_list; i += NT) { const int v = mv.t3[start + i]; atomicOr(&L.mask[v >> 5], 1u << (v & 31)); }
+      __syncthreads();
+    }
+    if (c.step < 2 && !mrow) {
+      if (tid == 0) mark_dead(c, row);
+      return;
+    }
+  }
+  // loads past the end of the row or of its mask words return 0 (hardware bounds check); bits past V are 0
+  const __amdgpu_buffer_rsrc_t rx = buffer_of(x, (uint32_t)(V & ~3) * 4), rm = buffer_of(mrow, (uint32_t)words * 4);
+  const ExpK ek = exp_consts();
+  float lmax[NV4], m = -INFINITY;                  // this thread's best valid logit of each load; the wavefront's of all
 #pragma unroll
-      for (int i = 0; i < kRegV4; i++) if (tid + i * kRowThreads < nv4) vbits |= 0xfu << (4 * i);
-    } else {
-      if (lds_mask) {
+  for (int i = 0; i < NV4; i++) lmax[i] = -INFINITY;
+  double S = 0.0;                                  // the wavefront's sum relative to m
+#pragma unroll 1
+  for (int v0 = 0; v0 < V; v0 += kBlockV) {
+    // ---- one block of the row: logits and validity bits requested together
+    u32x4 xr[NV4];
+    uint32_t mw[NV4];
 #pragma unroll
-        for (int i = 0; i < kRegV4; i++) {
-          const int p = tid + i * kRowThreads;
-          if (p < nv4) vbits |= ((s_mask[p >> 3] >> (4 * (p & 7))) & 0xfu) << (4 * i);
-        }
-      } else if (c.step == 2) {
-        for (int e = 0; e < n_list; e++) {
-          const int t = list[e];
-          if (((t >> 2) & (kRowThreads - 1)) == tid) vbits |= 1u << (4 * (t >> 10) + (t & 3));
-        }
-      } else if (mrow) {
-        vbits = mbits;
-      }
+    for (int i = 0; i < NV4; i++) xr[i] = __builtin_amdgcn_raw_buffer_load_b128(rx, (v0 + 4 * tid) * 4 + i * (NT * 16), 0, 0);
+    if (mrow) {
 #pragma unroll
-      for (int i = 0; i < kRegV4; i++) {
-        if (!((vbits >> (4 * i)) & 1u)) xr[i].x = -INFINITY;
-        if (!((vbits >> (4 * i)) & 2u)) xr[i].y = -INFINITY;
-        if (!((vbits >> (4 * i)) & 4u)) xr[i].z = -INFINITY;
-        if (!((vbits >> (4 * i)) & 8u)) xr[i].w = -INFINITY;
+      for (int i = 0; i < NV4; i++) mw[i] = __builtin_amdgcn_raw_buffer_load_b32(rm, (v0 >> 5) * 4 + (tid >> 3) * 4 + i * (NT / 2), 0, 0);
+    }
+    float xv[4 * NV4];
+    // validity bits: bit 4 i + j <-> token v0 + 4 (tid + i * NT) + j
+    uint32_t vbits = 0xffffffffu;
+    const bool whole = all_valid && v0 + kBlockV <= V;
+    if (!whole) {
+      vbits = 0;
+#pragma unroll
+      for (int i = 0; i < NV4; i++) {
+        const int v = v0 + 4 * (tid + i * NT);
+        uint32_t w;
+        if (mrow) w = mw[i] >> (4 * (tid & 7));
+        else if (all_valid) { const int left = V - v; w = left >= 4 ? 0xfu : left > 0 ? (1u << left) - 1u : 0u; }
+        else w = v < V ? L.mask[v >> 5] >> (v & 31) : 0u;
+        vbits |= (w & 0xfu) << (4 * i);
       }
     }
+    const int tail = (V >> 2) - (v0 >> 2);         // the float4 that the row ends in, when it is a part of one
+    if ((V & 3) && tail >= 0 && tail < kBlockV / 4 && (tail & (NT - 1)) == tid) {
+      u32x4 t = {0, 0, 0, 0};
+      const float* xt = x + (V & ~3);
+      t.x = __float_as_uint(xt[0]);
+      if ((V & 3) > 1) t.y = __float_as_uint(xt[1]);
+      if ((V & 3) > 2) t.z = __float_as_uint(xt[2]);
 #pragma unroll
-    for (int i = 0; i < kRegV4; i++) lmax = max_raw(max_raw(max_raw(lmax, xr[i].x), max_raw(xr[i].y, xr[i].z)), xr[i].w);
-    m = block_max<NW>(lmax, s_redf, par);
-    if (m > -INFINITY) {
-      const double rc = -(double)m * ek.c;
-      const float lo = m - 600.f;
-      // thinly populated row: the valid logits are packed into a queue (thread order, so the sum is
-      // reproducible) and exponentiated with full lanes.  The count of valid bits decides (it equals the child
-      // count where that was looked up; a row known to be well populated skips the count).
-      bool queued = c.blob && c.step >= 1 && n_list <= kQueueMax;
-      uint32_t total = 0, pos = 0;
-      if (queued) {
-        pos = block_excl_scan<NW>((uint32_t)__popc(vbits), &total, s_redu, par);
-        queued = total <= (uint32_t)kQueueMax;
+      for (int i = 0; i < NV4; i++) if (i == tail / NT) xr[i] = t;
+    }
+#pragma unroll
+    for (int i = 0; i < NV4; i++) {
+      xv[4 * i] = __uint_as_float(xr[i].x); xv[4 * i + 1] = __uint_as_float(xr[i].y);
+      xv[4 * i + 2] = __uint_as_float(xr[i].z); xv[4 * i + 3] = __uint_as_float(xr[i].w);
+    }
+    // invalid entries become -inf: they lose every max and add nothing to the sum
+    if (!whole) {
+#pragma unroll
+      for (int e = 0; e < 4 * NV4; e++) xv[e] = keep_if_bit(xv[e], vbits, e);
+    }
+    float bmax = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < NV4; i++) {
+      const float mi = max_raw(max_raw(xv[4 * i], xv[4 * i + 1]), max_raw(xv[4 * i + 2], xv[4 * i + 3]));
+      lmax[i] = max_raw(lmax[i], mi);
+      bmax = max_raw(bmax, mi);
+    }
+    const float mb = wave_max(bmax);
+    if (!(mb > -INFINITY)) continue;               // (wave-uniform)
+    const double rc = -(double)mb * ek.c;
+    const float lo = mb - 600.f;
+    double Sb = 0.0;
+    // Thinly populated block (up to a quarter of the wavefront's logits are valid): the valid ones are packed into a
+    // queue (lane order, so the sum is reproducible) and exponentiated with full lanes.
+    bool packed = false;
+    if (!whole) {
+      const uint32_t mine = (uint32_t)__popc(vbits), incl = wave_incl_scan(mine);
+      const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+      packed = total <= (uint32_t)(kBlockV / NWV / 4);
+      if (packed) {
+        float* q = L.q[wave];
+        uint32_t pos = incl - mine;
+#pragma unroll
+        for (int e = 0; e < 4 * NV4; e++)
+          if ((vbits >> e) & 1u) q[pos++] = xv[e];
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll 1
+        for (uint32_t i = tid & 63; i < total; i += 64) Sb = exp_add(Sb, max_raw(q[i], lo), rc, L.tab, ek);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       }
-      if (queued) {
+    }
+    if (!packed) {
 #pragma unroll
-        for (int i = 0; i < kRegV4; i++) {
-          if (((vbits >> (4 * i)) & 1u) && pos < (uint32_t)kQueueMax) s_q[pos++] = xr[i].x;
-          if (((vbits >> (4 * i)) & 2u) && pos < (uint32_t)kQueueMax) s_q[pos++] = xr[i].y;
-          if (((vbits >> (4 * i)) & 4u) && pos < (uint32_t)kQueueMax) s_q[pos++] = xr[i].z;
-          if (((vbits >> (4 * i)) & 8u) && pos < (uint32_t)kQueueMax) s_q[pos++] = xr[i].w;
-        }
-        __syncthreads();
-        const int nq = min((int)total, kQueueMax);
-        for (int i = tid; i < nq; i += kRowThreads) S += exp_rel(max_raw(s_q[i], lo), rc, s_tab, ek);
-      } else {
+      for (int i = 0; i < NV4; i++) {
+        if (v0 + 4 * NT * i < V) {                 // (uniform)
 #pragma unroll
-        for (int i = 0; i < kRegV4; i++) {
-          S += exp_rel(max_raw(xr[i].x, lo), rc, s_tab, ek);
-          S += exp_rel(max_raw(xr[i].y, lo), rc, s_tab, ek);
-          S += exp_rel(max_raw(xr[i].z, lo), rc, s_tab, ek);
-          S += exp_rel(max_raw(xr[i].w, lo), rc, s_tab, ek);
-          // keep the four exponentials of a load together: hoisting the first halves of all 32 costs a hundred registers
-          asm volatile("" : "+v"(S)::"memory");
-          __builtin_amdgcn_sched_barrier(0);
+          for (int j = 0; j < 4; j++) Sb = exp_add(Sb, max_raw(xv[4 * i + j], lo), rc, L.tab, ek);
         }
+        // keep the four exponentials of a load together: hoisting the first halves of all costs a hundred registers
+        asm volatile("" : "+v"(Sb)::"memory");
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    if (v0 > 0) {
+      // join with the blocks before (-inf counts nothing: what is cut off at -600 is below 1e-260 of the sum)
+      const float mn = max_raw(m, mb);
+      const double rn = -(double)mn * ek.c;
+      S = S * exp_rel(max_raw(m, mn - 600.f), rn, L.tab, ek);
+      Sb = Sb * exp_rel(max_raw(mb, mn - 600.f), rn, L.tab, ek);
+      m = mn;
+    } else {
+      m = mb;
+    }
+    S += Sb;
+  }
+  S = wave_sum(S);
+  if ((tid & 63) == 0) { L.m[set][wave] = m; L.s[set][wave] = S; }
+  // The best logit of every line = of eight neighbouring threads, for each of their NV4 loads: three exchange steps (first mirrored,
+  // so that every step stays inside eight lanes), each halving the values a lane still carries while there are several.
+  {
+    const bool b2 = tid & 4, b0 = tid & 1, b1 = tid & 2;
+    auto half = [&](float a, float b, bool bit, auto&& partner) {     // a for lanes without the bit, b for lanes with it
+      const float keep = bit ? b : a, send = bit ? a : b;
+      return max_raw(keep, partner(send));
+    };
+    auto mirror = [](float v) { return dpp_f32<kHalfMirror>(v); };
+    auto xor1 = [](float v) { return dpp_f32<kXor1>(v); };
+    auto xor2 = [](float v) { return dpp_f32<kXor2>(v); };
+    float* key = L.key[set] + (tid >> 3) * NV4;
+    if (NV4 == 8) {
+      float u[4], v[2];
+#pragma unroll
+      for (int i = 0; i < 4; i++) u[i] = half(lmax[i], lmax[i + NV4 / 2], b2, mirror);
+#pragma unroll
+      for (int i = 0; i < 2; i++) v[i] = half(u[i], u[i + 2], b0, xor1);
+      key[4 * b2 + 2 * b0 + b1] = half(v[0], v[1], b1, xor2);
+    } else {
+      float v[2];
+#pragma unroll
+      for (int i = 0; i < 2; i++) v[i] = half(lmax[i], lmax[i + 2], b2, mirror);
+      float r = half(v[0], v[1], b0, xor1);
+      r = max_raw(r, dpp_f32<kXor2>(r));
+      if (!b1) key[2 * b2 + b0] = r;
+    }
+  }
+  __syncthreads();
+  if (wave != 0) return;
+  m = (tid < NWV) ? L.m[set][tid] : -INFINITY;
+  S = (tid < NWV) ? L.s[set][tid] : 0.0;
+  const float M = wave_max(m);
+  if (!(M > -INFINITY)) {
+    if (tid == 0) mark_dead(c, row);
+    return;
+  }
+  const double T = wave_sum(S * exp_rel(max_raw(m, M - 600.f), -(double)M * ek.c, L.tab, ek));
+  const float lse = (float)((double)M + log(T));
+  const float bias = __fsub_rn(s_in, lse);
+  if (tid == 0) { c.row_bias[row] = bias; c.row_info[row] = ROW_DENSE; }
+  const float4 kl = *(const float4*)&L.key[set][4 * tid];
+  auto score = [&](float v) { return (v > -INFINITY) ? __fadd_rn(bias, v) : -INFINITY; };
+  const float k0 = score(kl.x), k1 = score(kl.y), k2 = score(kl.z), k3 = score(kl.w);
+  uint2 packed;
+  packed.x = key16_up(k0) | (key16_up(k1) << 16);
+  packed.y = key16_up(k2) | (key16_up(k3) << 16);
+  *(uint2*)(c.row_data + (size_t)row * kRowFloats + 2 * tid) = packed;
+  const float group = quad_max(max_raw(max_raw(k0, k1), max_raw(k2, k3)));
+  if ((tid & 3) == 0) c.row_group[(size_t)row * kGroups + (tid >> 2)] = group;
+}
+
+// ------------------------------------------------------------------------------------------------
+// Rows whose valid children are listed (Section 6.1's sparse form): only the valid logits are gathered, 512 at a time, by one
+// wavefront or by the four of a workgroup.  A row with at most kScoreMax children leaves every candidate's score, its groups
+// are of 16 children; one with more leaves one key per lane (children lane, lane + 64, ...), its groups are of four lanes.
+// ------------------------------------------------------------------------------------------------
+constexpr int kPartU = 8, kPart = 64 * kPartU;
+struct GatherPart {
+  float x[kPartU];           // the last kPart logits of this wavefront (all of a short row), -inf past the end
+  float best, m;             // best logit of this lane, of the wavefront
+  double S;                  // the wavefront's sum relative to m
+};
+__device__ __forceinline__ void gather_part(GatherPart& g, const float* x, const int32_t* list, int n, int first, int step, const double* tab,
+                                            const ExpK& ek) {
+  const int lane = threadIdx.x & 63;
+  int tok[kPartU];
+  double S = 0.0;
+  g.best = -INFINITY; g.m = -INFINITY;
+#pragma unroll
+  for (int k = 0; k < kPartU; k++)
+    if (first + 64 * k < n) tok[k] = list[min(first + lane + 64 * k, n - 1)];
+#pragma unroll 1
+  for (int base = first; base < n; base += step) {
+#pragma unroll
+    for (int k = 0; k < kPartU; k++)
+      if (base + 64 * k < n) g.x[k] = x[tok[k]];             // (uniform; the rest becomes -inf below)
+#pragma unroll
+    for (int k = 0; k < kPartU; k++)
+      if (base + step + 64 * k < n) tok[k] = list[min(base + step + lane + 64 * k, n - 1)];
+    float bmax = -INFINITY;
+#pragma unroll
+    for (int k = 0; k < kPartU; k++) {
+      if (base + 64 * k + lane >= n) g.x[k] = -INFINITY;
+      bmax = max_raw(bmax, g.x[k]);
+    }
+    g.best = max_raw(g.best, bmax);
+    const float mn = max_raw(g.m, wave_max(bmax)), lo = mn - 600.f;
+    const double rn = -(double)mn * ek.c;
+    if (base > first) S = S * exp_rel(max_raw(g.m, lo), rn, tab, ek);
+    g.m = mn;
+    if (mn > -INFINITY) {
+#pragma unroll
+      for (int k = 0; k < kPartU; k++)
+        if (base + 64 * k < n) S = exp_add(S, max_raw(g.x[k], lo), rn, tab, ek);     // (-inf adds less than 1e-260)
+    }
+  }
+  g.S = wave_sum(S);
+}
+// What a row leaves, from its (m, S), every lane's best logit, and the logits of a short row; one wavefront.
+__device__ __forceinline__ void gather_done(const SelCtx& c, const GatherPart& g, int row, float s_in, int start, int n) {
+  const int lane = threadIdx.x & 63;
+  if (!(g.m > -INFINITY)) {
+    if (lane == 0) mark_dead(c, row);
+    return;
+  }
+  const float lse = (float)((double)g.m + log(g.S));
+  const float bias = __fsub_rn(s_in, lse);
+  if (lane == 0) { c.row_bias[row] = bias; c.row_info[row] = ROW_SPARSE | (n << 2); c.row_start[row] = start; }
+  float* data = c.row_data + (size_t)row * kRowFloats;
+  float* group = c.row_group + (size_t)row * kGroups;
+  if (n <= kScoreMax) {
+#pragma unroll
+    for (int k = 0; k < (kScoreMax + 63) / 64; k++) {
+      if (64 * k < n) {
+        const float score = (g.x[k] > -INFINITY) ? __fadd_rn(bias, g.x[k]) : -INFINITY;
+        if (64 * k + lane < kScoreMax) data[64 * k + lane] = score;
+        float best = quad_max(score);                        // of 16 children
+        best = max_raw(best, dpp_f32<kHalfMirror>(best));
+        best = max_raw(best, dpp_f32<kMirror>(best));
+        if ((lane & 15) == 0) group[4 * k + (lane >> 4)] = best;
       }
     }
   } else {
-    // general shape: two passes over the row (the second one hits in cache); same chunk layout
-    const int epc = c.epc;
-    for (int e = 0; e < epc; e++) {
-      const int v = dense_slot_token(c, tid, e);
-      if (v < V && ((s_mask[v >> 5] >> (v & 31)) & 1u)) lmax = fmaxf(lmax, x[v]);
+    const float key = (g.best > -INFINITY) ? __fadd_rn(bias, g.best) : -INFINITY, best = quad_max(key);
+    data[lane] = key;
+    if ((lane & 3) == 0) group[lane >> 2] = best;
+  }
+}
+
+// Levels 1 and 2 with a mask.  Bound: cache lines drawn at random (32 x 256 beams, V = 8192, Zipf table, level 1: 165 MB of lines
+// in 46 us; what a row's children share no line with is wasted).  Lists up to 8192 children are gathered too: streaming the
+// long ones needs a second kind of workgroup, and whatever share was streamed (above 512, 1024 or 2048 children) the call
+// took as long.  Level 2, where nearly every row has one or two children, takes 9 us (19 us when every row also had a
+// workgroup for the case that it has to be streamed).
+//
+// A row per wavefront, then the workgroup's long rows by all of its wavefronts.
+constexpr int kGatherWaves = 4;
+__global__ void __launch_bounds__(kGatherWaves * 64, 8) k_rows_listed(SelCtx c) {
+  __shared__ double s_tab[kExpTab], s_S[2][kGatherWaves];
+  __shared__ float s_in4[kGatherWaves], s_m[2][kGatherWaves], s_best[2][kGatherWaves][64];
+  __shared__ int s_start[kGatherWaves], s_n[kGatherWaves];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), row0 = blockIdx.x * kGatherWaves;
+  const MaskView mv = mask_view(c.blob, c.V, c.depth);
+  float s_in = -INFINITY;
+  int start = 0, n = 0;
+  fill_exp_tab(s_tab, kGatherWaves * 64);
+  if (row0 + wave < c.B * c.W) {
+    s_in = c.scores_in[row0 + wave];
+    row_children(c, mv, row0 + wave, &start, &n);
+    if (!(s_in > -INFINITY) || n == 0) {
+      if (lane == 0) mark_dead(c, row0 + wave);
+      n = 0;
     }
-    m = block_max<NW>(lmax, s_redf, par);
-    if (m > -INFINITY) {
-      const double rc = -(double)m * ek.c;
-      const float lo = m - 600.f;
-      for (int e = 0; e < epc; e++) {
-        const int v = dense_slot_token(c, tid, e);
-        if (v < V && ((s_mask[v >> 5] >> (v & 31)) & 1u)) S += exp_rel(fmaxf(x[v], lo), rc, s_tab, ek);
+  }
+  if (lane == 0) { s_n[wave] = n; s_in4[wave] = s_in; s_start[wave] = start; }
+  __syncthreads();
+  const ExpK ek = exp_consts();
+  const int32_t* list = child_list(c, mv);
+  int set = 0;
+#pragma unroll 1
+  for (int j = -1; j < kGatherWaves; j++) {        // -1: this wavefront's own row
+    const bool own = j < 0;
+    const int w = own ? wave : j, nw = __builtin_amdgcn_readfirstlane(s_n[w]), sw = __builtin_amdgcn_readfirstlane(s_start[w]);
+    if (own ? (nw == 0 || nw > kWaveMax) : nw <= kWaveMax) continue;
+    GatherPart g;
+    gather_part(g, c.logits + (size_t)(row0 + w) * c.V, list + sw, nw, own ? 0 : wave * kPart, own ? kPart : kGatherWaves * kPart, s_tab, ek);
+    if (!own) {
+      if (lane == 0) { s_m[set][wave] = g.m; s_S[set][wave] = g.S; }
+      s_best[set][wave][lane] = g.best;
+      __syncthreads();
+      const int at = set;
+      set ^= 1;
+      if (wave != 0) continue;
+      // (lane w joins wavefront w's pair; the sums meet in all lanes)
+      const float mw = lane < kGatherWaves ? s_m[at][lane] : -INFINITY;
+      g.m = wave_max(mw);
+      if (g.m > -INFINITY)
+        g.S = wave_sum((lane < kGatherWaves ? s_S[at][lane] : 0.0) * exp_rel(max_raw(mw, g.m - 600.f), -(double)g.m * ek.c, s_tab, ek));
+      g.best = s_best[at][0][lane];
+#pragma unroll
+      for (int v = 1; v < kGatherWaves; v++) g.best = max_raw(g.best, s_best[at][v][lane]);
+    }
+    gather_done(c, g, row0 + w, s_in4[w], sw, nw);
+  }
+}
+
+// Rows that are streamed, dealt to workgroups
+//   one each: for calls whose rows are all streamed and, as a rule, all live;
+//   every gridDim-th (STRIDE): for level 0, where as a rule one row of a request is live: a workgroup asks for the scores of all
+//   its rows at once and turns to the live ones (8192 workgroups that only find a dead row cost 16 us to dispatch).  With so few
+//   rows at work a row is dealt to twice as many threads.
+constexpr size_t kStrideGrid = 1021;    // about four workgroups per CU; prime, so that equally spaced live rows fall to different ones
+template <bool STRIDE, int NT>
+__global__ void __launch_bounds__(NT, STRIDE ? 4 : 6) k_rows(SelCtx c) {
+  __shared__ RowLds<NT> L;
+  const int tid = threadIdx.x, lane = tid & 63, rows = c.B * c.W;
+  MaskView mv;
+  mv.ok = false;
+  if (!STRIDE) {
+    const int row = blockIdx.x;
+    const float s_in = c.scores_in[row];
+    const int t1 = (c.blob && c.step == 1) ? c.prefix_in[(size_t)row * c.depth] : -1;
+    if (c.blob) mv = mask_view(c.blob, c.V, c.depth);
+    if (!(s_in > -INFINITY)) {
+      if (tid == 0) mark_dead(c, row);
+      return;
+    }
+    fill_exp_tab(L.tab, NT);
+    int start = 0, n = 0;
+    if (c.blob && c.step == 2) row_children(c, mv, row, &start, &n);
+    __syncthreads();
+    row_dense(c, mv, L, row, s_in, t1, start, n, 0);
+  } else {
+    fill_exp_tab(L.tab, NT);
+    if (c.blob) mv = mask_view(c.blob, c.V, c.depth);
+    __syncthreads();
+    int set = 0;
+    for (int64_t base = blockIdx.x; base < rows; base += (int64_t)gridDim.x * 64) {
+      const int64_t r = base + (int64_t)lane * gridDim.x;
+      const float s = r < rows ? c.scores_in[r] : -INFINITY;
+      if (tid < 64 && r < rows && !(s > -INFINITY)) mark_dead(c, (int)r);
+      for (uint64_t live = __ballot(s > -INFINITY); live; live &= live - 1) {
+        const int l = __ffsll((unsigned long long)live) - 1;
+        row_dense(c, mv, L, (int)(base + (int64_t)l * gridDim.x), lane_f32(s, l), -1, 0, 0, set);
+        set ^= 1;
       }
     }
   }
-  if (!(m > -INFINITY)) {
-    if (tid == 0) { c.row_mode[row] = ROW_DEAD; c.row_bias[row] = -INFINITY; c.row_top[row] = -INFINITY; }
-    return;
-  }
-  S = block_sum<NW>(S, s_redd, par);
-  const float lse = (float)((double)m + log(S));
-  const float bias = __fsub_rn(s_in, lse);
-  if (tid == 0) {
-    c.row_bias[row] = bias;
-    c.row_mode[row] = ROW_DENSE;
-    c.row_top[row] = __fadd_rn(bias, m);
-  }
-  c.chunk_key[(size_t)row * kChunksPerRow + tid] = (lmax > -INFINITY) ? __fadd_rn(bias, lmax) : -INFINITY;
-}
-
-// ------------------------------------------------------------------------------------------------
-// Rows with few valid children: one wavefront each, gather only the valid logits (Section 6.1's
-// sparse form).  Chunk k of such a row = children k, k+64, k+128, ...
-// ------------------------------------------------------------------------------------------------
-__device__ __forceinline__ void rows_sparse(const SelCtx& c, int group) {
-  __shared__ double s_tab[64];
-  if (threadIdx.x < 64) s_tab[threadIdx.x] = c_exp_tab[threadIdx.x];
-  const ExpK ek = exp_consts();
-  __syncthreads();
-  const int row = group * (kRowThreads / 64) + (threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  if (row >= c.B * c.W) return;
-  float* keys = c.chunk_key + (size_t)row * kChunksPerRow;
-  const float s_in = c.scores_in[row];
-  const MaskView mv = mask_view(c.blob, c.V, c.depth);
-  const int32_t* list = nullptr;
-  int n = 0;
-  const bool live = s_in > -INFINITY;
-  if (live) {
-    row_children(c, mv, row, &list, &n);
-    if (!row_is_sparse(c, n)) return;          // a streamed row: row_dense owns it
-  }
-  if (!live || n == 0) {
-    if (lane == 0) { c.row_mode[row] = ROW_DEAD; c.row_bias[row] = -INFINITY; c.row_top[row] = -INFINITY; }
-    return;
-  }
-  const float* x = c.logits + (size_t)row * c.V;
-  float xv[kSparseMax / 64];
-  float lmax = -INFINITY;
-#pragma unroll
-  for (int k = 0; k < kSparseMax / 64; k++) {
-    const int i = lane + 64 * k;
-    xv[k] = (i < n) ? x[list[i]] : -INFINITY;
-    lmax = fmaxf(lmax, xv[k]);
-  }
-  const float m = gr_wave_max(lmax);
-  double S = 0.0;
-  const double rc = -(double)m * ek.c;
-  const float lo = m - 600.f;
-#pragma unroll
-  for (int k = 0; k < kSparseMax / 64; k++)
-    if (lane + 64 * k < n) S += exp_rel(fmaxf(xv[k], lo), rc, s_tab, ek);
-  S = gr_wave_sum(S);
-  const float lse = (float)((double)m + log(S));
-  const float bias = __fsub_rn(s_in, lse);
-  if (lane == 0) { c.row_bias[row] = bias; c.row_mode[row] = ROW_SPARSE; c.row_top[row] = __fadd_rn(bias, m); }
-  keys[lane] = (lmax > -INFINITY) ? __fadd_rn(bias, lmax) : -INFINITY;     // a sparse row has kSparseKeys keys
-}
-
-// One launch for both kinds of row: the first n_dense_blocks workgroups stream one row each (those come
-// first because they run longest), the rest gather four sparse rows each.  Every row is looked at by
-// both kinds; the shared test row_is_sparse decides which of them owns it.
-__global__ void __launch_bounds__(kRowThreads) k_rows(SelCtx c, int owns_dead, int n_dense_blocks) {
-  if ((int)blockIdx.x < n_dense_blocks) row_dense(c, owns_dead, (int)blockIdx.x);
-  else rows_sparse(c, (int)blockIdx.x - n_dense_blocks);
 }
 
 // ------------------------------------------------------------------------------------------------
 // Per-request selection.
 // ------------------------------------------------------------------------------------------------
-// Visit every finite candidate of request b.  f(score, flat, pred) is called wave-convergently
+// A candidate's place in its row: the token in a streamed row, the position in the child list in a gathered one (the list is
+// sorted, so both order the candidates of a row as its tokens do).
+//
+// Visit every finite candidate of request b.  f(score, w * V + place, pred) is called wave-convergently
 // (pred = this lane holds a candidate).  Rows given by bit masks are strided by the whole
 // workgroup; rows given by child lists are taken one per wavefront.
 template <class F>
@@ -505,7 +672,7 @@ __device__ __forceinline__ void for_each_candidate(const SelCtx& c, const MaskVi
   if (!c.blob || c.step == 0) {
     for (int w = 0; w < c.W; w++) {
       const int row = b * c.W + w;
-      if (c.row_mode[row] == ROW_DEAD) continue;
+      if (c.row_info[row] == ROW_DEAD) continue;
       const float bias = c.row_bias[row];
       const float* x = c.logits + (size_t)row * c.V;
       const uint32_t flat0 = (uint32_t)w * (uint32_t)c.V;
@@ -518,18 +685,19 @@ __device__ __forceinline__ void for_each_candidate(const SelCtx& c, const MaskVi
   } else {
     for (int w = wave; w < c.W; w += nw) {
       const int row = b * c.W + w;
-      if (c.row_mode[row] == ROW_DEAD) continue;
+      if (c.row_info[row] == ROW_DEAD) continue;
+      const bool gathered = (c.row_info[row] & 3) == ROW_SPARSE;
       const float bias = c.row_bias[row];
       const float* x = c.logits + (size_t)row * c.V;
       const uint32_t flat0 = (uint32_t)w * (uint32_t)c.V;
-      const int32_t* list;
-      int n;
-      row_children(c, mv, row, &list, &n);
+      int start, n;
+      row_children(c, mv, row, &start, &n);
+      const int32_t* list = child_list(c, mv) + start;
       for (int i0 = 0; i0 < n; i0 += 64) {
         const int i = i0 + lane;
         const bool pred = i < n;
         const int v = pred ? list[i] : 0;
-        f(pred ? __fadd_rn(bias, x[v]) : 0.f, flat0 + v, pred);
+        f(pred ? __fadd_rn(bias, x[v]) : 0.f, flat0 + (gathered ? i : v), pred);
       }
     }
   }
@@ -539,9 +707,13 @@ __device__ __forceinline__ uint64_t composite(float score, uint32_t flat) {
   return ((uint64_t)gr_ordkey(score + 0.0f) << 32) | (uint64_t)(0xffffffffu - flat);     // (+0.0f: -0 and +0 are one score)
 }
 
-// Monotone (non-increasing in the score) bin index below the request's best chunk key.
-__device__ __forceinline__ int key_bin(float hi, float score) {
-  return (int)fminf(fmaxf((hi - score) * 64.0f, 0.f), (float)(kHistBins - 1));
+// Monotone (non-increasing in the score) histogram bin below `hi`.
+__device__ __forceinline__ int key_bin(float hi, float scale, float score) {
+  return (int)fminf(fmaxf((hi - score) * scale, 0.f), (float)(kHistBins - 1));
+}
+// Bins per unit of score for a histogram that has to cover `range`.
+__device__ __forceinline__ float bin_scale(float range) {
+  return (range > 0.f && range < INFINITY) ? fminf((float)(kHistBins - 1) / range, 1e30f) : 0.f;
 }
 
 // Exact MSB radix select of the W best composite keys over ALL candidates (slow, always correct).
@@ -628,13 +800,13 @@ __device__ int radix_select_all(const SelCtx& c, const MaskView& mv, int b, uint
 // Smallest bin t with at least `want` entries in bins 0..t (bin 0 = best scores); the last bin when there are fewer
 // than `want` entries in total.  Done by the whole workgroup (every thread owns kHistBins / kSelThreads consecutive
 // bins; one scan, one barrier inside): a serial walk by one wavefront over 32 bins per lane costs more than a
-// microsecond.  The caller puts a barrier behind it before reading *s_thr.
-__device__ __forceinline__ void hist_threshold_all(const uint32_t* s_hist, uint32_t want, int* s_thr, uint32_t* s_redu, int& par) {
+// microsecond.  Leaves the histogram cleared.  The caller puts a barrier behind it before reading *s_thr.
+__device__ __forceinline__ void hist_threshold_all(uint32_t* s_hist, uint32_t want, int* s_thr, uint32_t* s_redu, int& par) {
   constexpr int per = kHistBins / kSelThreads;
   const int tid = threadIdx.x;
   uint32_t h[per], local = 0;
 #pragma unroll
-  for (int k = 0; k < per; k++) { h[k] = s_hist[tid * per + k]; local += h[k]; }
+  for (int k = 0; k < per; k++) { h[k] = s_hist[tid * per + k]; local += h[k]; s_hist[tid * per + k] = 0; }
   uint32_t total;
   const uint32_t below = block_excl_scan<kSelThreads / 64>(local, &total, s_redu, par);
   if (total < want) {
@@ -652,308 +824,407 @@ __device__ __forceinline__ void hist_threshold_all(const uint32_t* s_hist, uint3
   }
 }
 
+// Bound: latency - a chain of some six memory round trips and a dozen barriers in one workgroup per request - and, with cold
+// caches, the 40 GB/s at which one CU draws lines.  32 requests x 256 beams, V = 8192: 15 / 24 / 13 us at levels 0 / 1 / 2 and 16 us
+// without a mask (25 / 34 / 27 and 28 us when all 64 K chunk keys of a request were read and re-read chunks lay across eight lines);
+// one request x 16 beams 8 us (12 us).  Code size is part of it: unrolled over registers this kernel was 81 KB and took up
+// to twice as long, because each instruction line is fetched once per launch and used once; hence the rolled loops.
 __global__ void __launch_bounds__(kSelThreads) k_select(SelCtx c) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   uint64_t* s_list = (uint64_t*)smem;
-  uint32_t* s_hist = (uint32_t*)(smem + (size_t)kListCap * 8);
-  uint32_t* s_chunks = s_hist + kHistBins;
-  float* s_rbias = (float*)(s_chunks + kChunkCap);          // per beam row of the request: bias,
-  int32_t* s_rmode = (int32_t*)(s_rbias + kMaxW);            // mode,
-  int32_t* s_ra = s_rmode + kMaxW;                           // first token (step 1) or table range start (step 2),
-  int32_t* s_rb = s_ra + kMaxW;                              // start of the child list (step 1) or table range end (step 2),
-  int32_t* s_rc = s_rb + kMaxW;                              // end of the child list (step 1)
-  __shared__ float s_redf[kSelThreads / 64];
-  __shared__ uint32_t s_redu[2 * (kSelThreads / 64)];
-  __shared__ uint16_t s_live[kMaxW];
-  int par = 0;
-  __shared__ uint32_t s_n, s_nc, s_nlive;
-  __shared__ int s_thr;
-  const int b = blockIdx.x, tid = threadIdx.x;
+  float* s_group = (float*)smem;                             // (before the list) best score of every group, or of every unit
+  uint32_t* s_units = (uint32_t*)(s_list + kListCap);        // units that hold a candidate above the threshold: place in s_chunks << 8 | unit of the key
+  uint64_t* s_tmp = (uint64_t*)s_units;                      // (after them) the survivors by bin
+  constexpr int kTmpCap = kUnitCap / 2;
+  uint32_t* s_hist = s_units + kUnitCap;
+  uint32_t* s_chunks = s_hist + kHistBins;                   // row << 8 | key above the threshold, from the front; row << 8 | four scores, from the back
+  float* s_rbias = (float*)(s_chunks + kChunkCap);           // per beam row of the request: bias,
+  int32_t* s_rinfo = (int32_t*)(s_rbias + kMaxW);            // mode and child count,
+  int32_t* s_ra = s_rinfo + kMaxW;                           // first child (gathered), first token (streamed, level 1) or table range start
   constexpr int NW = kSelThreads / 64;
+  __shared__ float2 s_redf[2 * NW];
+  __shared__ uint32_t s_redu[2 * NW];
+  __shared__ uint32_t s_n, s_nd, s_ns, s_nu, s_most;
+  __shared__ int s_thr;
+  int parf = 0, paru = 0;
+  const int b = blockIdx.x, tid = threadIdx.x;
   MaskView mv;
   if (c.blob) mv = mask_view(c.blob, c.V, c.depth);
 
-  if (tid == 0) { s_n = 0; s_nc = 0; s_nlive = 0; }
-  for (int i = tid; i < kHistBins; i += kSelThreads) s_hist[i] = 0;
-  __syncthreads();
-  // ---- the request's rows: what the rows kernels left, the live ones listed, the best candidate overall
-  float hi = -INFINITY;
+  // ---- the groups' best scores that k_rows left (two by two for more than 1024 beams)
+  const float* data = c.row_data + (size_t)b * c.W * kRowFloats;
+  const float4* group4 = (const float4*)(c.row_group + (size_t)b * c.W * kGroups);
+  const int32_t* info_b = c.row_info + (size_t)b * c.W;
+  const int gsh = c.W * kGroups <= kGroupCap ? 4 : 3;        // log2 of the groups per row
+  const int ngroups = c.W << gsh;
+  float hi = -INFINITY, lo = INFINITY;                       // best and worst group
+#pragma unroll 2
+  for (int q = tid; q < c.W * (kGroups / 4); q += kSelThreads) {
+    const int w = q / (kGroups / 4), first = 4 * (q % (kGroups / 4)), info = info_b[w];
+    float4 g = group4[q];
+    const int ng = (info & 3) == ROW_DENSE ? kGroups : (info & 3) == ROW_SPARSE ? ((info >> 2) <= kScoreMax ? ((info >> 2) + 15) >> 4 : kGroups) : 0;
+    if (first >= ng) g.x = -INFINITY;
+    if (first + 1 >= ng) g.y = -INFINITY;
+    if (first + 2 >= ng) g.z = -INFINITY;
+    if (first + 3 >= ng) g.w = -INFINITY;
+    if (gsh == 4) *(float4*)&s_group[4 * q] = g;
+    else *(float2*)&s_group[2 * q] = make_float2(fmaxf(g.x, g.y), fmaxf(g.z, g.w));
+    hi = fmaxf(hi, fmaxf(fmaxf(g.x, g.y), fmaxf(g.z, g.w)));
+    auto low = [&](float v) { lo = fminf(lo, v > -INFINITY ? v : INFINITY); };
+    low(g.x); low(g.y); low(g.z); low(g.w);
+  }
+  // ---- the request's rows
+#pragma unroll 1
   for (int w = tid; w < c.W; w += kSelThreads) {
     const size_t row = (size_t)b * c.W + w;
-    // (everything a row can need is asked for at once; what a dead row returns is ignored)
-    const int mode = c.row_mode[row];
-    const float bias = c.row_bias[row], top = c.row_top[row];
-    int a = 0, bb = 0, cc = 0;
-    if (c.blob && c.step == 1) {
-      a = c.prefix_in[row * c.depth];
-    } else if (c.blob && c.step == 2) {
-      a = c.range_in[2 * row]; bb = c.range_in[2 * row + 1];
-    }
-    s_rmode[w] = mode;
-    s_rbias[w] = bias;
-    if (mode != ROW_DEAD) {
-      hi = fmaxf(hi, top);
-      s_live[atomicAdd(&s_nlive, 1u)] = (uint16_t)w;
-      if (c.blob && c.step == 1) {
-        // the row's child list, looked up once here for the re-read of gathered chunks and for the output
-        const bool ok = mv.ok && a >= 0 && a < c.V;
-        bb = ok ? mv.pair_off[a] : 0;
-        cc = ok ? mv.pair_off[a + 1] : 0;
-      } else if (c.blob && c.step == 2) {
-        if (!mv.ok || a < 0 || bb < a || (int64_t)bb > mv.n_items) { a = 0; bb = 0; }
-      }
-    } else {
-      a = 0; bb = 0;
-    }
-    s_ra[w] = a;
-    s_rb[w] = bb;
-    s_rc[w] = cc;
+    const int info = c.row_info[row], start = c.row_start[row];
+    int a = 0;
+    if (c.blob && c.step == 1) a = c.prefix_in[row * c.depth];
+    else if (c.blob && c.step == 2) a = c.range_in[2 * row];
+    s_rbias[w] = c.row_bias[row];
+    s_rinfo[w] = info;
+    s_ra[w] = (info & 3) == ROW_SPARSE ? start : a;
   }
-  hi = block_max2<NW>(hi, s_redf);         // (has the barriers that publish the row table)
-  const int nlive = (int)s_nlive;
+  if (tid == 0) { s_n = 0; s_nd = 0; s_ns = 0; s_nu = 0; s_most = 0; }
+  for (int i = tid; i < kHistBins; i += kSelThreads) s_hist[i] = 0;
+  block_max_min<NW>(hi, lo, s_redf, parf);                   // (its barrier publishes the row table and the groups)
 
-  // ---- threshold from the chunk keys of the live rows (the best candidate score of every 1/256th of a
-  // streamed row, every 1/64th of a gathered one).  Keys are read once and kept in registers for the
-  // second use when they fit (up to 256 live rows).
-  const float4* keys4 = (const float4*)(c.chunk_key + (size_t)b * c.W * kChunksPerRow);
-  constexpr int KR = 16;                   // float4 of keys per thread held in registers
-  const int ngroups = nlive * (kChunksPerRow / 4);
-  auto group_of = [&](int idx, int* w, int* g) {           // key group idx -> (row, group in row); false if it holds no keys
-    *w = s_live[idx / (kChunksPerRow / 4)];
-    *g = idx % (kChunksPerRow / 4);
-    return s_rmode[*w] == ROW_DENSE || *g < kSparseKeys / 4;
-  };
   int n = 0;
-  bool need_fallback = false;
   if (hi > -INFINITY) {
-    float4 kq[KR];
-#pragma unroll
-    for (int i = 0; i < KR; i++) {
-      const int idx = tid + i * kSelThreads;
-      int w, g;
-      kq[i] = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
-      if (idx < ngroups && group_of(idx, &w, &g)) kq[i] = keys4[(size_t)w * (kChunksPerRow / 4) + g];
-    }
-    auto bin4 = [&](const float4& k, auto&& f) {
-      if (k.x > -INFINITY) f(0, key_bin(hi, k.x));
-      if (k.y > -INFINITY) f(1, key_bin(hi, k.y));
-      if (k.z > -INFINITY) f(2, key_bin(hi, k.z));
-      if (k.w > -INFINITY) f(3, key_bin(hi, k.w));
+    // ---- threshold that at least W groups reach (no threshold when there are fewer): at least 64 bins per unit of score, more
+    // when the groups lie close together
+    const float scale = fmaxf(64.f, bin_scale(hi - lo));
+#pragma unroll 1
+    for (int i = tid; i < ngroups; i += kSelThreads)
+      if (s_group[i] > -INFINITY) atomicAdd(&s_hist[key_bin(hi, scale, s_group[i])], 1u);
+    __syncthreads();
+    hist_threshold_all(s_hist, (uint32_t)c.W, &s_thr, s_redu, paru);
+    __syncthreads();
+    // (a little low: rounding may only let more through)
+    auto threshold = [&](float per_score) {
+      return s_thr < kHistBins - 1 ? hi - ((float)s_thr + 1.01f) / per_score - 1e-6f * fabsf(hi) : -INFINITY;
     };
-    uint32_t kb[KR][2];                    // bins of the register-resident keys, 16 bits each (0xffff: no key)
-#pragma unroll
-    for (int i = 0; i < KR; i++) {
-      kb[i][0] = 0xffffffffu; kb[i][1] = 0xffffffffu;
-      bin4(kq[i], [&](int j, int bin) {
-        atomicAdd(&s_hist[bin], 1u);
-        kb[i][j >> 1] = (j & 1) ? ((kb[i][j >> 1] & 0x0000ffffu) | ((uint32_t)bin << 16)) : ((kb[i][j >> 1] & 0xffff0000u) | (uint32_t)bin);
-      });
-    }
-    for (int idx = tid + KR * kSelThreads; idx < ngroups; idx += kSelThreads) {
-      int w, g;
-      if (group_of(idx, &w, &g)) bin4(keys4[(size_t)w * (kChunksPerRow / 4) + g], [&](int, int bin) { atomicAdd(&s_hist[bin], 1u); });
+    float T = threshold(scale);
+    // ---- groups that reach it, then the finer keys behind them that do (four threads to a group, one round of loads for all)
+#pragma unroll 1
+    for (int i = tid; i < ngroups; i += kSelThreads) {
+      if (!(s_group[i] > -INFINITY) || s_group[i] < T) continue;
+      const uint32_t pos = atomicAdd(&s_n, 1u);
+      if (pos < (uint32_t)kUnitCap) s_units[pos] = (uint32_t)i;
     }
     __syncthreads();
-    hist_threshold_all(s_hist, (uint32_t)c.W, &s_thr, s_redu, par);
-    __syncthreads();
-    const int thr = s_thr;
-    // ---- chunks that reach the threshold
-    auto take = [&](int idx, const float4& k) {
-      int w, g;
-      group_of(idx, &w, &g);
-      bin4(k, [&](int j, int bin) {
-        if (bin <= thr) {
-          const uint32_t pos = atomicAdd(&s_nc, 1u);
-          if (pos < (uint32_t)kChunkCap) s_chunks[pos] = ((uint32_t)w << 8) | (uint32_t)(4 * g + j);
+    const int ng = (int)s_n, ssh = 6 - gsh;                  // log2 of the threads to a listed group
+    bool fallback = ng > kUnitCap;
+    const uint32_t T16 = max(key16_down(T), key16_up(-INFINITY));
+#pragma unroll 1
+    for (int i = tid; i < min(ng, kUnitCap) << ssh; i += kSelThreads) {
+      const int at = ((int)s_units[i >> ssh] << ssh) + (i & ((1 << ssh) - 1));      // quarter group: row << 6 | quarter of the row's 16 groups
+      const int w = at >> 6, q = at & 63, info = s_rinfo[w], cnt = info >> 2;
+      const float* fine = data + (size_t)w * kRowFloats;
+      auto add = [&](bool front, int key) {
+        const uint32_t pos = atomicAdd(front ? &s_nd : &s_ns, 1u);
+        if (pos < (uint32_t)kChunkCap) s_chunks[front ? pos : kChunkCap - 1 - pos] = ((uint32_t)w << 8) | (uint32_t)key;
+      };
+      if ((info & 3) == ROW_DENSE) {
+        const uint2 k = *(const uint2*)(fine + 2 * q);
+        if ((k.x & 0xffffu) >= T16) add(true, 4 * q);
+        if ((k.x >> 16) >= T16) add(true, 4 * q + 1);
+        if ((k.y & 0xffffu) >= T16) add(true, 4 * q + 2);
+        if ((k.y >> 16) >= T16) add(true, 4 * q + 3);
+      } else if (cnt <= kScoreMax) {
+        // (the scores of a row's last wavefront of children are -inf past its end; past that they are not written)
+        if (4 * q < cnt) {
+          const float4 k = *(const float4*)(fine + 4 * q);
+          if (fmaxf(fmaxf(k.x, k.y), fmaxf(k.z, k.w)) >= T) add(false, q);
         }
-      });
+      } else {
+        const float k = fine[q];
+        if (k > -INFINITY && k >= T) { add(true, q); atomicMax(&s_most, (uint32_t)cnt); }
+      }
+    }
+    __syncthreads();
+    if (tid == 0) s_n = 0;
+    const int nd = (int)s_nd, ns = (int)s_ns;
+    fallback = fallback || nd + ns > kChunkCap;
+    // units of four candidates behind a key in front: float4 of logits, or children 64 apart
+    const bool listed = s_most > 0;
+    int sh = c.unit_shift;
+    if (listed) { sh = 0; while ((kUnitSpan << sh) < (int)s_most) sh++; }
+    const int front_units = nd << sh;
+    const int lsh = c.row_threads == 512 ? 2 : 3;            // log2 of a thread's loads per block of a streamed row
+    auto unit_token = [&](int k, int e) {                    // first token of unit e of line k
+      return 32 * (k >> lsh) + 4 * c.row_threads * (k & ((1 << lsh) - 1)) + 4 * (e & 7) + kBlockV * (e >> 3);
     };
+    if (!fallback) {
+      // ---- units behind them that hold a candidate above the threshold (as far as the logits tell: validity comes next).  Four
+      // scores are a unit as they are.
+      auto entry = [&](int u, int* w, int* k, int* e) {
+        const uint32_t ent = s_chunks[u >> sh];
+        *w = (int)(ent >> 8); *k = (int)(ent & 255u); *e = u & ((1 << sh) - 1);
+      };
+      auto keep = [&](int u) {
+        const uint32_t pos = atomicAdd(&s_nu, 1u);
+        if (pos < (uint32_t)kUnitCap) s_units[pos] = ((uint32_t)(u >> sh) << 8) | (uint32_t)(u & ((1 << sh) - 1));
+      };
+      auto needed = [&](int w) {                             // logit that a candidate of row w needs
+        const float bias = s_rbias[w];
+        return T - bias - 1e-6f * (fabsf(T) + fabsf(bias));
+      };
+      // fewer groups than W, as at level 0 where all candidates are one row's: the units themselves yield a threshold
+      const bool by_unit = !listed && !(T > -INFINITY) && ns == 0 && front_units <= kGroupCap && !(c.blob && c.step == 2);
+      if (by_unit) {
+        constexpr int U = 2;
+#pragma unroll 1
+        for (int base = tid; base < front_units; base += U * kSelThreads) {
+          float best[U];
 #pragma unroll
-    for (int i = 0; i < KR; i++) {
-      const uint32_t b4[4] = {kb[i][0] & 0xffffu, kb[i][0] >> 16, kb[i][1] & 0xffffu, kb[i][1] >> 16};
-      const uint32_t thr_u = (uint32_t)thr;
-      if (b4[0] <= thr_u || b4[1] <= thr_u || b4[2] <= thr_u || b4[3] <= thr_u) {      // (0xffff never passes)
-        int w, g;
-        group_of(tid + i * kSelThreads, &w, &g);
-#pragma unroll
-        for (int j = 0; j < 4; j++)
-          if (b4[j] <= thr_u) {
-            const uint32_t pos = atomicAdd(&s_nc, 1u);
-            if (pos < (uint32_t)kChunkCap) s_chunks[pos] = ((uint32_t)w << 8) | (uint32_t)(4 * g + j);
+          for (int q = 0; q < U; q++) {
+            const int u = base + q * kSelThreads;
+            best[q] = -INFINITY;
+            if (u >= front_units) continue;
+            int w, k, e;
+            entry(u, &w, &k, &e);
+            const int v = unit_token(k, e);
+            if (v >= c.V) continue;
+            const float* x = c.logits + ((size_t)b * c.W + w) * c.V;
+            uint32_t bits = 0xfu;
+            if (c.blob) bits = (c.step == 0 ? mv.l0 : mv.l1 + (size_t)s_ra[w] * mv.words)[v >> 5] >> (v & 31);
+            f32x4u y;
+            if (v + 3 < c.V) y = *(const f32x4u*)(x + v);
+            else { y.x = x[v]; y.y = x[min(v + 1, c.V - 1)]; y.z = x[min(v + 2, c.V - 1)]; y.w = y.z; }
+            // (past the row's end a mask has no bits; without one the last token is taken again, which changes nothing here)
+            best[q] = fmaxf(fmaxf(bits & 1u ? y.x : -INFINITY, bits & 2u ? y.y : -INFINITY), fmaxf(bits & 4u ? y.z : -INFINITY, bits & 8u ? y.w : -INFINITY));
+            best[q] = __fadd_rn(s_rbias[w], best[q]);
           }
-      }
-    }
-    for (int idx = tid + KR * kSelThreads; idx < ngroups; idx += kSelThreads) {
-      int w, g;
-      if (group_of(idx, &w, &g)) take(idx, keys4[(size_t)w * (kChunksPerRow / 4) + g]);
-    }
-    __syncthreads();
-    const int nc = (int)s_nc;
-    if (nc > kChunkCap) {
-      need_fallback = true;
-    } else {
-      // ---- re-read only those chunks; keep their candidates that reach the threshold.  Twelve (chunk, element)
-      // slots per thread and round, all of their loads issued before any is used: the usual W-odd chunks of 32
-      // elements fit in one round.  bits: 0 = not a candidate, 1 = valid, 2 = valid if in the row's child list.
-      const int epc = max(c.epc, kSparseMax / kSparseKeys);
-      const int total = nc * epc;
-      constexpr int U = 12;
-      for (int base = 0; base < total; base += U * kSelThreads) {
-        int wv[U], tok[U];
-        float x[U];
-        uint32_t bits[U];
 #pragma unroll
-        for (int q = 0; q < U; q++) {
-          const int idx = base + q * kSelThreads + tid;
-          tok[q] = -1; x[q] = 0.f; bits[q] = 0; wv[q] = 0;
-          if (idx < total) {
-            const uint32_t ent = s_chunks[idx / epc];
-            const int e = idx % epc;
-            const int w = (int)(ent >> 8), k = (int)(ent & 255u);
-            wv[q] = w;
-            const float* xrow = c.logits + ((size_t)b * c.W + w) * c.V;
-            if (s_rmode[w] == ROW_DENSE) {
-              const int t = (e < c.epc) ? dense_slot_token(c, k, e) : c.V;
-              if (t < c.V) {
-                tok[q] = t;
-                x[q] = xrow[t];
-                if (!c.blob) bits[q] = 1u;
-                else if (c.step == 0) bits[q] = (mv.l0[t >> 5] >> (t & 31)) & 1u;
-                else if (c.step == 1) {
-                  const int t1 = s_ra[w];
-                  bits[q] = (t1 >= 0 && t1 < c.V) ? ((mv.l1[(size_t)t1 * mv.words + (t >> 5)] >> (t & 31)) & 1u) : 0u;
-                } else bits[q] = 2u;
-              }
-            } else {
-              // gathered row: chunk k = children k, k + 64, ...
-              const int32_t* list;
-              int nlist;
-              if (c.step == 1) { list = mv.pair_t2 + s_rb[w]; nlist = s_rc[w] - s_rb[w]; }
-              else { list = mv.t3 + s_ra[w]; nlist = s_rb[w] - s_ra[w]; }
-              const int i = k + kSparseKeys * e;
-              if (k < kSparseKeys && e < kSparseMax / kSparseKeys && i < nlist) {
-                const int t = list[i];
-                tok[q] = t;
-                x[q] = xrow[t];
-                bits[q] = 1u;
-              }
-            }
-          }
-        }
-#pragma unroll
-        for (int q = 0; q < U; q++) {
-          if (tok[q] < 0 || bits[q] == 0) continue;
-          if (bits[q] == 2u) {              // last level, streamed row: membership in the row's short child list
-            const int lo = s_ra[wv[q]], nl = s_rb[wv[q]] - lo;
-            const int pos = lower_bound_i32(mv.t3 + lo, nl, tok[q]);
-            if (!(pos < nl && mv.t3[lo + pos] == tok[q])) continue;
-          }
-          const float score = __fadd_rn(s_rbias[wv[q]], x[q]);
-          if (key_bin(hi, score) <= thr) {
-            const uint32_t pos = atomicAdd(&s_n, 1u);
-            if (pos < (uint32_t)kListCap) s_list[pos] = composite(score, (uint32_t)wv[q] * (uint32_t)c.V + (uint32_t)tok[q]);
-          }
-        }
-      }
-      __syncthreads();
-      if (s_n > (uint32_t)kListCap) need_fallback = true;
-      n = min((int)s_n, kListCap);
-    }
-    if (need_fallback) n = radix_select_all(c, mv, b, s_list, s_hist);
-
-    // ---- many survivors (few chunks, or a coarse first threshold): refine on the scores themselves
-    if (n > 2 * c.W) {
-      uint64_t mine[kListCap / kSelThreads];
-      float top = -INFINITY;
-#pragma unroll
-      for (int k = 0; k < kListCap / kSelThreads; k++) {
-        const int i = tid + k * kSelThreads;
-        mine[k] = (i < n) ? s_list[i] : 0;
-        if (i < n) top = fmaxf(top, gr_ordkey_inv((uint32_t)(mine[k] >> 32)));
-      }
-      top = block_max2<NW>(top, s_redf);
-      for (int i = tid; i < kHistBins; i += kSelThreads) s_hist[i] = 0;
-      if (tid == 0) s_n = 0;
-      __syncthreads();
-#pragma unroll
-      for (int k = 0; k < kListCap / kSelThreads; k++)
-        if (tid + k * kSelThreads < n) atomicAdd(&s_hist[key_bin(top, gr_ordkey_inv((uint32_t)(mine[k] >> 32)))], 1u);
-      __syncthreads();
-      hist_threshold_all(s_hist, (uint32_t)c.W, &s_thr, s_redu, par);
-      __syncthreads();
-      const int thr2 = s_thr;
-#pragma unroll
-      for (int k = 0; k < kListCap / kSelThreads; k++)
-        if (tid + k * kSelThreads < n && key_bin(top, gr_ordkey_inv((uint32_t)(mine[k] >> 32))) <= thr2)
-          s_list[atomicAdd(&s_n, 1u)] = mine[k];
-      __syncthreads();
-      n = (int)s_n;
-    }
-  }
-
-  // ---- order the survivors (descending composite key = score descending, flat index ascending)
-  const uint64_t* s_sorted = s_list;
-  if (n > 1 && 2 * n <= kListCap) {
-    // Bucket order: histogram bins are ordered by score, so a survivor's place is the number of survivors in
-    // better bins plus its rank inside its own (tiny) bin.  Counting sort by bin into the upper half of the list,
-    // then every survivor counts the larger keys of its bin.  Exact ties share a bin and are ranked by the key's
-    // flat-index half there.
-    float top = -INFINITY, bottom = INFINITY;
-    for (int i = tid; i < n; i += kSelThreads) { const float sc = gr_ordkey_inv((uint32_t)(s_list[i] >> 32)); top = fmaxf(top, sc); bottom = fminf(bottom, sc); }
-    top = block_max2<NW>(top, s_redf);
-    bottom = -block_max2<NW>(-bottom, s_redf);
-    const float range = top - bottom;
-    const float scale = (range > 0.f && range < INFINITY) ? (float)(kHistBins - 1) / range : 0.f;
-    auto bin_of = [&](uint64_t key) { return (int)fminf(fmaxf((top - gr_ordkey_inv((uint32_t)(key >> 32))) * scale, 0.f), (float)(kHistBins - 1)); };
-    for (int i = tid; i < kHistBins; i += kSelThreads) s_hist[i] = 0;
-    __syncthreads();
-    for (int i = tid; i < n; i += kSelThreads) atomicAdd(&s_hist[bin_of(s_list[i])], 1u);
-    __syncthreads();
-    {
-      // exclusive prefix over the bins, in place (each thread owns kHistBins / kSelThreads consecutive bins)
-      constexpr int per = kHistBins / kSelThreads;
-      uint32_t h[per], sum = 0;
-#pragma unroll
-      for (int k = 0; k < per; k++) { h[k] = s_hist[tid * per + k]; sum += h[k]; }
-      uint32_t total;
-      uint32_t run = block_excl_scan<NW>(sum, &total, s_redu, par);
-#pragma unroll
-      for (int k = 0; k < per; k++) { s_hist[tid * per + k] = run; run += h[k]; }
-    }
-    __syncthreads();
-    uint64_t* s_tmp = s_list + kListCap / 2;
-    for (int i = tid; i < n; i += kSelThreads) {
-      const uint64_t key = s_list[i];
-      s_tmp[atomicAdd(&s_hist[bin_of(key)], 1u)] = key;      // the bin's counter now runs to the bin's end
-    }
-    __syncthreads();
-    for (int q = tid; q < n; q += kSelThreads) {
-      const uint64_t key = s_tmp[q];
-      const int bin = bin_of(key);
-      const int s0 = bin ? (int)s_hist[bin - 1] : 0, s1 = (int)s_hist[bin];
-      int cnt = 0;
-      for (int j = s0; j < s1; j++) cnt += s_tmp[j] > key;
-      s_list[s0 + cnt] = key;
-    }
-    __syncthreads();
-  } else if (n > 1) {
-    int n2 = 1;
-    while (n2 < n) n2 <<= 1;
-    for (int i = n + tid; i < n2; i += kSelThreads) s_list[i] = 0;   // 0 sorts after every real key
-    __syncthreads();
-    for (int k = 2; k <= n2; k <<= 1) {
-      for (int j = k >> 1; j > 0; j >>= 1) {
-        for (int i = tid; i < n2; i += kSelThreads) {
-          const int ixj = i ^ j;
-          if (ixj > i) {
-            const uint64_t a = s_list[i], bb = s_list[ixj];
-            const bool desc = (i & k) == 0;
-            if (desc ? (a < bb) : (a > bb)) { s_list[i] = bb; s_list[ixj] = a; }
+          for (int q = 0; q < U; q++) {
+            const int u = base + q * kSelThreads;
+            if (u < front_units) s_group[u] = best[q];
+            if (best[q] > -INFINITY) atomicAdd(&s_hist[key_bin(hi, 64.f, best[q])], 1u);
           }
         }
         __syncthreads();
+        hist_threshold_all(s_hist, (uint32_t)c.W, &s_thr, s_redu, paru);
+        __syncthreads();
+        T = threshold(64.f);
+#pragma unroll 1
+        for (int u = tid; u < front_units; u += kSelThreads)
+          if (s_group[u] > -INFINITY && s_group[u] >= T) keep(u);
+      } else if (!listed) {
+        constexpr int U = 4;
+#pragma unroll 1
+        for (int base = tid; base < front_units; base += U * kSelThreads) {
+          float best[U], need[U];
+#pragma unroll
+          for (int q = 0; q < U; q++) {
+            const int u = base + q * kSelThreads;
+            best[q] = -INFINITY; need[q] = INFINITY;
+            if (u < front_units) {
+              int w, k, e;
+              entry(u, &w, &k, &e);
+              const int v = unit_token(k, e);
+              const float* x = c.logits + ((size_t)b * c.W + w) * c.V;
+              if (v + 3 < c.V) { const f32x4u t = *(const f32x4u*)(x + v); best[q] = fmaxf(fmaxf(t.x, t.y), fmaxf(t.z, t.w)); }
+              else if (v < c.V) best[q] = INFINITY;          // (the row's last tokens are looked at one by one below)
+              need[q] = needed(w);
+            }
+          }
+#pragma unroll
+          for (int q = 0; q < U; q++)
+            if (best[q] >= need[q]) keep(base + q * kSelThreads);
+        }
+      } else {
+        constexpr int U = 4;
+#pragma unroll 1
+        for (int base = tid; base < front_units; base += U * kSelThreads) {
+          float best[U], need[U];
+#pragma unroll
+          for (int q = 0; q < U; q++) {
+            const int u = base + q * kSelThreads;
+            best[q] = -INFINITY; need[q] = INFINITY;
+            if (u < front_units) {
+              int w, k, e;
+              entry(u, &w, &k, &e);
+              const int at = k + kUnitSpan * e, cnt = s_rinfo[w] >> 2;
+              const float* x = c.logits + ((size_t)b * c.W + w) * c.V;
+              const int32_t* list = child_list(c, mv) + s_ra[w];
+              if (at < cnt) {
+                const float y0 = x[list[at]], y1 = x[list[min(at + 64, cnt - 1)]], y2 = x[list[min(at + 128, cnt - 1)]], y3 = x[list[min(at + 192, cnt - 1)]];
+                best[q] = fmaxf(fmaxf(y0, y1), fmaxf(y2, y3));     // (a child taken twice changes nothing here)
+              }
+              need[q] = needed(w);
+            }
+          }
+#pragma unroll
+          for (int q = 0; q < U; q++)
+            if (best[q] >= need[q]) keep(base + q * kSelThreads);
+        }
+      }
+      __syncthreads();
+      fallback = s_nu > (uint32_t)kUnitCap;
+    }
+    if (!fallback) {
+      // ---- their candidates, counted in bins over what is above the threshold.  When they do not fit, the bins still tell
+      // where the W best end, and a second round takes only those.
+      const int nu = (int)s_nu, units = nu + ns;
+      const float scale_n = T > -INFINITY ? fmaxf(64.f, bin_scale(hi - T)) : 64.f;
+      int cut = kHistBins - 1;
+#pragma unroll 1
+      for (int round = 0; round < 2; round++) {
+#pragma unroll 1
+        for (int i = tid; i < units; i += kSelThreads) {
+          const uint32_t unit = i < nu ? s_units[i] : 0u;
+          const uint32_t ent = s_chunks[i < nu ? (int)(unit >> 8) : kChunkCap - 1 - (i - nu)];
+          const int w = (int)(ent >> 8), k = (int)(ent & 255u), cnt = s_rinfo[w] >> 2;
+          const float* xrow = c.logits + ((size_t)b * c.W + w) * c.V;
+          int place, stride = 1, end = cnt;                  // the unit's candidates: place, place + stride, ... < end
+          float bias = s_rbias[w], y[4];
+          uint32_t bits = 0xfu;
+          if (i < nu && !listed) {
+            place = unit_token(k, (int)(unit & 255u));
+            end = c.V;
+            if (c.blob && c.step == 0) bits = mv.l0[place >> 5] >> (place & 31);
+            else if (c.blob && c.step == 1) bits = mv.l1[(size_t)s_ra[w] * mv.words + (place >> 5)] >> (place & 31);
+#pragma unroll
+            for (int j = 0; j < 4; j++) y[j] = xrow[min(place + j, c.V - 1)];
+          } else if (i >= nu) {
+            place = 4 * k;
+            bias = 0.f;                                      // (these scores are complete)
+            const float4 t = *(const float4*)(data + (size_t)w * kRowFloats + place);
+            y[0] = t.x; y[1] = t.y; y[2] = t.z; y[3] = t.w;
+          } else {
+            place = k + kUnitSpan * (int)(unit & 255u);
+            stride = 64;
+            const int32_t* list = child_list(c, mv) + s_ra[w];
+            int tok[4];
+#pragma unroll
+            for (int j = 0; j < 4; j++) tok[j] = list[min(place + 64 * j, cnt - 1)];
+#pragma unroll
+            for (int j = 0; j < 4; j++) y[j] = xrow[tok[j]];
+          }
+#pragma unroll
+          for (int j = 0; j < 4; j++) {
+            const int at = place + j * stride;
+            const float score = __fadd_rn(bias, y[j]);       // (with bias 0 unchanged but for -0, which composite() makes 0)
+            if (at >= end || !((bits >> j) & 1u) || !(score > -INFINITY) || score < T) continue;
+            if (c.blob && c.step == 2 && i < nu && !listed) {           // last level, streamed row: the candidate has to be in the row's child list
+              const int32_t* list = mv.t3 + s_ra[w];
+              const int len = c.range_in[2 * ((size_t)b * c.W + w) + 1] - s_ra[w], pos = lower_bound_i32(list, len, at);
+              if (!(pos < len && list[pos] == at)) continue;
+            }
+            const int bin = key_bin(hi, scale_n, score);
+            if (bin > cut) continue;
+            if (round == 0) atomicAdd(&s_hist[bin], 1u);
+            const uint32_t pos = atomicAdd(&s_n, 1u);
+            if (pos < (uint32_t)kListCap) s_list[pos] = composite(score, (uint32_t)w * (uint32_t)c.V + (uint32_t)at);
+          }
+        }
+        __syncthreads();
+        n = (int)s_n;
+        if (round == 0) {
+          // exclusive prefix over the bins, in place, and the bin that holds the W-th candidate
+          constexpr int per = kHistBins / kSelThreads;
+          uint32_t h[per], sum = 0;
+#pragma unroll
+          for (int k = 0; k < per; k++) { h[k] = s_hist[tid * per + k]; sum += h[k]; }
+          uint32_t total;
+          uint32_t run = block_excl_scan<NW>(sum, &total, s_redu, paru);
+          if (tid == 0 && total < (uint32_t)c.W) s_thr = kHistBins - 1;
+#pragma unroll
+          for (int k = 0; k < per; k++) {
+            s_hist[tid * per + k] = run;
+            if (run < (uint32_t)c.W && run + h[k] >= (uint32_t)c.W) s_thr = tid * per + k;
+            run += h[k];
+          }
+          if (n > kListCap && tid == 0) s_n = 0;
+          __syncthreads();
+          cut = s_thr;
+        }
+        if (n <= kListCap) break;
+      }
+      // ---- order them (descending composite key = score descending, flat index ascending).  Histogram bins are ordered by
+      // score, so a survivor's place is the number of survivors in better bins plus its rank inside its own (tiny) bin.
+      // Counting sort by bin, then every survivor counts the larger keys of its bin.  Exact ties share a bin and are ranked
+      // by the key's flat-index half there.
+      auto bin_of = [&](uint64_t key) { return key_bin(hi, scale_n, gr_ordkey_inv((uint32_t)(key >> 32))); };
+      fallback = n > kListCap;
+      int m = 0;                                             // survivors up to the W-th one's bin
+      if (!fallback) {
+        m = cut < kHistBins - 1 ? (int)s_hist[cut + 1] : n;
+        fallback = m > kTmpCap;
+      }
+      if (!fallback) {
+        __syncthreads();                                     // (s_hist[cut + 1] is read before any counter moves; the units are done with)
+#pragma unroll 1
+        for (int i = tid; i < n; i += kSelThreads) {
+          const uint64_t key = s_list[i];
+          const int bin = bin_of(key);
+          if (bin <= cut) s_tmp[atomicAdd(&s_hist[bin], 1u)] = key;      // the bin's counter now runs to the bin's end
+        }
+        __syncthreads();
+#pragma unroll 1
+        for (int q = tid; q < m; q += kSelThreads) {
+          const uint64_t key = s_tmp[q];
+          const int bin = bin_of(key);
+          const int s0 = bin ? (int)s_hist[bin - 1] : 0, s1 = (int)s_hist[bin];
+          int cnt = 0;
+          for (int j = s0; j < s1; j++) cnt += s_tmp[j] > key;
+          s_list[s0 + cnt] = key;
+        }
+        n = m;
+        __syncthreads();
       }
     }
+    if (__builtin_expect(fallback, 0)) {
+      __syncthreads();
+      n = radix_select_all(c, mv, b, s_list, s_hist);
+      int n2 = 1;
+      while (n2 < n) n2 <<= 1;
+      for (int i = n + tid; i < n2; i += kSelThreads) s_list[i] = 0;   // 0 sorts after every real key
+      __syncthreads();
+      for (int k = 2; k <= n2; k <<= 1) {
+        for (int j = k >> 1; j > 0; j >>= 1) {
+          for (int i = tid; i < n2; i += kSelThreads) {
+            const int ixj = i ^ j;
+            if (ixj > i) {
+              const uint64_t a = s_list[i], bb = s_list[ixj];
+              const bool desc = (i & k) == 0;
+              if (desc ? (a < bb) : (a > bb)) { s_list[i] = bb; s_list[ixj] = a; }
+            }
+          }
+          __syncthreads();
+        }
+      }
+    }
+  }
+
+  // ---- level 1: which pair a survivor of a streamed row is = the valid tokens before it in its mask row, counted by four
+  // lanes in one round of loads (a binary search in the child list is a dozen dependent ones)
+  int32_t* s_rank = (int32_t*)s_hist;                        // [W] (kHistBins >= kMaxW)
+  if (c.blob && c.step == 1) {
+    for (int j0 = 0; j0 < min(n, c.W); j0 += kSelThreads / 4) {
+      const int j = j0 + (tid >> 2), g = tid & 3;
+      uint32_t cnt = 0;
+      if (j < min(n, c.W)) {
+        const uint32_t flat = 0xffffffffu - (uint32_t)s_list[j];
+        const int w = (int)(flat / (uint32_t)c.V), tok = (int)(flat % (uint32_t)c.V);
+        if ((s_rinfo[w] & 3) == ROW_DENSE) {
+          const uint32_t* mrow = mv.l1 + (size_t)s_ra[w] * mv.words;
+          const int full = tok >> 5;                         // whole words before the token's
+          if (g == 0) cnt = (uint32_t)mv.pair_off[s_ra[w]] + (uint32_t)__popc(mrow[full] & ((1u << (tok & 31)) - 1u));
+#pragma unroll 1
+          for (int i = 4 * g; i < full; i += 16) {           // (reads at most three words past the row: the blob goes on there)
+            const u32x4u q = *(const u32x4u*)(mrow + i);
+            cnt += (uint32_t)__popc(q.x) + (i + 1 < full ? (uint32_t)__popc(q.y) : 0u) + (i + 2 < full ? (uint32_t)__popc(q.z) : 0u) +
+                   (i + 3 < full ? (uint32_t)__popc(q.w) : 0u);
+          }
+        }
+      }
+      cnt += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)cnt, kXor1, 0xf, 0xf, true);
+      cnt += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)cnt, kXor2, 0xf, 0xf, true);
+      if (g == 0 && j < c.W) s_rank[j] = (int32_t)cnt;
+    }
+    __syncthreads();
   }
 
   // ---- write the new beam state, best first
@@ -963,29 +1234,32 @@ __global__ void __launch_bounds__(kSelThreads) k_select(SelCtx c) {
     for (int k = 0; k < c.depth; k++) po[k] = -1;
     int r_lo = 0, r_hi = 0, item = -1;
     if (j < n) {
-      const uint64_t key = s_sorted[j];
+      const uint64_t key = s_list[j];
       const uint32_t flat = 0xffffffffu - (uint32_t)key;
-      const int parent = (int)(flat / (uint32_t)c.V), token = (int)(flat % (uint32_t)c.V);
+      const int parent = (int)(flat / (uint32_t)c.V), place = (int)(flat % (uint32_t)c.V);
+      const bool gathered = (s_rinfo[parent] & 3) == ROW_SPARSE;
+      int token = place;
+      if (c.blob) {
+        if (c.step == 0) {
+          r_lo = mv.off1[token]; r_hi = mv.off1[token + 1];
+        } else if (c.step == 1) {
+          const int p = gathered ? s_ra[parent] + place : s_rank[j];
+          if (gathered) token = mv.pair_t2[p];
+          r_lo = mv.pair_row[p]; r_hi = mv.pair_row[p + 1];
+        } else {
+          const int first = s_ra[parent];
+          r_lo = first + (gathered ? place : lower_bound_i32(mv.t3 + first, c.range_in[2 * ((size_t)b * c.W + parent) + 1] - first, token));
+          if (gathered) token = mv.t3[r_lo];
+          r_hi = r_lo + 1;
+          item = r_lo;
+        }
+      }
       c.parent_out[o] = parent;
       c.token_out[o] = token;
       c.scores_out[o] = gr_ordkey_inv((uint32_t)(key >> 32));
       const size_t prow = (size_t)b * c.W + parent;
       for (int k = 0; k < c.step; k++) po[k] = c.prefix_in[prow * c.depth + k];
       po[c.step] = token;
-      if (c.blob) {
-        if (c.step == 0) {
-          r_lo = mv.off1[token]; r_hi = mv.off1[token + 1];
-        } else if (c.step == 1) {
-          const int p0 = s_rb[parent];                       // (the parent's child list, from the row table)
-          const int p = p0 + lower_bound_i32(mv.pair_t2 + p0, s_rc[parent] - p0, token);
-          r_lo = mv.pair_row[p]; r_hi = mv.pair_row[p + 1];
-        } else {
-          const int lo = s_ra[parent];
-          r_lo = lo + lower_bound_i32(mv.t3 + lo, s_rb[parent] - lo, token);
-          r_hi = r_lo + 1;
-          item = r_lo;
-        }
-      }
     } else {
       c.parent_out[o] = -1;
       c.token_out[o] = -1;
@@ -1002,7 +1276,7 @@ __global__ void __launch_bounds__(kSelThreads) k_select(SelCtx c) {
 extern "C" size_t gr_beam_select_workspace_bytes(int32_t B, int32_t W, int32_t V, int32_t depth) {
   if (B <= 0 || W <= 0 || V <= 0 || depth <= 0) return 0;
   const size_t rows = (size_t)B * W;
-  return 3 * gr_align256(rows * 4) + gr_align256(rows * kChunksPerRow * 4);
+  return 3 * gr_align256(rows * 4) + gr_align256(rows * (kGroups + kRowFloats) * 4);
 }
 
 extern "C" gr_status gr_beam_select(const gr_select_params* p, void* workspace, size_t workspace_bytes, void* stream_) {
@@ -1021,8 +1295,8 @@ extern "C" gr_status gr_beam_select(const gr_select_params* p, void* workspace, 
 
   SelCtx c;
   c.B = p->B; c.W = p->W; c.V = p->V; c.depth = p->depth; c.step = p->step; c.flags = p->flags;
-  c.vec4 = (p->V % 4 == 0) && (((uintptr_t)p->logits & 15) == 0);
-  c.epc = c.vec4 ? 4 * ((p->V / 4 + kChunksPerRow - 1) / kChunksPerRow) : (p->V + kChunksPerRow - 1) / kChunksPerRow;
+  c.unit_shift = 3;
+  while ((kBlockV >> 3) << c.unit_shift < p->V) c.unit_shift++;
   c.blob = (const char*)p->mask;
   c.logits = p->logits; c.scores_in = p->scores_in; c.prefix_in = p->prefix_in; c.range_in = p->range_in;
   c.parent_out = p->parent_out; c.token_out = p->token_out; c.scores_out = p->scores_out;
@@ -1030,13 +1304,18 @@ extern "C" gr_status gr_beam_select(const gr_select_params* p, void* workspace, 
   const size_t rows = (size_t)p->B * p->W;
   char* ws = (char*)workspace;
   c.row_bias = (float*)ws;                 ws += gr_align256(rows * 4);
-  c.row_mode = (int32_t*)ws;               ws += gr_align256(rows * 4);
-  c.row_top = (float*)ws;                  ws += gr_align256(rows * 4);
-  c.chunk_key = (float*)ws;
+  c.row_info = (int32_t*)ws;               ws += gr_align256(rows * 4);
+  c.row_start = (int32_t*)ws;              ws += gr_align256(rows * 4);
+  c.row_group = (float*)ws;                ws += rows * kGroups * 4;       // (whole 64 bytes a row: row_data stays 16-byte aligned)
+  c.row_data = (float*)ws;
 
-  const bool has_sparse = p->mask && p->step >= 1 && !(p->flags & GR_SELECT_FORCE_DENSE);
-  const size_t sparse_blocks = has_sparse ? (rows + kRowThreads / 64 - 1) / (kRowThreads / 64) : 0;
-  hipLaunchKernelGGL(k_rows, dim3((unsigned)(rows + sparse_blocks)), dim3(kRowThreads), 0, stream, c, has_sparse ? 0 : 1, (int)rows);
+  c.row_threads = p->step == 0 ? 512 : 256;
+  if (p->mask && p->step >= 1 && !(p->flags & GR_SELECT_FORCE_DENSE))
+    hipLaunchKernelGGL(k_rows_listed, dim3((unsigned)((rows + kGatherWaves - 1) / kGatherWaves)), dim3(kGatherWaves * 64), 0, stream, c);
+  else if (p->step == 0)
+    hipLaunchKernelGGL((k_rows<true, 512>), dim3((unsigned)(rows < kStrideGrid ? rows : kStrideGrid)), dim3(512), 0, stream, c);
+  else
+    hipLaunchKernelGGL((k_rows<false, 256>), dim3((unsigned)rows), dim3(256), 0, stream, c);
   // more than 64 KB of LDS must be opted into (per device; cheap, so done on every call)
   GR_HIP_TRY(hipFuncSetAttribute((const void*)k_select, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kSelLdsBytes));
   hipLaunchKernelGGL(k_select, dim3(p->B), dim3(kSelThreads), kSelLdsBytes, stream, c);

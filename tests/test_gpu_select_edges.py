@@ -1,0 +1,72 @@
+"""GPU: the item step where its kernels change hands, bit-exact against the oracle - rows around the blocks and lines that a
+streamed row is cut into, child counts around the limits of the gathered forms (scores kept, one wavefront, a workgroup) at
+levels 1 and 2, more beams than the selection keeps single groups for, and fewer groups than beams."""
+import numpy as np
+import pytest
+
+import gr_synth
+from gpu_util import assert_select_equal, run_select, to_dev
+from test_gpu_select import gr  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("step", [0, 1])
+@pytest.mark.parametrize("W,V", [(3, 3), (5, 31), (4, 2047), (6, 2050), (5, 8191), (5, 8193), (4, 16387), (3, 24575), (2, 32768), (70, 515), (1030, 33)])
+def test_streamed_rows_without_a_mask(gr, oracle_lib, W, V, step):  # noqa: F811
+    # step 0 deals rows to 512 threads, a later step to 256; some beams are dead
+    rng = np.random.default_rng(V + W + step)
+    B = 2
+    logits = (3.0 * rng.standard_normal((B, W, V))).astype(np.float32)
+    logits[0, 0, V - 1] = 9.0                                      # the row's last token wins
+    sc = (-3.0 * rng.random((B, W))).astype(np.float32)
+    sc[:, 2::3] = -np.inf
+    pf = np.full((B, W, 3), -1, np.int32)
+    pf[:, :, :step] = 0
+    rg = np.zeros((B, W, 2), np.int32)
+    assert_select_equal(run_select(gr, None, logits, sc, pf, rg, step), oracle_lib.beam_select(None, logits, sc, pf, step))
+
+
+def _children(rng, V, counts):
+    """Sorted distinct tokens per entry of `counts`."""
+    return [np.sort(rng.choice(V, size=n, replace=False)) for n in counts]
+
+
+@pytest.mark.parametrize("flags", [0, 1])
+@pytest.mark.parametrize("V,W", [(4100, 13), (4100, 600), (9001, 20)])
+def test_child_counts_at_the_limits(gr, oracle_lib, V, W, flags):  # noqa: F811
+    rng = np.random.default_rng(V + W)
+    counts = [1, 15, 16, 17, 239, 240, 241, 1023, 1024, 1025, 2300, 3900]
+    rows = []
+    for t1, second in enumerate(_children(rng, V, counts)):        # level 1: first token t1 has counts[t1] children
+        rows += [(t1, int(t2), int(rng.integers(V))) for t2 in second]
+    last = len(counts)
+    for t2, third in enumerate(_children(rng, V, counts)):         # level 2: pair (last, t2) has counts[t2] children
+        rows += [(last, t2, int(t3)) for t3 in third]
+    items = np.array(sorted(rows), dtype=np.int32)
+    mask = gr.gr_item_mask_build(to_dev(items), V)
+    sc, pf, rg = gr_synth.initial_beam_state(1, W, 3)
+    for step in range(3):
+        logits = (2.0 * rng.standard_normal((1, W, V))).astype(np.float32)
+        if step == 1:
+            logits[0, :, :len(counts)] += np.where(pf[0, :, 0] == last, 30.0, 0.0)[:, None].astype(np.float32)   # keep the pairs of `last`
+        want = oracle_lib.beam_select(items, logits, sc, pf, step)
+        assert_select_equal(run_select(gr, mask, logits, sc, pf, rg, step, flags), want, f"step {step}")
+        sc, pf, rg = want["scores"], want["prefix"], want["range"]
+
+
+@pytest.mark.parametrize("spread", [1e-4, 1e-2, 40.0])
+def test_scores_close_together_and_far_apart(gr, oracle_lib, spread):  # noqa: F811
+    # the histograms adapt their bins to the range of the scores; 40 reaches past what 2048 bins of 1/64 cover
+    rng = np.random.default_rng(5)
+    B, W, V = 2, 48, 3000
+    logits = (spread * rng.standard_normal((B, W, V))).astype(np.float32)
+    sc = (-0.1 * spread * rng.random((B, W))).astype(np.float32)
+    pf = np.full((B, W, 3), -1, np.int32)
+    rg = np.zeros((B, W, 2), np.int32)
+    for step in (0, 1):
+        pf[:, :, :step] = 0
+        assert_select_equal(run_select(gr, None, logits, sc, pf, rg, step), oracle_lib.beam_select(None, logits, sc, pf, step), f"step {step}")
+    one = np.full((B, W), -np.inf, np.float32)
+    one[:, 7] = 0.0                                                # a single live beam: fewer groups than beams
+    assert_select_equal(run_select(gr, None, logits, one, pf, rg, 0), oracle_lib.beam_select(None, logits, one, pf, 0))
