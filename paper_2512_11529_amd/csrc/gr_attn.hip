@@ -10,6 +10,7 @@
 // tiles) and used by all query rows of the block.  The unshared stage (each beam's own u decode tokens) and the merge
 // run in the epilogue of segment 0 on the same per-lane state; when the prompt is split into
 // segments, partial (max, sum, O) go to the workspace and k_attn_merge combines them.
+#include <type_traits>
 #include "gr_internal.hpp"
 
 namespace {
@@ -76,18 +77,33 @@ struct AttnTile {
   static constexpr int PPRW = D / 8;                                       // 16-byte pieces per row
   static __device__ __forceinline__ int swz_k(int r) { return D == 128 ? (r & 15) : ((r >> 1) & 7); }
   static __device__ __forceinline__ int swz_v(int r) { return D == 128 ? 4 * (r & 3) : 4 * ((r >> 1) & 1); }
-  // per-lane element offsets of the operand reads inside a tile (fixed for the whole kernel)
+  // Per-lane LDS addresses of the operand reads of a tile at the start of LDS, fixed for the whole kernel: what tile slot, slab and
+  // block add to them is known at compile time and goes into the instructions.
   struct Rd { int k[D / 16]; int v[D / 32]; };
-  static __device__ __forceinline__ Rd make_rd(int lane) {
+  static __device__ __forceinline__ Rd make_rd(int lane, int lds_base) {
     const int G = lane >> 5, n32 = lane & 31;
     Rd r;
 #pragma unroll
-    for (int ks = 0; ks < D / 16; ks++) r.k[ks] = n32 * D + ((2 * ks + G) ^ swz_k(n32)) * 8;
+    for (int ks = 0; ks < D / 16; ks++) r.k[ks] = lds_base + 2 * (n32 * D + ((2 * ks + G) ^ swz_k(n32)) * 8);
     const int vrow = 4 * G + ((lane & 15) >> 2);
 #pragma unroll
     for (int db = 0; db < D / 32; db++)
-      r.v[db] = vrow * D + ((4 * db + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) ^ swz_v(vrow)) * 8 + 4 * (lane & 1);
+      r.v[db] = lds_base + 2 * (vrow * D + ((4 * db + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) ^ swz_v(vrow)) * 8 + 4 * (lane & 1));
     return r;
+  }
+  // K operand of 32 tokens `sub` and 16 dimensions `ks`; V^T operand of 16 tokens `slab` and 32 dimensions `db`
+  static __device__ __forceinline__ bf16x8 read_k(int tile, const Rd& r, int sub, int ks) {         // `tile`: element offset in LDS
+    typedef const u32x4 __attribute__((address_space(3))) * lds_u32x4;
+    return __builtin_bit_cast(bf16x8, *(lds_u32x4)(uintptr_t)(uint32_t)(r.k[ks] + 2 * (tile + sub * 32 * D)));
+  }
+  static __device__ __forceinline__ bf16x8 read_v(int tile, const Rd& r, int slab, int db) {
+    typedef short s16x8 __attribute__((ext_vector_type(8)));
+    typedef s16x4 __attribute__((address_space(3))) * lds_s16x4;
+    const int at = r.v[db] + 2 * (tile + slab * 16 * D);
+    s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(uintptr_t)(uint32_t)at);
+    s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(uintptr_t)(uint32_t)(at + 2 * 8 * D));
+    s16x8 both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+    return __builtin_bit_cast(bf16x8, both);
   }
   static constexpr int KSTR = D + 8;     // padded rows of the Q / output staging and of the own-token mini-tiles (+16 B)
   // V rows: +64 B.  One ds_read_b64_tr_b16 serves 32 lanes per cycle = 4 rows x 2 column halves x 32 bytes; a row
@@ -96,7 +112,7 @@ struct AttnTile {
   static constexpr int VSTR = D + 32;    // (own-token mini-tiles only; prompt V tiles are unpadded and swizzled)
 
   // S^T = K . Q^T from the K tile in LDS (A operand) and Q in registers (B operand)
-  static __device__ __forceinline__ void qk(const uint16_t* sk, const bf16x8 (&qop)[NCB][D / 16], f32x16 (&s)[KT / 32][NCB],
+  static __device__ __forceinline__ void qk(int sk, const bf16x8 (&qop)[NCB][D / 16], f32x16 (&s)[KT / 32][NCB],
                                             const Rd& rdo) {
 #pragma unroll
     for (int sub = 0; sub < KT / 32; sub++)
@@ -108,10 +124,10 @@ struct AttnTile {
     constexpr int N = (KT / 32) * (D / 16), PF = 4;
     bf16x8 a[N];
 #pragma unroll
-    for (int i = 0; i < PF; i++) a[i] = as_bf16x8(*(const uint4*)(&sk[(i % 2) * 32 * D + rdo.k[i / 2]]));
+    for (int i = 0; i < PF; i++) a[i] = read_k(sk, rdo, i % 2, i / 2);
 #pragma unroll
     for (int i = 0; i < N; i++) {
-      if (i + PF < N) a[i + PF] = as_bf16x8(*(const uint4*)(&sk[((i + PF) % 2) * 32 * D + rdo.k[(i + PF) / 2]]));
+      if (i + PF < N) a[i + PF] = read_k(sk, rdo, (i + PF) % 2, (i + PF) / 2);
 #pragma unroll
       for (int cb = 0; cb < NCB; cb++) s[i % 2][cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], qop[cb][i / 2], s[i % 2][cb], 0, 0, 0);
     }
@@ -125,16 +141,9 @@ struct AttnTile {
   }
 
   // O^T += V^T . P^T.  V^T operand: d = 32*db + (lane%32), k slot e <-> token 16*s + 8*(e/4) + 4*G + e%4
-  static __device__ __forceinline__ void pv(const uint16_t* sv, const bf16x8 (&pop)[KT / 16][NCB], f32x16 (&o)[D / 32][NCB], const Rd& rdo) {
-    typedef short s16x8 __attribute__((ext_vector_type(8)));
+  static __device__ __forceinline__ void pv(int sv, const bf16x8 (&pop)[KT / 16][NCB], f32x16 (&o)[D / 32][NCB], const Rd& rdo) {
     constexpr int N = (KT / 16) * (D / 32), PF = 4;      // operand i: slab i / (D/32), d block i % (D/32)
-    auto rd = [&](int i) {
-      const uint16_t* p0 = sv + (i / (D / 32)) * 16 * D + rdo.v[i % (D / 32)];
-      s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(p0));
-      s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(p0 + 8 * D));
-      s16x8 both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-      return __builtin_bit_cast(bf16x8, both);
-    };
+    auto rd = [&](int i) { return read_v(sv, rdo, i / (D / 32), i % (D / 32)); };
     bf16x8 a[N];
 #pragma unroll
     for (int i = 0; i < PF; i++) a[i] = rd(i);
@@ -170,34 +179,32 @@ struct AttnTile {
   // the 32 quarter-rate exponentials per lane run in the shadow of the 32 MFMAs instead of after them.  P(t) is
   // complete before the second half of the PV MFMAs starts; those are interleaved with the column maximum of
   // S(t+1), which the next tile's decision needs.  Instruction order is pinned chunk by chunk.
+  // Measured at 32 x 4096 tokens x 256 beams, two wavefronts per SIMD: 507 us with the exponentials staged over three chunks, 515
+  // with each finished in one; 8 x 2048 x 128 (one wavefront per SIMD, 1.1 us a tile): 40.1 against 41.4 us.  Operand reads 5 or 6
+  // MFMAs ahead: no change.
   static constexpr int NQK = (KT / 32) * (D / 16), NPV = (KT / 16) * (D / 32), NMF = NQK + NPV;
-  static constexpr int EXP_BY = NQK + NPV / 2;            // all 32 exponentials are done after this many MFMAs
+  static constexpr int EXP_BY = NQK + NPV / 2;            // all 32 exponentials are issued after this many MFMAs
   static constexpr int exps_after(int j) {                // exponentials finished once MFMA j's chunk has been issued
     const int t = (32 * (j + 1) + EXP_BY - 1) / EXP_BY;
     return j < 0 ? 0 : (t > 32 ? 32 : t);
   }
-  static __device__ __forceinline__ void fused(const uint16_t* sk_next, const uint16_t* sv_cur, const bf16x8 (&qop)[NCB][D / 16],
+  static __device__ __forceinline__ void fused(int sk_next, int sv_cur, const bf16x8 (&qop)[NCB][D / 16],
                                                const f32x16 (&s_cur)[KT / 32][NCB], f32x16 (&s_next)[KT / 32][NCB],
                                                f32x16 (&o)[D / 32][NCB], float mc, float c, float& l_run, float& mx_next, const Rd& rdo) {
     static_assert(NCB == 1, "one column block per wave");
-    typedef short s16x8 __attribute__((ext_vector_type(8)));
-    auto rdk = [&](int i) { return as_bf16x8(*(const uint4*)(sk_next + (i % 2) * 32 * D + rdo.k[i / 2])); };
-    auto rdv = [&](int i) {
-      const uint16_t* p0 = sv_cur + (i / (D / 32)) * 16 * D + rdo.v[i % (D / 32)];
-      s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(p0));
-      s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(p0 + 8 * D));
-      s16x8 both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-      return __builtin_bit_cast(bf16x8, both);
-    };
+    auto rdk = [&](int i) { return read_k(sk_next, rdo, i % 2, i / 2); };
+    auto rdv = [&](int i) { return read_v(sv_cur, rdo, i / (D / 32), i % (D / 32)); };
     constexpr int PF = 4;                                   // operand reads run PF MFMAs ahead
     constexpr int SCAN0 = NMF - NPV / 2, EPC = 32 / (NPV / 2);   // maximum scan: EPC scores per chunk from MFMA SCAN0 on
     bf16x8 a[NMF];
     bf16x8 pop[KT / 16];
-    float p[8];
+    float p[32], arg[32];                                   // (a few of each are alive at a time)
     float rs = 0.f, mx = -INFINITY;
     const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int i = 0; i < PF; i++) a[i] = rdk(i);
+#pragma unroll
+    for (int e = 0; e < exps_after(0); e++) arg[e] = fmaf(s_cur[e / 16][0][e % 16], c, -mc);
 #pragma unroll
     for (int j = 0; j < NMF; j++) {
       if (j + PF < NMF) a[j + PF] = (j + PF < NQK) ? rdk(j + PF) : rdv(j + PF - NQK);
@@ -207,16 +214,21 @@ struct AttnTile {
         const int i = j - NQK;
         o[i % (D / 32)][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[j], pop[i / (D / 32)], o[i % (D / 32)][0], 0, 0, 0);
       }
+      // the exponentials' arguments, the exponentials and their sums and packing are three stages, one chunk apart, so that none
+      // waits for the one before
 #pragma unroll
-      for (int e = exps_after(j - 1); e < exps_after(j); e++) {
-        const float v = __builtin_amdgcn_exp2f(fmaf(s_cur[e / 16][0][e % 16], c, -mc));
-        rs += v;
-        p[e % 8] = v;
+      for (int e = exps_after(j - 2); e < exps_after(j - 1); e++) rs += p[e];
+#pragma unroll
+      for (int e = exps_after(j - 1); e < exps_after(j); e++) p[e] = __builtin_amdgcn_exp2f(arg[e]);
+#pragma unroll
+      for (int e = exps_after(j); e < exps_after(j + 1); e++) arg[e] = fmaf(s_cur[e / 16][0][e % 16], c, -mc);
+#pragma unroll
+      for (int e = exps_after(j - 2); e < exps_after(j - 1); e++) {
         if (e % 8 == 7) {
           bf16x8 pk;
 #pragma unroll
           for (int k = 0; k < 8; k += 2) {
-            f32x2 two = {p[k], p[k + 1]};
+            f32x2 two = {p[e - 7 + k], p[e - 7 + k + 1]};
             bf16x2 h = __builtin_convertvector(two, bf16x2);
             pk[k] = h[0];
             pk[k + 1] = h[1];
@@ -307,7 +319,8 @@ k_beam_attn(AttnCtx c) {
   constexpr int CPW = NCHUNK / NWAVES;           // chunks per wave and tile
   constexpr int RPC = 1024 / (D * 2);            // rows per chunk
   static_assert(NCHUNK % NWAVES == 0, "tile must divide over the waves");
-  // double-buffered tiles: K(j) in s_k[j%2], V(j) in s_v[j%2]; then (8-wave workgroups only: they own the CU's LDS
+  // double-buffered tiles: K(j) in s_k[slot], V(j) in s_v[slot], slot = (j + flip) % 2 (flip is chosen below so that the last
+  // tile is in slot 0: the main loop then names its slots at compile time); then (8-wave workgroups only: they own the CU's LDS
   // anyway) a separate region for the Q hand-over, so that the first tiles can be in flight while Q is staged
   extern __shared__ __attribute__((aligned(1024))) uint16_t smem[];
   uint16_t* s_k = smem;
@@ -341,7 +354,7 @@ k_beam_attn(AttnCtx c) {
   chunk = ((chunk + KT - 1) / KT) * KT;
   const int seg0 = CAUSAL ? 0 : min(Lb, sp * chunk);
   const int seg1 = CAUSAL ? (min((mbi + 1) * (NWAVES * 32 * NCB), Mb) - 1) / c.g + 1 : min(Lb, seg0 + chunk);
-  const int ntiles = (seg1 - seg0 + KT - 1) / KT;
+  const int ntiles = (seg1 - seg0 + KT - 1) / KT, flip = (ntiles - 1) & 1;
 
   // ---- Q: the workgroup's MWG query rows are fetched with coalesced 16-byte pieces (a row = PPR
   // consecutive lanes) and handed to the lanes that own them through LDS.  A lane reading its own
@@ -395,7 +408,7 @@ k_beam_attn(AttnCtx c) {
   const char* kbase = (const char*)c.ks + ((size_t)row0 * c.Hkv + kvh) * D * EB;
   const char* vbase = (const char*)c.vs + ((size_t)row0 * c.Hkv + kvh) * D * EB;
   const float cp = KV8 ? c.c * c.k_scale : c.c;              // exponent scale of the prompt loop
-  const typename T::Rd rdo = T::make_rd(lane);
+  const typename T::Rd rdo = T::make_rd(lane, (int)(uintptr_t)(__attribute__((address_space(3))) uint16_t*)smem);
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);
   int crow[CPW];                                             // this lane's row inside a tile, per chunk
   uint32_t koff[CPW], voff[CPW];                             // and its byte offsets from the tile's first row (full tiles)
@@ -492,7 +505,7 @@ k_beam_attn(AttnCtx c) {
   if (own_stage) {
     // the most beams any wave's 32 rows can span (exact when g divides 32, else an upper bound: a surplus
     // pass only sees masked rows)
-    const int nb_max = (32 % c.g == 0) ? 32 / c.g : (32 + c.g - 2) / c.g + 1;
+    const int nb_max = min(c.W, (32 % c.g == 0) ? 32 / c.g : (32 + c.g - 2) / c.g + 1);
     npass = (nb_max * c.u + UR - 1) / UR;
     R = wave_rows(wave, &beam0);
   }
@@ -529,8 +542,8 @@ k_beam_attn(AttnCtx c) {
   if (KV8) {
     if (ntiles > 0) { k8 = gload8(true, 0); v8 = gload8(false, 0); k8b = gload8(true, min(1, ntiles - 1)); }
   } else if (kQSeparate && ntiles > 0) {
-    tload(true, 0, 0); tload(false, 0, 0);
-    tload(true, 1, min(1, ntiles - 1));
+    tload(true, flip, 0); tload(false, flip, 0);
+    tload(true, flip ^ 1, min(1, ntiles - 1));
   }
   // Q as B operands: lane holds query column n32 of the wave's block, d = 16*ks + 8*G + (0..7)
   bf16x8 qop[NCB][D / 16];
@@ -546,12 +559,12 @@ k_beam_attn(AttnCtx c) {
     if (!kQSeparate) {
       __syncthreads();                               // the tile slots may now be overwritten
       if (!KV8 && ntiles > 0) {
-        tload(true, 0, 0); tload(false, 0, 0);
-        tload(true, 1, min(1, ntiles - 1));
+        tload(true, flip, 0); tload(false, flip, 0);
+        tload(true, flip ^ 1, min(1, ntiles - 1));
       }
     }
     if (KV8 && ntiles > 0) {
-      lstore8(s_k, true, k8); lstore8(s_v, false, v8); lstore8(s_k + TILE, true, k8b);
+      lstore8(s_k + flip * TILE, true, k8); lstore8(s_v + flip * TILE, false, v8); lstore8(s_k + (flip ^ 1) * TILE, true, k8b);
       k8 = gload8(true, min(2, ntiles - 1));
       v8 = gload8(false, min(1, ntiles - 1));
     }
@@ -589,7 +602,8 @@ k_beam_attn(AttnCtx c) {
           s[sub][0][i] = (kv > tokq) ? -INFINITY : s[sub][0][i];
         }
     };
-    auto step = [&](f32x16 (&s_in)[KT / 32][NCB], f32x16 (&s_out)[KT / 32][NCB], int t) {
+    auto step = [&](auto slot_c, f32x16 (&s_in)[KT / 32][NCB], f32x16 (&s_out)[KT / 32][NCB], int t) {      // tile t in slot slot_c
+      constexpr int slot = decltype(slot_c)::value;
       if (CAUSAL && seg0 + t * KT + KT - 1 > wave_tok0) {         // (wave-uniform) this tile reaches past the wave's first token
         causal_mask(s_in, seg0 + t * KT);
         mx_cur = T::colmax(s_in);
@@ -607,15 +621,15 @@ k_beam_attn(AttnCtx c) {
       tiles_landed();                                               // this wave's K(t+1) and V(t) loads (issued one step ago)
       __syncthreads();                                              // everyone's; and everyone is done with K(t) and V(t-1)
       if (KV8) {
-        lstore8(s_k + (t & 1) * TILE, true, k8);                    // K(t+2) over K(t)
-        lstore8(s_v + ((t + 1) & 1) * TILE, false, v8);             // V(t+1) over V(t-1)
+        lstore8(s_k + slot * TILE, true, k8);                       // K(t+2) over K(t)
+        lstore8(s_v + (slot ^ 1) * TILE, false, v8);                // V(t+1) over V(t-1)
         k8 = gload8(true, min(t + 3, tl));
         v8 = gload8(false, min(t + 2, tl));
       } else {
-        tload(true, t & 1, min(t + 2, tl));                         // K(t+2) over K(t)
-        tload(false, (t + 1) & 1, min(t + 1, tl));                  // V(t+1) over V(t-1)
+        tload(true, slot, min(t + 2, tl));                          // K(t+2) over K(t)
+        tload(false, slot ^ 1, min(t + 1, tl));                     // V(t+1) over V(t-1)
       }
-      T::fused(s_k + ((t + 1) & 1) * TILE, s_v + (t & 1) * TILE, qop, s_in, s_out, o_acc, m_run[0] * cp, cp, l_run[0], mx_cur, rdo);
+      T::fused((slot ^ 1) * TILE, (2 + slot) * TILE, qop, s_in, s_out, o_acc, m_run[0] * cp, cp, l_run[0], mx_cur, rdo);
     };
     // the last tile of the segment: the only one that can be partial, and it has no successor
     auto last = [&](f32x16 (&s_in)[KT / 32][NCB], int t) {
@@ -639,17 +653,17 @@ k_beam_attn(AttnCtx c) {
       bool upd[NCB];
       T::softmax(s_in, pop, m_run, l_run, alpha, upd, cp);
       rescale(alpha, upd);
-      T::pv(s_v + (t & 1) * TILE, pop, o_acc, rdo);
+      T::pv(2 * TILE, pop, o_acc, rdo);
     };
 
     f32x16 s_a[KT / 32][NCB], s_b[KT / 32][NCB];      // ping-pong score accumulators: no copies
-    T::qk(s_k, qop, s_a, rdo);
+    T::qk(flip * TILE, qop, s_a, rdo);
     if (ntiles > 1) mx_cur = T::colmax(s_a);
     // ntiles - 1 steps, then the last tile.  An odd step is peeled off first so that the loop runs
     // whole ping-pong pairs and the last tile is always in s_a.
     int t = 0;
-    if ((ntiles - 1) & 1) {
-      step(s_a, s_b, 0);
+    if (flip) {
+      step(std::integral_constant<int, 1>(), s_a, s_b, 0);
 #pragma unroll
       for (int sub = 0; sub < KT / 32; sub++)
 #pragma unroll
@@ -657,8 +671,8 @@ k_beam_attn(AttnCtx c) {
       t = 1;
     }
     for (; t + 1 < ntiles; t += 2) {
-      step(s_a, s_b, t);
-      step(s_b, s_a, t + 1);
+      step(std::integral_constant<int, 0>(), s_a, s_b, t);
+      step(std::integral_constant<int, 1>(), s_b, s_a, t + 1);
     }
     last(s_a, t);
     if (KV8) {                                         // prompt loop -> true units
@@ -685,13 +699,13 @@ k_beam_attn(AttnCtx c) {
     uint16_t* s_uv = smem + NWAVES * UR * KSTR + wave * UR * VSTR;
     if (ntiles == 0) uload(0);
     for (int pass = 0; pass < npass; pass++) {
-      if (pass > 0) uload(pass);
 #pragma unroll
       for (int i = 0; i < UP; i++) {
         const int pi = lane + 64 * i, row = pi / PPR, col = (pi % PPR) * 8;
         *(uint4*)(&s_uk[row * KSTR + col]) = ukp[i];
         *(uint4*)(&s_uv[row * VSTR + col]) = uvp[i];
       }
+      if (pass + 1 < npass) uload(pass + 1);               // (arrives while this pass is computed)
       __syncthreads();
       // scores of the 32 rows against the wave's 32 columns
       f32x16 su;
@@ -831,35 +845,57 @@ k_beam_attn(AttnCtx c) {
   }
 }
 
-// Merge of the per-segment partials (Section 5.2 merge stage): one wave per output row.
+// Merge of the per-segment partials (Section 5.2 merge stage): D / 4 lanes per output row, 16 bytes each.  The (max, sum) pairs
+// and the partials of four segments are requested together, so a row waits for memory once per four segments.  Bound: the
+// partials' bytes; 4096 rows x 5 segments of 128 (10.5 MB) take 4.3 us (6.7 us with 4-byte loads, one segment at a time).
 template <int D>
 __global__ void __launch_bounds__(256) k_attn_merge(AttnCtx c) {
-  const int lane = threadIdx.x & 63;
-  const size_t row = (size_t)blockIdx.x * 4 + (threadIdx.x >> 6);   // (b, w, hq) flattened
+  constexpr int LPR = D / 4, RPW = 256 / LPR;              // lanes per row, rows per workgroup
+  const int lane = threadIdx.x % LPR;
+  const size_t row = (size_t)blockIdx.x * RPW + threadIdx.x / LPR;      // (b, w, hq) flattened
   const size_t rows_per_b = (size_t)c.W * c.Hq;
   if (row >= (size_t)c.B * rows_per_b) return;
-  const size_t b = row / rows_per_b, rr = row % rows_per_b;
-  float M2 = -INFINITY;
-  for (int s = 0; s < c.nsplit; s++) M2 = fmaxf(M2, c.part_ml[((b * c.nsplit + s) * rows_per_b + rr) * 2]);
-  float L = 0.f;
-  float acc[D / 64];
+  const size_t b = row / rows_per_b, rr = row - b * rows_per_b;
+  const size_t prow0 = b * c.nsplit * rows_per_b + rr;     // this row of segment 0; the next segment's is rows_per_b further
+  float M2 = -INFINITY, L = 0.f;
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  constexpr int U = 4;
+#pragma unroll 1
+  for (int s0 = 0; s0 < c.nsplit; s0 += U) {
+    f32x2 ml[U];
+    f32x4 o[U];
 #pragma unroll
-  for (int k = 0; k < D / 64; k++) acc[k] = 0.f;
-  for (int s = 0; s < c.nsplit; s++) {
-    const size_t prow = (b * c.nsplit + s) * rows_per_b + rr;
-    const float m2 = c.part_ml[prow * 2], l = c.part_ml[prow * 2 + 1];
-    if (!(l > 0.f)) continue;
-    const float sc = __builtin_amdgcn_exp2f(m2 - M2);
-    L += l * sc;
+    for (int k = 0; k < U; k++) {
+      const size_t prow = prow0 + (size_t)min(s0 + k, c.nsplit - 1) * rows_per_b;
+      ml[k] = *(const f32x2*)(c.part_ml + prow * 2);
+      o[k] = *(const f32x4*)(c.part_o + prow * D + 4 * lane);
+    }
+    float mx = M2;
 #pragma unroll
-    for (int k = 0; k < D / 64; k++) acc[k] += c.part_o[prow * D + k * 64 + lane] * sc;
+    for (int k = 0; k < U; k++) {
+      if (s0 + k >= c.nsplit) ml[k].y = 0.f;               // (a repeated segment counts nothing)
+      if (ml[k].y > 0.f) mx = fmaxf(mx, ml[k].x);
+    }
+    if (!(mx > -INFINITY)) continue;
+    const float alpha = __builtin_amdgcn_exp2f(M2 - mx);
+    L *= alpha;
+#pragma unroll
+    for (int e = 0; e < 4; e++) acc[e] *= alpha;
+#pragma unroll
+    for (int k = 0; k < U; k++) {
+      if (!(ml[k].y > 0.f)) continue;
+      const float sc = __builtin_amdgcn_exp2f(ml[k].x - mx);
+      L += ml[k].y * sc;
+#pragma unroll
+      for (int e = 0; e < 4; e++) acc[e] += o[k][e] * sc;
+    }
+    M2 = mx;
   }
   const float inv = (L > 0.f) ? 1.0f / L : 0.f;
+  bf16x4 h;
 #pragma unroll
-  for (int k = 0; k < D / 64; k++) {
-    const __bf16 h = (__bf16)(acc[k] * inv);
-    c.out[row * D + k * 64 + lane] = __builtin_bit_cast(uint16_t, h);
-  }
+  for (int e = 0; e < 4; e++) h[e] = (__bf16)(acc[e] * inv);
+  *(bf16x4*)(c.out + row * D + 4 * lane) = h;
   if (c.lse && lane == 0) c.lse[row] = (L > 0.f) ? (M2 + __builtin_amdgcn_logf(L)) * kLn2 : -INFINITY;
 }
 
@@ -1025,7 +1061,8 @@ gr_status attn_run(const gr_attn_params* p, const int32_t* slot, bool kv8, float
 #undef GR_LAUNCH_ATTN
   if (c.nsplit > 1) {
     const int64_t rows = (int64_t)p->B * p->W * p->Hq;
-    const unsigned mgrid = (unsigned)((rows + 3) / 4);
+    const int rpw = 256 / (p->d / 4);                      // rows per workgroup
+    const unsigned mgrid = (unsigned)((rows + rpw - 1) / rpw);
     if (p->d == 128) hipLaunchKernelGGL((k_attn_merge<128>), dim3(mgrid), dim3(256), 0, stream, c);
     else hipLaunchKernelGGL((k_attn_merge<64>), dim3(mgrid), dim3(256), 0, stream, c);
   }
