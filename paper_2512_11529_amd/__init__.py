@@ -8,10 +8,12 @@ The calls have the names and meaning of the C ABI in include/gr.h:
     gr_beam_reorder      in-place move of the surviving beams' own KV cache to their new slots
 
 This module only marshals arguments (torch CUDA tensors -> device pointers, current stream ->
-hipStream_t).  Every step of the path runs in the HIP kernels; there is no CPU or PyTorch fallback,
-and loading fails loudly when the library has not been built.
+hipStream_t), for the calls of the decode loop in native code (csrc/gr_bind.cpp).  Every step of the path runs in the
+HIP kernels; there is no CPU or PyTorch fallback, and loading fails loudly when the library has not been built.
 """
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 
 from . import build as _build
@@ -24,6 +26,7 @@ __all__ = ["load_library", "gr_beam_attn", "gr_beam_attn_fp8kv", "gr_prefill_att
 LIB_PATH = _build.LIB_PATH
 GR_SELECT_FORCE_DENSE = 1
 _lib = None
+_native = None
 
 
 class GrError(RuntimeError):
@@ -117,6 +120,24 @@ def load_library(path: str = None):
     return lib
 
 
+def _marshal():
+    """The marshalling module, bound to the loaded library."""
+    global _native
+    if _native is None:
+        lib = load_library()
+        if not os.path.exists(_build.BIND_PATH):
+            raise RuntimeError(f"{_build.BIND_PATH} is missing: build it first (python -c 'import __graft_entry__ as g; g.build()')")
+        import torch  # noqa: F401  (its libraries have to be loaded before the module is)
+        loader = importlib.machinery.ExtensionFileLoader("gr_bind", _build.BIND_PATH)
+        native = importlib.util.module_from_spec(importlib.util.spec_from_loader("gr_bind", loader))
+        loader.exec_module(native)
+        native.bind(*(ctypes.cast(getattr(lib, f), ctypes.c_void_p).value for f in (
+            "gr_beam_attn", "gr_beam_attn_slots", "gr_beam_attn_fp8kv", "gr_beam_attn_workspace_bytes", "gr_prefill_attn", "gr_beam_select",
+            "gr_beam_select_noalloc", "gr_beam_select_workspace_bytes", "gr_beam_reorder", "gr_beam_slot_update")), _current_stream_handle)
+        _native = native
+    return _native
+
+
 def gr_status_string(status) -> str:
     return load_library().gr_status_string(int(status)).decode()
 
@@ -125,10 +146,13 @@ def _ptr(t):
     return None if t is None else ctypes.c_void_p(t.data_ptr())
 
 
-def _stream(stream):
+def _current_stream_handle():
     import torch
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+
+
+def _stream(stream):
+    return ctypes.c_void_p(_current_stream_handle() if stream is None else stream.cuda_stream)
 
 
 def _check(t, dtype, shape, name):
@@ -139,20 +163,6 @@ def _check(t, dtype, shape, name):
         raise TypeError(f"{name}: expected {dtype}, got {t.dtype}")
     if shape is not None and tuple(t.shape) != tuple(shape):
         raise ValueError(f"{name}: expected shape {tuple(shape)}, got {tuple(t.shape)}")
-
-
-def _attn_params(q, k_shared, v_shared, cu_seqlens, k_unshared, v_unshared, u, sm_scale, max_L, total_L, out, lse_out):
-    B, W, Hq, d = q.shape
-    Hkv = k_shared.shape[1]
-    ND = k_unshared.shape[2]
-    p = _AttnParams()
-    p.B, p.W, p.Hq, p.Hkv, p.d, p.ND, p.u = B, W, Hq, Hkv, d, ND, int(u)
-    p.max_L, p.total_L, p.sm_scale = int(max_L), int(total_L), float(sm_scale)
-    p.q, p.k_shared, p.v_shared = q.data_ptr(), k_shared.data_ptr(), v_shared.data_ptr()
-    p.cu_seqlens, p.k_unshared, p.v_unshared = cu_seqlens.data_ptr(), k_unshared.data_ptr(), v_unshared.data_ptr()
-    p.out = out.data_ptr() if out is not None else None
-    p.lse_out = lse_out.data_ptr() if lse_out is not None else None
-    return p
 
 
 def attn_workspace_bytes(B, W, Hq, Hkv, d, max_L, total_L=None) -> int:
@@ -169,35 +179,23 @@ def gr_beam_attn(q, k_shared, v_shared, cu_seqlens, k_unshared, v_unshared, u, s
     k/v_unshared [B,W,ND,Hkv,d]; cu_seqlens int32 [B+1].  max_L / total_L are host integers.
     `slot` (int32 [B,W,ND], optional) routes the call to gr_beam_attn_slots: the own-token rows are read through it.
     Returns (out bf16 [B,W,Hq,d], lse fp32 [B,W,Hq] or None).  Enqueues on `stream` (default: current)."""
-    import torch
-    lib = load_library()
-    B, W, Hq, d = q.shape
-    _check(q, torch.bfloat16, None, "q")
-    _check(k_shared, torch.bfloat16, (k_shared.shape[0], k_shared.shape[1], d), "k_shared")
-    _check(v_shared, torch.bfloat16, tuple(k_shared.shape), "v_shared")
-    _check(cu_seqlens, torch.int32, (B + 1,), "cu_seqlens")
-    _check(k_unshared, torch.bfloat16, (B, W, k_unshared.shape[2], k_shared.shape[1], d), "k_unshared")
-    _check(v_unshared, torch.bfloat16, tuple(k_unshared.shape), "v_unshared")
-    if k_shared.shape[0] < int(total_L):
-        raise ValueError("k_shared has fewer rows than total_L")
-    if out is None:
-        out = torch.empty_like(q)
-    _check(out, torch.bfloat16, tuple(q.shape), "out")
-    if lse_out is not None:
-        _check(lse_out, torch.float32, (B, W, Hq), "lse_out")
-    p = _attn_params(q, k_shared, v_shared, cu_seqlens, k_unshared, v_unshared, u, sm_scale, max_L, total_L, out, lse_out)
-    need = int(lib.gr_beam_attn_workspace_bytes(ctypes.byref(p)))
-    if workspace is None and need > 0:
-        workspace = _scratch(need, q.device, stream)
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    if slot is not None:
-        _check(slot, torch.int32, (B, W, k_unshared.shape[2]), "slot")
-        rc = lib.gr_beam_attn_slots(ctypes.byref(p), _ptr(slot), _ptr(workspace), ws_bytes, _stream(stream))
-    else:
-        rc = lib.gr_beam_attn(ctypes.byref(p), _ptr(workspace), ws_bytes, _stream(stream))
-    if rc != 0:
-        raise GrError(rc, "gr_beam_attn_slots" if slot is not None else "gr_beam_attn")
+    out = _attn(q, k_shared, v_shared, cu_seqlens, k_unshared, v_unshared, slot, u, sm_scale, max_L, total_L, out, lse_out, workspace, stream,
+                False, 1.0, 1.0, "gr_beam_attn" if slot is None else "gr_beam_attn_slots")
     return out, lse_out
+
+
+def _attn(q, k, v, cu_seqlens, k_unshared, v_unshared, slot, u, sm_scale, max_L, total_L, out, lse_out, workspace, stream, fp8, k_scale, v_scale, name):
+    native = _native or _marshal()
+    if out is None:
+        import torch
+        out = torch.empty_like(q)
+    rc = native.attn(q, k, v, cu_seqlens, k_unshared, v_unshared, slot, u, sm_scale, max_L, total_L, out, lse_out, workspace, stream, fp8, k_scale, v_scale)
+    if rc > 0:                                   # no workspace was given: so many bytes are needed
+        workspace = _scratch(rc, q.device, stream)
+        rc = native.attn(q, k, v, cu_seqlens, k_unshared, v_unshared, slot, u, sm_scale, max_L, total_L, out, lse_out, workspace, stream, fp8, k_scale, v_scale)
+    if rc != 0:
+        raise GrError(rc, name)
+    return out
 
 
 def gr_beam_attn_slots(q, k_shared, v_shared, cu_seqlens, k_unshared, v_unshared, slot, u, sm_scale, max_L, total_L,
@@ -213,56 +211,19 @@ def gr_beam_attn_fp8kv(q, k_shared_fp8, v_shared_fp8, k_scale, v_scale, cu_seqle
                        out=None, lse_out=None, workspace=None, stream=None):
     """gr_beam_attn over a prompt cache stored as FP8 E4M3 codes: k/v_shared_fp8 uint8 CUDA tensors [total_L,Hkv,d],
     value = code * scale.  Everything else as for gr_beam_attn."""
-    import torch
-    lib = load_library()
-    B, W, Hq, d = q.shape
-    _check(q, torch.bfloat16, None, "q")
-    _check(k_shared_fp8, torch.uint8, (k_shared_fp8.shape[0], k_shared_fp8.shape[1], d), "k_shared_fp8")
-    _check(v_shared_fp8, torch.uint8, tuple(k_shared_fp8.shape), "v_shared_fp8")
-    _check(cu_seqlens, torch.int32, (B + 1,), "cu_seqlens")
-    _check(k_unshared, torch.bfloat16, (B, W, k_unshared.shape[2], k_shared_fp8.shape[1], d), "k_unshared")
-    _check(v_unshared, torch.bfloat16, tuple(k_unshared.shape), "v_unshared")
-    if k_shared_fp8.shape[0] < int(total_L):
-        raise ValueError("k_shared_fp8 has fewer rows than total_L")
-    if out is None:
-        out = torch.empty_like(q)
-    _check(out, torch.bfloat16, tuple(q.shape), "out")
-    if lse_out is not None:
-        _check(lse_out, torch.float32, (B, W, Hq), "lse_out")
-    p = _AttnFp8Params(_attn_params(q, k_shared_fp8, v_shared_fp8, cu_seqlens, k_unshared, v_unshared, u, sm_scale, max_L, total_L, out, lse_out),
-                       float(k_scale), float(v_scale))
-    need = int(lib.gr_beam_attn_workspace_bytes(ctypes.byref(p.attn)))
-    if workspace is None and need > 0:
-        workspace = _scratch(need, q.device, stream)
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    rc = lib.gr_beam_attn_fp8kv(ctypes.byref(p), _ptr(workspace), ws_bytes, _stream(stream))
-    if rc != 0:
-        raise GrError(rc, "gr_beam_attn_fp8kv")
+    out = _attn(q, k_shared_fp8, v_shared_fp8, cu_seqlens, k_unshared, v_unshared, None, u, sm_scale, max_L, total_L, out, lse_out, workspace, stream,
+                True, k_scale, v_scale, "gr_beam_attn_fp8kv")
     return out, lse_out
 
 
 def gr_prefill_attn(q, k, v, cu_seqlens, sm_scale, max_L, total_L, out=None, lse_out=None, stream=None):
     """Causal self-attention over packed prompts.  bf16 CUDA tensors: q [total_L,Hq,d], k/v [total_L,Hkv,d];
     cu_seqlens int32 [B+1].  max_L / total_L are host integers.  Returns (out bf16 [total_L,Hq,d], lse or None)."""
-    import torch
-    lib = load_library()
-    T, Hq, d = q.shape
-    Hkv = k.shape[1]
-    B = cu_seqlens.shape[0] - 1
-    _check(q, torch.bfloat16, None, "q")
-    _check(k, torch.bfloat16, (T, Hkv, d), "k")
-    _check(v, torch.bfloat16, (T, Hkv, d), "v")
-    _check(cu_seqlens, torch.int32, (B + 1,), "cu_seqlens")
-    if T < int(total_L):
-        raise ValueError("q has fewer rows than total_L")
+    native = _native or _marshal()
     if out is None:
+        import torch
         out = torch.empty_like(q)
-    _check(out, torch.bfloat16, tuple(q.shape), "out")
-    if lse_out is not None:
-        _check(lse_out, torch.float32, (T, Hq), "lse_out")
-    p = _PrefillParams(B, Hq, Hkv, d, int(max_L), int(total_L), float(sm_scale), q.data_ptr(), k.data_ptr(), v.data_ptr(),
-                       cu_seqlens.data_ptr(), out.data_ptr(), lse_out.data_ptr() if lse_out is not None else None)
-    rc = lib.gr_prefill_attn(ctypes.byref(p), _stream(stream))
+    rc = native.prefill(q, k, v, cu_seqlens, sm_scale, max_L, total_L, out, lse_out, stream)
     if rc != 0:
         raise GrError(rc, "gr_prefill_attn")
     return out, lse_out
@@ -299,44 +260,36 @@ def _scratch(nbytes, device, stream):
         return torch.empty(nbytes, dtype=torch.uint8, device=device)
 
 
-def _select_call(mask, logits, scores_in, prefix_in, range_in, step, flags, out, allocate_outputs):
-    import torch
-    B, W, V = logits.shape
-    depth = prefix_in.shape[2]
-    _check(logits, torch.float32, None, "logits")
-    _check(scores_in, torch.float32, (B, W), "scores_in")
-    _check(prefix_in, torch.int32, (B, W, depth), "prefix_in")
-    _check(range_in, torch.int32, (B, W, 2), "range_in")
-    dev = logits.device
+_SELECT_OUT = ("parent", "token", "scores", "prefix", "range", "item_index")
+
+
+def _select_outputs(out, logits, depth, allocate):
+    """The output dict, complete: what is missing is allocated, or an error for a call that allocates nothing."""
     if out is None:
         out = {}
-    spec = dict(parent=((B, W), torch.int32), token=((B, W), torch.int32), scores=((B, W), torch.float32),
-                prefix=((B, W, depth), torch.int32), range=((B, W, 2), torch.int32), item_index=((B, W), torch.int32))
-    for k, (shape, dt) in spec.items():
-        if k not in out or out[k] is None:
-            if not allocate_outputs:
-                raise ValueError(f"out[{k!r}] must be preallocated for a call that allocates nothing")
-            out[k] = torch.empty(shape, dtype=dt, device=dev)
-        _check(out[k], dt, shape, k)
-    p = _SelectParams()
-    p.B, p.W, p.V, p.depth, p.step, p.flags = B, W, V, depth, int(step), int(flags)
-    p.mask = mask.data_ptr() if mask is not None else None
-    p.logits, p.scores_in = logits.data_ptr(), scores_in.data_ptr()
-    p.prefix_in, p.range_in = prefix_in.data_ptr(), range_in.data_ptr()
-    p.parent_out, p.token_out, p.scores_out = out["parent"].data_ptr(), out["token"].data_ptr(), out["scores"].data_ptr()
-    p.prefix_out, p.range_out, p.item_index_out = out["prefix"].data_ptr(), out["range"].data_ptr(), out["item_index"].data_ptr()
-    return p, out
+    if any(out.get(k) is None for k in _SELECT_OUT):
+        import torch
+        B, W, _ = logits.shape
+        shapes = dict(prefix=(B, W, depth), range=(B, W, 2))
+        for k in _SELECT_OUT:
+            if out.get(k) is None:
+                if not allocate:
+                    raise ValueError(f"out[{k!r}] must be preallocated for a call that allocates nothing")
+                out[k] = torch.empty(shapes.get(k, (B, W)), dtype=torch.float32 if k == "scores" else torch.int32, device=logits.device)
+    return out
 
 
 def gr_beam_select(mask, logits, scores_in, prefix_in, range_in, step, flags=0, out=None, workspace=None, stream=None):
     """Beam item step.  logits fp32 [B,W,V]; scores_in fp32 [B,W]; prefix_in int32 [B,W,depth]; range_in int32
     [B,W,2]; mask = blob from gr_item_mask_build or None.  `out` may hold preallocated tensors under the keys
     parent, token, scores, prefix, range, item_index.  Returns that dict.  Enqueues on `stream`."""
-    lib = load_library()
-    p, out = _select_call(mask, logits, scores_in, prefix_in, range_in, step, flags, out, True)
-    if workspace is None:
-        workspace = _scratch(int(lib.gr_beam_select_workspace_bytes(p.B, p.W, p.V, p.depth)), logits.device, stream)
-    rc = lib.gr_beam_select(ctypes.byref(p), _ptr(workspace), workspace.numel() * workspace.element_size(), _stream(stream))
+    native = _native or _marshal()
+    out = _select_outputs(out, logits, prefix_in.shape[2], True)
+    res = (out["parent"], out["token"], out["scores"], out["prefix"], out["range"], out["item_index"])
+    rc = native.select(mask, logits, scores_in, prefix_in, range_in, step, flags, *res, workspace, False, stream)
+    if workspace is None and rc >= 0:            # so many bytes are needed
+        workspace = _scratch(rc, logits.device, stream)
+        rc = native.select(mask, logits, scores_in, prefix_in, range_in, step, flags, *res, workspace, False, stream)
     if rc != 0:
         raise GrError(rc, "gr_beam_select")
     return out
@@ -345,9 +298,10 @@ def gr_beam_select(mask, logits, scores_in, prefix_in, range_in, step, flags=0, 
 def gr_beam_select_noalloc(mask, logits, scores_in, prefix_in, range_in, step, out, flags=0, stream=None):
     """The same item step through the entry point that allocates nothing: the workspace is a static device array inside
     the library and every output tensor must be passed in `out`.  Calls that overlap on one GPU race."""
-    lib = load_library()
-    p, out = _select_call(mask, logits, scores_in, prefix_in, range_in, step, flags, out, False)
-    rc = lib.gr_beam_select_noalloc(ctypes.byref(p), _stream(stream))
+    native = _native or _marshal()
+    out = _select_outputs(out, logits, prefix_in.shape[2], False)
+    rc = native.select(mask, logits, scores_in, prefix_in, range_in, step, flags, out["parent"], out["token"], out["scores"], out["prefix"],
+                       out["range"], out["item_index"], None, True, stream)
     if rc != 0:
         raise GrError(rc, "gr_beam_select_noalloc")
     return out
@@ -356,13 +310,7 @@ def gr_beam_select_noalloc(mask, logits, scores_in, prefix_in, range_in, step, o
 def gr_beam_reorder(parent, k_unshared, v_unshared, u, stream=None):
     """Move every surviving beam's own KV cache to its new slot, in place.  parent int32 [B,W] (from
     gr_beam_select); k/v_unshared bf16 [B,W,ND,Hkv,d]; token slots [0,u) move.  Enqueues on `stream`."""
-    import torch
-    lib = load_library()
-    B, W, ND, Hkv, d = k_unshared.shape
-    _check(parent, torch.int32, (B, W), "parent")
-    _check(k_unshared, torch.bfloat16, None, "k_unshared")
-    _check(v_unshared, torch.bfloat16, tuple(k_unshared.shape), "v_unshared")
-    rc = lib.gr_beam_reorder(B, W, ND, Hkv, d, int(u), _ptr(parent), _ptr(k_unshared), _ptr(v_unshared), _stream(stream))
+    rc = (_native or _marshal()).reorder(parent, k_unshared, v_unshared, u, stream)
     if rc != 0:
         raise GrError(rc, "gr_beam_reorder")
 
@@ -370,16 +318,12 @@ def gr_beam_reorder(parent, k_unshared, v_unshared, u, stream=None):
 def gr_beam_slot_update(parent, slot_in, u, ND, out=None, stream=None):
     """The slot table after a beam step (nothing in the caches moves): out[b,j,t] = slot_in[b,parent[b,j],t] for t < u,
     j*ND + t otherwise.  parent int32 [B,W]; slot_in int32 [B,W,ND] or None (identity).  Returns out int32 [B,W,ND]."""
-    import torch
-    lib = load_library()
-    B, W = parent.shape
-    _check(parent, torch.int32, (B, W), "parent")
-    if slot_in is not None:
-        _check(slot_in, torch.int32, (B, W, int(ND)), "slot_in")
+    native = _native or _marshal()
     if out is None:
+        import torch
+        B, W = parent.shape
         out = _scratch(B * W * int(ND) * 4, parent.device, stream).view(torch.int32).view(B, W, int(ND))
-    _check(out, torch.int32, (B, W, int(ND)), "out")
-    rc = lib.gr_beam_slot_update(B, W, int(ND), int(u), _ptr(parent), _ptr(slot_in), _ptr(out), _stream(stream))
+    rc = native.slot_update(parent, slot_in, u, ND, out, stream)
     if rc != 0:
         raise GrError(rc, "gr_beam_slot_update")
     return out

@@ -1046,10 +1046,10 @@ gr_status attn_run(const gr_attn_params* p, const int32_t* slot, bool kv8, float
 #define GR_LAUNCH_ATTN(DD, NCB_, NW_)                                                                                        \
   do {                                                                                                                       \
     if (kv8) {                                                                                                               \
-      GR_HIP_TRY(hipFuncSetAttribute((const void*)k_beam_attn<DD, NCB_, NW_, false, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)); \
+      if (const gr_status st = gr_allow_lds<k_beam_attn<DD, NCB_, NW_, false, true>>(lds)) return st; \
       hipLaunchKernelGGL((k_beam_attn<DD, NCB_, NW_, false, true>), dim3((unsigned)grid), dim3(NW_ * 64), lds, stream, c);   \
     } else {                                                                                                                 \
-      GR_HIP_TRY(hipFuncSetAttribute((const void*)k_beam_attn<DD, NCB_, NW_, false, false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)); \
+      if (const gr_status st = gr_allow_lds<k_beam_attn<DD, NCB_, NW_, false, false>>(lds)) return st; \
       hipLaunchKernelGGL((k_beam_attn<DD, NCB_, NW_, false, false>), dim3((unsigned)grid), dim3(NW_ * 64), lds, stream, c);  \
     }                                                                                                                        \
   } while (0)
@@ -1127,7 +1127,7 @@ extern "C" gr_status gr_prefill_attn(const gr_prefill_params* p, void* stream_) 
   const size_t lds = attn_lds_bytes(p->d, mwg);
 #define GR_LAUNCH_PREFILL(DD, NW_)                                                                                              \
   do {                                                                                                                         \
-    GR_HIP_TRY(hipFuncSetAttribute((const void*)k_beam_attn<DD, 1, NW_, true, false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)); \
+    if (const gr_status st = gr_allow_lds<k_beam_attn<DD, 1, NW_, true, false>>(lds)) return st; \
     hipLaunchKernelGGL((k_beam_attn<DD, 1, NW_, true, false>), dim3((unsigned)grid), dim3(NW_ * 64), lds, stream, c);          \
   } while (0)
   if (p->d == 128) {

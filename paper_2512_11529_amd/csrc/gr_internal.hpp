@@ -2,6 +2,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <atomic>
 #include "gr.h"
 
 #define GR_HIP_TRY(expr)                          \
@@ -9,6 +10,20 @@
     hipError_t e_ = (expr);                       \
     if (e_ != hipSuccess) return GR_ERR_HIP;      \
   } while (0)
+
+// More than 64 KB of dynamic LDS must be opted into, per kernel and device.  Every call of a kernel asks for the same number of bytes,
+// so it is done when a device first runs it (asking costs the host about as much as a third of a launch).
+template <auto KERNEL>
+static inline gr_status gr_allow_lds(size_t bytes) {
+  static std::atomic<uint64_t> done{0};      // bit per device
+  int dev = -1;
+  GR_HIP_TRY(hipGetDevice(&dev));
+  const uint64_t bit = (dev >= 0 && dev < 64) ? (uint64_t)1 << dev : 0;
+  if (bit && (done.load(std::memory_order_relaxed) & bit)) return GR_OK;
+  GR_HIP_TRY(hipFuncSetAttribute((const void*)KERNEL, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
+  done.fetch_or(bit, std::memory_order_relaxed);
+  return GR_OK;
+}
 
 static inline size_t gr_align256(size_t n) { return (n + 255) & ~(size_t)255; }
 

@@ -1316,8 +1316,7 @@ extern "C" gr_status gr_beam_select(const gr_select_params* p, void* workspace, 
     hipLaunchKernelGGL((k_rows<true, 512>), dim3((unsigned)(rows < kStrideGrid ? rows : kStrideGrid)), dim3(512), 0, stream, c);
   else
     hipLaunchKernelGGL((k_rows<false, 256>), dim3((unsigned)rows), dim3(256), 0, stream, c);
-  // more than 64 KB of LDS must be opted into (per device; cheap, so done on every call)
-  GR_HIP_TRY(hipFuncSetAttribute((const void*)k_select, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kSelLdsBytes));
+  if (const gr_status st = gr_allow_lds<k_select>(kSelLdsBytes)) return st;
   hipLaunchKernelGGL(k_select, dim3(p->B), dim3(kSelThreads), kSelLdsBytes, stream, c);
   GR_HIP_TRY(hipGetLastError());
   return GR_OK;
