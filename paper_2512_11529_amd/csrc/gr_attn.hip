@@ -1111,7 +1111,12 @@ extern "C" gr_status gr_prefill_attn(const gr_prefill_params* p, void* stream_) 
   AttnCtx c;
   c.B = p->B; c.W = 0; c.Hq = p->Hq; c.Hkv = p->Hkv; c.g = g; c.ND = 0; c.u = 0;
   c.M = p->max_L * g;                                        // the longest request's rows size the grid
-  const int mwg = c.M <= 128 ? 128 : 256;
+  // 128 rows, two workgroups to a CU: one computes while the other waits for its queries or stores its output, which is most of
+  // the life of a block of a short prompt.  256 rows stage every K/V tile half as often, which only counts for long prompts of
+  // head size 128.  us with 256 and 128 rows (32 query and 8 KV heads of 128 unless noted): 1 x 1024 tokens 28.7, 21.8; 16 prompts of
+  // 62-512 38.2, 33.9; 64 x 512 249, 240; 64 x 2048 2283, 2232; but 1 x 4096 128, 138 and 8 of 1024-8192 1674, 1700; 4 x 2048 141, 146
+  // is the worst on this side of the line.  8 heads of 64: 1 x 4096 71, 50; 16 x 4096 383, 344.
+  const int mwg = p->d == 64 || p->max_L <= 2048 || c.M <= 128 ? 128 : 256;
   c.MB = (c.M + mwg - 1) / mwg;
   c.nsplit = 1;
   c.n_groups = p->B * p->Hkv;
@@ -1133,7 +1138,7 @@ extern "C" gr_status gr_prefill_attn(const gr_prefill_params* p, void* stream_) 
   if (p->d == 128) {
     if (mwg == 256) GR_LAUNCH_PREFILL(128, 8); else GR_LAUNCH_PREFILL(128, 4);
   } else {
-    if (mwg == 256) GR_LAUNCH_PREFILL(64, 8); else GR_LAUNCH_PREFILL(64, 4);
+    GR_LAUNCH_PREFILL(64, 4);
   }
 #undef GR_LAUNCH_PREFILL
   GR_HIP_TRY(hipGetLastError());

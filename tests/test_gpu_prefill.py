@@ -54,6 +54,29 @@ def test_prefill_matches_oracle(oracle_lib, lens, Hq, Hkv, d):
     np.testing.assert_allclose(lse[:T], ref_lse, rtol=0, atol=2e-3)
 
 
+@pytest.mark.parametrize("max_L", [2048, 2049])        # head size 128: workgroups of 128 and of 256 query rows
+@pytest.mark.parametrize("lens,Hq,Hkv", [
+    ((1, 31, 33, 63, 65), 32, 8),          # g = 4: 32 and 64 tokens per row block
+    ((257, 128, 129, 2), 4, 4),            # g = 1: row blocks of 128 and 256 tokens
+    ((43, 86, 90), 6, 2),                  # g = 3: a token's heads lie in two row blocks
+])
+def test_prefill_row_blocks_of_both_sizes(oracle_lib, lens, Hq, Hkv, max_L):
+    """max_L is a bound that the longest prompt need not reach; it decides the size of a row block."""
+    import paper_2512_11529_amd as gr
+    import torch
+    gr.load_library()
+    d = 128
+    c = _case(sum(lens), lens, Hq, Hkv, d)
+    scale = float(np.float32(1 / np.sqrt(d)))
+    T = int(c["cu"][-1])
+    lse = torch.empty((T, Hq), dtype=torch.float32, device="cuda:0")
+    out, _ = gr.gr_prefill_attn(bf16_to_dev(c["q"]), bf16_to_dev(c["k"]), bf16_to_dev(c["v"]), to_dev(c["cu"]), scale, max_L, T, lse_out=lse)
+    torch.cuda.synchronize()
+    ref, ref_lse = oracle_lib.prefill_attn_causal(c["q"], c["k"], c["v"], c["cu"], scale)
+    assert np.abs(out.float().cpu().numpy() - ref.reshape(T, Hq, d)).max() <= 2e-2
+    np.testing.assert_allclose(lse.cpu().numpy(), ref_lse.reshape(T, Hq), rtol=0, atol=2e-3)
+
+
 def test_prefill_long_prompt_sampled_rows(oracle_lib):
     """L = 4096 at the benchmark's head geometry: 16 row blocks per KV head, up to 64 tiles per block.  Rows checked:
     the first and last token of every 64-token block (diagonal tiles, block edges) and a seeded sample, every head."""
