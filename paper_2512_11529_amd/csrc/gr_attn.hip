@@ -25,6 +25,23 @@ typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int KT = 64;        // kv tokens per LDS tile
+
+// Dynamic LDS of k_beam_attn: K and V tiles, double-buffered (unpadded); the Q hand-over (unpadded, swizzled), behind the tiles
+// for workgroups of 8 wavefronts and on top of them for those of 4; one padded 32-row K and V mini-tile per wave for the own-token
+// stage and the padded output staging (on top of everything else, after the prompt loop).  Behind all of it 256 bytes per wave
+// that loads issued only to bring lines into L2 write to.
+// Workgroups whose two halves share the prompt (ks = 2): tiles of the first half, Q, tiles of the second half.  The last 2 KiB
+// of Q's place take those 256 bytes per wave, then the second half's (maximum, sum).
+constexpr int attn_tiles_bytes(int d) { return 4 * KT * d * 2; }
+constexpr int attn_lds_used(int d, int mwg) {
+  const int tiles = attn_tiles_bytes(d), rows = mwg * d * 2;
+  const int main_loop = mwg == 256 ? tiles + rows : (tiles > rows ? tiles : rows);
+  const int own = mwg * ((d + 8) + (d + 32)) * 2;
+  return main_loop > own ? main_loop : own;
+}
+constexpr int attn_lds_bytes(int d, int mwg, int ks) {
+  return ks == 2 ? 2 * attn_tiles_bytes(d) + mwg * d * 2 : attn_lds_used(d, mwg) + mwg / 32 * 256;
+}
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 
@@ -306,11 +323,16 @@ struct AttnTile {
 // a ds_write into the same swizzled layout the direct loads fill.  The scales never touch the tiles: the K scale goes into
 // the exponent scale of the prompt loop, and at the end of the loop the running maximum (x k_scale) and O (x v_scale) are
 // put into true units, which is where the bf16 own-token stage and the epilogue work.
-template <int D, int NCB, int NWAVES, bool CAUSAL, bool KV8>
-__global__ void __launch_bounds__(NWAVES * 64) __attribute__((amdgpu_waves_per_eu(NCB == 1 ? 2 : 1, NCB == 1 ? 2 : 1)))
+// KS = 2: two sets of NWAVES wavefronts hold the same query rows and take one half of the segment's tiles each, with tiles
+// of their own in LDS; the second set's (maximum, sum, O) goes through LDS into the first's before the epilogue.  For launches of at
+// most one 128-row workgroup per CU, whose SIMDs would otherwise hold one wavefront each and wait out every chain of its tile
+// (1.1 us a tile and wavefront, 0.9 with a second one beside it).
+template <int D, int NCB, int NWAVES, bool CAUSAL, bool KV8, int KS>
+__global__ void __launch_bounds__(NWAVES * 64 * KS) __attribute__((amdgpu_waves_per_eu(NCB == 1 ? 2 : 1, NCB == 1 ? 2 : 1)))
 k_beam_attn(AttnCtx c) {
   using T = AttnTile<D, NCB>;
-  constexpr int NT = NWAVES * 64;
+  constexpr int NT = NWAVES * 64;                // threads of a set
+  static_assert(KS == 1 || (KS == 2 && NWAVES == 4 && !CAUSAL), "two sets of four wavefronts");
   constexpr int MWG = NWAVES * 32 * NCB;
   constexpr int KSTR = T::KSTR, VSTR = T::VSTR;
   constexpr int PPR = D / 8;                     // 16-byte pieces per row
@@ -323,12 +345,14 @@ k_beam_attn(AttnCtx c) {
   // tile is in slot 0: the main loop then names its slots at compile time); then (8-wave workgroups only: they own the CU's LDS
   // anyway) a separate region for the Q hand-over, so that the first tiles can be in flight while Q is staged
   extern __shared__ __attribute__((aligned(1024))) uint16_t smem[];
-  uint16_t* s_k = smem;
-  uint16_t* s_v = smem + 2 * TILE;
-  constexpr bool kQSeparate = NWAVES == 8;
+  const int set = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x / NT);
+  uint16_t* s_tiles = smem + (KS == 1 ? 0 : set * (4 * TILE + MWG * D));
+  uint16_t* s_k = s_tiles;
+  uint16_t* s_v = s_tiles + 2 * TILE;
+  constexpr bool kQSeparate = NWAVES * KS == 8;
   uint16_t* s_q = kQSeparate ? smem + 4 * TILE : smem;
 
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, G = lane >> 5, n32 = lane & 31;
+  const int tid = (int)threadIdx.x % NT, wave = tid >> 6, lane = tid & 63, G = lane >> 5, n32 = lane & 31;
 
   // XCD-aware unit order: workgroups are dealt round-robin to the 8 XCDs, so ids congruent mod 8
   // share an L2.  The MB row blocks that read the same K/V stream get consecutive slots of one XCD.
@@ -352,23 +376,31 @@ k_beam_attn(AttnCtx c) {
   if (CAUSAL && mbi * (NWAVES * 32 * NCB) >= Mb) return;       // (before any barrier: the whole workgroup leaves)
   int chunk = (int)(((unsigned)Lb + (unsigned)c.nsplit - 1u) / (unsigned)c.nsplit);
   chunk = ((chunk + KT - 1) / KT) * KT;
-  const int seg0 = CAUSAL ? 0 : min(Lb, sp * chunk);
-  const int seg1 = CAUSAL ? (min((mbi + 1) * (NWAVES * 32 * NCB), Mb) - 1) / c.g + 1 : min(Lb, seg0 + chunk);
-  const int ntiles = (seg1 - seg0 + KT - 1) / KT, flip = (ntiles - 1) & 1;
+  int seg0 = CAUSAL ? 0 : min(Lb, sp * chunk);
+  int seg1 = CAUSAL ? (min((mbi + 1) * (NWAVES * 32 * NCB), Mb) - 1) / c.g + 1 : min(Lb, seg0 + chunk);
+  int ntiles = (seg1 - seg0 + KT - 1) / KT, set1_idle = 0;     // set1_idle: barriers that the second set waits at beside its own
+  if (KS == 2) {                                               // the first set takes the odd tile
+    const int n0 = (ntiles + 1) / 2, n1 = ntiles - n0;
+    set1_idle = (n0 > 0 ? n0 + 1 : 0) - (n1 > 0 ? n1 + 1 : 0);
+    const int mid = min(seg1, seg0 + n0 * KT);
+    if (set == 0) seg1 = mid; else seg0 = mid;
+    ntiles = set == 0 ? n0 : n1;
+  }
+  const int flip = (ntiles - 1) & 1;
 
   // ---- Q: the workgroup's MWG query rows are fetched with coalesced 16-byte pieces (a row = PPR
   // consecutive lanes) and handed to the lanes that own them through LDS.  A lane reading its own
   // row straight from global memory touches 32 different rows per load instruction, which keeps the
   // address unit busy for microseconds while the CU has nothing else to do.
   static_assert(NCB == 1, "one column block per wave");
-  constexpr int QP = MWG * PPR / NT;             // 16-byte pieces of Q per thread
+  constexpr int QP = MWG * PPR / (NT * KS);      // 16-byte pieces of Q per thread
   const float rcp_g = 1.0f / (float)c.g;
   // this request's queries (decode: its W beams; prefill: its own tokens); offsets inside it fit 32 bits
   const uint16_t* q_b = c.q + (CAUSAL ? (size_t)row0 : (size_t)b * c.W) * c.Hq * D;
   uint4 qpiece[QP];
 #pragma unroll
   for (int i = 0; i < QP; i++) {
-    const int p = tid + i * NT, rl = p / PPR, col = (p % PPR) * 8;
+    const int p = (int)threadIdx.x + i * (NT * KS), rl = p / PPR, col = (p % PPR) * 8;
     const int r = mbi * MWG + rl;
     int w, j;
     divmod_small(r, c.g, rcp_g, &w, &j);
@@ -408,7 +440,7 @@ k_beam_attn(AttnCtx c) {
   const char* kbase = (const char*)c.ks + ((size_t)row0 * c.Hkv + kvh) * D * EB;
   const char* vbase = (const char*)c.vs + ((size_t)row0 * c.Hkv + kvh) * D * EB;
   const float cp = KV8 ? c.c * c.k_scale : c.c;              // exponent scale of the prompt loop
-  const typename T::Rd rdo = T::make_rd(lane, (int)(uintptr_t)(__attribute__((address_space(3))) uint16_t*)smem);
+  const typename T::Rd rdo = T::make_rd(lane, (int)(uintptr_t)(__attribute__((address_space(3))) uint16_t*)s_tiles);
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);
   int crow[CPW];                                             // this lane's row inside a tile, per chunk
   uint32_t koff[CPW], voff[CPW];                             // and its byte offsets from the tile's first row (full tiles)
@@ -441,7 +473,8 @@ k_beam_attn(AttnCtx c) {
       }
     }
   };
-  auto tiles_landed = [&]() { if (!KV8) __builtin_amdgcn_s_waitcnt(0x0F70); };     // vmcnt(0)
+  auto all_landed = [&]() { __builtin_amdgcn_s_waitcnt(0x0F70); };                 // vmcnt(0)
+  auto tiles_landed = [&]() { if (!KV8) all_landed(); };
   // FP8 tiles: piece p = tid + i * NT of a tile = 8 codes of row p / PPR; registers one tile ahead
   constexpr int P8 = KT * PPR / NT;                          // pieces per thread and tile
   struct Stage8 { uint2 r[P8]; };
@@ -493,7 +526,7 @@ k_beam_attn(AttnCtx c) {
   static_assert(NCB == 1, "one column block per wave");
   constexpr int UR = 32;                                 // rows of a mini-tile
   constexpr int UP = UR * PPR / 64;                      // 16-byte pieces per lane and tensor
-  const bool own_stage = !CAUSAL && sp == 0 && c.u > 0;
+  const bool own_stage = !CAUSAL && set == 0 && sp == 0 && c.u > 0;
   auto wave_rows = [&](int wv, int* first_beam) {        // rows of wave wv's mini-tiles, and its first beam
     const int r_first = mbi * MWG + wv * 32;
     if (r_first >= Mb) { *first_beam = 0; return 0; }
@@ -512,29 +545,47 @@ k_beam_attn(AttnCtx c) {
   const int my_lo = (qrow[0] >= 0) ? (qrow[0] / c.g - beam0) * c.u : -1;         // this column's rows [my_lo, my_lo + u)
   uint4 ukp[UP], uvp[UP];
   const float rcp_u = 1.0f / (float)max(c.u, 1);
-  auto uload = [&](int pass) {                           // 32 rows x D/8 pieces per tensor; a row = PPR consecutive lanes
-    const uint16_t* ku_b = c.ku + (size_t)b * c.W * c.ND * c.Hkv * D;      // this request's own-token caches
-    const uint16_t* vu_b = c.vu + (size_t)b * c.W * c.ND * c.Hkv * D;
-    const int32_t* slot_b = c.slot ? c.slot + (size_t)b * c.W * c.ND : nullptr;
+  // Row of the request's own-token block behind row pass * 32 + lane % 32 of the mini-tiles (past the last one: the first's)
+  auto own_row = [&](int pass) {
+    const int rho = pass * UR + n32;
+    int bl, tok;
+    divmod_small(rho < R ? rho : 0, c.u, rcp_u, &bl, &tok);
+    int prow = (beam0 + bl) * c.ND + tok;
+    if (c.slot && R > 0) {                                 // (an entry outside the block falls back to the beam's own row)
+      const int sl = c.slot[(size_t)b * c.W * c.ND + prow];
+      prow = ((unsigned)sl < (unsigned)(c.W * c.ND)) ? sl : prow;
+    }
+    return prow;
+  };
+  const uint16_t* ku_b = c.ku + (size_t)b * c.W * c.ND * c.Hkv * D;        // this request's own-token caches
+  const uint16_t* vu_b = c.vu + (size_t)b * c.W * c.ND * c.Hkv * D;
+  auto uload = [&](int pass, int prow_l) {               // 32 rows x D/8 pieces per tensor; a row = PPR consecutive lanes
 #pragma unroll
     for (int i = 0; i < UP; i++) {
       const int pi = lane + 64 * i, row = pi / PPR, col = (pi % PPR) * 8;
-      const int rho = pass * UR + row;
+      const int prow = __shfl(prow_l, row, 64);
       ukp[i] = make_uint4(0, 0, 0, 0);
       uvp[i] = make_uint4(0, 0, 0, 0);
-      if (rho < R) {
-        int bl, tok;
-        divmod_small(rho, c.u, rcp_u, &bl, &tok);
-        int prow = (beam0 + bl) * c.ND + tok;
-        if (slot_b) {                                      // (an entry outside the block falls back to the beam's own row)
-          const int sl = slot_b[prow];
-          prow = ((unsigned)sl < (unsigned)(c.W * c.ND)) ? sl : prow;
-        }
+      if (pass * UR + row < R) {
         const uint32_t off = (uint32_t)(prow * (c.Hkv * D) + kvh * D + col);
         ukp[i] = *(const uint4*)(ku_b + off);
         uvp[i] = *(const uint4*)(vu_b + off);
       }
     }
+  };
+
+  // The own-token rows are what the end of a unit waits for: they are asked for three tiles before the last one, one 4-byte load
+  // per 128-byte line into LDS that nobody reads, so that the loads into registers (which have no room earlier) find them in L2.
+  const uint32_t lds_dump = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint16_t*)smem +
+                            (KS == 2 ? attn_tiles_bytes(D) + MWG * D * 2 - 2048 + set * 1024 : attn_lds_used(D, MWG)) + (uint32_t)wave_u * 256;
+  auto touch = [&](const void* gbase, uint32_t off) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds_dump), "v"(off), "s"(gbase) : "memory", "m0");
+  };
+  const int touch_own = own_stage && R > 0 ? max(0, ntiles - 4) : 0x7fffffff;
+  auto touch_own_rows = [&](int prow) {
+    const uint32_t off = (uint32_t)(prow * (c.Hkv * D) + kvh * D) * 2 + (D == 128 ? 128 * G : 0);
+    touch(ku_b, off);
+    touch(vu_b, off);
   };
 
   // first prompt tiles: requested before anything waits on memory (when Q has its own LDS region)
@@ -545,17 +596,18 @@ k_beam_attn(AttnCtx c) {
     tload(true, flip, 0); tload(false, flip, 0);
     tload(true, flip ^ 1, min(1, ntiles - 1));
   }
+  int prow0 = own_stage ? own_row(0) : 0;
   // Q as B operands: lane holds query column n32 of the wave's block, d = 16*ks + 8*G + (0..7)
   bf16x8 qop[NCB][D / 16];
   {
 #pragma unroll
     for (int i = 0; i < QP; i++) {
-      const int p = tid + i * NT, rl = p / PPR, col = (p % PPR) * 8;
-      *(uint4*)(&s_q[rl * KSTR + col]) = qpiece[i];
+      const int p = (int)threadIdx.x + i * (NT * KS), rl = p / PPR, piece = p % PPR;
+      *(uint4*)(&s_q[rl * D + (piece ^ T::swz_k(rl)) * 8]) = qpiece[i];
     }
     __syncthreads();
 #pragma unroll
-    for (int ks = 0; ks < D / 16; ks++) qop[0][ks] = as_bf16x8(*(const uint4*)(&s_q[(wave * 32 + n32) * KSTR + ks * 16 + G * 8]));
+    for (int ks = 0; ks < D / 16; ks++) qop[0][ks] = as_bf16x8(*(const uint4*)(&s_q[(wave * 32 + n32) * D + ((2 * ks + G) ^ T::swz_k(n32)) * 8]));
     if (!kQSeparate) {
       __syncthreads();                               // the tile slots may now be overwritten
       if (!KV8 && ntiles > 0) {
@@ -577,6 +629,7 @@ k_beam_attn(AttnCtx c) {
     // last tile (harmless re-reads; a duplicate K tile lands in a buffer nobody reads any more).
     const int tl = ntiles - 1;
     tiles_landed();
+    asm volatile("" : "+v"(prow0));                    // (waited for here, not at its first use)
     __syncthreads();                                   // K(0), V(0), K(1) are in LDS
 
     auto rescale = [&](const float (&alpha)[NCB], const bool (&upd)[NCB]) {
@@ -629,12 +682,13 @@ k_beam_attn(AttnCtx c) {
         tload(true, slot, min(t + 2, tl));                          // K(t+2) over K(t)
         tload(false, slot ^ 1, min(t + 1, tl));                     // V(t+1) over V(t-1)
       }
+      if (t == touch_own) touch_own_rows(prow0);
       T::fused((slot ^ 1) * TILE, (2 + slot) * TILE, qop, s_in, s_out, o_acc, m_run[0] * cp, cp, l_run[0], mx_cur, rdo);
     };
     // the last tile of the segment: the only one that can be partial, and it has no successor
     auto last = [&](f32x16 (&s_in)[KT / 32][NCB], int t) {
-      tiles_landed();
-      if (own_stage) uload(0);
+      all_landed();
+      if (own_stage) uload(0, prow0);
       __syncthreads();
       const int tok0 = seg0 + t * KT;
       if (tok0 + KT > seg1) {
@@ -684,6 +738,9 @@ k_beam_attn(AttnCtx c) {
     }
   }
 
+  float* s_set1 = (float*)(smem + 4 * TILE + MWG * D);     // KS = 2: the second set's O (in place of its tiles), as its lanes hold it,
+  float* s_set1_ml = s_set1 - 512;                         // and its (maximum, sum) pairs
+
   // ---- unshared stage (segment 0): every beam's own u decode tokens, through the same MFMA path.
   // The 32 query columns of a wave belong to a handful of beams (32/g of them when g divides 32).
   // Their K rows (then V rows) are laid out as private 32-row mini-tiles, row rho = beam_local * u +
@@ -692,12 +749,26 @@ k_beam_attn(AttnCtx c) {
   // rows (the rest are masked to -inf), and O^T += V_u^T . P^T follows.  Compared with per-lane dot
   // products this reads each beam's rows once instead of once per query head and replaces ~1000
   // VALU operations per lane by 16 MFMAs per wave.
+  if (KS == 2) {
+    if (set == 1)
+      for (int i = 0; i < set1_idle; i++) __syncthreads();
+    __syncthreads();                                       // every wave is done with the prompt tiles
+    if (set == 1) {
+#pragma unroll
+      for (int e = 0; e < D / 8; e++) {
+        const f32x4 v = {o_acc[e / 4][0][4 * (e % 4)], o_acc[e / 4][0][4 * (e % 4) + 1], o_acc[e / 4][0][4 * (e % 4) + 2], o_acc[e / 4][0][4 * (e % 4) + 3]};
+        *(f32x4*)(s_set1 + ((wave * (D / 8) + e) * 64 + lane) * 4) = v;
+      }
+      const f32x2 ml = {m_run[0], l_run[0]};
+      *(f32x2*)(s_set1_ml + (wave * 64 + lane) * 2) = ml;
+    }
+  }
   if (own_stage) {
     float m = m_run[0], l = l_run[0];
-    __syncthreads();                                       // every wave is done with the prompt tiles
+    if (KS == 1) __syncthreads();                          // every wave is done with the prompt tiles
     uint16_t* s_uk = smem + wave * UR * KSTR;
     uint16_t* s_uv = smem + NWAVES * UR * KSTR + wave * UR * VSTR;
-    if (ntiles == 0) uload(0);
+    if (ntiles == 0) uload(0, prow0);
     for (int pass = 0; pass < npass; pass++) {
 #pragma unroll
       for (int i = 0; i < UP; i++) {
@@ -705,8 +776,8 @@ k_beam_attn(AttnCtx c) {
         *(uint4*)(&s_uk[row * KSTR + col]) = ukp[i];
         *(uint4*)(&s_uv[row * VSTR + col]) = uvp[i];
       }
-      if (pass + 1 < npass) uload(pass + 1);               // (arrives while this pass is computed)
-      __syncthreads();
+      if (pass + 1 < npass) uload(pass + 1, own_row(pass + 1));               // (arrives while this pass is computed)
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");                  // (the mini-tiles are this wave's alone, and LDS serves a wave in order)
       // scores of the 32 rows against the wave's 32 columns
       f32x16 su;
 #pragma unroll
@@ -761,9 +832,28 @@ k_beam_attn(AttnCtx c) {
             o_acc[db][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, both), pu[t], o_acc[db][0], 0, 0, 0);
           }
       }
-      if (pass + 1 < npass) __syncthreads();               // the mini-tiles are rewritten by the next pass
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");                  // the mini-tiles are rewritten by the next pass
     }
     m_run[0] = m; l_run[0] = l;
+  }
+
+  // ---- the second set's half of the segment joins the first's
+  if (KS == 2) {
+    __syncthreads();
+    if (set == 1) return;
+    const f32x2 ml = *(const f32x2*)(s_set1_ml + (wave * 64 + lane) * 2);
+    const float m_new = fmaxf(m_run[0], ml.x);
+    const bool any_key = m_new > -INFINITY;                // false only for a column that has seen no key at all
+    const float a0 = any_key ? __builtin_amdgcn_exp2f((m_run[0] - m_new) * c.c) : 1.f;
+    const float a1 = any_key ? __builtin_amdgcn_exp2f((ml.x - m_new) * c.c) : 0.f;
+    l_run[0] = l_run[0] * a0 + ml.y * a1;
+    m_run[0] = m_new;
+#pragma unroll
+    for (int e = 0; e < D / 8; e++) {
+      const f32x4 v = *(const f32x4*)(s_set1 + ((wave * (D / 8) + e) * 64 + lane) * 4);
+#pragma unroll
+      for (int k = 0; k < 4; k++) o_acc[e / 4][0][4 * (e % 4) + k] = o_acc[e / 4][0][4 * (e % 4) + k] * a0 + v[k] * a1;
+    }
   }
 
   // ---- epilogue: merge is already done in registers; normalise or write this segment's partials
@@ -774,7 +864,7 @@ k_beam_attn(AttnCtx c) {
     if (c.nsplit == 1) {
       // The wave's 32 rows x D outputs go through its own slice of LDS so that global memory sees whole
       // 256-byte rows (16 lanes x 16 bytes) instead of 8-byte pieces of 32 different rows per store.
-      if (!own_stage && ntiles > 0) __syncthreads();       // nobody reads the tile slots any more
+      if (KS == 1 && !own_stage && ntiles > 0) __syncthreads();       // nobody reads the tile slots any more
       uint16_t* s_o = smem + wave * 32 * KSTR;
       const float inv = (l_tot > 0.f) ? 1.0f / l_tot : 0.f;
 #pragma unroll
@@ -808,7 +898,7 @@ k_beam_attn(AttnCtx c) {
     } else {
       // this segment's unnormalised fp32 partial O and (max, sum): staged through LDS like the final
       // output, half of the columns at a time
-      if (!own_stage && ntiles > 0) __syncthreads();       // nobody reads the tile slots any more
+      if (KS == 1 && !own_stage && ntiles > 0) __syncthreads();       // nobody reads the tile slots any more
       float* s_p = (float*)(smem + wave * 32 * KSTR);
       constexpr int CW = D / 2;                            // columns per round: a wave's slice holds 32 rows x CW floats
       constexpr int PSTR = KSTR / 2;                       // floats per staged row (CW + padding)
@@ -914,34 +1004,29 @@ __global__ void __launch_bounds__(256) k_attn_order(const int32_t* cu, int B, in
   }
 }
 
-// Dynamic LDS of k_beam_attn: K and V tiles, double-buffered (unpadded); the Q hand-over / output staging (padded rows),
-// behind the tiles for 256-row workgroups and on top of them for 128-row ones; one padded 32-row K and V mini-tile per
-// wave for the own-token stage (on top of everything else, after the prompt loop).
-size_t attn_lds_bytes(int d, int mwg) {
-  const size_t tiles = (size_t)4 * KT * d * 2;
-  const size_t rows = (size_t)mwg * (d + 8) * 2;
-  const size_t main_loop = mwg == 256 ? tiles + rows : (tiles > rows ? tiles : rows);
-  const size_t own = (size_t)(mwg / 32) * 32 * ((d + 8) + (d + 32)) * 2;
-  return main_loop > own ? main_loop : own;
-}
-
-// Host-side launch plan, fitted to a measured sweep over (B, L, W) on the MI355X.  8-wave workgroups
-// of 256 query rows stage each K/V tile once per 256 rows and win once there are at least 256 of them
-// (one per CU); below that, 4-wave workgroups of 128 rows (two fit a CU) fill the chip better than
-// splitting the prompt further.  Splitting the prompt into L segments costs fp32 partials through HBM
-// plus the merge kernel, so it only pays while it fills idle CUs: segments are added until about one
-// workgroup per CU exists (never fewer than four tiles per segment), and not at all once 256 units
-// exist without it.
-struct AttnPlan { int mwg, nsplit; };
+// Host-side launch plan, fitted to measured sweeps over (B, L, W) on the MI355X.  8-wave workgroups of 256 query rows stage each
+// K/V tile once per 256 rows and win once there are at least 256 of them (one per CU); below that, workgroups of 128 rows: two of
+// 4 waves to a CU, or, where there is at most one per CU, one of 8 waves in two sets that share the prompt (ks = 2: 8 requests of
+// 2048 tokens x 128 beams, 256 workgroups, 46.3 -> 41.8 us; 2 x 256 x 16 of head size 64 8.4 -> 7.7).
+// Splitting the prompt into L segments costs fp32 partials through memory and the merge kernel.  With fewer workgroups than
+// CUs, the number of segments is the one for which this sum is least, in us: 1.6 (head size 128) or 1.07 (64) for a tile of each
+// set that a segment holds, 3.5 for the merge, and the partials written and read at 4 TB/s.  It is within 10 % of what 60 shapes of
+// 256 to 12000 tokens took: 8 requests of 700 tokens, 128 beams, 16 query and 2 KV heads: 17.5, 25.0, 25.8, 26.1 us with 1 to 4 segments
+// (about one workgroup per CU means 2); one of 4096 tokens 54.2, 35.4, 23.8, 20.8, 25.2 with 1, 2, 4, 8, 16 (16).
+struct AttnPlan { int mwg, nsplit, ks; };
 int g_plan_rows = 0, g_plan_segments = 0;                  // gr_diag_attn_plan: 0 = use the rule below
 AttnPlan plan_attn(const gr_attn_params* p) {
   const int g = p->Hq / p->Hkv;
   const int64_t M = (int64_t)p->W * g;
   AttnPlan plan;
+  auto wants_sets = [&](const AttnPlan& q) {
+    return q.mwg == 128 && p->max_L > KT && (int64_t)p->B * p->Hkv * ((M + 127) / 128) * q.nsplit <= 256 ? 2 : 1;
+  };
   if (g_plan_rows) {                                        // a sweep asked for this tiling; keep at least one tile per segment
     const int64_t cap = p->max_L / KT;
     plan.mwg = g_plan_rows;
     plan.nsplit = (int)(g_plan_segments < cap ? g_plan_segments : (cap < 1 ? 1 : cap));
+    plan.ks = wants_sets(plan);
     return plan;
   }
   const int64_t units256 = (int64_t)p->B * p->Hkv * ((M + 255) / 256);
@@ -949,11 +1034,18 @@ AttnPlan plan_attn(const gr_attn_params* p) {
   const int64_t units = (int64_t)p->B * p->Hkv * ((M + plan.mwg - 1) / plan.mwg);
   plan.nsplit = 1;
   if (units < 256 && p->max_L > 4 * KT) {
-    const int64_t want = (256 + units / 2) / units;       // nearest to one workgroup per CU
-    const int64_t cap = p->max_L / (4 * KT);              // at least four tiles per segment
-    const int64_t n = want < cap ? want : cap;
-    plan.nsplit = (int)(n > 16 ? 16 : (n < 1 ? 1 : n));
+    const int64_t want = (256 + units / 2) / units, cap = p->max_L / (4 * KT);        // about one workgroup per CU; at least four tiles per segment
+    const int most = (int)(want < cap ? (want < 16 ? want : 16) : (cap < 16 ? cap : 16));
+    const int tiles = (p->max_L + KT - 1) / KT;
+    const double partial_us = 2.0 * p->B * p->W * p->Hq * p->d * 4 / 4e6;             // of one segment
+    double least = 0;
+    for (int n = 1; n <= most; n++) {
+      const int ks = units * n <= 256 ? 2 : 1, per_set = ((tiles + n - 1) / n + ks - 1) / ks;
+      const double us = (p->d == 64 ? 1.07 : 1.6) * per_set + (n > 1 ? 3.5 + partial_us * n : 0.0);
+      if (n == 1 || us < least) { least = us; plan.nsplit = n; }
+    }
   }
+  plan.ks = wants_sets(plan);
   return plan;
 }
 
@@ -1042,21 +1134,21 @@ gr_status attn_run(const gr_attn_params* p, const int32_t* slot, bool kv8, float
   const int64_t groups_padded = ((int64_t)c.n_groups + 7) / 8 * 8;
   const int64_t grid = groups_padded * c.MB;
   if (grid >= ((int64_t)1 << 31)) return GR_ERR_UNSUPPORTED;
-  const size_t lds = attn_lds_bytes(p->d, plan.mwg);
-#define GR_LAUNCH_ATTN(DD, NCB_, NW_)                                                                                        \
+  const size_t lds = attn_lds_bytes(p->d, plan.mwg, plan.ks);
+#define GR_LAUNCH_ATTN(DD, NW_, KS_)                                                                                        \
   do {                                                                                                                       \
     if (kv8) {                                                                                                               \
-      if (const gr_status st = gr_allow_lds<k_beam_attn<DD, NCB_, NW_, false, true>>(lds)) return st; \
-      hipLaunchKernelGGL((k_beam_attn<DD, NCB_, NW_, false, true>), dim3((unsigned)grid), dim3(NW_ * 64), lds, stream, c);   \
+      if (const gr_status st = gr_allow_lds<k_beam_attn<DD, 1, NW_, false, true, KS_>>(lds)) return st; \
+      hipLaunchKernelGGL((k_beam_attn<DD, 1, NW_, false, true, KS_>), dim3((unsigned)grid), dim3(NW_ * 64 * KS_), lds, stream, c);   \
     } else {                                                                                                                 \
-      if (const gr_status st = gr_allow_lds<k_beam_attn<DD, NCB_, NW_, false, false>>(lds)) return st; \
-      hipLaunchKernelGGL((k_beam_attn<DD, NCB_, NW_, false, false>), dim3((unsigned)grid), dim3(NW_ * 64), lds, stream, c);  \
+      if (const gr_status st = gr_allow_lds<k_beam_attn<DD, 1, NW_, false, false, KS_>>(lds)) return st; \
+      hipLaunchKernelGGL((k_beam_attn<DD, 1, NW_, false, false, KS_>), dim3((unsigned)grid), dim3(NW_ * 64 * KS_), lds, stream, c);  \
     }                                                                                                                        \
   } while (0)
   if (p->d == 128) {
-    if (plan.mwg == 256) GR_LAUNCH_ATTN(128, 1, 8); else GR_LAUNCH_ATTN(128, 1, 4);
+    if (plan.mwg == 256) GR_LAUNCH_ATTN(128, 8, 1); else if (plan.ks == 2) GR_LAUNCH_ATTN(128, 4, 2); else GR_LAUNCH_ATTN(128, 4, 1);
   } else {
-    if (plan.mwg == 256) GR_LAUNCH_ATTN(64, 1, 8); else GR_LAUNCH_ATTN(64, 1, 4);
+    if (plan.mwg == 256) GR_LAUNCH_ATTN(64, 8, 1); else if (plan.ks == 2) GR_LAUNCH_ATTN(64, 4, 2); else GR_LAUNCH_ATTN(64, 4, 1);
   }
 #undef GR_LAUNCH_ATTN
   if (c.nsplit > 1) {
@@ -1129,11 +1221,11 @@ extern "C" gr_status gr_prefill_attn(const gr_prefill_params* p, void* stream_) 
   const int64_t groups_padded = ((int64_t)c.n_groups + 7) / 8 * 8;
   const int64_t grid = groups_padded * c.MB;
   if (grid >= ((int64_t)1 << 31)) return GR_ERR_UNSUPPORTED;
-  const size_t lds = attn_lds_bytes(p->d, mwg);
+  const size_t lds = attn_lds_bytes(p->d, mwg, 1);
 #define GR_LAUNCH_PREFILL(DD, NW_)                                                                                              \
   do {                                                                                                                         \
-    if (const gr_status st = gr_allow_lds<k_beam_attn<DD, 1, NW_, true, false>>(lds)) return st; \
-    hipLaunchKernelGGL((k_beam_attn<DD, 1, NW_, true, false>), dim3((unsigned)grid), dim3(NW_ * 64), lds, stream, c);          \
+    if (const gr_status st = gr_allow_lds<k_beam_attn<DD, 1, NW_, true, false, 1>>(lds)) return st; \
+    hipLaunchKernelGGL((k_beam_attn<DD, 1, NW_, true, false, 1>), dim3((unsigned)grid), dim3(NW_ * 64), lds, stream, c);          \
   } while (0)
   if (p->d == 128) {
     if (mwg == 256) GR_LAUNCH_PREFILL(128, 8); else GR_LAUNCH_PREFILL(128, 4);

@@ -161,3 +161,24 @@ def test_every_launch_plan_matches_oracle(gr, oracle_lib, d, rows, segments):
         _check(gr, oracle_lib, a, float(np.float32(1 / np.sqrt(d))), tri)
     finally:
         gr.gr_diag_attn_plan(0, 0)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("g,u", [(1, 3), (3, 2), (4, 0), (8, 1)])
+def test_two_sets_of_wavefronts_split_the_prompt(gr, oracle_lib, d, g, u):
+    """Few enough row blocks that two sets of wavefronts share each: prompts of no tile, one, an odd and an even number of tiles, each
+    with a whole and a partial last one (the second set has no tile, one less than the first, or as many); g = 1 needs three passes of the
+    own-token stage."""
+    lens = (0, 1, 64, 65, 128, 129, 192, 200, 256, 320, 321)
+    a = rand_attn_case(700 + d + g + u, len(lens), 33, g, 1, d, 3, u, lens)
+    _check(gr, oracle_lib, a, float(np.float32(1 / np.sqrt(d))))
+
+
+@pytest.mark.parametrize("d,B", [(64, 32), (64, 33), (128, 32), (128, 33)])
+def test_one_and_two_sets_of_wavefronts(gr, oracle_lib, d, B):
+    """256 row blocks (one per CU, two sets each) and 264 (one set each)."""
+    lens = tuple(70 + 9 * (b % 5) for b in range(B))
+    a = rand_attn_case(800 + d + B, B, 20, 16, 8, d, 3, 2, lens)
+    rng = np.random.default_rng(8)
+    tri = np.stack([np.arange(300) % B, rng.integers(0, 20, 300), rng.integers(0, 16, 300)], axis=1).astype(np.int32)
+    _check(gr, oracle_lib, a, float(np.float32(1 / np.sqrt(d))), tri)

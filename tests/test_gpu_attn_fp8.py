@@ -81,6 +81,16 @@ def test_fp8kv_every_launch_plan(gr, oracle_lib, d, rows, segments):
         gr.gr_diag_attn_plan(0, 0)
 
 
+@pytest.mark.parametrize("d,B", [(64, 11), (64, 36), (128, 11), (128, 36)])
+def test_fp8kv_one_and_two_sets_of_wavefronts(gr, oracle_lib, d, B):
+    """88 row blocks (two sets of wavefronts share each one's prompt: no, one, odd and even numbers of tiles) and 288 (one set)."""
+    lens = ((0, 1, 64, 65, 128, 129, 192, 200, 256, 320, 321) * 4)[:B]
+    a = rand_attn_case(500 + d + B, B, 20, 8, 8, d, 3, 2, lens)
+    rng = np.random.default_rng(9)
+    tri = np.stack([np.arange(400) % B, rng.integers(0, 20, 400), rng.integers(0, 8, 400)], axis=1).astype(np.int32)
+    _check(gr, oracle_lib, a, float(np.float32(1 / np.sqrt(d))), tri)
+
+
 def test_fp8kv_every_code_is_widened_exactly(gr, oracle_lib):
     """All 254 finite codes appear in K and V (one dominant key per query picks single V rows, so a wrong code -> value
     map or a wrong byte order inside the 8-byte pieces shows up at full magnitude)."""
