@@ -27,7 +27,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 constexpr int KT = 64;        // kv tokens per LDS tile
 
 // Dynamic LDS of k_beam_attn: K and V tiles, double-buffered (unpadded); the Q hand-over (unpadded, swizzled), behind the tiles
-// for workgroups of 8 wavefronts and on top of them for those of 4; one padded 32-row K and V mini-tile per wave for the own-token
+// for workgroups of 8 wavefronts and in the V tiles' place for those of 4; one padded 32-row K and V mini-tile per wave for the own-token
 // stage and the padded output staging (on top of everything else, after the prompt loop).  Behind all of it 256 bytes per wave
 // that loads issued only to bring lines into L2 write to.
 // Workgroups whose two halves share the prompt (ks = 2): tiles of the first half, Q, tiles of the second half.  The last 2 KiB
@@ -350,7 +350,8 @@ k_beam_attn(AttnCtx c) {
   uint16_t* s_k = s_tiles;
   uint16_t* s_v = s_tiles + 2 * TILE;
   constexpr bool kQSeparate = NWAVES * KS == 8;
-  uint16_t* s_q = kQSeparate ? smem + 4 * TILE : smem;
+  uint16_t* s_q = smem + (kQSeparate ? 4 : 2) * TILE;          // (4 waves: in place of the V tiles, MWG * D = 2 * TILE)
+  static_assert(kQSeparate || MWG * D <= 2 * TILE, "Q fits the V tiles' place");
 
   const int tid = (int)threadIdx.x % NT, wave = tid >> 6, lane = tid & 63, G = lane >> 5, n32 = lane & 31;
 
@@ -588,12 +589,14 @@ k_beam_attn(AttnCtx c) {
     touch(vu_b, off);
   };
 
-  // first prompt tiles: requested before anything waits on memory (when Q has its own LDS region)
+  // first prompt tiles: requested before anything waits on memory; V(0) once Q has left its place where Q has no LDS of its own.
+  // (With Q on top of the K tiles all requests of 4-wave workgroups waited for it: 16 causal prompts of 60-700 tokens 46.5 -> 45.8 us.)
   Stage8 k8b;
   if (KV8) {
     if (ntiles > 0) { k8 = gload8(true, 0); v8 = gload8(false, 0); k8b = gload8(true, min(1, ntiles - 1)); }
-  } else if (kQSeparate && ntiles > 0) {
-    tload(true, flip, 0); tload(false, flip, 0);
+  } else if (ntiles > 0) {
+    tload(true, flip, 0);
+    if (kQSeparate) tload(false, flip, 0);
     tload(true, flip ^ 1, min(1, ntiles - 1));
   }
   int prow0 = own_stage ? own_row(0) : 0;
@@ -609,11 +612,8 @@ k_beam_attn(AttnCtx c) {
 #pragma unroll
     for (int ks = 0; ks < D / 16; ks++) qop[0][ks] = as_bf16x8(*(const uint4*)(&s_q[(wave * 32 + n32) * D + ((2 * ks + G) ^ T::swz_k(n32)) * 8]));
     if (!kQSeparate) {
-      __syncthreads();                               // the tile slots may now be overwritten
-      if (!KV8 && ntiles > 0) {
-        tload(true, flip, 0); tload(false, flip, 0);
-        tload(true, flip ^ 1, min(1, ntiles - 1));
-      }
+      __syncthreads();                               // the V tile slots may now be overwritten
+      if (!KV8 && ntiles > 0) tload(false, flip, 0);
     }
     if (KV8 && ntiles > 0) {
       lstore8(s_k + flip * TILE, true, k8); lstore8(s_v + flip * TILE, false, v8); lstore8(s_k + (flip ^ 1) * TILE, true, k8b);
@@ -628,9 +628,11 @@ k_beam_attn(AttnCtx c) {
     // barrier per tile orders every buffer reuse.  Loads for tiles past the end are clamped to the
     // last tile (harmless re-reads; a duplicate K tile lands in a buffer nobody reads any more).
     const int tl = ntiles - 1;
-    tiles_landed();
+    // (V(0), requested last where Q had its place, may be on its way: the first step or the last tile waits for it)
+    if (!kQSeparate && !KV8) __builtin_amdgcn_s_waitcnt(0x0F70 | CPW);               // vmcnt(CPW)
+    else tiles_landed();
     asm volatile("" : "+v"(prow0));                    // (waited for here, not at its first use)
-    __syncthreads();                                   // K(0), V(0), K(1) are in LDS
+    __syncthreads();                                   // K(0), K(1) are in LDS, and V(0) where it was requested with them
 
     auto rescale = [&](const float (&alpha)[NCB], const bool (&upd)[NCB]) {
 #pragma unroll
