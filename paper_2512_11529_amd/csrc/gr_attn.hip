@@ -343,7 +343,7 @@ k_beam_attn(AttnCtx c) {
   static_assert(NCHUNK % NWAVES == 0, "tile must divide over the waves");
   // double-buffered tiles: K(j) in s_k[slot], V(j) in s_v[slot], slot = (j + flip) % 2 (flip is chosen below so that the last
   // tile is in slot 0: the main loop then names its slots at compile time); then (8-wave workgroups only: they own the CU's LDS
-  // anyway) a separate region for the Q hand-over, so that the first tiles can be in flight while Q is staged
+  // anyway) a separate region for the Q hand-over, so that the first tiles can be in flight while Q is staged; of 4 waves, K's only
   extern __shared__ __attribute__((aligned(1024))) uint16_t smem[];
   const int set = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x / NT);
   uint16_t* s_tiles = smem + (KS == 1 ? 0 : set * (4 * TILE + MWG * D));

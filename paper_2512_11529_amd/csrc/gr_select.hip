@@ -1324,7 +1324,7 @@ extern "C" gr_status gr_beam_select(const gr_select_params* p, void* workspace, 
 
 // ------------------------------------------------------------------------------------------------
 // gr_beam_select_noalloc: the same item step for callers that cannot allocate or hand in a workspace.
-// The kernels' scratch memory (row bias / mode / best score and the chunk keys) lives in a static device
+// The kernels' scratch memory (row bias / mode / first child, group maxima and keys) lives in a static device
 // array; every GPU the library runs on holds its own copy at its own address, obtained once per device.
 // ------------------------------------------------------------------------------------------------
 namespace {
