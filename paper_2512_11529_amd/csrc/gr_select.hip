@@ -515,13 +515,13 @@ __device__ __forceinline__ void gather_part(GatherPart& g, const float* x, const
     g.best = max_raw(g.best, bmax);
     const float mn = max_raw(g.m, wave_max(bmax)), lo = mn - 600.f;
     const double rn = -(double)mn * ek.c;
-    if (base > first) S = S * exp_rel(max_raw(g.m, lo), rn, tab, ek);
-    g.m = mn;
-    if (mn > -INFINITY) {
+    if (mn > -INFINITY) {                                    // (before the first finite logit S is 0, and rn infinite)
+      if (base > first) S = S * exp_rel(max_raw(g.m, lo), rn, tab, ek);
 #pragma unroll
       for (int k = 0; k < kPartU; k++)
         if (base + 64 * k < n) S = exp_add(S, max_raw(g.x[k], lo), rn, tab, ek);     // (-inf adds less than 1e-260)
     }
+    g.m = mn;
   }
   g.S = wave_sum(S);
 }

@@ -70,3 +70,39 @@ def test_scores_close_together_and_far_apart(gr, oracle_lib, spread):  # noqa: F
     one = np.full((B, W), -np.inf, np.float32)
     one[:, 7] = 0.0                                                # a single live beam: fewer groups than beams
     assert_select_equal(run_select(gr, None, logits, one, pf, rg, 0), oracle_lib.beam_select(None, logits, one, pf, 0))
+
+
+def _suppressed(pattern, n):
+    """Positions in a child list of n whose logits are -inf."""
+    at = np.arange(n)
+    return dict(wave_0=(at % 2048) < 512,                          # every part of 512 that the first of four wavefronts takes
+                wave_3=(at % 2048) >= 1536,
+                all_but_last=at < n - 1, all_but_one=at != min(700, n - 1), all=at >= 0, second_half=at >= n // 2)[pattern]
+
+
+@pytest.mark.parametrize("step", [1, 2])
+@pytest.mark.parametrize("pattern", ["wave_0", "wave_3", "all_but_last", "all_but_one", "all", "second_half"])
+def test_long_child_lists_with_suppressed_tokens(gr, oracle_lib, pattern, step):  # noqa: F811
+    # -inf logits (a top-k or category filter in front of the item step) over whole parts of rows that a workgroup gathers
+    rng = np.random.default_rng(step)
+    V, counts = 8200, (300, 1025, 2049, 3000, 8192)
+    lists = _children(rng, V, counts)
+    if step == 1:
+        items = np.array([(t1, t2, int(rng.integers(V))) for t1, lst in enumerate(lists) for t2 in lst], dtype=np.int32)
+    else:
+        items = np.array([(4, t2, t3) for t2, lst in enumerate(lists) for t3 in lst], dtype=np.int32)
+    mask = gr.gr_item_mask_build(to_dev(items), V)
+    W = 2 * len(counts)
+    pf = np.full((2, W, 3), -1, np.int32)
+    rg = np.zeros((2, W, 2), np.int32)
+    end = np.cumsum(counts)
+    logits = (2.0 * rng.standard_normal((2, W, V))).astype(np.float32)
+    for w in range(W):
+        i = w % len(counts)
+        pf[:, w, :step] = [i] if step == 1 else [4, i]
+        rg[:, w] = end[i] - counts[i], end[i]
+        logits[0, w, lists[i][_suppressed(pattern, counts[i])]] = -np.inf
+    logits[1] = logits[0]
+    sc = (-3.0 * rng.random((2, W))).astype(np.float32)
+    sc[1, np.arange(W) != 3] = -np.inf                             # request 1: a row of 3000 is its only live beam
+    assert_select_equal(run_select(gr, mask, logits, sc, pf, rg, step), oracle_lib.beam_select(items, logits, sc, pf, step))
