@@ -678,8 +678,9 @@ __device__ __forceinline__ void for_each_candidate(const SelCtx& c, const MaskVi
       const uint32_t flat0 = (uint32_t)w * (uint32_t)c.V;
       for (int v0 = 0; v0 < c.V; v0 += blockDim.x) {
         const int v = v0 + threadIdx.x;
-        const bool pred = v < c.V && (!c.blob || ((mv.l0[v >> 5] >> (v & 31)) & 1u));
-        f(pred ? __fadd_rn(bias, x[v]) : 0.f, flat0 + v, pred);
+        const bool valid = v < c.V && (!c.blob || ((mv.l0[v >> 5] >> (v & 31)) & 1u));
+        const float score = valid ? __fadd_rn(bias, x[v]) : -INFINITY;
+        f(score, flat0 + v, score > -INFINITY);
       }
     }
   } else {
@@ -695,9 +696,9 @@ __device__ __forceinline__ void for_each_candidate(const SelCtx& c, const MaskVi
       const int32_t* list = child_list(c, mv) + start;
       for (int i0 = 0; i0 < n; i0 += 64) {
         const int i = i0 + lane;
-        const bool pred = i < n;
-        const int v = pred ? list[i] : 0;
-        f(pred ? __fadd_rn(bias, x[v]) : 0.f, flat0 + (gathered ? i : v), pred);
+        const int v = i < n ? list[i] : 0;
+        const float score = i < n ? __fadd_rn(bias, x[v]) : -INFINITY;
+        f(score, flat0 + (gathered ? i : v), score > -INFINITY);
       }
     }
   }

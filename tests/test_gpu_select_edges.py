@@ -106,3 +106,31 @@ def test_long_child_lists_with_suppressed_tokens(gr, oracle_lib, pattern, step):
     sc = (-3.0 * rng.random((2, W))).astype(np.float32)
     sc[1, np.arange(W) != 3] = -np.inf                             # request 1: a row of 3000 is its only live beam
     assert_select_equal(run_select(gr, mask, logits, sc, pf, rg, step), oracle_lib.beam_select(items, logits, sc, pf, step))
+
+
+@pytest.mark.parametrize("live,finite", [(200, 1), (20, 1), (3, 1), (1, 200), (12, 20), (256, 0)])
+@pytest.mark.parametrize("masked", [False, True])
+def test_fewer_finite_candidates_than_beams(gr, oracle_lib, live, finite, masked):  # noqa: F811
+    # every live beam has `finite` finite logits, so that most slots of the new generation are dead
+    rng = np.random.default_rng(live + finite)
+    B, W, V = 2, 256, 8192
+    logits = np.full((B, W, V), -np.inf, np.float32)
+    items = mask = None
+    pf = np.full((B, W, 3), -1, np.int32)
+    rg = np.zeros((B, W, 2), np.int32)
+    pf[:, :, 0] = 0
+    if masked:                                                     # every first token has 5000 children
+        children = _children(rng, V, [5000] * 4)
+        items = np.array([(t1, t2, 7) for t1 in range(4) for t2 in children[t1]], dtype=np.int32)
+        mask = gr.gr_item_mask_build(to_dev(items), V)
+        pf[:, :, 0] = np.arange(W) % 4
+        rg[:, :, 0], rg[:, :, 1] = 5000 * pf[:, :, 0], 5000 * (pf[:, :, 0] + 1)
+    for b in range(B):
+        for w in range(W):
+            at = rng.choice(V if not masked else 5000, size=finite, replace=False)
+            at = children[w % 4][at] if masked else at
+            logits[b, w, at] = rng.standard_normal(finite)
+    sc = np.full((B, W), -np.inf, np.float32)
+    for b in range(B):
+        sc[b, rng.choice(W, size=live, replace=False)] = -rng.random(live)
+    assert_select_equal(run_select(gr, mask, logits, sc, pf, rg, 1), oracle_lib.beam_select(items, logits, sc, pf, 1))
