@@ -110,7 +110,8 @@ __device__ __forceinline__ void row_children(const SelCtx& c, const MaskView& mv
     if (t1 >= 0 && t1 < c.V) { *start = mv.pair_off[t1]; *n = mv.pair_off[t1 + 1] - *start; }
   } else {
     const int lo = c.range_in[2 * (size_t)row], hi = c.range_in[2 * (size_t)row + 1];
-    if (lo >= 0 && hi >= lo && (int64_t)hi <= mv.n_items) { *start = lo; *n = hi - lo; }
+    // (at most V: the place of a child and the unit it falls in are packed for no more)
+    if (lo >= 0 && hi >= lo && (int64_t)hi <= mv.n_items && hi - lo <= c.V) { *start = lo; *n = hi - lo; }
   }
 }
 __device__ __forceinline__ const int32_t* child_list(const SelCtx& c, const MaskView& mv) { return c.step == 1 ? mv.pair_t2 : mv.t3; }

@@ -134,3 +134,23 @@ def test_fewer_finite_candidates_than_beams(gr, oracle_lib, live, finite, masked
     for b in range(B):
         sc[b, rng.choice(W, size=live, replace=False)] = -rng.random(live)
     assert_select_equal(run_select(gr, mask, logits, sc, pf, rg, 1), oracle_lib.beam_select(items, logits, sc, pf, 1))
+
+
+@pytest.mark.parametrize("flags", [0, 1])
+def test_a_range_no_mask_produces_has_no_children(gr, oracle_lib, flags):  # noqa: F811
+    # wider than the vocabulary, outside the table, or backwards: the beam is dead, the others are selected as without it
+    rng = np.random.default_rng(3)
+    V, W, children = 64, 8, 40
+    thirds = _children(rng, V, [children] * 60)
+    items = np.array([(0, t2, t3) for t2, lst in enumerate(thirds) for t3 in lst], dtype=np.int32)
+    mask = gr.gr_item_mask_build(to_dev(items), V)
+    logits = (2.0 * rng.standard_normal((1, W, V))).astype(np.float32)
+    pf = np.full((1, W, 3), -1, np.int32)
+    pf[:, :, 0], pf[:, :, 1] = 0, np.arange(W)
+    rg = np.stack([children * np.arange(W), children * (np.arange(W) + 1)], 1).astype(np.int32)[None]
+    sc = -rng.random((1, W)).astype(np.float32)
+    bad = [1, 3, 4, 6]
+    rg[0, bad] = [[0, V + 1], [0, len(items)], [len(items) - 3, len(items) + 1], [90, 80]]
+    live = sc.copy()
+    live[0, bad] = -np.inf
+    assert_select_equal(run_select(gr, mask, logits, sc, pf, rg, 2, flags), oracle_lib.beam_select(items, logits, live, pf, 2))
