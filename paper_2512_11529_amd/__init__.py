@@ -65,8 +65,9 @@ class _SelectParams(ctypes.Structure):
 
 
 def load_library(path: str = None):
-    """dlopen libgr.so and declare the C signatures.  Raises if the library is not built."""
-    global _lib
+    """dlopen libgr.so and declare the C signatures.  Raises if the library is not built.  Another library given by `path` takes
+    the place of the one before for every call."""
+    global _lib, _native
     if _lib is not None and path is None:
         return _lib
     path = path or LIB_PATH
@@ -116,7 +117,7 @@ def load_library(path: str = None):
     lib.gr_diag_mfma_flops.argtypes = [ctypes.c_int32, ctypes.c_int32]
     lib.gr_beam_reorder.restype = ctypes.c_int32
     lib.gr_beam_reorder.argtypes = [ctypes.c_int32] * 6 + [ctypes.c_void_p] * 4
-    _lib = lib
+    _lib, _native = lib, None            # (the marshalling module binds to this library at its next call)
     return lib
 
 

@@ -27,6 +27,30 @@ def test_tensors_off_the_gpu_and_other_objects_are_refused(gr):
         gr.gr_beam_select_noalloc(None, torch.zeros(1, 1, 4), t, torch.zeros(1, 1, 3), t, 0, {})
 
 
+def test_a_library_loaded_later_takes_the_calls(gr, monkeypatch, tmp_path):
+    # the marshalling module is bound again when load_library() is given another library
+    import ctypes
+    import shutil
+
+    bound = []
+
+    class Recorder:
+        def bind(self, *a):
+            bound.append(a[0])
+
+    address = lambda lib: ctypes.cast(lib.gr_beam_attn, ctypes.c_void_p).value
+    monkeypatch.setattr(gr, "_lib", None)
+    monkeypatch.setattr(gr, "_native", None)
+    monkeypatch.setattr(gr.importlib.util, "module_from_spec", lambda spec: Recorder())
+    monkeypatch.setattr(gr.importlib.machinery.ExtensionFileLoader, "exec_module", lambda self, module: None)
+    first = gr.load_library()
+    gr._marshal()
+    other = gr.load_library(shutil.copy(gr.LIB_PATH, tmp_path / "libgr_other.so"))
+    gr._marshal()
+    assert address(first) != address(other)
+    assert bound == [address(first), address(other)]
+
+
 @pytest.mark.gpu
 def test_types_shapes_and_strides_are_checked(gr):
     dev = torch.device("cuda:0")
