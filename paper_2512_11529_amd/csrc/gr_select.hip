@@ -8,11 +8,12 @@
 //   k_select       one workgroup per request: top-W of the request's candidates by (score descending, flat index
 //                  ascending).  It never sorts the W*V candidates: k_rows leaves the best candidate score of every 16th of a
 //                  row; a histogram of these yields a threshold that at least W candidates reach, only what reaches
-//                  it is read again (by finer keys that k_rows left too), and a second histogram over that yields the few
-//                  candidates that are sorted (the early-termination idea of Section 6.2: stop as soon as the
-//                  survivors are fixed).  One CU draws some 40 GB/s from memory it has not seen, so what counts
-//                  is how few cache lines it has to touch.  If the survivors do not fit in LDS
-//                  (massive ties) an exact MSB radix select over all candidates takes over.
+//                  it is read again (by finer keys that k_rows left too, which yield a higher threshold where the first lets
+//                  too much through), and another histogram over that yields the few candidates that are sorted (the
+//                  early-termination idea of Section 6.2: stop as soon as the survivors are fixed).  One CU draws some
+//                  40 GB/s from memory it has not seen, so what counts is how few cache lines it has to touch.  If the
+//                  survivors do not fit in LDS (thousands of equal scores) an exact MSB radix select over all candidates
+//                  takes over.
 //
 // Arithmetic that decides beam order is fixed: m = fp32 max over valid logits, S = fp64 sum of
 // exp(x - m), lse = fp32(m + log S), bias = score_in - lse (fp32), cand = bias + x (fp32), with no
@@ -23,7 +24,7 @@ namespace {
 
 constexpr int kGroups = 16;         // groups of a row's candidates; the best score of each is kept
 // and, per row, this many floats of finer data behind them:
-//   streamed row: 256 keys of 16 bits, one for every line of 32 consecutive logits of a block (the best score, rounded up);
+//   streamed row: 256 keys of 16 bits, one for every line of 32 consecutive logits of a block (how far its best score is below the row's);
 //   gathered row with at most kScoreMax children: all of their scores;
 //   gathered row with more: 64 keys (children k, k + 64, ...).
 constexpr int kRowFloats = 240;
@@ -33,7 +34,7 @@ constexpr int kScoreMax = kRowFloats;
 constexpr int kWaveMax = 1024;      // a row with at most this many children is gathered by one wavefront, one with more by a workgroup
 constexpr int kSelThreads = 1024;
 constexpr int kListCap = 8192;      // survivors that fit in LDS
-constexpr int kChunkCap = 6144;     // keys whose candidates are looked at again by the fast path
+constexpr int kChunkCap = 4096;     // keys whose candidates are looked at again by the fast path
 constexpr int kUnitSpan = 256;      // children that one unit of four, 64 apart, reaches over
 constexpr int kUnitCap = 8192;      // units of four candidates that are
 constexpr int kHistBins = 2048;
@@ -41,7 +42,7 @@ constexpr int kMaxMaskWords = 1024; // V <= 32768
 constexpr int kBlockV = 8192;       // logits of a row that a workgroup holds in registers at a time
 constexpr int kMaxW = 2048;
 constexpr int kGroupCap = 2 * kListCap;  // key groups (floats in the list's place)
-constexpr size_t kSelLdsBytes = (size_t)kListCap * 8 + (size_t)kUnitCap * 4 + (size_t)kHistBins * 4 + (size_t)kChunkCap * 4 + (size_t)kMaxW * 12;
+constexpr size_t kSelLdsBytes = (size_t)kListCap * 8 + (size_t)kUnitCap * 4 + (size_t)kHistBins * 4 + (size_t)kChunkCap * 4 + (size_t)kMaxW * 16;
 
 enum { ROW_DEAD = 0, ROW_DENSE = 1, ROW_SPARSE = 2 };      // low bits of row_info; the child count of a gathered row above them
 
@@ -63,6 +64,7 @@ struct SelCtx {
   float* row_bias;           // workspace [B*W]
   int32_t* row_info;         // workspace [B*W]
   int32_t* row_start;        // workspace [B*W]: first child of a gathered row in the pair list (level 1) or in the table (level 2)
+  float* row_best;           // the same words: best score of a streamed row
   float* row_group;          // workspace [B*W*kGroups]
   float* row_data;           // workspace [B*W*kRowFloats]
 };
@@ -278,9 +280,16 @@ __device__ __forceinline__ float keep_if_bit(float x, uint32_t bits, int k) {   
   return __uint_as_float((mask & __float_as_uint(x)) | (~mask & 0xff800000u));
 }
 
-// A score to 16 bits that order as scores do, rounded up; and a bound rounded down: key16_up(s) >= key16_down(t) wherever s >= t.
-__device__ __forceinline__ uint32_t key16_up(float f) { return (gr_ordkey(f) + 0xffffu) >> 16; }
-__device__ __forceinline__ uint32_t key16_down(float f) { return gr_ordkey(f) >> 16; }
+// The 16-bit key of a score in a row: its distance to the row's best score, rounded down to 8 bits of mantissa (so that scores close
+// together but far from 0 keep their order).  Larger scores have smaller or equal keys: what reaches a threshold T <= best has a
+// key of at most key16(best, T).  The key of -inf is above those of all finite scores.
+constexpr uint32_t kKeyLast = 0xfeffu;
+__device__ __forceinline__ uint32_t key16(float best, float score) {
+  const uint32_t k = __float_as_uint(best - score) >> 15;
+  return score > -INFINITY ? min(k, kKeyLast) : kKeyLast + 1u;
+}
+// a score that one with this key is not below (the rounding of these differences is allowed for where a threshold is made of it)
+__device__ __forceinline__ float key16_low(float best, uint32_t key) { return best - __uint_as_float((key + 1u) << 15); }
 
 __device__ __forceinline__ void mark_dead(const SelCtx& c, int row) { c.row_info[row] = ROW_DEAD; }
 
@@ -467,13 +476,13 @@ __device__ __forceinline__ void row_dense(const SelCtx& c, const MaskView& mv, R
   const double T = wave_sum(S * exp_rel(max_raw(m, M - 600.f), -(double)M * ek.c, L.tab, ek));
   const float lse = (float)((double)M + log(T));
   const float bias = __fsub_rn(s_in, lse);
-  if (tid == 0) { c.row_bias[row] = bias; c.row_info[row] = ROW_DENSE; }
+  const float best = __fadd_rn(bias, M);
+  if (tid == 0) { c.row_bias[row] = bias; c.row_info[row] = ROW_DENSE; c.row_best[row] = best; }
   const float4 kl = *(const float4*)&L.key[set][4 * tid];
-  auto score = [&](float v) { return (v > -INFINITY) ? __fadd_rn(bias, v) : -INFINITY; };
-  const float k0 = score(kl.x), k1 = score(kl.y), k2 = score(kl.z), k3 = score(kl.w);
+  const float k0 = __fadd_rn(bias, kl.x), k1 = __fadd_rn(bias, kl.y), k2 = __fadd_rn(bias, kl.z), k3 = __fadd_rn(bias, kl.w);      // (bias is finite)
   uint2 packed;
-  packed.x = key16_up(k0) | (key16_up(k1) << 16);
-  packed.y = key16_up(k2) | (key16_up(k3) << 16);
+  packed.x = key16(best, k0) | (key16(best, k1) << 16);
+  packed.y = key16(best, k2) | (key16(best, k3) << 16);
   *(uint2*)(c.row_data + (size_t)row * kRowFloats + 2 * tid) = packed;
   const float group = quad_max(max_raw(max_raw(k0, k1), max_raw(k2, k3)));
   if ((tid & 3) == 0) c.row_group[(size_t)row * kGroups + (tid >> 2)] = group;
@@ -709,13 +718,31 @@ __device__ __forceinline__ uint64_t composite(float score, uint32_t flat) {
   return ((uint64_t)gr_ordkey(score + 0.0f) << 32) | (uint64_t)(0xffffffffu - flat);     // (+0.0f: -0 and +0 are one score)
 }
 
-// Monotone (non-increasing in the score) histogram bin below `hi`.
+// Monotone (non-increasing in the score) histogram bin of a score below the best, `hi`; bins of one width.
 __device__ __forceinline__ int key_bin(float hi, float scale, float score) {
   return (int)fminf(fmaxf((hi - score) * scale, 0.f), (float)(kHistBins - 1));
 }
-// Bins per unit of score for a histogram that has to cover `range`.
-__device__ __forceinline__ float bin_scale(float range) {
-  return (range > 0.f && range < INFINITY) ? fminf((float)(kHistBins - 1) / range, 1e30f) : 0.f;
+
+constexpr float kNoThreshold = -3.402823466e38f;       // the lowest float: every candidate reaches it
+
+// Bins for thresholds, of the distance below the best score `hi` (monotone: a better score is never in a later bin), even in the logarithm:
+// 128 to an octave over the 16 octaves below `range`, or below 4096 where that is wider.  So they are as fine for scores that
+// lie close together as for scores far apart, and a few scores far below do not make the others' bins coarse.  What lies
+// lower is in the last bin.
+struct Bins {
+  float hi;
+  int base;
+  __device__ __forceinline__ int of(float score) const {
+    return min(max((int)(__float_as_uint(fmaxf(hi - score, 0.f)) >> 16) - base, 0), kHistBins - 1);
+  }
+  // a score that everything in bins 0..thr reaches (a little low: rounding may only let more through)
+  __device__ __forceinline__ float floor_of(int thr) const {
+    const float d = __uint_as_float((uint32_t)(thr + 1 + base) << 16);
+    return thr < kHistBins - 1 ? hi - d - 1e-6f * (fabsf(hi) + d) : kNoThreshold;
+  }
+};
+__device__ __forceinline__ Bins make_bins(float hi, float range) {
+  return Bins{hi, (int)(__float_as_uint(fminf(range, 4096.f)) >> 16) - (kHistBins - 2)};
 }
 
 // Exact MSB radix select of the W best composite keys over ALL candidates (slow, always correct).
@@ -842,7 +869,8 @@ __global__ void __launch_bounds__(kSelThreads) k_select(SelCtx c) {
   uint32_t* s_chunks = s_hist + kHistBins;                   // row << 8 | key above the threshold, from the front; row << 8 | four scores, from the back
   float* s_rbias = (float*)(s_chunks + kChunkCap);           // per beam row of the request: bias,
   int32_t* s_rinfo = (int32_t*)(s_rbias + kMaxW);            // mode and child count,
-  int32_t* s_ra = s_rinfo + kMaxW;                           // first child (gathered), first token (streamed, level 1) or table range start
+  int32_t* s_ra = s_rinfo + kMaxW;                           // first child (gathered), first token (streamed, level 1) or table range start,
+  float* s_rbest = (float*)(s_ra + kMaxW);                   // and best score (streamed)
   constexpr int NW = kSelThreads / 64;
   __shared__ float2 s_redf[2 * NW];
   __shared__ uint32_t s_redu[2 * NW];
@@ -886,6 +914,7 @@ __global__ void __launch_bounds__(kSelThreads) k_select(SelCtx c) {
     s_rbias[w] = c.row_bias[row];
     s_rinfo[w] = info;
     s_ra[w] = (info & 3) == ROW_SPARSE ? start : a;
+    s_rbest[w] = __int_as_float(start);
   }
   if (tid == 0) { s_n = 0; s_nd = 0; s_ns = 0; s_nu = 0; s_most = 0; }
   for (int i = tid; i < kHistBins; i += kSelThreads) s_hist[i] = 0;
@@ -893,66 +922,100 @@ __global__ void __launch_bounds__(kSelThreads) k_select(SelCtx c) {
 
   int n = 0;
   if (hi > -INFINITY) {
-    // ---- threshold that at least W groups reach (no threshold when there are fewer): at least 64 bins per unit of score, more
-    // when the groups lie close together
-    const float scale = fmaxf(64.f, bin_scale(hi - lo));
+    // ---- threshold that at least W groups reach (no threshold when there are fewer)
+    Bins bins = make_bins(hi, hi - lo);
 #pragma unroll 1
     for (int i = tid; i < ngroups; i += kSelThreads)
-      if (s_group[i] > -INFINITY) atomicAdd(&s_hist[key_bin(hi, scale, s_group[i])], 1u);
+      if (s_group[i] > -INFINITY) atomicAdd(&s_hist[bins.of(s_group[i])], 1u);
     __syncthreads();
     hist_threshold_all(s_hist, (uint32_t)c.W, &s_thr, s_redu, paru);
     __syncthreads();
-    // (a little low: rounding may only let more through)
-    auto threshold = [&](float per_score) {
-      return s_thr < kHistBins - 1 ? hi - ((float)s_thr + 1.01f) / per_score - 1e-6f * fabsf(hi) : -INFINITY;
-    };
-    float T = threshold(scale);
-    // ---- groups that reach it, then the finer keys behind them that do (four threads to a group, one round of loads for all)
+    float T = bins.floor_of(s_thr);
+    // ---- groups that reach it
 #pragma unroll 1
     for (int i = tid; i < ngroups; i += kSelThreads) {
-      if (!(s_group[i] > -INFINITY) || s_group[i] < T) continue;
+      if (!(s_group[i] >= T)) continue;
       const uint32_t pos = atomicAdd(&s_n, 1u);
       if (pos < (uint32_t)kUnitCap) s_units[pos] = (uint32_t)i;
     }
     __syncthreads();
     const int ng = (int)s_n, ssh = 6 - gsh;                  // log2 of the threads to a listed group
     bool fallback = ng > kUnitCap;
-    const uint32_t T16 = max(key16_down(T), key16_up(-INFINITY));
+    const int quarters = min(ng, kUnitCap) << ssh;
+    auto quarter = [&](int i) { return ((int)s_units[i >> ssh] << ssh) + (i & ((1 << ssh) - 1)); };      // row << 6 | quarter of the row's 16 groups
+    // ---- the finer keys behind them that reach it (four threads to a group, one round of loads for all)
+    int nd, ns, sh;
+    bool listed, raised = false;                             // (listed: the keys in front are of gathered rows)
 #pragma unroll 1
-    for (int i = tid; i < min(ng, kUnitCap) << ssh; i += kSelThreads) {
-      const int at = ((int)s_units[i >> ssh] << ssh) + (i & ((1 << ssh) - 1));      // quarter group: row << 6 | quarter of the row's 16 groups
-      const int w = at >> 6, q = at & 63, info = s_rinfo[w], cnt = info >> 2;
-      const float* fine = data + (size_t)w * kRowFloats;
-      auto add = [&](bool front, int key) {
-        const uint32_t pos = atomicAdd(front ? &s_nd : &s_ns, 1u);
-        if (pos < (uint32_t)kChunkCap) s_chunks[front ? pos : kChunkCap - 1 - pos] = ((uint32_t)w << 8) | (uint32_t)key;
-      };
-      if ((info & 3) == ROW_DENSE) {
-        const uint2 k = *(const uint2*)(fine + 2 * q);
-        if ((k.x & 0xffffu) >= T16) add(true, 4 * q);
-        if ((k.x >> 16) >= T16) add(true, 4 * q + 1);
-        if ((k.y & 0xffffu) >= T16) add(true, 4 * q + 2);
-        if ((k.y >> 16) >= T16) add(true, 4 * q + 3);
-      } else if (cnt <= kScoreMax) {
-        // (the scores of a row's last wavefront of children are -inf past its end; past that they are not written)
-        if (4 * q < cnt) {
-          const float4 k = *(const float4*)(fine + 4 * q);
-          if (fmaxf(fmaxf(k.x, k.y), fmaxf(k.z, k.w)) >= T) add(false, q);
+    for (;;) {
+#pragma unroll 1
+      for (int i = tid; i < quarters; i += kSelThreads) {
+        const int at = quarter(i), w = at >> 6, q = at & 63, info = s_rinfo[w], cnt = info >> 2;
+        const float* fine = data + (size_t)w * kRowFloats;
+        auto add = [&](bool front, int key) {
+          const uint32_t pos = atomicAdd(front ? &s_nd : &s_ns, 1u);
+          if (pos < (uint32_t)kChunkCap) s_chunks[front ? pos : kChunkCap - 1 - pos] = ((uint32_t)w << 8) | (uint32_t)key;
+        };
+        if ((info & 3) == ROW_DENSE) {
+          const uint2 k = *(const uint2*)(fine + 2 * q);
+          const float best = s_rbest[w];
+          const int last = best < T ? -1 : (int)key16(best, T);
+          if ((int)(k.x & 0xffffu) <= last) add(true, 4 * q);
+          if ((int)(k.x >> 16) <= last) add(true, 4 * q + 1);
+          if ((int)(k.y & 0xffffu) <= last) add(true, 4 * q + 2);
+          if ((int)(k.y >> 16) <= last) add(true, 4 * q + 3);
+        } else if (cnt <= kScoreMax) {
+          // (the scores of a row's last wavefront of children are -inf past its end; past that they are not written)
+          if (4 * q < cnt) {
+            const float4 k = *(const float4*)(fine + 4 * q);
+            if (fmaxf(fmaxf(k.x, k.y), fmaxf(k.z, k.w)) >= T) add(false, q);
+          }
+        } else if (fine[q] >= T) {
+          add(true, q);
+          atomicMax(&s_most, (uint32_t)cnt);
         }
-      } else {
-        const float k = fine[q];
-        if (k > -INFINITY && k >= T) { add(true, q); atomicMax(&s_most, (uint32_t)cnt); }
       }
+      __syncthreads();
+      nd = (int)s_nd; ns = (int)s_ns;
+      // units of four candidates behind a key in front: float4 of logits, or children 64 apart
+      listed = s_most > 0;
+      sh = c.unit_shift;
+      if (listed) { sh = 0; while ((kUnitSpan << sh) < (int)s_most) sh++; }
+      // Where the W best are many to a group (few beams far ahead of the others, long rows) the groups' threshold is too low and the
+      // keys' own takes its place, which W of them reach.  The line: 32 requests of 128 beams, 8192 tokens, logits of width 6 and then 1
+      // have 11 keys a beam above the groups' threshold and take 38 us without a mask, 54 us when all of them are looked at.
+      if (raised || fallback || !(nd + ns > kChunkCap || (nd > (listed ? 2 : 4) * c.W && nd << sh > kUnitCap / 2))) break;
+      raised = true;
+      bins = make_bins(hi, hi - T);
+#pragma unroll 1
+      for (int i = tid; i < quarters; i += kSelThreads) {
+        const int at = quarter(i), w = at >> 6, q = at & 63, info = s_rinfo[w], cnt = info >> 2;
+        const float* fine = data + (size_t)w * kRowFloats;
+        if ((info & 3) == ROW_DENSE) {
+          const uint2 k = *(const uint2*)(fine + 2 * q);
+          const float best = s_rbest[w];
+          const int last = best < T ? -1 : (int)key16(best, T);
+          uint64_t keys = (uint64_t)k.y << 32 | k.x;
+#pragma unroll 1
+          for (int j = 0; j < 4; j++, keys >>= 16)
+            if ((int)(keys & 0xffffu) <= last) atomicAdd(&s_hist[bins.of(key16_low(best, (uint32_t)keys & 0xffffu))], 1u);
+        } else {
+          float k = -INFINITY;
+          if (cnt > kScoreMax) k = fine[q];
+          else if (4 * q < cnt) { const float4 f = *(const float4*)(fine + 4 * q); k = fmaxf(fmaxf(f.x, f.y), fmaxf(f.z, f.w)); }
+          if (k >= T) atomicAdd(&s_hist[bins.of(k)], 1u);
+        }
+      }
+      __syncthreads();
+      if (tid == 0) { s_nd = 0; s_ns = 0; s_most = 0; }
+      hist_threshold_all(s_hist, (uint32_t)c.W, &s_thr, s_redu, paru);
+      __syncthreads();
+      T = fmaxf(T, bins.floor_of(s_thr));
     }
-    __syncthreads();
     if (tid == 0) s_n = 0;
-    const int nd = (int)s_nd, ns = (int)s_ns;
     fallback = fallback || nd + ns > kChunkCap;
-    // units of four candidates behind a key in front: float4 of logits, or children 64 apart
-    const bool listed = s_most > 0;
-    int sh = c.unit_shift;
-    if (listed) { sh = 0; while ((kUnitSpan << sh) < (int)s_most) sh++; }
     const int front_units = nd << sh;
+    float scale = 0.f;                                       // bins per unit of score for the candidates
     const int lsh = c.row_threads == 512 ? 2 : 3;            // log2 of a thread's loads per block of a streamed row
     auto unit_token = [&](int k, int e) {                    // first token of unit e of line k
       return 32 * (k >> lsh) + 4 * c.row_threads * (k & ((1 << lsh) - 1)) + 4 * (e & 7) + kBlockV * (e >> 3);
@@ -968,195 +1031,216 @@ __global__ void __launch_bounds__(kSelThreads) k_select(SelCtx c) {
         const uint32_t pos = atomicAdd(&s_nu, 1u);
         if (pos < (uint32_t)kUnitCap) s_units[pos] = ((uint32_t)(u >> sh) << 8) | (uint32_t)(u & ((1 << sh) - 1));
       };
-      auto needed = [&](int w) {                             // logit that a candidate of row w needs
-        const float bias = s_rbias[w];
-        return T - bias - 1e-6f * (fabsf(T) + fabsf(bias));
+      // best logit of a gathered row's unit
+      auto child_best = [&](int w, int k, int e) {
+        const int at = k + kUnitSpan * e, cnt = s_rinfo[w] >> 2;
+        const float* x = c.logits + ((size_t)b * c.W + w) * c.V;
+        const int32_t* list = child_list(c, mv) + s_ra[w];
+        if (at >= cnt) return -INFINITY;
+        const float y0 = x[list[at]], y1 = x[list[min(at + 64, cnt - 1)]], y2 = x[list[min(at + 128, cnt - 1)]], y3 = x[list[min(at + 192, cnt - 1)]];
+        return fmaxf(fmaxf(y0, y1), fmaxf(y2, y3));          // (a child taken twice changes nothing here)
       };
-      // fewer groups than W, as at level 0 where all candidates are one row's: the units themselves yield a threshold
-      const bool by_unit = !listed && !(T > -INFINITY) && ns == 0 && front_units <= kGroupCap && !(c.blob && c.step == 2);
-      if (by_unit) {
-        constexpr int U = 2;
+      // Fewer groups than W, as at level 0 where all candidates are one row's, or more units or candidates above the threshold than there
+      // is room for: the units themselves yield a threshold.  (Not where a streamed row's validity is only looked up
+      // below; the best candidates of the first kGroupCap units are kept, beyond that they are looked for again.)
+      const bool countable = listed || !(c.blob && c.step == 2);
+      bool by_unit = countable && T == kNoThreshold && front_units >= c.W;
 #pragma unroll 1
-        for (int base = tid; base < front_units; base += U * kSelThreads) {
-          float best[U];
-#pragma unroll
-          for (int q = 0; q < U; q++) {
-            const int u = base + q * kSelThreads;
-            best[q] = -INFINITY;
-            if (u >= front_units) continue;
-            int w, k, e;
-            entry(u, &w, &k, &e);
-            const int v = unit_token(k, e);
-            if (v >= c.V) continue;
-            const float* x = c.logits + ((size_t)b * c.W + w) * c.V;
-            uint32_t bits = 0xfu;
-            if (c.blob) bits = (c.step == 0 ? mv.l0 : mv.l1 + (size_t)s_ra[w] * mv.words)[v >> 5] >> (v & 31);
-            f32x4u y;
-            if (v + 3 < c.V) y = *(const f32x4u*)(x + v);
-            else { y.x = x[v]; y.y = x[min(v + 1, c.V - 1)]; y.z = x[min(v + 2, c.V - 1)]; y.w = y.z; }
-            // (past the row's end a mask has no bits; without one the last token is taken again, which changes nothing here)
-            best[q] = fmaxf(fmaxf(bits & 1u ? y.x : -INFINITY, bits & 2u ? y.y : -INFINITY), fmaxf(bits & 4u ? y.z : -INFINITY, bits & 8u ? y.w : -INFINITY));
-            best[q] = __fadd_rn(s_rbias[w], best[q]);
-          }
-#pragma unroll
-          for (int q = 0; q < U; q++) {
-            const int u = base + q * kSelThreads;
-            if (u < front_units) s_group[u] = best[q];
-            if (best[q] > -INFINITY) atomicAdd(&s_hist[key_bin(hi, 64.f, best[q])], 1u);
-          }
-        }
-        __syncthreads();
-        hist_threshold_all(s_hist, (uint32_t)c.W, &s_thr, s_redu, paru);
-        __syncthreads();
-        T = threshold(64.f);
+      for (;;) {
+        if (by_unit) {
+          bins = make_bins(hi, hi - T);
+          auto count = [&](int u, float best) {
+            if (u < min(front_units, kGroupCap)) s_group[u] = best;
+            if (best >= T) atomicAdd(&s_hist[bins.of(best)], 1u);
+          };
+          constexpr int U = 2;
 #pragma unroll 1
-        for (int u = tid; u < front_units; u += kSelThreads)
-          if (s_group[u] > -INFINITY && s_group[u] >= T) keep(u);
-      } else if (!listed) {
-        constexpr int U = 4;
-#pragma unroll 1
-        for (int base = tid; base < front_units; base += U * kSelThreads) {
-          float best[U], need[U];
+          for (int base = tid; !listed && base < front_units; base += U * kSelThreads) {
+            float best[U];
 #pragma unroll
-          for (int q = 0; q < U; q++) {
-            const int u = base + q * kSelThreads;
-            best[q] = -INFINITY; need[q] = INFINITY;
-            if (u < front_units) {
+            for (int q = 0; q < U; q++) {
+              const int u = base + q * kSelThreads;
+              best[q] = -INFINITY;
+              if (u >= front_units) continue;
               int w, k, e;
               entry(u, &w, &k, &e);
               const int v = unit_token(k, e);
+              if (v >= c.V) continue;
               const float* x = c.logits + ((size_t)b * c.W + w) * c.V;
-              if (v + 3 < c.V) { const f32x4u t = *(const f32x4u*)(x + v); best[q] = fmaxf(fmaxf(t.x, t.y), fmaxf(t.z, t.w)); }
-              else if (v < c.V) best[q] = INFINITY;          // (the row's last tokens are looked at one by one below)
-              need[q] = needed(w);
+              uint32_t bits = 0xfu;
+              if (c.blob) bits = (c.step == 0 ? mv.l0 : mv.l1 + (size_t)s_ra[w] * mv.words)[v >> 5] >> (v & 31);
+              f32x4u y;
+              if (v + 3 < c.V) y = *(const f32x4u*)(x + v);
+              else { y.x = x[v]; y.y = x[min(v + 1, c.V - 1)]; y.z = x[min(v + 2, c.V - 1)]; y.w = y.z; }
+              // (past the row's end a mask has no bits; without one the last token is taken again, which changes nothing here)
+              best[q] = fmaxf(fmaxf(bits & 1u ? y.x : -INFINITY, bits & 2u ? y.y : -INFINITY), fmaxf(bits & 4u ? y.z : -INFINITY, bits & 8u ? y.w : -INFINITY));
+              best[q] = __fadd_rn(s_rbias[w], best[q]);
             }
+#pragma unroll
+            for (int q = 0; q < U; q++) count(base + q * kSelThreads, best[q]);
           }
-#pragma unroll
-          for (int q = 0; q < U; q++)
-            if (best[q] >= need[q]) keep(base + q * kSelThreads);
-        }
-      } else {
-        constexpr int U = 4;
 #pragma unroll 1
-        for (int base = tid; base < front_units; base += U * kSelThreads) {
-          float best[U], need[U];
+          for (int u = tid; listed && u < front_units; u += kSelThreads) {
+            int w, k, e;
+            entry(u, &w, &k, &e);
+            count(u, __fadd_rn(s_rbias[w], child_best(w, k, e)));
+          }
+          __syncthreads();
+          hist_threshold_all(s_hist, (uint32_t)c.W, &s_thr, s_redu, paru);
+          __syncthreads();
+          T = fmaxf(T, bins.floor_of(s_thr));
+        }
+        if (by_unit && front_units <= kGroupCap) {
+#pragma unroll 1
+          for (int u = tid; u < front_units; u += kSelThreads)
+            if (s_group[u] >= T) keep(u);
+        } else if (!listed) {
+          constexpr int U = 4;
+#pragma unroll 1
+          for (int base = tid; base < front_units; base += U * kSelThreads) {
+            float best[U], bias[U];
 #pragma unroll
-          for (int q = 0; q < U; q++) {
-            const int u = base + q * kSelThreads;
-            best[q] = -INFINITY; need[q] = INFINITY;
-            if (u < front_units) {
-              int w, k, e;
-              entry(u, &w, &k, &e);
-              const int at = k + kUnitSpan * e, cnt = s_rinfo[w] >> 2;
-              const float* x = c.logits + ((size_t)b * c.W + w) * c.V;
-              const int32_t* list = child_list(c, mv) + s_ra[w];
-              if (at < cnt) {
-                const float y0 = x[list[at]], y1 = x[list[min(at + 64, cnt - 1)]], y2 = x[list[min(at + 128, cnt - 1)]], y3 = x[list[min(at + 192, cnt - 1)]];
-                best[q] = fmaxf(fmaxf(y0, y1), fmaxf(y2, y3));     // (a child taken twice changes nothing here)
+            for (int q = 0; q < U; q++) {
+              const int u = base + q * kSelThreads;
+              best[q] = -INFINITY; bias[q] = 0.f;
+              if (u < front_units) {
+                int w, k, e;
+                entry(u, &w, &k, &e);
+                const int v = unit_token(k, e);
+                const float* x = c.logits + ((size_t)b * c.W + w) * c.V;
+                if (v + 3 < c.V) { const f32x4u t = *(const f32x4u*)(x + v); best[q] = fmaxf(fmaxf(t.x, t.y), fmaxf(t.z, t.w)); }
+                else if (v < c.V) best[q] = INFINITY;        // (the row's last tokens are looked at one by one below)
+                bias[q] = s_rbias[w];
               }
-              need[q] = needed(w);
             }
+#pragma unroll
+            for (int q = 0; q < U; q++)
+              if (__fadd_rn(bias[q], best[q]) >= T) keep(base + q * kSelThreads);
           }
-#pragma unroll
-          for (int q = 0; q < U; q++)
-            if (best[q] >= need[q]) keep(base + q * kSelThreads);
-        }
-      }
-      __syncthreads();
-      fallback = s_nu > (uint32_t)kUnitCap;
-    }
-    if (!fallback) {
-      // ---- their candidates, counted in bins over what is above the threshold.  When they do not fit, the bins still tell
-      // where the W best end, and a second round takes only those.
-      const int nu = (int)s_nu, units = nu + ns;
-      const float scale_n = T > -INFINITY ? fmaxf(64.f, bin_scale(hi - T)) : 64.f;
-      int cut = kHistBins - 1;
+        } else {
+          constexpr int U = 4;
 #pragma unroll 1
-      for (int round = 0; round < 2; round++) {
-#pragma unroll 1
-        for (int i = tid; i < units; i += kSelThreads) {
-          const uint32_t unit = i < nu ? s_units[i] : 0u;
-          const uint32_t ent = s_chunks[i < nu ? (int)(unit >> 8) : kChunkCap - 1 - (i - nu)];
-          const int w = (int)(ent >> 8), k = (int)(ent & 255u), cnt = s_rinfo[w] >> 2;
-          const float* xrow = c.logits + ((size_t)b * c.W + w) * c.V;
-          int place, stride = 1, end = cnt;                  // the unit's candidates: place, place + stride, ... < end
-          float bias = s_rbias[w], y[4];
-          uint32_t bits = 0xfu;
-          if (i < nu && !listed) {
-            place = unit_token(k, (int)(unit & 255u));
-            end = c.V;
-            if (c.blob && c.step == 0) bits = mv.l0[place >> 5] >> (place & 31);
-            else if (c.blob && c.step == 1) bits = mv.l1[(size_t)s_ra[w] * mv.words + (place >> 5)] >> (place & 31);
+          for (int base = tid; base < front_units; base += U * kSelThreads) {
+            float best[U], bias[U];
 #pragma unroll
-            for (int j = 0; j < 4; j++) y[j] = xrow[min(place + j, c.V - 1)];
-          } else if (i >= nu) {
-            place = 4 * k;
-            bias = 0.f;                                      // (these scores are complete)
-            const float4 t = *(const float4*)(data + (size_t)w * kRowFloats + place);
-            y[0] = t.x; y[1] = t.y; y[2] = t.z; y[3] = t.w;
-          } else {
-            place = k + kUnitSpan * (int)(unit & 255u);
-            stride = 64;
-            const int32_t* list = child_list(c, mv) + s_ra[w];
-            int tok[4];
-#pragma unroll
-            for (int j = 0; j < 4; j++) tok[j] = list[min(place + 64 * j, cnt - 1)];
-#pragma unroll
-            for (int j = 0; j < 4; j++) y[j] = xrow[tok[j]];
-          }
-#pragma unroll
-          for (int j = 0; j < 4; j++) {
-            const int at = place + j * stride;
-            const float score = __fadd_rn(bias, y[j]);       // (with bias 0 unchanged but for -0, which composite() makes 0)
-            if (at >= end || !((bits >> j) & 1u) || !(score > -INFINITY) || score < T) continue;
-            if (c.blob && c.step == 2 && i < nu && !listed) {           // last level, streamed row: the candidate has to be in the row's child list
-              const int32_t* list = mv.t3 + s_ra[w];
-              const int len = c.range_in[2 * ((size_t)b * c.W + w) + 1] - s_ra[w], pos = lower_bound_i32(list, len, at);
-              if (!(pos < len && list[pos] == at)) continue;
+            for (int q = 0; q < U; q++) {
+              const int u = base + q * kSelThreads;
+              best[q] = -INFINITY; bias[q] = 0.f;
+              if (u < front_units) {
+                int w, k, e;
+                entry(u, &w, &k, &e);
+                best[q] = child_best(w, k, e);
+                bias[q] = s_rbias[w];
+              }
             }
-            const int bin = key_bin(hi, scale_n, score);
-            if (bin > cut) continue;
-            if (round == 0) atomicAdd(&s_hist[bin], 1u);
-            const uint32_t pos = atomicAdd(&s_n, 1u);
-            if (pos < (uint32_t)kListCap) s_list[pos] = composite(score, (uint32_t)w * (uint32_t)c.V + (uint32_t)at);
+#pragma unroll
+            for (int q = 0; q < U; q++)
+              if (__fadd_rn(bias[q], best[q]) >= T) keep(base + q * kSelThreads);
           }
         }
         __syncthreads();
-        n = (int)s_n;
-        if (round == 0) {
-          // exclusive prefix over the bins, in place, and the bin that holds the W-th candidate
-          constexpr int per = kHistBins / kSelThreads;
-          uint32_t h[per], sum = 0;
+        const int nu = (int)s_nu, units = nu + ns;
+        scale = T > kNoThreshold ? 0.f : 64.f;
+        if (T > kNoThreshold && hi > T) scale = fminf((float)(kHistBins - 1) / (hi - T), 1e30f);
+        fallback = nu > kUnitCap;
+        if (!fallback) {
+          // ---- their candidates, counted in bins of one width from the best score down to the threshold
+#pragma unroll 1
+          for (int i = tid; i < units; i += kSelThreads) {
+            const uint32_t unit = i < nu ? s_units[i] : 0u;
+            const uint32_t ent = s_chunks[i < nu ? (int)(unit >> 8) : kChunkCap - 1 - (i - nu)];
+            const int w = (int)(ent >> 8), k = (int)(ent & 255u), cnt = s_rinfo[w] >> 2;
+            const float* xrow = c.logits + ((size_t)b * c.W + w) * c.V;
+            int place, stride = 1, end = cnt;                // the unit's candidates: place, place + stride, ... < end
+            float bias = s_rbias[w], y[4];
+            uint32_t bits = 0xfu;
+            if (i < nu && !listed) {
+              place = unit_token(k, (int)(unit & 255u));
+              end = c.V;
+              if (c.blob && c.step == 0) bits = mv.l0[place >> 5] >> (place & 31);
+              else if (c.blob && c.step == 1) bits = mv.l1[(size_t)s_ra[w] * mv.words + (place >> 5)] >> (place & 31);
 #pragma unroll
-          for (int k = 0; k < per; k++) { h[k] = s_hist[tid * per + k]; sum += h[k]; }
-          uint32_t total;
-          uint32_t run = block_excl_scan<NW>(sum, &total, s_redu, paru);
-          if (tid == 0 && total < (uint32_t)c.W) s_thr = kHistBins - 1;
+              for (int j = 0; j < 4; j++) y[j] = xrow[min(place + j, c.V - 1)];
+            } else if (i >= nu) {
+              place = 4 * k;
+              bias = 0.f;                                    // (these scores are complete)
+              const float4 t = *(const float4*)(data + (size_t)w * kRowFloats + place);
+              y[0] = t.x; y[1] = t.y; y[2] = t.z; y[3] = t.w;
+            } else {
+              place = k + kUnitSpan * (int)(unit & 255u);
+              stride = 64;
+              const int32_t* list = child_list(c, mv) + s_ra[w];
+              int tok[4];
 #pragma unroll
-          for (int k = 0; k < per; k++) {
-            s_hist[tid * per + k] = run;
-            if (run < (uint32_t)c.W && run + h[k] >= (uint32_t)c.W) s_thr = tid * per + k;
-            run += h[k];
+              for (int j = 0; j < 4; j++) tok[j] = list[min(place + 64 * j, cnt - 1)];
+#pragma unroll
+              for (int j = 0; j < 4; j++) y[j] = xrow[tok[j]];
+            }
+#pragma unroll
+            for (int j = 0; j < 4; j++) {
+              const int at = place + j * stride;
+              const float score = __fadd_rn(bias, y[j]);     // (with bias 0 unchanged but for -0, which composite() makes 0)
+              if (at >= end || !((bits >> j) & 1u) || !(score >= T)) continue;
+              if (c.blob && c.step == 2 && i < nu && !listed) {        // last level, streamed row: the candidate has to be in the row's child list
+                const int32_t* list = mv.t3 + s_ra[w];
+                const int len = c.range_in[2 * ((size_t)b * c.W + w) + 1] - s_ra[w], pos = lower_bound_i32(list, len, at);
+                if (!(pos < len && list[pos] == at)) continue;
+              }
+              atomicAdd(&s_hist[key_bin(hi, scale, score)], 1u);
+              const uint32_t pos = atomicAdd(&s_n, 1u);
+              if (pos < (uint32_t)kListCap) s_list[pos] = composite(score, (uint32_t)w * (uint32_t)c.V + (uint32_t)at);
+            }
           }
-          if (n > kListCap && tid == 0) s_n = 0;
           __syncthreads();
-          cut = s_thr;
+          n = (int)s_n;
+          fallback = n > kListCap;
         }
-        if (n <= kListCap) break;
+        if (__builtin_expect(!fallback || by_unit || !countable, 1)) break;
+        // more than there is room for: once again above the threshold that the units yield
+        by_unit = true;
+        fallback = false;
+        __syncthreads();
+        if (tid == 0) { s_nu = 0; s_n = 0; }
+        for (int i = tid; i < kHistBins; i += kSelThreads) s_hist[i] = 0;
+        __syncthreads();
       }
+    }
+    if (!fallback) {
       // ---- order them (descending composite key = score descending, flat index ascending).  Histogram bins are ordered by
       // score, so a survivor's place is the number of survivors in better bins plus its rank inside its own (tiny) bin.
       // Counting sort by bin, then every survivor counts the larger keys of its bin.  Exact ties share a bin and are ranked
       // by the key's flat-index half there.
-      auto bin_of = [&](uint64_t key) { return key_bin(hi, scale_n, gr_ordkey_inv((uint32_t)(key >> 32))); };
-      fallback = n > kListCap;
-      int m = 0;                                             // survivors up to the W-th one's bin
-      if (!fallback) {
-        m = cut < kHistBins - 1 ? (int)s_hist[cut + 1] : n;
-        fallback = m > kTmpCap;
+      auto score_of = [&](uint64_t key) { return gr_ordkey_inv((uint32_t)(key >> 32)); };
+      auto bin_of = [&](uint64_t key) { return key_bin(hi, scale, score_of(key)); };
+      if (__builtin_expect(T == kNoThreshold && s_hist[kHistBins - 1] > 64u, 0)) {     // (no threshold, and many lie below the bins: down to the worst of them)
+        float mx = -INFINITY, mn = INFINITY;
+        for (int i = tid; i < n; i += kSelThreads) mn = fminf(mn, score_of(s_list[i]));
+        __syncthreads();
+        for (int i = tid; i < kHistBins; i += kSelThreads) s_hist[i] = 0;
+        block_max_min<NW>(mx, mn, s_redf, parf);             // (its barrier: the histogram is clear)
+        scale = hi > mn ? fminf((float)(kHistBins - 1) / (hi - mn), 1e30f) : 0.f;
+        for (int i = tid; i < n; i += kSelThreads) atomicAdd(&s_hist[bin_of(s_list[i])], 1u);
+        __syncthreads();
       }
+      // exclusive prefix over the bins, in place, and the bin that holds the W-th candidate
+      constexpr int per = kHistBins / kSelThreads;
+      uint32_t h[per], sum = 0;
+#pragma unroll
+      for (int k = 0; k < per; k++) { h[k] = s_hist[tid * per + k]; sum += h[k]; }
+      uint32_t total;
+      uint32_t run = block_excl_scan<NW>(sum, &total, s_redu, paru);
+      if (tid == 0 && total < (uint32_t)c.W) s_thr = kHistBins - 1;
+#pragma unroll
+      for (int k = 0; k < per; k++) {
+        s_hist[tid * per + k] = run;
+        if (run < (uint32_t)c.W && run + h[k] >= (uint32_t)c.W) s_thr = tid * per + k;
+        run += h[k];
+      }
+      __syncthreads();
+      const int cut = s_thr, m = cut < kHistBins - 1 ? (int)s_hist[cut + 1] : n;       // survivors up to the W-th one's bin
+      fallback = m > kTmpCap;
       if (!fallback) {
-        __syncthreads();                                     // (s_hist[cut + 1] is read before any counter moves; the units are done with)
+        __syncthreads();                                     // (s_hist[cut + 1] is read before any counter moves)
 #pragma unroll 1
         for (int i = tid; i < n; i += kSelThreads) {
           const uint64_t key = s_list[i];
@@ -1307,7 +1391,8 @@ extern "C" gr_status gr_beam_select(const gr_select_params* p, void* workspace, 
   char* ws = (char*)workspace;
   c.row_bias = (float*)ws;                 ws += gr_align256(rows * 4);
   c.row_info = (int32_t*)ws;               ws += gr_align256(rows * 4);
-  c.row_start = (int32_t*)ws;              ws += gr_align256(rows * 4);
+  c.row_start = (int32_t*)ws;
+  c.row_best = (float*)ws;                 ws += gr_align256(rows * 4);
   c.row_group = (float*)ws;                ws += rows * kGroups * 4;       // (whole 64 bytes a row: row_data stays 16-byte aligned)
   c.row_data = (float*)ws;
 

@@ -154,3 +154,90 @@ def test_a_range_no_mask_produces_has_no_children(gr, oracle_lib, flags):  # noq
     live = sc.copy()
     live[0, bad] = -np.inf
     assert_select_equal(run_select(gr, mask, logits, sc, pf, rg, 2, flags), oracle_lib.beam_select(items, logits, live, pf, 2))
+
+
+def _second_level(rng, W, V, widths, items, oracle_lib):
+    """Inputs of the step after a first one: beams as the oracle selects them from logits of widths[0], logits of widths[1]."""
+    sc, pf, rg = gr_synth.initial_beam_state(1, W, 3)
+    logits = (widths[0] * rng.standard_normal((1, W, V))).astype(np.float32)
+    first = oracle_lib.beam_select(items, logits, sc, pf, 0)
+    logits = (widths[1] * rng.standard_normal((1, W, V))).astype(np.float32)
+    return logits, first["scores"], first["prefix"], first["range"]
+
+
+# widths of the logits at the first and the second level: few beams far ahead of the others, all close together, far apart
+_WIDTHS = [(6.0, 1.0), (10.0, 2.0), (0.05, 0.05), (20.0, 20.0)]
+
+
+@pytest.mark.parametrize("widths", _WIDTHS)
+@pytest.mark.parametrize("W,V", [(128, 8192), (512, 8192), (300, 20000), (1100, 2000), (2048, 1024)])
+def test_spread_of_beam_scores_without_a_mask(gr, oracle_lib, W, V, widths):  # noqa: F811
+    logits, sc, pf, rg = _second_level(np.random.default_rng(W + V), W, V, widths, None, oracle_lib)
+    assert_select_equal(run_select(gr, None, logits, sc, pf, rg, 1), oracle_lib.beam_select(None, logits, sc, pf, 1))
+
+
+@pytest.mark.parametrize("widths", _WIDTHS)
+@pytest.mark.parametrize("first,children,W", [(5, 5000, 256), (8, 8192, 512), (8, 8192, 2048), (40, 3000, 256), (600, 700, 512), (64, 200, 300), (9, 100, 1200)])
+def test_spread_of_beam_scores_with_few_first_tokens(gr, oracle_lib, first, children, W, widths):  # noqa: F811
+    rng = np.random.default_rng(first + W)
+    V = 8192
+    items = np.array([(13 * t1, t2, 5) for t1, lst in enumerate(_children(rng, V, [children] * first)) for t2 in lst], dtype=np.int32)
+    mask = gr.gr_item_mask_build(to_dev(items), V)
+    logits, sc, pf, rg = _second_level(rng, W, V, widths, items, oracle_lib)
+    assert_select_equal(run_select(gr, mask, logits, sc, pf, rg, 1), oracle_lib.beam_select(items, logits, sc, pf, 1))
+
+
+@pytest.mark.parametrize("low", [-np.inf, np.finfo(np.float32).min, -1e9, -65504.0])
+@pytest.mark.parametrize("W,live", [(128, 1), (128, 128), (700, 10)])
+def test_filtered_logits(gr, oracle_lib, W, live, low):  # noqa: F811
+    # 50 tokens of every row are left by a filter, the others are set to a lowest value that is a candidate of its own where finite
+    rng = np.random.default_rng(W)
+    V = 4100
+    logits = np.full((2, W, V), low, np.float32)
+    for b in range(2):
+        for w in range(W):
+            logits[b, w, rng.choice(V, size=50, replace=False)] = 2.0 * rng.standard_normal(50)
+    sc = np.full((2, W), -np.inf, np.float32)
+    sc[:, :live] = -rng.random((2, live))
+    pf = np.full((2, W, 3), -1, np.int32)
+    rg = np.zeros((2, W, 2), np.int32)
+    for step in (0, 1):
+        pf[:, :, :step] = 0
+        assert_select_equal(run_select(gr, None, logits, sc, pf, rg, step), oracle_lib.beam_select(None, logits, sc, pf, step), f"step {step}")
+
+
+def test_spread_of_beam_scores_does_not_change_the_time(gr):  # noqa: F811
+    # the exact fallback takes 20 times as long as the selection it stands in for; it is for ties, not for score distributions
+    import torch
+    B, W, V = 8, 512, 8192
+    g = torch.Generator(device="cuda:0")
+
+    def time(widths, mask):
+        g.manual_seed(7)
+        sc = torch.full((B, W), -np.inf, device="cuda:0")
+        sc[:, 0] = 0.0
+        beams = dict(scores=sc, prefix=torch.full((B, W, 3), -1, dtype=torch.int32, device="cuda:0"),
+                     range=torch.zeros(B, W, 2, dtype=torch.int32, device="cuda:0"))
+        for step in (0, 1):
+            x = torch.empty(B, W, V, device="cuda:0").normal_(generator=g).mul_(widths[step])
+            run = lambda: gr.gr_beam_select(mask, x, beams["scores"], beams["prefix"], beams["range"], step)
+            after = run()
+            if step == 1:
+                best = np.inf
+                for _ in range(5):
+                    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+                    a.record()
+                    for _ in range(5):
+                        run()
+                    b.record()
+                    b.synchronize()
+                    best = min(best, a.elapsed_time(b))
+            beams = after
+        return best
+
+    children = _children(np.random.default_rng(1), V, [5000] * 12)
+    mask = gr.gr_item_mask_build(to_dev(np.array([(t1, t2, 5) for t1, lst in enumerate(children) for t2 in lst], dtype=np.int32)), V)
+    usual = time((3.0, 3.0), None)
+    for widths in [(3.0, 1.0)] + _WIDTHS:
+        assert time(widths, None) < 5 * usual, widths
+        assert time(widths, mask) < 5 * usual, widths
