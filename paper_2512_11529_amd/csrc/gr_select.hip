@@ -26,16 +26,14 @@ constexpr int kGroups = 16;         // groups of a row's candidates; the best sc
 // and, per row, this many floats of finer data behind them:
 //   streamed row: 256 keys of 16 bits, one for every line of 32 consecutive logits of a block (how far its best score is below the row's);
 //   gathered row with at most kScoreMax children: all of their scores;
-//   gathered row with more: 64 keys (children k, k + 64, ...).
+//   gathered row with more: up to 256 such keys, one for every 8 << key_shift(n) consecutive children.
 constexpr int kRowFloats = 240;
 constexpr int kLines = 256;
-constexpr int kKeys = 64;
 constexpr int kScoreMax = kRowFloats;
 constexpr int kWaveMax = 1024;      // a row with at most this many children is gathered by one wavefront, one with more by a workgroup
 constexpr int kSelThreads = 1024;
 constexpr int kListCap = 8192;      // survivors that fit in LDS
 constexpr int kChunkCap = 4096;     // keys whose candidates are looked at again by the fast path
-constexpr int kUnitSpan = 256;      // children that one unit of four, 64 apart, reaches over
 constexpr int kUnitCap = 8192;      // units of four candidates that are
 constexpr int kHistBins = 2048;
 constexpr int kMaxMaskWords = 1024; // V <= 32768
@@ -64,7 +62,6 @@ struct SelCtx {
   float* row_bias;           // workspace [B*W]
   int32_t* row_info;         // workspace [B*W]
   int32_t* row_start;        // workspace [B*W]: first child of a gathered row in the pair list (level 1) or in the table (level 2)
-  float* row_best;           // the same words: best score of a streamed row
   float* row_group;          // workspace [B*W*kGroups]
   float* row_data;           // workspace [B*W*kRowFloats]
 };
@@ -100,6 +97,14 @@ __device__ __forceinline__ MaskView mask_view(const char* blob, int V, int depth
   m.n_items = h->n_items;
   m.ok = h->magic == GR_MASK_MAGIC && h->V == V && h->depth == depth;
   return m;
+}
+
+// The kernel's arguments, read where this stands and not before.
+typedef const __attribute__((address_space(4))) SelCtx* LateArgs;
+__device__ __forceinline__ LateArgs late_args() {
+  LateArgs a = (LateArgs)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(a));
+  return a;
 }
 
 // The valid children of a beam row (steps 1 and 2): entries [start, start + n) of the pair list or of the table.  A prefix
@@ -191,7 +196,7 @@ template <int CTRL>
 __device__ __forceinline__ float dpp_f32(float v) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
 }
-constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kHalfMirror = 0x141, kMirror = 0x140;
+constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kHalfMirror = 0x141, kMirror = 0x140, kXor8 = 0x128;       // (row_ror:8)
 __device__ __forceinline__ float quad_max(float v) {
   v = max_raw(v, dpp_f32<kXor1>(v));
   return max_raw(v, dpp_f32<kXor2>(v));
@@ -202,6 +207,21 @@ __device__ __forceinline__ float wave_max(float v) {
   v = max_raw(v, dpp_f32<kHalfMirror>(v));
   v = max_raw(v, dpp_f32<kMirror>(v));
   return max_raw(max_raw(lane_f32(v, 0), lane_f32(v, 16)), max_raw(lane_f32(v, 32), lane_f32(v, 48)));
+}
+// The maximum over eight lanes of each of several values, in exchange steps (the first mirrored, so that every step stays inside the
+// eight lanes) that each halve the values a lane still carries: `a` is carried on by lanes without the bit, `b` by lanes with it.
+template <int CTRL>
+__device__ __forceinline__ float half_max(float a, float b, bool bit) { return max_raw(bit ? b : a, dpp_f32<CTRL>(bit ? a : b)); }
+// eight values: a lane ends with value 4 (bit 2) + 2 (bit 0) + (bit 1) of its number
+__device__ __forceinline__ float best_of_eight(const float (&x)[8]) {
+  const int lane = threadIdx.x;
+  const bool b2 = lane & 4, b0 = lane & 1, b1 = lane & 2;
+  float u[4], v[2];
+#pragma unroll
+  for (int i = 0; i < 4; i++) u[i] = half_max<kHalfMirror>(x[i], x[i + 4], b2);
+#pragma unroll
+  for (int i = 0; i < 2; i++) v[i] = half_max<kXor1>(u[i], u[i + 2], b0);
+  return half_max<kXor2>(v[0], v[1], b1);
 }
 template <int CTRL>
 __device__ __forceinline__ double dpp_f64(double v) {
@@ -436,30 +456,17 @@ __device__ __forceinline__ void row_dense(const SelCtx& c, const MaskView& mv, R
   }
   S = wave_sum(S);
   if ((tid & 63) == 0) { L.m[set][wave] = m; L.s[set][wave] = S; }
-  // The best logit of every line = of eight neighbouring threads, for each of their NV4 loads: three exchange steps (first mirrored,
-  // so that every step stays inside eight lanes), each halving the values a lane still carries while there are several.
+  // The best logit of every line = of eight neighbouring threads, for each of their NV4 loads.
   {
     const bool b2 = tid & 4, b0 = tid & 1, b1 = tid & 2;
-    auto half = [&](float a, float b, bool bit, auto&& partner) {     // a for lanes without the bit, b for lanes with it
-      const float keep = bit ? b : a, send = bit ? a : b;
-      return max_raw(keep, partner(send));
-    };
-    auto mirror = [](float v) { return dpp_f32<kHalfMirror>(v); };
-    auto xor1 = [](float v) { return dpp_f32<kXor1>(v); };
-    auto xor2 = [](float v) { return dpp_f32<kXor2>(v); };
     float* key = L.key[set] + (tid >> 3) * NV4;
-    if (NV4 == 8) {
-      float u[4], v[2];
-#pragma unroll
-      for (int i = 0; i < 4; i++) u[i] = half(lmax[i], lmax[i + NV4 / 2], b2, mirror);
-#pragma unroll
-      for (int i = 0; i < 2; i++) v[i] = half(u[i], u[i + 2], b0, xor1);
-      key[4 * b2 + 2 * b0 + b1] = half(v[0], v[1], b1, xor2);
+    if constexpr (NV4 == 8) {
+      key[4 * b2 + 2 * b0 + b1] = best_of_eight(lmax);
     } else {
       float v[2];
 #pragma unroll
-      for (int i = 0; i < 2; i++) v[i] = half(lmax[i], lmax[i + 2], b2, mirror);
-      float r = half(v[0], v[1], b0, xor1);
+      for (int i = 0; i < 2; i++) v[i] = half_max<kHalfMirror>(lmax[i], lmax[i + 2], b2);
+      float r = half_max<kXor1>(v[0], v[1], b0);
       r = max_raw(r, dpp_f32<kXor2>(r));
       if (!b1) key[2 * b2 + b0] = r;
     }
@@ -477,7 +484,7 @@ __device__ __forceinline__ void row_dense(const SelCtx& c, const MaskView& mv, R
   const float lse = (float)((double)M + log(T));
   const float bias = __fsub_rn(s_in, lse);
   const float best = __fadd_rn(bias, M);
-  if (tid == 0) { c.row_bias[row] = bias; c.row_info[row] = ROW_DENSE; c.row_best[row] = best; }
+  if (tid == 0) { c.row_bias[row] = bias; c.row_info[row] = ROW_DENSE; }
   const float4 kl = *(const float4*)&L.key[set][4 * tid];
   const float k0 = __fadd_rn(bias, kl.x), k1 = __fadd_rn(bias, kl.y), k2 = __fadd_rn(bias, kl.z), k3 = __fadd_rn(bias, kl.w);      // (bias is finite)
   uint2 packed;
@@ -491,38 +498,56 @@ __device__ __forceinline__ void row_dense(const SelCtx& c, const MaskView& mv, R
 // ------------------------------------------------------------------------------------------------
 // Rows whose valid children are listed (Section 6.1's sparse form): only the valid logits are gathered, 512 at a time, by one
 // wavefront or by the four of a workgroup.  A row with at most kScoreMax children leaves every candidate's score, its groups
-// are of 16 children; one with more leaves one key per lane (children lane, lane + 64, ...), its groups are of four lanes.
+// are of 16 children; one with more leaves a key for every few consecutive children, as a streamed row does for its lines:
+// what is read again of it lies together in the child list and, where the list is dense, in the row.  (With 64 keys a row, of
+// children 64 apart, k_select took 93 us where 256 beams of each of 16 requests had 8192 children, now 24 us.)
 // ------------------------------------------------------------------------------------------------
 constexpr int kPartU = 8, kPart = 64 * kPartU;
 struct GatherPart {
   float x[kPartU];           // the last kPart logits of this wavefront (all of a short row), -inf past the end
-  float best, m;             // best logit of this lane, of the wavefront
+  float m;                   // best logit of the wavefront
   double S;                  // the wavefront's sum relative to m
 };
+// log2 of the eights of consecutive children behind a key: at most kLines keys
+__device__ __forceinline__ int key_shift(int n) { return n <= 8 * kLines ? 0 : 21 - __clz(n - 1); }
+// keys of a row and log2 of the keys of a group (at most kGroups groups)
+__device__ __forceinline__ int key_count(int n) { return ((n - 1) >> (3 + key_shift(n))) + 1; }
+__device__ __forceinline__ int group_shift(int keys) { return keys <= 4 * kGroups ? 2 : keys <= 8 * kGroups ? 3 : 4; }
+
 __device__ __forceinline__ void gather_part(GatherPart& g, const float* x, const int32_t* list, int n, int first, int step, const double* tab,
-                                            const ExpK& ek) {
-  const int lane = threadIdx.x & 63;
-  int tok[kPartU];
+                                            const ExpK& ek, float* keys) {
+  const int lane = threadIdx.x & 63, ks = key_shift(n);
+  uint32_t tok[kPartU];      // (row and list at most 128 KB: 32-bit offsets from addresses that all lanes share)
+  auto child = [&](int i) { return *(const uint32_t*)((const char*)list + 4u * (uint32_t)min(i + lane, n - 1)); };
   double S = 0.0;
-  g.best = -INFINITY; g.m = -INFINITY;
+  g.m = -INFINITY;
 #pragma unroll
   for (int k = 0; k < kPartU; k++)
-    if (first + 64 * k < n) tok[k] = list[min(first + lane + 64 * k, n - 1)];
+    if (first + 64 * k < n) tok[k] = child(first + 64 * k);
 #pragma unroll 1
   for (int base = first; base < n; base += step) {
 #pragma unroll
     for (int k = 0; k < kPartU; k++)
-      if (base + 64 * k < n) g.x[k] = x[tok[k]];             // (uniform; the rest becomes -inf below)
+      if (base + 64 * k < n) g.x[k] = *(const float*)((const char*)x + 4u * tok[k]);       // (uniform; the rest becomes -inf below)
 #pragma unroll
     for (int k = 0; k < kPartU; k++)
-      if (base + step + 64 * k < n) tok[k] = list[min(base + step + lane + 64 * k, n - 1)];
+      if (base + step + 64 * k < n) tok[k] = child(base + step + 64 * k);
     float bmax = -INFINITY;
 #pragma unroll
     for (int k = 0; k < kPartU; k++) {
       if (base + 64 * k + lane >= n) g.x[k] = -INFINITY;
       bmax = max_raw(bmax, g.x[k]);
     }
-    g.best = max_raw(g.best, bmax);
+    if (n > kScoreMax) {
+      // the best of children base + 64 k + 8 (lane / 8) .. + 7, then of as many eights of these as belong to a key
+      float v = best_of_eight(g.x);
+      const int k = (lane & 4) + 2 * (lane & 1) + ((lane >> 1) & 1);
+      if (ks > 0) v = max_raw(v, dpp_f32<kXor8>(v));
+      if (ks > 1) v = max_raw(v, __shfl_xor(v, 16, 64));
+      if (ks > 2) v = max_raw(v, __shfl_xor(v, 32, 64));
+      if (ks > 3) v = max_raw(v, dpp_f32<kXor2>(v));
+      keys[((base >> 3) + 8 * k + (lane >> 3)) >> ks] = v;
+    }
     const float mn = max_raw(g.m, wave_max(bmax)), lo = mn - 600.f;
     const double rn = -(double)mn * ek.c;
     if (mn > -INFINITY) {                                    // (before the first finite logit S is 0, and rn infinite)
@@ -535,8 +560,8 @@ __device__ __forceinline__ void gather_part(GatherPart& g, const float* x, const
   }
   g.S = wave_sum(S);
 }
-// What a row leaves, from its (m, S), every lane's best logit, and the logits of a short row; one wavefront.
-__device__ __forceinline__ void gather_done(const SelCtx& c, const GatherPart& g, int row, float s_in, int start, int n) {
+// What a row leaves, from its (m, S), the logits of a short row and the best logits of a long one's keys; one wavefront.
+__device__ __forceinline__ void gather_done(const SelCtx& c, const GatherPart& g, int row, float s_in, int start, int n, const float* keys) {
   const int lane = threadIdx.x & 63;
   if (!(g.m > -INFINITY)) {
     if (lane == 0) mark_dead(c, row);
@@ -560,34 +585,52 @@ __device__ __forceinline__ void gather_done(const SelCtx& c, const GatherPart& g
       }
     }
   } else {
-    const float key = (g.best > -INFINITY) ? __fadd_rn(bias, g.best) : -INFINITY, best = quad_max(key);
-    data[lane] = key;
-    if ((lane & 3) == 0) group[lane >> 2] = best;
+    const int nk = key_count(n), gs = group_shift(nk) - 2;
+    const float best = __fadd_rn(bias, g.m);
+    float v[4];
+#pragma unroll
+    for (int j = 0; j < 4; j++) v[j] = 4 * lane + j < nk ? __fadd_rn(bias, keys[4 * lane + j]) : -INFINITY;
+    uint2 packed;
+    packed.x = key16(best, v[0]) | (key16(best, v[1]) << 16);
+    packed.y = key16(best, v[2]) | (key16(best, v[3]) << 16);
+    *(uint2*)(data + 2 * lane) = packed;
+    float top = max_raw(max_raw(v[0], v[1]), max_raw(v[2], v[3]));       // of the keys of a group: this lane's, or of two or four lanes
+    if (gs > 0) top = max_raw(top, dpp_f32<kXor1>(top));
+    if (gs > 1) top = max_raw(top, dpp_f32<kXor2>(top));
+    if ((lane & ((1 << gs) - 1)) == 0 && (lane >> gs) < kGroups) group[lane >> gs] = top;
   }
 }
 
 // Levels 1 and 2 with a mask.  Bound: cache lines drawn at random (32 x 256 beams, V = 8192, Zipf table, level 1: 165 MB of lines
 // in 46 us; what a row's children share no line with is wasted).  Lists up to 8192 children are gathered too: streaming the
 // long ones needs a second kind of workgroup, and whatever share was streamed (above 512, 1024 or 2048 children) the call
-// took as long.  Level 2, where nearly every row has one or two children, takes 9 us (19 us when every row also had a
-// workgroup for the case that it has to be streamed).
+// took as long.  Level 2, where nearly every row has one or two children, takes 10 us (19 us when every row also had a
+// workgroup for the case that it has to be streamed).  Lists as long as the row are where streaming was ahead: 16 x 256 rows of
+// 8192 children take 47 us (39 us streamed), 16 x 8 of them 14 us (15 us).
 //
 // A row per wavefront, then the workgroup's long rows by all of its wavefronts.
 constexpr int kGatherWaves = 4;
+constexpr int kDeal = 64;
 __global__ void __launch_bounds__(kGatherWaves * 64, 8) k_rows_listed(SelCtx c) {
   __shared__ double s_tab[kExpTab], s_S[2][kGatherWaves];
-  __shared__ float s_in4[kGatherWaves], s_m[2][kGatherWaves], s_best[2][kGatherWaves][64];
+  __shared__ float s_in4[kGatherWaves], s_m[2][kGatherWaves];
+  __shared__ float s_own[kGatherWaves][kLines], s_keys[2][kLines];       // best logits of the keys of a wavefront's own row, of a workgroup's
   __shared__ int s_start[kGatherWaves], s_n[kGatherWaves];
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), row0 = blockIdx.x * kGatherWaves;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // Long rows are neighbours, as a rule: of every 256 rows a workgroup takes four that are 64 apart.  (16 requests of 256 beams whose first
+  // 64 have 8192 children: 41 us an item step, 65 with rows 16 apart.  Not further: rows from the four quarters of a batch of 49 MB of
+  // logits took 16.7 us where these take 13.5.)
+  auto row_of = [&](int w) { return (int)(blockIdx.x / kDeal * kDeal * kGatherWaves + blockIdx.x % kDeal) + kDeal * w; };
   const MaskView mv = mask_view(c.blob, c.V, c.depth);
   float s_in = -INFINITY;
   int start = 0, n = 0;
+  const int own_row = row_of(wave);
   fill_exp_tab(s_tab, kGatherWaves * 64);
-  if (row0 + wave < c.B * c.W) {
-    s_in = c.scores_in[row0 + wave];
-    row_children(c, mv, row0 + wave, &start, &n);
+  if (own_row < c.B * c.W) {
+    s_in = c.scores_in[own_row];
+    row_children(c, mv, own_row, &start, &n);
     if (!(s_in > -INFINITY) || n == 0) {
-      if (lane == 0) mark_dead(c, row0 + wave);
+      if (lane == 0) mark_dead(c, own_row);
       n = 0;
     }
   }
@@ -595,17 +638,24 @@ __global__ void __launch_bounds__(kGatherWaves * 64, 8) k_rows_listed(SelCtx c) 
   __syncthreads();
   const ExpK ek = exp_consts();
   const int32_t* list = child_list(c, mv);
+  // where all rows are long, each wavefront keeps to its own all the same: it has as many parts to go through as with its share of all
+  uint32_t joint = 0;                              // the rows that all wavefronts gather
+#pragma unroll
+  for (int w = 0; w < kGatherWaves; w++) joint |= (uint32_t)(s_n[w] > kWaveMax) << w;
+  joint = __builtin_amdgcn_readfirstlane(joint);
+  if (joint == (1u << kGatherWaves) - 1u) joint = 0;
   int set = 0;
+  n = __builtin_amdgcn_readfirstlane(n);
+  bool own = n > 0 && !((joint >> wave) & 1u);     // first this wavefront's own row, then those
 #pragma unroll 1
-  for (int j = -1; j < kGatherWaves; j++) {        // -1: this wavefront's own row
-    const bool own = j < 0;
-    const int w = own ? wave : j, nw = __builtin_amdgcn_readfirstlane(s_n[w]), sw = __builtin_amdgcn_readfirstlane(s_start[w]);
-    if (own ? (nw == 0 || nw > kWaveMax) : nw <= kWaveMax) continue;
+  for (; own || joint; own = false) {
+    const int w = own ? wave : __ffs(joint) - 1, nw = __builtin_amdgcn_readfirstlane(s_n[w]), sw = __builtin_amdgcn_readfirstlane(s_start[w]), row = row_of(w);
+    if (!own) joint &= joint - 1;
     GatherPart g;
-    gather_part(g, c.logits + (size_t)(row0 + w) * c.V, list + sw, nw, own ? 0 : wave * kPart, own ? kPart : kGatherWaves * kPart, s_tab, ek);
+    float* keys = own ? s_own[wave] : s_keys[set];
+    gather_part(g, c.logits + (size_t)row * c.V, list + sw, nw, own ? 0 : wave * kPart, own ? kPart : kGatherWaves * kPart, s_tab, ek, keys);
     if (!own) {
       if (lane == 0) { s_m[set][wave] = g.m; s_S[set][wave] = g.S; }
-      s_best[set][wave][lane] = g.best;
       __syncthreads();
       const int at = set;
       set ^= 1;
@@ -615,11 +665,10 @@ __global__ void __launch_bounds__(kGatherWaves * 64, 8) k_rows_listed(SelCtx c) 
       g.m = wave_max(mw);
       if (g.m > -INFINITY)
         g.S = wave_sum((lane < kGatherWaves ? s_S[at][lane] : 0.0) * exp_rel(max_raw(mw, g.m - 600.f), -(double)g.m * ek.c, s_tab, ek));
-      g.best = s_best[at][0][lane];
-#pragma unroll
-      for (int v = 1; v < kGatherWaves; v++) g.best = max_raw(g.best, s_best[at][v][lane]);
+    } else {
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     }
-    gather_done(c, g, row0 + w, s_in4[w], sw, nw);
+    gather_done(c, g, row, s_in4[w], sw, nw, keys);
   }
 }
 
@@ -870,7 +919,7 @@ __global__ void __launch_bounds__(kSelThreads) k_select(SelCtx c) {
   float* s_rbias = (float*)(s_chunks + kChunkCap);           // per beam row of the request: bias,
   int32_t* s_rinfo = (int32_t*)(s_rbias + kMaxW);            // mode and child count,
   int32_t* s_ra = s_rinfo + kMaxW;                           // first child (gathered), first token (streamed, level 1) or table range start,
-  float* s_rbest = (float*)(s_ra + kMaxW);                   // and best score (streamed)
+  float* s_rbest = (float*)(s_ra + kMaxW);                   // best score
   constexpr int NW = kSelThreads / 64;
   __shared__ float2 s_redf[2 * NW];
   __shared__ uint32_t s_redu[2 * NW];
@@ -899,7 +948,9 @@ __global__ void __launch_bounds__(kSelThreads) k_select(SelCtx c) {
     if (first + 3 >= ng) g.w = -INFINITY;
     if (gsh == 4) *(float4*)&s_group[4 * q] = g;
     else *(float2*)&s_group[2 * q] = make_float2(fmaxf(g.x, g.y), fmaxf(g.z, g.w));
-    hi = fmaxf(hi, fmaxf(fmaxf(g.x, g.y), fmaxf(g.z, g.w)));
+    const float best = quad_max(fmaxf(fmaxf(g.x, g.y), fmaxf(g.z, g.w)));      // (a row's groups are in four neighbouring lanes)
+    if (first == 0) s_rbest[w] = best;
+    hi = fmaxf(hi, best);
     auto low = [&](float v) { lo = fminf(lo, v > -INFINITY ? v : INFINITY); };
     low(g.x); low(g.y); low(g.z); low(g.w);
   }
@@ -914,7 +965,6 @@ __global__ void __launch_bounds__(kSelThreads) k_select(SelCtx c) {
     s_rbias[w] = c.row_bias[row];
     s_rinfo[w] = info;
     s_ra[w] = (info & 3) == ROW_SPARSE ? start : a;
-    s_rbest[w] = __int_as_float(start);
   }
   if (tid == 0) { s_n = 0; s_nd = 0; s_ns = 0; s_nu = 0; s_most = 0; }
   for (int i = tid; i < kHistBins; i += kSelThreads) s_hist[i] = 0;
@@ -943,79 +993,98 @@ __global__ void __launch_bounds__(kSelThreads) k_select(SelCtx c) {
     bool fallback = ng > kUnitCap;
     const int quarters = min(ng, kUnitCap) << ssh;
     auto quarter = [&](int i) { return ((int)s_units[i >> ssh] << ssh) + (i & ((1 << ssh) - 1)); };      // row << 6 | quarter of the row's 16 groups
+    // the keys of a quarter group of a streamed or long gathered row: the first one's number, and how many
+    auto quarter_keys = [&](const float* fine, int q, int info, int* key, int* num) {
+      const int gs = (info & 3) == ROW_DENSE ? 4 : group_shift(key_count(info >> 2));
+      *num = 1 << (gs - 2);
+      *key = ((q >> 2) << gs) + ((q & 3) << (gs - 2));
+      const uint2 k = *(const uint2*)(fine + 2 * (*key >> 2));
+      return ((uint64_t)k.y << 32 | k.x) >> (16 * (*key & 3));
+    };
+    auto last_key = [&](int w) { return s_rbest[w] < T ? -1 : (int)key16(s_rbest[w], T); };
+    auto add = [&](bool front, int w, int key) {
+      const uint32_t pos = atomicAdd(front ? &s_nd : &s_ns, 1u);
+      if (pos < (uint32_t)kChunkCap) s_chunks[front ? pos : kChunkCap - 1 - pos] = ((uint32_t)w << 8) | (uint32_t)key;
+    };
+    // (an atomic per thread whose row is longer than those before it, not per key: lanes with values of their own go one by one)
+    uint32_t most = 0;
+    auto note_most = [&]() { if (most > 0 && most > *(volatile uint32_t*)&s_most) atomicMax(&s_most, most); };
     // ---- the finer keys behind them that reach it (four threads to a group, one round of loads for all)
-    int nd, ns, sh;
-    bool listed, raised = false;                             // (listed: the keys in front are of gathered rows)
 #pragma unroll 1
-    for (;;) {
-#pragma unroll 1
-      for (int i = tid; i < quarters; i += kSelThreads) {
-        const int at = quarter(i), w = at >> 6, q = at & 63, info = s_rinfo[w], cnt = info >> 2;
-        const float* fine = data + (size_t)w * kRowFloats;
-        auto add = [&](bool front, int key) {
-          const uint32_t pos = atomicAdd(front ? &s_nd : &s_ns, 1u);
-          if (pos < (uint32_t)kChunkCap) s_chunks[front ? pos : kChunkCap - 1 - pos] = ((uint32_t)w << 8) | (uint32_t)key;
-        };
-        if ((info & 3) == ROW_DENSE) {
-          const uint2 k = *(const uint2*)(fine + 2 * q);
-          const float best = s_rbest[w];
-          const int last = best < T ? -1 : (int)key16(best, T);
-          if ((int)(k.x & 0xffffu) <= last) add(true, 4 * q);
-          if ((int)(k.x >> 16) <= last) add(true, 4 * q + 1);
-          if ((int)(k.y & 0xffffu) <= last) add(true, 4 * q + 2);
-          if ((int)(k.y >> 16) <= last) add(true, 4 * q + 3);
-        } else if (cnt <= kScoreMax) {
-          // (the scores of a row's last wavefront of children are -inf past its end; past that they are not written)
-          if (4 * q < cnt) {
-            const float4 k = *(const float4*)(fine + 4 * q);
-            if (fmaxf(fmaxf(k.x, k.y), fmaxf(k.z, k.w)) >= T) add(false, q);
-          }
-        } else if (fine[q] >= T) {
-          add(true, q);
-          atomicMax(&s_most, (uint32_t)cnt);
+    for (int i = tid; i < quarters; i += kSelThreads) {
+      const int at = quarter(i), w = at >> 6, q = at & 63, info = s_rinfo[w], cnt = info >> 2;
+      const float* fine = data + (size_t)w * kRowFloats;
+      if ((info & 3) == ROW_DENSE) {
+        const uint2 k = *(const uint2*)(fine + 2 * q);
+        const int last = last_key(w);
+        if ((int)(k.x & 0xffffu) <= last) add(true, w, 4 * q);
+        if ((int)(k.x >> 16) <= last) add(true, w, 4 * q + 1);
+        if ((int)(k.y & 0xffffu) <= last) add(true, w, 4 * q + 2);
+        if ((int)(k.y >> 16) <= last) add(true, w, 4 * q + 3);
+      } else if (cnt <= kScoreMax) {
+        // (the scores of a row's last wavefront of children are -inf past its end; past that they are not written)
+        if (4 * q < cnt) {
+          const float4 k = *(const float4*)(fine + 4 * q);
+          if (fmaxf(fmaxf(k.x, k.y), fmaxf(k.z, k.w)) >= T) add(false, w, q);
         }
+      } else {
+        const int last = last_key(w);
+        int key, num;
+        uint64_t keys = quarter_keys(fine, q, info, &key, &num);
+#pragma unroll 1
+        for (; num > 0; num--, key++, keys >>= 16)
+          if ((int)(keys & 0xffffu) <= last) { add(true, w, key); most = max(most, (uint32_t)cnt); }
       }
-      __syncthreads();
-      nd = (int)s_nd; ns = (int)s_ns;
-      // units of four candidates behind a key in front: float4 of logits, or children 64 apart
-      listed = s_most > 0;
-      sh = c.unit_shift;
-      if (listed) { sh = 0; while ((kUnitSpan << sh) < (int)s_most) sh++; }
-      // Where the W best are many to a group (few beams far ahead of the others, long rows) the groups' threshold is too low and the
-      // keys' own takes its place, which W of them reach.  The line: 32 requests of 128 beams, 8192 tokens, logits of width 6 and then 1
-      // have 11 keys a beam above the groups' threshold and take 38 us without a mask, 54 us when all of them are looked at.
-      if (raised || fallback || !(nd + ns > kChunkCap || (nd > (listed ? 2 : 4) * c.W && nd << sh > kUnitCap / 2))) break;
-      raised = true;
+    }
+    note_most();
+    __syncthreads();
+    int nd = (int)s_nd, ns = (int)s_ns;
+    // Where the W best are many to a group (few beams far ahead of the others, long rows) the groups' threshold is too low and the
+    // keys' own takes its place, which W of them reach: they are counted, then listed again.  The line: 32 requests of 128 beams, 8192
+    // tokens, logits of width 6 and then 1 have 11 keys a beam above the groups' threshold and take 37 us without a mask, 54 us when
+    // all of them are looked at; gathered keys cost more lines of memory each.
+    if (__builtin_expect(!fallback && (nd + ns > kChunkCap || nd > c.W + (s_most > 0 ? 256 : 512)), 0)) {
       bins = make_bins(hi, hi - T);
 #pragma unroll 1
-      for (int i = tid; i < quarters; i += kSelThreads) {
-        const int at = quarter(i), w = at >> 6, q = at & 63, info = s_rinfo[w], cnt = info >> 2;
-        const float* fine = data + (size_t)w * kRowFloats;
-        if ((info & 3) == ROW_DENSE) {
-          const uint2 k = *(const uint2*)(fine + 2 * q);
-          const float best = s_rbest[w];
-          const int last = best < T ? -1 : (int)key16(best, T);
-          uint64_t keys = (uint64_t)k.y << 32 | k.x;
+      for (int pass = 0; pass < 2; pass++) {
+        most = 0;
 #pragma unroll 1
-          for (int j = 0; j < 4; j++, keys >>= 16)
-            if ((int)(keys & 0xffffu) <= last) atomicAdd(&s_hist[bins.of(key16_low(best, (uint32_t)keys & 0xffffu))], 1u);
-        } else {
-          float k = -INFINITY;
-          if (cnt > kScoreMax) k = fine[q];
-          else if (4 * q < cnt) { const float4 f = *(const float4*)(fine + 4 * q); k = fmaxf(fmaxf(f.x, f.y), fmaxf(f.z, f.w)); }
-          if (k >= T) atomicAdd(&s_hist[bins.of(k)], 1u);
+        for (int i = tid; i < quarters; i += kSelThreads) {
+          const int at = quarter(i), w = at >> 6, q = at & 63, info = s_rinfo[w], cnt = info >> 2;
+          const float* fine = data + (size_t)w * kRowFloats;
+          if ((info & 3) == ROW_DENSE || cnt > kScoreMax) {
+            const int last = last_key(w);
+            int key, num;
+            uint64_t keys = quarter_keys(fine, q, info, &key, &num);
+#pragma unroll 1
+            for (; num > 0; num--, key++, keys >>= 16) {
+              if ((int)(keys & 0xffffu) > last) continue;
+              if (pass == 0) atomicAdd(&s_hist[bins.of(key16_low(s_rbest[w], (uint32_t)keys & 0xffffu))], 1u);
+              else { add(true, w, key); most = max(most, (uint32_t)cnt); }
+            }
+          } else if (4 * q < cnt) {
+            const float4 f = *(const float4*)(fine + 4 * q);
+            const float k = fmaxf(fmaxf(f.x, f.y), fmaxf(f.z, f.w));
+            if (k >= T && pass == 0) atomicAdd(&s_hist[bins.of(k)], 1u);
+            if (k >= T && pass == 1) add(false, w, q);
+          }
         }
+        if (pass == 1) note_most();
+        __syncthreads();
+        if (pass == 1) break;
+        if (tid == 0) { s_nd = 0; s_ns = 0; s_most = 0; }
+        hist_threshold_all(s_hist, (uint32_t)c.W, &s_thr, s_redu, paru);
+        __syncthreads();
+        T = fmaxf(T, bins.floor_of(s_thr));
       }
-      __syncthreads();
-      if (tid == 0) { s_nd = 0; s_ns = 0; s_most = 0; }
-      hist_threshold_all(s_hist, (uint32_t)c.W, &s_thr, s_redu, paru);
-      __syncthreads();
-      T = fmaxf(T, bins.floor_of(s_thr));
+      nd = (int)s_nd; ns = (int)s_ns;
     }
+    // units of four candidates behind a key in front: float4 of logits, or consecutive children
+    const bool listed = s_most > 0;                          // the keys in front are of gathered rows
+    const int sh = listed ? 1 + key_shift((int)s_most) : c.unit_shift;
     if (tid == 0) s_n = 0;
     fallback = fallback || nd + ns > kChunkCap;
     const int front_units = nd << sh;
-    float scale = 0.f;                                       // bins per unit of score for the candidates
     const int lsh = c.row_threads == 512 ? 2 : 3;            // log2 of a thread's loads per block of a streamed row
     auto unit_token = [&](int k, int e) {                    // first token of unit e of line k
       return 32 * (k >> lsh) + 4 * c.row_threads * (k & ((1 << lsh) - 1)) + 4 * (e & 7) + kBlockV * (e >> 3);
@@ -1033,212 +1102,235 @@ __global__ void __launch_bounds__(kSelThreads) k_select(SelCtx c) {
       };
       // best logit of a gathered row's unit
       auto child_best = [&](int w, int k, int e) {
-        const int at = k + kUnitSpan * e, cnt = s_rinfo[w] >> 2;
+        const int cnt = s_rinfo[w] >> 2, ks = key_shift(cnt), at = (k << (3 + ks)) + 4 * e;
         const float* x = c.logits + ((size_t)b * c.W + w) * c.V;
         const int32_t* list = child_list(c, mv) + s_ra[w];
-        if (at >= cnt) return -INFINITY;
-        const float y0 = x[list[at]], y1 = x[list[min(at + 64, cnt - 1)]], y2 = x[list[min(at + 128, cnt - 1)]], y3 = x[list[min(at + 192, cnt - 1)]];
+        if (e >= 2 << ks || at >= cnt) return -INFINITY;     // (rows of fewer children have fewer units behind a key)
+        const float y0 = x[list[at]], y1 = x[list[min(at + 1, cnt - 1)]], y2 = x[list[min(at + 2, cnt - 1)]], y3 = x[list[min(at + 3, cnt - 1)]];
         return fmaxf(fmaxf(y0, y1), fmaxf(y2, y3));          // (a child taken twice changes nothing here)
       };
-      // Fewer groups than W, as at level 0 where all candidates are one row's, or more units or candidates above the threshold than there
-      // is room for: the units themselves yield a threshold.  (Not where a streamed row's validity is only looked up
-      // below; the best candidates of the first kGroupCap units are kept, beyond that they are looked for again.)
-      const bool countable = listed || !(c.blob && c.step == 2);
-      bool by_unit = countable && T == kNoThreshold && front_units >= c.W;
+      // best valid logit of a streamed row's unit
+      auto token_best = [&](int w, int k, int e) {
+        const int v = unit_token(k, e);
+        if (v >= c.V) return -INFINITY;
+        const float* x = c.logits + ((size_t)b * c.W + w) * c.V;
+        uint32_t bits = 0xfu;
+        if (c.blob) bits = (c.step == 0 ? mv.l0 : mv.l1 + (size_t)s_ra[w] * mv.words)[v >> 5] >> (v & 31);
+        f32x4u y;
+        if (v + 3 < c.V) y = *(const f32x4u*)(x + v);
+        else { y.x = x[v]; y.y = x[min(v + 1, c.V - 1)]; y.z = x[min(v + 2, c.V - 1)]; y.w = y.z; }
+        // (past the row's end a mask has no bits; without one the last token is taken again, which changes nothing here)
+        return fmaxf(fmaxf(bits & 1u ? y.x : -INFINITY, bits & 2u ? y.y : -INFINITY), fmaxf(bits & 4u ? y.z : -INFINITY, bits & 8u ? y.w : -INFINITY));
+      };
+      auto listed_units = [&](auto&& f) {                    // f(unit, its best score) for every unit in front, four at a time
+        constexpr int U = 4;
 #pragma unroll 1
-      for (;;) {
-        if (by_unit) {
-          bins = make_bins(hi, hi - T);
-          auto count = [&](int u, float best) {
-            if (u < min(front_units, kGroupCap)) s_group[u] = best;
-            if (best >= T) atomicAdd(&s_hist[bins.of(best)], 1u);
-          };
-          constexpr int U = 2;
-#pragma unroll 1
-          for (int base = tid; !listed && base < front_units; base += U * kSelThreads) {
-            float best[U];
+        for (int base = tid; base < front_units; base += U * kSelThreads) {
+          float best[U];
 #pragma unroll
-            for (int q = 0; q < U; q++) {
-              const int u = base + q * kSelThreads;
-              best[q] = -INFINITY;
-              if (u >= front_units) continue;
+          for (int q = 0; q < U; q++) {
+            const int u = base + q * kSelThreads;
+            best[q] = -INFINITY;
+            if (u < front_units) {
+              int w, k, e;
+              entry(u, &w, &k, &e);
+              best[q] = __fadd_rn(s_rbias[w], child_best(w, k, e));
+            }
+          }
+#pragma unroll
+          for (int q = 0; q < U; q++)
+            if (base + q * kSelThreads < front_units) f(base + q * kSelThreads, best[q]);
+        }
+      };
+      // Fewer groups than W, as at level 0 where all candidates are one row's: the units themselves yield a threshold.  (Not where a streamed
+      // row's validity is only looked up below; the best candidates of the first kGroupCap units are kept, beyond that they are
+      // looked for again.)
+      const bool countable = listed || !(c.blob && c.step == 2);
+      const bool by_unit = countable && T == kNoThreshold && front_units >= c.W, kept = by_unit && front_units <= kGroupCap;
+      if (by_unit) {
+        bins = make_bins(hi, hi - T);
+        auto count = [&](int u, float best) {
+          if (u < min(front_units, kGroupCap)) s_group[u] = best;
+          if (best >= T) atomicAdd(&s_hist[bins.of(best)], 1u);
+        };
+        constexpr int U = 2;
+#pragma unroll 1
+        for (int base = tid; !listed && base < front_units; base += U * kSelThreads) {
+          float best[U];
+#pragma unroll
+          for (int q = 0; q < U; q++) {
+            const int u = base + q * kSelThreads;
+            best[q] = -INFINITY;
+            if (u >= front_units) continue;
+            int w, k, e;
+            entry(u, &w, &k, &e);
+            best[q] = token_best(w, k, e);
+            best[q] = __fadd_rn(s_rbias[w], best[q]);
+          }
+#pragma unroll
+          for (int q = 0; q < U; q++) count(base + q * kSelThreads, best[q]);
+        }
+        if (listed) listed_units(count);
+        __syncthreads();
+        hist_threshold_all(s_hist, (uint32_t)c.W, &s_thr, s_redu, paru);
+        __syncthreads();
+        T = fmaxf(T, bins.floor_of(s_thr));
+      }
+      if (kept) {
+#pragma unroll 1
+        for (int u = tid; u < front_units; u += kSelThreads)
+          if (s_group[u] >= T) keep(u);
+      } else if (!listed) {
+        constexpr int U = 4;
+#pragma unroll 1
+        for (int base = tid; base < front_units; base += U * kSelThreads) {
+          float best[U], bias[U];
+#pragma unroll
+          for (int q = 0; q < U; q++) {
+            const int u = base + q * kSelThreads;
+            best[q] = -INFINITY; bias[q] = 0.f;
+            if (u < front_units) {
               int w, k, e;
               entry(u, &w, &k, &e);
               const int v = unit_token(k, e);
-              if (v >= c.V) continue;
               const float* x = c.logits + ((size_t)b * c.W + w) * c.V;
-              uint32_t bits = 0xfu;
-              if (c.blob) bits = (c.step == 0 ? mv.l0 : mv.l1 + (size_t)s_ra[w] * mv.words)[v >> 5] >> (v & 31);
-              f32x4u y;
-              if (v + 3 < c.V) y = *(const f32x4u*)(x + v);
-              else { y.x = x[v]; y.y = x[min(v + 1, c.V - 1)]; y.z = x[min(v + 2, c.V - 1)]; y.w = y.z; }
-              // (past the row's end a mask has no bits; without one the last token is taken again, which changes nothing here)
-              best[q] = fmaxf(fmaxf(bits & 1u ? y.x : -INFINITY, bits & 2u ? y.y : -INFINITY), fmaxf(bits & 4u ? y.z : -INFINITY, bits & 8u ? y.w : -INFINITY));
-              best[q] = __fadd_rn(s_rbias[w], best[q]);
+              if (v + 3 < c.V) { const f32x4u t = *(const f32x4u*)(x + v); best[q] = fmaxf(fmaxf(t.x, t.y), fmaxf(t.z, t.w)); }
+              else if (v < c.V) best[q] = INFINITY;        // (the row's last tokens are looked at one by one below)
+              bias[q] = s_rbias[w];
             }
-#pragma unroll
-            for (int q = 0; q < U; q++) count(base + q * kSelThreads, best[q]);
           }
+#pragma unroll
+          for (int q = 0; q < U; q++)
+            if (__fadd_rn(bias[q], best[q]) >= T) keep(base + q * kSelThreads);
+        }
+      } else {
+        listed_units([&](int u, float best) { if (best >= T) keep(u); });
+      }
+      __syncthreads();
+      // more units than there is room for: the same, over those that reach the threshold
+      if (__builtin_expect(s_nu > (uint32_t)kUnitCap && countable && !by_unit, 0)) {
+        bins = make_bins(hi, hi - T);
 #pragma unroll 1
-          for (int u = tid; listed && u < front_units; u += kSelThreads) {
+        for (int pass = 0; pass < 2; pass++) {               // count, keep
+#pragma unroll 1
+          for (int u = tid; u < front_units; u += kSelThreads) {
             int w, k, e;
             entry(u, &w, &k, &e);
-            count(u, __fadd_rn(s_rbias[w], child_best(w, k, e)));
+            const float best = __fadd_rn(s_rbias[w], listed ? child_best(w, k, e) : token_best(w, k, e));
+            if (!(best >= T)) continue;
+            if (pass == 0) atomicAdd(&s_hist[bins.of(best)], 1u);
+            else keep(u);
           }
           __syncthreads();
+          if (pass == 1) break;
+          if (tid == 0) s_nu = 0;
           hist_threshold_all(s_hist, (uint32_t)c.W, &s_thr, s_redu, paru);
           __syncthreads();
           T = fmaxf(T, bins.floor_of(s_thr));
         }
-        if (by_unit && front_units <= kGroupCap) {
-#pragma unroll 1
-          for (int u = tid; u < front_units; u += kSelThreads)
-            if (s_group[u] >= T) keep(u);
-        } else if (!listed) {
-          constexpr int U = 4;
-#pragma unroll 1
-          for (int base = tid; base < front_units; base += U * kSelThreads) {
-            float best[U], bias[U];
-#pragma unroll
-            for (int q = 0; q < U; q++) {
-              const int u = base + q * kSelThreads;
-              best[q] = -INFINITY; bias[q] = 0.f;
-              if (u < front_units) {
-                int w, k, e;
-                entry(u, &w, &k, &e);
-                const int v = unit_token(k, e);
-                const float* x = c.logits + ((size_t)b * c.W + w) * c.V;
-                if (v + 3 < c.V) { const f32x4u t = *(const f32x4u*)(x + v); best[q] = fmaxf(fmaxf(t.x, t.y), fmaxf(t.z, t.w)); }
-                else if (v < c.V) best[q] = INFINITY;        // (the row's last tokens are looked at one by one below)
-                bias[q] = s_rbias[w];
-              }
-            }
-#pragma unroll
-            for (int q = 0; q < U; q++)
-              if (__fadd_rn(bias[q], best[q]) >= T) keep(base + q * kSelThreads);
-          }
-        } else {
-          constexpr int U = 4;
-#pragma unroll 1
-          for (int base = tid; base < front_units; base += U * kSelThreads) {
-            float best[U], bias[U];
-#pragma unroll
-            for (int q = 0; q < U; q++) {
-              const int u = base + q * kSelThreads;
-              best[q] = -INFINITY; bias[q] = 0.f;
-              if (u < front_units) {
-                int w, k, e;
-                entry(u, &w, &k, &e);
-                best[q] = child_best(w, k, e);
-                bias[q] = s_rbias[w];
-              }
-            }
-#pragma unroll
-            for (int q = 0; q < U; q++)
-              if (__fadd_rn(bias[q], best[q]) >= T) keep(base + q * kSelThreads);
-          }
-        }
-        __syncthreads();
-        const int nu = (int)s_nu, units = nu + ns;
-        scale = T > kNoThreshold ? 0.f : 64.f;
-        if (T > kNoThreshold && hi > T) scale = fminf((float)(kHistBins - 1) / (hi - T), 1e30f);
-        fallback = nu > kUnitCap;
-        if (!fallback) {
-          // ---- their candidates, counted in bins of one width from the best score down to the threshold
-#pragma unroll 1
-          for (int i = tid; i < units; i += kSelThreads) {
-            const uint32_t unit = i < nu ? s_units[i] : 0u;
-            const uint32_t ent = s_chunks[i < nu ? (int)(unit >> 8) : kChunkCap - 1 - (i - nu)];
-            const int w = (int)(ent >> 8), k = (int)(ent & 255u), cnt = s_rinfo[w] >> 2;
-            const float* xrow = c.logits + ((size_t)b * c.W + w) * c.V;
-            int place, stride = 1, end = cnt;                // the unit's candidates: place, place + stride, ... < end
-            float bias = s_rbias[w], y[4];
-            uint32_t bits = 0xfu;
-            if (i < nu && !listed) {
-              place = unit_token(k, (int)(unit & 255u));
-              end = c.V;
-              if (c.blob && c.step == 0) bits = mv.l0[place >> 5] >> (place & 31);
-              else if (c.blob && c.step == 1) bits = mv.l1[(size_t)s_ra[w] * mv.words + (place >> 5)] >> (place & 31);
-#pragma unroll
-              for (int j = 0; j < 4; j++) y[j] = xrow[min(place + j, c.V - 1)];
-            } else if (i >= nu) {
-              place = 4 * k;
-              bias = 0.f;                                    // (these scores are complete)
-              const float4 t = *(const float4*)(data + (size_t)w * kRowFloats + place);
-              y[0] = t.x; y[1] = t.y; y[2] = t.z; y[3] = t.w;
-            } else {
-              place = k + kUnitSpan * (int)(unit & 255u);
-              stride = 64;
-              const int32_t* list = child_list(c, mv) + s_ra[w];
-              int tok[4];
-#pragma unroll
-              for (int j = 0; j < 4; j++) tok[j] = list[min(place + 64 * j, cnt - 1)];
-#pragma unroll
-              for (int j = 0; j < 4; j++) y[j] = xrow[tok[j]];
-            }
-#pragma unroll
-            for (int j = 0; j < 4; j++) {
-              const int at = place + j * stride;
-              const float score = __fadd_rn(bias, y[j]);     // (with bias 0 unchanged but for -0, which composite() makes 0)
-              if (at >= end || !((bits >> j) & 1u) || !(score >= T)) continue;
-              if (c.blob && c.step == 2 && i < nu && !listed) {        // last level, streamed row: the candidate has to be in the row's child list
-                const int32_t* list = mv.t3 + s_ra[w];
-                const int len = c.range_in[2 * ((size_t)b * c.W + w) + 1] - s_ra[w], pos = lower_bound_i32(list, len, at);
-                if (!(pos < len && list[pos] == at)) continue;
-              }
-              atomicAdd(&s_hist[key_bin(hi, scale, score)], 1u);
-              const uint32_t pos = atomicAdd(&s_n, 1u);
-              if (pos < (uint32_t)kListCap) s_list[pos] = composite(score, (uint32_t)w * (uint32_t)c.V + (uint32_t)at);
-            }
-          }
-          __syncthreads();
-          n = (int)s_n;
-          fallback = n > kListCap;
-        }
-        if (__builtin_expect(!fallback || by_unit || !countable, 1)) break;
-        // more than there is room for: once again above the threshold that the units yield
-        by_unit = true;
-        fallback = false;
-        __syncthreads();
-        if (tid == 0) { s_nu = 0; s_n = 0; }
-        for (int i = tid; i < kHistBins; i += kSelThreads) s_hist[i] = 0;
-        __syncthreads();
       }
+      fallback = s_nu > (uint32_t)kUnitCap;
     }
     if (!fallback) {
+      // ---- their candidates, counted in bins of one width from the best score down to the threshold.  When they do not fit, the
+      // bins still tell where the W best end, and a second round takes only those.
+      const int nu = (int)s_nu, units = nu + ns;
+      float scale = T > kNoThreshold ? (hi > T ? fminf((float)(kHistBins - 1) / (hi - T), 1e30f) : 0.f) : 64.f;
+      int cut = kHistBins - 1;
+#pragma unroll 1
+      for (int round = 0; round < 2; round++) {
+#pragma unroll 1
+        for (int i = tid; i < units; i += kSelThreads) {
+          const uint32_t unit = i < nu ? s_units[i] : 0u;
+          const uint32_t ent = s_chunks[i < nu ? (int)(unit >> 8) : kChunkCap - 1 - (i - nu)];
+          const int w = (int)(ent >> 8), k = (int)(ent & 255u), cnt = s_rinfo[w] >> 2;
+          const float* xrow = c.logits + ((size_t)b * c.W + w) * c.V;
+          int place, end = cnt;                            // the unit's candidates: place .. place + 3, < end
+          float bias = s_rbias[w], y[4];
+          uint32_t bits = 0xfu;
+          if (i < nu && !listed) {
+            place = unit_token(k, (int)(unit & 255u));
+            end = c.V;
+            if (c.blob && c.step == 0) bits = mv.l0[place >> 5] >> (place & 31);
+            else if (c.blob && c.step == 1) bits = mv.l1[(size_t)s_ra[w] * mv.words + (place >> 5)] >> (place & 31);
+#pragma unroll
+            for (int j = 0; j < 4; j++) y[j] = xrow[min(place + j, c.V - 1)];
+          } else if (i >= nu) {
+            place = 4 * k;
+            bias = 0.f;                                    // (these scores are complete)
+            const float4 t = *(const float4*)(data + (size_t)w * kRowFloats + place);
+            y[0] = t.x; y[1] = t.y; y[2] = t.z; y[3] = t.w;
+          } else {
+            place = (k << (3 + key_shift(cnt))) + 4 * (int)(unit & 255u);
+            const int32_t* list = child_list(c, mv) + s_ra[w];
+            int tok[4];
+#pragma unroll
+            for (int j = 0; j < 4; j++) tok[j] = list[min(place + j, cnt - 1)];
+#pragma unroll
+            for (int j = 0; j < 4; j++) y[j] = xrow[tok[j]];
+          }
+#pragma unroll
+          for (int j = 0; j < 4; j++) {
+            const int at = place + j;
+            const float score = __fadd_rn(bias, y[j]);     // (with bias 0 unchanged but for -0, which composite() makes 0)
+            if (at >= end || !((bits >> j) & 1u) || !(score >= T)) continue;
+            if (c.blob && c.step == 2 && i < nu && !listed) {        // last level, streamed row: the candidate has to be in the row's child list
+              const int32_t* list = mv.t3 + s_ra[w];
+              const int len = c.range_in[2 * ((size_t)b * c.W + w) + 1] - s_ra[w], pos = lower_bound_i32(list, len, at);
+              if (!(pos < len && list[pos] == at)) continue;
+            }
+            const int bin = key_bin(hi, scale, score);
+            if (bin > cut) continue;
+            if (round == 0) atomicAdd(&s_hist[bin], 1u);
+            const uint32_t pos = atomicAdd(&s_n, 1u);
+            if (pos < (uint32_t)kListCap) s_list[pos] = composite(score, (uint32_t)w * (uint32_t)c.V + (uint32_t)at);
+          }
+        }
+        __syncthreads();
+        n = (int)s_n;
+        if (round == 0) {
+          if (__builtin_expect(T == kNoThreshold && n <= kListCap && s_hist[kHistBins - 1] > 64u, 0)) {
+            // (no threshold, and many lie below the bins: down to the worst of them)
+            float mx = -INFINITY, mn = INFINITY;
+            for (int i = tid; i < n; i += kSelThreads) mn = fminf(mn, gr_ordkey_inv((uint32_t)(s_list[i] >> 32)));
+            __syncthreads();
+            for (int i = tid; i < kHistBins; i += kSelThreads) s_hist[i] = 0;
+            block_max_min<NW>(mx, mn, s_redf, parf);         // (its barrier: the histogram is clear)
+            scale = hi > mn ? fminf((float)(kHistBins - 1) / (hi - mn), 1e30f) : 0.f;
+            for (int i = tid; i < n; i += kSelThreads) atomicAdd(&s_hist[key_bin(hi, scale, gr_ordkey_inv((uint32_t)(s_list[i] >> 32)))], 1u);
+            __syncthreads();
+          }
+          // exclusive prefix over the bins, in place, and the bin that holds the W-th candidate
+          constexpr int per = kHistBins / kSelThreads;
+          uint32_t h[per], sum = 0;
+#pragma unroll
+          for (int k = 0; k < per; k++) { h[k] = s_hist[tid * per + k]; sum += h[k]; }
+          uint32_t total;
+          uint32_t run = block_excl_scan<NW>(sum, &total, s_redu, paru);
+          if (tid == 0 && total < (uint32_t)c.W) s_thr = kHistBins - 1;
+#pragma unroll
+          for (int k = 0; k < per; k++) {
+            s_hist[tid * per + k] = run;
+            if (run < (uint32_t)c.W && run + h[k] >= (uint32_t)c.W) s_thr = tid * per + k;
+            run += h[k];
+          }
+          if (n > kListCap && tid == 0) s_n = 0;
+          __syncthreads();
+          cut = s_thr;
+        }
+        if (n <= kListCap) break;
+      }
       // ---- order them (descending composite key = score descending, flat index ascending).  Histogram bins are ordered by
       // score, so a survivor's place is the number of survivors in better bins plus its rank inside its own (tiny) bin.
       // Counting sort by bin, then every survivor counts the larger keys of its bin.  Exact ties share a bin and are ranked
       // by the key's flat-index half there.
-      auto score_of = [&](uint64_t key) { return gr_ordkey_inv((uint32_t)(key >> 32)); };
-      auto bin_of = [&](uint64_t key) { return key_bin(hi, scale, score_of(key)); };
-      if (__builtin_expect(T == kNoThreshold && s_hist[kHistBins - 1] > 64u, 0)) {     // (no threshold, and many lie below the bins: down to the worst of them)
-        float mx = -INFINITY, mn = INFINITY;
-        for (int i = tid; i < n; i += kSelThreads) mn = fminf(mn, score_of(s_list[i]));
-        __syncthreads();
-        for (int i = tid; i < kHistBins; i += kSelThreads) s_hist[i] = 0;
-        block_max_min<NW>(mx, mn, s_redf, parf);             // (its barrier: the histogram is clear)
-        scale = hi > mn ? fminf((float)(kHistBins - 1) / (hi - mn), 1e30f) : 0.f;
-        for (int i = tid; i < n; i += kSelThreads) atomicAdd(&s_hist[bin_of(s_list[i])], 1u);
-        __syncthreads();
+      auto bin_of = [&](uint64_t key) { return key_bin(hi, scale, gr_ordkey_inv((uint32_t)(key >> 32))); };
+      fallback = n > kListCap;
+      int m = 0;                                             // survivors up to the W-th one's bin
+      if (!fallback) {
+        m = cut < kHistBins - 1 ? (int)s_hist[cut + 1] : n;
+        fallback = m > kTmpCap;
       }
-      // exclusive prefix over the bins, in place, and the bin that holds the W-th candidate
-      constexpr int per = kHistBins / kSelThreads;
-      uint32_t h[per], sum = 0;
-#pragma unroll
-      for (int k = 0; k < per; k++) { h[k] = s_hist[tid * per + k]; sum += h[k]; }
-      uint32_t total;
-      uint32_t run = block_excl_scan<NW>(sum, &total, s_redu, paru);
-      if (tid == 0 && total < (uint32_t)c.W) s_thr = kHistBins - 1;
-#pragma unroll
-      for (int k = 0; k < per; k++) {
-        s_hist[tid * per + k] = run;
-        if (run < (uint32_t)c.W && run + h[k] >= (uint32_t)c.W) s_thr = tid * per + k;
-        run += h[k];
-      }
-      __syncthreads();
-      const int cut = s_thr, m = cut < kHistBins - 1 ? (int)s_hist[cut + 1] : n;       // survivors up to the W-th one's bin
-      fallback = m > kTmpCap;
       if (!fallback) {
         __syncthreads();                                     // (s_hist[cut + 1] is read before any counter moves)
 #pragma unroll 1
@@ -1313,47 +1405,49 @@ __global__ void __launch_bounds__(kSelThreads) k_select(SelCtx c) {
     __syncthreads();
   }
 
-  // ---- write the new beam state, best first
-  for (int j = tid; j < c.W; j += kSelThreads) {
-    const size_t o = (size_t)b * c.W + j;
-    int32_t* po = c.prefix_out + o * c.depth;
-    for (int k = 0; k < c.depth; k++) po[k] = -1;
+  // ---- write the new beam state, best first.  (The arguments are read again here: held from the start on, the scalar registers they
+  // take are spilled and reloaded all through the kernel.)
+  const LateArgs late = late_args();
+  for (int j = tid; j < late->W; j += kSelThreads) {
+    const size_t o = (size_t)b * late->W + j;
+    int32_t* po = late->prefix_out + o * late->depth;
+    for (int k = 0; k < late->depth; k++) po[k] = -1;
     int r_lo = 0, r_hi = 0, item = -1;
     if (j < n) {
       const uint64_t key = s_list[j];
       const uint32_t flat = 0xffffffffu - (uint32_t)key;
-      const int parent = (int)(flat / (uint32_t)c.V), place = (int)(flat % (uint32_t)c.V);
+      const int parent = (int)(flat / (uint32_t)late->V), place = (int)(flat % (uint32_t)late->V);
       const bool gathered = (s_rinfo[parent] & 3) == ROW_SPARSE;
       int token = place;
-      if (c.blob) {
-        if (c.step == 0) {
+      if (late->blob) {
+        if (late->step == 0) {
           r_lo = mv.off1[token]; r_hi = mv.off1[token + 1];
-        } else if (c.step == 1) {
+        } else if (late->step == 1) {
           const int p = gathered ? s_ra[parent] + place : s_rank[j];
           if (gathered) token = mv.pair_t2[p];
           r_lo = mv.pair_row[p]; r_hi = mv.pair_row[p + 1];
         } else {
           const int first = s_ra[parent];
-          r_lo = first + (gathered ? place : lower_bound_i32(mv.t3 + first, c.range_in[2 * ((size_t)b * c.W + parent) + 1] - first, token));
+          r_lo = first + (gathered ? place : lower_bound_i32(mv.t3 + first, late->range_in[2 * ((size_t)b * late->W + parent) + 1] - first, token));
           if (gathered) token = mv.t3[r_lo];
           r_hi = r_lo + 1;
           item = r_lo;
         }
       }
-      c.parent_out[o] = parent;
-      c.token_out[o] = token;
-      c.scores_out[o] = gr_ordkey_inv((uint32_t)(key >> 32));
-      const size_t prow = (size_t)b * c.W + parent;
-      for (int k = 0; k < c.step; k++) po[k] = c.prefix_in[prow * c.depth + k];
-      po[c.step] = token;
+      late->parent_out[o] = parent;
+      late->token_out[o] = token;
+      late->scores_out[o] = gr_ordkey_inv((uint32_t)(key >> 32));
+      const size_t prow = (size_t)b * late->W + parent;
+      for (int k = 0; k < late->step; k++) po[k] = late->prefix_in[prow * late->depth + k];
+      po[late->step] = token;
     } else {
-      c.parent_out[o] = -1;
-      c.token_out[o] = -1;
-      c.scores_out[o] = -INFINITY;
+      late->parent_out[o] = -1;
+      late->token_out[o] = -1;
+      late->scores_out[o] = -INFINITY;
     }
-    c.range_out[2 * o] = r_lo;
-    c.range_out[2 * o + 1] = r_hi;
-    if (c.item_index_out) c.item_index_out[o] = item;
+    late->range_out[2 * o] = r_lo;
+    late->range_out[2 * o + 1] = r_hi;
+    if (late->item_index_out) late->item_index_out[o] = item;
   }
 }
 
@@ -1391,14 +1485,13 @@ extern "C" gr_status gr_beam_select(const gr_select_params* p, void* workspace, 
   char* ws = (char*)workspace;
   c.row_bias = (float*)ws;                 ws += gr_align256(rows * 4);
   c.row_info = (int32_t*)ws;               ws += gr_align256(rows * 4);
-  c.row_start = (int32_t*)ws;
-  c.row_best = (float*)ws;                 ws += gr_align256(rows * 4);
+  c.row_start = (int32_t*)ws;              ws += gr_align256(rows * 4);
   c.row_group = (float*)ws;                ws += rows * kGroups * 4;       // (whole 64 bytes a row: row_data stays 16-byte aligned)
   c.row_data = (float*)ws;
 
   c.row_threads = p->step == 0 ? 512 : 256;
   if (p->mask && p->step >= 1 && !(p->flags & GR_SELECT_FORCE_DENSE))
-    hipLaunchKernelGGL(k_rows_listed, dim3((unsigned)((rows + kGatherWaves - 1) / kGatherWaves)), dim3(kGatherWaves * 64), 0, stream, c);
+    hipLaunchKernelGGL(k_rows_listed, dim3((unsigned)((rows + kDeal * kGatherWaves - 1) / (kDeal * kGatherWaves) * kDeal)), dim3(kGatherWaves * 64), 0, stream, c);
   else if (p->step == 0)
     hipLaunchKernelGGL((k_rows<true, 512>), dim3((unsigned)(rows < kStrideGrid ? rows : kStrideGrid)), dim3(512), 0, stream, c);
   else
