@@ -1206,11 +1206,15 @@ extern "C" gr_status gr_prefill_attn(const gr_prefill_params* p, void* stream_) 
   c.B = p->B; c.W = 0; c.Hq = p->Hq; c.Hkv = p->Hkv; c.g = g; c.ND = 0; c.u = 0;
   c.M = p->max_L * g;                                        // the longest request's rows size the grid
   // 128 rows, two workgroups to a CU: one computes while the other waits for its queries or stores its output, which is most of
-  // the life of a block of a short prompt.  256 rows stage every K/V tile half as often, which only counts for long prompts of
-  // head size 128.  us with 256 and 128 rows (32 query and 8 KV heads of 128 unless noted): 1 x 1024 tokens 28.7, 21.8; 16 prompts of
-  // 62-512 38.2, 33.9; 64 x 512 249, 240; 64 x 2048 2283, 2232; but 1 x 4096 128, 138 and 8 of 1024-8192 1674, 1700; 4 x 2048 141, 146
-  // is the worst on this side of the line.  8 heads of 64: 1 x 4096 71, 50; 16 x 4096 383, 344.
-  const int mwg = p->d == 64 || p->max_L <= 2048 || c.M <= 128 ? 128 : 256;
+  // the life of a block of a short prompt.  256 rows stage every K/V tile half as often, which counts for long prompts of head size
+  // 128, and for shorter ones where an XCD has one or two (prompt, KV head) pairs and 1.25 to 2 such blocks per CU (counted by
+  // the tokens there are), so that the few heaviest blocks are what the call waits for.  us with 256 and 128 rows (32 query and 8 KV heads of 128 unless noted):
+  // 1 x 1024 tokens 29.7, 22.3; 16 prompts of 62-512 38.2, 33.9; 4 x 1024 56, 49; 1 x 2048 55.1, 47.6; 16 x 2048 596, 579; 4 of
+  // 190-1500 with 16 query and 4 KV heads 43.6, 36.7; but 1 x 4096 128, 138 and 8 of 1024-8192 1674, 1700; 2 x 2048 74.5, 77.9 and 1 to 4 x 2048 of 16 query and 2 KV heads 69-75, 75-79.  8 heads of 64:
+  // 1 x 4096 71, 50; 16 x 4096 383, 344.
+  const int64_t pairs = (int64_t)p->B * p->Hkv, rows_per_xcd = p->total_L * p->Hq / (pairs < 8 ? pairs : 8);
+  const bool heavy = p->max_L > 2048 || (pairs <= 16 && rows_per_xcd > 40 * 256 && rows_per_xcd <= 64 * 256);
+  const int mwg = p->d == 64 || !heavy || c.M <= 128 ? 128 : 256;
   c.MB = (c.M + mwg - 1) / mwg;
   c.nsplit = 1;
   c.n_groups = p->B * p->Hkv;

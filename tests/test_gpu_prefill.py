@@ -54,12 +54,11 @@ def test_prefill_matches_oracle(oracle_lib, lens, Hq, Hkv, d):
     np.testing.assert_allclose(lse[:T], ref_lse, rtol=0, atol=2e-3)
 
 
-@pytest.mark.parametrize("max_L", [2048, 2049])        # head size 128: workgroups of 128 and of 256 query rows
-@pytest.mark.parametrize("lens,Hq,Hkv", [
+@pytest.mark.parametrize("lens,Hq,Hkv,max_L", [(*case, n) for n in (2048, 2049) for case in (      # head size 128: blocks of 128 and of 256 query rows
     ((1, 31, 33, 63, 65), 32, 8),          # g = 4: 32 and 64 tokens per row block
     ((257, 128, 129, 2), 4, 4),            # g = 1: row blocks of 128 and 256 tokens
     ((43, 86, 90), 6, 2),                  # g = 3: a token's heads lie in two row blocks
-])
+)] + [((n,), 8, 1, n) for n in (1280, 1281, 2048)])        # one (prompt, KV head) pair of 40 to 64 blocks of 256 rows: 128, 256, 256
 def test_prefill_row_blocks_of_both_sizes(oracle_lib, lens, Hq, Hkv, max_L):
     """max_L is a bound that the longest prompt need not reach; it decides the size of a row block."""
     import paper_2512_11529_amd as gr
