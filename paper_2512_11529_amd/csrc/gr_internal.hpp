@@ -67,22 +67,6 @@ static inline void gr_mask_layout(int64_t n_items, int32_t V, gr_mask_header* h)
 // ------------------------------------------------------------------ wave64 primitives
 __device__ __forceinline__ int gr_lane() { return (int)__lane_id(); }
 
-__device__ __forceinline__ float gr_wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-  return v;
-}
-__device__ __forceinline__ double gr_wave_sum(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-__device__ __forceinline__ uint32_t gr_wave_sum_u32(uint32_t v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-
 // Order-preserving map fp32 -> uint32 (larger float <=> larger key); no NaN expected.
 __device__ __forceinline__ uint32_t gr_ordkey(float f) {
   uint32_t u = __float_as_uint(f);

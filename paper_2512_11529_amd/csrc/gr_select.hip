@@ -45,7 +45,7 @@ constexpr size_t kSelLdsBytes = (size_t)kListCap * 8 + (size_t)kUnitCap * 4 + (s
 enum { ROW_DEAD = 0, ROW_DENSE = 1, ROW_SPARSE = 2 };      // low bits of row_info; the child count of a gathered row above them
 
 struct SelCtx {
-  int B, W, V, depth, step, flags;
+  int B, W, V, depth, step;
   int row_threads;           // threads that stream a row: thread t holds tokens 4 (t + row_threads i) .. + 3 for all i
   int unit_shift;            // log2 of the units (float4 of logits) behind a key of a streamed row: 8 per block of kBlockV logits, to a power of two
   const char* blob;          // mask blob or nullptr
@@ -1474,7 +1474,7 @@ extern "C" gr_status gr_beam_select(const gr_select_params* p, void* workspace, 
   if (workspace_bytes < gr_beam_select_workspace_bytes(p->B, p->W, p->V, p->depth)) return GR_ERR_WORKSPACE_TOO_SMALL;
 
   SelCtx c;
-  c.B = p->B; c.W = p->W; c.V = p->V; c.depth = p->depth; c.step = p->step; c.flags = p->flags;
+  c.B = p->B; c.W = p->W; c.V = p->V; c.depth = p->depth; c.step = p->step;
   c.unit_shift = 3;
   while ((kBlockV >> 3) << c.unit_shift < p->V) c.unit_shift++;
   c.blob = (const char*)p->mask;
@@ -1530,7 +1530,8 @@ extern "C" gr_status gr_beam_select_noalloc(const gr_select_params* p, void* str
     if (!ptr) return GR_ERR_HIP;
     g_scratch_ptr[dev] = ptr;
   }
-  // nothing in the workspace has to start at zero: every word a call reads is written by that call first
+  // nothing in the workspace has to start at zero: a row's mode is always written by the call that reads it, and what else a call reads
+  // of a row is used only where the mode says that it was written (a dead row's bias, start and groups are not)
   return gr_beam_select(p, g_scratch_ptr[dev], kStaticScratchBytes, stream_);
 }
 
