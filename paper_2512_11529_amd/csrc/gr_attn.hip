@@ -192,10 +192,9 @@ struct AttnTile {
 
   // One steady-state tile with the matrix and vector pipes kept busy together.  The wave issues, in this order,
   // the MFMAs of S(t+1) = K(t+1).Q^T and then those of O += V(t).P(t); between consecutive MFMAs it
-  // exponentiates a fixed share of tile t's scores (reference maximum already decided: mc = m_ref * c), so that
+  // exponentiates a fixed share of tile t's scores (their reference m2 is already decided), so that
   // the 32 quarter-rate exponentials per lane run in the shadow of the 32 MFMAs instead of after them.  P(t) is
-  // complete before the second half of the PV MFMAs starts; those are interleaved with the column maximum of
-  // S(t+1), which the next tile's decision needs.  Instruction order is pinned chunk by chunk.
+  // complete before the second half of the PV MFMAs starts.  Instruction order is pinned chunk by chunk.
   // Measured at 32 x 4096 tokens x 256 beams, two wavefronts per SIMD: 507 us with the exponentials staged over three chunks, 515
   // with each finished in one; 8 x 2048 x 128 (one wavefront per SIMD, 1.1 us a tile): 40.1 against 41.4 us.  Operand reads 5 or 6
   // MFMAs ahead: no change.
@@ -207,21 +206,20 @@ struct AttnTile {
   }
   static __device__ __forceinline__ void fused(int sk_next, int sv_cur, const bf16x8 (&qop)[NCB][D / 16],
                                                const f32x16 (&s_cur)[KT / 32][NCB], f32x16 (&s_next)[KT / 32][NCB],
-                                               f32x16 (&o)[D / 32][NCB], float mc, float c, float& l_run, float& mx_next, const Rd& rdo) {
+                                               f32x16 (&o)[D / 32][NCB], float m2, float c, float& rs, const Rd& rdo) {
     static_assert(NCB == 1, "one column block per wave");
     auto rdk = [&](int i) { return read_k(sk_next, rdo, i % 2, i / 2); };
     auto rdv = [&](int i) { return read_v(sv_cur, rdo, i / (D / 32), i % (D / 32)); };
     constexpr int PF = 4;                                   // operand reads run PF MFMAs ahead
-    constexpr int SCAN0 = NMF - NPV / 2, EPC = 32 / (NPV / 2);   // maximum scan: EPC scores per chunk from MFMA SCAN0 on
     bf16x8 a[NMF];
     bf16x8 pop[KT / 16];
     float p[32], arg[32];                                   // (a few of each are alive at a time)
-    float rs = 0.f, mx = -INFINITY;
+    rs = 0.f;
     const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int i = 0; i < PF; i++) a[i] = rdk(i);
 #pragma unroll
-    for (int e = 0; e < exps_after(0); e++) arg[e] = fmaf(s_cur[e / 16][0][e % 16], c, -mc);
+    for (int e = 0; e < exps_after(0); e++) arg[e] = fmaf(s_cur[e / 16][0][e % 16], c, -m2);
 #pragma unroll
     for (int j = 0; j < NMF; j++) {
       if (j + PF < NMF) a[j + PF] = (j + PF < NQK) ? rdk(j + PF) : rdv(j + PF - NQK);
@@ -238,7 +236,7 @@ struct AttnTile {
 #pragma unroll
       for (int e = exps_after(j - 1); e < exps_after(j); e++) p[e] = __builtin_amdgcn_exp2f(arg[e]);
 #pragma unroll
-      for (int e = exps_after(j); e < exps_after(j + 1); e++) arg[e] = fmaf(s_cur[e / 16][0][e % 16], c, -mc);
+      for (int e = exps_after(j); e < exps_after(j + 1); e++) arg[e] = fmaf(s_cur[e / 16][0][e % 16], c, -m2);
 #pragma unroll
       for (int e = exps_after(j - 2); e < exps_after(j - 1); e++) {
         if (e % 8 == 7) {
@@ -253,25 +251,25 @@ struct AttnTile {
           pop[e / 8] = pk;
         }
       }
-      if (j >= SCAN0) {
-#pragma unroll
-        for (int e = (j - SCAN0) * EPC; e < (j - SCAN0 + 1) * EPC; e += 2)
-          mx = fmaxf(fmaxf(mx, s_next[e / 16][0][e % 16]), s_next[e / 16][0][e % 16 + 1]);
-      }
-      asm volatile("" : "+v"(rs), "+v"(mx));                 // the running sum and maximum are due here, not at the end of the tile
+      asm volatile("" : "+v"(rs));                           // the running sum is due here, not at the end of the tile
       __builtin_amdgcn_sched_barrier(0);
     }
-    l_run += rs;
-    mx_next = fmaxf(mx, __shfl_xor(mx, 32, 64));
   }
 
   // Online softmax of one tile, one query column per lane (its other half lives in lane^32).
-  // The running reference m_ref is only raised when some column of the wave exceeds it by more than
-  // kLazy (log2 units): exp2 arguments stay <= kLazy, which fp32 sums and bf16 P hold easily, and the
+  // The running reference m2 (log2 units) is only raised when some column of the wave exceeds it by more than
+  // kLazy: exp2 arguments stay <= kLazy, which fp32 sums and bf16 P hold easily, and the
   // O accumulators need rescaling only on those rare tiles.  Returns (per column block) whether O
   // must be multiplied by alpha[cb].
   static constexpr float kLazy = 8.0f;
-  static __device__ __forceinline__ void softmax(f32x16 (&s)[KT / 32][NCB], bf16x8 (&pop)[KT / 16][NCB], float (&m_ref)[NCB],
+  // The steady-state tiles do not look for their maximum (16 vector instructions a tile and an exchange between lanes).  The reference is
+  // the first tile's maximum plus kHead: probabilities start 2^-24 low, what lies far below the reference is lost at 2^-102 of the maximum
+  // (nothing to a sum of fp32), and scores may rise 48 bits inside one tile.  A column whose tile sums to more than 1 gets a higher
+  // reference after that tile; one with more than 2^kHead (where O could overflow) is computed again from the first token by a
+  // loop that looks for maxima (k_beam_attn's `redo`).  The loop is bound by what it issues beside the MFMAs, so this is worth 3 to 4 %:
+  // 32 x 4096 tokens x 256 beams 17 us of 505, 4 x 16384 x 512 in FP8 477 -> 459 us, 8 causal prompts of 1024-8192 1606 -> 1556.
+  static constexpr float kHead = 24.0f, kTooHigh = 16777216.0f;
+  static __device__ __forceinline__ void softmax(f32x16 (&s)[KT / 32][NCB], bf16x8 (&pop)[KT / 16][NCB], float (&m2)[NCB],
                                                  float (&l_run)[NCB], float (&alpha)[NCB], bool (&upd)[NCB], float c) {
 #pragma unroll
     for (int cb = 0; cb < NCB; cb++) {
@@ -281,21 +279,20 @@ struct AttnTile {
 #pragma unroll
         for (int i = 0; i < 16; i++) mx = fmaxf(mx, s[sub][cb][i]);
       mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-      upd[cb] = __any(mx * c > m_ref[cb] * c + kLazy);
-      const float m_new = upd[cb] ? fmaxf(m_ref[cb], mx) : m_ref[cb];
-      alpha[cb] = __builtin_amdgcn_exp2f((m_ref[cb] - m_new) * c);
-      const float mc = m_new * c;
+      upd[cb] = __any(mx * c > m2[cb] + kLazy);
+      const float m_new = upd[cb] ? fmaxf(m2[cb], mx * c) : m2[cb];
+      alpha[cb] = __builtin_amdgcn_exp2f(m2[cb] - m_new);
       float rs = 0.f;
 #pragma unroll
       for (int sub = 0; sub < KT / 32; sub++)
 #pragma unroll
         for (int i = 0; i < 16; i++) {
-          const float p = __builtin_amdgcn_exp2f(fmaf(s[sub][cb][i], c, -mc));
+          const float p = __builtin_amdgcn_exp2f(fmaf(s[sub][cb][i], c, -m_new));
           s[sub][cb][i] = p;
           rs += p;
         }
       l_run[cb] = l_run[cb] * alpha[cb] + rs;
-      m_ref[cb] = m_new;
+      m2[cb] = m_new;
       // P^T as B operands: slab t = accumulator registers 8*(t%2) .. +7 of sub-tile t/2
 #pragma unroll
       for (int t = 0; t < KT / 16; t++) {
@@ -425,7 +422,7 @@ k_beam_attn(AttnCtx c) {
     for (int cb = 0; cb < NCB; cb++)
 #pragma unroll
       for (int i = 0; i < 16; i++) o_acc[db][cb][i] = 0.f;
-  float m_run[NCB], l_run[NCB];
+  float m_run[NCB], l_run[NCB];                                // reference of the exponentials in log2 units, and sum
 #pragma unroll
   for (int cb = 0; cb < NCB; cb++) { m_run[cb] = -INFINITY; l_run[cb] = 0.f; }
 
@@ -499,18 +496,21 @@ k_beam_attn(AttnCtx c) {
     }
     return st;
   };
+  auto widen8 = [](uint2 r) {
+    const bf16x2 e01 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8((int)r.x, 1.0f, false);
+    const bf16x2 e23 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8((int)r.x, 1.0f, true);
+    const bf16x2 e45 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8((int)r.y, 1.0f, false);
+    const bf16x2 e67 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8((int)r.y, 1.0f, true);
+    uint4 v;
+    v.x = __builtin_bit_cast(uint32_t, e01); v.y = __builtin_bit_cast(uint32_t, e23);
+    v.z = __builtin_bit_cast(uint32_t, e45); v.w = __builtin_bit_cast(uint32_t, e67);
+    return v;
+  };
   auto lstore8 = [&](uint16_t* dst, bool is_k, const Stage8& st) {
 #pragma unroll
     for (int i = 0; i < P8; i++) {
       const int p = tid + i * NT, row = p / PPR, slot = (p % PPR) ^ (is_k ? T::swz_k(row) : T::swz_v(row));
-      const bf16x2 e01 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8((int)st.r[i].x, 1.0f, false);
-      const bf16x2 e23 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8((int)st.r[i].x, 1.0f, true);
-      const bf16x2 e45 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8((int)st.r[i].y, 1.0f, false);
-      const bf16x2 e67 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8((int)st.r[i].y, 1.0f, true);
-      uint4 v;
-      v.x = __builtin_bit_cast(uint32_t, e01); v.y = __builtin_bit_cast(uint32_t, e23);
-      v.z = __builtin_bit_cast(uint32_t, e45); v.w = __builtin_bit_cast(uint32_t, e67);
-      *(uint4*)(dst + row * D + slot * 8) = v;
+      *(uint4*)(dst + row * D + slot * 8) = widen8(st.r[i]);
     }
   };
   Stage8 k8, v8;
@@ -622,6 +622,7 @@ k_beam_attn(AttnCtx c) {
     }
   }
 
+  bool too_high = false;                               // some column's scores rose too fast for the loop below
   if (ntiles > 0) {
     // Pipeline: iteration t issues S(t+1) = K(t+1).Q^T together with the softmax of S(t), then O += V(t).P(t).
     // K(t+2) and V(t+1) are written to LDS right after the barrier that opens iteration t, so one
@@ -644,10 +645,25 @@ k_beam_attn(AttnCtx c) {
             for (int i = 0; i < 16; i++) o_acc[db][cb][i] *= alpha[cb];
         }
     };
-    // one steady-state iteration: tile t (scores in s_in, column maxima in mx_cur) has a successor whose scores
-    // go to s_out.  The reference maximum is settled first (raising it, and rescaling O and the running sum, is a
-    // rare wave-uniform branch), so that the tile's MFMAs and exponentials form one straight-line block.
-    float mx_cur = -INFINITY;
+    // One steady-state iteration: tile t (scores in s_in) has a successor whose scores go to s_out.  What the tile before brought
+    // is settled first (raising the reference, and rescaling O and the running sum, is a rare wave-uniform branch), so that the
+    // tile's MFMAs and exponentials form one straight-line block.
+    float rs = 0.f;                                    // the tile's sum
+    auto settle = [&]() {
+      l_run[0] += rs;
+      if (__any(!(rs <= 1.f))) {
+        const float r = fmaxf(rs, __shfl_xor(rs, 32, 64));
+        too_high = too_high || __any(!(r <= T::kTooHigh));
+        const float m_new = r > 1.f ? m_run[0] + (T::kHead + (float)__builtin_amdgcn_frexp_expf(r)) : m_run[0];
+        const float alpha = __builtin_amdgcn_exp2f(m_run[0] - m_new);
+#pragma unroll
+        for (int db = 0; db < D / 32; db++)
+#pragma unroll
+          for (int i = 0; i < 16; i++) o_acc[db][0][i] *= alpha;
+        l_run[0] *= alpha;
+        m_run[0] = m_new;
+      }
+    };
     auto causal_mask = [&](f32x16 (&s)[KT / 32][NCB], int tok0) {
 #pragma unroll
       for (int sub = 0; sub < KT / 32; sub++)
@@ -659,20 +675,8 @@ k_beam_attn(AttnCtx c) {
     };
     auto step = [&](auto slot_c, f32x16 (&s_in)[KT / 32][NCB], f32x16 (&s_out)[KT / 32][NCB], int t) {      // tile t in slot slot_c
       constexpr int slot = decltype(slot_c)::value;
-      if (CAUSAL && seg0 + t * KT + KT - 1 > wave_tok0) {         // (wave-uniform) this tile reaches past the wave's first token
-        causal_mask(s_in, seg0 + t * KT);
-        mx_cur = T::colmax(s_in);
-      }
-      if (__any(mx_cur * cp > m_run[0] * cp + T::kLazy)) {
-        const float m_new = fmaxf(m_run[0], mx_cur);
-        const float alpha = __builtin_amdgcn_exp2f((m_run[0] - m_new) * cp);
-#pragma unroll
-        for (int db = 0; db < D / 32; db++)
-#pragma unroll
-          for (int i = 0; i < 16; i++) o_acc[db][0][i] *= alpha;
-        l_run[0] *= alpha;
-        m_run[0] = m_new;
-      }
+      settle();
+      if (CAUSAL && seg0 + t * KT + KT - 1 > wave_tok0) causal_mask(s_in, seg0 + t * KT);       // (wave-uniform) past the wave's first token
       tiles_landed();                                               // this wave's K(t+1) and V(t) loads (issued one step ago)
       __syncthreads();                                              // everyone's; and everyone is done with K(t) and V(t-1)
       if (KV8) {
@@ -685,10 +689,11 @@ k_beam_attn(AttnCtx c) {
         tload(false, slot ^ 1, min(t + 1, tl));                     // V(t+1) over V(t-1)
       }
       if (t == touch_own) touch_own_rows(prow0);
-      T::fused((slot ^ 1) * TILE, (2 + slot) * TILE, qop, s_in, s_out, o_acc, m_run[0] * cp, cp, l_run[0], mx_cur, rdo);
+      T::fused((slot ^ 1) * TILE, (2 + slot) * TILE, qop, s_in, s_out, o_acc, m_run[0], cp, rs, rdo);
     };
     // the last tile of the segment: the only one that can be partial, and it has no successor
     auto last = [&](f32x16 (&s_in)[KT / 32][NCB], int t) {
+      settle();
       all_landed();
       if (own_stage) uload(0, prow0);
       __syncthreads();
@@ -714,7 +719,10 @@ k_beam_attn(AttnCtx c) {
 
     f32x16 s_a[KT / 32][NCB], s_b[KT / 32][NCB];      // ping-pong score accumulators: no copies
     T::qk(flip * TILE, qop, s_a, rdo);
-    if (ntiles > 1) mx_cur = T::colmax(s_a);
+    if (ntiles > 1) {
+      if (CAUSAL && seg0 + KT - 1 > wave_tok0) causal_mask(s_a, seg0);
+      m_run[0] = T::colmax(s_a) * cp + T::kHead;       // (every column sees the segment's first token)
+    }
     // ntiles - 1 steps, then the last tile.  An odd step is peeled off first so that the loop runs
     // whole ping-pong pairs and the last tile is always in s_a.
     int t = 0;
@@ -731,13 +739,6 @@ k_beam_attn(AttnCtx c) {
       step(std::integral_constant<int, 1>(), s_b, s_a, t + 1);
     }
     last(s_a, t);
-    if (KV8) {                                         // prompt loop -> true units
-      m_run[0] *= c.k_scale;
-#pragma unroll
-      for (int db = 0; db < D / 32; db++)
-#pragma unroll
-        for (int i = 0; i < 16; i++) o_acc[db][0][i] *= c.v_scale;
-    }
   }
 
   float* s_set1 = (float*)(smem + 4 * TILE + MWG * D);     // KS = 2: the second set's O (in place of its tiles), as its lanes hold it,
@@ -751,25 +752,111 @@ k_beam_attn(AttnCtx c) {
   // rows (the rest are masked to -inf), and O^T += V_u^T . P^T follows.  Compared with per-lane dot
   // products this reads each beam's rows once instead of once per query head and replaces ~1000
   // VALU operations per lane by 16 MFMAs per wave.
-  if (KS == 2) {
-    if (set == 1)
-      for (int i = 0; i < set1_idle; i++) __syncthreads();
-    __syncthreads();                                       // every wave is done with the prompt tiles
-    if (set == 1) {
+  if (KS == 2 && set == 1)
+    for (int i = 0; i < set1_idle; i++) __syncthreads();
+  if (KS == 2 || own_stage || ntiles > 0) __syncthreads(); // every wave is done with the prompt tiles
+  uint16_t* s_uk = smem + wave * UR * KSTR;
+  uint16_t* s_uv = smem + NWAVES * UR * KSTR + wave * UR * VSTR;
+  // Online-softmax update of (m, l, O) by 32 rows in LDS, this wave's alone; keep(rho): the column sees row rho.
+  auto mini_tile = [&](const uint16_t* s_uk, int kstr, const uint16_t* s_uv, int vstr, auto&& keep, float cs, float& m, float& l) {
+    f32x16 su;
 #pragma unroll
-      for (int e = 0; e < D / 8; e++) {
-        const f32x4 v = {o_acc[e / 4][0][4 * (e % 4)], o_acc[e / 4][0][4 * (e % 4) + 1], o_acc[e / 4][0][4 * (e % 4) + 2], o_acc[e / 4][0][4 * (e % 4) + 3]};
-        *(f32x4*)(s_set1 + ((wave * (D / 8) + e) * 64 + lane) * 4) = v;
-      }
-      const f32x2 ml = {m_run[0], l_run[0]};
-      *(f32x2*)(s_set1_ml + (wave * 64 + lane) * 2) = ml;
+    for (int i = 0; i < 16; i++) su[i] = 0.f;
+#pragma unroll
+    for (int ks = 0; ks < D / 16; ks++) {
+      const bf16x8 a = as_bf16x8(*(const uint4*)(&s_uk[n32 * kstr + ks * 16 + G * 8]));
+      su = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qop[0][ks], su, 0, 0, 0);
     }
+    float mx = -INFINITY;
+    bool mine[16];
+#pragma unroll
+    for (int i = 0; i < 16; i++) {
+      mine[i] = keep(8 * (i / 4) + 4 * G + (i % 4));
+      if (mine[i]) mx = fmaxf(mx, su[i]);
+    }
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    const float m_new = fmaxf(m, mx * cs);
+    const bool any_key = m_new > -INFINITY;                // false only while the column has seen no key at all
+    const float alpha = any_key ? __builtin_amdgcn_exp2f(m - m_new) : 1.f;
+    float rsum = 0.f;
+#pragma unroll
+    for (int i = 0; i < 16; i++) {
+      const float pr = mine[i] ? __builtin_amdgcn_exp2f(fmaf(su[i], cs, -m_new)) : 0.f;
+      su[i] = pr;
+      rsum += pr;
+    }
+    l = l * alpha + rsum;
+    m = m_new;
+#pragma unroll
+    for (int db = 0; db < D / 32; db++)
+#pragma unroll
+      for (int i = 0; i < 16; i++) o_acc[db][0][i] *= alpha;
+    bf16x8 pu[UR / 16];
+#pragma unroll
+    for (int t = 0; t < UR / 16; t++)
+#pragma unroll
+      for (int e = 0; e < 8; e++) pu[t][e] = (__bf16)su[8 * t + e];
+    {
+      typedef short s16x8 __attribute__((ext_vector_type(8)));
+      const uint16_t* vb = s_uv + (4 * G + ((lane & 15) >> 2)) * vstr + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
+#pragma unroll
+      for (int t = 0; t < UR / 16; t++)
+#pragma unroll
+        for (int db = 0; db < D / 32; db++) {
+          const uint16_t* p0 = vb + t * 16 * vstr + db * 32;
+          s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(p0));
+          s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(p0 + 8 * vstr));
+          s16x8 both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+          o_acc[db][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, both), pu[t], o_acc[db][0], 0, 0, 0);
+        }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");                    // the mini-tiles are rewritten by the next pass
+  };
+  // The segment again for a wave with a column whose scores rose too fast: 32 tokens at a time through its mini-tiles, maxima first.  (The
+  // second set's waves have no more LDS to themselves than what they hand over in: their rows are not padded.)
+  auto redo = [&]() {
+    const bool packed = KS == 2 && set == 1;
+    uint16_t* k32 = packed ? (uint16_t*)s_set1 + wave * 2 * UR * D : s_uk;
+    uint16_t* v32 = packed ? k32 + UR * D : s_uv;
+    const int kstr = packed ? D : KSTR, vstr = packed ? D : VSTR;
+    m_run[0] = -INFINITY; l_run[0] = 0.f;
+#pragma unroll
+    for (int db = 0; db < D / 32; db++)
+#pragma unroll
+      for (int i = 0; i < 16; i++) o_acc[db][0][i] = 0.f;
+#pragma unroll 1
+    for (int tok0 = seg0; tok0 < seg1; tok0 += UR) {
+#pragma unroll 1
+      for (int i = 0; i < UP; i++) {
+        const int pi = lane + 64 * i, row = pi / PPR, col = (pi % PPR) * 8;
+        const size_t off = (size_t)min(tok0 + row, seg1 - 1) * tok_bytes + (size_t)col * EB;
+        uint4 kp, vp;
+        if constexpr (KV8) { kp = widen8(*(const uint2*)(kbase + off)); vp = widen8(*(const uint2*)(vbase + off)); }
+        else { kp = *(const uint4*)(kbase + off); vp = *(const uint4*)(vbase + off); }
+        *(uint4*)(&k32[row * kstr + col]) = kp;
+        *(uint4*)(&v32[row * vstr + col]) = vp;
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");                  // (the mini-tiles are this wave's alone, and LDS serves a wave in order)
+      mini_tile(k32, kstr, v32, vstr, [&](int rho) { return tok0 + rho < seg1 && tok0 + rho <= tokq; }, cp, m_run[0], l_run[0]);
+    }
+  };
+  if (__builtin_expect(too_high, 0)) redo();
+  if (KV8 && ntiles > 0) {                                 // prompt loop -> true units
+#pragma unroll
+    for (int db = 0; db < D / 32; db++)
+#pragma unroll
+      for (int i = 0; i < 16; i++) o_acc[db][0][i] *= c.v_scale;
+  }
+  if (KS == 2 && set == 1) {
+#pragma unroll
+    for (int e = 0; e < D / 8; e++) {
+      const f32x4 v = {o_acc[e / 4][0][4 * (e % 4)], o_acc[e / 4][0][4 * (e % 4) + 1], o_acc[e / 4][0][4 * (e % 4) + 2], o_acc[e / 4][0][4 * (e % 4) + 3]};
+      *(f32x4*)(s_set1 + ((wave * (D / 8) + e) * 64 + lane) * 4) = v;
+    }
+    const f32x2 ml = {m_run[0], l_run[0]};
+    *(f32x2*)(s_set1_ml + (wave * 64 + lane) * 2) = ml;
   }
   if (own_stage) {
-    float m = m_run[0], l = l_run[0];
-    if (KS == 1) __syncthreads();                          // every wave is done with the prompt tiles
-    uint16_t* s_uk = smem + wave * UR * KSTR;
-    uint16_t* s_uv = smem + NWAVES * UR * KSTR + wave * UR * VSTR;
     if (ntiles == 0) uload(0, prow0);
     for (int pass = 0; pass < npass; pass++) {
 #pragma unroll
@@ -779,64 +866,9 @@ k_beam_attn(AttnCtx c) {
         *(uint4*)(&s_uv[row * VSTR + col]) = uvp[i];
       }
       if (pass + 1 < npass) uload(pass + 1, own_row(pass + 1));               // (arrives while this pass is computed)
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");                  // (the mini-tiles are this wave's alone, and LDS serves a wave in order)
-      // scores of the 32 rows against the wave's 32 columns
-      f32x16 su;
-#pragma unroll
-      for (int i = 0; i < 16; i++) su[i] = 0.f;
-#pragma unroll
-      for (int ks = 0; ks < D / 16; ks++) {
-        const bf16x8 a = as_bf16x8(*(const uint4*)(&s_uk[n32 * KSTR + ks * 16 + G * 8]));
-        su = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qop[0][ks], su, 0, 0, 0);
-      }
-      // keep the column's own rows; online-softmax update of (m, l, O)
-      float mx = -INFINITY;
-      bool mine[16];
-#pragma unroll
-      for (int i = 0; i < 16; i++) {
-        const int rho = pass * UR + 8 * (i / 4) + 4 * G + (i % 4);
-        mine[i] = my_lo >= 0 && rho >= my_lo && rho < my_lo + c.u;
-        if (mine[i]) mx = fmaxf(mx, su[i]);
-      }
-      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-      const float m_new = fmaxf(m, mx);
-      const bool any_key = m_new > -INFINITY;              // false only while the column has seen no key at all
-      const float alpha = any_key ? __builtin_amdgcn_exp2f((m - m_new) * c.c) : 1.f;
-      float rs = 0.f;
-#pragma unroll
-      for (int i = 0; i < 16; i++) {
-        const float pr = mine[i] ? __builtin_amdgcn_exp2f((su[i] - m_new) * c.c) : 0.f;
-        su[i] = pr;
-        rs += pr;
-      }
-      l = l * alpha + rs;
-      m = m_new;
-#pragma unroll
-      for (int db = 0; db < D / 32; db++)
-#pragma unroll
-        for (int i = 0; i < 16; i++) o_acc[db][0][i] *= alpha;
-      bf16x8 pu[UR / 16];
-#pragma unroll
-      for (int t = 0; t < UR / 16; t++)
-#pragma unroll
-        for (int e = 0; e < 8; e++) pu[t][e] = (__bf16)su[8 * t + e];
-      {
-        typedef short s16x8 __attribute__((ext_vector_type(8)));
-        const uint16_t* vb = s_uv + (4 * G + ((lane & 15) >> 2)) * VSTR + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
-#pragma unroll
-        for (int t = 0; t < UR / 16; t++)
-#pragma unroll
-          for (int db = 0; db < D / 32; db++) {
-            const uint16_t* p0 = vb + t * 16 * VSTR + db * 32;
-            s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(p0));
-            s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(p0 + 8 * VSTR));
-            s16x8 both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-            o_acc[db][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, both), pu[t], o_acc[db][0], 0, 0, 0);
-          }
-      }
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");                  // the mini-tiles are rewritten by the next pass
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      mini_tile(s_uk, KSTR, s_uv, VSTR, [&](int rho) { rho += pass * UR; return my_lo >= 0 && rho >= my_lo && rho < my_lo + c.u; }, c.c, m_run[0], l_run[0]);
     }
-    m_run[0] = m; l_run[0] = l;
   }
 
   // ---- the second set's half of the segment joins the first's
@@ -846,8 +878,8 @@ k_beam_attn(AttnCtx c) {
     const f32x2 ml = *(const f32x2*)(s_set1_ml + (wave * 64 + lane) * 2);
     const float m_new = fmaxf(m_run[0], ml.x);
     const bool any_key = m_new > -INFINITY;                // false only for a column that has seen no key at all
-    const float a0 = any_key ? __builtin_amdgcn_exp2f((m_run[0] - m_new) * c.c) : 1.f;
-    const float a1 = any_key ? __builtin_amdgcn_exp2f((ml.x - m_new) * c.c) : 0.f;
+    const float a0 = any_key ? __builtin_amdgcn_exp2f(m_run[0] - m_new) : 1.f;
+    const float a1 = any_key ? __builtin_amdgcn_exp2f(ml.x - m_new) : 0.f;
     l_run[0] = l_run[0] * a0 + ml.y * a1;
     m_run[0] = m_new;
 #pragma unroll
@@ -866,7 +898,6 @@ k_beam_attn(AttnCtx c) {
     if (c.nsplit == 1) {
       // The wave's 32 rows x D outputs go through its own slice of LDS so that global memory sees whole
       // 256-byte rows (16 lanes x 16 bytes) instead of 8-byte pieces of 32 different rows per store.
-      if (KS == 1 && !own_stage && ntiles > 0) __syncthreads();       // nobody reads the tile slots any more
       uint16_t* s_o = smem + wave * 32 * KSTR;
       const float inv = (l_tot > 0.f) ? 1.0f / l_tot : 0.f;
 #pragma unroll
@@ -895,12 +926,11 @@ k_beam_attn(AttnCtx c) {
       if (c.lse && G == 0 && r >= 0) {
         int w, j;
         divmod_small(r, c.g, rcp_g2, &w, &j);
-        c.lse[((CAUSAL ? (size_t)row0 : (size_t)b * c.W) + w) * c.Hq + kvh * c.g + j] = (l_tot > 0.f) ? (m * c.c + __builtin_amdgcn_logf(l_tot)) * kLn2 : -INFINITY;
+        c.lse[((CAUSAL ? (size_t)row0 : (size_t)b * c.W) + w) * c.Hq + kvh * c.g + j] = (l_tot > 0.f) ? (m + __builtin_amdgcn_logf(l_tot)) * kLn2 : -INFINITY;
       }
     } else {
       // this segment's unnormalised fp32 partial O and (max, sum): staged through LDS like the final
       // output, half of the columns at a time
-      if (KS == 1 && !own_stage && ntiles > 0) __syncthreads();       // nobody reads the tile slots any more
       float* s_p = (float*)(smem + wave * 32 * KSTR);
       constexpr int CW = D / 2;                            // columns per round: a wave's slice holds 32 rows x CW floats
       constexpr int PSTR = KSTR / 2;                       // floats per staged row (CW + padding)
@@ -930,7 +960,7 @@ k_beam_attn(AttnCtx c) {
         int w, j;
         divmod_small(r, c.g, rcp_g2, &w, &j);
         const size_t prow = ((size_t)b * c.nsplit + sp) * ((size_t)c.W * c.Hq) + (size_t)w * c.Hq + kvh * c.g + j;
-        f32x2 ml = {(l_tot > 0.f) ? m * c.c : -INFINITY, l_tot};
+        f32x2 ml = {(l_tot > 0.f) ? m : -INFINITY, l_tot};
         *(f32x2*)(c.part_ml + prow * 2) = ml;
       }
     }

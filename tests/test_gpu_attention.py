@@ -182,3 +182,23 @@ def test_one_and_two_sets_of_wavefronts(gr, oracle_lib, d, B):
     rng = np.random.default_rng(8)
     tri = np.stack([np.arange(300) % B, rng.integers(0, 20, 300), rng.integers(0, 16, 300)], axis=1).astype(np.int32)
     _check(gr, oracle_lib, a, float(np.float32(1 / np.sqrt(d))), tri)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("rows,segments", [(128, 1), (256, 1), (256, 2)])
+@pytest.mark.parametrize("factor", [3.0, 7.0])
+def test_scores_that_jump_inside_the_prompt(gr, oracle_lib, d, rows, segments, factor):
+    """Keys that one beam's queries meet 34 to 50 bits (factor 3: its reference is raised after the tile) or 80 to 114 bits (factor 7: the
+    wavefront computes its columns again) above everything before them, in an early, a middle and the last tile of a prompt whose
+    tiles are even or odd in number, for workgroups of one and of two sets of wavefronts."""
+    lens, W, Hq, Hkv = (330, 400, 460), 40, 8, 2
+    a = rand_attn_case(900 + d + rows, len(lens), W, Hq, Hkv, d, 3, 2, lens)
+    q, k = gr_synth.bf16_bits_to_f32(a["q"]), gr_synth.bf16_bits_to_f32(a["k_shared"]).copy()
+    for b, (w, head, tok) in enumerate([(3, 1, 70), (39, 6, 200), (0, 4, 459)]):
+        k[a["cu_seqlens"][b] + tok, head // (Hq // Hkv)] = factor * q[b, w, head]
+    a["k_shared"] = gr_synth.f32_to_bf16_bits(k)
+    gr.gr_diag_attn_plan(rows, segments)
+    try:
+        _check(gr, oracle_lib, a, float(np.float32(1 / np.sqrt(d))))
+    finally:
+        gr.gr_diag_attn_plan(0, 0)

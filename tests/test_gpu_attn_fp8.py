@@ -121,3 +121,20 @@ def test_fp8kv_rejects_bad_scales(gr):
             gr.gr_beam_attn_fp8kv(bf16_to_dev(a["q"]), to_dev(k8), to_dev(k8), ks, vs, to_dev(a["cu_seqlens"]),
                                   bf16_to_dev(a["k_unshared"]), bf16_to_dev(a["v_unshared"]), 1, 1.0, 5, 5)
         assert e.value.status == -1
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("rows,factor", [(128, 3.0), (128, 7.0), (256, 7.0)])
+def test_fp8kv_scores_that_jump_inside_the_prompt(gr, oracle_lib, d, rows, factor):
+    """Keys far above everything before them: the reference is raised after the tile, or the wavefront computes its columns again."""
+    lens, W, Hq, Hkv = (330, 460), 40, 8, 2
+    a = rand_attn_case(950 + d + rows, len(lens), W, Hq, Hkv, d, 3, 2, lens)
+    q, k = gr_synth.bf16_bits_to_f32(a["q"]), gr_synth.bf16_bits_to_f32(a["k_shared"]).copy()
+    for b, (w, head, tok) in enumerate([(3, 1, 70), (0, 4, 300)]):
+        k[a["cu_seqlens"][b] + tok, head // (Hq // Hkv)] = factor * q[b, w, head]
+    a["k_shared"] = gr_synth.f32_to_bf16_bits(k)
+    gr.gr_diag_attn_plan(rows, 1)
+    try:
+        _check(gr, oracle_lib, a, float(np.float32(1 / np.sqrt(d))))
+    finally:
+        gr.gr_diag_attn_plan(0, 0)

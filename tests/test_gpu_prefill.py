@@ -162,3 +162,24 @@ def test_prefill_ragged_long_batch_sampled_rows(oracle_lib):
     assert err <= 2e-2, f"max-abs {err}"
     np.testing.assert_allclose(lse[rows, tri[:, 2]], ref_lse, rtol=0, atol=2e-3)
     assert np.isfinite(out[:int(c["cu"][-1])]).all()
+
+
+@pytest.mark.parametrize("d,max_L", [(64, 330), (128, 330), (128, 2049)])      # blocks of 128, 128 and 256 query rows
+@pytest.mark.parametrize("factor", [3.0, 7.0])
+def test_prefill_scores_that_jump_inside_the_prompt(oracle_lib, d, max_L, factor):
+    """Keys far above everything before them, in a tile before and on a block's diagonal: the reference is raised after the tile, or
+    the wavefront computes its columns again."""
+    import torch
+    import paper_2512_11529_amd as gr
+    gr.load_library()
+    c = _case(77 + d, (330, 200), 8, 2, d)
+    q, k = gr_synth.bf16_bits_to_f32(c["q"]), gr_synth.bf16_bits_to_f32(c["k"]).copy()
+    for row, head, tok in [(300, 1, 100), (329, 5, 328), (330 + 199, 0, 330 + 130)]:
+        k[tok, head // 4] = factor * q[row, head]
+    c["k"] = gr_synth.f32_to_bf16_bits(k)
+    scale = float(np.float32(1 / np.sqrt(d)))
+    out = torch.empty(c["q"].shape, dtype=torch.bfloat16, device="cuda:0")
+    gr.gr_prefill_attn(bf16_to_dev(c["q"]), bf16_to_dev(c["k"]), bf16_to_dev(c["v"]), to_dev(c["cu"]), scale, max_L, 530, out=out)
+    ref, _ = oracle_lib.prefill_attn_causal(c["q"], c["k"], c["v"], c["cu"], scale)
+    err = np.abs(out.float().cpu().numpy() - ref.reshape(out.shape)).max()
+    assert err <= 2e-2, f"max-abs {err}"
