@@ -17,9 +17,9 @@
  *   - All data pointers are DEVICE pointers unless a comment says "host".  Parameter structs and
  *     scalar arguments are host values read before the call returns.
  *   - The caller owns every buffer, including workspaces and the mask blob.  The library never
- *     allocates, frees or keeps device memory and holds no state between calls (two exceptions, stated
- *     where they are declared: the static scratch array of gr_beam_select_noalloc and the launch-plan
- *     override of gr_diag_attn_plan).
+ *     allocates, frees or keeps device memory and holds no state between calls (three exceptions, stated
+ *     where they are declared: the static scratch array of gr_beam_select_noalloc, the launch-plan
+ *     override of gr_diag_attn_plan and the page of host memory that gr_item_mask_build reports through).
  *   - The attention calls, gr_beam_select and gr_beam_reorder only enqueue kernels on `stream` (a hipStream_t passed as
  *     void*, NULL = default stream); they never synchronise.  gr_item_mask_build is a load-time
  *     call and synchronises `stream` once to report table errors.
@@ -157,7 +157,9 @@ size_t gr_item_mask_build_workspace_bytes(int64_t n_items, int32_t depth, int32_
 
 /* items_sorted: device int32 [n_items, depth].  mask_out: device, 256-byte aligned, mask_bytes >=
  * gr_item_mask_bytes().  Synchronises `stream`; returns GR_ERR_BAD_TABLE if the on-device check of
- * order / distinctness / token range fails (mask_out is then unspecified). */
+ * order / distinctness / token range fails (mask_out is then unspecified).  The first call of a process allocates one
+ * page of pinned host memory through which the kernels report (kept until the process ends; calls may run
+ * concurrently from any threads, on any streams and GPUs). */
 gr_status gr_item_mask_build(const int32_t* items_sorted, int64_t n_items, int32_t depth, int32_t V,
                              void* mask_out, size_t mask_bytes, void* workspace, size_t workspace_bytes,
                              void* stream);

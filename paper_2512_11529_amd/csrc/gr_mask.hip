@@ -10,6 +10,7 @@
 // taken in runs per thread (96-byte strides between lanes) and bits set by atomics in memory.
 // Both passes bring a block's rows in with whole-line 16-byte loads through LDS and take rows lane by lane, so
 // that every store is contiguous over the wavefront; a row's place in the pair list is a ballot rank.
+#include <mutex>
 #include "gr_internal.hpp"
 
 namespace {
@@ -75,8 +76,10 @@ __device__ __forceinline__ bool row_ok_and_flags(const int32_t* s_rows, int r, i
   return ok && gt;
 }
 
-// pass 1: validate rows, count pair starts per block
-__global__ void __launch_bounds__(kBuildThreads) k_mask_count(const int32_t* items, int64_t n, int V, int32_t* block_counts, int32_t* err) {
+// pass 1: validate rows, count pair starts per block; the sign bit of a block's count tells that its rows are not valid (so that no word
+// has to be cleared before: a launch of its own, 5 us).  The first block also writes the header.
+constexpr int32_t kBadBlock = (int32_t)0x80000000;
+__global__ void __launch_bounds__(kBuildThreads) k_mask_count(const int32_t* items, int64_t n, int V, int32_t* block_counts, gr_mask_header* head, gr_mask_header h) {
   __shared__ int32_t s_rows[3 * kRowsPerBlock + 3];
   __shared__ int s_cnt[kBuildWaves];
   const int rows = stage_rows(items, n, s_rows);
@@ -89,25 +92,33 @@ __global__ void __launch_bounds__(kBuildThreads) k_mask_count(const int32_t* ite
     if (r < rows && !row_ok_and_flags(s_rows, r, V, &t1, &pr)) bad = true;
     cnt += __popcll(__ballot(pr));
   }
-  if (bad) atomicOr(err, 1);
+  if (__any(bad)) cnt |= kBadBlock;
   if ((threadIdx.x & 63) == 0) s_cnt[threadIdx.x >> 6] = cnt;
   __syncthreads();
   if (threadIdx.x == 0) {
-    int sum = 0;
+    int sum = 0, sign = 0;
 #pragma unroll
-    for (int w = 0; w < kBuildWaves; w++) sum += s_cnt[w];
-    block_counts[blockIdx.x] = sum;
+    for (int w = 0; w < kBuildWaves; w++) { sum += s_cnt[w] & ~kBadBlock; sign |= s_cnt[w] & kBadBlock; }
+    block_counts[blockIdx.x] = sum | sign;
+    if (blockIdx.x == 0) *head = h;
   }
 }
 
-// Exclusive scan of the per-block counts by a single workgroup (large tables only, see kSumBlocks).
+// Exclusive scan of the per-block counts by a single workgroup (large tables only, see kSumBlocks).  The sign bit of a sum tells that some
+// block up to this one is not valid.
 __global__ void __launch_bounds__(1024) k_mask_scan(int32_t* counts, int nblocks) {
   __shared__ int s_part[1024];
+  __shared__ int s_first_bad;
   const int t = threadIdx.x;
   const int per = (nblocks + 1023) / 1024;
   const int lo = min(nblocks, t * per), hi = min(nblocks, lo + per);
+  if (t == 0) s_first_bad = nblocks;
+  __syncthreads();
   int sum = 0;
-  for (int i = lo; i < hi; i++) sum += counts[i];
+  for (int i = lo; i < hi; i++) {
+    sum += counts[i] & ~kBadBlock;
+    if (counts[i] < 0) atomicMin(&s_first_bad, i);
+  }
   s_part[t] = sum;
   __syncthreads();
   for (int o = 1; o < 1024; o <<= 1) {   // Hillis-Steele inclusive scan
@@ -117,34 +128,42 @@ __global__ void __launch_bounds__(1024) k_mask_scan(int32_t* counts, int nblocks
     __syncthreads();
   }
   int run = s_part[t] - sum;
-  for (int i = lo; i < hi; i++) { int c = counts[i]; counts[i] = run; run += c; }
+  for (int i = lo; i < hi; i++) { int c = counts[i] & ~kBadBlock; counts[i] = run | (i >= s_first_bad ? kBadBlock : 0); run += c; }
 }
 
 // pass 2: scatter pairs, fill offsets, copy the third column
 __global__ void __launch_bounds__(kBuildThreads) k_mask_scatter(const int32_t* items, int64_t n, int V, const int32_t* block_counts,
-                                                                bool scanned, MaskParts m, const int32_t* err) {
+                                                                bool scanned, MaskParts m, int32_t* err, int32_t* host_err) {
   __shared__ int32_t s_rows[3 * kRowsPerBlock + 3];
-  __shared__ int s_base[kBuildWaves];
+  __shared__ int s_base[kBuildWaves], s_bad[kBuildWaves];
   __shared__ int s_cnt[kRowsPerThread * kBuildWaves + 1];  // pair starts of every 64 consecutive rows, then their exclusive prefix and sum
-  if (*err) return;   // a bad table could index out of bounds; the host reports GR_ERR_BAD_TABLE
   const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
-  // pairs of all blocks in front of this one
-  int part = 0;
-  if (scanned) part = t == 0 ? block_counts[blockIdx.x] : 0;
-  else
-    for (int i = 4 * t; i < (int)blockIdx.x; i += 4 * kBuildThreads) {
+  // pairs of all blocks in front of this one, and whether one of these or this one is not valid
+  int part = 0, sign = 0;
+  if (scanned) {
+    if (t == 0) { sign = block_counts[blockIdx.x]; part = sign & ~kBadBlock; }
+  } else {
+    for (int i = 4 * t; i <= (int)blockIdx.x; i += 4 * kBuildThreads) {
       const int4 q = *(const int4*)(block_counts + i);     // (reads at most three counts past the last: inside the workspace)
       const int left = (int)blockIdx.x - i;
-      part += q.x + (left > 1 ? q.y : 0) + (left > 2 ? q.z : 0) + (left > 3 ? q.w : 0);
+      sign |= q.x | (left > 0 ? q.y : 0) | (left > 1 ? q.z : 0) | (left > 2 ? q.w : 0);
+      part += (left > 0 ? q.x & ~kBadBlock : 0) + (left > 1 ? q.y & ~kBadBlock : 0) + (left > 2 ? q.z & ~kBadBlock : 0) + (left > 3 ? q.w & ~kBadBlock : 0);
     }
+  }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) part += __shfl_xor(part, o, 64);
-  if (lane == 0) s_base[wave] = part;
+  const bool bad = __any(sign < 0);
+  if (lane == 0) { s_base[wave] = part; s_bad[wave] = bad; }
   const int rows = stage_rows(items, n, s_rows);           // (its barrier publishes s_base)
-  int base = 0;
+  int base = 0, stop = 0;
 #pragma unroll
-  for (int w = 0; w < kBuildWaves; w++) base += s_base[w];
+  for (int w = 0; w < kBuildWaves; w++) { base += s_base[w]; stop |= s_bad[w]; }
   const int64_t first = (int64_t)blockIdx.x * kRowsPerBlock;
+  if (t == 0 && first + rows == n) {                       // (the last block knows of all)
+    *err = stop;
+    if (host_err) *host_err = stop;
+  }
+  if (stop) return;   // (what lies behind bad rows could index out of bounds; the host reports GR_ERR_BAD_TABLE)
   bool nt1[kRowsPerThread], npr[kRowsPerThread];
   int rank[kRowsPerThread];
 #pragma unroll
@@ -239,7 +258,41 @@ __global__ void __launch_bounds__(kBitThreads) k_mask_bits(int V, MaskParts m, c
   }
 }
 
-__global__ void k_mask_begin(gr_mask_header* head, gr_mask_header h, int32_t* err) { *head = h; *err = 0; }
+// Words of host memory that the last block writes its verdict to, so that the call's end is one wait for the stream (a copy of four
+// bytes to pageable memory is a kernel, a staging buffer and a second wait: 12 us of a call).  One page for the process, until it ends;
+// a word belongs to one call at a time.  A call that finds none free copies the verdict from its workspace instead.
+class VerdictWords {
+ public:
+  int take() {                                             // a word's number, or -1
+    std::call_once(once_, [this] {
+      void* p = nullptr;
+      if (hipHostMalloc(&p, kWords * kStride, hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent) == hipSuccess) host_ = (char*)p;
+      else (void)hipGetLastError();
+    });
+    if (!host_) return -1;
+    uint64_t used = used_.load(std::memory_order_relaxed);
+    while (~used) {
+      const int w = __builtin_ctzll(~used);
+      if (used_.compare_exchange_weak(used, used | (uint64_t)1 << w, std::memory_order_acquire)) return w;
+    }
+    return -1;
+  }
+  void give_back(int w) { used_.fetch_and(~((uint64_t)1 << w), std::memory_order_release); }
+  volatile int32_t* host(int w) const { return (volatile int32_t*)(host_ + w * kStride); }
+  int32_t* device(int w) const {                           // on the current device
+    void* d = nullptr;
+    if (hipHostGetDevicePointer(&d, host_ + w * kStride, 0) == hipSuccess) return (int32_t*)d;
+    (void)hipGetLastError();
+    return nullptr;
+  }
+
+ private:
+  static constexpr int kWords = 64, kStride = 64;
+  std::once_flag once_;
+  std::atomic<uint64_t> used_{0};
+  char* host_ = nullptr;
+};
+VerdictWords g_verdicts;
 
 }  // namespace
 
@@ -281,14 +334,18 @@ extern "C" gr_status gr_item_mask_build(const int32_t* items_sorted, int64_t n_i
   m.pair_row = (int32_t*)(blob + h.off_pair_row);
   m.t3 = (int32_t*)(blob + h.off_t3);
 
-  hipLaunchKernelGGL(k_mask_begin, dim3(1), dim3(1), 0, stream, m.head, h, err);
-  hipLaunchKernelGGL(k_mask_count, dim3(nblocks), dim3(kBuildThreads), 0, stream, items_sorted, n_items, V, counts, err);
+  const int word = g_verdicts.take();
+  int32_t* host_err = word >= 0 ? g_verdicts.device(word) : nullptr;
+  hipLaunchKernelGGL(k_mask_count, dim3(nblocks), dim3(kBuildThreads), 0, stream, items_sorted, n_items, V, counts, m.head, h);
   if (scanned) hipLaunchKernelGGL(k_mask_scan, dim3(1), dim3(1024), 0, stream, counts, nblocks);
-  hipLaunchKernelGGL(k_mask_scatter, dim3(nblocks), dim3(kBuildThreads), 0, stream, items_sorted, n_items, V, counts, scanned, m, err);
+  hipLaunchKernelGGL(k_mask_scatter, dim3(nblocks), dim3(kBuildThreads), 0, stream, items_sorted, n_items, V, counts, scanned, m, err, host_err);
   hipLaunchKernelGGL(k_mask_bits, dim3(V), dim3(kBitThreads), (size_t)h.words * 32, stream, V, m, err);
-  GR_HIP_TRY(hipGetLastError());
-  int32_t host_err = 0;
-  GR_HIP_TRY(hipMemcpyAsync(&host_err, err, sizeof(int32_t), hipMemcpyDeviceToHost, stream));
-  GR_HIP_TRY(hipStreamSynchronize(stream));
-  return host_err ? GR_ERR_BAD_TABLE : GR_OK;
+  hipError_t hip = hipGetLastError();
+  int32_t verdict = 0;
+  if (hip == hipSuccess && !host_err) hip = hipMemcpyAsync(&verdict, err, sizeof(int32_t), hipMemcpyDeviceToHost, stream);
+  const hipError_t waited = hipStreamSynchronize(stream);  // (also after a failed launch: no kernel of this call writes the word later)
+  if (host_err) verdict = *g_verdicts.host(word);
+  if (word >= 0) g_verdicts.give_back(word);
+  if (hip != hipSuccess || waited != hipSuccess) return GR_ERR_HIP;
+  return verdict ? GR_ERR_BAD_TABLE : GR_OK;
 }
