@@ -157,29 +157,6 @@ struct AttnTile {
     __builtin_amdgcn_sched_group_barrier(0x008, PF * NCB, 0);
   }
 
-  // O^T += V^T . P^T.  V^T operand: d = 32*db + (lane%32), k slot e <-> token 16*s + 8*(e/4) + 4*G + e%4
-  static __device__ __forceinline__ void pv(int sv, const bf16x8 (&pop)[KT / 16][NCB], f32x16 (&o)[D / 32][NCB], const Rd& rdo) {
-    constexpr int N = (KT / 16) * (D / 32), PF = 4;      // operand i: slab i / (D/32), d block i % (D/32)
-    auto rd = [&](int i) { return read_v(sv, rdo, i / (D / 32), i % (D / 32)); };
-    bf16x8 a[N];
-#pragma unroll
-    for (int i = 0; i < PF; i++) a[i] = rd(i);
-#pragma unroll
-    for (int i = 0; i < N; i++) {
-      if (i + PF < N) a[i + PF] = rd(i + PF);
-#pragma unroll
-      for (int cb = 0; cb < NCB; cb++)
-        o[i % (D / 32)][cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], pop[i / (D / 32)][cb], o[i % (D / 32)][cb], 0, 0, 0);
-    }
-    __builtin_amdgcn_sched_group_barrier(0x100, 2 * PF, 1);
-#pragma unroll
-    for (int i = 0; i < N - PF; i++) {
-      __builtin_amdgcn_sched_group_barrier(0x008, NCB, 1);
-      __builtin_amdgcn_sched_group_barrier(0x100, 2, 1);
-    }
-    __builtin_amdgcn_sched_group_barrier(0x008, PF * NCB, 1);
-  }
-
   // Per-lane maximum of a tile's scores for the lane's query column (both halves of the column).
   static __device__ __forceinline__ float colmax(const f32x16 (&s)[KT / 32][NCB]) {
     float mx = -INFINITY;
@@ -256,56 +233,54 @@ struct AttnTile {
     }
   }
 
-  // Online softmax of one tile, one query column per lane (its other half lives in lane^32).
-  // The running reference m2 (log2 units) is only raised when some column of the wave exceeds it by more than
-  // kLazy: exp2 arguments stay <= kLazy, which fp32 sums and bf16 P hold easily, and the
-  // O accumulators need rescaling only on those rare tiles.  Returns (per column block) whether O
-  // must be multiplied by alpha[cb].
-  static constexpr float kLazy = 8.0f;
-  // The steady-state tiles do not look for their maximum (16 vector instructions a tile and an exchange between lanes).  The reference is
+  // No tile after a segment's first is searched for its maximum (16 vector instructions a tile and an exchange between lanes).  The reference is
   // the first tile's maximum plus kHead: probabilities start 2^-24 low, what lies far below the reference is lost at 2^-102 of the maximum
   // (nothing to a sum of fp32), and scores may rise 48 bits inside one tile.  A column whose tile sums to more than 1 gets a higher
   // reference after that tile; one with more than 2^kHead (where O could overflow) is computed again from the first token by a
   // loop that looks for maxima (k_beam_attn's `redo`).  The loop is bound by what it issues beside the MFMAs, so this is worth 3 to 4 %:
   // 32 x 4096 tokens x 256 beams 17 us of 505, 4 x 16384 x 512 in FP8 477 -> 459 us, 8 causal prompts of 1024-8192 1606 -> 1556.
   static constexpr float kHead = 24.0f, kTooHigh = 16777216.0f;
-  static __device__ __forceinline__ void softmax(f32x16 (&s)[KT / 32][NCB], bf16x8 (&pop)[KT / 16][NCB], float (&m2)[NCB],
-                                                 float (&l_run)[NCB], float (&alpha)[NCB], bool (&upd)[NCB], float c) {
+
+  // The segment's last tile, which no scores follow: O += V . P with the exponentials of the next 16 tokens between the MFMAs of the present
+  // ones.  V^T operand: d = 32*db + (lane%32), k slot e <-> token 16*s + 8*(e/4) + 4*G + e%4.
+  static __device__ __forceinline__ void finish(int sv, const f32x16 (&s)[KT / 32][NCB], f32x16 (&o)[D / 32][NCB], float m2, float c, float& rs, const Rd& rdo) {
+    static_assert(NCB == 1, "one column block per wave");
+    constexpr int DB = D / 32, N = NPV, PF = 4, EPC = 8 / DB;
+    auto rdv = [&](int i) { return read_v(sv, rdo, i / DB, i % DB); };
+    bf16x8 a[N], pop[KT / 16];
+    float p[32];
+    rs = 0.f;
+    auto exps = [&](int e0, int n) {
 #pragma unroll
-    for (int cb = 0; cb < NCB; cb++) {
-      float mx = s[0][cb][0];
-#pragma unroll
-      for (int sub = 0; sub < KT / 32; sub++)
-#pragma unroll
-        for (int i = 0; i < 16; i++) mx = fmaxf(mx, s[sub][cb][i]);
-      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-      upd[cb] = __any(mx * c > m2[cb] + kLazy);
-      const float m_new = upd[cb] ? fmaxf(m2[cb], mx * c) : m2[cb];
-      alpha[cb] = __builtin_amdgcn_exp2f(m2[cb] - m_new);
-      float rs = 0.f;
-#pragma unroll
-      for (int sub = 0; sub < KT / 32; sub++)
-#pragma unroll
-        for (int i = 0; i < 16; i++) {
-          const float p = __builtin_amdgcn_exp2f(fmaf(s[sub][cb][i], c, -m_new));
-          s[sub][cb][i] = p;
-          rs += p;
-        }
-      l_run[cb] = l_run[cb] * alpha[cb] + rs;
-      m2[cb] = m_new;
-      // P^T as B operands: slab t = accumulator registers 8*(t%2) .. +7 of sub-tile t/2
-#pragma unroll
-      for (int t = 0; t < KT / 16; t++) {
-        bf16x8 pvv;
-#pragma unroll
-        for (int e = 0; e < 8; e += 2) {
-          f32x2 two = {s[t / 2][cb][8 * (t % 2) + e], s[t / 2][cb][8 * (t % 2) + e + 1]};
-          bf16x2 h = __builtin_convertvector(two, bf16x2);
-          pvv[e] = h[0];
-          pvv[e + 1] = h[1];
-        }
-        pop[t][cb] = pvv;
+      for (int e = e0; e < e0 + n; e++) {
+        p[e] = __builtin_amdgcn_exp2f(fmaf(s[e / 16][0][e % 16], c, -m2));
+        rs += p[e];
       }
+    };
+    auto pack = [&](int t) {
+#pragma unroll
+      for (int k = 0; k < 8; k += 2) {
+        const f32x2 two = {p[8 * t + k], p[8 * t + k + 1]};
+        const bf16x2 h = __builtin_convertvector(two, bf16x2);
+        pop[t][k] = h[0];
+        pop[t][k + 1] = h[1];
+      }
+    };
+#pragma unroll
+    for (int i = 0; i < PF; i++) a[i] = rdv(i);
+    exps(0, 8);
+    pack(0);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < N; i++) {
+      const int t = i / DB, k = i % DB;
+      if (i + PF < N) a[i + PF] = rdv(i + PF);
+      o[k][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], pop[t], o[k][0], 0, 0, 0);
+      if (t + 1 < KT / 16) {
+        exps(8 * (t + 1) + EPC * k, EPC);
+        if (k == DB - 1) pack(t + 1);
+      }
+      __builtin_amdgcn_sched_barrier(0);
     }
   }
 };
@@ -560,13 +535,15 @@ k_beam_attn(AttnCtx c) {
   };
   const uint16_t* ku_b = c.ku + (size_t)b * c.W * c.ND * c.Hkv * D;        // this request's own-token caches
   const uint16_t* vu_b = c.vu + (size_t)b * c.W * c.ND * c.Hkv * D;
+  const int Ru = __builtin_amdgcn_readfirstlane(R);
   auto uload = [&](int pass, int prow_l) {               // 32 rows x D/8 pieces per tensor; a row = PPR consecutive lanes
 #pragma unroll
     for (int i = 0; i < UP; i++) {
       const int pi = lane + 64 * i, row = pi / PPR, col = (pi % PPR) * 8;
-      const int prow = __shfl(prow_l, row, 64);
       ukp[i] = make_uint4(0, 0, 0, 0);
       uvp[i] = make_uint4(0, 0, 0, 0);
+      if (pass * UR + i * (64 / PPR) >= Ru) continue;      // (wave-uniform)
+      const int prow = __shfl(prow_l, row, 64);
       if (pass * UR + row < R) {
         const uint32_t off = (uint32_t)(prow * (c.Hkv * D) + kvh * D + col);
         ukp[i] = *(const uint4*)(ku_b + off);
@@ -635,16 +612,6 @@ k_beam_attn(AttnCtx c) {
     asm volatile("" : "+v"(prow0));                    // (waited for here, not at its first use)
     __syncthreads();                                   // K(0), K(1) are in LDS, and V(0) where it was requested with them
 
-    auto rescale = [&](const float (&alpha)[NCB], const bool (&upd)[NCB]) {
-#pragma unroll
-      for (int cb = 0; cb < NCB; cb++)
-        if (upd[cb]) {
-#pragma unroll
-          for (int db = 0; db < D / 32; db++)
-#pragma unroll
-            for (int i = 0; i < 16; i++) o_acc[db][cb][i] *= alpha[cb];
-        }
-    };
     // One steady-state iteration: tile t (scores in s_in) has a successor whose scores go to s_out.  What the tile before brought
     // is settled first (raising the reference, and rescaling O and the running sum, is a rare wave-uniform branch), so that the
     // tile's MFMAs and exponentials form one straight-line block.
@@ -704,17 +671,13 @@ k_beam_attn(AttnCtx c) {
 #pragma unroll
           for (int i = 0; i < 16; i++) {
             const int kv = tok0 + sub * 32 + 8 * (i / 4) + 4 * G + (i % 4);
-#pragma unroll
-            for (int cb = 0; cb < NCB; cb++) s_in[sub][cb][i] = (kv >= seg1) ? -INFINITY : s_in[sub][cb][i];
+            s_in[sub][0][i] = (kv >= seg1) ? -INFINITY : s_in[sub][0][i];
           }
       }
       if (CAUSAL) causal_mask(s_in, tok0);
-      bf16x8 pop[KT / 16][NCB];
-      float alpha[NCB];
-      bool upd[NCB];
-      T::softmax(s_in, pop, m_run, l_run, alpha, upd, cp);
-      rescale(alpha, upd);
-      T::pv(2 * TILE, pop, o_acc, rdo);
+      if (t == 0) m_run[0] = T::colmax(s_in) * cp + T::kHead;
+      T::finish(2 * TILE, s_in, o_acc, m_run[0], cp, rs, rdo);
+      settle();
     };
 
     f32x16 s_a[KT / 32][NCB], s_b[KT / 32][NCB];      // ping-pong score accumulators: no copies
@@ -757,8 +720,9 @@ k_beam_attn(AttnCtx c) {
   if (KS == 2 || own_stage || ntiles > 0) __syncthreads(); // every wave is done with the prompt tiles
   uint16_t* s_uk = smem + wave * UR * KSTR;
   uint16_t* s_uv = smem + NWAVES * UR * KSTR + wave * UR * VSTR;
-  // Online-softmax update of (m, l, O) by 32 rows in LDS, this wave's alone; keep(rho): the column sees row rho.
-  auto mini_tile = [&](const uint16_t* s_uk, int kstr, const uint16_t* s_uv, int vstr, auto&& keep, float cs, float& m, float& l) {
+  // (m, l, O) joined by 32 rows in LDS, this wave's alone; the column sees row base + k where base + k is below `rows` (as unsigned numbers).
+  // The reference is raised first only where the rows' sum shows that it has to be.
+  auto mini_tile = [&](const uint16_t* s_uk, int kstr, const uint16_t* s_uv, int vstr, int base, unsigned rows, float cs, float& m, float& l) {
     f32x16 su;
 #pragma unroll
     for (int i = 0; i < 16; i++) su[i] = 0.f;
@@ -767,35 +731,41 @@ k_beam_attn(AttnCtx c) {
       const bf16x8 a = as_bf16x8(*(const uint4*)(&s_uk[n32 * kstr + ks * 16 + G * 8]));
       su = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qop[0][ks], su, 0, 0, 0);
     }
-    float mx = -INFINITY;
-    bool mine[16];
+#pragma unroll
+    for (int i = 0; i < 16; i++) su[i] = (unsigned)(base + 8 * (i / 4) + 4 * G + (i % 4)) < rows ? su[i] : -INFINITY;
+    float pr[16], rsum = 0.f;
 #pragma unroll
     for (int i = 0; i < 16; i++) {
-      mine[i] = keep(8 * (i / 4) + 4 * G + (i % 4));
-      if (mine[i]) mx = fmaxf(mx, su[i]);
+      pr[i] = __builtin_amdgcn_exp2f(fmaf(su[i], cs, -m));
+      rsum += pr[i];
     }
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-    const float m_new = fmaxf(m, mx * cs);
-    const bool any_key = m_new > -INFINITY;                // false only while the column has seen no key at all
-    const float alpha = any_key ? __builtin_amdgcn_exp2f(m - m_new) : 1.f;
-    float rsum = 0.f;
+    if (__any(!(rsum <= T::kTooHigh))) {                   // (or the column has seen no key yet: m is -inf)
+      float mx = -INFINITY;
 #pragma unroll
-    for (int i = 0; i < 16; i++) {
-      const float pr = mine[i] ? __builtin_amdgcn_exp2f(fmaf(su[i], cs, -m_new)) : 0.f;
-      su[i] = pr;
-      rsum += pr;
+      for (int i = 0; i < 16; i++) mx = fmaxf(mx, su[i]);
+      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+      const float m_new = fmaxf(m, mx * cs + T::kHead);
+      const bool any_key = m_new > -INFINITY;
+      const float alpha = any_key ? __builtin_amdgcn_exp2f(m - m_new) : 1.f;
+      rsum = 0.f;
+#pragma unroll
+      for (int i = 0; i < 16; i++) {
+        pr[i] = any_key ? __builtin_amdgcn_exp2f(fmaf(su[i], cs, -m_new)) : 0.f;
+        rsum += pr[i];
+      }
+      l *= alpha;
+      m = m_new;
+#pragma unroll
+      for (int db = 0; db < D / 32; db++)
+#pragma unroll
+        for (int i = 0; i < 16; i++) o_acc[db][0][i] *= alpha;
     }
-    l = l * alpha + rsum;
-    m = m_new;
-#pragma unroll
-    for (int db = 0; db < D / 32; db++)
-#pragma unroll
-      for (int i = 0; i < 16; i++) o_acc[db][0][i] *= alpha;
+    l += rsum;
     bf16x8 pu[UR / 16];
 #pragma unroll
     for (int t = 0; t < UR / 16; t++)
 #pragma unroll
-      for (int e = 0; e < 8; e++) pu[t][e] = (__bf16)su[8 * t + e];
+      for (int e = 0; e < 8; e++) pu[t][e] = (__bf16)pr[8 * t + e];
     {
       typedef short s16x8 __attribute__((ext_vector_type(8)));
       const uint16_t* vb = s_uv + (4 * G + ((lane & 15) >> 2)) * vstr + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
@@ -837,7 +807,7 @@ k_beam_attn(AttnCtx c) {
         *(uint4*)(&v32[row * vstr + col]) = vp;
       }
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");                  // (the mini-tiles are this wave's alone, and LDS serves a wave in order)
-      mini_tile(k32, kstr, v32, vstr, [&](int rho) { return tok0 + rho < seg1 && tok0 + rho <= tokq; }, cp, m_run[0], l_run[0]);
+      mini_tile(k32, kstr, v32, vstr, tok0, CAUSAL ? min((unsigned)seg1, (unsigned)tokq + 1u) : (unsigned)seg1, cp, m_run[0], l_run[0]);
     }
   };
   if (__builtin_expect(too_high, 0)) redo();
@@ -867,7 +837,7 @@ k_beam_attn(AttnCtx c) {
       }
       if (pass + 1 < npass) uload(pass + 1, own_row(pass + 1));               // (arrives while this pass is computed)
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      mini_tile(s_uk, KSTR, s_uv, VSTR, [&](int rho) { rho += pass * UR; return my_lo >= 0 && rho >= my_lo && rho < my_lo + c.u; }, c.c, m_run[0], l_run[0]);
+      mini_tile(s_uk, KSTR, s_uv, VSTR, pass * UR - my_lo, my_lo >= 0 ? (unsigned)c.u : 0u, c.c, m_run[0], l_run[0]);
     }
   }
 
