@@ -35,6 +35,7 @@ constexpr int kSelThreads = 1024;
 constexpr int kListCap = 8192;      // survivors that fit in LDS
 constexpr int kChunkCap = 4096;     // keys whose candidates are looked at again by the fast path
 constexpr int kUnitCap = 8192;      // units of four candidates that are
+constexpr int kDirectQuads = 512;   // quads of scores of short gathered rows that are all taken at once
 constexpr int kHistBins = 2048;
 constexpr int kMaxMaskWords = 1024; // V <= 32768
 constexpr int kBlockV = 8192;       // logits of a row that a workgroup holds in registers at a time
@@ -725,10 +726,10 @@ __global__ void __launch_bounds__(NT, STRIDE ? 4 : 6) k_rows(SelCtx c) {
 // Visit every finite candidate of request b.  f(score, w * V + place, pred) is called wave-convergently
 // (pred = this lane holds a candidate).  Rows given by bit masks are strided by the whole
 // workgroup; rows given by child lists are taken one per wavefront.
-template <class F>
+template <bool LISTED, class F>
 __device__ __forceinline__ void for_each_candidate(const SelCtx& c, const MaskView& mv, int b, F&& f) {
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, nw = blockDim.x >> 6;
-  if (!c.blob || c.step == 0) {
+  if (!LISTED && (!c.blob || c.step == 0)) {
     for (int w = 0; w < c.W; w++) {
       const int row = b * c.W + w;
       if (c.row_info[row] == ROW_DEAD) continue;
@@ -746,7 +747,6 @@ __device__ __forceinline__ void for_each_candidate(const SelCtx& c, const MaskVi
     for (int w = wave; w < c.W; w += nw) {
       const int row = b * c.W + w;
       if (c.row_info[row] == ROW_DEAD) continue;
-      const bool gathered = (c.row_info[row] & 3) == ROW_SPARSE;
       const float bias = c.row_bias[row];
       const float* x = c.logits + (size_t)row * c.V;
       const uint32_t flat0 = (uint32_t)w * (uint32_t)c.V;
@@ -757,7 +757,7 @@ __device__ __forceinline__ void for_each_candidate(const SelCtx& c, const MaskVi
         const int i = i0 + lane;
         const int v = i < n ? list[i] : 0;
         const float score = i < n ? __fadd_rn(bias, x[v]) : -INFINITY;
-        f(score, flat0 + (gathered ? i : v), score > -INFINITY);
+        f(score, flat0 + (LISTED ? i : v), score > -INFINITY);
       }
     }
   }
@@ -796,6 +796,7 @@ __device__ __forceinline__ Bins make_bins(float hi, float range) {
 
 // Exact MSB radix select of the W best composite keys over ALL candidates (slow, always correct).
 // Leaves the survivors in s_list and returns their number.
+template <bool LISTED>
 __device__ int radix_select_all(const SelCtx& c, const MaskView& mv, int b, uint64_t* s_list, uint32_t* s_hist) {
   __shared__ uint64_t s_prefix;
   __shared__ uint32_t s_need, s_bin, s_cnt;
@@ -811,7 +812,7 @@ __device__ int radix_select_all(const SelCtx& c, const MaskView& mv, int b, uint
     const int nbins = 1 << width;
     for (int i = tid; i < nbins; i += kSelThreads) s_hist[i] = 0;
     __syncthreads();
-    for_each_candidate(c, mv, b, [&](float score, uint32_t flat, bool pred) {
+    for_each_candidate<LISTED>(c, mv, b, [&](float score, uint32_t flat, bool pred) {
       const uint64_t k = composite(score, flat);
       const bool in = pred && (pass == 0 || (k >> shift) == prefix);
       const uint32_t dgt = (uint32_t)(k >> lo_shift) & (uint32_t)(nbins - 1);
@@ -864,7 +865,7 @@ __device__ int radix_select_all(const SelCtx& c, const MaskView& mv, int b, uint
   }
   if (tid == 0) s_cnt = 0;
   __syncthreads();
-  for_each_candidate(c, mv, b, [&](float score, uint32_t flat, bool pred) {
+  for_each_candidate<LISTED>(c, mv, b, [&](float score, uint32_t flat, bool pred) {
     const uint64_t k = composite(score, flat);
     if (pred && (take_all || (k >> shift) >= prefix)) {
       const uint32_t idx = atomicAdd(&s_cnt, 1u);
@@ -907,6 +908,8 @@ __device__ __forceinline__ void hist_threshold_all(uint32_t* s_hist, uint32_t wa
 // without a mask (25 / 34 / 27 and 28 us when all 64 K chunk keys of a request were read and re-read chunks lay across eight lines);
 // one request x 16 beams 8 us (12 us).  Code size is part of it: unrolled over registers this kernel was 81 KB and took up
 // to twice as long, because each instruction line is fetched once per launch and used once; hence the rolled loops.
+// LISTED: the call's rows are gathered ones (k_rows_listed), else streamed ones (k_rows); each is half of the code.
+template <bool LISTED>
 __global__ void __launch_bounds__(kSelThreads) k_select(SelCtx c) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   uint64_t* s_list = (uint64_t*)smem;
@@ -922,8 +925,8 @@ __global__ void __launch_bounds__(kSelThreads) k_select(SelCtx c) {
   float* s_rbest = (float*)(s_ra + kMaxW);                   // best score
   constexpr int NW = kSelThreads / 64;
   __shared__ float2 s_redf[2 * NW];
-  __shared__ uint32_t s_redu[2 * NW];
-  __shared__ uint32_t s_n, s_nd, s_ns, s_nu, s_most;
+  __shared__ uint32_t s_redu[2 * NW], s_quads[NW];
+  __shared__ uint32_t s_n, s_ng, s_nd, s_ns, s_nu, s_most;
   __shared__ int s_thr;
   int parf = 0, paru = 0;
   const int b = blockIdx.x, tid = threadIdx.x;
@@ -937,11 +940,30 @@ __global__ void __launch_bounds__(kSelThreads) k_select(SelCtx c) {
   const int gsh = c.W * kGroups <= kGroupCap ? 4 : 3;        // log2 of the groups per row
   const int ngroups = c.W << gsh;
   float hi = -INFINITY, lo = INFINITY;                       // best and worst group
+  // what k_rows left of a row beside them; asked for together with the groups (by themselves they are a round trip of their own, 0.5 us)
+  struct Row { int info, a; float bias; };
+  auto row_of = [&](int w) {
+    const size_t row = (size_t)b * c.W + w;
+    Row r;
+    r.info = c.row_info[row]; r.bias = c.row_bias[row];
+    r.a = 0;
+    if (LISTED) r.a = c.row_start[row];
+    else if (c.blob && c.step == 1) r.a = c.prefix_in[row * c.depth];
+    else if (c.blob && c.step == 2) r.a = c.range_in[2 * row];
+    return r;
+  };
+  auto keep_row = [&](int w, const Row& r) {
+    s_rbias[w] = r.bias;
+    s_rinfo[w] = r.info;
+    s_ra[w] = r.a;
+  };
+  Row own = {ROW_DEAD, 0, 0.f};
+  if (tid < c.W) own = row_of(tid);
 #pragma unroll 2
   for (int q = tid; q < c.W * (kGroups / 4); q += kSelThreads) {
     const int w = q / (kGroups / 4), first = 4 * (q % (kGroups / 4)), info = info_b[w];
     float4 g = group4[q];
-    const int ng = (info & 3) == ROW_DENSE ? kGroups : (info & 3) == ROW_SPARSE ? ((info >> 2) <= kScoreMax ? ((info >> 2) + 15) >> 4 : kGroups) : 0;
+    const int ng = (info & 3) == ROW_DEAD ? 0 : LISTED && (info >> 2) <= kScoreMax ? ((info >> 2) + 15) >> 4 : kGroups;
     if (first >= ng) g.x = -INFINITY;
     if (first + 1 >= ng) g.y = -INFINITY;
     if (first + 2 >= ng) g.z = -INFINITY;
@@ -955,66 +977,109 @@ __global__ void __launch_bounds__(kSelThreads) k_select(SelCtx c) {
     low(g.x); low(g.y); low(g.z); low(g.w);
   }
   // ---- the request's rows
+  if (tid < c.W) keep_row(tid, own);
 #pragma unroll 1
-  for (int w = tid; w < c.W; w += kSelThreads) {
-    const size_t row = (size_t)b * c.W + w;
-    const int info = c.row_info[row], start = c.row_start[row];
-    int a = 0;
-    if (c.blob && c.step == 1) a = c.prefix_in[row * c.depth];
-    else if (c.blob && c.step == 2) a = c.range_in[2 * row];
-    s_rbias[w] = c.row_bias[row];
-    s_rinfo[w] = info;
-    s_ra[w] = (info & 3) == ROW_SPARSE ? start : a;
+  for (int w = tid + kSelThreads; w < c.W; w += kSelThreads) keep_row(w, row_of(w));
+  // quads of scores that they left, kNotShort for a row that is not a short one; and a bit for a dead row
+  constexpr uint32_t kNotShort = 1u << 16, kSomeDead = 1u << 27;       // (1024 rows of at most 60 quads stay below the one, all of the one below the other)
+  uint32_t own_quads = 0, quads_incl = 0;
+  if (LISTED) {
+    own_quads = (own.info & 3) == ROW_DEAD ? 0u : (own.info >> 2) <= kScoreMax ? (uint32_t)((own.info >> 2) + 3) >> 2 : kNotShort;
+    quads_incl = wave_incl_scan(own_quads);
+    const bool some_dead = __any((own.info & 3) == ROW_DEAD && tid < c.W);
+    if (gr_lane() == 63) s_quads[tid >> 6] = quads_incl | (some_dead ? kSomeDead : 0u);
   }
-  if (tid == 0) { s_n = 0; s_nd = 0; s_ns = 0; s_nu = 0; s_most = 0; }
+  if (tid == 0) { s_n = 0; s_ng = 0; s_nd = 0; s_ns = 0; s_nu = 0; s_most = 0; }
   for (int i = tid; i < kHistBins; i += kSelThreads) s_hist[i] = 0;
   block_max_min<NW>(hi, lo, s_redf, parf);                   // (its barrier publishes the row table and the groups)
 
   int n = 0;
   if (hi > -INFINITY) {
-    // ---- threshold that at least W groups reach (no threshold when there are fewer)
-    Bins bins = make_bins(hi, hi - lo);
-#pragma unroll 1
-    for (int i = tid; i < ngroups; i += kSelThreads)
-      if (s_group[i] > -INFINITY) atomicAdd(&s_hist[bins.of(s_group[i])], 1u);
-    __syncthreads();
-    hist_threshold_all(s_hist, (uint32_t)c.W, &s_thr, s_redu, paru);
-    __syncthreads();
-    float T = bins.floor_of(s_thr);
-    // ---- groups that reach it
-#pragma unroll 1
-    for (int i = tid; i < ngroups; i += kSelThreads) {
-      if (!(s_group[i] >= T)) continue;
-      const uint32_t pos = atomicAdd(&s_n, 1u);
-      if (pos < (uint32_t)kUnitCap) s_units[pos] = (uint32_t)i;
+    // Few scores of short gathered rows (the last level, as a rule): all of them are candidates, and the worst of the groups, which as many as
+    // there are rows reach, is the threshold.  (Up to kDirectQuads: scores as good as equal are ranked one by one further down.  The
+    // last level of 8 x 128 beams 9.7 -> 6.6 us, of one request x 16 beams 8.1 -> 5.3.)
+    uint32_t per_wave = 0, sum = 0;
+    if (LISTED) {
+      per_wave = wave_incl_scan(gr_lane() < NW ? s_quads[gr_lane() & (NW - 1)] : 0u);
+      sum = (uint32_t)__builtin_amdgcn_readlane((int)per_wave, 63);
     }
-    __syncthreads();
-    const int ng = (int)s_n, ssh = 6 - gsh;                  // log2 of the threads to a listed group
-    bool fallback = ng > kUnitCap;
-    const int quarters = min(ng, kUnitCap) << ssh;
+    const uint32_t quads = sum & (kSomeDead - 1u);
+    const bool short_rows = LISTED && c.W <= kSelThreads && quads < kNotShort, direct = short_rows && quads <= (uint32_t)kDirectQuads;
+    Bins bins = make_bins(hi, hi - lo);
+    float T, scale;                                          // threshold; bins of one width down to it
+    auto scale_to = [&](float t) { return t > kNoThreshold ? (hi > t ? fminf((float)(kHistBins - 1) / (hi - t), 1e30f) : 0.f) : 64.f; };
+    bool fallback = false;
+    int quarters = 0;
+    const int ssh = 6 - gsh;                                 // log2 of the threads to a listed group
+    uint32_t most = 0;
+    // (an atomic per thread whose row is longer than those before it, not per key: lanes with values of their own go one by one)
+    auto note_most = [&]() { if (most > 0 && most > *(volatile uint32_t*)&s_most) atomicMax(&s_most, most); };
+    auto add = [&](bool front, int w, int key) {
+      const uint32_t pos = atomicAdd(front ? &s_nd : &s_ns, 1u);
+      if (pos < (uint32_t)kChunkCap) s_chunks[front ? pos : kChunkCap - 1 - pos] = ((uint32_t)w << 8) | (uint32_t)key;
+    };
+    auto take = [&](int w, int q, const float4& f) {         // the candidates of a short gathered row's quad
+      const float v[4] = {f.x, f.y, f.z, f.w};
+      const int left = (s_rinfo[w] >> 2) - 4 * q;            // (past the row's last wavefront of children nothing was written)
+#pragma unroll
+      for (int j = 0; j < 4; j++) {
+        if (j >= left || !(v[j] >= T)) continue;
+        atomicAdd(&s_hist[key_bin(hi, scale, v[j])], 1u);
+        const uint32_t pos = atomicAdd(&s_n, 1u);
+        if (pos < (uint32_t)kListCap) s_list[pos] = composite(v[j], (uint32_t)w * (uint32_t)c.V + (uint32_t)(4 * q + j));
+      }
+    };
     auto quarter = [&](int i) { return ((int)s_units[i >> ssh] << ssh) + (i & ((1 << ssh) - 1)); };      // row << 6 | quarter of the row's 16 groups
     // the keys of a quarter group of a streamed or long gathered row: the first one's number, and how many
     auto quarter_keys = [&](const float* fine, int q, int info, int* key, int* num) {
-      const int gs = (info & 3) == ROW_DENSE ? 4 : group_shift(key_count(info >> 2));
+      const int gs = !LISTED ? 4 : group_shift(key_count(info >> 2));
       *num = 1 << (gs - 2);
       *key = ((q >> 2) << gs) + ((q & 3) << (gs - 2));
       const uint2 k = *(const uint2*)(fine + 2 * (*key >> 2));
       return ((uint64_t)k.y << 32 | k.x) >> (16 * (*key & 3));
     };
     auto last_key = [&](int w) { return s_rbest[w] < T ? -1 : (int)key16(s_rbest[w], T); };
-    auto add = [&](bool front, int w, int key) {
-      const uint32_t pos = atomicAdd(front ? &s_nd : &s_ns, 1u);
-      if (pos < (uint32_t)kChunkCap) s_chunks[front ? pos : kChunkCap - 1 - pos] = ((uint32_t)w << 8) | (uint32_t)key;
-    };
-    // (an atomic per thread whose row is longer than those before it, not per key: lanes with values of their own go one by one)
-    uint32_t most = 0;
-    auto note_most = [&]() { if (most > 0 && most > *(volatile uint32_t*)&s_most) atomicMax(&s_most, most); };
-    // ---- the finer keys behind them that reach it (four threads to a group, one round of loads for all)
+    if (direct) {
+      const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+      const uint32_t quad0 = (wave ? (uint32_t)__builtin_amdgcn_readlane((int)per_wave, wave - 1) & (kSomeDead - 1u) : 0u) + quads_incl - own_quads;
+      for (uint32_t k = 0; k < own_quads; k++) s_chunks[kChunkCap - 1 - (quad0 + k)] = ((uint32_t)tid << 8) | k;
+      T = sum < kSomeDead ? lo : kNoThreshold;
+      scale = scale_to(T);
+      if (tid == 0) s_ns = quads;
+      __syncthreads();                                       // (the list takes the groups' place)
+      for (uint32_t i = tid; i < quads; i += kSelThreads) {
+        const uint32_t ent = s_chunks[kChunkCap - 1 - i];
+        const int w = (int)(ent >> 8), q = (int)(ent & 255u);
+        take(w, q, *(const float4*)(data + (size_t)w * kRowFloats + 4 * q));
+      }
+    } else {
+    // ---- threshold that at least W groups reach (no threshold when there are fewer)
+#pragma unroll 1
+    for (int i = tid; i < ngroups; i += kSelThreads)
+      if (s_group[i] > -INFINITY) atomicAdd(&s_hist[bins.of(s_group[i])], 1u);
+    __syncthreads();
+    hist_threshold_all(s_hist, (uint32_t)c.W, &s_thr, s_redu, paru);
+    __syncthreads();
+    T = bins.floor_of(s_thr);
+    scale = scale_to(T);
+    // ---- groups that reach it
+#pragma unroll 1
+    for (int i = tid; i < ngroups; i += kSelThreads) {
+      if (!(s_group[i] >= T)) continue;
+      const uint32_t pos = atomicAdd(&s_ng, 1u);
+      if (pos < (uint32_t)kUnitCap) s_units[pos] = (uint32_t)i;
+    }
+    __syncthreads();
+    const int ng = (int)s_ng;
+    fallback = ng > kUnitCap;
+    quarters = min(ng, kUnitCap) << ssh;
+    // ---- the finer keys behind them that reach it (four threads to a group, one round of loads for all).  Where all rows
+    // left scores these are candidates at once, and nothing has to be read again: 15 thousand children of 128 beams 10.4 -> 8.7 us.
 #pragma unroll 1
     for (int i = tid; i < quarters; i += kSelThreads) {
       const int at = quarter(i), w = at >> 6, q = at & 63, info = s_rinfo[w], cnt = info >> 2;
       const float* fine = data + (size_t)w * kRowFloats;
-      if ((info & 3) == ROW_DENSE) {
+      if constexpr (!LISTED) {
         const uint2 k = *(const uint2*)(fine + 2 * q);
         const int last = last_key(w);
         if ((int)(k.x & 0xffffu) <= last) add(true, w, 4 * q);
@@ -1025,7 +1090,10 @@ __global__ void __launch_bounds__(kSelThreads) k_select(SelCtx c) {
         // (the scores of a row's last wavefront of children are -inf past its end; past that they are not written)
         if (4 * q < cnt) {
           const float4 k = *(const float4*)(fine + 4 * q);
-          if (fmaxf(fmaxf(k.x, k.y), fmaxf(k.z, k.w)) >= T) add(false, w, q);
+          if (fmaxf(fmaxf(k.x, k.y), fmaxf(k.z, k.w)) >= T) {
+            add(false, w, q);
+            if (short_rows) take(w, q, k);
+          }
         }
       } else {
         const int last = last_key(w);
@@ -1036,9 +1104,19 @@ __global__ void __launch_bounds__(kSelThreads) k_select(SelCtx c) {
           if ((int)(keys & 0xffffu) <= last) { add(true, w, key); most = max(most, (uint32_t)cnt); }
       }
     }
+    }
     note_most();
     __syncthreads();
     int nd = (int)s_nd, ns = (int)s_ns;
+    n = (int)s_n;
+    const bool taken = short_rows && !fallback && n <= kListCap && ns <= kChunkCap;    // the list is complete
+    if (!taken) {
+    if (__builtin_expect(n > 0, 0)) {
+      __syncthreads();
+      for (int i = tid; i < kHistBins; i += kSelThreads) s_hist[i] = 0;
+      if (tid == 0) s_n = 0;
+      __syncthreads();
+    }
     // Where the W best are many to a group (few beams far ahead of the others, long rows) the groups' threshold is too low and the
     // keys' own takes its place, which W of them reach: they are counted, then listed again.  The line: 32 requests of 128 beams, 8192
     // tokens, logits of width 6 and then 1 have 11 keys a beam above the groups' threshold and take 37 us without a mask, 54 us when
@@ -1052,7 +1130,7 @@ __global__ void __launch_bounds__(kSelThreads) k_select(SelCtx c) {
         for (int i = tid; i < quarters; i += kSelThreads) {
           const int at = quarter(i), w = at >> 6, q = at & 63, info = s_rinfo[w], cnt = info >> 2;
           const float* fine = data + (size_t)w * kRowFloats;
-          if ((info & 3) == ROW_DENSE || cnt > kScoreMax) {
+          if (!LISTED || cnt > kScoreMax) {
             const int last = last_key(w);
             int key, num;
             uint64_t keys = quarter_keys(fine, q, info, &key, &num);
@@ -1079,17 +1157,16 @@ __global__ void __launch_bounds__(kSelThreads) k_select(SelCtx c) {
       }
       nd = (int)s_nd; ns = (int)s_ns;
     }
+    }
     // units of four candidates behind a key in front: float4 of logits, or consecutive children
-    const bool listed = s_most > 0;                          // the keys in front are of gathered rows
-    const int sh = listed ? 1 + key_shift((int)s_most) : c.unit_shift;
-    if (tid == 0) s_n = 0;
+    const int sh = LISTED ? 1 + key_shift((int)s_most) : c.unit_shift;
     fallback = fallback || nd + ns > kChunkCap;
     const int front_units = nd << sh;
     const int lsh = c.row_threads == 512 ? 2 : 3;            // log2 of a thread's loads per block of a streamed row
     auto unit_token = [&](int k, int e) {                    // first token of unit e of line k
       return 32 * (k >> lsh) + 4 * c.row_threads * (k & ((1 << lsh) - 1)) + 4 * (e & 7) + kBlockV * (e >> 3);
     };
-    if (!fallback) {
+    if (!fallback && !taken) {
       // ---- units behind them that hold a candidate above the threshold (as far as the logits tell: validity comes next).  Four
       // scores are a unit as they are.
       auto entry = [&](int u, int* w, int* k, int* e) {
@@ -1145,7 +1222,7 @@ __global__ void __launch_bounds__(kSelThreads) k_select(SelCtx c) {
       // Fewer groups than W, as at level 0 where all candidates are one row's: the units themselves yield a threshold.  (Not where a streamed
       // row's validity is only looked up below; the best candidates of the first kGroupCap units are kept, beyond that they are
       // looked for again.)
-      const bool countable = listed || !(c.blob && c.step == 2);
+      const bool countable = LISTED || !(c.blob && c.step == 2);
       const bool by_unit = countable && T == kNoThreshold && front_units >= c.W, kept = by_unit && front_units <= kGroupCap;
       if (by_unit) {
         bins = make_bins(hi, hi - T);
@@ -1155,7 +1232,7 @@ __global__ void __launch_bounds__(kSelThreads) k_select(SelCtx c) {
         };
         constexpr int U = 2;
 #pragma unroll 1
-        for (int base = tid; !listed && base < front_units; base += U * kSelThreads) {
+        for (int base = tid; !LISTED && base < front_units; base += U * kSelThreads) {
           float best[U];
 #pragma unroll
           for (int q = 0; q < U; q++) {
@@ -1170,7 +1247,7 @@ __global__ void __launch_bounds__(kSelThreads) k_select(SelCtx c) {
 #pragma unroll
           for (int q = 0; q < U; q++) count(base + q * kSelThreads, best[q]);
         }
-        if (listed) listed_units(count);
+        if constexpr (LISTED) listed_units(count);
         __syncthreads();
         hist_threshold_all(s_hist, (uint32_t)c.W, &s_thr, s_redu, paru);
         __syncthreads();
@@ -1180,7 +1257,7 @@ __global__ void __launch_bounds__(kSelThreads) k_select(SelCtx c) {
 #pragma unroll 1
         for (int u = tid; u < front_units; u += kSelThreads)
           if (s_group[u] >= T) keep(u);
-      } else if (!listed) {
+      } else if constexpr (!LISTED) {
         constexpr int U = 4;
 #pragma unroll 1
         for (int base = tid; base < front_units; base += U * kSelThreads) {
@@ -1216,7 +1293,7 @@ __global__ void __launch_bounds__(kSelThreads) k_select(SelCtx c) {
           for (int u = tid; u < front_units; u += kSelThreads) {
             int w, k, e;
             entry(u, &w, &k, &e);
-            const float best = __fadd_rn(s_rbias[w], listed ? child_best(w, k, e) : token_best(w, k, e));
+            const float best = __fadd_rn(s_rbias[w], LISTED ? child_best(w, k, e) : token_best(w, k, e));
             if (!(best >= T)) continue;
             if (pass == 0) atomicAdd(&s_hist[bins.of(best)], 1u);
             else keep(u);
@@ -1235,12 +1312,12 @@ __global__ void __launch_bounds__(kSelThreads) k_select(SelCtx c) {
       // ---- their candidates, counted in bins of one width from the best score down to the threshold.  When they do not fit, the
       // bins still tell where the W best end, and a second round takes only those.
       const int nu = (int)s_nu, units = nu + ns;
-      float scale = T > kNoThreshold ? (hi > T ? fminf((float)(kHistBins - 1) / (hi - T), 1e30f) : 0.f) : 64.f;
+      scale = scale_to(T);
       int cut = kHistBins - 1;
 #pragma unroll 1
       for (int round = 0; round < 2; round++) {
 #pragma unroll 1
-        for (int i = tid; i < units; i += kSelThreads) {
+        for (int i = taken && round == 0 ? units : tid; i < units; i += kSelThreads) {
           const uint32_t unit = i < nu ? s_units[i] : 0u;
           const uint32_t ent = s_chunks[i < nu ? (int)(unit >> 8) : kChunkCap - 1 - (i - nu)];
           const int w = (int)(ent >> 8), k = (int)(ent & 255u), cnt = s_rinfo[w] >> 2;
@@ -1248,7 +1325,7 @@ __global__ void __launch_bounds__(kSelThreads) k_select(SelCtx c) {
           int place, end = cnt;                            // the unit's candidates: place .. place + 3, < end
           float bias = s_rbias[w], y[4];
           uint32_t bits = 0xfu;
-          if (i < nu && !listed) {
+          if (!LISTED) {
             place = unit_token(k, (int)(unit & 255u));
             end = c.V;
             if (c.blob && c.step == 0) bits = mv.l0[place >> 5] >> (place & 31);
@@ -1274,7 +1351,7 @@ __global__ void __launch_bounds__(kSelThreads) k_select(SelCtx c) {
             const int at = place + j;
             const float score = __fadd_rn(bias, y[j]);     // (with bias 0 unchanged but for -0, which composite() makes 0)
             if (at >= end || !((bits >> j) & 1u) || !(score >= T)) continue;
-            if (c.blob && c.step == 2 && i < nu && !listed) {        // last level, streamed row: the candidate has to be in the row's child list
+            if (!LISTED && c.blob && c.step == 2) {        // last level, streamed row: the candidate has to be in the row's child list
               const int32_t* list = mv.t3 + s_ra[w];
               const int len = c.range_in[2 * ((size_t)b * c.W + w) + 1] - s_ra[w], pos = lower_bound_i32(list, len, at);
               if (!(pos < len && list[pos] == at)) continue;
@@ -1355,7 +1432,7 @@ __global__ void __launch_bounds__(kSelThreads) k_select(SelCtx c) {
     }
     if (__builtin_expect(fallback, 0)) {
       __syncthreads();
-      n = radix_select_all(c, mv, b, s_list, s_hist);
+      n = radix_select_all<LISTED>(c, mv, b, s_list, s_hist);
       int n2 = 1;
       while (n2 < n) n2 <<= 1;
       for (int i = n + tid; i < n2; i += kSelThreads) s_list[i] = 0;   // 0 sorts after every real key
@@ -1379,14 +1456,14 @@ __global__ void __launch_bounds__(kSelThreads) k_select(SelCtx c) {
   // ---- level 1: which pair a survivor of a streamed row is = the valid tokens before it in its mask row, counted by four
   // lanes in one round of loads (a binary search in the child list is a dozen dependent ones)
   int32_t* s_rank = (int32_t*)s_hist;                        // [W] (kHistBins >= kMaxW)
-  if (c.blob && c.step == 1) {
+  if (!LISTED && c.blob && c.step == 1) {
     for (int j0 = 0; j0 < min(n, c.W); j0 += kSelThreads / 4) {
       const int j = j0 + (tid >> 2), g = tid & 3;
       uint32_t cnt = 0;
       if (j < min(n, c.W)) {
         const uint32_t flat = 0xffffffffu - (uint32_t)s_list[j];
         const int w = (int)(flat / (uint32_t)c.V), tok = (int)(flat % (uint32_t)c.V);
-        if ((s_rinfo[w] & 3) == ROW_DENSE) {
+        {
           const uint32_t* mrow = mv.l1 + (size_t)s_ra[w] * mv.words;
           const int full = tok >> 5;                         // whole words before the token's
           if (g == 0) cnt = (uint32_t)mv.pair_off[s_ra[w]] + (uint32_t)__popc(mrow[full] & ((1u << (tok & 31)) - 1u));
@@ -1417,7 +1494,7 @@ __global__ void __launch_bounds__(kSelThreads) k_select(SelCtx c) {
       const uint64_t key = s_list[j];
       const uint32_t flat = 0xffffffffu - (uint32_t)key;
       const int parent = (int)(flat / (uint32_t)late->V), place = (int)(flat % (uint32_t)late->V);
-      const bool gathered = (s_rinfo[parent] & 3) == ROW_SPARSE;
+      constexpr bool gathered = LISTED;
       int token = place;
       if (late->blob) {
         if (late->step == 0) {
@@ -1496,8 +1573,13 @@ extern "C" gr_status gr_beam_select(const gr_select_params* p, void* workspace, 
     hipLaunchKernelGGL((k_rows<true, 512>), dim3((unsigned)(rows < kStrideGrid ? rows : kStrideGrid)), dim3(512), 0, stream, c);
   else
     hipLaunchKernelGGL((k_rows<false, 256>), dim3((unsigned)rows), dim3(256), 0, stream, c);
-  if (const gr_status st = gr_allow_lds<k_select>(kSelLdsBytes)) return st;
-  hipLaunchKernelGGL(k_select, dim3(p->B), dim3(kSelThreads), kSelLdsBytes, stream, c);
+  if (p->mask && p->step >= 1 && !(p->flags & GR_SELECT_FORCE_DENSE)) {
+    if (const gr_status st = gr_allow_lds<k_select<true>>(kSelLdsBytes)) return st;
+    hipLaunchKernelGGL(k_select<true>, dim3(p->B), dim3(kSelThreads), kSelLdsBytes, stream, c);
+  } else {
+    if (const gr_status st = gr_allow_lds<k_select<false>>(kSelLdsBytes)) return st;
+    hipLaunchKernelGGL(k_select<false>, dim3(p->B), dim3(kSelThreads), kSelLdsBytes, stream, c);
+  }
   GR_HIP_TRY(hipGetLastError());
   return GR_OK;
 }
