@@ -18,6 +18,7 @@
 // Arithmetic that decides beam order is fixed: m = fp32 max over valid logits, S = fp64 sum of
 // exp(x - m), lse = fp32(m + log S), bias = score_in - lse (fp32), cand = bias + x (fp32), with no
 // fused multiply-add in the last two operations.
+#include <type_traits>
 #include "gr_internal.hpp"
 
 namespace {
@@ -43,7 +44,8 @@ constexpr int kMaxW = 2048;
 constexpr int kGroupCap = 2 * kListCap;  // key groups (floats in the list's place)
 constexpr size_t kSelLdsBytes = (size_t)kListCap * 8 + (size_t)kUnitCap * 4 + (size_t)kHistBins * 4 + (size_t)kChunkCap * 4 + (size_t)kMaxW * 16;
 
-enum { ROW_DEAD = 0, ROW_DENSE = 1, ROW_SPARSE = 2 };      // low bits of row_info; the child count of a gathered row above them
+enum { ROW_DEAD = 0, ROW_DENSE = 1, ROW_SPARSE = 2, ROW_DONE = 3 };      // low bits of row_info; the child count of a gathered row above them.  DONE (a
+                                                                         // request's first row): k_rows has written the request's outputs
 
 struct SelCtx {
   int B, W, V, depth, step;
@@ -279,6 +281,111 @@ __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* total,
   return base + incl - v;
 }
 
+__device__ __forceinline__ uint64_t composite(float score, uint32_t flat) {
+  return ((uint64_t)gr_ordkey(score + 0.0f) << 32) | (uint64_t)(0xffffffffu - flat);     // (+0.0f: -0 and +0 are one score)
+}
+
+// Monotone (non-increasing in the score) histogram bin of a score below the best, `hi`; bins of one width.
+__device__ __forceinline__ int key_bin(float hi, float scale, float score) {
+  return (int)fminf(fmaxf((hi - score) * scale, 0.f), (float)(kHistBins - 1));
+}
+
+constexpr float kNoThreshold = -3.402823466e38f;       // the lowest float: every candidate reaches it
+
+// Bins for thresholds, of the distance below the best score `hi` (monotone: a better score is never in a later bin), even in the logarithm:
+// 128 to an octave over the 16 octaves below `range`, or below 4096 where that is wider.  So they are as fine for scores that
+// lie close together as for scores far apart, and a few scores far below do not make the others' bins coarse.  What lies
+// lower is in the last bin.
+struct Bins {
+  float hi;
+  int base;
+  __device__ __forceinline__ int of(float score) const {
+    return min(max((int)(__float_as_uint(fmaxf(hi - score, 0.f)) >> 16) - base, 0), kHistBins - 1);
+  }
+  // a score that everything in bins 0..thr reaches (a little low: rounding may only let more through)
+  __device__ __forceinline__ float floor_of(int thr) const {
+    const float d = __uint_as_float((uint32_t)(thr + 1 + base) << 16);
+    return thr < kHistBins - 1 ? hi - d - 1e-6f * (fabsf(hi) + d) : kNoThreshold;
+  }
+};
+__device__ __forceinline__ Bins make_bins(float hi, float range) {
+  return Bins{hi, (int)(__float_as_uint(fminf(range, 4096.f)) >> 16) - (kHistBins - 2)};
+}
+
+// Smallest bin t with at least `want` entries in bins 0..t (bin 0 = best scores); the last bin when there are fewer
+// than `want` entries in total.  Done by the whole workgroup (every thread owns kHistBins / NT consecutive
+// bins; one scan, one barrier inside): a serial walk by one wavefront over 32 bins per lane costs more than a
+// microsecond.  Leaves the histogram cleared.  The caller puts a barrier behind it before reading *s_thr.
+template <int NT>
+__device__ __forceinline__ void hist_threshold_all(uint32_t* s_hist, uint32_t want, int* s_thr, uint32_t* s_redu, int& par) {
+  constexpr int per = kHistBins / NT;
+  const int tid = threadIdx.x;
+  uint32_t h[per], local = 0;
+#pragma unroll
+  for (int k = 0; k < per; k++) { h[k] = s_hist[tid * per + k]; local += h[k]; s_hist[tid * per + k] = 0; }
+  uint32_t total;
+  const uint32_t below = block_excl_scan<NT / 64>(local, &total, s_redu, par);
+  if (total < want) {
+    if (tid == 0) *s_thr = kHistBins - 1;
+  } else if (below < want && want <= below + local) {
+    uint32_t acc = below;
+    int bin = tid * per;
+#pragma unroll
+    for (int k = 0; k < per; k++) {
+      acc += h[k];
+      if (acc >= want) break;
+      bin++;
+    }
+    *s_thr = bin;
+  }
+}
+
+// Histogram of the candidates' bins -> its exclusive prefix, in place, and in *s_thr the bin that holds the want-th candidate (the last one
+// when there are fewer).  The caller puts a barrier behind it.  Returns the most candidates in one of this thread's bins.
+template <int NT>
+__device__ __forceinline__ uint32_t hist_prefix(uint32_t* s_hist, uint32_t want, int* s_thr, uint32_t* s_redu, int& par) {
+  constexpr int per = kHistBins / NT;
+  const int tid = threadIdx.x;
+  uint32_t h[per], sum = 0, most = 0;
+#pragma unroll
+  for (int k = 0; k < per; k++) { h[k] = s_hist[tid * per + k]; sum += h[k]; most = max(most, h[k]); }
+  uint32_t total;
+  uint32_t run = block_excl_scan<NT / 64>(sum, &total, s_redu, par);
+  if (tid == 0 && total < want) *s_thr = kHistBins - 1;
+#pragma unroll
+  for (int k = 0; k < per; k++) {
+    s_hist[tid * per + k] = run;
+    if (run < want && run + h[k] >= want) *s_thr = tid * per + k;
+    run += h[k];
+  }
+  return most;
+}
+// Orders the m candidates of `list` (n in all) in bins up to `cut` (descending composite key = score descending, flat index ascending).
+// Histogram bins are ordered by score, so a survivor's place is the number of survivors in better bins plus its rank inside its own
+// (tiny) bin.  Counting sort by bin, then every survivor counts the larger keys of its bin.  Exact ties share a bin and are ranked
+// by the key's flat-index half there.
+template <int NT>
+__device__ __forceinline__ void order_by_bins(uint64_t* list, uint64_t* tmp, uint32_t* s_hist, int n, int m, int cut, float hi, float scale) {
+  auto bin_of = [&](uint64_t key) { return key_bin(hi, scale, gr_ordkey_inv((uint32_t)(key >> 32))); };
+#pragma unroll 1
+  for (int i = threadIdx.x; i < n; i += NT) {
+    const uint64_t key = list[i];
+    const int bin = bin_of(key);
+    if (bin <= cut) tmp[atomicAdd(&s_hist[bin], 1u)] = key;            // the bin's counter now runs to the bin's end
+  }
+  __syncthreads();
+#pragma unroll 1
+  for (int q = threadIdx.x; q < m; q += NT) {
+    const uint64_t key = tmp[q];
+    const int bin = bin_of(key);
+    const int s0 = bin ? (int)s_hist[bin - 1] : 0, s1 = (int)s_hist[bin];
+    int cnt = 0;
+    for (int j = s0; j < s1; j++) cnt += tmp[j] > key;
+    list[s0 + cnt] = key;
+  }
+  __syncthreads();
+}
+
 // ------------------------------------------------------------------------------------------------
 // Rows that are streamed in full: one workgroup per row.
 // ------------------------------------------------------------------------------------------------
@@ -290,6 +397,19 @@ struct RowLds {
   float m[2][NT / 64];                 // by successive rows
   float key[2][kLines];
   uint32_t mask[kMaxMaskWords];        // validity bits of a last-level row with many children
+};
+
+// What the workgroup of a request's only live row needs to select as well.
+constexpr int kPickCap = 2048;         // candidates that reach the threshold
+constexpr int kPickW = 1024;
+struct PickLds {
+  uint64_t list[kPickCap], tmp[kPickCap];
+  uint32_t hist[kHistBins];
+  uint32_t red[2 * 8];
+  float low[2][8];                     // per wavefront: the worst of its threads' best logits of a load
+  uint32_t others[2][8];               // and whether it saw another live row of the request
+  uint32_t n, crowded;
+  int thr;
 };
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -314,6 +434,72 @@ __device__ __forceinline__ float key16_low(float best, uint32_t key) { return be
 
 __device__ __forceinline__ void mark_dead(const SelCtx& c, int row) { c.row_info[row] = ROW_DEAD; }
 
+// The W best of one row's candidates, which the workgroup holds in registers (thread t: tokens 4 (t + NT i) + j), written as the
+// request's new beams.  False where they are too many for it (thousands of scores as good as equal); nothing is written then.
+template <int NT>
+__device__ __forceinline__ bool row_pick(const SelCtx& c, const MaskView& mv, PickLds& P, int row, const float (&xv)[kBlockV / NT], float bias, float hi, float lo) {
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));                              // (what follows from it is not made ahead of the loop over rows and spilled)
+  int par = 0;
+  // threshold that W candidates reach
+  const Bins bins = make_bins(hi, hi - lo);
+#pragma unroll
+  for (int e = 0; e < kBlockV / NT; e++)
+    if (xv[e] > -INFINITY) atomicAdd(&P.hist[bins.of(__fadd_rn(bias, xv[e]))], 1u);
+  __syncthreads();
+  hist_threshold_all<NT>(P.hist, (uint32_t)c.W, &P.thr, P.red, par);
+  __syncthreads();
+  const float T = bins.floor_of(P.thr);
+  if (T == kNoThreshold) return false;
+  // what reaches it, in bins of one width
+  const float scale = hi > T ? fminf((float)(kHistBins - 1) / (hi - T), 1e30f) : 0.f;
+#pragma unroll
+  for (int e = 0; e < kBlockV / NT; e++) {
+    const float score = __fadd_rn(bias, xv[e]);
+    if (!(score >= T)) continue;
+    atomicAdd(&P.hist[key_bin(hi, scale, score)], 1u);
+    const uint32_t pos = atomicAdd(&P.n, 1u);
+    if (pos < (uint32_t)kPickCap) P.list[pos] = composite(score, (uint32_t)(4 * (tid + NT * (e / 4)) + (e & 3)));
+  }
+  __syncthreads();
+  const int n = (int)P.n;
+  bool fits = n <= kPickCap;
+  if (fits) {
+    if (hist_prefix<NT>(P.hist, (uint32_t)c.W, &P.thr, P.red, par) > 128u) P.crowded = 1u;
+    __syncthreads();
+    fits = !P.crowded;
+  }
+  if (!fits) {
+    __syncthreads();                                         // (the next row clears what this was seen by)
+    return false;
+  }
+  const int cut = P.thr, m = cut < kHistBins - 1 ? (int)P.hist[cut + 1] : n;
+  __syncthreads();                                           // (the bin after the cut is read before any counter moves)
+  order_by_bins<NT>(P.list, P.tmp, P.hist, n, m, cut, hi, scale);
+  const LateArgs late = late_args();
+  for (int j = tid; j < late->W; j += NT) {
+    const size_t o = (size_t)row + j;
+    int32_t* po = late->prefix_out + o * late->depth;
+    int token = -1, r_lo = 0, r_hi = 0;
+    float score = -INFINITY;
+    if (j < m) {
+      const uint64_t key = P.list[j];
+      token = (int)(0xffffffffu - (uint32_t)key);
+      score = gr_ordkey_inv((uint32_t)(key >> 32));
+      if (late->blob) { r_lo = mv.off1[token]; r_hi = mv.off1[token + 1]; }
+    }
+    late->parent_out[o] = j < m ? 0 : -1;
+    late->token_out[o] = token;
+    late->scores_out[o] = score;
+    po[0] = token;
+    for (int k = 1; k < late->depth; k++) po[k] = -1;
+    late->range_out[2 * o] = r_lo;
+    late->range_out[2 * o + 1] = r_hi;
+    if (late->item_index_out) late->item_index_out[o] = -1;
+  }
+  return true;
+}
+
 // Bound: HBM and, close behind, the fp64 exponentials: 8192 rows of 8192 logits take 53 us = 5.1 TB/s, of which the vector
 // instructions alone are 34 us (650 a wavefront; with the 64-entry table, a polynomial term and an addition more per exponential, a
 // barrier per reduction and a compare per validity bit it was 68 us).  Six workgroups a CU: 80 registers, no spills (seven: 66 us).
@@ -321,8 +507,14 @@ __device__ __forceinline__ void mark_dead(const SelCtx& c, int row) { c.row_info
 // `row` is live; t1 = first token of its prefix (level 1), [start, start + n_list) = its children where they were looked up
 // (all wave-uniform).  Every wavefront works relative to its own maximum and the workgroup meets once: the first wavefront then joins
 // the (max, sum) pairs and writes the row's results, while the others are free for the next row (or gone).
-template <int NT>
-__device__ __forceinline__ void row_dense(const SelCtx& c, const MaskView& mv, RowLds<NT>& L, int row, float s_in, int t1, int start, int n_list, int set) {
+//
+// PICK (level 0): where the row is its request's `first` and `rivals`, the scores of the request's other rows, are all dead, the workgroup, which
+// holds all of the request's candidates in registers, selects the W best too.  k_select then only finds that it is done: a level-0
+// step of 8 x 128 beams over 8192 tokens 19.4 -> 14.0 us, of 128 x 256 22.5 -> 15.7, of one x 16 over 256 13.9 -> 10.5; where all rows
+// are live nothing is gained (8 x 128 25.5 -> 24.2, 32 x 256 90.8 -> 94.4).
+template <int NT, bool PICK>
+__device__ __forceinline__ void row_dense(const SelCtx& c, const MaskView& mv, RowLds<NT>& L, int row, float s_in, int t1, int start, int n_list, int set,
+                                          PickLds* P = nullptr, bool first = false, float2 rivals = {0.f, 0.f}) {
   constexpr int NV4 = kBlockV / 4 / NT, NWV = NT / 64;        // float4 per thread; wavefronts
   const int tid = threadIdx.x, wave = tid >> 6, V = c.V;
   const float* x = c.logits + (size_t)row * V;
@@ -353,6 +545,7 @@ __device__ __forceinline__ void row_dense(const SelCtx& c, const MaskView& mv, R
 #pragma unroll
   for (int i = 0; i < NV4; i++) lmax[i] = -INFINITY;
   double S = 0.0;                                  // the wavefront's sum relative to m
+  float xv[4 * NV4];
 #pragma unroll 1
   for (int v0 = 0; v0 < V; v0 += kBlockV) {
     // ---- one block of the row: logits and validity bits requested together
@@ -364,7 +557,6 @@ __device__ __forceinline__ void row_dense(const SelCtx& c, const MaskView& mv, R
 #pragma unroll
       for (int i = 0; i < NV4; i++) mw[i] = __builtin_amdgcn_raw_buffer_load_b32(rm, (v0 >> 5) * 4 + (tid >> 3) * 4 + i * (NT / 2), 0, 0);
     }
-    float xv[4 * NV4];
     // validity bits: bit 4 i + j <-> token v0 + 4 (tid + i * NT) + j
     uint32_t vbits = 0xffffffffu;
     const bool whole = all_valid && v0 + kBlockV <= V;
@@ -472,10 +664,23 @@ __device__ __forceinline__ void row_dense(const SelCtx& c, const MaskView& mv, R
       if (!b1) key[2 * b2 + b0] = r;
     }
   }
+  if (PICK && first) {
+    float low = INFINITY;
+#pragma unroll
+    for (int i = 0; i < NV4; i++) low = fminf(low, lmax[i] > -INFINITY ? lmax[i] : INFINITY);
+    low = -wave_max(-low);
+    const bool any = __any(rivals.x > -INFINITY || rivals.y > -INFINITY);
+    if ((tid & 63) == 0) { P->low[set][wave] = low; P->others[set][wave] = any; }
+    for (int i = tid; i < kHistBins; i += NT) P->hist[i] = 0;
+    if (tid == 0) { P->n = 0; P->crowded = 0; }
+  }
   __syncthreads();
-  if (wave != 0) return;
-  m = (tid < NWV) ? L.m[set][tid] : -INFINITY;
-  S = (tid < NWV) ? L.s[set][tid] : 0.0;
+  const int lane = tid & 63;
+  bool pick = false;
+  if (PICK && first) pick = !__any(lane < NWV && P->others[set][lane & (NWV - 1)]);       // (the same for all wavefronts)
+  if (wave != 0 && !pick) return;
+  m = (lane < NWV) ? L.m[set][lane] : -INFINITY;
+  S = (lane < NWV) ? L.s[set][lane] : 0.0;
   const float M = wave_max(m);
   if (!(M > -INFINITY)) {
     if (tid == 0) mark_dead(c, row);
@@ -485,6 +690,16 @@ __device__ __forceinline__ void row_dense(const SelCtx& c, const MaskView& mv, R
   const float lse = (float)((double)M + log(T));
   const float bias = __fsub_rn(s_in, lse);
   const float best = __fadd_rn(bias, M);
+  if constexpr (PICK) {
+    if (pick) {
+      const float low = -wave_max(lane < NWV ? -P->low[set][lane & (NWV - 1)] : -INFINITY);
+      if (row_pick<NT>(c, mv, *P, row, xv, bias, best, __fadd_rn(bias, low))) {
+        if (tid == 0) c.row_info[row] = ROW_DONE;
+        return;
+      }
+      if (wave != 0) return;
+    }
+  }
   if (tid == 0) { c.row_bias[row] = bias; c.row_info[row] = ROW_DENSE; }
   const float4 kl = *(const float4*)&L.key[set][4 * tid];
   const float k0 = __fadd_rn(bias, kl.x), k1 = __fadd_rn(bias, kl.y), k2 = __fadd_rn(bias, kl.z), k3 = __fadd_rn(bias, kl.w);      // (bias is finite)
@@ -675,17 +890,19 @@ __global__ void __launch_bounds__(kGatherWaves * 64, 8) k_rows_listed(SelCtx c) 
 
 // Rows that are streamed, dealt to workgroups
 //   one each: for calls whose rows are all streamed and, as a rule, all live;
-//   every gridDim-th (STRIDE): for level 0, where as a rule one row of a request is live: a workgroup asks for the scores of all
-//   its rows at once and turns to the live ones (8192 workgroups that only find a dead row cost 16 us to dispatch).  With so few
-//   rows at work a row is dealt to twice as many threads.
-constexpr size_t kStrideGrid = 1021;    // about four workgroups per CU; prime, so that equally spaced live rows fall to different ones
+//   every gridDim-th (STRIDE): for level 0, where as a rule one row of a request is live, its first: these rows are dealt first, then a
+//   workgroup asks for the scores of all its other rows at once and turns to the live ones (8192 workgroups that only find a dead row
+//   cost 16 us to dispatch; the live rows of 8 requests spread over 1021 workgroups 3 us more than at the front of 512, which is
+//   two to a CU).  With so few rows at work a row is dealt to twice as many threads.
+constexpr size_t kStrideGrid = 512;
 template <bool STRIDE, int NT>
 __global__ void __launch_bounds__(NT, STRIDE ? 4 : 6) k_rows(SelCtx c) {
   __shared__ RowLds<NT> L;
+  __shared__ std::conditional_t<STRIDE, PickLds, char> P;
   const int tid = threadIdx.x, lane = tid & 63, rows = c.B * c.W;
   MaskView mv;
   mv.ok = false;
-  if (!STRIDE) {
+  if constexpr (!STRIDE) {
     const int row = blockIdx.x;
     const float s_in = c.scores_in[row];
     const int t1 = (c.blob && c.step == 1) ? c.prefix_in[(size_t)row * c.depth] : -1;
@@ -698,19 +915,31 @@ __global__ void __launch_bounds__(NT, STRIDE ? 4 : 6) k_rows(SelCtx c) {
     int start = 0, n = 0;
     if (c.blob && c.step == 2) row_children(c, mv, row, &start, &n);
     __syncthreads();
-    row_dense(c, mv, L, row, s_in, t1, start, n, 0);
+    row_dense<NT, false>(c, mv, L, row, s_in, t1, start, n, 0);
   } else {
     fill_exp_tab(L.tab, NT);
     if (c.blob) mv = mask_view(c.blob, c.V, c.depth);
     __syncthreads();
+    // the requests' first rows come first, then all others
+    auto row_at = [&](int64_t at) {
+      if (at < c.B) return (int)at * c.W;
+      const int left = (int)at - c.B, b = left / (c.W - 1);
+      return b * c.W + 1 + (left - b * (c.W - 1));
+    };
     int set = 0;
     for (int64_t base = blockIdx.x; base < rows; base += (int64_t)gridDim.x * 64) {
-      const int64_t r = base + (int64_t)lane * gridDim.x;
-      const float s = r < rows ? c.scores_in[r] : -INFINITY;
-      if (tid < 64 && r < rows && !(s > -INFINITY)) mark_dead(c, (int)r);
+      const int64_t at = base + (int64_t)lane * gridDim.x;
+      const int r = at < rows ? row_at(at) : 0;
+      const float s = at < rows ? c.scores_in[r] : -INFINITY;
+      if (tid < 64 && at < rows && !(s > -INFINITY)) mark_dead(c, r);
       for (uint64_t live = __ballot(s > -INFINITY); live; live &= live - 1) {
-        const int l = __ffsll((unsigned long long)live) - 1;
-        row_dense(c, mv, L, (int)(base + (int64_t)l * gridDim.x), lane_f32(s, l), -1, 0, 0, set);
+        const int l = __ffsll((unsigned long long)live) - 1, row = __builtin_amdgcn_readlane(r, l);
+        const bool first = c.V <= kBlockV && c.W <= kPickW && base + (int64_t)l * gridDim.x < c.B;
+        float2 rivals = {-INFINITY, -INFINITY};              // (asked for here, looked at when the row's logits have been)
+        static_assert(kPickW <= 2 * NT, "two other rows to a thread");
+        if (first && 1 + tid < c.W) rivals.x = c.scores_in[row + 1 + tid];
+        if (first && 1 + tid + NT < c.W) rivals.y = c.scores_in[row + 1 + tid + NT];
+        row_dense<NT, true>(c, mv, L, row, lane_f32(s, l), -1, 0, 0, set, &P, first, rivals);
         set ^= 1;
       }
     }
@@ -761,37 +990,6 @@ __device__ __forceinline__ void for_each_candidate(const SelCtx& c, const MaskVi
       }
     }
   }
-}
-
-__device__ __forceinline__ uint64_t composite(float score, uint32_t flat) {
-  return ((uint64_t)gr_ordkey(score + 0.0f) << 32) | (uint64_t)(0xffffffffu - flat);     // (+0.0f: -0 and +0 are one score)
-}
-
-// Monotone (non-increasing in the score) histogram bin of a score below the best, `hi`; bins of one width.
-__device__ __forceinline__ int key_bin(float hi, float scale, float score) {
-  return (int)fminf(fmaxf((hi - score) * scale, 0.f), (float)(kHistBins - 1));
-}
-
-constexpr float kNoThreshold = -3.402823466e38f;       // the lowest float: every candidate reaches it
-
-// Bins for thresholds, of the distance below the best score `hi` (monotone: a better score is never in a later bin), even in the logarithm:
-// 128 to an octave over the 16 octaves below `range`, or below 4096 where that is wider.  So they are as fine for scores that
-// lie close together as for scores far apart, and a few scores far below do not make the others' bins coarse.  What lies
-// lower is in the last bin.
-struct Bins {
-  float hi;
-  int base;
-  __device__ __forceinline__ int of(float score) const {
-    return min(max((int)(__float_as_uint(fmaxf(hi - score, 0.f)) >> 16) - base, 0), kHistBins - 1);
-  }
-  // a score that everything in bins 0..thr reaches (a little low: rounding may only let more through)
-  __device__ __forceinline__ float floor_of(int thr) const {
-    const float d = __uint_as_float((uint32_t)(thr + 1 + base) << 16);
-    return thr < kHistBins - 1 ? hi - d - 1e-6f * (fabsf(hi) + d) : kNoThreshold;
-  }
-};
-__device__ __forceinline__ Bins make_bins(float hi, float range) {
-  return Bins{hi, (int)(__float_as_uint(fminf(range, 4096.f)) >> 16) - (kHistBins - 2)};
 }
 
 // Exact MSB radix select of the W best composite keys over ALL candidates (slow, always correct).
@@ -876,33 +1074,6 @@ __device__ int radix_select_all(const SelCtx& c, const MaskView& mv, int b, uint
   return min((int)s_cnt, kListCap);
 }
 
-// Smallest bin t with at least `want` entries in bins 0..t (bin 0 = best scores); the last bin when there are fewer
-// than `want` entries in total.  Done by the whole workgroup (every thread owns kHistBins / kSelThreads consecutive
-// bins; one scan, one barrier inside): a serial walk by one wavefront over 32 bins per lane costs more than a
-// microsecond.  Leaves the histogram cleared.  The caller puts a barrier behind it before reading *s_thr.
-__device__ __forceinline__ void hist_threshold_all(uint32_t* s_hist, uint32_t want, int* s_thr, uint32_t* s_redu, int& par) {
-  constexpr int per = kHistBins / kSelThreads;
-  const int tid = threadIdx.x;
-  uint32_t h[per], local = 0;
-#pragma unroll
-  for (int k = 0; k < per; k++) { h[k] = s_hist[tid * per + k]; local += h[k]; s_hist[tid * per + k] = 0; }
-  uint32_t total;
-  const uint32_t below = block_excl_scan<kSelThreads / 64>(local, &total, s_redu, par);
-  if (total < want) {
-    if (tid == 0) *s_thr = kHistBins - 1;
-  } else if (below < want && want <= below + local) {
-    uint32_t acc = below;
-    int bin = tid * per;
-#pragma unroll
-    for (int k = 0; k < per; k++) {
-      acc += h[k];
-      if (acc >= want) break;
-      bin++;
-    }
-    *s_thr = bin;
-  }
-}
-
 // Bound: latency - a chain of some six memory round trips and a dozen barriers in one workgroup per request - and, with cold
 // caches, the 40 GB/s at which one CU draws lines.  32 requests x 256 beams, V = 8192: 15 / 24 / 13 us at levels 0 / 1 / 2 and 16 us
 // without a mask (25 / 34 / 27 and 28 us when all 64 K chunk keys of a request were read and re-read chunks lay across eight lines);
@@ -930,6 +1101,8 @@ __global__ void __launch_bounds__(kSelThreads) k_select(SelCtx c) {
   __shared__ int s_thr;
   int parf = 0, paru = 0;
   const int b = blockIdx.x, tid = threadIdx.x;
+  const bool maybe_done = !LISTED && c.step == 0;
+  const int first_info = maybe_done ? c.row_info[(size_t)b * c.W] : 0;
   MaskView mv;
   if (c.blob) mv = mask_view(c.blob, c.V, c.depth);
 
@@ -976,6 +1149,7 @@ __global__ void __launch_bounds__(kSelThreads) k_select(SelCtx c) {
     auto low = [&](float v) { lo = fminf(lo, v > -INFINITY ? v : INFINITY); };
     low(g.x); low(g.y); low(g.z); low(g.w);
   }
+  if (maybe_done && first_info == ROW_DONE) return;          // (asked for first, looked at here: nobody waits for it alone)
   // ---- the request's rows
   if (tid < c.W) keep_row(tid, own);
 #pragma unroll 1
@@ -1058,7 +1232,7 @@ __global__ void __launch_bounds__(kSelThreads) k_select(SelCtx c) {
     for (int i = tid; i < ngroups; i += kSelThreads)
       if (s_group[i] > -INFINITY) atomicAdd(&s_hist[bins.of(s_group[i])], 1u);
     __syncthreads();
-    hist_threshold_all(s_hist, (uint32_t)c.W, &s_thr, s_redu, paru);
+    hist_threshold_all<kSelThreads>(s_hist, (uint32_t)c.W, &s_thr, s_redu, paru);
     __syncthreads();
     T = bins.floor_of(s_thr);
     scale = scale_to(T);
@@ -1151,7 +1325,7 @@ __global__ void __launch_bounds__(kSelThreads) k_select(SelCtx c) {
         __syncthreads();
         if (pass == 1) break;
         if (tid == 0) { s_nd = 0; s_ns = 0; s_most = 0; }
-        hist_threshold_all(s_hist, (uint32_t)c.W, &s_thr, s_redu, paru);
+        hist_threshold_all<kSelThreads>(s_hist, (uint32_t)c.W, &s_thr, s_redu, paru);
         __syncthreads();
         T = fmaxf(T, bins.floor_of(s_thr));
       }
@@ -1249,7 +1423,7 @@ __global__ void __launch_bounds__(kSelThreads) k_select(SelCtx c) {
         }
         if constexpr (LISTED) listed_units(count);
         __syncthreads();
-        hist_threshold_all(s_hist, (uint32_t)c.W, &s_thr, s_redu, paru);
+        hist_threshold_all<kSelThreads>(s_hist, (uint32_t)c.W, &s_thr, s_redu, paru);
         __syncthreads();
         T = fmaxf(T, bins.floor_of(s_thr));
       }
@@ -1301,7 +1475,7 @@ __global__ void __launch_bounds__(kSelThreads) k_select(SelCtx c) {
           __syncthreads();
           if (pass == 1) break;
           if (tid == 0) s_nu = 0;
-          hist_threshold_all(s_hist, (uint32_t)c.W, &s_thr, s_redu, paru);
+          hist_threshold_all<kSelThreads>(s_hist, (uint32_t)c.W, &s_thr, s_redu, paru);
           __syncthreads();
           T = fmaxf(T, bins.floor_of(s_thr));
         }
@@ -1377,31 +1551,13 @@ __global__ void __launch_bounds__(kSelThreads) k_select(SelCtx c) {
             for (int i = tid; i < n; i += kSelThreads) atomicAdd(&s_hist[key_bin(hi, scale, gr_ordkey_inv((uint32_t)(s_list[i] >> 32)))], 1u);
             __syncthreads();
           }
-          // exclusive prefix over the bins, in place, and the bin that holds the W-th candidate
-          constexpr int per = kHistBins / kSelThreads;
-          uint32_t h[per], sum = 0;
-#pragma unroll
-          for (int k = 0; k < per; k++) { h[k] = s_hist[tid * per + k]; sum += h[k]; }
-          uint32_t total;
-          uint32_t run = block_excl_scan<NW>(sum, &total, s_redu, paru);
-          if (tid == 0 && total < (uint32_t)c.W) s_thr = kHistBins - 1;
-#pragma unroll
-          for (int k = 0; k < per; k++) {
-            s_hist[tid * per + k] = run;
-            if (run < (uint32_t)c.W && run + h[k] >= (uint32_t)c.W) s_thr = tid * per + k;
-            run += h[k];
-          }
+          hist_prefix<kSelThreads>(s_hist, (uint32_t)c.W, &s_thr, s_redu, paru);
           if (n > kListCap && tid == 0) s_n = 0;
           __syncthreads();
           cut = s_thr;
         }
         if (n <= kListCap) break;
       }
-      // ---- order them (descending composite key = score descending, flat index ascending).  Histogram bins are ordered by
-      // score, so a survivor's place is the number of survivors in better bins plus its rank inside its own (tiny) bin.
-      // Counting sort by bin, then every survivor counts the larger keys of its bin.  Exact ties share a bin and are ranked
-      // by the key's flat-index half there.
-      auto bin_of = [&](uint64_t key) { return key_bin(hi, scale, gr_ordkey_inv((uint32_t)(key >> 32))); };
       fallback = n > kListCap;
       int m = 0;                                             // survivors up to the W-th one's bin
       if (!fallback) {
@@ -1410,24 +1566,8 @@ __global__ void __launch_bounds__(kSelThreads) k_select(SelCtx c) {
       }
       if (!fallback) {
         __syncthreads();                                     // (s_hist[cut + 1] is read before any counter moves)
-#pragma unroll 1
-        for (int i = tid; i < n; i += kSelThreads) {
-          const uint64_t key = s_list[i];
-          const int bin = bin_of(key);
-          if (bin <= cut) s_tmp[atomicAdd(&s_hist[bin], 1u)] = key;      // the bin's counter now runs to the bin's end
-        }
-        __syncthreads();
-#pragma unroll 1
-        for (int q = tid; q < m; q += kSelThreads) {
-          const uint64_t key = s_tmp[q];
-          const int bin = bin_of(key);
-          const int s0 = bin ? (int)s_hist[bin - 1] : 0, s1 = (int)s_hist[bin];
-          int cnt = 0;
-          for (int j = s0; j < s1; j++) cnt += s_tmp[j] > key;
-          s_list[s0 + cnt] = key;
-        }
+        order_by_bins<kSelThreads>(s_list, s_tmp, s_hist, n, m, cut, hi, scale);
         n = m;
-        __syncthreads();
       }
     }
     if (__builtin_expect(fallback, 0)) {

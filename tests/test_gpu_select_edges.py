@@ -241,3 +241,69 @@ def test_spread_of_beam_scores_does_not_change_the_time(gr):  # noqa: F811
     for widths in [(3.0, 1.0)] + _WIDTHS:
         assert time(widths, None) < 5 * usual, widths
         assert time(widths, mask) < 5 * usual, widths
+
+
+@pytest.mark.parametrize("V,W", [(1, 1), (3, 1), (5, 16), (255, 16), (2048, 512), (2049, 1023), (8191, 256), (8192, 1024), (8192, 1025), (8193, 128)])
+@pytest.mark.parametrize("masked", [False, True])
+@pytest.mark.parametrize("pattern", ["normal", "equal", "close", "one far ahead", "one far below", "inf"])
+def test_level_0_of_one_live_beam(gr, oracle_lib, V, W, masked, pattern):  # noqa: F811
+    """The first beam of every request alone is live: its workgroup selects as well, unless the row is longer than a block, the beams
+    are too many, or thousands of scores are as good as equal.  Around these limits, fewer tokens than beams, requests beside
+    them that start otherwise (another beam, two beams, none)."""
+    rng = np.random.default_rng(V + W)
+    B = 5
+    x = rng.standard_normal((B, W, V))
+    if pattern == "equal":
+        x[:] = 1.25
+    elif pattern == "close":
+        x = 1.0 + 1e-6 * x
+    elif pattern == "one far ahead":
+        x[:, :, V // 2] = 400.0
+    elif pattern == "one far below":
+        x[:, :, V // 3] = -1e6
+    elif pattern == "inf":
+        x[:, :, rng.random(V) < 0.5] = -np.inf
+    logits = x.astype(np.float32)
+    sc = np.full((B, W), -np.inf, np.float32)
+    sc[:3, 0] = [0.0, -2.5, 7.0]
+    sc[3, W - 1] = -1.0                                            # a beam that is not the first (or is: W = 1)
+    if W > 1:
+        sc[2, W - 1] = 6.5                                         # two; request 4 has none
+    pf, rg = np.full((B, W, 3), -1, np.int32), np.zeros((B, W, 2), np.int32)
+    items = mask = None
+    if masked:
+        t1 = np.flatnonzero(rng.random(V) < 0.6) if V > 1 else np.array([0])
+        if len(t1) == 0:
+            t1 = np.array([V - 1])
+        items = np.stack([np.repeat(t1, 2), np.tile([0, V - 1], len(t1)), np.zeros(2 * len(t1), np.int64)], axis=1).astype(np.int32)
+        items = np.unique(items, axis=0)
+        mask = gr.gr_item_mask_build(to_dev(items), V)
+    want = oracle_lib.beam_select(items, logits, sc, pf, 0)
+    for _ in range(2):
+        assert_select_equal(run_select(gr, mask, logits, sc, pf, rg, 0), want)
+
+
+@pytest.mark.parametrize("W,counts", [(3, [1, 2, 5]), (40, [4, 5, 60, 64]), (128, [16, 17]), (129, [16, 17]), (500, [1, 4, 5]), (600, [1, 4, 5]), (1024, [1, 3]), (1030, [1, 3]),
+                                      (64, [240]), (64, [240, 241])])
+@pytest.mark.parametrize("close", [False, True])
+def test_short_lists_taken_at_once(gr, oracle_lib, W, counts, close):  # noqa: F811
+    """The last level with few scores (taken all at once, up to 512 quads), more of them (listed first) and a row that leaves keys; with
+    dead beams among them or without, and with scores as good as equal."""
+    rng = np.random.default_rng(W + sum(counts))
+    V = max(300, W)
+    rows = []
+    for t1, third in enumerate(_children(rng, V, [counts[i % len(counts)] for i in range(W)])):
+        rows += [(t1, 0, int(t3)) for t3 in third]
+    items = np.array(rows, dtype=np.int32)
+    mask = gr.gr_item_mask_build(to_dev(items), V)
+    starts = np.searchsorted(items[:, 0], np.arange(W + 1))
+    for dead in (False, True):
+        logits = (1.25 + (1e-6 if close else 2.0) * rng.standard_normal((1, W, V))).astype(np.float32)     # (sums of 1 in fp32, not beside 0)
+        sc = np.sort(-(0.0 if close else 3.0) * rng.random((1, W))).astype(np.float32)[:, ::-1].copy()
+        if dead:
+            sc[0, W // 2:: 3] = -np.inf
+        pf = np.full((1, W, 3), -1, np.int32)
+        pf[0, :, 0], pf[0, :, 1] = np.arange(W), 0
+        rg = np.stack([starts[:-1], starts[1:]], axis=1)[None].astype(np.int32)
+        want = oracle_lib.beam_select(items, logits, sc, pf, 2)
+        assert_select_equal(run_select(gr, mask, logits, sc, pf, rg, 2), want, f"dead {dead}")
