@@ -1007,7 +1007,7 @@ __global__ void __launch_bounds__(256) k_attn_order(const int32_t* cu, int B, in
 }
 
 // Host-side launch plan, fitted to measured sweeps over (B, L, W) on the MI355X.  8-wave workgroups of 256 query rows stage each
-// K/V tile once per 256 rows and win once there are at least 256 of them (one per CU); below that, workgroups of 128 rows: two of
+// K/V tile once per 256 rows and win for long prompts once there are at least 256 of them (one per CU); else, workgroups of 128 rows: two of
 // 4 waves to a CU, or, where there is at most one per CU, one of 8 waves in two sets that share the prompt (ks = 2: 8 requests of
 // 2048 tokens x 128 beams, 256 workgroups, 46.3 -> 41.8 us; 2 x 256 x 16 of head size 64 8.4 -> 7.7).
 // Splitting the prompt into L segments costs fp32 partials through memory and the merge kernel.  With fewer workgroups than
@@ -1015,9 +1015,17 @@ __global__ void __launch_bounds__(256) k_attn_order(const int32_t* cu, int B, in
 // set that a segment holds, 3.5 for the merge, and the partials written and read at 4 TB/s.  It is within 10 % of what 60 shapes of
 // 256 to 12000 tokens took: 8 requests of 700 tokens, 128 beams, 16 query and 2 KV heads: 17.5, 25.0, 25.8, 26.1 us with 1 to 4 segments
 // (about one workgroup per CU means 2); one of 4096 tokens 54.2, 35.4, 23.8, 20.8, 25.2 with 1, 2, 4, 8, 16 (16).
-struct AttnPlan { int mwg, nsplit, ks; };
+//
+// With 256 workgroups of 256 rows or more, 128 rows win nevertheless, us with 128 and 256 rows:
+//   where they waste fewer rows of the last block (more than 5 %; 8 % for FP8 codes, which every workgroup widens for itself): 128 requests of
+//     100-900 tokens x 200 beams, 32 query and 8 KV heads of 128: 319, 350 (FP8 329, 350); 48 of 512-8192 x 300, 8 heads of 64: 210, 271;
+//   for prompts of up to 1024 tokens on average in more than one round: two workgroups to a CU cover each other's queries, own tokens and
+//     output, which are 40 % of the life of a unit of 8 tiles: 64 x 512 x 128 96.8, 101.6; 32 x 1024 x 256 149.6, 153.9; 128 x 128 x 256 of
+//     16 query and 2 KV heads 93, 103, of 8 and 2 heads of 64 28.3, 32.0.  But 64 x 1500 x 256 425, 421, 32 x 4096 x 256 504, 498, with FP8 codes
+//     128 x 512 x 256 385, 373, and where queries and outputs are twice what the Infinity Cache holds 128 x 128 x 256 of 32 heads 223, 216.
+struct AttnPlan { int mwg, nsplit, ks; bool many; };       // many: more workgroups than CUs before the choice of 128 rows for their own sake
 int g_plan_rows = 0, g_plan_segments = 0;                  // gr_diag_attn_plan: 0 = use the rule below
-AttnPlan plan_attn(const gr_attn_params* p) {
+AttnPlan plan_attn(const gr_attn_params* p, bool kv8) {
   const int g = p->Hq / p->Hkv;
   const int64_t M = (int64_t)p->W * g;
   AttnPlan plan;
@@ -1029,6 +1037,7 @@ AttnPlan plan_attn(const gr_attn_params* p) {
     plan.mwg = g_plan_rows;
     plan.nsplit = (int)(g_plan_segments < cap ? g_plan_segments : (cap < 1 ? 1 : cap));
     plan.ks = wants_sets(plan);
+    plan.many = (int64_t)p->B * p->Hkv * ((M + plan.mwg - 1) / plan.mwg) * plan.nsplit > 256;
     return plan;
   }
   const int64_t units256 = (int64_t)p->B * p->Hkv * ((M + 255) / 256);
@@ -1047,6 +1056,13 @@ AttnPlan plan_attn(const gr_attn_params* p) {
       if (n == 1 || us < least) { least = us; plan.nsplit = n; }
     }
   }
+  plan.many = units * plan.nsplit > 256;
+  if (plan.mwg == 256) {
+    const int64_t rows128 = (M + 127) / 128 * 128, rows256 = (M + 255) / 256 * 256;
+    const bool fewer_rows = rows256 * 100 > rows128 * (kv8 ? 108 : 105);
+    const bool short_prompts = !kv8 && p->total_L <= (int64_t)p->B * 1024 && units256 > 256 && (int64_t)p->B * p->W * p->Hq * p->d * 4 <= ((int64_t)400 << 20);
+    if (fewer_rows || short_prompts) plan.mwg = 128;
+  }
   plan.ks = wants_sets(plan);
   return plan;
 }
@@ -1054,9 +1070,7 @@ AttnPlan plan_attn(const gr_attn_params* p) {
 // Ragged batches with more units than CUs are worth ordering by length (measured: 4 % on 128 requests of
 // 512..8192 tokens); a uniform batch (total_L == B * max_L) is not touched.
 bool attn_wants_order(const gr_attn_params* p, const AttnPlan& plan) {
-  const int64_t M = (int64_t)p->W * (p->Hq / p->Hkv);
-  const int64_t units = (int64_t)p->B * p->Hkv * ((M + plan.mwg - 1) / plan.mwg) * plan.nsplit;
-  return p->B >= 2 && p->B <= kMaxOrderB && p->total_L != (int64_t)p->B * p->max_L && units > 256;
+  return p->B >= 2 && p->B <= kMaxOrderB && p->total_L != (int64_t)p->B * p->max_L && plan.many;
 }
 
 }  // namespace
@@ -1070,7 +1084,7 @@ extern "C" gr_status gr_diag_attn_plan(int32_t rows_per_workgroup, int32_t l_seg
 
 extern "C" size_t gr_beam_attn_workspace_bytes(const gr_attn_params* p) {
   if (!p || p->B <= 0 || p->W <= 0 || p->Hq <= 0 || p->Hkv <= 0 || p->Hq % p->Hkv) return 0;
-  const AttnPlan plan = plan_attn(p);
+  const AttnPlan plan = plan_attn(p, false);               // (what it says about the workspace is the same for FP8 codes)
   size_t need = attn_wants_order(p, plan) ? gr_align256((size_t)p->B * 4) : 0;
   if (plan.nsplit > 1) {
     const size_t rows = (size_t)p->B * plan.nsplit * p->W * p->Hq;
@@ -1107,7 +1121,7 @@ gr_status attn_run(const gr_attn_params* p, const int32_t* slot, bool kv8, float
   AttnCtx c;
   c.B = p->B; c.W = p->W; c.Hq = p->Hq; c.Hkv = p->Hkv; c.g = g; c.ND = p->ND; c.u = p->u;
   c.M = p->W * g;
-  const AttnPlan plan = plan_attn(p);
+  const AttnPlan plan = plan_attn(p, kv8);
   c.MB = (c.M + plan.mwg - 1) / plan.mwg;
   c.nsplit = plan.nsplit;
   c.n_groups = p->B * p->Hkv * c.nsplit;

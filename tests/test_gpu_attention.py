@@ -202,3 +202,16 @@ def test_scores_that_jump_inside_the_prompt(gr, oracle_lib, d, rows, segments, f
         _check(gr, oracle_lib, a, float(np.float32(1 / np.sqrt(d))))
     finally:
         gr.gr_diag_attn_plan(0, 0)
+
+
+@pytest.mark.parametrize("B,W,uniform", [(32, 80, False), (32, 64, False), (33, 64, False), (33, 64, True)])
+def test_many_workgroups_of_either_size(gr, oracle_lib, B, W, uniform):
+    """256 workgroups of 256 query rows or more: 128 rows where they leave fewer rows unused (80 beams x 4 heads), 256 rows in one round, 128
+    rows for short prompts in more than one, with requests of one length and ordered by length."""
+    lens = tuple(70 if uniform else 1 + 9 * (b % 16) for b in range(B))
+    a = rand_attn_case(960 + B + W, B, W, 32, 8, 128, 3, 3, lens)
+    rng = np.random.default_rng(9)
+    n = 400
+    tri = np.stack([np.arange(n) % B, rng.integers(0, W, n), rng.integers(0, 32, n)], axis=1).astype(np.int32)
+    tri[:4, 1] = [0, W - 1, 31, min(W - 1, 32)]
+    _check(gr, oracle_lib, a, float(np.float32(1 / np.sqrt(128))), tri)

@@ -138,3 +138,14 @@ def test_fp8kv_scores_that_jump_inside_the_prompt(gr, oracle_lib, d, rows, facto
         _check(gr, oracle_lib, a, float(np.float32(1 / np.sqrt(d))))
     finally:
         gr.gr_diag_attn_plan(0, 0)
+
+
+@pytest.mark.parametrize("W", [64, 80])
+def test_fp8kv_many_workgroups_of_either_size(gr, oracle_lib, W):
+    """256 workgroups of 256 query rows or more: 256 rows, and 128 rows where they leave fewer unused."""
+    B = 33
+    a = rand_attn_case(970 + W, B, W, 32, 8, 128, 3, 2, tuple(1 + 9 * (b % 16) for b in range(B)))
+    rng = np.random.default_rng(9)
+    n = 300
+    tri = np.stack([np.arange(n) % B, rng.integers(0, W, n), rng.integers(0, 32, n)], axis=1).astype(np.int32)
+    _check(gr, oracle_lib, a, float(np.float32(1 / np.sqrt(128))), tri)
