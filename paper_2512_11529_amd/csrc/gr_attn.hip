@@ -51,6 +51,8 @@ struct AttnCtx {
   int MB;           // row blocks per (b, kv head)
   int nsplit;       // L segments per request
   int n_groups;     // B * Hkv * nsplit
+  int by_weight;    // causal: an XCD's row blocks are dealt heaviest first over all of its (request, KV head) pairs
+  float rcp_hkv;    // 1 / Hkv, a little high: n * rcp_hkv is n / Hkv rounded down for 0 <= n < 512
   float c;          // sm_scale * log2(e)
   float k_scale, v_scale;   // FP8 prompt cache: value = code * scale (1 for the bf16 cache)
   const uint16_t* q;
@@ -79,6 +81,16 @@ __device__ __forceinline__ void divmod_small(int n, int d, float rcp_d, int* q, 
   if (rr >= d) { qq++; rr -= d; }
   if (rr < 0) { qq--; rr += d; }
   *q = qq; *r = rr;
+}
+
+__device__ __forceinline__ int wave_total(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);      // row_shr:1
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);      // row_shr:2
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);      // row_shr:4
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);      // row_shr:8
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);      // lane 15 of rows 0, 2 to rows 1, 3
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);      // lane 31 to rows 2, 3
+  return __builtin_amdgcn_readlane(v, 63);
 }
 
 // Per-tile building blocks.  A tile is KT = 64 prompt tokens; S^T of a tile is [64 kv x 32*NCB q]
@@ -333,9 +345,36 @@ k_beam_attn(AttnCtx c) {
   const unsigned id = blockIdx.x;
   const int xcd = (int)(id & 7u);
   const unsigned slot = id >> 3;
-  const int group = (int)(slot / (unsigned)c.MB) * 8 + xcd;
+  int group = (int)(slot / (unsigned)c.MB) * 8 + xcd;
   int mbi = (int)(slot % (unsigned)c.MB);
   if (CAUSAL) mbi = c.MB - 1 - mbi;            // the blocks with the most keys to visit start first
+  int len_l = 0, row0_l = 0;
+  if (CAUSAL && c.by_weight) {
+    // Lane i knows pair xcd + 8 i.  Unit `slot` of the order by falling block number: its number mbi is the largest with more than `slot`
+    // blocks of that number or above, and of the pairs that have such a block it is the one behind the rest.
+    const int mine = xcd + 8 * lane;
+    if (mine < c.n_groups) {
+      const int bm = (int)((float)mine * c.rcp_hkv);         // (exact: see the host)
+      row0_l = c.cu[bm];
+      len_l = c.cu[bm + 1] - row0_l;
+    }
+    const int blocks = (len_l * c.g + MWG - 1) / MWG;
+    auto from = [&](int m) { return wave_total(max(blocks - m, 0)); };
+    int above = c.MB, rank = (int)slot;
+    mbi = 0;
+    while (above - mbi > 1) {
+      const int mid = (mbi + above) >> 1, n = from(mid);
+      if (n > (int)slot) mbi = mid;
+      else { above = mid; rank = (int)slot - n; }
+    }
+    const uint64_t have = __ballot(blocks > mbi);
+    const uint64_t it = __ballot(blocks > mbi && (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(have >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)have, 0)) == rank);
+    if (it == 0) return;                       // (past the last unit)
+    const int l = __ffsll((unsigned long long)it) - 1;
+    group = xcd + 8 * l;
+    row0_l = __builtin_amdgcn_readlane(row0_l, l);
+    len_l = __builtin_amdgcn_readlane(len_l, l);
+  }
   if (group >= c.n_groups) return;
   const unsigned gq = (unsigned)group / (unsigned)c.nsplit;
   const int sp = (int)((unsigned)group - gq * (unsigned)c.nsplit);
@@ -343,8 +382,9 @@ k_beam_attn(AttnCtx c) {
   const int kvh = (int)(gq - (unsigned)bi * (unsigned)c.Hkv);
   const int b = c.order ? c.order[bi] : bi;
 
-  const int row0 = c.cu[b];
-  const int Lb = c.cu[b + 1] - row0;
+  const bool looked_up = CAUSAL && c.by_weight;
+  const int row0 = looked_up ? row0_l : c.cu[b];
+  const int Lb = looked_up ? len_l : c.cu[b + 1] - row0;
   const int Mb = CAUSAL ? Lb * c.g : c.M;                      // query rows of this (request, KV head)
   if (CAUSAL && mbi * (NWAVES * 32 * NCB) >= Mb) return;       // (before any barrier: the whole workgroup leaves)
   int chunk = (int)(((unsigned)Lb + (unsigned)c.nsplit - 1u) / (unsigned)c.nsplit);
@@ -1130,7 +1170,7 @@ gr_status attn_run(const gr_attn_params* p, const int32_t* slot, bool kv8, float
   c.q = (const uint16_t*)p->q; c.ks = (const uint16_t*)p->k_shared; c.vs = (const uint16_t*)p->v_shared;
   c.cu = p->cu_seqlens; c.ku = (const uint16_t*)p->k_unshared; c.vu = (const uint16_t*)p->v_unshared;
   c.out = (uint16_t*)p->out; c.lse = p->lse_out;
-  c.part_o = nullptr; c.part_ml = nullptr; c.order = nullptr; c.slot = slot;
+  c.part_o = nullptr; c.part_ml = nullptr; c.order = nullptr; c.slot = slot; c.by_weight = 0; c.rcp_hkv = 0.f;
   const size_t need = gr_beam_attn_workspace_bytes(p);
   if (need > 0) {
     if (!workspace || ((uintptr_t)workspace & 255)) return GR_ERR_INVALID_ARG;
@@ -1239,7 +1279,23 @@ extern "C" gr_status gr_prefill_attn(const gr_prefill_params* p, void* stream_) 
   c.out = (uint16_t*)p->out; c.lse = p->lse_out;
   c.part_o = nullptr; c.part_ml = nullptr; c.order = nullptr; c.slot = nullptr;
   const int64_t groups_padded = ((int64_t)c.n_groups + 7) / 8 * 8;
-  const int64_t grid = groups_padded * c.MB;
+  int64_t grid = groups_padded * c.MB;
+  // Row blocks dealt heaviest first over all pairs of an XCD: the blocks that prompts shorter than the longest do not have are not dealt
+  // (pair by pair they come first, and hold a place while they find that out), and the call ends with light blocks.  Against that stand
+  // 0.4 us at the start of every block and K/V that more pairs share the L2 at a time, so: where not all blocks have a place at once;
+  // for head size 64 always, for 128 (blocks of 128 rows) with 4 to 8 pairs to an XCD, or up to 16 of different lengths whose K/V take two thirds of
+  // an XCD's 4 MiB.  us pair by pair, by weight: 16 prompts of 60-700 tokens, 32 query and 8 KV heads of 128, 40.6, 38.7; 8 of 200-2000 135, 130; 4 of
+  // 300-1500 29.0, 27.0; 24 of 60-700 with 16 and 4 heads 42.9, 39.6; 8 heads of 64: 12 of 100-1000 19.3, 15.3, 16 of 1000-4000 149, 130, 64 x 1000 119, 114.
+  // But with 8 KV heads of 128 32 of 100-600 73.8, 79.1 and 64 x 1000 647, 797.
+  const int64_t pairs_per_xcd = groups_padded / 8, kv_per_xcd = p->total_L * p->Hkv * p->d * 4 / 8;
+  const bool few_pairs = pairs_per_xcd >= 4 && pairs_per_xcd <= 8;
+  const bool in_l2 = pairs_per_xcd <= 16 && pairs_per_xcd >= 4 && p->total_L * 5 < (int64_t)p->B * p->max_L * 4 && kv_per_xcd <= ((int64_t)4 << 20) * 2 / 3;
+  c.by_weight = groups_padded <= 512 && grid > 512 && (p->d == 64 || (mwg == 128 && (few_pairs || in_l2)));
+  c.rcp_hkv = 1.0f / (float)p->Hkv * 1.00001f;
+  if (c.by_weight && p->Hkv % 8 == 0) {                      // (every XCD has Hkv / 8 heads of all requests)
+    const int64_t most = (int64_t)p->Hkv * (p->total_L * g / mwg + p->B);
+    if (most < grid) grid = most;
+  }
   if (grid >= ((int64_t)1 << 31)) return GR_ERR_UNSUPPORTED;
   const size_t lds = attn_lds_bytes(p->d, mwg, 1);
 #define GR_LAUNCH_PREFILL(DD, NW_)                                                                                              \

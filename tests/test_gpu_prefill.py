@@ -183,3 +183,30 @@ def test_prefill_scores_that_jump_inside_the_prompt(oracle_lib, d, max_L, factor
     ref, _ = oracle_lib.prefill_attn_causal(c["q"], c["k"], c["v"], c["cu"], scale)
     err = np.abs(out.float().cpu().numpy() - ref.reshape(out.shape)).max()
     assert err <= 2e-2, f"max-abs {err}"
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,d,L_min,L_max", [
+    (24, 8, 8, 64, 0, 300),         # head size 64, prompts without a block among them
+    (64, 8, 8, 64, 100, 256),       # the most (request, KV head) pairs that are dealt by weight: 64 to an XCD
+    (65, 8, 8, 64, 100, 256),       # one request more: pair by pair
+    (8, 32, 8, 128, 1, 290),        # 8 pairs to an XCD
+    (16, 32, 8, 128, 1, 200),       # 16 of different lengths
+    (16, 6, 3, 128, 300, 700),      # KV heads that do not divide the XCDs evenly
+    (17, 16, 2, 128, 20, 220),      # 34 pairs: some XCDs have one more
+    (8, 32, 8, 128, 256, 256),      # one length, every block full
+])
+def test_prefill_blocks_dealt_by_weight(oracle_lib, B, Hq, Hkv, d, L_min, L_max):
+    """More row blocks than have a place at once, dealt heaviest first over all pairs of an XCD: every row of every request is written
+    once and is right."""
+    import paper_2512_11529_amd as gr
+    gr.load_library()
+    rng = np.random.default_rng(B + L_max)
+    lens = rng.integers(L_min, L_max + 1, B)
+    lens[B // 2] = L_max
+    c = _case(B + d, tuple(int(n) for n in lens), Hq, Hkv, d)
+    scale = float(np.float32(1 / np.sqrt(d)))
+    out, lse = _run(gr, c, scale)
+    ref, ref_lse = oracle_lib.prefill_attn_causal(c["q"], c["k"], c["v"], c["cu"], scale)
+    T = int(c["cu"][-1])
+    assert np.abs(out[:T] - ref.reshape(T, Hq, d)).max() <= 2e-2
+    np.testing.assert_allclose(lse[:T], ref_lse.reshape(T, Hq), rtol=0, atol=2e-3)
