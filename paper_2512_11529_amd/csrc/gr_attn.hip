@@ -51,7 +51,6 @@ struct AttnCtx {
   int MB;           // row blocks per (b, kv head)
   int nsplit;       // L segments per request
   int n_groups;     // B * Hkv * nsplit
-  int by_weight;    // causal: an XCD's row blocks are dealt heaviest first over all of its (request, KV head) pairs
   float rcp_hkv;    // 1 / Hkv, a little high: n * rcp_hkv is n / Hkv rounded down for 0 <= n < 512
   float c;          // sm_scale * log2(e)
   float k_scale, v_scale;   // FP8 prompt cache: value = code * scale (1 for the bf16 cache)
@@ -91,6 +90,39 @@ __device__ __forceinline__ int wave_total(int v) {
   v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);      // lane 15 of rows 0, 2 to rows 1, 3
   v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);      // lane 31 to rows 2, 3
   return __builtin_amdgcn_readlane(v, 63);
+}
+
+__device__ __forceinline__ int rank_in(uint64_t mask) {     // lanes of the mask in front of this one
+  return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0));
+}
+// The request of rank `rank` by decreasing prompt length (ties by index), its first row and its length; every wavefront by itself, lane i
+// with requests i and i + 64.  About 0.2 us, which the two dependent loads that it takes the place of (the order, then the
+// request's rows) cost as well; a kernel for the order is 5.6 us in front of the call.
+constexpr int kRankB = 128;
+__device__ __forceinline__ int request_by_length(const int32_t* cu, int B, int rank, int lane, int* row0, int* len) {
+  int first[2], l[2];
+#pragma unroll
+  for (int k = 0; k < 2; k++) {
+    first[k] = 0; l[k] = -1;
+    if (lane + 64 * k < B) { first[k] = cu[lane + 64 * k]; l[k] = cu[lane + 64 * k + 1] - first[k]; }
+  }
+  auto reach = [&](int n) { return __popcll(__ballot(l[0] >= n)) + __popcll(__ballot(l[1] >= n)); };
+  int lo = 0, hi = 64;                                       // more than `rank` requests reach lo, not so many hi
+  while (hi < 1 << 30 && reach(hi) > rank) { lo = hi; hi <<= 1; }
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if (reach(mid) > rank) lo = mid; else hi = mid;
+  }
+  rank -= reach(hi);                                         // among those of length lo
+  const uint64_t same0 = __ballot(l[0] == lo), same1 = __ballot(l[1] == lo);
+  const bool upper = rank >= __popcll(same0);
+  const uint64_t same = upper ? same1 : same0;
+  rank -= upper ? __popcll(same0) : 0;
+  const uint64_t it = __ballot(((same >> lane) & 1) && rank_in(same) == rank);
+  const int at = __ffsll((unsigned long long)it) - 1;
+  *row0 = __builtin_amdgcn_readlane(upper ? first[1] : first[0], at);
+  *len = lo;
+  return at + (upper ? 64 : 0);
 }
 
 // Per-tile building blocks.  A tile is KT = 64 prompt tokens; S^T of a tile is [64 kv x 32*NCB q]
@@ -311,7 +343,10 @@ struct AttnTile {
 // of their own in LDS; the second set's (maximum, sum, O) goes through LDS into the first's before the epilogue.  For launches of at
 // most one 128-row workgroup per CU, whose SIMDs would otherwise hold one wavefront each and wait out every chain of its tile
 // (1.1 us a tile and wavefront, 0.9 with a second one beside it).
-template <int D, int NCB, int NWAVES, bool CAUSAL, bool KV8, int KS>
+// FIND = true: a workgroup finds out from the lengths which unit it is: CAUSAL = false, requests by decreasing prompt length (at most kRankB);
+// CAUSAL = true, an XCD's row blocks heaviest first over all of its (request, KV head) pairs.  (Kernels of their own: the others took 0.3 us
+// longer with that code to jump over.)
+template <int D, int NCB, int NWAVES, bool CAUSAL, bool KV8, int KS, bool FIND>
 __global__ void __launch_bounds__(NWAVES * 64 * KS) __attribute__((amdgpu_waves_per_eu(NCB == 1 ? 2 : 1, NCB == 1 ? 2 : 1)))
 k_beam_attn(AttnCtx c) {
   using T = AttnTile<D, NCB>;
@@ -349,7 +384,7 @@ k_beam_attn(AttnCtx c) {
   int mbi = (int)(slot % (unsigned)c.MB);
   if (CAUSAL) mbi = c.MB - 1 - mbi;            // the blocks with the most keys to visit start first
   int len_l = 0, row0_l = 0;
-  if (CAUSAL && c.by_weight) {
+  if constexpr (CAUSAL && FIND) {
     // Lane i knows pair xcd + 8 i.  Unit `slot` of the order by falling block number: its number mbi is the largest with more than `slot`
     // blocks of that number or above, and of the pairs that have such a block it is the one behind the rest.
     const int mine = xcd + 8 * lane;
@@ -368,7 +403,7 @@ k_beam_attn(AttnCtx c) {
       else { above = mid; rank = (int)slot - n; }
     }
     const uint64_t have = __ballot(blocks > mbi);
-    const uint64_t it = __ballot(blocks > mbi && (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(have >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)have, 0)) == rank);
+    const uint64_t it = __ballot(blocks > mbi && rank_in(have) == rank);
     if (it == 0) return;                       // (past the last unit)
     const int l = __ffsll((unsigned long long)it) - 1;
     group = xcd + 8 * l;
@@ -380,11 +415,10 @@ k_beam_attn(AttnCtx c) {
   const int sp = (int)((unsigned)group - gq * (unsigned)c.nsplit);
   const int bi = (int)(gq / (unsigned)c.Hkv);
   const int kvh = (int)(gq - (unsigned)bi * (unsigned)c.Hkv);
-  const int b = c.order ? c.order[bi] : bi;
-
-  const bool looked_up = CAUSAL && c.by_weight;
-  const int row0 = looked_up ? row0_l : c.cu[b];
-  const int Lb = looked_up ? len_l : c.cu[b + 1] - row0;
+  int b = c.order ? c.order[bi] : bi;
+  if constexpr (!CAUSAL && FIND) b = request_by_length(c.cu, c.B, bi, lane, &row0_l, &len_l);
+  const int row0 = FIND ? row0_l : c.cu[b];
+  const int Lb = FIND ? len_l : c.cu[b + 1] - row0;
   const int Mb = CAUSAL ? Lb * c.g : c.M;                      // query rows of this (request, KV head)
   if (CAUSAL && mbi * (NWAVES * 32 * NCB) >= Mb) return;       // (before any barrier: the whole workgroup leaves)
   int chunk = (int)(((unsigned)Lb + (unsigned)c.nsplit - 1u) / (unsigned)c.nsplit);
@@ -546,7 +580,8 @@ k_beam_attn(AttnCtx c) {
   static_assert(NCB == 1, "one column block per wave");
   constexpr int UR = 32;                                 // rows of a mini-tile
   constexpr int UP = UR * PPR / 64;                      // 16-byte pieces per lane and tensor
-  const bool own_stage = !CAUSAL && set == 0 && sp == own_sp && c.u > 0;
+  const bool may_own = !CAUSAL && set == 0 && (sp == 0 || sp == c.nsplit - 1) && c.u > 0;     // (known before the prompt's length is)
+  const bool own_stage = may_own && sp == own_sp;
   auto wave_rows = [&](int wv, int* first_beam) {        // rows of wave wv's mini-tiles, and its first beam
     const int r_first = mbi * MWG + wv * 32;
     if (r_first >= Mb) { *first_beam = 0; return 0; }
@@ -555,7 +590,7 @@ k_beam_attn(AttnCtx c) {
     return (r_last / c.g - *first_beam + 1) * c.u;
   };
   int beam0 = 0, npass = 0, R = 0;
-  if (own_stage) {
+  if (may_own) {
     // the most beams any wave's 32 rows can span (exact when g divides 32, else an upper bound: a surplus
     // pass only sees masked rows)
     const int nb_max = min(c.W, (32 % c.g == 0) ? 32 / c.g : (32 + c.g - 2) / c.g + 1);
@@ -620,7 +655,7 @@ k_beam_attn(AttnCtx c) {
     if (kQSeparate) tload(false, flip, 0);
     tload(true, flip ^ 1, min(1, ntiles - 1));
   }
-  int prow0 = own_stage ? own_row(0) : 0;
+  int prow0 = may_own ? own_row(0) : 0;
   // Q as B operands: lane holds query column n32 of the wave's block, d = 16*ks + 8*G + (0..7)
   bf16x8 qop[NCB][D / 16];
   {
@@ -1112,7 +1147,9 @@ AttnPlan plan_attn(const gr_attn_params* p, bool kv8) {
 }
 
 // Ragged batches with more units than CUs are worth ordering by length (measured: 4 % on 128 requests of
-// 512..8192 tokens); a uniform batch (total_L == B * max_L) is not touched.
+// 512..8192 tokens); a uniform batch (total_L == B * max_L) is not touched.  Up to kRankB requests every workgroup finds its own by
+// rank (FIND), beyond that a kernel of one workgroup writes the order first: 128 of 40-120 tokens x 30 beams, 32 query and 8 KV
+// heads of 128, 36.9 us with that kernel, 33.2 without; 100 of 50-500 x 40, 8 and 2 heads of 64, 16.0, 12.6.
 bool attn_wants_order(const gr_attn_params* p, const AttnPlan& plan) {
   return p->B >= 2 && p->B <= kMaxOrderB && p->total_L != (int64_t)p->B * p->max_L && plan.many;
 }
@@ -1174,13 +1211,16 @@ gr_status attn_run(const gr_attn_params* p, const int32_t* slot, bool kv8, float
   c.q = (const uint16_t*)p->q; c.ks = (const uint16_t*)p->k_shared; c.vs = (const uint16_t*)p->v_shared;
   c.cu = p->cu_seqlens; c.ku = (const uint16_t*)p->k_unshared; c.vu = (const uint16_t*)p->v_unshared;
   c.out = (uint16_t*)p->out; c.lse = p->lse_out;
-  c.part_o = nullptr; c.part_ml = nullptr; c.order = nullptr; c.slot = slot; c.by_weight = 0; c.rcp_hkv = 0.f;
+  c.part_o = nullptr; c.part_ml = nullptr; c.order = nullptr; c.slot = slot; c.rcp_hkv = 0.f;
   const size_t need = gr_beam_attn_workspace_bytes(p);
+  bool find = false;
   if (need > 0) {
     if (!workspace || ((uintptr_t)workspace & 255)) return GR_ERR_INVALID_ARG;
     if (workspace_bytes < need) return GR_ERR_WORKSPACE_TOO_SMALL;
     char* ws = (char*)workspace;
-    if (attn_wants_order(p, plan)) {
+    if (attn_wants_order(p, plan) && p->B <= kRankB && plan.ks == 1) {
+      find = true;
+    } else if (attn_wants_order(p, plan)) {
       hipLaunchKernelGGL(k_attn_order, dim3(1), dim3(256), 0, stream, p->cu_seqlens, p->B, (int32_t*)ws);
       c.order = (const int32_t*)ws;
       ws += gr_align256((size_t)p->B * 4);
@@ -1195,21 +1235,25 @@ gr_status attn_run(const gr_attn_params* p, const int32_t* slot, bool kv8, float
   const int64_t grid = groups_padded * c.MB;
   if (grid >= ((int64_t)1 << 31)) return GR_ERR_UNSUPPORTED;
   const size_t lds = attn_lds_bytes(p->d, plan.mwg, plan.ks);
-#define GR_LAUNCH_ATTN(DD, NW_, KS_)                                                                                        \
-  do {                                                                                                                       \
-    if (kv8) {                                                                                                               \
-      if (const gr_status st = gr_allow_lds<k_beam_attn<DD, 1, NW_, false, true, KS_>>(lds)) return st; \
-      hipLaunchKernelGGL((k_beam_attn<DD, 1, NW_, false, true, KS_>), dim3((unsigned)grid), dim3(NW_ * 64 * KS_), lds, stream, c);   \
-    } else {                                                                                                                 \
-      if (const gr_status st = gr_allow_lds<k_beam_attn<DD, 1, NW_, false, false, KS_>>(lds)) return st; \
-      hipLaunchKernelGGL((k_beam_attn<DD, 1, NW_, false, false, KS_>), dim3((unsigned)grid), dim3(NW_ * 64 * KS_), lds, stream, c);  \
-    }                                                                                                                        \
+#define GR_LAUNCH(...)                                                                                       \
+  do {                                                                                                       \
+    if (const gr_status st = gr_allow_lds<k_beam_attn<__VA_ARGS__>>(lds)) return st;                         \
+    hipLaunchKernelGGL((k_beam_attn<__VA_ARGS__>), dim3((unsigned)grid), dim3(threads), lds, stream, c);     \
   } while (0)
+#define GR_LAUNCH_ATTN(DD, NW_)                                                                              \
+  do {                                                                                                       \
+    if (find) { if (kv8) GR_LAUNCH(DD, 1, NW_, false, true, 1, true); else GR_LAUNCH(DD, 1, NW_, false, false, 1, true); }      \
+    else { if (kv8) GR_LAUNCH(DD, 1, NW_, false, true, 1, false); else GR_LAUNCH(DD, 1, NW_, false, false, 1, false); }         \
+  } while (0)
+#define GR_LAUNCH_SETS(DD)                                                                                   \
+  do { if (kv8) GR_LAUNCH(DD, 1, 4, false, true, 2, false); else GR_LAUNCH(DD, 1, 4, false, false, 2, false); } while (0)
+  const unsigned threads = plan.mwg == 256 || plan.ks == 2 ? 512 : 256;
   if (p->d == 128) {
-    if (plan.mwg == 256) GR_LAUNCH_ATTN(128, 8, 1); else if (plan.ks == 2) GR_LAUNCH_ATTN(128, 4, 2); else GR_LAUNCH_ATTN(128, 4, 1);
+    if (plan.mwg == 256) GR_LAUNCH_ATTN(128, 8); else if (plan.ks == 2) GR_LAUNCH_SETS(128); else GR_LAUNCH_ATTN(128, 4);
   } else {
-    if (plan.mwg == 256) GR_LAUNCH_ATTN(64, 8, 1); else if (plan.ks == 2) GR_LAUNCH_ATTN(64, 4, 2); else GR_LAUNCH_ATTN(64, 4, 1);
+    if (plan.mwg == 256) GR_LAUNCH_ATTN(64, 8); else if (plan.ks == 2) GR_LAUNCH_SETS(64); else GR_LAUNCH_ATTN(64, 4);
   }
+#undef GR_LAUNCH_SETS
 #undef GR_LAUNCH_ATTN
   if (c.nsplit > 1) {
     const int64_t rows = (int64_t)p->B * p->W * p->Hq;
@@ -1294,25 +1338,23 @@ extern "C" gr_status gr_prefill_attn(const gr_prefill_params* p, void* stream_) 
   const int64_t pairs_per_xcd = groups_padded / 8, kv_per_xcd = p->total_L * p->Hkv * p->d * 4 / 8;
   const bool few_pairs = pairs_per_xcd >= 4 && pairs_per_xcd <= 8;
   const bool in_l2 = pairs_per_xcd <= 16 && pairs_per_xcd >= 4 && p->total_L * 5 < (int64_t)p->B * p->max_L * 4 && kv_per_xcd <= ((int64_t)4 << 20) * 2 / 3;
-  c.by_weight = groups_padded <= 512 && grid > 512 && (p->d == 64 || (mwg == 128 && (few_pairs || in_l2)));
+  const bool by_weight = groups_padded <= 512 && grid > 512 && (p->d == 64 || (mwg == 128 && (few_pairs || in_l2)));
   c.rcp_hkv = 1.0f / (float)p->Hkv * 1.00001f;
-  if (c.by_weight && p->Hkv % 8 == 0) {                      // (every XCD has Hkv / 8 heads of all requests)
+  if (by_weight && p->Hkv % 8 == 0) {                      // (every XCD has Hkv / 8 heads of all requests)
     const int64_t most = (int64_t)p->Hkv * (p->total_L * g / mwg + p->B);
     if (most < grid) grid = most;
   }
   if (grid >= ((int64_t)1 << 31)) return GR_ERR_UNSUPPORTED;
   const size_t lds = attn_lds_bytes(p->d, mwg, 1);
-#define GR_LAUNCH_PREFILL(DD, NW_)                                                                                              \
-  do {                                                                                                                         \
-    if (const gr_status st = gr_allow_lds<k_beam_attn<DD, 1, NW_, true, false, 1>>(lds)) return st; \
-    hipLaunchKernelGGL((k_beam_attn<DD, 1, NW_, true, false, 1>), dim3((unsigned)grid), dim3(NW_ * 64), lds, stream, c);          \
-  } while (0)
+  const unsigned threads = 2 * mwg;
   if (p->d == 128) {
-    if (mwg == 256) GR_LAUNCH_PREFILL(128, 8); else GR_LAUNCH_PREFILL(128, 4);
+    if (mwg == 256) GR_LAUNCH(128, 1, 8, true, false, 1, false);
+    else if (by_weight) GR_LAUNCH(128, 1, 4, true, false, 1, true);
+    else GR_LAUNCH(128, 1, 4, true, false, 1, false);
   } else {
-    GR_LAUNCH_PREFILL(64, 4);
+    if (by_weight) GR_LAUNCH(64, 1, 4, true, false, 1, true); else GR_LAUNCH(64, 1, 4, true, false, 1, false);
   }
-#undef GR_LAUNCH_PREFILL
+#undef GR_LAUNCH
   GR_HIP_TRY(hipGetLastError());
   return GR_OK;
 }

@@ -215,3 +215,17 @@ def test_many_workgroups_of_either_size(gr, oracle_lib, B, W, uniform):
     tri = np.stack([np.arange(n) % B, rng.integers(0, W, n), rng.integers(0, 32, n)], axis=1).astype(np.int32)
     tri[:4, 1] = [0, W - 1, 31, min(W - 1, 32)]
     _check(gr, oracle_lib, a, float(np.float32(1 / np.sqrt(128))), tri)
+
+
+@pytest.mark.parametrize("B", [63, 64, 65, 127, 128, 129])
+@pytest.mark.parametrize("lens", ["ragged", "two lengths", "one long"])
+def test_requests_by_decreasing_length(gr, oracle_lib, B, lens):
+    """More workgroups than CUs: every workgroup finds its request by rank (up to 128 requests; a kernel orders more); equal lengths,
+    requests without a prompt, lengths around powers of two."""
+    rng = np.random.default_rng(B)
+    n = {"ragged": rng.integers(0, 150, B), "two lengths": np.where(rng.random(B) < 0.5, 63, 64), "one long": np.where(np.arange(B) == B - 1, 513, 1)}[lens]
+    n[:2] = [128, 0]
+    a = rand_attn_case(980 + B, B, 40, 8, 8, 64, 3, 1, tuple(int(x) for x in n))
+    m = 3 * B
+    tri = np.stack([np.arange(m) % B, rng.integers(0, 40, m), rng.integers(0, 8, m)], axis=1).astype(np.int32)
+    _check(gr, oracle_lib, a, 0.125, tri)
