@@ -1090,10 +1090,12 @@ __global__ void __launch_bounds__(256) k_attn_order(const int32_t* cu, int B, in
 // 4 waves to a CU, or, where there is at most one per CU, one of 8 waves in two sets that share the prompt (ks = 2: 8 requests of
 // 2048 tokens x 128 beams, 256 workgroups, 46.3 -> 41.8 us; 2 x 256 x 16 of head size 64 8.4 -> 7.7).
 // Splitting the prompt into L segments costs fp32 partials through memory and the merge kernel.  With fewer workgroups than
-// CUs, the number of segments is the one for which this sum is least, in us: 1.6 (head size 128) or 1.07 (64) for a tile of each
-// set that a segment holds, 3.5 for the merge, and the partials written and read at 4 TB/s.  It is within 10 % of what 60 shapes of
-// 256 to 12000 tokens took: 8 requests of 700 tokens, 128 beams, 16 query and 2 KV heads: 17.5, 25.0, 25.8, 26.1 us with 1 to 4 segments
-// (about one workgroup per CU means 2); one of 4096 tokens 54.2, 35.4, 23.8, 20.8, 25.2 with 1, 2, 4, 8, 16 (16).
+// CUs, the number of segments is the one for which this sum is least, in us: for every round of workgroups of an XCD (32 CUs, one or two
+// to a CU; a segment of a (request, KV head) pair stays on one XCD) 6 and 1.6 (head size 128) or 1.07 (64) for a tile of each
+// set that a segment holds, 3.5 for the merge, and the partials written and read at 3 TB/s (64: 3.5).  Over 48 shapes of 400 to 12000 tokens it is 2 %
+// above the best number on average (3.4 % without the rounds and with 4 TB/s): 2 requests of 8000 tokens x 200
+// beams, 8 query and 2 KV heads of 64: 29.2 us with 9 segments, whose 36 pairs put 35 workgroups on some XCDs, 20.5 with 8; 4 x 2048 x 128 of 8
+// heads of 64 20.9 with 8, 15.9 with 4; one of 800 x 128 of these 13.9, 13.7, 12.5, 11.5, 12.8 with 1 to 5.
 //
 // With 256 workgroups of 256 rows or more, 128 rows win nevertheless, us with 128 and 256 rows:
 //   where they waste fewer rows of the last block (more than 5 %; 8 % for FP8 codes, which every workgroup widens for itself): 128 requests of
@@ -1124,14 +1126,15 @@ AttnPlan plan_attn(const gr_attn_params* p, bool kv8) {
   const int64_t units = (int64_t)p->B * p->Hkv * ((M + plan.mwg - 1) / plan.mwg);
   plan.nsplit = 1;
   if (units < 256 && p->max_L > 4 * KT) {
-    const int64_t want = (256 + units / 2) / units, cap = p->max_L / (4 * KT);        // about one workgroup per CU; at least four tiles per segment
+    const int64_t want = (256 + units / 2) / units, cap = p->max_L / ((p->d == 64 ? 3 : 4) * KT);      // about one workgroup per CU; at least so many tiles per segment
     const int most = (int)(want < cap ? (want < 16 ? want : 16) : (cap < 16 ? cap : 16));
     const int tiles = (p->max_L + KT - 1) / KT;
-    const double partial_us = 2.0 * p->B * p->W * p->Hq * p->d * 4 / 4e6;             // of one segment
+    const double partial_us = 2.0 * p->B * p->W * p->Hq * p->d * 4 / (p->d == 64 ? 3.5e6 : 3e6);             // of one segment
     double least = 0;
     for (int n = 1; n <= most; n++) {
       const int ks = units * n <= 256 ? 2 : 1, per_set = ((tiles + n - 1) / n + ks - 1) / ks;
-      const double us = (p->d == 64 ? 1.07 : 1.6) * per_set + (n > 1 ? 3.5 + partial_us * n : 0.0);
+      const int64_t on_xcd = ((int64_t)p->B * p->Hkv * n + 7) / 8 * ((M + 127) / 128), rounds = (on_xcd + 64 / ks - 1) / (64 / ks);
+      const double us = (double)rounds * (6.0 + (p->d == 64 ? 1.07 : 1.6) * per_set) + (n > 1 ? 3.5 + partial_us * n : 0.0);
       if (n == 1 || us < least) { least = us; plan.nsplit = n; }
     }
   }
