@@ -50,6 +50,7 @@ enum { ROW_DEAD = 0, ROW_DENSE = 1, ROW_SPARSE = 2, ROW_DONE = 3 };      // low 
 struct SelCtx {
   int B, W, V, depth, step;
   int row_threads;           // threads that stream a row: thread t holds tokens 4 (t + row_threads i) .. + 3 for all i
+  int pick_b;                // level 0: requests whose only live row's workgroup may select as well (all of them or none)
   int unit_shift;            // log2 of the units (float4 of logits) behind a key of a streamed row: 8 per block of kBlockV logits, to a power of two
   const char* blob;          // mask blob or nullptr
   const float* logits;
@@ -934,7 +935,7 @@ __global__ void __launch_bounds__(NT, STRIDE ? 4 : 6) k_rows(SelCtx c) {
       if (tid < 64 && at < rows && !(s > -INFINITY)) mark_dead(c, r);
       for (uint64_t live = __ballot(s > -INFINITY); live; live &= live - 1) {
         const int l = __ffsll((unsigned long long)live) - 1, row = __builtin_amdgcn_readlane(r, l);
-        const bool first = c.V <= kBlockV && c.W <= kPickW && base + (int64_t)l * gridDim.x < c.B;
+        const bool first = base + (int64_t)l * gridDim.x < c.pick_b;
         float2 rivals = {-INFINITY, -INFINITY};              // (asked for here, looked at when the row's logits have been)
         static_assert(kPickW <= 2 * NT, "two other rows to a thread");
         if (first && 1 + tid < c.W) rivals.x = c.scores_in[row + 1 + tid];
@@ -1707,6 +1708,10 @@ extern "C" gr_status gr_beam_select(const gr_select_params* p, void* workspace, 
   c.row_data = (float*)ws;
 
   c.row_threads = p->step == 0 ? 512 : 256;
+  // A workgroup that selects writes its request's scores while others may still look for live rows: not where these are the scores that came
+  // in (k_select, a launch behind all readers, writes them then).
+  const bool in_place = (uintptr_t)p->scores_out < (uintptr_t)(p->scores_in + rows) && (uintptr_t)p->scores_in < (uintptr_t)(p->scores_out + rows);
+  c.pick_b = p->V <= kBlockV && p->W <= kPickW && !in_place ? p->B : 0;
   if (p->mask && p->step >= 1 && !(p->flags & GR_SELECT_FORCE_DENSE))
     hipLaunchKernelGGL(k_rows_listed, dim3((unsigned)((rows + kDeal * kGatherWaves - 1) / (kDeal * kGatherWaves) * kDeal)), dim3(kGatherWaves * 64), 0, stream, c);
   else if (p->step == 0)

@@ -3,6 +3,7 @@ streamed row is cut into, child counts around the limits of the gathered forms (
 levels 1 and 2, more beams than the selection keeps single groups for, and fewer groups than beams."""
 import numpy as np
 import pytest
+import torch
 
 import gr_synth
 from gpu_util import assert_select_equal, run_select, to_dev
@@ -281,6 +282,24 @@ def test_level_0_of_one_live_beam(gr, oracle_lib, V, W, masked, pattern):  # noq
     want = oracle_lib.beam_select(items, logits, sc, pf, 0)
     for _ in range(2):
         assert_select_equal(run_select(gr, mask, logits, sc, pf, rg, 0), want)
+
+
+@pytest.mark.parametrize("B,W,V", [(1, 16, 256), (5, 128, 8192), (600, 60, 64)])
+def test_level_0_with_scores_in_place(gr, oracle_lib, B, W, V):  # noqa: F811
+    """Scores written over the ones that came in, also for more rows than one look of every workgroup at its rows' scores covers (600 x 60):
+    the incoming scores are read before any is written, so only the selection's own launch writes them."""
+    rng = np.random.default_rng(B + W + V)
+    logits = (3.0 * rng.standard_normal((B, W, V))).astype(np.float32)
+    sc = np.full((B, W), -np.inf, np.float32)
+    sc[:, 0] = -rng.random(B)
+    pf, rg = np.full((B, W, 3), -1, np.int32), np.zeros((B, W, 2), np.int32)
+    want = oracle_lib.beam_select(None, logits, sc, pf, 0)
+    scores = to_dev(sc)
+    i32 = lambda *shape: torch.empty(shape, dtype=torch.int32, device="cuda:0")
+    out = {"parent": i32(B, W), "token": i32(B, W), "scores": scores, "prefix": i32(B, W, 3), "range": i32(B, W, 2), "item_index": i32(B, W)}
+    gr.gr_beam_select(None, to_dev(logits), scores, to_dev(pf), to_dev(rg), 0, out=out)
+    torch.cuda.synchronize()
+    assert_select_equal({k: v.cpu().numpy() for k, v in out.items()}, want)
 
 
 @pytest.mark.parametrize("W,counts", [(3, [1, 2, 5]), (40, [4, 5, 60, 64]), (128, [16, 17]), (129, [16, 17]), (500, [1, 4, 5]), (600, [1, 4, 5]), (1024, [1, 3]), (1030, [1, 3]),
