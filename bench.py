@@ -73,20 +73,25 @@ def measured_peaks(torch, gr, dev):
 
 def summarize_trace(path):
     """Mean kernel duration per decode level over the last 60 steps of a rocprofv3 kernel-trace CSV of this benchmark
-    (run with --no-extras: the trace then ends with the timed steps, each = k_beam_attn, k_rows, k_select)."""
+    (run with --no-extras: the trace then ends with the timed steps, each = k_beam_attn, k_rows where the rows have a kernel
+    of their own, k_select)."""
     import collections
     import csv
     rows = [r for r in csv.DictReader(open(path)) if any(k in r["Kernel_Name"] for k in ("k_rows", "k_select", "k_beam_attn"))]
     rows.sort(key=lambda r: int(r["Start_Timestamp"]))
-    seq = [("k_rows" if "k_rows" in r["Kernel_Name"] else "k_select" if "k_select" in r["Kernel_Name"] else "k_beam_attn",
-            int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) for r in rows][-180:]
+    steps = []
+    for r in rows:
+        name = next(k for k in ("k_rows", "k_select", "k_beam_attn") if k in r["Kernel_Name"])
+        if name == "k_beam_attn":
+            steps.append({})
+        if steps:
+            steps[-1][name] = int(r["End_Timestamp"]) - int(r["Start_Timestamp"])
     acc = collections.defaultdict(list)
-    for i in range(0, len(seq) - 2, 3):
-        trio = seq[i:i + 3]
-        if [t[0] for t in trio] != ["k_beam_attn", "k_rows", "k_select"]:
-            raise SystemExit(f"unexpected kernel order at {i}: {trio}")
-        for name, dur in trio:
-            acc[((i // 3) % 3, name)].append(dur)
+    for i, step in enumerate(steps[-60:]):
+        if "k_select" not in step:
+            raise SystemExit(f"unexpected kernel order in step {i}: {step}")
+        for name, dur in step.items():
+            acc[(i % 3, name)].append(dur)
     for name in ("k_beam_attn", "k_rows", "k_select"):
         print(f"{name:12s} " + "   ".join(f"level{lvl} {sum(acc[(lvl, name)]) / max(len(acc[(lvl, name)]), 1) / 1e3:7.1f} us" for lvl in range(3)))
 

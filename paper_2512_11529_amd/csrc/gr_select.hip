@@ -1,6 +1,6 @@
 // gr_beam_select: beam item step (paper Sections 6.1-6.3) on gfx950.
 //
-// Two kernels per call (no host synchronisation, no allocation; everything lives in caller buffers):
+// Two kernels per call, or one for few beams over a short vocabulary (no host synchronisation, no allocation; everything lives in caller buffers):
 //   k_rows         one pass over the logits.  A streamed row is read ONCE by a workgroup with 16-byte loads and kept in
 //                  registers for the max, the fp64 sum-exp and the keys; the validity bits come straight from the mask
 //                  row in memory.  A row with few valid children is gathered by one wavefront, which leaves all of its
@@ -889,6 +889,34 @@ __global__ void __launch_bounds__(kGatherWaves * 64, 8) k_rows_listed(SelCtx c) 
   }
 }
 
+// All rows of request b, a row to a wavefront, for the workgroup that selects too; a row is too short to be shared out.
+constexpr int kGatherRows = kSelThreads / 64, kGatherV = kPart;
+__device__ __forceinline__ void gather_rows(const SelCtx& c, const MaskView& mv, int b, char* lds) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), row = b * c.W + wave;
+  double* tab = (double*)lds;
+  float* keys = (float*)(tab + kExpTab) + wave * kLines;
+  float s_in = -INFINITY;
+  int start = 0, n = 0;
+  if (wave < c.W) {
+    s_in = c.scores_in[row];
+    row_children(c, mv, row, &start, &n);
+  }
+  fill_exp_tab(tab, kSelThreads);
+  __syncthreads();
+  if (wave >= c.W) return;
+  n = __builtin_amdgcn_readfirstlane(n);
+  start = __builtin_amdgcn_readfirstlane(start);
+  if (!(s_in > -INFINITY) || n == 0) {
+    if ((threadIdx.x & 63) == 0) mark_dead(c, row);
+    return;
+  }
+  GatherPart g;
+  const ExpK ek = exp_consts();
+  gather_part(g, c.logits + (size_t)row * c.V, child_list(c, mv) + start, n, 0, kPart, tab, ek, keys);
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  gather_done(c, g, row, s_in, start, n, keys);
+}
+
 // Rows that are streamed, dealt to workgroups
 //   one each: for calls whose rows are all streamed and, as a rule, all live;
 //   every gridDim-th (STRIDE): for level 0, where as a rule one row of a request is live, its first: these rows are dealt first, then a
@@ -1076,13 +1104,15 @@ __device__ int radix_select_all(const SelCtx& c, const MaskView& mv, int b, uint
 }
 
 // Bound: latency - a chain of some six memory round trips and a dozen barriers in one workgroup per request - and, with cold
-// caches, the 40 GB/s at which one CU draws lines.  32 requests x 256 beams, V = 8192: 15 / 24 / 13 us at levels 0 / 1 / 2 and 16 us
-// without a mask (25 / 34 / 27 and 28 us when all 64 K chunk keys of a request were read and re-read chunks lay across eight lines);
-// one request x 16 beams 8 us (12 us).  Code size is part of it: unrolled over registers this kernel was 81 KB and took up
+// caches, the 40 GB/s at which one CU draws lines.  32 requests x 256 beams, V = 8192: 17 / 9 us at levels 1 / 2 (34 and 27 us when all
+// 64 K chunk keys of a request were read and re-read chunks lay across eight lines); 4 us at level 0, where k_rows has selected as a rule.
+// Code size is part of it: unrolled over registers this kernel was 81 KB and took up
 // to twice as long, because each instruction line is fetched once per launch and used once; hence the rolled loops.
 // LISTED: the call's rows are gathered ones (k_rows_listed), else streamed ones (k_rows); each is half of the code.
-template <bool LISTED>
+// GATHER: the workgroup gathers its request's rows itself, a wavefront a row, and no kernel runs in front of this one.
+template <bool LISTED, bool GATHER>
 __global__ void __launch_bounds__(kSelThreads) k_select(SelCtx c) {
+  static_assert(LISTED || !GATHER, "streamed rows have kernels of their own");
   extern __shared__ __attribute__((aligned(16))) char smem[];
   uint64_t* s_list = (uint64_t*)smem;
   float* s_group = (float*)smem;                             // (before the list) best score of every group, or of every unit
@@ -1092,9 +1122,10 @@ __global__ void __launch_bounds__(kSelThreads) k_select(SelCtx c) {
   uint32_t* s_hist = s_units + kUnitCap;
   uint32_t* s_chunks = s_hist + kHistBins;                   // row << 8 | key above the threshold, from the front; row << 8 | four scores, from the back
   float* s_rbias = (float*)(s_chunks + kChunkCap);           // per beam row of the request: bias,
-  int32_t* s_rinfo = (int32_t*)(s_rbias + kMaxW);            // mode and child count,
-  int32_t* s_ra = s_rinfo + kMaxW;                           // first child (gathered), first token (streamed, level 1) or table range start,
-  float* s_rbest = (float*)(s_ra + kMaxW);                   // best score
+  constexpr int kRows = GATHER ? kGatherRows : kMaxW;
+  int32_t* s_rinfo = (int32_t*)(s_rbias + kRows);            // mode and child count,
+  int32_t* s_ra = s_rinfo + kRows;                           // first child (gathered), first token (streamed, level 1) or table range start,
+  float* s_rbest = (float*)(s_ra + kRows);                   // best score
   constexpr int NW = kSelThreads / 64;
   __shared__ float2 s_redf[2 * NW];
   __shared__ uint32_t s_redu[2 * NW], s_quads[NW];
@@ -1106,6 +1137,19 @@ __global__ void __launch_bounds__(kSelThreads) k_select(SelCtx c) {
   const int first_info = maybe_done ? c.row_info[(size_t)b * c.W] : 0;
   MaskView mv;
   if (c.blob) mv = mask_view(c.blob, c.V, c.depth);
+  if constexpr (GATHER) {
+    // what the rows leave stays in LDS: the places of this request's rows in the workspace lie there
+    __shared__ __attribute__((aligned(16))) float s_data[kGatherRows * kRowFloats], s_groups[kGatherRows * kGroups], s_bias[kGatherRows];
+    __shared__ int32_t s_info[kGatherRows], s_first[kGatherRows];
+    const uintptr_t row0 = (uintptr_t)b * c.W;
+    c.row_data = (float*)((uintptr_t)s_data - row0 * kRowFloats * 4);
+    c.row_group = (float*)((uintptr_t)s_groups - row0 * kGroups * 4);
+    c.row_bias = (float*)((uintptr_t)s_bias - row0 * 4);
+    c.row_info = (int32_t*)((uintptr_t)s_info - row0 * 4);
+    c.row_start = (int32_t*)((uintptr_t)s_first - row0 * 4);
+    gather_rows(c, mv, b, smem);
+    __syncthreads();                                         // (publishes the rows, and gives the rest of the LDS back)
+  }
 
   // ---- the groups' best scores that k_rows left (two by two for more than 1024 beams)
   const float* data = c.row_data + (size_t)b * c.W * kRowFloats;
@@ -1712,19 +1756,28 @@ extern "C" gr_status gr_beam_select(const gr_select_params* p, void* workspace, 
   // in (k_select, a launch behind all readers, writes them then).
   const bool in_place = (uintptr_t)p->scores_out < (uintptr_t)(p->scores_in + rows) && (uintptr_t)p->scores_in < (uintptr_t)(p->scores_out + rows);
   c.pick_b = p->V <= kBlockV && p->W <= kPickW && !in_place ? p->B : 0;
-  if (p->mask && p->step >= 1 && !(p->flags & GR_SELECT_FORCE_DENSE))
+  const bool listed = p->mask && p->step >= 1 && !(p->flags & GR_SELECT_FORCE_DENSE);
+  // One kernel instead of two where every wavefront of the selecting workgroup has at most one row, and that row one round of loads (longer ones
+  // are drawn faster by more CUs).  us of a level with two kernels and with one: one request x 16 beams, V = 256, 8 children a row 10.3, 9.4, 250 children 13.7,
+  // 13.0; V = 512, 500 children 14.1, 13.5; 256 x 16 12.9, 9.7 and 17.8, 14.6; 300 x 4 16.6, 15.6; 8 x 4 10.5, 8.5.  But two rows a wavefront
+  // (32 beams) 10.5, 12.0, and two rounds (1000 children of V = 1024, 16 beams) 15.4, 15.9.
+  const bool gather = listed && p->W <= kGatherRows && p->V <= kGatherV;
+  if (listed && !gather)
     hipLaunchKernelGGL(k_rows_listed, dim3((unsigned)((rows + kDeal * kGatherWaves - 1) / (kDeal * kGatherWaves) * kDeal)), dim3(kGatherWaves * 64), 0, stream, c);
-  else if (p->step == 0)
+  else if (!listed && p->step == 0)
     hipLaunchKernelGGL((k_rows<true, 512>), dim3((unsigned)(rows < kStrideGrid ? rows : kStrideGrid)), dim3(512), 0, stream, c);
-  else
+  else if (!listed)
     hipLaunchKernelGGL((k_rows<false, 256>), dim3((unsigned)rows), dim3(256), 0, stream, c);
-  if (p->mask && p->step >= 1 && !(p->flags & GR_SELECT_FORCE_DENSE)) {
-    if (const gr_status st = gr_allow_lds<k_select<true>>(kSelLdsBytes)) return st;
-    hipLaunchKernelGGL(k_select<true>, dim3(p->B), dim3(kSelThreads), kSelLdsBytes, stream, c);
-  } else {
-    if (const gr_status st = gr_allow_lds<k_select<false>>(kSelLdsBytes)) return st;
-    hipLaunchKernelGGL(k_select<false>, dim3(p->B), dim3(kSelThreads), kSelLdsBytes, stream, c);
-  }
+  const size_t lds = kSelLdsBytes - (gather ? (size_t)(kMaxW - kGatherRows) * 16 : 0);      // (the row tables are that much shorter)
+#define GR_LAUNCH_SELECT(...)                                                                                         \
+  do {                                                                                                                \
+    if (const gr_status st = gr_allow_lds<k_select<__VA_ARGS__>>(lds)) return st;                                     \
+    hipLaunchKernelGGL((k_select<__VA_ARGS__>), dim3(p->B), dim3(kSelThreads), lds, stream, c);                       \
+  } while (0)
+  if (gather) GR_LAUNCH_SELECT(true, true);
+  else if (listed) GR_LAUNCH_SELECT(true, false);
+  else GR_LAUNCH_SELECT(false, false);
+#undef GR_LAUNCH_SELECT
   GR_HIP_TRY(hipGetLastError());
   return GR_OK;
 }

@@ -326,3 +326,37 @@ def test_short_lists_taken_at_once(gr, oracle_lib, W, counts, close):  # noqa: F
         rg = np.stack([starts[:-1], starts[1:]], axis=1)[None].astype(np.int32)
         want = oracle_lib.beam_select(items, logits, sc, pf, 2)
         assert_select_equal(run_select(gr, mask, logits, sc, pf, rg, 2), want, f"dead {dead}")
+
+
+@pytest.mark.parametrize("W,V", [(1, 1), (2, 64), (16, 256), (15, 1024), (16, 512), (16, 513), (16, 1024), (16, 1025), (17, 1024)])
+@pytest.mark.parametrize("counts", [[1], [0, 3, 64], [240, 241, 512, 513], [10 ** 6]])
+def test_requests_that_one_workgroup_gathers(gr, oracle_lib, W, V, counts):  # noqa: F811
+    """Levels 1 and 2 around the most beams and the longest vocabulary that the selecting workgroup gathers itself: rows without children,
+    with few, of every length up to the vocabulary; dead beams, a request of dead beams alone, scores in place."""
+    rng = np.random.default_rng(W + V + len(counts))
+    B, T = 3, min(V, 40)
+    counts = [min(counts[i % len(counts)], V) for i in range(T)]
+    second = _children(rng, V, counts)
+    items = np.array([(t1, int(t2), int(t3)) for t1, row in enumerate(second) for t2 in row for t3 in sorted({0, V // 2, V - 1})], dtype=np.int32)
+    if len(items) == 0:
+        items = np.zeros((1, 3), np.int32)
+    mask = gr.gr_item_mask_build(to_dev(items), V)
+    sc = np.sort(-3.0 * rng.random((B, W)), axis=1)[:, ::-1].astype(np.float32).copy()
+    sc[1, ::3] = -np.inf
+    sc[2] = -np.inf
+    pf, rg = np.full((B, W, 3), -1, np.int32), np.zeros((B, W, 2), np.int32)
+    pf[:, :, 0] = rng.integers(0, T, (B, W))
+    for step in (1, 2):
+        logits = (3.0 * rng.standard_normal((B, W, V))).astype(np.float32)
+        if step == 1:
+            rg[:, :, 0], rg[:, :, 1] = np.searchsorted(items[:, 0], pf[:, :, 0]), np.searchsorted(items[:, 0], pf[:, :, 0] + 1)
+        want = oracle_lib.beam_select(items, logits, sc, pf, step)
+        got = run_select(gr, mask, logits, sc, pf, rg, step)
+        assert_select_equal(got, want, f"step {step}")
+        scores = to_dev(sc)
+        out = {k: torch.empty_like(to_dev(v)) for k, v in got.items()}
+        out["scores"] = scores
+        gr.gr_beam_select(mask, to_dev(logits), scores, to_dev(pf), to_dev(rg), step, out=out)
+        torch.cuda.synchronize()
+        assert_select_equal({k: v.cpu().numpy() for k, v in out.items()}, want, f"step {step}, in place")
+        sc, pf, rg = want["scores"], want["prefix"], want["range"]
