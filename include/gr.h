@@ -202,7 +202,7 @@ typedef struct {
   const int32_t* range_in;        /* int32 [B, W, 2]                                                */
   int32_t*       parent_out;      /* int32 [B, W] index of the beam each survivor extends           */
   int32_t*       token_out;       /* int32 [B, W] token appended                                    */
-  float*         scores_out;      /* fp32 [B, W] cumulative log-probability, non-increasing         */
+  float*         scores_out;      /* fp32 [B, W] cumulative log-probability, non-increasing; may be scores_in */
   int32_t*       prefix_out;      /* int32 [B, W, depth]; must not alias prefix_in                  */
   int32_t*       range_out;       /* int32 [B, W, 2];     must not alias range_in                   */
   int32_t*       item_index_out;  /* int32 [B, W] table row of the finished item when step ==       */
