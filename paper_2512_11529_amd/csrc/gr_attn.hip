@@ -125,6 +125,12 @@ __device__ __forceinline__ int request_by_length(const int32_t* cu, int B, int r
   return at + (upper ? 64 : 0);
 }
 
+// The larger of a value and the other half's (of lane ^ 32).
+__device__ __forceinline__ float halves_max(float v) {
+  const auto both = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(both[0]), __uint_as_float(both[1]));
+}
+
 // Per-tile building blocks.  A tile is KT = 64 prompt tokens; S^T of a tile is [64 kv x 32*NCB q]
 // = 2 sub-tiles x NCB column blocks of 32x32 fp32 accumulators.
 template <int D, int NCB>
@@ -208,7 +214,7 @@ struct AttnTile {
     for (int sub = 0; sub < KT / 32; sub++)
 #pragma unroll
       for (int i = 0; i < 16; i += 2) mx = fmaxf(fmaxf(mx, s[sub][0][i]), s[sub][0][i + 1]);
-    return fmaxf(mx, __shfl_xor(mx, 32, 64));
+    return halves_max(mx);
   }
 
   // One steady-state tile with the matrix and vector pipes kept busy together.  The wave issues, in this order,
@@ -227,13 +233,12 @@ struct AttnTile {
   }
   static __device__ __forceinline__ void fused(int sk_next, int sv_cur, const bf16x8 (&qop)[NCB][D / 16],
                                                const f32x16 (&s_cur)[KT / 32][NCB], f32x16 (&s_next)[KT / 32][NCB],
-                                               f32x16 (&o)[D / 32][NCB], float m2, float c, float& rs, const Rd& rdo) {
+                                               f32x16 (&o)[D / 32][NCB], float m2, float c, float& rs, bf16x8 (&pop)[KT / 16], const Rd& rdo) {
     static_assert(NCB == 1, "one column block per wave");
     auto rdk = [&](int i) { return read_k(sk_next, rdo, i % 2, i / 2); };
     auto rdv = [&](int i) { return read_v(sv_cur, rdo, i / (D / 32), i % (D / 32)); };
     constexpr int PF = 4;                                   // operand reads run PF MFMAs ahead
     bf16x8 a[NMF];
-    bf16x8 pop[KT / 16];
     float p[32], arg[32];                                   // (a few of each are alive at a time)
     rs = 0.f;
     const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -277,13 +282,21 @@ struct AttnTile {
     }
   }
 
-  // No tile after a segment's first is searched for its maximum (16 vector instructions a tile and an exchange between lanes).  The reference is
-  // the first tile's maximum plus kHead: probabilities start 2^-24 low, what lies far below the reference is lost at 2^-102 of the maximum
-  // (nothing to a sum of fp32), and scores may rise 48 bits inside one tile.  A column whose tile sums to more than 1 gets a higher
-  // reference after that tile; one with more than 2^kHead (where O could overflow) is computed again from the first token by a
-  // loop that looks for maxima (k_beam_attn's `redo`).  The loop is bound by what it issues beside the MFMAs, so this is worth 3 to 4 %:
-  // 32 x 4096 tokens x 256 beams 17 us of 505, 4 x 16384 x 512 in FP8 477 -> 459 us, 8 causal prompts of 1024-8192 1606 -> 1556.
-  static constexpr float kHead = 24.0f, kTooHigh = 16777216.0f;
+  // A segment's first and last tile are searched for the columns' maxima before their probabilities are made, the tiles between only from where a
+  // wavefront meets scores that rise: 16 vector instructions a tile and an exchange between lanes, in a loop bound by what it issues
+  // beside the MFMAs.  Worth 3 to 4 %: 32 x 4096 tokens x 256 beams 17 us of 505, 4 x 16384 x 512 in FP8 477 -> 459 us, 8 causal prompts of
+  // 1024-8192 1606 -> 1556.
+  // The reference is the first tile's maximum.  Where a lane's half of a column of a later tile sums to more than kRaise = 2^kLazy, which no
+  // column does without a score kLazy - 5 bits above its reference, the column gets a higher reference after that tile, a power of two
+  // for which this sum lies between 1 and 2, and the wavefront searches from there on: the reference becomes the maximum before a tile's
+  // probabilities are made, once it is exceeded by more than kLazy.  us with the search in every tile, with it from the first rise, and with
+  // neither, but columns that rose by 48 bits in a tile computed again: 32 x 4096 x 256 beams 509, 495, 492, and with scores of eight times
+  // the width that N(0,1) queries and keys give 535, 542, 860; 4 causal prompts of 3000 278, 268, 268 and 297, 302, 495.
+  //   Precision, in the one tile of the rise: the best token's probability, which may be nearly all of the sum, is not 1 as with the true
+  // maximum; O has it rounded to bf16 and the sum has not.  What the rounding changed of the tile's sum is kept and O scaled by it at the end.
+  //   Range: O may have overflowed there although the result does not.  A wavefront that met a rise looks through its O at the end, and where
+  // it finds that, or where a sum passed kTooHigh, it computes its columns again (k_beam_attn's `redo`).
+  static constexpr float kLazy = 8.0f, kRaise = 256.0f, kTooHigh = 0x1p100f;
 
   // The segment's last tile, which no scores follow: O += V . P with the exponentials of the next 16 tokens between the MFMAs of the present
   // ones.  V^T operand: d = 32*db + (lane%32), k slot e <-> token 16*s + 8*(e/4) + 4*G + e%4.
@@ -678,7 +691,8 @@ k_beam_attn(AttnCtx c) {
     }
   }
 
-  bool too_high = false;                               // some column's scores rose too fast for the loop below
+  float rounded = 0.f;                                 // what O has more of the sum than l_run, by rounding, in a tile of a rise
+  bool rise = false, again = false;                    // some column's scores rose far above its reference; too far
   if (ntiles > 0) {
     // Pipeline: iteration t issues S(t+1) = K(t+1).Q^T together with the softmax of S(t), then O += V(t).P(t).
     // K(t+2) and V(t+1) are written to LDS right after the barrier that opens iteration t, so one
@@ -691,22 +705,38 @@ k_beam_attn(AttnCtx c) {
     asm volatile("" : "+v"(prow0));                    // (waited for here, not at its first use)
     __syncthreads();                                   // K(0), K(1) are in LDS, and V(0) where it was requested with them
 
-    // One steady-state iteration: tile t (scores in s_in) has a successor whose scores go to s_out.  What the tile before brought
-    // is settled first (raising the reference, and rescaling O and the running sum, is a rare wave-uniform branch), so that the
-    // tile's MFMAs and exponentials form one straight-line block.
-    float rs = 0.f;                                    // the tile's sum
-    auto settle = [&]() {
+    // One steady-state iteration: tile t (scores in s_in) has a successor whose scores go to s_out.  The references are settled
+    // first (raising them, and rescaling O and the running sum, is a rare wave-uniform branch), so that the tile's MFMAs and
+    // exponentials form one straight-line block.
+    float rs = 0.f;                                    // sum of the tile before
+    bf16x8 pop[KT / 16];                               // the probabilities behind rs
+    auto rescale = [&](float alpha) __attribute__((always_inline)) {
+#pragma unroll
+      for (int db = 0; db < D / 32; db++)
+#pragma unroll
+        for (int i = 0; i < 16; i++) o_acc[db][0][i] *= alpha;
+      l_run[0] *= alpha;
+      rounded *= alpha;
+    };
+    auto settle = [&]() __attribute__((always_inline)) {       // by the sum of the tile before
       l_run[0] += rs;
-      if (__any(!(rs <= 1.f))) {
-        const float r = fmaxf(rs, __shfl_xor(rs, 32, 64));
-        too_high = too_high || __any(!(r <= T::kTooHigh));
-        const float m_new = r > 1.f ? m_run[0] + (T::kHead + (float)__builtin_amdgcn_frexp_expf(r)) : m_run[0];
-        const float alpha = __builtin_amdgcn_exp2f(m_run[0] - m_new);
+      if (__builtin_expect(!rise && __any(!(rs <= T::kRaise)), 0)) {
+        rise = true;
+        const float r = halves_max(rs);
+        again = again || __any(!(r <= T::kTooHigh));
+        float in_o = 0.f;
 #pragma unroll
-        for (int db = 0; db < D / 32; db++)
-#pragma unroll
-          for (int i = 0; i < 16; i++) o_acc[db][0][i] *= alpha;
-        l_run[0] *= alpha;
+        for (int e = 0; e < 32; e++) in_o += (float)pop[e / 8][e % 8];
+        if (r > T::kRaise) rounded += in_o - rs;
+        const float m_new = r > T::kRaise ? m_run[0] + (float)(__builtin_amdgcn_frexp_expf(r) - 1) : m_run[0];
+        rescale(__builtin_amdgcn_exp2f(m_run[0] - m_new));
+        m_run[0] = m_new;
+      }
+    };
+    auto raise_to = [&](float mx) __attribute__((always_inline)) {       // by the maximum of this tile
+      if (__any(mx > m_run[0] + T::kLazy)) {
+        const float m_new = fmaxf(m_run[0], mx);
+        rescale(__builtin_amdgcn_exp2f(m_run[0] - m_new));
         m_run[0] = m_new;
       }
     };
@@ -723,6 +753,7 @@ k_beam_attn(AttnCtx c) {
       constexpr int slot = decltype(slot_c)::value;
       settle();
       if (CAUSAL && seg0 + t * KT + KT - 1 > wave_tok0) causal_mask(s_in, seg0 + t * KT);       // (wave-uniform) past the wave's first token
+      if (__builtin_expect(rise, 0)) raise_to(T::colmax(s_in) * cp);
       tiles_landed();                                               // this wave's K(t+1) and V(t) loads (issued one step ago)
       __syncthreads();                                              // everyone's; and everyone is done with K(t) and V(t-1)
       if (KV8) {
@@ -735,7 +766,7 @@ k_beam_attn(AttnCtx c) {
         tload(false, slot ^ 1, min(t + 1, tl));                     // V(t+1) over V(t-1)
       }
       if (t == touch_own) touch_own_rows(prow0);
-      T::fused((slot ^ 1) * TILE, (2 + slot) * TILE, qop, s_in, s_out, o_acc, m_run[0], cp, rs, rdo);
+      T::fused((slot ^ 1) * TILE, (2 + slot) * TILE, qop, s_in, s_out, o_acc, m_run[0], cp, rs, pop, rdo);
     };
     // the last tile of the segment: the only one that can be partial, and it has no successor
     auto last = [&](f32x16 (&s_in)[KT / 32][NCB], int t) {
@@ -754,16 +785,17 @@ k_beam_attn(AttnCtx c) {
           }
       }
       if (CAUSAL) causal_mask(s_in, tok0);
-      if (t == 0) m_run[0] = T::colmax(s_in) * cp + T::kHead;
+      const float top = T::colmax(s_in) * cp;
+      if (t == 0) m_run[0] = top; else raise_to(top);
       T::finish(2 * TILE, s_in, o_acc, m_run[0], cp, rs, rdo);
-      settle();
+      l_run[0] += rs;
     };
 
     f32x16 s_a[KT / 32][NCB], s_b[KT / 32][NCB];      // ping-pong score accumulators: no copies
     T::qk(flip * TILE, qop, s_a, rdo);
     if (ntiles > 1) {
       if (CAUSAL && seg0 + KT - 1 > wave_tok0) causal_mask(s_a, seg0);
-      m_run[0] = T::colmax(s_a) * cp + T::kHead;       // (every column sees the segment's first token)
+      m_run[0] = T::colmax(s_a) * cp;                  // (every column sees the segment's first token)
     }
     // ntiles - 1 steps, then the last tile.  An odd step is peeled off first so that the loop runs
     // whole ping-pong pairs and the last tile is always in s_a.
@@ -800,7 +832,8 @@ k_beam_attn(AttnCtx c) {
   uint16_t* s_uk = smem + wave * UR * KSTR;
   uint16_t* s_uv = smem + NWAVES * UR * KSTR + wave * UR * VSTR;
   // (m, l, O) joined by 32 rows in LDS, this wave's alone; the column sees row base + k where base + k is below `rows` (as unsigned numbers).
-  // The reference is raised first only where the rows' sum shows that it has to be.
+  // The reference is the maximum of what the column has seen, so that the best own token's probability, which may be nearly all of the sum, is
+  // 1 and not rounded.
   auto mini_tile = [&](const uint16_t* s_uk, int kstr, const uint16_t* s_uv, int vstr, int base, unsigned rows, float cs, float& m, float& l) {
     f32x16 su;
 #pragma unroll
@@ -812,32 +845,26 @@ k_beam_attn(AttnCtx c) {
     }
 #pragma unroll
     for (int i = 0; i < 16; i++) su[i] = (unsigned)(base + 8 * (i / 4) + 4 * G + (i % 4)) < rows ? su[i] : -INFINITY;
-    float pr[16], rsum = 0.f;
+    float mx = -INFINITY;
 #pragma unroll
-    for (int i = 0; i < 16; i++) {
-      pr[i] = __builtin_amdgcn_exp2f(fmaf(su[i], cs, -m));
-      rsum += pr[i];
-    }
-    if (__any(!(rsum <= T::kTooHigh))) {                   // (or the column has seen no key yet: m is -inf)
-      float mx = -INFINITY;
-#pragma unroll
-      for (int i = 0; i < 16; i++) mx = fmaxf(mx, su[i]);
-      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-      const float m_new = fmaxf(m, mx * cs + T::kHead);
-      const bool any_key = m_new > -INFINITY;
-      const float alpha = any_key ? __builtin_amdgcn_exp2f(m - m_new) : 1.f;
-      rsum = 0.f;
-#pragma unroll
-      for (int i = 0; i < 16; i++) {
-        pr[i] = any_key ? __builtin_amdgcn_exp2f(fmaf(su[i], cs, -m_new)) : 0.f;
-        rsum += pr[i];
-      }
-      l *= alpha;
+    for (int i = 0; i < 16; i++) mx = fmaxf(mx, su[i]);
+    mx = halves_max(mx) * cs;
+    if (__any(mx > m)) {
+      const float m_new = fmaxf(m, mx), alpha = __builtin_amdgcn_exp2f(m - m_new);      // (m_new is -inf while the column has seen no key at all)
+      const float scale = mx > m ? alpha : 1.f;
+      l *= scale;
       m = m_new;
 #pragma unroll
       for (int db = 0; db < D / 32; db++)
 #pragma unroll
-        for (int i = 0; i < 16; i++) o_acc[db][0][i] *= alpha;
+        for (int i = 0; i < 16; i++) o_acc[db][0][i] *= scale;
+    }
+    const float ref = m > -INFINITY ? m : 0.f;
+    float pr[16], rsum = 0.f;
+#pragma unroll
+    for (int i = 0; i < 16; i++) {
+      pr[i] = __builtin_amdgcn_exp2f(fmaf(su[i], cs, -ref));
+      rsum += pr[i];
     }
     l += rsum;
     bf16x8 pu[UR / 16];
@@ -861,8 +888,8 @@ k_beam_attn(AttnCtx c) {
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");                    // the mini-tiles are rewritten by the next pass
   };
-  // The segment again for a wave with a column whose scores rose too fast: 32 tokens at a time through its mini-tiles, maxima first.  (The
-  // second set's waves have no more LDS to themselves than what they hand over in: their rows are not padded.)
+  // The segment again for a wave with a column whose scores rose too fast or whose O overflowed: 32 tokens at a time through its mini-tiles,
+  // maxima first.  (The second set's waves have no more LDS to themselves than what they hand over in: their rows are not padded.)
   auto redo = [&]() {
     const bool packed = KS == 2 && set == 1;
     uint16_t* k32 = packed ? (uint16_t*)s_set1 + wave * 2 * UR * D : s_uk;
@@ -889,7 +916,23 @@ k_beam_attn(AttnCtx c) {
       mini_tile(k32, kstr, v32, vstr, tok0, CAUSAL ? min((unsigned)seg1, (unsigned)tokq + 1u) : (unsigned)seg1, cp, m_run[0], l_run[0]);
     }
   };
-  if (__builtin_expect(too_high, 0)) redo();
+  if (__builtin_expect(rise, 0)) {
+    float z = l_run[0] * 0.f;                              // (0 unless something is infinite or no number)
+#pragma unroll
+    for (int db = 0; db < D / 32; db++)
+#pragma unroll
+      for (int i = 0; i < 16; i++) z = fmaf(o_acc[db][0][i], 0.f, z);
+    if (again || __any(!(z == 0.f))) {
+      redo();
+    } else {
+      const float l = l_run[0] + __shfl_xor(l_run[0], 32, 64), more = rounded + __shfl_xor(rounded, 32, 64);
+      const float scale = more == 0.f ? 1.f : l / (l + more);
+#pragma unroll
+      for (int db = 0; db < D / 32; db++)
+#pragma unroll
+        for (int i = 0; i < 16; i++) o_acc[db][0][i] *= scale;
+    }
+  }
   if (KV8 && ntiles > 0) {                                 // prompt loop -> true units
 #pragma unroll
     for (int db = 0; db < D / 32; db++)
@@ -1193,7 +1236,7 @@ gr_status attn_run(const gr_attn_params* p, const int32_t* slot, bool kv8, float
   if ((((uintptr_t)p->q | (uintptr_t)p->k_shared | (uintptr_t)p->v_shared | (uintptr_t)p->k_unshared | (uintptr_t)p->v_unshared |
         (uintptr_t)p->out) & 15) || ((uintptr_t)p->cu_seqlens & 3) || ((uintptr_t)p->lse_out & 3) || ((uintptr_t)slot & 3))
     return GR_ERR_INVALID_ARG;                                                          // every tensor is moved in 16-byte pieces
-  if (!(p->sm_scale > 0.f) || !(p->sm_scale < INFINITY)) return GR_ERR_INVALID_ARG;   // (also rejects NaN: the lazy-maximum test assumes a positive scale)
+  if (!(p->sm_scale > 0.f) || !(p->sm_scale < INFINITY)) return GR_ERR_INVALID_ARG;   // (also rejects NaN: the largest score is taken before it is scaled)
   if (p->d != 64 && p->d != 128) return GR_ERR_UNSUPPORTED;
   if (p->total_L >= ((int64_t)1 << 31)) return GR_ERR_UNSUPPORTED;
   if ((int64_t)p->max_L * p->Hkv * p->d * 2 >= ((int64_t)1 << 32)) return GR_ERR_UNSUPPORTED;   // one request's K (or V) must fit a buffer descriptor

@@ -186,10 +186,10 @@ def test_one_and_two_sets_of_wavefronts(gr, oracle_lib, d, B):
 
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("rows,segments", [(128, 1), (256, 1), (256, 2)])
-@pytest.mark.parametrize("factor", [3.0, 7.0])
+@pytest.mark.parametrize("factor", [3.0, 7.0, 12.0])
 def test_scores_that_jump_inside_the_prompt(gr, oracle_lib, d, rows, segments, factor):
-    """Keys that one beam's queries meet 34 to 50 bits (factor 3: its reference is raised after the tile) or 80 to 114 bits (factor 7: the
-    wavefront computes its columns again) above everything before them, in an early, a middle and the last tile of a prompt whose
+    """Keys that one beam's queries meet 34 to 50 bits (factor 3), 80 (7, head size 64: its reference is raised after the tile), 114 (7, head size
+    128) or 138 bits and more (12: the wavefront computes its columns again) above everything before them, in an early, a middle and the last tile of a prompt whose
     tiles are even or odd in number, for workgroups of one and of two sets of wavefronts."""
     lens, W, Hq, Hkv = (330, 400, 460), 40, 8, 2
     a = rand_attn_case(900 + d + rows, len(lens), W, Hq, Hkv, d, 3, 2, lens)
@@ -229,3 +229,91 @@ def test_requests_by_decreasing_length(gr, oracle_lib, B, lens):
     m = 3 * B
     tri = np.stack([np.arange(m) % B, rng.integers(0, 40, m), rng.integers(0, 8, m)], axis=1).astype(np.int32)
     _check(gr, oracle_lib, a, 0.125, tri)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("rows,segments", [(128, 1), (256, 1), (128, 2)])
+@pytest.mark.parametrize("power", [-118, 110])
+def test_values_near_the_ends_of_the_range(gr, oracle_lib, d, rows, segments, power):
+    """V times a power of two gives the output times that power, down to where products of V and probabilities meet fp32's smallest numbers
+    and up to where the un-normalised sums do not overflow unless a reference is far below the maximum; also for queries whose scores
+    jump by 34 to 50 bits inside the prompt or at an own token.  The bound is _check's: two roundings to bf16, 2^-7 max|V|."""
+    lens, W, Hq, Hkv = (330, 400, 60), 40, 8, 2
+    a = rand_attn_case(1000 + d + rows, len(lens), W, Hq, Hkv, d, 3, 2, lens)
+    q, k, ko = (gr_synth.bf16_bits_to_f32(a[n]).copy() for n in ("q", "k_shared", "k_unshared"))
+    for b, (w, head, tok) in enumerate([(3, 1, 70), (39, 6, 399)]):
+        k[a["cu_seqlens"][b] + tok, head // (Hq // Hkv)] = 3.0 * q[b, w, head]
+    for b, (w, head, tok) in enumerate([(4, 1, 0), (11, 6, 1), (20, 3, 1)]):
+        ko[b, w, tok, head // (Hq // Hkv)] = 3.0 * q[b, w, head]
+    a["k_shared"], a["k_unshared"] = gr_synth.f32_to_bf16_bits(k), gr_synth.f32_to_bf16_bits(ko)
+    scale = float(np.float32(1 / np.sqrt(d)))
+    gr.gr_diag_attn_plan(rows, segments)
+    try:
+        _check(gr, oracle_lib, a, scale)
+        want, want_lse = run_attn(gr, a, scale)
+        scaled = dict(a)
+        for n in ("v_shared", "v_unshared"):
+            scaled[n] = gr_synth.f32_to_bf16_bits(np.ldexp(gr_synth.bf16_bits_to_f32(a[n]), power))
+        out, lse = run_attn(gr, scaled, scale)
+    finally:
+        gr.gr_diag_attn_plan(0, 0)
+    vmax = max(float(np.abs(gr_synth.bf16_bits_to_f32(a[n])).max()) for n in ("v_shared", "v_unshared"))
+    assert np.isfinite(out).all()
+    assert np.abs(np.ldexp(out, -power) - want).max() <= 2.0 ** -7 * vmax
+    np.testing.assert_allclose(lse, want_lse, rtol=0, atol=2e-3)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("rows,segments", [(128, 1), (256, 1), (128, 2)])
+@pytest.mark.parametrize("factor", [3.0, 7.0, 12.0])
+def test_a_token_that_is_nearly_all_of_the_sum(gr, d, rows, segments, factor):
+    """A key 34 bits or more above all others of its column, in the first tile, a later one, the last one or among the own tokens: the others
+    add less than 2^-20 to values between 1 and 2, so the output is that token's V row, every bit of it.  (A probability that O takes
+    rounded and the sum does not gives values a bit off.)"""
+    lens, W, Hq, Hkv = (330, 400, 460), 40, 8, 2
+    a = rand_attn_case(1100 + d + rows, len(lens), W, Hq, Hkv, d, 3, 2, lens)
+    rng = np.random.default_rng(11)
+    values = lambda shape: gr_synth.f32_to_bf16_bits((rng.choice([-1.0, 1.0], shape) * rng.uniform(1.0, 2.0, shape)).astype(np.float32))
+    a["v_shared"], a["v_unshared"] = values(a["v_shared"].shape), values(a["v_unshared"].shape)
+    q, k, ko = (gr_synth.bf16_bits_to_f32(a[n]).copy() for n in ("q", "k_shared", "k_unshared"))
+    rows_of = []
+    for b in range(len(lens)):
+        toks = [5, 70, 129, 200, 250, lens[b] - 1, -1, -2]                   # -1 - t: own token t
+        for i, tok in enumerate(toks):
+            for kvh in range(Hkv):
+                w, head = 5 * i + b, kvh * (Hq // Hkv) + i % (Hq // Hkv)
+                if tok >= 0:
+                    at = (a["cu_seqlens"][b] + tok, kvh)
+                    k[at] = factor * q[b, w, head]
+                else:
+                    at = (b, w, -1 - tok, kvh)
+                    ko[at] = factor * q[b, w, head]
+                rows_of.append((b, w, head, tok, at))
+    a["k_shared"], a["k_unshared"] = gr_synth.f32_to_bf16_bits(k), gr_synth.f32_to_bf16_bits(ko)
+    gr.gr_diag_attn_plan(rows, segments)
+    try:
+        out, _ = run_attn(gr, a, float(np.float32(1 / np.sqrt(d))))
+    finally:
+        gr.gr_diag_attn_plan(0, 0)
+    for b, w, head, tok, at in rows_of:
+        want = gr_synth.bf16_bits_to_f32(a["v_shared" if tok >= 0 else "v_unshared"])[at]
+        np.testing.assert_array_equal(out[b, w, head], want, err_msg=f"request {b}, beam {w}, head {head}, token {tok}")
+
+
+@pytest.mark.parametrize("d,W", [(64, 16), (64, 40), (128, 40)])
+@pytest.mark.parametrize("uniform", [True, False])
+@pytest.mark.parametrize("factor", [3.0, 7.0, 12.0])
+def test_scores_that_jump_in_many_workgroups(gr, oracle_lib, d, W, uniform, factor):
+    """More than 256 workgroups of 128 rows: one set of four wavefronts, its requests of one length or found by rank.  Scores that jump by 34 to
+    50, 80 to 114 (the reference is raised after the tile, or the wavefront computes its columns again) or 138 bits and more (again)."""
+    B, H = 40, 8
+    lens = tuple(260 if uniform else 130 + 9 * (b % 16) for b in range(B))
+    a = rand_attn_case(1200 + d + W, B, W, H, H, d, 3, 2, lens)
+    q, k = gr_synth.bf16_bits_to_f32(a["q"]), gr_synth.bf16_bits_to_f32(a["k_shared"]).copy()
+    tri = []
+    for b in range(B):
+        w, head, tok = b % W, b % H, (70 + 3 * b) % lens[b]
+        k[a["cu_seqlens"][b] + tok, head] = factor * q[b, w, head]
+        tri += [(b, w, head), (b, (w + 1) % W, head), (b, w, (head + 1) % H), (b, W - 1, head)]
+    a["k_shared"] = gr_synth.f32_to_bf16_bits(k)
+    _check(gr, oracle_lib, a, float(np.float32(1 / np.sqrt(d))), np.array(tri, dtype=np.int32))

@@ -124,7 +124,7 @@ def test_fp8kv_rejects_bad_scales(gr):
 
 
 @pytest.mark.parametrize("d", [64, 128])
-@pytest.mark.parametrize("rows,factor", [(128, 3.0), (128, 7.0), (256, 7.0)])
+@pytest.mark.parametrize("rows,factor", [(128, 3.0), (128, 7.0), (256, 7.0), (128, 12.0), (256, 12.0)])
 def test_fp8kv_scores_that_jump_inside_the_prompt(gr, oracle_lib, d, rows, factor):
     """Keys far above everything before them: the reference is raised after the tile, or the wavefront computes its columns again."""
     lens, W, Hq, Hkv = (330, 460), 40, 8, 2
@@ -149,3 +149,49 @@ def test_fp8kv_many_workgroups_of_either_size(gr, oracle_lib, W):
     n = 300
     tri = np.stack([np.arange(n) % B, rng.integers(0, W, n), rng.integers(0, 32, n)], axis=1).astype(np.int32)
     _check(gr, oracle_lib, a, float(np.float32(1 / np.sqrt(128))), tri)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("uniform", [True, False])
+@pytest.mark.parametrize("factor", [3.0, 12.0])
+def test_fp8kv_scores_that_jump_in_many_workgroups(gr, oracle_lib, d, uniform, factor):
+    """More than 256 workgroups of 128 rows: one set of four wavefronts, its requests of one length or found by rank."""
+    B, W, H = 40, 20, 8
+    lens = tuple(260 if uniform else 130 + 9 * (b % 16) for b in range(B))
+    a = rand_attn_case(1300 + d, B, W, H, H, d, 3, 2, lens)
+    q, k = gr_synth.bf16_bits_to_f32(a["q"]), gr_synth.bf16_bits_to_f32(a["k_shared"]).copy()
+    tri = []
+    for b in range(B):
+        w, head, tok = b % W, b % H, (70 + 3 * b) % lens[b]
+        k[a["cu_seqlens"][b] + tok, head] = factor * q[b, w, head]
+        tri += [(b, w, head), (b, (w + 1) % W, head), (b, w, (head + 1) % H)]
+    a["k_shared"] = gr_synth.f32_to_bf16_bits(k)
+    _check(gr, oracle_lib, a, float(np.float32(1 / np.sqrt(d))), np.array(tri, dtype=np.int32))
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("rows", [128, 256])
+@pytest.mark.parametrize("factor", [4.0, 12.0])
+def test_fp8kv_a_token_that_is_nearly_all_of_the_sum(gr, d, rows, factor):
+    """The output is that token's V row: codes of values between 1 and 2, times a scale that is a power of two."""
+    lens, W, H = (330, 460), 20, 4
+    a = rand_attn_case(1400 + d + rows, len(lens), W, H, H, d, 3, 2, lens)
+    rng = np.random.default_rng(12)
+    v = (rng.choice([-1.0, 1.0], a["v_shared"].shape) * (1.0 + rng.integers(0, 8, a["v_shared"].shape) / 8.0)).astype(np.float32)
+    q, k = gr_synth.bf16_bits_to_f32(a["q"]), gr_synth.bf16_bits_to_f32(a["k_shared"]).copy()
+    rows_of = []
+    for b in range(len(lens)):
+        for i, tok in enumerate([5, 70, 129, 200, 250, lens[b] - 1]):
+            for head in range(H):
+                k[a["cu_seqlens"][b] + tok, head] = factor * q[b, 3 * i + b, head]
+                rows_of.append((b, 3 * i + b, head, a["cu_seqlens"][b] + tok))
+    codes, scale = _quantise(gr_synth.f32_to_bf16_bits(k))
+    gr.gr_diag_attn_plan(rows, 1)
+    try:
+        out, _ = gr.gr_beam_attn_fp8kv(bf16_to_dev(a["q"]), to_dev(codes), to_dev(gr_synth.f32_to_e4m3_bits(v)), float(scale), 0.25, to_dev(a["cu_seqlens"]),
+                                       bf16_to_dev(a["k_unshared"]), bf16_to_dev(a["v_unshared"]), 2, float(np.float32(1 / np.sqrt(d))), 460, 790)
+        out = out.float().cpu().numpy()
+    finally:
+        gr.gr_diag_attn_plan(0, 0)
+    for b, w, head, at in rows_of:
+        np.testing.assert_array_equal(out[b, w, head], 0.25 * v[at, head], err_msg=f"request {b}, beam {w}, head {head}")

@@ -165,7 +165,7 @@ def test_prefill_ragged_long_batch_sampled_rows(oracle_lib):
 
 
 @pytest.mark.parametrize("d,max_L", [(64, 330), (128, 330), (128, 2049)])      # blocks of 128, 128 and 256 query rows
-@pytest.mark.parametrize("factor", [3.0, 7.0])
+@pytest.mark.parametrize("factor", [3.0, 7.0, 12.0])
 def test_prefill_scores_that_jump_inside_the_prompt(oracle_lib, d, max_L, factor):
     """Keys far above everything before them, in a tile before and on a block's diagonal: the reference is raised after the tile, or
     the wavefront computes its columns again."""
@@ -210,3 +210,51 @@ def test_prefill_blocks_dealt_by_weight(oracle_lib, B, Hq, Hkv, d, L_min, L_max)
     T = int(c["cu"][-1])
     assert np.abs(out[:T] - ref.reshape(T, Hq, d)).max() <= 2e-2
     np.testing.assert_allclose(lse[:T], ref_lse.reshape(T, Hq), rtol=0, atol=2e-3)
+
+
+@pytest.mark.parametrize("d,max_L", [(64, 330), (128, 330), (128, 2049)])      # blocks of 128, 128 and 256 query rows
+@pytest.mark.parametrize("power", [-118, 110])
+def test_prefill_values_near_the_ends_of_the_range(d, max_L, power):
+    """V times a power of two gives the output times that power, also where a row's scores jump by 34 to 50 bits.  The bound: two roundings
+    to bf16, 2^-7 max|V|."""
+    import torch
+    import paper_2512_11529_amd as gr
+    gr.load_library()
+    c = _case(79 + d, (330, 200), 8, 2, d)
+    q, k, v = (gr_synth.bf16_bits_to_f32(c[n]).copy() for n in ("q", "k", "v"))
+    for row, head, tok in [(300, 1, 100), (329, 5, 328), (330 + 199, 0, 330 + 130)]:
+        k[tok, head // 4] = 3.0 * q[row, head]
+    c["k"] = gr_synth.f32_to_bf16_bits(k)
+    scale = float(np.float32(1 / np.sqrt(d)))
+
+    def run(values):
+        out = torch.empty(c["q"].shape, dtype=torch.bfloat16, device="cuda:0")
+        gr.gr_prefill_attn(bf16_to_dev(c["q"]), bf16_to_dev(c["k"]), bf16_to_dev(gr_synth.f32_to_bf16_bits(values)), to_dev(c["cu"]), scale, max_L, 530, out=out)
+        return out.float().cpu().numpy()
+
+    want, out = run(v), run(np.ldexp(v, power))
+    assert np.isfinite(out).all()
+    assert np.abs(np.ldexp(out, -power) - want).max() <= 2.0 ** -7 * float(np.abs(v).max())
+
+
+@pytest.mark.parametrize("d,max_L", [(64, 330), (128, 330), (128, 2049)])
+@pytest.mark.parametrize("factor", [3.0, 12.0])
+def test_prefill_a_token_that_is_nearly_all_of_the_sum(d, max_L, factor):
+    """A key 34 bits or more above all others of a row: the output is its V row, every bit of it (values between 1 and 2)."""
+    import torch
+    import paper_2512_11529_amd as gr
+    gr.load_library()
+    c = _case(83 + d, (330, 200), 8, 2, d)
+    rng = np.random.default_rng(13)
+    v = (rng.choice([-1.0, 1.0], c["v"].shape) * rng.uniform(1.0, 2.0, c["v"].shape)).astype(np.float32)
+    c["v"] = gr_synth.f32_to_bf16_bits(v)
+    q, k = gr_synth.bf16_bits_to_f32(c["q"]), gr_synth.bf16_bits_to_f32(c["k"]).copy()
+    rows_of = [(300, 1, 100), (329, 5, 328), (310, 6, 70), (200, 2, 5), (180, 3, 179), (160, 7, 140), (330 + 199, 0, 330 + 130), (330 + 150, 4, 330 + 149)]
+    for row, head, tok in rows_of:
+        k[tok, head // 4] = factor * q[row, head]
+    c["k"] = gr_synth.f32_to_bf16_bits(k)
+    out = torch.empty(c["q"].shape, dtype=torch.bfloat16, device="cuda:0")
+    gr.gr_prefill_attn(bf16_to_dev(c["q"]), bf16_to_dev(c["k"]), bf16_to_dev(c["v"]), to_dev(c["cu"]), float(np.float32(1 / np.sqrt(d))), max_L, 530, out=out)
+    out, v = out.float().cpu().numpy(), gr_synth.bf16_bits_to_f32(c["v"])
+    for row, head, tok in rows_of:
+        np.testing.assert_array_equal(out[row, head], v[tok, head // 4], err_msg=f"row {row}, head {head}")
