@@ -1752,16 +1752,22 @@ extern "C" gr_status gr_beam_select(const gr_select_params* p, void* workspace, 
   c.row_data = (float*)ws;
 
   c.row_threads = p->step == 0 ? 512 : 256;
-  // A workgroup that selects writes its request's scores while others may still look for live rows: not where these are the scores that came
-  // in (k_select, a launch behind all readers, writes them then).
-  const bool in_place = (uintptr_t)p->scores_out < (uintptr_t)(p->scores_in + rows) && (uintptr_t)p->scores_in < (uintptr_t)(p->scores_out + rows);
-  c.pick_b = p->V <= kBlockV && p->W <= kPickW && !in_place ? p->B : 0;
+  // A workgroup that reads scores and selects as well writes its request's outputs while others may still read theirs: not where an output
+  // lies on the incoming scores (k_select, a launch behind all readers, writes it then).  Levels 1 and 2 read a request's scores in its own
+  // workgroup only, so there the scores may be the ones that came in.
+  auto on_scores = [&](const void* out, size_t per_row) {
+    return out && (uintptr_t)out < (uintptr_t)(p->scores_in + rows) && (uintptr_t)p->scores_in < (uintptr_t)out + rows * per_row * 4;
+  };
+  const bool others_on = on_scores(p->parent_out, 1) || on_scores(p->token_out, 1) || on_scores(p->prefix_out, (size_t)p->depth) || on_scores(p->range_out, 2) ||
+                         on_scores(p->item_index_out, 1);
+  const bool scores_on = on_scores(p->scores_out, 1);
+  c.pick_b = p->V <= kBlockV && p->W <= kPickW && !others_on && !scores_on ? p->B : 0;
   const bool listed = p->mask && p->step >= 1 && !(p->flags & GR_SELECT_FORCE_DENSE);
   // One kernel instead of two where every wavefront of the selecting workgroup has at most one row, and that row one round of loads (longer ones
   // are drawn faster by more CUs).  us of a level with two kernels and with one: one request x 16 beams, V = 256, 8 children a row 10.3, 9.4, 250 children 13.7,
   // 13.0; V = 512, 500 children 14.1, 13.5; 256 x 16 12.9, 9.7 and 17.8, 14.6; 300 x 4 16.6, 15.6; 8 x 4 10.5, 8.5.  But two rows a wavefront
   // (32 beams) 10.5, 12.0, and two rounds (1000 children of V = 1024, 16 beams) 15.4, 15.9.
-  const bool gather = listed && p->W <= kGatherRows && p->V <= kGatherV;
+  const bool gather = listed && p->W <= kGatherRows && p->V <= kGatherV && !others_on && (!scores_on || p->scores_out == p->scores_in);
   if (listed && !gather)
     hipLaunchKernelGGL(k_rows_listed, dim3((unsigned)((rows + kDeal * kGatherWaves - 1) / (kDeal * kGatherWaves) * kDeal)), dim3(kGatherWaves * 64), 0, stream, c);
   else if (!listed && p->step == 0)

@@ -360,3 +360,47 @@ def test_requests_that_one_workgroup_gathers(gr, oracle_lib, W, V, counts):  # n
         torch.cuda.synchronize()
         assert_select_equal({k: v.cpu().numpy() for k, v in out.items()}, want, f"step {step}, in place")
         sc, pf, rg = want["scores"], want["prefix"], want["range"]
+
+
+@pytest.mark.parametrize("step", [0, 1, 2])
+@pytest.mark.parametrize("where", ["scores one request further", "scores one request before", "prefix", "range"])
+def test_outputs_that_lie_on_the_incoming_scores(gr, oracle_lib, step, where):  # noqa: F811
+    """The incoming scores are read before any output is written, also where an output begins elsewhere in them: more requests than run at a
+    time, so that first ones would be written while later ones have not been read."""
+    rng = np.random.default_rng(step)
+    B, W, V = 3000, 6, 64
+    second = _children(rng, V, [1 + i % 5 for i in range(V)])
+    items = np.array([(t1, int(t2), t3) for t1, row in enumerate(second) for t2 in row for t3 in (3, 40)], dtype=np.int32)
+    mask = gr.gr_item_mask_build(to_dev(items), V)
+    logits = (2.0 * rng.standard_normal((B, W, V))).astype(np.float32)
+    sc = np.sort(-3.0 * rng.random((B, W)), axis=1)[:, ::-1].astype(np.float32).copy()
+    pf, rg = np.full((B, W, 3), -1, np.int32), np.zeros((B, W, 2), np.int32)
+    if step == 0:
+        sc[:, 1:] = -np.inf
+    else:
+        pf[:, :, 0] = rng.integers(0, V, (B, W))
+        if step == 1:
+            rg[:, :, 0], rg[:, :, 1] = np.searchsorted(items[:, 0], pf[:, :, 0]), np.searchsorted(items[:, 0], pf[:, :, 0] + 1)
+        else:
+            pair = rng.integers(0, len(items) // 2, (B, W))
+            pf[:, :, 0], pf[:, :, 1] = items[2 * pair, 0], items[2 * pair, 1]
+            rg[:, :, 0], rg[:, :, 1] = 2 * pair, 2 * pair + 2
+    want = oracle_lib.beam_select(items, logits, sc, pf, step)
+    arena = torch.full((8 * B * W,), -7, dtype=torch.int32, device="cuda:0")
+    at = {"scores one request further": W, "scores one request before": -W, "prefix": -(B * W) // 2 // W * W, "range": -W}[where]
+    scores = arena[4 * B * W:5 * B * W].view(torch.float32).view(B, W)
+    scores.copy_(to_dev(sc))
+    i32 = lambda *shape: torch.empty(shape, dtype=torch.int32, device="cuda:0")
+    out = {"parent": i32(B, W), "token": i32(B, W), "scores": torch.empty((B, W), dtype=torch.float32, device="cuda:0"), "prefix": i32(B, W, 3), "range": i32(B, W, 2),
+           "item_index": i32(B, W)}
+    lies = lambda *shape: arena[4 * B * W + at:4 * B * W + at + int(np.prod(shape))].view(*shape)
+    if where == "prefix":
+        out["prefix"] = lies(B, W, 3)
+    elif where == "range":
+        out["range"] = lies(B, W, 2)
+    else:
+        out["scores"] = lies(B, W).view(torch.float32)
+    d_logits, d_pf, d_rg = to_dev(logits), to_dev(pf), to_dev(rg)
+    gr.gr_beam_select(mask, d_logits, scores, d_pf, d_rg, step, out=out)
+    torch.cuda.synchronize()
+    assert_select_equal({k: v.cpu().numpy() for k, v in out.items()}, want, f"step {step}")
