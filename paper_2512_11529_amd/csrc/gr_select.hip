@@ -50,7 +50,6 @@ enum { ROW_DEAD = 0, ROW_DENSE = 1, ROW_SPARSE = 2, ROW_DONE = 3 };      // low 
 struct SelCtx {
   int B, W, V, depth, step;
   int row_threads;           // threads that stream a row: thread t holds tokens 4 (t + row_threads i) .. + 3 for all i
-  int pick_b;                // level 0: requests whose only live row's workgroup may select as well (all of them or none)
   int unit_shift;            // log2 of the units (float4 of logits) behind a key of a streamed row: 8 per block of kBlockV logits, to a power of two
   const char* blob;          // mask blob or nullptr
   const float* logits;
@@ -270,7 +269,9 @@ __device__ __forceinline__ void block_max_min(float& mx, float& mn, float2* s_re
 // exclusive prefix of v over the workgroup's threads (thread order), and the total
 template <int NWAVES>
 __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* total, uint32_t* s_red, int& par) {
-  const int lane = gr_lane(), wave = threadIdx.x >> 6;
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));                              // (k_rows: the comparisons below, made ahead of its loop over rows, took up its scalar registers)
+  const int lane = gr_lane(), wave = tid >> 6;
   const uint32_t incl = wave_incl_scan(v);
   uint32_t* slot = s_red + (par++ & 1) * NWAVES;
   if (lane == 63) slot[wave] = incl;
@@ -509,13 +510,12 @@ __device__ __forceinline__ bool row_pick(const SelCtx& c, const MaskView& mv, Pi
 // (all wave-uniform).  Every wavefront works relative to its own maximum and the workgroup meets once: the first wavefront then joins
 // the (max, sum) pairs and writes the row's results, while the others are free for the next row (or gone).
 //
-// PICK (level 0): where the row is its request's `first` and `rivals`, the scores of the request's other rows, are all dead, the workgroup, which
+// PICK (level 0): the row is its request's first.  Where `rivals`, the scores of the request's other rows, are all dead, the workgroup, which
 // holds all of the request's candidates in registers, selects the W best too.  k_select then only finds that it is done: a level-0
-// step of 8 x 128 beams over 8192 tokens 19.4 -> 14.0 us, of 128 x 256 22.5 -> 15.7, of one x 16 over 256 13.9 -> 10.5; where all rows
-// are live nothing is gained (8 x 128 25.5 -> 24.2, 32 x 256 90.8 -> 94.4).
+// step of 8 x 128 beams over 8192 tokens 18.0 -> 12.9 us, of 128 x 256 18.8 -> 13.6, of one x 16 over 256 13.4 -> 10.1.
 template <int NT, bool PICK>
 __device__ __forceinline__ void row_dense(const SelCtx& c, const MaskView& mv, RowLds<NT>& L, int row, float s_in, int t1, int start, int n_list, int set,
-                                          PickLds* P = nullptr, bool first = false, float2 rivals = {0.f, 0.f}) {
+                                          PickLds* P = nullptr, float2 rivals = {0.f, 0.f}) {
   constexpr int NV4 = kBlockV / 4 / NT, NWV = NT / 64;        // float4 per thread; wavefronts
   const int tid = threadIdx.x, wave = tid >> 6, V = c.V;
   const float* x = c.logits + (size_t)row * V;
@@ -665,7 +665,7 @@ __device__ __forceinline__ void row_dense(const SelCtx& c, const MaskView& mv, R
       if (!b1) key[2 * b2 + b0] = r;
     }
   }
-  if (PICK && first) {
+  if (PICK) {
     float low = INFINITY;
 #pragma unroll
     for (int i = 0; i < NV4; i++) low = fminf(low, lmax[i] > -INFINITY ? lmax[i] : INFINITY);
@@ -678,7 +678,7 @@ __device__ __forceinline__ void row_dense(const SelCtx& c, const MaskView& mv, R
   __syncthreads();
   const int lane = tid & 63;
   bool pick = false;
-  if (PICK && first) pick = !__any(lane < NWV && P->others[set][lane & (NWV - 1)]);       // (the same for all wavefronts)
+  if (PICK) pick = !__any(lane < NWV && P->others[set][lane & (NWV - 1)]);       // (the same for all wavefronts)
   if (wave != 0 && !pick) return;
   m = (lane < NWV) ? L.m[set][lane] : -INFINITY;
   S = (lane < NWV) ? L.s[set][lane] : 0.0;
@@ -923,11 +923,15 @@ __device__ __forceinline__ void gather_rows(const SelCtx& c, const MaskView& mv,
 //   workgroup asks for the scores of all its other rows at once and turns to the live ones (8192 workgroups that only find a dead row
 //   cost 16 us to dispatch; the live rows of 8 requests spread over 1021 workgroups 3 us more than at the front of 512, which is
 //   two to a CU).  With so few rows at work a row is dealt to twice as many threads.
+//   PICK: first rows may select as well.  They have a loop of their own: what the selection keeps in registers slows other rows down.  us where
+//   all rows are live, with one loop, with two and in the kernel without PICK: 32 x 256 beams over 8192 tokens 79.6, 77.2, 76.5; 8 x 128
+//   21.9, 21.6, 21.3; 64 x 128 over 1000 63.4, 60.6, 58.5 (59.0 before there was a selection here, the only one of these that lost by it).
 constexpr size_t kStrideGrid = 512;
-template <bool STRIDE, int NT>
+template <bool STRIDE, int NT, bool PICK>
 __global__ void __launch_bounds__(NT, STRIDE ? 4 : 6) k_rows(SelCtx c) {
+  static_assert(STRIDE || !PICK, "requests are selected from at level 0 only");
   __shared__ RowLds<NT> L;
-  __shared__ std::conditional_t<STRIDE, PickLds, char> P;
+  __shared__ std::conditional_t<PICK, PickLds, char> P;
   const int tid = threadIdx.x, lane = tid & 63, rows = c.B * c.W;
   MaskView mv;
   mv.ok = false;
@@ -946,6 +950,7 @@ __global__ void __launch_bounds__(NT, STRIDE ? 4 : 6) k_rows(SelCtx c) {
     __syncthreads();
     row_dense<NT, false>(c, mv, L, row, s_in, t1, start, n, 0);
   } else {
+    c.step = 0;                                              // (no other level comes here: what those need of row_dense is left out)
     fill_exp_tab(L.tab, NT);
     if (c.blob) mv = mask_view(c.blob, c.V, c.depth);
     __syncthreads();
@@ -961,14 +966,23 @@ __global__ void __launch_bounds__(NT, STRIDE ? 4 : 6) k_rows(SelCtx c) {
       const int r = at < rows ? row_at(at) : 0;
       const float s = at < rows ? c.scores_in[r] : -INFINITY;
       if (tid < 64 && at < rows && !(s > -INFINITY)) mark_dead(c, r);
-      for (uint64_t live = __ballot(s > -INFINITY); live; live &= live - 1) {
+      uint64_t live = __ballot(s > -INFINITY);
+      if constexpr (PICK) {
+        uint64_t firsts = live & __ballot(at < c.B);
+        live &= ~firsts;
+        for (; firsts; firsts &= firsts - 1) {
+          const int l = __ffsll((unsigned long long)firsts) - 1, row = __builtin_amdgcn_readlane(r, l);
+          float2 rivals = {-INFINITY, -INFINITY};            // (asked for here, looked at when the row's logits have been)
+          static_assert(kPickW <= 2 * NT, "two other rows to a thread");
+          if (1 + tid < c.W) rivals.x = c.scores_in[row + 1 + tid];
+          if (1 + tid + NT < c.W) rivals.y = c.scores_in[row + 1 + tid + NT];
+          row_dense<NT, true>(c, mv, L, row, lane_f32(s, l), -1, 0, 0, set, &P, rivals);
+          set ^= 1;
+        }
+      }
+      for (; live; live &= live - 1) {
         const int l = __ffsll((unsigned long long)live) - 1, row = __builtin_amdgcn_readlane(r, l);
-        const bool first = base + (int64_t)l * gridDim.x < c.pick_b;
-        float2 rivals = {-INFINITY, -INFINITY};              // (asked for here, looked at when the row's logits have been)
-        static_assert(kPickW <= 2 * NT, "two other rows to a thread");
-        if (first && 1 + tid < c.W) rivals.x = c.scores_in[row + 1 + tid];
-        if (first && 1 + tid + NT < c.W) rivals.y = c.scores_in[row + 1 + tid + NT];
-        row_dense<NT, true>(c, mv, L, row, lane_f32(s, l), -1, 0, 0, set, &P, first, rivals);
+        row_dense<NT, false>(c, mv, L, row, lane_f32(s, l), -1, 0, 0, set);
         set ^= 1;
       }
     }
@@ -1761,7 +1775,7 @@ extern "C" gr_status gr_beam_select(const gr_select_params* p, void* workspace, 
   const bool others_on = on_scores(p->parent_out, 1) || on_scores(p->token_out, 1) || on_scores(p->prefix_out, (size_t)p->depth) || on_scores(p->range_out, 2) ||
                          on_scores(p->item_index_out, 1);
   const bool scores_on = on_scores(p->scores_out, 1);
-  c.pick_b = p->V <= kBlockV && p->W <= kPickW && !others_on && !scores_on ? p->B : 0;
+  const bool pick = p->step == 0 && p->V <= kBlockV && p->W <= kPickW && !others_on && !scores_on;
   const bool listed = p->mask && p->step >= 1 && !(p->flags & GR_SELECT_FORCE_DENSE);
   // One kernel instead of two where every wavefront of the selecting workgroup has at most one row, and that row one round of loads (longer ones
   // are drawn faster by more CUs).  us of a level with two kernels and with one: one request x 16 beams, V = 256, 8 children a row 10.3, 9.4, 250 children 13.7,
@@ -1770,10 +1784,12 @@ extern "C" gr_status gr_beam_select(const gr_select_params* p, void* workspace, 
   const bool gather = listed && p->W <= kGatherRows && p->V <= kGatherV && !others_on && (!scores_on || p->scores_out == p->scores_in);
   if (listed && !gather)
     hipLaunchKernelGGL(k_rows_listed, dim3((unsigned)((rows + kDeal * kGatherWaves - 1) / (kDeal * kGatherWaves) * kDeal)), dim3(kGatherWaves * 64), 0, stream, c);
-  else if (!listed && p->step == 0)
-    hipLaunchKernelGGL((k_rows<true, 512>), dim3((unsigned)(rows < kStrideGrid ? rows : kStrideGrid)), dim3(512), 0, stream, c);
+  else if (pick)
+    hipLaunchKernelGGL((k_rows<true, 512, true>), dim3((unsigned)(rows < kStrideGrid ? rows : kStrideGrid)), dim3(512), 0, stream, c);
+  else if (p->step == 0)
+    hipLaunchKernelGGL((k_rows<true, 512, false>), dim3((unsigned)(rows < kStrideGrid ? rows : kStrideGrid)), dim3(512), 0, stream, c);
   else if (!listed)
-    hipLaunchKernelGGL((k_rows<false, 256>), dim3((unsigned)rows), dim3(256), 0, stream, c);
+    hipLaunchKernelGGL((k_rows<false, 256, false>), dim3((unsigned)rows), dim3(256), 0, stream, c);
   const size_t lds = kSelLdsBytes - (gather ? (size_t)(kMaxW - kGatherRows) * 16 : 0);      // (the row tables are that much shorter)
 #define GR_LAUNCH_SELECT(...)                                                                                         \
   do {                                                                                                                \
