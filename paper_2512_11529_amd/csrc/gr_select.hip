@@ -482,17 +482,13 @@ __device__ __forceinline__ bool row_pick(const SelCtx& c, const MaskView& mv, Pi
   for (int j = tid; j < late->W; j += NT) {
     const size_t o = (size_t)row + j;
     int32_t* po = late->prefix_out + o * late->depth;
-    int token = -1, r_lo = 0, r_hi = 0;
-    float score = -INFINITY;
-    if (j < m) {
-      const uint64_t key = P.list[j];
-      token = (int)(0xffffffffu - (uint32_t)key);
-      score = gr_ordkey_inv((uint32_t)(key >> 32));
-      if (late->blob) { r_lo = mv.off1[token]; r_hi = mv.off1[token + 1]; }
-    }
-    late->parent_out[o] = j < m ? 0 : -1;
+    const uint64_t key = P.list[j];                          // (at least W reached the threshold)
+    const int token = (int)(0xffffffffu - (uint32_t)key);
+    int r_lo = 0, r_hi = 0;
+    if (late->blob) { r_lo = mv.off1[token]; r_hi = mv.off1[token + 1]; }
+    late->parent_out[o] = 0;
     late->token_out[o] = token;
-    late->scores_out[o] = score;
+    late->scores_out[o] = gr_ordkey_inv((uint32_t)(key >> 32));
     po[0] = token;
     for (int k = 1; k < late->depth; k++) po[k] = -1;
     late->range_out[2 * o] = r_lo;
