@@ -888,7 +888,7 @@ __global__ void __launch_bounds__(kGatherWaves * 64, 8) k_rows_listed(SelCtx c) 
 // All rows of request b, a row to a wavefront, for the workgroup that selects too; a row is too short to be shared out.
 constexpr int kGatherRows = kSelThreads / 64, kGatherV = kPart;
 __device__ __forceinline__ void gather_rows(const SelCtx& c, const MaskView& mv, int b, char* lds) {
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), row = b * c.W + wave;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), row = b * c.W + wave;       // (what row `wave` of the request leaves goes to places of that number)
   double* tab = (double*)lds;
   float* keys = (float*)(tab + kExpTab) + wave * kLines;
   float s_in = -INFINITY;
@@ -903,14 +903,14 @@ __device__ __forceinline__ void gather_rows(const SelCtx& c, const MaskView& mv,
   n = __builtin_amdgcn_readfirstlane(n);
   start = __builtin_amdgcn_readfirstlane(start);
   if (!(s_in > -INFINITY) || n == 0) {
-    if ((threadIdx.x & 63) == 0) mark_dead(c, row);
+    if ((threadIdx.x & 63) == 0) mark_dead(c, wave);
     return;
   }
   GatherPart g;
   const ExpK ek = exp_consts();
   gather_part(g, c.logits + (size_t)row * c.V, child_list(c, mv) + start, n, 0, kPart, tab, ek, keys);
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  gather_done(c, g, row, s_in, start, n, keys);
+  gather_done(c, g, wave, s_in, start, n, keys);
 }
 
 // Rows that are streamed, dealt to workgroups
@@ -921,7 +921,7 @@ __device__ __forceinline__ void gather_rows(const SelCtx& c, const MaskView& mv,
 //   two to a CU).  With so few rows at work a row is dealt to twice as many threads.
 //   PICK: first rows may select as well.  They have a loop of their own: what the selection keeps in registers slows other rows down.  us where
 //   all rows are live, with one loop, with two and in the kernel without PICK: 32 x 256 beams over 8192 tokens 79.6, 77.2, 76.5; 8 x 128
-//   21.9, 21.6, 21.3; 64 x 128 over 1000 63.4, 60.6, 58.5 (59.0 before there was a selection here, the only one of these that lost by it).
+//   21.9, 21.6, 21.3; 64 x 128 over 1000 63.4, 60.0, 58.5 (59.0 before there was a selection here, the only one of these that lost by it).
 constexpr size_t kStrideGrid = 512;
 template <bool STRIDE, int NT, bool PICK>
 __global__ void __launch_bounds__(NT, STRIDE ? 4 : 6) k_rows(SelCtx c) {
@@ -992,16 +992,16 @@ __global__ void __launch_bounds__(NT, STRIDE ? 4 : 6) k_rows(SelCtx c) {
 // sorted, so both order the candidates of a row as its tokens do).
 //
 // Visit every finite candidate of request b.  f(score, w * V + place, pred) is called wave-convergently
-// (pred = this lane holds a candidate).  Rows given by bit masks are strided by the whole
+// (pred = this lane holds a candidate); left0 = the place of what the request's first row left.  Rows given by bit masks are strided by the whole
 // workgroup; rows given by child lists are taken one per wavefront.
 template <bool LISTED, class F>
-__device__ __forceinline__ void for_each_candidate(const SelCtx& c, const MaskView& mv, int b, F&& f) {
+__device__ __forceinline__ void for_each_candidate(const SelCtx& c, const MaskView& mv, int b, size_t left0, F&& f) {
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, nw = blockDim.x >> 6;
   if (!LISTED && (!c.blob || c.step == 0)) {
     for (int w = 0; w < c.W; w++) {
       const int row = b * c.W + w;
-      if (c.row_info[row] == ROW_DEAD) continue;
-      const float bias = c.row_bias[row];
+      if (c.row_info[left0 + w] == ROW_DEAD) continue;
+      const float bias = c.row_bias[left0 + w];
       const float* x = c.logits + (size_t)row * c.V;
       const uint32_t flat0 = (uint32_t)w * (uint32_t)c.V;
       for (int v0 = 0; v0 < c.V; v0 += blockDim.x) {
@@ -1014,8 +1014,8 @@ __device__ __forceinline__ void for_each_candidate(const SelCtx& c, const MaskVi
   } else {
     for (int w = wave; w < c.W; w += nw) {
       const int row = b * c.W + w;
-      if (c.row_info[row] == ROW_DEAD) continue;
-      const float bias = c.row_bias[row];
+      if (c.row_info[left0 + w] == ROW_DEAD) continue;
+      const float bias = c.row_bias[left0 + w];
       const float* x = c.logits + (size_t)row * c.V;
       const uint32_t flat0 = (uint32_t)w * (uint32_t)c.V;
       int start, n;
@@ -1034,7 +1034,7 @@ __device__ __forceinline__ void for_each_candidate(const SelCtx& c, const MaskVi
 // Exact MSB radix select of the W best composite keys over ALL candidates (slow, always correct).
 // Leaves the survivors in s_list and returns their number.
 template <bool LISTED>
-__device__ int radix_select_all(const SelCtx& c, const MaskView& mv, int b, uint64_t* s_list, uint32_t* s_hist) {
+__device__ int radix_select_all(const SelCtx& c, const MaskView& mv, int b, size_t left0, uint64_t* s_list, uint32_t* s_hist) {
   __shared__ uint64_t s_prefix;
   __shared__ uint32_t s_need, s_bin, s_cnt;
   __shared__ int s_all;
@@ -1049,7 +1049,7 @@ __device__ int radix_select_all(const SelCtx& c, const MaskView& mv, int b, uint
     const int nbins = 1 << width;
     for (int i = tid; i < nbins; i += kSelThreads) s_hist[i] = 0;
     __syncthreads();
-    for_each_candidate<LISTED>(c, mv, b, [&](float score, uint32_t flat, bool pred) {
+    for_each_candidate<LISTED>(c, mv, b, left0, [&](float score, uint32_t flat, bool pred) {
       const uint64_t k = composite(score, flat);
       const bool in = pred && (pass == 0 || (k >> shift) == prefix);
       const uint32_t dgt = (uint32_t)(k >> lo_shift) & (uint32_t)(nbins - 1);
@@ -1102,7 +1102,7 @@ __device__ int radix_select_all(const SelCtx& c, const MaskView& mv, int b, uint
   }
   if (tid == 0) s_cnt = 0;
   __syncthreads();
-  for_each_candidate<LISTED>(c, mv, b, [&](float score, uint32_t flat, bool pred) {
+  for_each_candidate<LISTED>(c, mv, b, left0, [&](float score, uint32_t flat, bool pred) {
     const uint64_t k = composite(score, flat);
     if (pred && (take_all || (k >> shift) >= prefix)) {
       const uint32_t idx = atomicAdd(&s_cnt, 1u);
@@ -1148,23 +1148,19 @@ __global__ void __launch_bounds__(kSelThreads) k_select(SelCtx c) {
   MaskView mv;
   if (c.blob) mv = mask_view(c.blob, c.V, c.depth);
   if constexpr (GATHER) {
-    // what the rows leave stays in LDS: the places of this request's rows in the workspace lie there
+    // what the rows leave stays in LDS, which takes the workspace's place
     __shared__ __attribute__((aligned(16))) float s_data[kGatherRows * kRowFloats], s_groups[kGatherRows * kGroups], s_bias[kGatherRows];
     __shared__ int32_t s_info[kGatherRows], s_first[kGatherRows];
-    const uintptr_t row0 = (uintptr_t)b * c.W;
-    c.row_data = (float*)((uintptr_t)s_data - row0 * kRowFloats * 4);
-    c.row_group = (float*)((uintptr_t)s_groups - row0 * kGroups * 4);
-    c.row_bias = (float*)((uintptr_t)s_bias - row0 * 4);
-    c.row_info = (int32_t*)((uintptr_t)s_info - row0 * 4);
-    c.row_start = (int32_t*)((uintptr_t)s_first - row0 * 4);
+    c.row_data = s_data; c.row_group = s_groups; c.row_bias = s_bias; c.row_info = s_info; c.row_start = s_first;
     gather_rows(c, mv, b, smem);
     __syncthreads();                                         // (publishes the rows, and gives the rest of the LDS back)
   }
 
   // ---- the groups' best scores that k_rows left (two by two for more than 1024 beams)
-  const float* data = c.row_data + (size_t)b * c.W * kRowFloats;
-  const float4* group4 = (const float4*)(c.row_group + (size_t)b * c.W * kGroups);
-  const int32_t* info_b = c.row_info + (size_t)b * c.W;
+  const size_t left0 = GATHER ? 0 : (size_t)b * c.W;         // where what they left of the request's first row lies
+  const float* data = c.row_data + left0 * kRowFloats;
+  const float4* group4 = (const float4*)(c.row_group + left0 * kGroups);
+  const int32_t* info_b = c.row_info + left0;
   const int gsh = c.W * kGroups <= kGroupCap ? 4 : 3;        // log2 of the groups per row
   const int ngroups = c.W << gsh;
   float hi = -INFINITY, lo = INFINITY;                       // best and worst group
@@ -1173,9 +1169,9 @@ __global__ void __launch_bounds__(kSelThreads) k_select(SelCtx c) {
   auto row_of = [&](int w) {
     const size_t row = (size_t)b * c.W + w;
     Row r;
-    r.info = c.row_info[row]; r.bias = c.row_bias[row];
+    r.info = c.row_info[left0 + w]; r.bias = c.row_bias[left0 + w];
     r.a = 0;
-    if (LISTED) r.a = c.row_start[row];
+    if (LISTED) r.a = c.row_start[left0 + w];
     else if (c.blob && c.step == 1) r.a = c.prefix_in[row * c.depth];
     else if (c.blob && c.step == 2) r.a = c.range_in[2 * row];
     return r;
@@ -1627,7 +1623,7 @@ __global__ void __launch_bounds__(kSelThreads) k_select(SelCtx c) {
     }
     if (__builtin_expect(fallback, 0)) {
       __syncthreads();
-      n = radix_select_all<LISTED>(c, mv, b, s_list, s_hist);
+      n = radix_select_all<LISTED>(c, mv, b, left0, s_list, s_hist);
       int n2 = 1;
       while (n2 < n) n2 <<= 1;
       for (int i = n + tid; i < n2; i += kSelThreads) s_list[i] = 0;   // 0 sorts after every real key
