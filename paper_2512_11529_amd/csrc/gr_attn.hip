@@ -1385,8 +1385,8 @@ extern "C" gr_status gr_prefill_attn(const gr_prefill_params* p, void* stream_) 
   c.out = (uint16_t*)p->out; c.lse = p->lse_out;
   c.part_o = nullptr; c.part_ml = nullptr; c.order = nullptr; c.slot = nullptr;
   const int64_t groups_padded = ((int64_t)c.n_groups + 7) / 8 * 8;
-  int64_t grid = groups_padded * c.MB;
-  // Row blocks dealt heaviest first over all pairs of an XCD: the blocks that prompts shorter than the longest do not have are not dealt
+  const int64_t grid = groups_padded * c.MB;
+  // Row blocks dealt heaviest first over all pairs of an XCD: the blocks that prompts shorter than the longest do not have come last
   // (pair by pair they come first, and hold a place while they find that out), and the call ends with light blocks.  Against that stand
   // 0.4 us at the start of every block and K/V that more pairs share the L2 at a time, so: where not all blocks have a place at once;
   // for head size 64 always, for 128 (blocks of 128 rows) with 4 to 8 pairs to an XCD, or up to 16 of different lengths whose K/V take two thirds of
@@ -1398,10 +1398,6 @@ extern "C" gr_status gr_prefill_attn(const gr_prefill_params* p, void* stream_) 
   const bool in_l2 = pairs_per_xcd <= 16 && pairs_per_xcd >= 4 && p->total_L * 5 < (int64_t)p->B * p->max_L * 4 && kv_per_xcd <= ((int64_t)4 << 20) * 2 / 3;
   const bool by_weight = groups_padded <= 512 && grid > 512 && (p->d == 64 || (mwg == 128 && (few_pairs || in_l2)));
   c.rcp_hkv = 1.0f / (float)p->Hkv * 1.00001f;
-  if (by_weight && p->Hkv % 8 == 0) {                      // (every XCD has Hkv / 8 heads of all requests)
-    const int64_t most = (int64_t)p->Hkv * (p->total_L * g / mwg + p->B);
-    if (most < grid) grid = most;
-  }
   if (grid >= ((int64_t)1 << 31)) return GR_ERR_UNSUPPORTED;
   const size_t lds = attn_lds_bytes(p->d, mwg, 1);
   const unsigned threads = 2 * mwg;

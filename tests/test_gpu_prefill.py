@@ -258,3 +258,16 @@ def test_prefill_a_token_that_is_nearly_all_of_the_sum(d, max_L, factor):
     out, v = out.float().cpu().numpy(), gr_synth.bf16_bits_to_f32(c["v"])
     for row, head, tok in rows_of:
         np.testing.assert_array_equal(out[row, head], v[tok, head // 4], err_msg=f"row {row}, head {head}")
+
+
+def test_prefill_rows_do_not_depend_on_total_L(oracle_lib):
+    """total_L only chooses a plan: a number that is too small leaves no row out, also where blocks are dealt by weight."""
+    import torch
+    import paper_2512_11529_amd as gr
+    gr.load_library()
+    c = _case(91, (290, 200, 250, 280, 210, 290, 260, 230), 32, 8, 128)
+    scale = float(np.float32(1 / np.sqrt(128)))
+    want, _ = _run(gr, c, scale)
+    out = torch.full(c["q"].shape, 7.0, dtype=torch.bfloat16, device="cuda:0")
+    gr.gr_prefill_attn(bf16_to_dev(c["q"]), bf16_to_dev(c["k"]), bf16_to_dev(c["v"]), to_dev(c["cu"]), scale, 290, 300, out=out)
+    np.testing.assert_array_equal(out.float().cpu().numpy(), want)
