@@ -1388,15 +1388,17 @@ extern "C" gr_status gr_prefill_attn(const gr_prefill_params* p, void* stream_) 
   const int64_t grid = groups_padded * c.MB;
   // Row blocks dealt heaviest first over all pairs of an XCD: the blocks that prompts shorter than the longest do not have come last
   // (pair by pair they come first, and hold a place while they find that out), and the call ends with light blocks.  Against that stand
-  // 0.4 us at the start of every block and K/V that more pairs share the L2 at a time, so: where not all blocks have a place at once;
-  // for head size 64 always, for 128 (blocks of 128 rows) with 4 to 8 pairs to an XCD, or up to 16 of different lengths whose K/V take two thirds of
-  // an XCD's 4 MiB.  us pair by pair, by weight: 16 prompts of 60-700 tokens, 32 query and 8 KV heads of 128, 40.6, 38.7; 8 of 200-2000 135, 130; 4 of
-  // 300-1500 29.0, 27.0; 24 of 60-700 with 16 and 4 heads 42.9, 39.6; 8 heads of 64: 12 of 100-1000 19.3, 15.3, 16 of 1000-4000 149, 130, 64 x 1000 119, 114.
-  // But with 8 KV heads of 128 32 of 100-600 73.8, 79.1 and 64 x 1000 647, 797.
-  const int64_t pairs_per_xcd = groups_padded / 8, kv_per_xcd = p->total_L * p->Hkv * p->d * 4 / 8;
-  const bool few_pairs = pairs_per_xcd >= 4 && pairs_per_xcd <= 8;
-  const bool in_l2 = pairs_per_xcd <= 16 && pairs_per_xcd >= 4 && p->total_L * 5 < (int64_t)p->B * p->max_L * 4 && kv_per_xcd <= ((int64_t)4 << 20) * 2 / 3;
-  const bool by_weight = groups_padded <= 512 && grid > 512 && (p->d == 64 || (mwg == 128 && (few_pairs || in_l2)));
+  // 0.4 us at the start of every block and K/V of more pairs that share the L2 at a time.  So: where not all blocks have a place at once, and an XCD's
+  // pairs times the rows of a token in each are at most 48 (head size 128) or 128 (64), or more, up to 64 with head size 128, where the
+  // prompts are on average shorter than two thirds of the longest.  Time by weight over pair by pair, of 1300 shapes of 300 to 5000 tokens,
+  // mean: head size 128 with up to 48 0.96, 64 uneven 0.98 and even 1.03, 80 and more 1.04; head size 64 with up to 128 0.88, with more
+  // uneven 0.96 and even 1.01.  us pair by pair, by weight: 16 prompts of 60-700 tokens, 32 query and 8 KV heads of 128, 44.7, 41.6; 8 of 200-2000 136.7,
+  // 133; 10 of 300-1000 57.5, 55.8; 40 of 100-900, 8 and 2 heads, 47.2, 44.1; 8 heads of 64: 12 of 100-1000 18.9, 15.1, 16 of 1000-4000 153, 140.
+  // But 32 of 100-600, 32 and 8 heads of 128, 69, 78; 16 x 600 70, 74; 64 of 100-600, 16 and 2 heads, 68, 71.
+  const int64_t rows_of_token = groups_padded / 8 * g;
+  const bool uneven = p->total_L * 3 < (int64_t)p->B * p->max_L * 2;
+  const bool by_weight = groups_padded <= 512 && grid > 512 && mwg == 128 &&
+                         (rows_of_token <= (p->d == 64 ? 128 : 48) || (uneven && (p->d == 64 || rows_of_token <= 64)));
   c.rcp_hkv = 1.0f / (float)p->Hkv * 1.00001f;
   if (grid >= ((int64_t)1 << 31)) return GR_ERR_UNSUPPORTED;
   const size_t lds = attn_lds_bytes(p->d, mwg, 1);

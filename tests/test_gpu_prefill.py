@@ -190,10 +190,18 @@ def test_prefill_scores_that_jump_inside_the_prompt(oracle_lib, d, max_L, factor
     (64, 8, 8, 64, 100, 256),       # the most (request, KV head) pairs that are dealt by weight: 64 to an XCD
     (65, 8, 8, 64, 100, 256),       # one request more: pair by pair
     (8, 32, 8, 128, 1, 290),        # 8 pairs to an XCD
-    (16, 32, 8, 128, 1, 200),       # 16 of different lengths
+    (16, 32, 8, 128, 1, 200),       # 64 rows of a token, prompts of unlike length
     (16, 6, 3, 128, 300, 700),      # KV heads that do not divide the XCDs evenly
     (17, 16, 2, 128, 20, 220),      # 34 pairs: some XCDs have one more
-    (8, 32, 8, 128, 256, 256),      # one length, every block full
+    (8, 32, 8, 128, 256, 256),      # one length, every block full, all with a place at once (pair by pair)
+    (8, 32, 8, 128, 288, 288),      # the same with more blocks
+    (12, 32, 8, 128, 150, 200),     # 48 rows of a token to an XCD, the most of prompts of like length
+    (13, 32, 8, 128, 150, 200),     # 52 of prompts of like length: pair by pair
+    (13, 32, 8, 128, 1, 200),       # 52, and prompts of unlike length
+    (17, 32, 8, 128, 1, 200),       # 68: pair by pair
+    (32, 32, 8, 64, 100, 128),      # head size 64, 128 rows of a token, like lengths
+    (33, 32, 8, 64, 100, 128),      # 132: pair by pair
+    (33, 32, 8, 64, 0, 128),        # unlike lengths
 ])
 def test_prefill_blocks_dealt_by_weight(oracle_lib, B, Hq, Hkv, d, L_min, L_max):
     """More row blocks than have a place at once, dealt heaviest first over all pairs of an XCD: every row of every request is written
