@@ -86,7 +86,8 @@ typedef struct {
 size_t gr_beam_attn_workspace_bytes(const gr_attn_params* p);
 
 /* Enqueue the attention.  `workspace` (device, 256-byte aligned) holds split-L partials and, for a
- * ragged batch, the order in which requests are dispatched (longest prompt first); contents
+ * ragged batch of more than 128 requests, the order in which they are dispatched (longest prompt first; fewer
+ * requests find their place themselves, though the order's bytes are part of the size for any ragged batch); contents
  * before and after the call are unspecified.  Errors: INVALID_ARG, UNSUPPORTED,
  * WORKSPACE_TOO_SMALL, HIP. */
 gr_status gr_beam_attn(const gr_attn_params* p, void* workspace, size_t workspace_bytes, void* stream);

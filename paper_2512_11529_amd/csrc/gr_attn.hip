@@ -1224,7 +1224,7 @@ extern "C" gr_status gr_diag_attn_plan(int32_t rows_per_workgroup, int32_t l_seg
 extern "C" size_t gr_beam_attn_workspace_bytes(const gr_attn_params* p) {
   if (!p || p->B <= 0 || p->W <= 0 || p->Hq <= 0 || p->Hkv <= 0 || p->Hq % p->Hkv) return 0;
   const AttnPlan plan = plan_attn(p, false);               // (what it says about the workspace is the same for FP8 codes)
-  size_t need = attn_wants_order(p, plan) ? gr_align256((size_t)p->B * 4) : 0;
+  size_t need = attn_wants_order(p, plan) ? gr_align256((size_t)p->B * 4) : 0;      // (up to kRankB requests: asked for as ever, and not used)
   if (plan.nsplit > 1) {
     const size_t rows = (size_t)p->B * plan.nsplit * p->W * p->Hq;
     need += gr_align256(rows * p->d * 4) + gr_align256(rows * 8);
@@ -1271,18 +1271,16 @@ gr_status attn_run(const gr_attn_params* p, const int32_t* slot, bool kv8, float
   c.out = (uint16_t*)p->out; c.lse = p->lse_out;
   c.part_o = nullptr; c.part_ml = nullptr; c.order = nullptr; c.slot = slot; c.rcp_hkv = 0.f;
   const size_t need = gr_beam_attn_workspace_bytes(p);
-  bool find = false;
+  const bool ordered = attn_wants_order(p, plan), find = ordered && p->B <= kRankB;       // (these have one set of wavefronts: two are for at most 256 workgroups)
   if (need > 0) {
     if (!workspace || ((uintptr_t)workspace & 255)) return GR_ERR_INVALID_ARG;
     if (workspace_bytes < need) return GR_ERR_WORKSPACE_TOO_SMALL;
     char* ws = (char*)workspace;
-    if (attn_wants_order(p, plan) && p->B <= kRankB && plan.ks == 1) {
-      find = true;
-    } else if (attn_wants_order(p, plan)) {
+    if (ordered && !find) {
       hipLaunchKernelGGL(k_attn_order, dim3(1), dim3(256), 0, stream, p->cu_seqlens, p->B, (int32_t*)ws);
       c.order = (const int32_t*)ws;
-      ws += gr_align256((size_t)p->B * 4);
     }
+    if (ordered) ws += gr_align256((size_t)p->B * 4);
     if (c.nsplit > 1) {
       const size_t rows = (size_t)p->B * c.nsplit * p->W * p->Hq;
       c.part_o = (float*)ws;
