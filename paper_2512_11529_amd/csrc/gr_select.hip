@@ -317,9 +317,9 @@ __device__ __forceinline__ Bins make_bins(float hi, float range) {
 // Smallest bin t with at least `want` entries in bins 0..t (bin 0 = best scores); the last bin when there are fewer
 // than `want` entries in total.  Done by the whole workgroup (every thread owns kHistBins / NT consecutive
 // bins; one scan, one barrier inside): a serial walk by one wavefront over 32 bins per lane costs more than a
-// microsecond.  Leaves the histogram cleared.  The caller puts a barrier behind it before reading *s_thr.
+// microsecond.  Leaves the histogram cleared.  The caller puts a barrier behind it before reading *s_thr.  Returns the number of entries.
 template <int NT>
-__device__ __forceinline__ void hist_threshold_all(uint32_t* s_hist, uint32_t want, int* s_thr, uint32_t* s_redu, int& par) {
+__device__ __forceinline__ uint32_t hist_threshold_all(uint32_t* s_hist, uint32_t want, int* s_thr, uint32_t* s_redu, int& par) {
   constexpr int per = kHistBins / NT;
   const int tid = threadIdx.x;
   uint32_t h[per], local = 0;
@@ -340,6 +340,7 @@ __device__ __forceinline__ void hist_threshold_all(uint32_t* s_hist, uint32_t wa
     }
     *s_thr = bin;
   }
+  return total;
 }
 
 // Histogram of the candidates' bins -> its exclusive prefix, in place, and in *s_thr the bin that holds the want-th candidate (the last one
@@ -408,7 +409,7 @@ struct PickLds {
   uint64_t list[kPickCap], tmp[kPickCap];
   uint32_t hist[kHistBins];
   uint32_t red[2 * 8];
-  float low[2][8];                     // per wavefront: the worst of its threads' best logits of a load
+  float low[2][8];                     // per wavefront: the logit down to which the threshold is looked for
   uint32_t others[2][8];               // and whether it saw another live row of the request
   uint32_t n, crowded;
   int thr;
@@ -437,7 +438,8 @@ __device__ __forceinline__ float key16_low(float best, uint32_t key) { return be
 __device__ __forceinline__ void mark_dead(const SelCtx& c, int row) { c.row_info[row] = ROW_DEAD; }
 
 // The W best of one row's candidates, which the workgroup holds in registers (thread t: tokens 4 (t + NT i) + j), written as the
-// request's new beams.  False where they are too many for it (thousands of scores as good as equal); nothing is written then.
+// request's new beams; lo = a score that few lie below (none where all fit in the list).  False where they are too many for it (thousands of
+// scores as good as equal), or the W-th lies below lo; nothing is written then.
 template <int NT>
 __device__ __forceinline__ bool row_pick(const SelCtx& c, const MaskView& mv, PickLds& P, int row, const float (&xv)[kBlockV / NT], float bias, float hi, float lo) {
   int tid = threadIdx.x;
@@ -449,12 +451,12 @@ __device__ __forceinline__ bool row_pick(const SelCtx& c, const MaskView& mv, Pi
   for (int e = 0; e < kBlockV / NT; e++)
     if (xv[e] > -INFINITY) atomicAdd(&P.hist[bins.of(__fadd_rn(bias, xv[e]))], 1u);
   __syncthreads();
-  hist_threshold_all<NT>(P.hist, (uint32_t)c.W, &P.thr, P.red, par);
+  const uint32_t total = hist_threshold_all<NT>(P.hist, (uint32_t)c.W, &P.thr, P.red, par);
   __syncthreads();
   const float T = bins.floor_of(P.thr);
-  if (T == kNoThreshold) return false;
-  // what reaches it, in bins of one width
-  const float scale = hi > T ? fminf((float)(kHistBins - 1) / (hi - T), 1e30f) : 0.f;
+  if (T == kNoThreshold && total >= (uint32_t)c.W) return false;
+  // what reaches it (all of fewer than W), in bins of one width
+  const float end = T == kNoThreshold ? lo : T, scale = hi > end ? fminf((float)(kHistBins - 1) / (hi - end), 1e30f) : 0.f;
 #pragma unroll
   for (int e = 0; e < kBlockV / NT; e++) {
     const float score = __fadd_rn(bias, xv[e]);
@@ -482,13 +484,17 @@ __device__ __forceinline__ bool row_pick(const SelCtx& c, const MaskView& mv, Pi
   for (int j = tid; j < late->W; j += NT) {
     const size_t o = (size_t)row + j;
     int32_t* po = late->prefix_out + o * late->depth;
-    const uint64_t key = P.list[j];                          // (at least W reached the threshold)
-    const int token = (int)(0xffffffffu - (uint32_t)key);
-    int r_lo = 0, r_hi = 0;
-    if (late->blob) { r_lo = mv.off1[token]; r_hi = mv.off1[token + 1]; }
-    late->parent_out[o] = 0;
+    int token = -1, r_lo = 0, r_hi = 0;
+    float score = -INFINITY;
+    if (j < m) {
+      const uint64_t key = P.list[j];
+      token = (int)(0xffffffffu - (uint32_t)key);
+      score = gr_ordkey_inv((uint32_t)(key >> 32));
+      if (late->blob) { r_lo = mv.off1[token]; r_hi = mv.off1[token + 1]; }
+    }
+    late->parent_out[o] = j < m ? 0 : -1;
     late->token_out[o] = token;
-    late->scores_out[o] = gr_ordkey_inv((uint32_t)(key >> 32));
+    late->scores_out[o] = score;
     po[0] = token;
     for (int k = 1; k < late->depth; k++) po[k] = -1;
     late->range_out[2 * o] = r_lo;
@@ -661,10 +667,18 @@ __device__ __forceinline__ void row_dense(const SelCtx& c, const MaskView& mv, R
       if (!b1) key[2 * b2 + b0] = r;
     }
   }
-  if (PICK) {
+  if constexpr (PICK) {
+    // down to where the threshold is looked for: the worst of all where they fit in the list (W may be most of them: 163 beams over 256
+    // tokens gave up with the best of every four, 17.9 us instead of 11.2), else the worst of the threads' best of a load
     float low = INFINITY;
+    static_assert(kPickCap == 4 * NT, "a list of one load");
+    if (V <= kPickCap) {
 #pragma unroll
-    for (int i = 0; i < NV4; i++) low = fminf(low, lmax[i] > -INFINITY ? lmax[i] : INFINITY);
+      for (int j = 0; j < 4; j++) low = fminf(low, xv[j] > -INFINITY ? xv[j] : INFINITY);
+    } else {
+#pragma unroll
+      for (int i = 0; i < NV4; i++) low = fminf(low, lmax[i] > -INFINITY ? lmax[i] : INFINITY);
+    }
     low = -wave_max(-low);
     const bool any = __any(rivals.x > -INFINITY || rivals.y > -INFINITY);
     if ((tid & 63) == 0) { P->low[set][wave] = low; P->others[set][wave] = any; }

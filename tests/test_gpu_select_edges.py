@@ -404,3 +404,25 @@ def test_outputs_that_lie_on_the_incoming_scores(gr, oracle_lib, step, where):  
     gr.gr_beam_select(mask, d_logits, scores, d_pf, d_rg, step, out=out)
     torch.cuda.synchronize()
     assert_select_equal({k: v.cpu().numpy() for k, v in out.items()}, want, f"step {step}")
+
+
+@pytest.mark.parametrize("V,W,first_tokens", [(256, 163, None), (256, 255, None), (256, 256, None), (256, 257, None), (2048, 1024, None), (2048, 1000, 900), (2049, 1024, None),
+                                              (2052, 900, 880), (8192, 1024, 1023), (8192, 256, 8), (300, 16, 15), (300, 16, 16), (300, 16, 17)])
+@pytest.mark.parametrize("spread", [1e-3, 3.0, 2000.0])
+def test_level_0_with_about_as_many_beams_as_first_tokens(gr, oracle_lib, V, W, first_tokens, spread):  # noqa: F811
+    """One live beam a request and a beam for most of its candidates, for all of them, or for more than there are: around the longest row that
+    fits the list of the workgroup that selects."""
+    rng = np.random.default_rng(V + W)
+    B = 4
+    logits = (1.25 + spread * rng.standard_normal((B, W, V))).astype(np.float32)
+    logits[1, 0, ::7] = -np.inf
+    sc = np.full((B, W), -np.inf, np.float32)
+    sc[:, 0] = [0.0, -2.5, 7.0, -1.0]
+    pf, rg = np.full((B, W, 3), -1, np.int32), np.zeros((B, W, 2), np.int32)
+    items = mask = None
+    if first_tokens:
+        t1 = np.sort(rng.choice(V, first_tokens, replace=False))
+        items = np.stack([t1, np.zeros_like(t1), np.zeros_like(t1)], axis=1).astype(np.int32)
+        mask = gr.gr_item_mask_build(to_dev(items), V)
+    want = oracle_lib.beam_select(items, logits, sc, pf, 0)
+    assert_select_equal(run_select(gr, mask, logits, sc, pf, rg, 0), want)
