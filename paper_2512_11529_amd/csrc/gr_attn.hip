@@ -1386,16 +1386,18 @@ extern "C" gr_status gr_prefill_attn(const gr_prefill_params* p, void* stream_) 
   const int64_t grid = groups_padded * c.MB;
   // Row blocks dealt heaviest first over all pairs of an XCD: the blocks that prompts shorter than the longest do not have come last
   // (pair by pair they come first, and hold a place while they find that out), and the call ends with light blocks.  Against that stand
-  // 0.4 us at the start of every block and K/V of more pairs that share the L2 at a time.  So: where not all blocks have a place at once, and an XCD's
-  // pairs times the rows of a token in each are at most 48 (head size 128) or 128 (64), or more, up to 64 with head size 128, where the
-  // prompts are on average shorter than two thirds of the longest.  Time by weight over pair by pair, of 1300 shapes of 300 to 5000 tokens,
-  // mean: head size 128 with up to 48 0.96, 64 uneven 0.98 and even 1.03, 80 and more 1.04; head size 64 with up to 128 0.88, with more
-  // uneven 0.96 and even 1.01.  us pair by pair, by weight: 16 prompts of 60-700 tokens, 32 query and 8 KV heads of 128, 44.7, 41.6; 8 of 200-2000 136.7,
-  // 133; 10 of 300-1000 57.5, 55.8; 40 of 100-900, 8 and 2 heads, 47.2, 44.1; 8 heads of 64: 12 of 100-1000 18.9, 15.1, 16 of 1000-4000 153, 140.
-  // But 32 of 100-600, 32 and 8 heads of 128, 69, 78; 16 x 600 70, 74; 64 of 100-600, 16 and 2 heads, 68, 71.
+  // 0.4 us at the start of every block and K/V that is read again when it has left the L2.  So: where not all blocks have a place at once,
+  //   an XCD's pairs times the rows of a token in each are at most 48 (head size 128) or 128 (64), or more, up to 64 with head size 128,
+  //     where the prompts are on average shorter than two thirds of the longest, and
+  //   the K/V of an XCD's pairs times the rows of a token take at most 24 MiB: 64 x 4500 tokens of 8 heads of 64 1647 us pair by pair, 2266 by
+  //     weight, 32 x 3000 with 32 and 8 heads 1397, 1532, 48 of 960-1200 with 8 heads of 128 162, 188; but 32 x 3000 with 8 heads 405, 387.
+  // 2400 shapes of 250 to 11000 tokens: where the rule deals by weight that takes 0.94 of pair by pair in the mean (head size 64 0.91, 128
+  // 0.95), and in one of 90 more than 1.06.  us pair by pair, by weight: 16 prompts of 60-700 tokens, 32 query and 8 KV heads of 128, 44.7, 41.6; 8 of
+  // 200-2000 136.7, 133; 10 of 300-1000 57.5, 55.8; 40 of 100-900, 8 and 2 heads, 47.2, 44.1; 8 heads of 64: 12 of 100-1000 18.9, 15.1, 16 of
+  // 1000-4000 153, 140.  But 32 of 100-600, 32 and 8 heads of 128, 69, 78; 16 x 600 70, 74; 64 of 100-600, 16 and 2 heads, 68, 71.
   const int64_t rows_of_token = groups_padded / 8 * g;
   const bool uneven = p->total_L * 3 < (int64_t)p->B * p->max_L * 2;
-  const bool by_weight = groups_padded <= 512 && grid > 512 && mwg == 128 &&
+  const bool by_weight = groups_padded <= 512 && grid > 512 && mwg == 128 && p->total_L * p->Hq * p->d <= (int64_t)48 << 20 &&
                          (rows_of_token <= (p->d == 64 ? 128 : 48) || (uneven && (p->d == 64 || rows_of_token <= 64)));
   c.rcp_hkv = 1.0f / (float)p->Hkv * 1.00001f;
   if (grid >= ((int64_t)1 << 31)) return GR_ERR_UNSUPPORTED;
