@@ -63,7 +63,8 @@ const char* gr_status_string(gr_status s);
  * or is the query position.
  *
  * Supported: d in {64, 128}; Hq % Hkv == 0; 1 <= u <= ND; L_b >= 0 (L_b + u >= 1).  All bf16 tensors must be
- * 16-byte aligned (INVALID_ARG otherwise) and hold finite values.
+ * 16-byte aligned (INVALID_ARG otherwise) and hold finite values.  Sums are fp32 and normalised at the end:
+ * |v| * 2^8 * (L_b + u) has to stay below 2^128.
  * ------------------------------------------------------------------------------------------------ */
 typedef struct {
   int32_t B, W, Hq, Hkv, d;   /* requests, beam width, query heads, KV heads, head dim              */
@@ -125,7 +126,7 @@ gr_status gr_beam_attn_fp8kv(const gr_attn_fp8kv_params* p, void* workspace, siz
 typedef struct {
   int32_t B, Hq, Hkv, d;
   int32_t max_L;              /* host copy of max_b L_b (sizes the grid)                             */
-  int64_t total_L;            /* host copy of cu_seqlens[B]                                          */
+  int64_t total_L;            /* host copy of cu_seqlens[B] (chooses the plan)                       */
   float   sm_scale;           /* multiplies the scores; must be positive and finite                  */
   const void*    q;           /* bf16 [total_L, Hq, d]  (device), packed like k and v                */
   const void*    k;           /* bf16 [total_L, Hkv, d]                                              */
@@ -160,7 +161,8 @@ size_t gr_item_mask_build_workspace_bytes(int64_t n_items, int32_t depth, int32_
  * gr_item_mask_bytes().  Synchronises `stream`; returns GR_ERR_BAD_TABLE if the on-device check of
  * order / distinctness / token range fails (mask_out is then unspecified).  The first call of a process allocates one
  * page of pinned host memory through which the kernels report (kept until the process ends; calls may run
- * concurrently from any threads, on any streams and GPUs). */
+ * concurrently from any threads, on any streams and GPUs).  As calls that synchronise do, it breaks off a graph capture
+ * that another thread has open in global mode. */
 gr_status gr_item_mask_build(const int32_t* items_sorted, int64_t n_items, int32_t depth, int32_t V,
                              void* mask_out, size_t mask_bytes, void* workspace, size_t workspace_bytes,
                              void* stream);
@@ -203,7 +205,8 @@ typedef struct {
   const int32_t* range_in;        /* int32 [B, W, 2]                                                */
   int32_t*       parent_out;      /* int32 [B, W] index of the beam each survivor extends           */
   int32_t*       token_out;       /* int32 [B, W] token appended                                    */
-  float*         scores_out;      /* fp32 [B, W] cumulative log-probability, non-increasing; may be scores_in */
+  float*         scores_out;      /* fp32 [B, W] cumulative log-probability, non-increasing; may be scores_in (all outputs may */
+                                  /* lie on scores_in, which is read before any of them is written) */
   int32_t*       prefix_out;      /* int32 [B, W, depth]; must not alias prefix_in                  */
   int32_t*       range_out;       /* int32 [B, W, 2];     must not alias range_in                   */
   int32_t*       item_index_out;  /* int32 [B, W] table row of the finished item when step ==       */

@@ -284,8 +284,7 @@ struct AttnTile {
 
   // A segment's first and last tile are searched for the columns' maxima before their probabilities are made, the tiles between only from where a
   // wavefront meets scores that rise: 16 vector instructions a tile and an exchange between lanes, in a loop bound by what it issues
-  // beside the MFMAs.  Worth 3 to 4 %: 32 x 4096 tokens x 256 beams 17 us of 505, 4 x 16384 x 512 in FP8 477 -> 459 us, 8 causal prompts of
-  // 1024-8192 1606 -> 1556.
+  // beside the MFMAs.  Worth 3 %: 32 x 4096 tokens x 256 beams 509 -> 495 us, 4 x 16384 x 512 in FP8 467 -> 454, 4 causal prompts of 3000 278 -> 268.
   // The reference is the first tile's maximum.  Where a lane's half of a column of a later tile sums to more than kRaise = 2^kLazy, which no
   // column does without a score kLazy - 5 bits above its reference, the column gets a higher reference after that tile, a power of two
   // for which this sum lies between 1 and 2, and the wavefront searches from there on: the reference becomes the maximum before a tile's
@@ -350,8 +349,8 @@ struct AttnTile {
 // KV8 = true: the prompt K/V are FP8 E4M3 codes with one scale per tensor (value = code * scale).  The tiles are widened
 // to bf16 (exactly) on their way into LDS: 8-byte loads into registers one tile ahead, four conversions per 16-byte piece,
 // a ds_write into the same swizzled layout the direct loads fill.  The scales never touch the tiles: the K scale goes into
-// the exponent scale of the prompt loop, and at the end of the loop the running maximum (x k_scale) and O (x v_scale) are
-// put into true units, which is where the bf16 own-token stage and the epilogue work.
+// the exponent scale of the prompt loop, whose references are in log2 units of the true scores, and at the end of the loop O is
+// multiplied by v_scale: the bf16 own-token stage and the epilogue work in true units.
 // KS = 2: two sets of NWAVES wavefronts hold the same query rows and take one half of the segment's tiles each, with tiles
 // of their own in LDS; the second set's (maximum, sum, O) goes through LDS into the first's before the epilogue.  For launches of at
 // most one 128-row workgroup per CU, whose SIMDs would otherwise hold one wavefront each and wait out every chain of its tile

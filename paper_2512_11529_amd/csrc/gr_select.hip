@@ -935,7 +935,8 @@ __device__ __forceinline__ void gather_rows(const SelCtx& c, const MaskView& mv,
 //   two to a CU).  With so few rows at work a row is dealt to twice as many threads.
 //   PICK: first rows may select as well.  They have a loop of their own: what the selection keeps in registers slows other rows down.  us where
 //   all rows are live, with one loop, with two and in the kernel without PICK: 32 x 256 beams over 8192 tokens 79.6, 77.2, 76.5; 8 x 128
-//   21.9, 21.6, 21.3; 64 x 128 over 1000 63.4, 60.0, 58.5 (59.0 before there was a selection here, the only one of these that lost by it).
+//   21.9, 21.6, 21.3; 64 x 128 over 1000 63.4, 60.1, 58.5; 185 x 485 over 500 564, 535 (507 before there was a selection here: many short
+//   rows are what still loses by it).
 constexpr size_t kStrideGrid = 512;
 template <bool STRIDE, int NT, bool PICK>
 __global__ void __launch_bounds__(NT, STRIDE ? 4 : 6) k_rows(SelCtx c) {
