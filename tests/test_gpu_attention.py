@@ -317,3 +317,19 @@ def test_scores_that_jump_in_many_workgroups(gr, oracle_lib, d, W, uniform, fact
         tri += [(b, w, head), (b, (w + 1) % W, head), (b, w, (head + 1) % H), (b, W - 1, head)]
     a["k_shared"] = gr_synth.f32_to_bf16_bits(k)
     _check(gr, oracle_lib, a, float(np.float32(1 / np.sqrt(d))), np.array(tri, dtype=np.int32))
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("rows,segments", [(128, 1), (256, 1), (128, 2)])
+@pytest.mark.parametrize("width", [4.0, 32.0])
+def test_scores_that_are_wide_from_the_first_tile_on(gr, oracle_lib, d, rows, segments, width):
+    """Queries times 4, where some wavefronts' first tile passes 16 bits and makes them search from the start, and others search from a rise
+    on or not at all; and times 32, where all of them do and scores go on to rise by tens of bits."""
+    lens, W, Hq, Hkv = (330, 400, 65), 40, 8, 2
+    a = rand_attn_case(1500 + d + rows, len(lens), W, Hq, Hkv, d, 3, 2, lens)
+    a["q"] = gr_synth.f32_to_bf16_bits(width * gr_synth.bf16_bits_to_f32(a["q"]))
+    gr.gr_diag_attn_plan(rows, segments)
+    try:
+        _check(gr, oracle_lib, a, float(np.float32(1 / np.sqrt(d))))
+    finally:
+        gr.gr_diag_attn_plan(0, 0)

@@ -195,3 +195,18 @@ def test_fp8kv_a_token_that_is_nearly_all_of_the_sum(gr, d, rows, factor):
         gr.gr_diag_attn_plan(0, 0)
     for b, w, head, at in rows_of:
         np.testing.assert_array_equal(out[b, w, head], 0.25 * v[at, head], err_msg=f"request {b}, beam {w}, head {head}")
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("rows", [128, 256])
+@pytest.mark.parametrize("width", [4.0, 32.0])
+def test_fp8kv_scores_that_are_wide_from_the_first_tile_on(gr, oracle_lib, d, rows, width):
+    """Some wavefronts, or all, search from the first tile on."""
+    lens, W, Hq, Hkv = (330, 65), 40, 8, 2
+    a = rand_attn_case(1600 + d + rows, len(lens), W, Hq, Hkv, d, 3, 2, lens)
+    a["q"] = gr_synth.f32_to_bf16_bits(width * gr_synth.bf16_bits_to_f32(a["q"]))
+    gr.gr_diag_attn_plan(rows, 1)
+    try:
+        _check(gr, oracle_lib, a, float(np.float32(1 / np.sqrt(d))))
+    finally:
+        gr.gr_diag_attn_plan(0, 0)

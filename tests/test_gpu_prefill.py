@@ -279,3 +279,21 @@ def test_prefill_rows_do_not_depend_on_total_L(oracle_lib):
     out = torch.full(c["q"].shape, 7.0, dtype=torch.bfloat16, device="cuda:0")
     gr.gr_prefill_attn(bf16_to_dev(c["q"]), bf16_to_dev(c["k"]), bf16_to_dev(c["v"]), to_dev(c["cu"]), scale, 290, 300, out=out)
     np.testing.assert_array_equal(out.float().cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("d,max_L", [(64, 330), (128, 330), (128, 2049)])
+@pytest.mark.parametrize("width", [4.0, 32.0])
+def test_prefill_scores_that_are_wide_from_the_first_tile_on(oracle_lib, d, max_L, width):
+    """Some wavefronts, or all, search from the first tile on."""
+    import torch
+    import paper_2512_11529_amd as gr
+    gr.load_library()
+    c = _case(97 + d, (330, 65, 200), 8, 2, d)
+    c["q"] = gr_synth.f32_to_bf16_bits(width * gr_synth.bf16_bits_to_f32(c["q"]))
+    scale = float(np.float32(1 / np.sqrt(d)))
+    out = torch.empty(c["q"].shape, dtype=torch.bfloat16, device="cuda:0")
+    lse = torch.empty(c["q"].shape[:2], dtype=torch.float32, device="cuda:0")
+    gr.gr_prefill_attn(bf16_to_dev(c["q"]), bf16_to_dev(c["k"]), bf16_to_dev(c["v"]), to_dev(c["cu"]), scale, max_L, 595, out=out, lse_out=lse)
+    ref, ref_lse = oracle_lib.prefill_attn_causal(c["q"], c["k"], c["v"], c["cu"], scale)
+    assert np.abs(out.float().cpu().numpy() - ref.reshape(out.shape)).max() <= 2e-2
+    np.testing.assert_allclose(lse.cpu().numpy(), ref_lse.reshape(lse.shape), rtol=0, atol=2e-3)
