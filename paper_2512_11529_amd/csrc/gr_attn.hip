@@ -62,8 +62,8 @@ struct AttnCtx {
   const uint16_t* vu;
   uint16_t* out;
   float* lse;
-  float* part_o;    // [B, nsplit, W*Hq, D] fp32, unnormalised
-  float* part_ml;   // [B, nsplit, W*Hq, 2] (max in log2 domain, sum)
+  float* part_o;    // [B, nsplit, Hkv, M rows in blocks of 32: D / 4, row, 4] fp32, unnormalised
+  float* part_ml;   // [B, nsplit, Hkv, M, 2] (max in log2 domain, sum)
   const int32_t* order;   // [B] requests by decreasing prompt length, or nullptr (requests taken in index order)
   const int32_t* slot;    // [B, W, ND] row of the request's own-token block that holds (beam, token), or nullptr (= w * ND + t)
 };
@@ -1036,56 +1036,43 @@ k_beam_attn(AttnCtx c) {
         c.lse[((CAUSAL ? (size_t)row0 : (size_t)b * c.W) + w) * c.Hq + kvh * c.g + j] = (l_tot > 0.f) ? (m + __builtin_amdgcn_logf(l_tot)) * kLn2 : -INFINITY;
       }
     } else {
-      // this segment's unnormalised fp32 partial O and (max, sum): staged through LDS like the final
-      // output, half of the columns at a time
-      float* s_p = (float*)(smem + wave * 32 * KSTR);
-      constexpr int CW = D / 2;                            // columns per round: a wave's slice holds 32 rows x CW floats
-      constexpr int PSTR = KSTR / 2;                       // floats per staged row (CW + padding)
-      const float rcp_g2 = 1.0f / (float)c.g;
-      float* part_b = c.part_o + ((size_t)b * c.nsplit + sp) * ((size_t)c.W * c.Hq) * D;
+      // this segment's unnormalised fp32 partial O and (max, sum), as the lanes hold them (see k_attn_merge): every store is a run of whole lines.
+      // (Staged through LDS into rows of D floats they took 2.1 us of a unit's 13.5.)
+      const int first = mbi * MWG + wave_u * 32, left = min(32, Mb - first);       // the wave's rows
+      const size_t row_p = (((size_t)b * c.nsplit + sp) * c.Hkv + kvh) * c.M + first;
+      if (r >= 0) {
+        f32x4* part = (f32x4*)(c.part_o + row_p * D) + G * left + n32;
 #pragma unroll
-      for (int h = 0; h < 2; h++) {
-#pragma unroll
-        for (int dd = 0; dd < CW / 32; dd++)
-#pragma unroll
-          for (int q4 = 0; q4 < 4; q4++) {
-            const int db = h * (CW / 32) + dd;
-            const f32x4 st = {o_acc[db][0][4 * q4], o_acc[db][0][4 * q4 + 1], o_acc[db][0][4 * q4 + 2], o_acc[db][0][4 * q4 + 3]};
-            *(f32x4*)(&s_p[n32 * PSTR + dd * 32 + 8 * q4 + 4 * G]) = st;
-          }
-#pragma unroll
-        for (int i = 0; i < CW / 8; i++) {
-          const int p = lane + 64 * i, rl = p / (CW / 4), col = (p % (CW / 4)) * 4;
-          const int rr = mbi * MWG + wave * 32 + rl;
-          int w, j;
-          divmod_small(rr, c.g, rcp_g2, &w, &j);
-          const f32x4 v = *(const f32x4*)(&s_p[rl * PSTR + col]);
-          if (rr < Mb) *(f32x4*)(part_b + (size_t)(w * c.Hq + kvh * c.g + j) * D + h * CW + col) = v;
+        for (int e = 0; e < D / 8; e++) {
+          const f32x4 v = {o_acc[e / 4][0][4 * (e % 4)], o_acc[e / 4][0][4 * (e % 4) + 1], o_acc[e / 4][0][4 * (e % 4) + 2], o_acc[e / 4][0][4 * (e % 4) + 3]};
+          part[2 * e * left] = v;
         }
-      }
-      if (G == 0 && r >= 0) {
-        int w, j;
-        divmod_small(r, c.g, rcp_g2, &w, &j);
-        const size_t prow = ((size_t)b * c.nsplit + sp) * ((size_t)c.W * c.Hq) + (size_t)w * c.Hq + kvh * c.g + j;
-        f32x2 ml = {(l_tot > 0.f) ? m : -INFINITY, l_tot};
-        *(f32x2*)(c.part_ml + prow * 2) = ml;
+        if (G == 0) {
+          const f32x2 ml = {(l_tot > 0.f) ? m : -INFINITY, l_tot};
+          *(f32x2*)(c.part_ml + (row_p + n32) * 2) = ml;
+        }
       }
     }
   }
 }
 
-// Merge of the per-segment partials (Section 5.2 merge stage): D / 4 lanes per output row, 16 bytes each.  The (max, sum) pairs
+// Merge of the per-segment partials (Section 5.2 merge stage).  They lie as k_beam_attn's lanes hold them: per (request, segment, KV head) its M rows
+// in blocks of up to 32, of a block first columns 0..3 of all its rows, then columns 4..7, and so on.  A lane takes four columns of a row; the
+// eight rows of eight neighbouring lanes are a line, and the eight lanes of a row write 64 bytes of it.  The (max, sum) pairs
 // and the partials of four segments are requested together, so a row waits for memory once per four segments.  Bound: the
 // partials' bytes; 4096 rows x 5 segments of 128 (10.5 MB) take 4.3 us (6.7 us with 4-byte loads, one segment at a time).
 template <int D>
 __global__ void __launch_bounds__(256) k_attn_merge(AttnCtx c) {
-  constexpr int LPR = D / 4, RPW = 256 / LPR;              // lanes per row, rows per workgroup
-  const int lane = threadIdx.x % LPR;
-  const size_t row = (size_t)blockIdx.x * RPW + threadIdx.x / LPR;      // (b, w, hq) flattened
-  const size_t rows_per_b = (size_t)c.W * c.Hq;
-  if (row >= (size_t)c.B * rows_per_b) return;
-  const size_t b = row / rows_per_b, rr = row - b * rows_per_b;
-  const size_t prow0 = b * c.nsplit * rows_per_b + rr;     // this row of segment 0; the next segment's is rows_per_b further
+  constexpr int RPW = 1024 / D;                            // rows per workgroup, of one (request, KV head) pair
+  static_assert(RPW % 8 == 0 && 32 % RPW == 0, "whole lines of one block");
+  const unsigned per_pair = ((unsigned)c.M + RPW - 1) / RPW, pair = blockIdx.x / per_pair;
+  const int b = (int)(pair / (unsigned)c.Hkv), kvh = (int)(pair - (unsigned)b * (unsigned)c.Hkv);
+  const int t = (int)threadIdx.x, piece = (t >> 3) % (D / 4), r = (int)(blockIdx.x - pair * per_pair) * RPW + (t & 7) + 8 * (t / (2 * D));
+  if (r >= c.M) return;
+  const int left = min(32, c.M - (r & ~31));               // rows of this row's block
+  const size_t per_seg = (size_t)c.Hkv * c.M;              // rows of a segment of the request
+  const size_t row0 = ((size_t)b * c.nsplit * c.Hkv + kvh) * c.M + r;
+  const float* part = c.part_o + (row0 - (r & 31)) * D + 4 * (piece * left + (r & 31));
   float M2 = -INFINITY, L = 0.f;
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
   constexpr int U = 4;
@@ -1095,9 +1082,9 @@ __global__ void __launch_bounds__(256) k_attn_merge(AttnCtx c) {
     f32x4 o[U];
 #pragma unroll
     for (int k = 0; k < U; k++) {
-      const size_t prow = prow0 + (size_t)min(s0 + k, c.nsplit - 1) * rows_per_b;
-      ml[k] = *(const f32x2*)(c.part_ml + prow * 2);
-      o[k] = *(const f32x4*)(c.part_o + prow * D + 4 * lane);
+      const size_t skip = (size_t)min(s0 + k, c.nsplit - 1) * per_seg;
+      ml[k] = *(const f32x2*)(c.part_ml + (row0 + skip) * 2);
+      o[k] = *(const f32x4*)(part + skip * D);
     }
     float mx = M2;
 #pragma unroll
@@ -1124,8 +1111,10 @@ __global__ void __launch_bounds__(256) k_attn_merge(AttnCtx c) {
   bf16x4 h;
 #pragma unroll
   for (int e = 0; e < 4; e++) h[e] = (__bf16)(acc[e] * inv);
-  *(bf16x4*)(c.out + row * D + 4 * lane) = h;
-  if (c.lse && lane == 0) c.lse[row] = (L > 0.f) ? (M2 + __builtin_amdgcn_logf(L)) * kLn2 : -INFINITY;
+  const int w = (int)((unsigned)r / (unsigned)c.g);
+  const size_t row = ((size_t)b * c.W + w) * c.Hq + kvh * c.g + (r - w * c.g);
+  *(bf16x4*)(c.out + row * D + 4 * piece) = h;
+  if (c.lse && piece == 0) c.lse[row] = (L > 0.f) ? (M2 + __builtin_amdgcn_logf(L)) * kLn2 : -INFINITY;
 }
 
 // Requests by decreasing prompt length (ties by index), so that the longest units are dispatched first
@@ -1315,9 +1304,8 @@ gr_status attn_run(const gr_attn_params* p, const int32_t* slot, bool kv8, float
 #undef GR_LAUNCH_SETS
 #undef GR_LAUNCH_ATTN
   if (c.nsplit > 1) {
-    const int64_t rows = (int64_t)p->B * p->W * p->Hq;
-    const int rpw = 256 / (p->d / 4);                      // rows per workgroup
-    const unsigned mgrid = (unsigned)((rows + rpw - 1) / rpw);
+    const int rpw = 1024 / p->d;                           // rows per workgroup
+    const unsigned mgrid = (unsigned)((int64_t)p->B * p->Hkv * ((c.M + rpw - 1) / rpw));
     if (p->d == 128) hipLaunchKernelGGL((k_attn_merge<128>), dim3(mgrid), dim3(256), 0, stream, c);
     else hipLaunchKernelGGL((k_attn_merge<64>), dim3(mgrid), dim3(256), 0, stream, c);
   }

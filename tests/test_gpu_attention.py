@@ -333,3 +333,15 @@ def test_scores_that_are_wide_from_the_first_tile_on(gr, oracle_lib, d, rows, se
         _check(gr, oracle_lib, a, float(np.float32(1 / np.sqrt(d))))
     finally:
         gr.gr_diag_attn_plan(0, 0)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("W,Hq,Hkv", [(1, 2, 2), (31, 2, 2), (11, 6, 2), (43, 3, 1), (17, 8, 1), (257, 2, 2)])      # 1, 31, 33, 129, 136 and 257 rows per KV head
+def test_partials_of_blocks_that_are_not_full(gr, oracle_lib, d, W, Hq, Hkv):
+    # a segment's partials lie in blocks of up to 32 rows, column pieces first: rows that end inside a block, a line or a workgroup of the merge
+    a = rand_attn_case(W, 2, W, Hq, Hkv, d, 3, 2, (330, 200))
+    gr.gr_diag_attn_plan(128, 5)
+    try:
+        _check(gr, oracle_lib, a, float(np.float32(1 / np.sqrt(d))))
+    finally:
+        gr.gr_diag_attn_plan(0, 0)
