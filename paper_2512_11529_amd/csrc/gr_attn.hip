@@ -26,19 +26,14 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int KT = 64;        // kv tokens per LDS tile
 
-// Dynamic LDS of k_beam_attn: K and V tiles, double-buffered (unpadded); the Q hand-over (unpadded, swizzled), behind the tiles
-// for workgroups of 8 wavefronts and in the V tiles' place for those of 4; one padded 32-row K and V mini-tile per wave for the own-token
-// stage and the padded output staging (on top of everything else, after the prompt loop).  Behind all of it 256 bytes per wave
-// that loads issued only to bring lines into L2 write to.
+// Dynamic LDS of k_beam_attn: K and V tiles, double-buffered; the Q hand-over, behind the tiles for workgroups of 8 wavefronts and in the V
+// tiles' place for those of 4.  After the prompt loop a wavefront's 32 own-token rows take the K tiles' place (of K; Q's where 8 wavefronts hold
+// 256 rows) and the V tiles' (of V; all tiles' there), and its 32 rows of output K's again.  All of it in unpadded, swizzled rows.  Behind it 256
+// bytes per wave that loads issued only to bring lines into L2 write to.
 // Workgroups whose two halves share the prompt (ks = 2): tiles of the first half, Q, tiles of the second half.  The last 2 KiB
 // of Q's place take those 256 bytes per wave, then the second half's (maximum, sum).
 constexpr int attn_tiles_bytes(int d) { return 4 * KT * d * 2; }
-constexpr int attn_lds_used(int d, int mwg) {
-  const int tiles = attn_tiles_bytes(d), rows = mwg * d * 2;
-  const int main_loop = mwg == 256 ? tiles + rows : (tiles > rows ? tiles : rows);
-  const int own = mwg * ((d + 8) + (d + 32)) * 2;
-  return main_loop > own ? main_loop : own;
-}
+constexpr int attn_lds_used(int d, int mwg) { return attn_tiles_bytes(d) + (mwg == 256 ? mwg * d * 2 : 0); }
 constexpr int attn_lds_bytes(int d, int mwg, int ks) {
   return ks == 2 ? 2 * attn_tiles_bytes(d) + mwg * d * 2 : attn_lds_used(d, mwg) + mwg / 32 * 256;
 }
@@ -52,6 +47,8 @@ struct AttnCtx {
   int nsplit;       // L segments per request
   int n_groups;     // B * Hkv * nsplit
   float rcp_hkv;    // 1 / Hkv, a little high: n * rcp_hkv is n / Hkv rounded down for 0 <= n < 512
+  float rcp_g, rcp_u;       // 1 / g, 1 / max(u, 1)
+  uint32_t inv_mb, inv_split, inv_hkv;       // for div_by
   float c;          // sm_scale * log2(e)
   float k_scale, v_scale;   // FP8 prompt cache: value = code * scale (1 for the bf16 cache)
   const uint16_t* q;
@@ -81,6 +78,17 @@ __device__ __forceinline__ void divmod_small(int n, int d, float rcp_d, int* q, 
   if (rr < 0) { qq--; rr += d; }
   *q = qq; *r = rr;
 }
+
+// n / d for any n, with inv = (2^32 - 1) / d rounded down from the host: the product's high word is n / d or one less.  (In scalar registers; the generic
+// division by a number from memory is three times as long, and a unit starts with four of them.)
+constexpr uint32_t div_inv(uint32_t d) { return 0xffffffffu / d; }
+__device__ __forceinline__ unsigned div_by(unsigned n, unsigned d, uint32_t inv) {
+  const unsigned q = __umulhi(n, inv);
+  return q + (n - q * d >= d ? 1u : 0u);
+}
+// r / g for 0 <= r < 2^22, with rcp = 1 / g rounded to nearest: (r + 1/2) / g is at least 1/(2g) from a whole number, and two roundings move it by less
+// than (r + 1/2) / g * 2^-23 (1 + 2^-25) < 1/(2g).
+__device__ __forceinline__ int small_div(int r, float rcp) { return (int)fmaf((float)r, rcp, 0.5f * rcp); }
 
 __device__ __forceinline__ int wave_total(int v) {
   v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);      // row_shr:1
@@ -172,12 +180,6 @@ struct AttnTile {
     s16x8 both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
     return __builtin_bit_cast(bf16x8, both);
   }
-  static constexpr int KSTR = D + 8;     // padded rows of the Q / output staging and of the own-token mini-tiles (+16 B)
-  // V rows: +64 B.  One ds_read_b64_tr_b16 serves 32 lanes per cycle = 4 rows x 2 column halves x 32 bytes; a row
-  // stride of 64 B modulo 256 B puts those eight 32-byte groups on eight different bank groups (with +32 B the
-  // second half of row r and the first half of row r+1 share banks: a 2-way conflict on every V operand read).
-  static constexpr int VSTR = D + 32;    // (own-token mini-tiles only; prompt V tiles are unpadded and swizzled)
-
   // S^T = K . Q^T from the K tile in LDS (A operand) and Q in registers (B operand)
   static __device__ __forceinline__ void qk(int sk, const bf16x8 (&qop)[NCB][D / 16], f32x16 (&s)[KT / 32][NCB],
                                             const Rd& rdo) {
@@ -368,7 +370,6 @@ k_beam_attn(AttnCtx c) {
   constexpr int NT = NWAVES * 64;                // threads of a set
   static_assert(KS == 1 || (KS == 2 && NWAVES == 4 && !CAUSAL), "two sets of four wavefronts");
   constexpr int MWG = NWAVES * 32 * NCB;
-  constexpr int KSTR = T::KSTR, VSTR = T::VSTR;
   constexpr int PPR = D / 8;                     // 16-byte pieces per row
   constexpr int TILE = KT * D;                   // elements of one K or V tile (unpadded, swizzled rows)
   constexpr int NCHUNK = TILE * 2 / 1024;        // 1 KiB chunks (= wave-level loads) per tile
@@ -391,12 +392,12 @@ k_beam_attn(AttnCtx c) {
 
   // XCD-aware unit order: workgroups are dealt round-robin to the 8 XCDs, so ids congruent mod 8
   // share an L2.  The MB row blocks that read the same K/V stream get consecutive slots of one XCD.
-  // (unsigned arithmetic: these scalar divisions run once per workgroup, but every wave runs them)
   const unsigned id = blockIdx.x;
   const int xcd = (int)(id & 7u);
   const unsigned slot = id >> 3;
-  int group = (int)(slot / (unsigned)c.MB) * 8 + xcd;
-  int mbi = (int)(slot % (unsigned)c.MB);
+  const unsigned nth = div_by(slot, (unsigned)c.MB, c.inv_mb);
+  int group = (int)nth * 8 + xcd;
+  int mbi = (int)(slot - nth * (unsigned)c.MB);
   if (CAUSAL) mbi = c.MB - 1 - mbi;            // the blocks with the most keys to visit start first
   int len_l = 0, row0_l = 0;
   if constexpr (CAUSAL && FIND) {
@@ -426,62 +427,44 @@ k_beam_attn(AttnCtx c) {
     len_l = __builtin_amdgcn_readlane(len_l, l);
   }
   if (group >= c.n_groups) return;
-  const unsigned gq = (unsigned)group / (unsigned)c.nsplit;
-  const int sp = (int)((unsigned)group - gq * (unsigned)c.nsplit);
-  const int bi = (int)(gq / (unsigned)c.Hkv);
+  const unsigned gq = CAUSAL ? (unsigned)group : div_by((unsigned)group, (unsigned)c.nsplit, c.inv_split);
+  const int sp = CAUSAL ? 0 : (int)((unsigned)group - gq * (unsigned)c.nsplit);
+  const int bi = (int)div_by(gq, (unsigned)c.Hkv, c.inv_hkv);
   const int kvh = (int)(gq - (unsigned)bi * (unsigned)c.Hkv);
   int b = c.order ? c.order[bi] : bi;
   if constexpr (!CAUSAL && FIND) b = request_by_length(c.cu, c.B, bi, lane, &row0_l, &len_l);
   const int row0 = FIND ? row0_l : c.cu[b];
   const int Lb = FIND ? len_l : c.cu[b + 1] - row0;
   const int Mb = CAUSAL ? Lb * c.g : c.M;                      // query rows of this (request, KV head)
-  if (CAUSAL && mbi * (NWAVES * 32 * NCB) >= Mb) return;       // (before any barrier: the whole workgroup leaves)
-  int chunk = (int)(((unsigned)Lb + (unsigned)c.nsplit - 1u) / (unsigned)c.nsplit);
+  if (CAUSAL && mbi * MWG >= Mb) return;                       // (before any barrier: the whole workgroup leaves)
+  int chunk = CAUSAL ? Lb : (int)div_by((unsigned)Lb + (unsigned)c.nsplit - 1u, (unsigned)c.nsplit, c.inv_split);
   chunk = ((chunk + KT - 1) / KT) * KT;
   // The segment whose unit takes the beams' own tokens too: the first, which starts first, or the last where its wavefronts have fewer tiles (4
   // requests of 500-1500 tokens x 64 beams, 8 heads of 64: 13.9 -> 12.6 us).
   const int last_tiles = max(0, Lb - (c.nsplit - 1) * chunk + KT - 1) / KT;
   const int own_sp = (last_tiles + KS - 1) / KS < (chunk / KT + KS - 1) / KS ? c.nsplit - 1 : 0;
   int seg0 = CAUSAL ? 0 : min(Lb, sp * chunk);
-  int seg1 = CAUSAL ? (min((mbi + 1) * (NWAVES * 32 * NCB), Mb) - 1) / c.g + 1 : min(Lb, seg0 + chunk);
+  int seg1 = CAUSAL ? __builtin_amdgcn_readfirstlane(small_div(min((mbi + 1) * MWG, Mb) - 1, c.rcp_g)) + 1 : min(Lb, seg0 + chunk);
   int ntiles = (seg1 - seg0 + KT - 1) / KT, set1_idle = 0;     // set1_idle: barriers that the second set waits at beside its own
   if (KS == 2) {                                               // the first set takes the odd tile
     const int n0 = (ntiles + 1) / 2, n1 = ntiles - n0;
-    set1_idle = (n0 > 0 ? n0 + 1 : 0) - (n1 > 0 ? n1 + 1 : 0);
+    set1_idle = n0 - n1;
     const int mid = min(seg1, seg0 + n0 * KT);
     if (set == 0) seg1 = mid; else seg0 = mid;
     ntiles = set == 0 ? n0 : n1;
   }
   const int flip = (ntiles - 1) & 1;
 
-  // ---- Q: the workgroup's MWG query rows are fetched with coalesced 16-byte pieces (a row = PPR
-  // consecutive lanes) and handed to the lanes that own them through LDS.  A lane reading its own
-  // row straight from global memory touches 32 different rows per load instruction, which keeps the
-  // address unit busy for microseconds while the CU has nothing else to do.
   static_assert(NCB == 1, "one column block per wave");
-  constexpr int QP = MWG * PPR / (NT * KS);      // 16-byte pieces of Q per thread
-  const float rcp_g = 1.0f / (float)c.g;
-  // this request's queries (decode: its W beams; prefill: its own tokens); offsets inside it fit 32 bits
-  const uint16_t* q_b = c.q + (CAUSAL ? (size_t)row0 : (size_t)b * c.W) * c.Hq * D;
-  uint4 qpiece[QP];
-#pragma unroll
-  for (int i = 0; i < QP; i++) {
-    const int p = (int)threadIdx.x + i * (NT * KS), rl = p / PPR, col = (p % PPR) * 8;
-    const int r = mbi * MWG + rl;
-    int w, j;
-    divmod_small(r, c.g, rcp_g, &w, &j);
-    qpiece[i] = make_uint4(0, 0, 0, 0);
-    if (r < Mb) qpiece[i] = *(const uint4*)(q_b + (uint32_t)((w * c.Hq + kvh * c.g + j) * D + col));
-  }
+  const int wave_u = __builtin_amdgcn_readfirstlane(wave);
+  const int row_w = mbi * MWG + wave_u * 32;                   // the wave's first query row
   int qrow[NCB];       // local query row or -1
-  {
-    const int r = mbi * MWG + wave * 32 + n32;
-    qrow[0] = (r < Mb) ? r : -1;
-  }
+  qrow[0] = row_w + n32 < Mb ? row_w + n32 : -1;
+  const int beam_q = small_div(max(qrow[0], 0), c.rcp_g);      // the query's beam, or token
   // causal mode: the last key a column may see, and the first token of the wave's 32 columns (tiles that end at or
   // before it need no masking).  Columns past the end of the request keep everything (their output is dropped).
-  const int tokq = (CAUSAL && qrow[0] >= 0) ? qrow[0] / c.g : 0x7fffffff;
-  const int wave_tok0 = CAUSAL ? (mbi * MWG + wave * 32 * NCB) / c.g : 0x7fffffff;
+  const int tokq = (CAUSAL && qrow[0] >= 0) ? beam_q : 0x7fffffff;
+  const int wave_tok0 = CAUSAL ? __builtin_amdgcn_readfirstlane(small_div(row_w, c.rcp_g)) : 0x7fffffff;
 
   f32x16 o_acc[D / 32][NCB];
 #pragma unroll
@@ -507,7 +490,6 @@ k_beam_attn(AttnCtx c) {
   const char* vbase = (const char*)c.vs + ((size_t)row0 * c.Hkv + kvh) * D * EB;
   const float cp = KV8 ? c.c * c.k_scale : c.c;              // exponent scale of the prompt loop
   const typename T::Rd rdo = T::make_rd(lane, (int)(uintptr_t)(__attribute__((address_space(3))) uint16_t*)s_tiles);
-  const int wave_u = __builtin_amdgcn_readfirstlane(wave);
   int crow[CPW];                                             // this lane's row inside a tile, per chunk
   uint32_t koff[CPW], voff[CPW];                             // and its byte offsets from the tile's first row (full tiles)
 #pragma unroll
@@ -539,7 +521,7 @@ k_beam_attn(AttnCtx c) {
       }
     }
   };
-  auto all_landed = [&]() { __builtin_amdgcn_s_waitcnt(0x0F70); };                 // vmcnt(0)
+  auto all_landed = [&]() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); };
   auto tiles_landed = [&]() { if (!KV8) all_landed(); };
   // FP8 tiles: piece p = tid + i * NT of a tile = 8 codes of row p / PPR; registers one tile ahead
   constexpr int P8 = KT * PPR / NT;                          // pieces per thread and tile
@@ -585,64 +567,46 @@ k_beam_attn(AttnCtx c) {
 
   // ---- geometry of the unshared stage (one segment only): every beam's own u decode tokens go through
   // the same MFMA path as the prompt.  The 32 query columns of a wave belong to a handful of beams
-  // (32/g of them when g divides 32).  Their K rows (then V rows) form private 32-row mini-tiles,
-  // row rho = beam_local * u + token, loaded with coalesced 16-byte pieces into the wave's own slice
-  // of the (by then idle) tile memory; S^T = K_u . Q^T is a full 32 x 32 block of which a column
+  // (32/g of them when g divides 32).  Their K rows and V rows form private 32-row mini-tiles,
+  // row rho = beam_local * u + token, which direct loads bring into the wave's own slice of LDS in the prompt tiles' layout;
+  // S^T = K_u . Q^T is a full 32 x 32 block of which a column
   // keeps only its own beam's u rows (the rest are masked to -inf), and O^T += V_u^T . P^T follows.
   // Compared with per-lane dot products this reads each beam's rows once instead of once per query
-  // head and replaces ~1000 VALU operations per lane by 16 MFMAs per wave.  The first mini-tile is
-  // fetched into registers while the last prompt tile is still being processed.
-  static_assert(NCB == 1, "one column block per wave");
+  // head and replaces ~1000 VALU operations per lane by 16 MFMAs per wave.  The first mini-tile's K is
+  // asked for while the last prompt tile is being processed, its V while the scores are made.  (Through registers the rows took 330
+  // instructions of the last tile's critical path.)
   constexpr int UR = 32;                                 // rows of a mini-tile
-  constexpr int UP = UR * PPR / 64;                      // 16-byte pieces per lane and tensor
   const bool may_own = !CAUSAL && set == 0 && (sp == 0 || sp == c.nsplit - 1) && c.u > 0;     // (known before the prompt's length is)
   const bool own_stage = may_own && sp == own_sp;
-  auto wave_rows = [&](int wv, int* first_beam) {        // rows of wave wv's mini-tiles, and its first beam
-    const int r_first = mbi * MWG + wv * 32;
-    if (r_first >= Mb) { *first_beam = 0; return 0; }
-    const int r_last = min(r_first + 31, Mb - 1);
-    *first_beam = r_first / c.g;
-    return (r_last / c.g - *first_beam + 1) * c.u;
-  };
-  int beam0 = 0, npass = 0, R = 0;
-  if (may_own) {
-    // the most beams any wave's 32 rows can span (exact when g divides 32, else an upper bound: a surplus
-    // pass only sees masked rows)
-    const int nb_max = min(c.W, (32 % c.g == 0) ? 32 / c.g : (32 + c.g - 2) / c.g + 1);
-    npass = (nb_max * c.u + UR - 1) / UR;
-    R = wave_rows(wave, &beam0);
+  int beam0 = 0, Ru = 0;                                 // the wave's first beam, and its beams' own rows
+  if (may_own && row_w < Mb) {
+    beam0 = __builtin_amdgcn_readfirstlane(small_div(row_w, c.rcp_g));
+    Ru = (__builtin_amdgcn_readfirstlane(small_div(min(row_w + 31, Mb - 1), c.rcp_g)) - beam0 + 1) * c.u;
   }
-  const int my_lo = (qrow[0] >= 0) ? (qrow[0] / c.g - beam0) * c.u : -1;         // this column's rows [my_lo, my_lo + u)
-  uint4 ukp[UP], uvp[UP];
-  const float rcp_u = 1.0f / (float)max(c.u, 1);
-  // Row of the request's own-token block behind row pass * 32 + lane % 32 of the mini-tiles (past the last one: the first's)
+  const int my_lo = (qrow[0] >= 0) ? (beam_q - beam0) * c.u : -1;                // this column's rows [my_lo, my_lo + u)
+  // Byte offset in the request's own-token block of the row behind row pass * 32 + lane % 32 of the mini-tiles (past the last one: the first's)
+  const uint32_t own_bytes = (uint32_t)c.Hkv * D * 2;
   auto own_row = [&](int pass) {
     const int rho = pass * UR + n32;
     int bl, tok;
-    divmod_small(rho < R ? rho : 0, c.u, rcp_u, &bl, &tok);
+    divmod_small(rho < Ru ? rho : 0, c.u, c.rcp_u, &bl, &tok);
     int prow = (beam0 + bl) * c.ND + tok;
-    if (c.slot && R > 0) {                                 // (an entry outside the block falls back to the beam's own row)
+    if (c.slot && Ru > 0) {                                // (an entry outside the block falls back to the beam's own row)
       const int sl = c.slot[(size_t)b * c.W * c.ND + prow];
       prow = ((unsigned)sl < (unsigned)(c.W * c.ND)) ? sl : prow;
     }
-    return prow;
+    return (uint32_t)prow * own_bytes;
   };
-  const uint16_t* ku_b = c.ku + (size_t)b * c.W * c.ND * c.Hkv * D;        // this request's own-token caches
-  const uint16_t* vu_b = c.vu + (size_t)b * c.W * c.ND * c.Hkv * D;
-  const int Ru = __builtin_amdgcn_readfirstlane(R);
-  auto uload = [&](int pass, int prow_l) {               // 32 rows x D/8 pieces per tensor; a row = PPR consecutive lanes
+  const char* ku_b = (const char*)(c.ku + (size_t)b * c.W * c.ND * c.Hkv * D + (size_t)kvh * D);        // this request's own-token caches
+  const char* vu_b = (const char*)(c.vu + (size_t)b * c.W * c.ND * c.Hkv * D + (size_t)kvh * D);
+  // element offsets from s_tiles of the wave's mini-tiles: K in place of the K tiles, which the last tile's step no longer reads, or of Q
+  const int own_k = (NWAVES == 8 ? 4 * TILE : 0) + wave_u * UR * D, own_v = (NWAVES == 8 ? 0 : 2 * TILE) + wave_u * UR * D;
+  auto uload = [&](bool is_k, uint32_t row_off, int rows) {               // the first `rows` rows of a mini-tile, and what else is in their 1 KiB chunks
 #pragma unroll
-    for (int i = 0; i < UP; i++) {
-      const int pi = lane + 64 * i, row = pi / PPR, col = (pi % PPR) * 8;
-      ukp[i] = make_uint4(0, 0, 0, 0);
-      uvp[i] = make_uint4(0, 0, 0, 0);
-      if (pass * UR + i * (64 / PPR) >= Ru) continue;      // (wave-uniform)
-      const int prow = __shfl(prow_l, row, 64);
-      if (pass * UR + row < R) {
-        const uint32_t off = (uint32_t)(prow * (c.Hkv * D) + kvh * D + col);
-        ukp[i] = *(const uint4*)(ku_b + off);
-        uvp[i] = *(const uint4*)(vu_b + off);
-      }
+    for (int i = 0; i < UR / RPC; i++) {
+      if (i * RPC >= rows) break;                          // (wave-uniform)
+      const int row = i * RPC + lane / PPR, piece = (lane % PPR) ^ (is_k ? T::swz_k(row) : T::swz_v(row));
+      dma(lds_k + (uint32_t)((is_k ? own_k : own_v) * 2 + i * 1024), is_k ? ku_b : vu_b, (uint32_t)__shfl((int)row_off, row, 64) + (uint32_t)piece * 16);
     }
   };
 
@@ -653,15 +617,29 @@ k_beam_attn(AttnCtx c) {
   auto touch = [&](const void* gbase, uint32_t off) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds_dump), "v"(off), "s"(gbase) : "memory", "m0");
   };
-  const int touch_own = own_stage && R > 0 ? max(0, ntiles - 4) : 0x7fffffff;
-  auto touch_own_rows = [&](int prow) {
-    const uint32_t off = (uint32_t)(prow * (c.Hkv * D) + kvh * D) * 2 + (D == 128 ? 128 * G : 0);
+  const int touch_own = own_stage && Ru > 0 ? max(0, ntiles - 4) : 0x7fffffff;
+  auto touch_own_rows = [&](uint32_t row_off) {
+    const uint32_t off = row_off + (D == 128 ? 128 * G : 0);
     touch(ku_b, off);
     touch(vu_b, off);
   };
 
+  // ---- Q: the workgroup's MWG query rows come into LDS like K tiles (a lane that reads its own row straight from memory touches 32 rows
+  // with every load), rows past the last one as that one: their columns are dropped.
+  {
+    constexpr int NWG = NWAVES * KS, QPW = MWG / RPC / NWG;    // 1 KiB chunks per wave
+    // this request's queries (decode: its W beams; prefill: its own tokens); offsets inside it fit 32 bits
+    const char* q_b = (const char*)(c.q + ((CAUSAL ? (size_t)row0 : (size_t)b * c.W) * c.Hq + kvh * c.g) * D);
+    const int wg_wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const uint32_t lds_q = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint16_t*)s_q;
+    const uint32_t skip = (uint32_t)(c.Hq - c.g) * D * 2;      // from a beam's last row of this KV head to the next beam's first
+#pragma unroll
+    for (int i = 0; i < QPW; i++) {
+      const int ch = i * NWG + wg_wave, rl = ch * RPC + lane / PPR, r = min(mbi * MWG + rl, Mb - 1);
+      dma(lds_q + (uint32_t)ch * 1024, q_b, (uint32_t)r * (D * 2) + (uint32_t)small_div(r, c.rcp_g) * skip + (uint32_t)(((lane % PPR) ^ T::swz_k(rl)) * 16));
+    }
+  }
   // first prompt tiles: requested before anything waits on memory; V(0) once Q has left its place where Q has no LDS of its own.
-  // (With Q on top of the K tiles all requests of 4-wave workgroups waited for it: 16 causal prompts of 60-700 tokens 46.5 -> 45.8 us.)
   Stage8 k8b;
   if (KV8) {
     if (ntiles > 0) { k8 = gload8(true, 0); v8 = gload8(false, 0); k8b = gload8(true, min(1, ntiles - 1)); }
@@ -670,26 +648,31 @@ k_beam_attn(AttnCtx c) {
     if (kQSeparate) tload(false, flip, 0);
     tload(true, flip ^ 1, min(1, ntiles - 1));
   }
-  int prow0 = may_own ? own_row(0) : 0;
+  uint32_t prow0 = may_own ? own_row(0) : 0;
   // Q as B operands: lane holds query column n32 of the wave's block, d = 16*ks + 8*G + (0..7)
   bf16x8 qop[NCB][D / 16];
   {
-#pragma unroll
-    for (int i = 0; i < QP; i++) {
-      const int p = (int)threadIdx.x + i * (NT * KS), rl = p / PPR, piece = p % PPR;
-      *(uint4*)(&s_q[rl * D + (piece ^ T::swz_k(rl)) * 8]) = qpiece[i];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int ks = 0; ks < D / 16; ks++) qop[0][ks] = as_bf16x8(*(const uint4*)(&s_q[(wave * 32 + n32) * D + ((2 * ks + G) ^ T::swz_k(n32)) * 8]));
-    if (!kQSeparate) {
-      __syncthreads();                               // the V tile slots may now be overwritten
-      if (!KV8 && ntiles > 0) tload(false, flip, 0);
-    }
-    if (KV8 && ntiles > 0) {
+    if (KV8 && kQSeparate && ntiles > 0) {
       lstore8(s_k + flip * TILE, true, k8); lstore8(s_v + flip * TILE, false, v8); lstore8(s_k + (flip ^ 1) * TILE, true, k8b);
       k8 = gload8(true, min(2, ntiles - 1));
       v8 = gload8(false, min(1, ntiles - 1));
+    }
+    // (Q and K(0), which the first scores take; what was asked for after them may be on its way.  The FP8 codes that were waited for came after Q.)
+    if (ntiles == 0) all_landed();
+    else if (!KV8) asm volatile("s_waitcnt vmcnt(%0)" ::"i"(kQSeparate ? 2 * CPW : CPW) : "memory");
+    else if (!kQSeparate) all_landed();
+    __syncthreads();
+#pragma unroll
+    for (int ks = 0; ks < D / 16; ks++) qop[0][ks] = T::read_k((int)(s_q - s_tiles) + wave_u * 32 * D, rdo, 0, ks);
+    if (!kQSeparate) {
+      __syncthreads();                               // the V tile slots may now be overwritten
+      if (!KV8 && ntiles > 0) tload(false, flip, 0);
+      if (KV8 && ntiles > 0) {
+        lstore8(s_k + flip * TILE, true, k8); lstore8(s_v + flip * TILE, false, v8); lstore8(s_k + (flip ^ 1) * TILE, true, k8b);
+        k8 = gload8(true, min(2, ntiles - 1));
+        v8 = gload8(false, min(1, ntiles - 1));
+        __syncthreads();
+      }
     }
   }
 
@@ -701,11 +684,6 @@ k_beam_attn(AttnCtx c) {
     // barrier per tile orders every buffer reuse.  Loads for tiles past the end are clamped to the
     // last tile (harmless re-reads; a duplicate K tile lands in a buffer nobody reads any more).
     const int tl = ntiles - 1;
-    // (V(0), requested last where Q had its place, may be on its way: the first step or the last tile waits for it)
-    if (!kQSeparate && !KV8) __builtin_amdgcn_s_waitcnt(0x0F70 | CPW);               // vmcnt(CPW)
-    else tiles_landed();
-    asm volatile("" : "+v"(prow0));                    // (waited for here, not at its first use)
-    __syncthreads();                                   // K(0), K(1) are in LDS, and V(0) where it was requested with them
 
     // One steady-state iteration: tile t (scores in s_in) has a successor whose scores go to s_out.  The references are settled
     // first (raising them, and rescaling O and the running sum, is a rare wave-uniform branch), so that the tile's MFMAs and
@@ -774,8 +752,8 @@ k_beam_attn(AttnCtx c) {
     auto last = [&](f32x16 (&s_in)[KT / 32][NCB], int t) {
       settle();
       all_landed();
-      if (own_stage) uload(0, prow0);
       __syncthreads();
+      if (own_stage) uload(true, prow0, Ru);               // (into the place of K tiles that nobody reads any more)
       const int tok0 = seg0 + t * KT;
       if (tok0 + KT > seg1) {
 #pragma unroll
@@ -795,6 +773,7 @@ k_beam_attn(AttnCtx c) {
 
     f32x16 s_a[KT / 32][NCB], s_b[KT / 32][NCB];      // ping-pong score accumulators: no copies
     T::qk(flip * TILE, qop, s_a, rdo);
+    asm volatile("" : "+v"(prow0));                    // (waited for here, not at its first use)
     if (ntiles > 1) {
       if (CAUSAL && seg0 + KT - 1 > wave_tok0) causal_mask(s_a, seg0);
       m_run[0] = T::colmax(s_a) * cp;                  // (every column sees the segment's first token)
@@ -818,8 +797,11 @@ k_beam_attn(AttnCtx c) {
     last(s_a, t);
   }
 
-  float* s_set1 = (float*)(smem + 4 * TILE + MWG * D);     // KS = 2: the second set's O (in place of its tiles), as its lanes hold it,
-  float* s_set1_ml = s_set1 - 512;                         // and its (maximum, sum) pairs
+  // KS = 2: the second set's O, as its lanes hold it, in place of its tiles (each wave's in the places of its mini-tiles: another may still compute its
+  // columns again in its own), and its (maximum, sum) pairs
+  uint16_t* s_set1 = smem + 4 * TILE + MWG * D;
+  auto set1_o = [&](int e) { return (f32x4*)(s_set1 + (e < D / 16 ? own_k : own_v) + (e % (D / 16)) * 512) + lane; };
+  float* s_set1_ml = (float*)s_set1 - 512;
 
   // ---- unshared stage: every beam's own u decode tokens, through the same MFMA path.
   // The 32 query columns of a wave belong to a handful of beams (32/g of them when g divides 32).
@@ -832,20 +814,15 @@ k_beam_attn(AttnCtx c) {
   if (KS == 2 && set == 1)
     for (int i = 0; i < set1_idle; i++) __syncthreads();
   if (KS == 2 || own_stage || ntiles > 0) __syncthreads(); // every wave is done with the prompt tiles
-  uint16_t* s_uk = smem + wave * UR * KSTR;
-  uint16_t* s_uv = smem + NWAVES * UR * KSTR + wave * UR * VSTR;
-  // (m, l, O) joined by 32 rows in LDS, this wave's alone; the column sees row base + k where base + k is below `rows` (as unsigned numbers).
-  // The reference is the maximum of what the column has seen, so that the best own token's probability, which may be nearly all of the sum, is
-  // 1 and not rounded.
-  auto mini_tile = [&](const uint16_t* s_uk, int kstr, const uint16_t* s_uv, int vstr, int base, unsigned rows, float cs, float& m, float& l) {
+  // (m, l, O) joined by 32 rows in LDS, this wave's alone; the column sees row base + k where base + k is below `rows` (as unsigned numbers), and rows
+  // from `used` on are seen by none.  The reference is the maximum of what the column has seen, so that the best own token's probability, which may
+  // be nearly all of the sum, is 1 and not rounded.  before_v: what has to be done before V is read.
+  auto mini_tile = [&](int base, unsigned rows, int used, float cs, float& m, float& l, auto&& before_v) {
     f32x16 su;
 #pragma unroll
     for (int i = 0; i < 16; i++) su[i] = 0.f;
 #pragma unroll
-    for (int ks = 0; ks < D / 16; ks++) {
-      const bf16x8 a = as_bf16x8(*(const uint4*)(&s_uk[n32 * kstr + ks * 16 + G * 8]));
-      su = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qop[0][ks], su, 0, 0, 0);
-    }
+    for (int ks = 0; ks < D / 16; ks++) su = __builtin_amdgcn_mfma_f32_32x32x16_bf16(T::read_k(own_k, rdo, 0, ks), qop[0][ks], su, 0, 0, 0);
 #pragma unroll
     for (int i = 0; i < 16; i++) su[i] = (unsigned)(base + 8 * (i / 4) + 4 * G + (i % 4)) < rows ? su[i] : -INFINITY;
     float mx = -INFINITY;
@@ -875,31 +852,25 @@ k_beam_attn(AttnCtx c) {
     for (int t = 0; t < UR / 16; t++)
 #pragma unroll
       for (int e = 0; e < 8; e++) pu[t][e] = (__bf16)pr[8 * t + e];
-    {
-      typedef short s16x8 __attribute__((ext_vector_type(8)));
-      const uint16_t* vb = s_uv + (4 * G + ((lane & 15) >> 2)) * vstr + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
+    before_v();
 #pragma unroll
-      for (int t = 0; t < UR / 16; t++)
+    for (int t = 0; t < UR / 16; t++) {
+      if (t > 0 && used <= 16 * t) break;                  // (wave-uniform)
 #pragma unroll
-        for (int db = 0; db < D / 32; db++) {
-          const uint16_t* p0 = vb + t * 16 * vstr + db * 32;
-          s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(p0));
-          s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(p0 + 8 * vstr));
-          s16x8 both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-          o_acc[db][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, both), pu[t], o_acc[db][0], 0, 0, 0);
-        }
+      for (int db = 0; db < D / 32; db++)
+        o_acc[db][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(T::read_v(own_v, rdo, t, db), pu[t], o_acc[db][0], 0, 0, 0);
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");                    // the mini-tiles are rewritten by the next pass
   };
   // The segment again for a wave with a column whose scores rose too fast or whose O overflowed: 32 tokens at a time through its mini-tiles,
-  // maxima first.  (The second set's waves have no more LDS to themselves than what they hand over in: their rows are not padded.)  It waits for
+  // maxima first.  It waits for
   // memory and computes by turns while the rest of the chip idles: 4 requests of 16384 tokens x 256 beams in which four wavefronts have to
   // take 571 us instead of 276 (1010 with the pieces fetched one after the other), one of 8000 x 128 49 instead of 29 (72).
   auto redo = [&]() {
-    const bool packed = KS == 2 && set == 1;
-    uint16_t* k32 = packed ? (uint16_t*)s_set1 + wave * 2 * UR * D : s_uk;
-    uint16_t* v32 = packed ? k32 + UR * D : s_uv;
-    const int kstr = packed ? D : KSTR, vstr = packed ? D : VSTR;
+    constexpr int UP = UR * PPR / 64;                      // 16-byte pieces per lane and tensor
+    uint16_t* k32 = s_tiles + own_k;
+    uint16_t* v32 = s_tiles + own_v;
+    all_landed();                                          // (the own tokens' K, which is written over)
     m_run[0] = -INFINITY; l_run[0] = 0.f;
 #pragma unroll
     for (int db = 0; db < D / 32; db++)
@@ -922,14 +893,14 @@ k_beam_attn(AttnCtx c) {
       }
 #pragma unroll
       for (int i = 0; i < UP; i++) {
-        const int pi = lane + 64 * i, row = pi / PPR, col = (pi % PPR) * 8;
-        *(f32x4*)(&k32[row * kstr + col]) = kp[i];
-        *(f32x4*)(&v32[row * vstr + col]) = vp[i];
+        const int pi = lane + 64 * i, row = pi / PPR, piece = pi % PPR;
+        *(f32x4*)(&k32[row * D + (piece ^ T::swz_k(row)) * 8]) = kp[i];
+        *(f32x4*)(&v32[row * D + (piece ^ T::swz_v(row)) * 8]) = vp[i];
       }
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");                  // (the mini-tiles are this wave's alone, and LDS serves a wave in order)
-      mini_tile(k32, kstr, v32, vstr, tok0, CAUSAL ? min((unsigned)seg1, (unsigned)tokq + 1u) : (unsigned)seg1, cp, m_run[0], l_run[0]);
+      mini_tile(tok0, CAUSAL ? min((unsigned)seg1, (unsigned)tokq + 1u) : (unsigned)seg1, UR, cp, m_run[0], l_run[0], [] {});
     }
-    if constexpr (!CAUSAL) uload(0, prow0);                // (fetched again: their registers are the prompt's in here)
+    if (own_stage) uload(true, prow0, Ru);                 // (fetched again)
   };
   if (__builtin_expect(rise, 0)) {
     float z = l_run[0] * 0.f;                              // (0 unless something is infinite or no number)
@@ -958,23 +929,22 @@ k_beam_attn(AttnCtx c) {
 #pragma unroll
     for (int e = 0; e < D / 8; e++) {
       const f32x4 v = {o_acc[e / 4][0][4 * (e % 4)], o_acc[e / 4][0][4 * (e % 4) + 1], o_acc[e / 4][0][4 * (e % 4) + 2], o_acc[e / 4][0][4 * (e % 4) + 3]};
-      *(f32x4*)(s_set1 + ((wave * (D / 8) + e) * 64 + lane) * 4) = v;
+      *set1_o(e) = v;
     }
     const f32x2 ml = {m_run[0], l_run[0]};
     *(f32x2*)(s_set1_ml + (wave * 64 + lane) * 2) = ml;
   }
   if (own_stage) {
-    if (ntiles == 0) uload(0, prow0);
-    for (int pass = 0; pass < npass; pass++) {
-#pragma unroll
-      for (int i = 0; i < UP; i++) {
-        const int pi = lane + 64 * i, row = pi / PPR, col = (pi % PPR) * 8;
-        *(uint4*)(&s_uk[row * KSTR + col]) = ukp[i];
-        *(uint4*)(&s_uv[row * VSTR + col]) = uvp[i];
-      }
-      if (pass + 1 < npass) uload(pass + 1, own_row(pass + 1));               // (arrives while this pass is computed)
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      mini_tile(s_uk, KSTR, s_uv, VSTR, pass * UR - my_lo, my_lo >= 0 ? (unsigned)c.u : 0u, c.c, m_run[0], l_run[0]);
+    if (ntiles == 0) uload(true, prow0, Ru);
+    uint32_t row_off = prow0;
+    for (int pass = 0; pass * UR < Ru; pass++) {
+      const int used = Ru - pass * UR;                     // (V: whole halves of 16 rows, whose probabilities are 0 past the last one)
+      asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");      // (K is there, and the pass before has read V)
+      uload(false, row_off, min(UR, (used + 15) & ~15));
+      mini_tile(pass * UR - my_lo, my_lo >= 0 ? (unsigned)c.u : 0u, used, c.c, m_run[0], l_run[0], [&] {
+        if (used > UR) { row_off = own_row(pass + 1); uload(true, row_off, used - UR); }       // (K has been read)
+        all_landed();
+      });
     }
   }
 
@@ -991,7 +961,7 @@ k_beam_attn(AttnCtx c) {
     m_run[0] = m_new;
 #pragma unroll
     for (int e = 0; e < D / 8; e++) {
-      const f32x4 v = *(const f32x4*)(s_set1 + ((wave * (D / 8) + e) * 64 + lane) * 4);
+      const f32x4 v = *set1_o(e);
 #pragma unroll
       for (int k = 0; k < 4; k++) o_acc[e / 4][0][4 * (e % 4) + k] = o_acc[e / 4][0][4 * (e % 4) + k] * a0 + v[k] * a1;
     }
@@ -1005,7 +975,7 @@ k_beam_attn(AttnCtx c) {
     if (c.nsplit == 1) {
       // The wave's 32 rows x D outputs go through its own slice of LDS so that global memory sees whole
       // 256-byte rows (16 lanes x 16 bytes) instead of 8-byte pieces of 32 different rows per store.
-      uint16_t* s_o = smem + wave * 32 * KSTR;
+      uint16_t* s_o = s_tiles + own_k;
       const float inv = (l_tot > 0.f) ? 1.0f / l_tot : 0.f;
 #pragma unroll
       for (int db = 0; db < D / 32; db++)
@@ -1017,24 +987,17 @@ k_beam_attn(AttnCtx c) {
           uint2 st;
           st.x = __builtin_bit_cast(uint32_t, ha);
           st.y = __builtin_bit_cast(uint32_t, hb);
-          *(uint2*)(&s_o[n32 * KSTR + db * 32 + 8 * q4 + 4 * G]) = st;
+          *(uint2*)(&s_o[n32 * D + ((4 * db + q4) ^ (n32 & (PPR - 1))) * 8 + 4 * G]) = st;
         }
-      const float rcp_g2 = 1.0f / (float)c.g;
-      uint16_t* out_b = c.out + (CAUSAL ? (size_t)row0 : (size_t)b * c.W) * c.Hq * D;
+      uint16_t* out_b = c.out + ((CAUSAL ? (size_t)row0 : (size_t)b * c.W) * c.Hq + kvh * c.g) * D;
 #pragma unroll
       for (int i = 0; i < 32 * PPR / 64; i++) {
-        const int p = lane + 64 * i, rl = p / PPR, col = (p % PPR) * 8;
-        const int rr = mbi * MWG + wave * 32 + rl;
-        int w, j;
-        divmod_small(rr, c.g, rcp_g2, &w, &j);
-        const uint4 v = *(const uint4*)(&s_o[rl * KSTR + col]);
-        if (rr < Mb) *(uint4*)(out_b + (uint32_t)((w * c.Hq + kvh * c.g + j) * D + col)) = v;
+        const int p = lane + 64 * i, rl = p / PPR, piece = p % PPR, rr = row_w + rl;
+        const uint4 v = *(const uint4*)(&s_o[rl * D + (piece ^ (rl & (PPR - 1))) * 8]);
+        if (rr < Mb) *(uint4*)(out_b + (uint32_t)((rr + small_div(rr, c.rcp_g) * (c.Hq - c.g)) * D + piece * 8)) = v;
       }
-      if (c.lse && G == 0 && r >= 0) {
-        int w, j;
-        divmod_small(r, c.g, rcp_g2, &w, &j);
-        c.lse[((CAUSAL ? (size_t)row0 : (size_t)b * c.W) + w) * c.Hq + kvh * c.g + j] = (l_tot > 0.f) ? (m + __builtin_amdgcn_logf(l_tot)) * kLn2 : -INFINITY;
-      }
+      if (c.lse && G == 0 && r >= 0)
+        c.lse[((CAUSAL ? (size_t)row0 : (size_t)b * c.W) + beam_q) * c.Hq + kvh * c.g + (r - beam_q * c.g)] = (l_tot > 0.f) ? (m + __builtin_amdgcn_logf(l_tot)) * kLn2 : -INFINITY;
     } else {
       // this segment's unnormalised fp32 partial O and (max, sum), as the lanes hold them (see k_attn_merge): every store is a run of whole lines.
       // (Staged through LDS into rows of D floats they took 2.1 us of a unit's 13.5.)
@@ -1256,6 +1219,8 @@ gr_status attn_run(const gr_attn_params* p, const int32_t* slot, bool kv8, float
   c.MB = (c.M + plan.mwg - 1) / plan.mwg;
   c.nsplit = plan.nsplit;
   c.n_groups = p->B * p->Hkv * c.nsplit;
+  c.rcp_g = 1.0f / (float)g; c.rcp_u = 1.0f / (float)(p->u > 1 ? p->u : 1);
+  c.inv_mb = div_inv((uint32_t)c.MB); c.inv_split = div_inv((uint32_t)c.nsplit); c.inv_hkv = div_inv((uint32_t)c.Hkv);
   c.c = p->sm_scale * kLog2e;
   c.k_scale = kv8 ? k_scale : 1.f; c.v_scale = kv8 ? v_scale : 1.f;
   c.q = (const uint16_t*)p->q; c.ks = (const uint16_t*)p->k_shared; c.vs = (const uint16_t*)p->v_shared;
@@ -1367,6 +1332,8 @@ extern "C" gr_status gr_prefill_attn(const gr_prefill_params* p, void* stream_) 
   c.MB = (c.M + mwg - 1) / mwg;
   c.nsplit = 1;
   c.n_groups = p->B * p->Hkv;
+  c.rcp_g = 1.0f / (float)g; c.rcp_u = 1.f;
+  c.inv_mb = div_inv((uint32_t)c.MB); c.inv_split = div_inv(1); c.inv_hkv = div_inv((uint32_t)c.Hkv);
   c.c = p->sm_scale * kLog2e;
   c.k_scale = 1.f; c.v_scale = 1.f;
   c.q = (const uint16_t*)p->q; c.ks = (const uint16_t*)p->k; c.vs = (const uint16_t*)p->v;
