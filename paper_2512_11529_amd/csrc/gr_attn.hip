@@ -30,12 +30,12 @@ constexpr int KT = 64;        // kv tokens per LDS tile
 // tiles' place for those of 4.  After the prompt loop a wavefront's 32 own-token rows take the K tiles' place (of K; Q's where 8 wavefronts hold
 // 256 rows) and the V tiles' (of V; all tiles' there), and its 32 rows of output K's again.  All of it in unpadded, swizzled rows.  Behind it 256
 // bytes per wave that loads issued only to bring lines into L2 write to.
-// Workgroups whose two halves share the prompt (ks = 2): tiles of the first half, Q, tiles of the second half.  The last 2 KiB
-// of Q's place take those 256 bytes per wave, then the second half's (maximum, sum).
+// Workgroups whose two halves share the prompt (ks = 2): each half's tiles and a place for one more (a third V tile where the head size is 128), which
+// takes half of Q at first and, after the loop, the second half's (maximum, sum).
 constexpr int attn_tiles_bytes(int d) { return 4 * KT * d * 2; }
 constexpr int attn_lds_used(int d, int mwg) { return attn_tiles_bytes(d) + (mwg == 256 ? mwg * d * 2 : 0); }
 constexpr int attn_lds_bytes(int d, int mwg, int ks) {
-  return ks == 2 ? 2 * attn_tiles_bytes(d) + mwg * d * 2 : attn_lds_used(d, mwg) + mwg / 32 * 256;
+  return ks == 2 ? 2 * 5 * KT * d * 2 : attn_lds_used(d, mwg) + mwg / 32 * 256;
 }
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
@@ -233,30 +233,43 @@ struct AttnTile {
     const int t = (32 * (j + 1) + EXP_BY - 1) / EXP_BY;
     return j < 0 ? 0 : (t > 32 ? 32 : t);
   }
-  static __device__ __forceinline__ void fused(int sk_next, int sv_cur, const bf16x8 (&qop)[NCB][D / 16],
+  // The workgroup meets before the tile's last HEAD MFMAs (0: after all), whose operands are in registers by then: loads for the tile after have landed, everybody has
+  // read K(t+1) and V(t), and the next tile's first HEAD operands are read beside those MFMAs.  With the meeting between two tiles every wave of
+  // the CU asked LDS for its first operands at once, with nothing to compute meanwhile: 8 causal prompts of 1024-8192 tokens 1210 -> 1189 us, 4 x 16384
+  // x 512 beams in FP8 456.7 -> 452.7, 64 ragged requests of 512-8192 x 256 864 -> 853.  (4 MFMAs: 1189, 450, 860, but 32 x 4096 x 256 478 instead of
+  // 476; 1: 1199, 456, 859.)
+  // `between` is called in every chunk: the loads of tiles ahead are issued there, one every second MFMA (head size 64: every one).  Issued
+  // together at the start of a tile they held all waves up while the CU's address unit worked them off: 32 x 4096 x 256 beams 486 -> 472 us, the 64
+  // ragged requests 873 -> 849, 16 x 2000 x 200 beams of head size 64 21.4 -> 20.5.
+  static constexpr int PF = 4;                           // operand reads run PF MFMAs ahead
+  static constexpr int SPREAD = D == 128 ? 2 : 1;
+  template <int HEAD, class F, class G>
+  static __device__ __forceinline__ void fused(F&& between, G&& meet, bf16x8 (&head)[PF], int sk_after, int sk_next, int sv_cur, const bf16x8 (&qop)[NCB][D / 16],
                                                const f32x16 (&s_cur)[KT / 32][NCB], f32x16 (&s_next)[KT / 32][NCB],
                                                f32x16 (&o)[D / 32][NCB], float m2, float c, float& rs, bf16x8 (&pop)[KT / 16], const Rd& rdo) {
     static_assert(NCB == 1, "one column block per wave");
     auto rdk = [&](int i) { return read_k(sk_next, rdo, i % 2, i / 2); };
     auto rdv = [&](int i) { return read_v(sv_cur, rdo, i / (D / 32), i % (D / 32)); };
-    constexpr int PF = 4;                                   // operand reads run PF MFMAs ahead
     bf16x8 a[NMF];
     float p[32], arg[32];                                   // (a few of each are alive at a time)
     rs = 0.f;
     const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int i = 0; i < PF; i++) a[i] = rdk(i);
+    for (int i = 0; i < PF; i++) a[i] = i < HEAD ? head[i < HEAD ? i : 0] : rdk(i);
 #pragma unroll
     for (int e = 0; e < exps_after(0); e++) arg[e] = fmaf(s_cur[e / 16][0][e % 16], c, -m2);
 #pragma unroll
     for (int j = 0; j < NMF; j++) {
+      if (j == NMF - HEAD) meet();
       if (j + PF < NMF) a[j + PF] = (j + PF < NQK) ? rdk(j + PF) : rdv(j + PF - NQK);
+      else if (j >= NMF - HEAD) head[j + HEAD - NMF] = read_k(sk_after, rdo, (j + HEAD - NMF) % 2, (j + HEAD - NMF) / 2);
       if (j < NQK) {
         s_next[j % 2][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[j], qop[0][j / 2], j < 2 ? zero : s_next[j % 2][0], 0, 0, 0);
       } else {
         const int i = j - NQK;
         o[i % (D / 32)][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[j], pop[i / (D / 32)], o[i % (D / 32)][0], 0, 0, 0);
       }
+      between(j);
       // the exponentials' arguments, the exponentials and their sums and packing are three stages, one chunk apart, so that none
       // waits for the one before
 #pragma unroll
@@ -282,6 +295,7 @@ struct AttnTile {
       asm volatile("" : "+v"(rs));                           // the running sum is due here, not at the end of the tile
       __builtin_amdgcn_sched_barrier(0);
     }
+    if (HEAD == 0) meet();
   }
 
   // A segment's first and last tile are searched for the columns' maxima before their probabilities are made, the tiles between only from where a
@@ -381,12 +395,20 @@ k_beam_attn(AttnCtx c) {
   // anyway) a separate region for the Q hand-over, so that the first tiles can be in flight while Q is staged; of 4 waves, K's only
   extern __shared__ __attribute__((aligned(1024))) uint16_t smem[];
   const int set = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x / NT);
-  uint16_t* s_tiles = smem + (KS == 1 ? 0 : set * (4 * TILE + MWG * D));
+  // V tiles in LDS.  Two sets of a large head have three and ask for V two tiles ahead: their units are few, so that memory's latency is waited for, and with the
+  // loads spread over the MFMAs one tile is not always enough.  us from HBM with two and three: 8 x 2048 x 128 beams 44.4, 41.9; 8 x 3000 x 128 59.6, 55.6
+  // (from the caches 37.3, 38.1; head size 64: 16 x 2000 x 200 21.6, 21.9 and 20.6, 21.0).
+  constexpr int VS = KS == 2 && D == 128 ? 3 : 2;
+  uint16_t* s_tiles = smem + set * 5 * TILE;
   uint16_t* s_k = s_tiles;
   uint16_t* s_v = s_tiles + 2 * TILE;
   constexpr bool kQSeparate = NWAVES * KS == 8;
-  uint16_t* s_q = smem + (kQSeparate ? 4 : 2) * TILE;          // (4 waves: in place of the V tiles, MWG * D = 2 * TILE)
-  static_assert(kQSeparate || MWG * D <= 2 * TILE, "Q fits the V tiles' place");
+  // (workgroups of 4 waves meet between tiles: another one on the CU computes meanwhile, and waits for memory are longer the earlier a tile's loads have to
+  // have landed; 16 prompts of 60-700 tokens 36.2 us with 3, 35.6)
+  constexpr int HEAD = NWAVES * KS == 4 ? 0 : D == 128 ? 3 : 2;
+  // Q's rows: behind the tiles, of two sets half of them behind either's; of 4 waves, in place of the V tiles
+  static_assert(NWAVES == 8 || MWG * D == 2 * TILE, "Q fits the V tiles' place");
+  auto q_at = [&](int row) { return KS == 2 ? 4 * TILE + row * D + (row >= MWG / 2 ? 5 * TILE - TILE : 0) : (kQSeparate ? 4 : 2) * TILE + row * D; };
 
   const int tid = (int)threadIdx.x % NT, wave = tid >> 6, lane = tid & 63, G = lane >> 5, n32 = lane & 31;
 
@@ -482,14 +504,14 @@ k_beam_attn(AttnCtx c) {
   // ch * RPC + l / PPR, and therefore fetches piece slot ^ swz(row) of that row.  Rows past the end of the segment
   // (last tile only) re-read the last valid row: finite values that the -inf score mask (K) and zero probabilities
   // (V) make irrelevant.  The loads are issued from inline assembly so that the compiler, which cannot tell the
-  // tile buffers apart, does not make every later LDS read wait for them; `tiles_landed` waits for all of this
+  // tile buffers apart, does not make every later LDS read wait for them; `all_landed` waits for all of this
   // wave's loads, and the barrier that follows publishes every wave's.
   constexpr int EB = KV8 ? 1 : 2;                            // bytes per stored K/V element
   const uint32_t tok_bytes = (uint32_t)c.Hkv * D * EB;      // bytes between consecutive tokens
   const char* kbase = (const char*)c.ks + ((size_t)row0 * c.Hkv + kvh) * D * EB;
   const char* vbase = (const char*)c.vs + ((size_t)row0 * c.Hkv + kvh) * D * EB;
   const float cp = KV8 ? c.c * c.k_scale : c.c;              // exponent scale of the prompt loop
-  const typename T::Rd rdo = T::make_rd(lane, (int)(uintptr_t)(__attribute__((address_space(3))) uint16_t*)s_tiles);
+  typename T::Rd rdo = T::make_rd(lane, (int)(uintptr_t)(__attribute__((address_space(3))) uint16_t*)s_tiles);
   int crow[CPW];                                             // this lane's row inside a tile, per chunk
   uint32_t koff[CPW], voff[CPW];                             // and its byte offsets from the tile's first row (full tiles)
 #pragma unroll
@@ -504,46 +526,58 @@ k_beam_attn(AttnCtx c) {
   auto dma = [&](uint32_t lds_addr, const char* gbase, uint32_t off) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr), "v"(off), "s"(gbase) : "memory", "m0");
   };
-  auto tload = [&](bool is_k, int buf, int t) {
-    const int tok0 = seg0 + t * KT;                          // wave-uniform
-    const char* tile = (is_k ? kbase : vbase) + (size_t)tok0 * tok_bytes;
-    const uint32_t lds0 = (is_k ? lds_k : lds_v) + (uint32_t)buf * (TILE * 2);
-    const int nvalid = seg1 - tok0;                          // >= 1
-    if (nvalid >= KT) {
+  struct Tile { const char* base; uint32_t off[CPW]; };
+  auto tile_at = [&](bool is_k, int t) __attribute__((always_inline)) {
+    const int tok0 = seg0 + t * KT, nvalid = seg1 - tok0;    // (wave-uniform; nvalid >= 1)
+    Tile at;
+    at.base = (is_k ? kbase : vbase) + (size_t)tok0 * tok_bytes;
 #pragma unroll
-      for (int i = 0; i < CPW; i++) dma(lds0 + (uint32_t)(i * NWAVES + wave_u) * 1024, tile, is_k ? koff[i] : voff[i]);
-    } else {
+    for (int i = 0; i < CPW; i++) at.off[i] = is_k ? koff[i] : voff[i];
+    if (nvalid < KT) {
 #pragma unroll
       for (int i = 0; i < CPW; i++) {
         const int row = min(crow[i], nvalid - 1), slot = lane % PPR;
-        const uint32_t off = (uint32_t)row * tok_bytes + (uint32_t)((slot ^ (is_k ? T::swz_k(crow[i]) : T::swz_v(crow[i]))) * 16);
-        dma(lds0 + (uint32_t)(i * NWAVES + wave_u) * 1024, tile, off);
+        at.off[i] = (uint32_t)row * tok_bytes + (uint32_t)((slot ^ (is_k ? T::swz_k(crow[i]) : T::swz_v(crow[i]))) * 16);
       }
     }
+    return at;
+  };
+  auto tload_chunk = [&](bool is_k, int buf, const Tile& at, int i) {
+    dma((is_k ? lds_k : lds_v) + (uint32_t)(buf * (TILE * 2) + (i * NWAVES + wave_u) * 1024), at.base, at.off[i]);
+  };
+  auto tload = [&](bool is_k, int buf, int t) {
+    const Tile at = tile_at(is_k, t);
+#pragma unroll
+    for (int i = 0; i < CPW; i++) tload_chunk(is_k, buf, at, i);
   };
   auto all_landed = [&]() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); };
-  auto tiles_landed = [&]() { if (!KV8) all_landed(); };
   // FP8 tiles: piece p = tid + i * NT of a tile = 8 codes of row p / PPR; registers one tile ahead
   constexpr int P8 = KT * PPR / NT;                          // pieces per thread and tile
   struct Stage8 { uint2 r[P8]; };
   uint32_t off8[P8];                                         // byte offsets of this thread's pieces inside a full tile
 #pragma unroll
   for (int i = 0; i < P8; i++) { const int p = tid + i * NT; off8[i] = (uint32_t)(p / PPR) * tok_bytes + (uint32_t)(p % PPR) * 8; }
-  auto gload8 = [&](bool is_k, int t) {
-    const int tok0 = seg0 + t * KT;
-    const char* tile = (is_k ? kbase : vbase) + (size_t)tok0 * tok_bytes;
-    const int nvalid = seg1 - tok0;                          // >= 1; rows past the end re-read the last valid row
-    Stage8 st;
-    if (nvalid >= KT) {
+  struct Tile8 { const char* base; uint32_t off[P8]; };
+  auto tile8_at = [&](bool is_k, int t) __attribute__((always_inline)) {
+    const int tok0 = seg0 + t * KT, nvalid = seg1 - tok0;    // (wave-uniform; nvalid >= 1); rows past the end re-read the last valid row
+    Tile8 at;
+    at.base = (is_k ? kbase : vbase) + (size_t)tok0 * tok_bytes;
 #pragma unroll
-      for (int i = 0; i < P8; i++) st.r[i] = *(const uint2*)(tile + off8[i]);
-    } else {
+    for (int i = 0; i < P8; i++) at.off[i] = off8[i];
+    if (nvalid < KT) {
 #pragma unroll
       for (int i = 0; i < P8; i++) {
-        const int p = tid + i * NT, row = min(p / PPR, nvalid - 1), col = p % PPR;
-        st.r[i] = *(const uint2*)(tile + (size_t)row * tok_bytes + col * 8);
+        const int p = tid + i * NT;
+        at.off[i] = (uint32_t)min(p / PPR, nvalid - 1) * tok_bytes + (uint32_t)(p % PPR) * 8;
       }
     }
+    return at;
+  };
+  auto gload8 = [&](bool is_k, int t) {
+    const Tile8 at = tile8_at(is_k, t);
+    Stage8 st;
+#pragma unroll
+    for (int i = 0; i < P8; i++) st.r[i] = *(const uint2*)(at.base + at.off[i]);
     return st;
   };
   auto widen8 = [](uint2 r) {
@@ -556,12 +590,13 @@ k_beam_attn(AttnCtx c) {
     v.z = __builtin_bit_cast(uint32_t, e45); v.w = __builtin_bit_cast(uint32_t, e67);
     return v;
   };
+  auto lstore8_piece = [&](uint16_t* dst, bool is_k, uint2 codes, int i) {
+    const int p = tid + i * NT, row = p / PPR, slot = (p % PPR) ^ (is_k ? T::swz_k(row) : T::swz_v(row));
+    *(uint4*)(dst + row * D + slot * 8) = widen8(codes);
+  };
   auto lstore8 = [&](uint16_t* dst, bool is_k, const Stage8& st) {
 #pragma unroll
-    for (int i = 0; i < P8; i++) {
-      const int p = tid + i * NT, row = p / PPR, slot = (p % PPR) ^ (is_k ? T::swz_k(row) : T::swz_v(row));
-      *(uint4*)(dst + row * D + slot * 8) = widen8(st.r[i]);
-    }
+    for (int i = 0; i < P8; i++) lstore8_piece(dst, is_k, st.r[i], i);
   };
   Stage8 k8, v8;
 
@@ -612,16 +647,16 @@ k_beam_attn(AttnCtx c) {
 
   // The own-token rows are what the end of a unit waits for: they are asked for three tiles before the last one, one 4-byte load
   // per 128-byte line into LDS that nobody reads, so that the loads into registers (which have no room earlier) find them in L2.
-  const uint32_t lds_dump = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint16_t*)smem +
-                            (KS == 2 ? attn_tiles_bytes(D) + MWG * D * 2 - 2048 + set * 1024 : attn_lds_used(D, MWG)) + (uint32_t)wave_u * 256;
-  auto touch = [&](const void* gbase, uint32_t off) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds_dump), "v"(off), "s"(gbase) : "memory", "m0");
+  const uint32_t lds_dump = KS == 2 ? lds_k + 4 * TILE * 2 + (uint32_t)wave_u * 256 : lds_k + attn_lds_used(D, MWG) + (uint32_t)wave_u * 256;
+  auto touch = [&](uint32_t dump, const void* gbase, uint32_t off) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(dump), "v"(off), "s"(gbase) : "memory", "m0");
   };
-  const int touch_own = own_stage && Ru > 0 ? max(0, ntiles - 4) : 0x7fffffff;
-  auto touch_own_rows = [&](uint32_t row_off) {
+  // (with three V tiles: one tile before the last one, when the place of the V tile after that is free)
+  const int touch_own = own_stage && Ru > 0 ? max(0, ntiles - (VS == 3 ? 2 : 4)) : 0x7fffffff;
+  auto touch_own_rows = [&](uint32_t dump, uint32_t row_off) {
     const uint32_t off = row_off + (D == 128 ? 128 * G : 0);
-    touch(ku_b, off);
-    touch(vu_b, off);
+    touch(dump, ku_b, off);
+    touch(dump, vu_b, off);
   };
 
   // ---- Q: the workgroup's MWG query rows come into LDS like K tiles (a lane that reads its own row straight from memory touches 32 rows
@@ -631,12 +666,12 @@ k_beam_attn(AttnCtx c) {
     // this request's queries (decode: its W beams; prefill: its own tokens); offsets inside it fit 32 bits
     const char* q_b = (const char*)(c.q + ((CAUSAL ? (size_t)row0 : (size_t)b * c.W) * c.Hq + kvh * c.g) * D);
     const int wg_wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    const uint32_t lds_q = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint16_t*)s_q;
+    const uint32_t lds_0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint16_t*)smem;
     const uint32_t skip = (uint32_t)(c.Hq - c.g) * D * 2;      // from a beam's last row of this KV head to the next beam's first
 #pragma unroll
     for (int i = 0; i < QPW; i++) {
       const int ch = i * NWG + wg_wave, rl = ch * RPC + lane / PPR, r = min(mbi * MWG + rl, Mb - 1);
-      dma(lds_q + (uint32_t)ch * 1024, q_b, (uint32_t)r * (D * 2) + (uint32_t)small_div(r, c.rcp_g) * skip + (uint32_t)(((lane % PPR) ^ T::swz_k(rl)) * 16));
+      dma(lds_0 + (uint32_t)q_at(ch * RPC) * 2, q_b, (uint32_t)r * (D * 2) + (uint32_t)small_div(r, c.rcp_g) * skip + (uint32_t)(((lane % PPR) ^ T::swz_k(rl)) * 16));
     }
   }
   // first prompt tiles: requested before anything waits on memory; V(0) once Q has left its place where Q has no LDS of its own.
@@ -645,25 +680,26 @@ k_beam_attn(AttnCtx c) {
     if (ntiles > 0) { k8 = gload8(true, 0); v8 = gload8(false, 0); k8b = gload8(true, min(1, ntiles - 1)); }
   } else if (ntiles > 0) {
     tload(true, flip, 0);
-    if (kQSeparate) tload(false, flip, 0);
+    if (kQSeparate) tload(false, VS == 3 ? 0 : flip, 0);
     tload(true, flip ^ 1, min(1, ntiles - 1));
+    if (VS == 3) tload(false, 1, min(1, ntiles - 1));
   }
   uint32_t prow0 = may_own ? own_row(0) : 0;
   // Q as B operands: lane holds query column n32 of the wave's block, d = 16*ks + 8*G + (0..7)
   bf16x8 qop[NCB][D / 16];
   {
     if (KV8 && kQSeparate && ntiles > 0) {
-      lstore8(s_k + flip * TILE, true, k8); lstore8(s_v + flip * TILE, false, v8); lstore8(s_k + (flip ^ 1) * TILE, true, k8b);
+      lstore8(s_k + flip * TILE, true, k8); lstore8(s_v + (VS == 3 ? 0 : flip * TILE), false, v8); lstore8(s_k + (flip ^ 1) * TILE, true, k8b);
       k8 = gload8(true, min(2, ntiles - 1));
       v8 = gload8(false, min(1, ntiles - 1));
     }
     // (Q and K(0), which the first scores take; what was asked for after them may be on its way.  The FP8 codes that were waited for came after Q.)
     if (ntiles == 0) all_landed();
-    else if (!KV8) asm volatile("s_waitcnt vmcnt(%0)" ::"i"(kQSeparate ? 2 * CPW : CPW) : "memory");
+    else if (!KV8) asm volatile("s_waitcnt vmcnt(%0)" ::"i"((kQSeparate ? VS : 1) * CPW) : "memory");
     else if (!kQSeparate) all_landed();
     __syncthreads();
 #pragma unroll
-    for (int ks = 0; ks < D / 16; ks++) qop[0][ks] = T::read_k((int)(s_q - s_tiles) + wave_u * 32 * D, rdo, 0, ks);
+    for (int ks = 0; ks < D / 16; ks++) qop[0][ks] = T::read_k(q_at(wave_u * 32) - (int)(s_tiles - smem), rdo, 0, ks);
     if (!kQSeparate) {
       __syncthreads();                               // the V tile slots may now be overwritten
       if (!KV8 && ntiles > 0) tload(false, flip, 0);
@@ -680,8 +716,8 @@ k_beam_attn(AttnCtx c) {
   bool rise = false, again = false;                    // some column's scores rose far above its reference; too far
   if (ntiles > 0) {
     // Pipeline: iteration t issues S(t+1) = K(t+1).Q^T together with the softmax of S(t), then O += V(t).P(t).
-    // K(t+2) and V(t+1) are written to LDS right after the barrier that opens iteration t, so one
-    // barrier per tile orders every buffer reuse.  Loads for tiles past the end are clamped to the
+    // Meanwhile K(t+2) and V(t+1) are on their way into LDS, in the places of K(t) and V(t-1), which everybody had read when the
+    // workgroup met near the end of the iteration before: one barrier per tile orders every buffer reuse.  Loads for tiles past the end are clamped to the
     // last tile (harmless re-reads; a duplicate K tile lands in a buffer nobody reads any more).
     const int tl = ntiles - 1;
 
@@ -729,30 +765,49 @@ k_beam_attn(AttnCtx c) {
           s[sub][0][i] = (kv > tokq) ? -INFINITY : s[sub][0][i];
         }
     };
+    // (inline assembly, so that no read of LDS is moved ahead of it; FP8 tiles are written by ds_write)
+    auto meet = [&]() __attribute__((always_inline)) {
+      if (KV8) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      else asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"i"(VS == 3 ? CPW : 0) : "memory");      // (three V tiles: the last one asked for is not needed yet)
+    };
+    bf16x8 head[T::PF];
+    int vs = 0;                                        // three V tiles: the place of V(t), which rdo.v has in it
     auto step = [&](auto slot_c, f32x16 (&s_in)[KT / 32][NCB], f32x16 (&s_out)[KT / 32][NCB], int t) {      // tile t in slot slot_c
       constexpr int slot = decltype(slot_c)::value;
       settle();
       if (CAUSAL && seg0 + t * KT + KT - 1 > wave_tok0) causal_mask(s_in, seg0 + t * KT);       // (wave-uniform) past the wave's first token
       if (__builtin_expect(rise, 0)) raise_to(T::colmax(s_in) * cp);
-      tiles_landed();                                               // this wave's K(t+1) and V(t) loads (issued one step ago)
-      __syncthreads();                                              // everyone's; and everyone is done with K(t) and V(t-1)
-      if (KV8) {
-        lstore8(s_k + slot * TILE, true, k8);                       // K(t+2) over K(t)
-        lstore8(s_v + (slot ^ 1) * TILE, false, v8);                // V(t+1) over V(t-1)
-        k8 = gload8(true, min(t + 3, tl));
-        v8 = gload8(false, min(t + 2, tl));
-      } else {
-        tload(true, slot, min(t + 2, tl));                          // K(t+2) over K(t)
-        tload(false, slot ^ 1, min(t + 1, tl));                     // V(t+1) over V(t-1)
+      const int v_to = VS == 3 ? (vs == 0 ? 2 : vs - 1) : slot ^ 1;
+      if (t == touch_own) touch_own_rows(VS == 3 ? lds_v + (uint32_t)v_to * (TILE * 2) + (uint32_t)wave_u * 256 : lds_dump, prow0);
+      const Tile k_t = tile_at(true, min(t + 2, tl)), v_t = tile_at(false, min(t + VS - 1, tl));
+      const Tile8 k8_t = tile8_at(true, min(t + 3, tl)), v8_t = tile8_at(false, min(t + 2, tl));
+      T::template fused<HEAD>([&](int j) __attribute__((always_inline)) {
+        const int i = j / T::SPREAD;
+        if (KV8) {
+          if (j % T::SPREAD || i >= 2 * P8) return;
+          if (i < P8) {
+            lstore8_piece(s_k + slot * TILE, true, k8.r[i], i);     // K(t+2) over K(t)
+            k8.r[i] = *(const uint2*)(k8_t.base + k8_t.off[i]);     // K(t+3)
+          } else {
+            lstore8_piece(s_v + (VS == 3 ? (vs == 2 ? 0 : vs + 1) : slot ^ 1) * TILE, false, v8.r[i - P8], i - P8);       // V(t+1)
+            v8.r[i - P8] = *(const uint2*)(v8_t.base + v8_t.off[i - P8]);              // V(t+2)
+          }
+          return;
+        }
+        if (j % T::SPREAD || i >= 2 * CPW) return;
+        if (i < CPW) tload_chunk(true, slot, k_t, i);               // K(t+2) over K(t)
+        else tload_chunk(false, v_to, v_t, i - CPW);                // V(t+1), of three V tiles V(t+2), over V(t-1)
+      }, meet, head, slot * TILE, (slot ^ 1) * TILE, (VS == 3 ? 2 : 2 + slot) * TILE, qop, s_in, s_out, o_acc, m_run[0], cp, rs, pop, rdo);
+      if (VS == 3) {
+        const int on = (vs == 2 ? -2 : 1) * (TILE * 2);
+#pragma unroll
+        for (int db = 0; db < D / 32; db++) rdo.v[db] += on;
+        vs = vs == 2 ? 0 : vs + 1;
       }
-      if (t == touch_own) touch_own_rows(prow0);
-      T::fused((slot ^ 1) * TILE, (2 + slot) * TILE, qop, s_in, s_out, o_acc, m_run[0], cp, rs, pop, rdo);
     };
     // the last tile of the segment: the only one that can be partial, and it has no successor
     auto last = [&](f32x16 (&s_in)[KT / 32][NCB], int t) {
       settle();
-      all_landed();
-      __syncthreads();
       if (own_stage) uload(true, prow0, Ru);               // (into the place of K tiles that nobody reads any more)
       const int tok0 = seg0 + t * KT;
       if (tok0 + KT > seg1) {
@@ -769,6 +824,11 @@ k_beam_attn(AttnCtx c) {
       if (t == 0) m_run[0] = top; else raise_to(top);
       T::finish(2 * TILE, s_in, o_acc, m_run[0], cp, rs, rdo);
       l_run[0] += rs;
+      if (VS == 3) {
+        all_landed();                                  // (the copy of the last V tile that came for nothing, before its place is used)
+#pragma unroll
+        for (int db = 0; db < D / 32; db++) rdo.v[db] -= vs * (TILE * 2);
+      }
     };
 
     f32x16 s_a[KT / 32][NCB], s_b[KT / 32][NCB];      // ping-pong score accumulators: no copies
@@ -778,6 +838,11 @@ k_beam_attn(AttnCtx c) {
       if (CAUSAL && seg0 + KT - 1 > wave_tok0) causal_mask(s_a, seg0);
       m_run[0] = T::colmax(s_a) * cp;                  // (every column sees the segment's first token)
       rise = __any(m_run[0] > T::kWide);
+    }
+    meet();                                            // K(1) and V(0) are there
+    if (ntiles > 1) {
+#pragma unroll
+      for (int i = 0; i < HEAD; i++) head[i] = T::read_k((flip ^ 1) * TILE, rdo, i % 2, i / 2);
     }
     // ntiles - 1 steps, then the last tile.  An odd step is peeled off first so that the loop runs
     // whole ping-pong pairs and the last tile is always in s_a.
@@ -799,9 +864,9 @@ k_beam_attn(AttnCtx c) {
 
   // KS = 2: the second set's O, as its lanes hold it, in place of its tiles (each wave's in the places of its mini-tiles: another may still compute its
   // columns again in its own), and its (maximum, sum) pairs
-  uint16_t* s_set1 = smem + 4 * TILE + MWG * D;
+  uint16_t* s_set1 = smem + 5 * TILE;
   auto set1_o = [&](int e) { return (f32x4*)(s_set1 + (e < D / 16 ? own_k : own_v) + (e % (D / 16)) * 512) + lane; };
-  float* s_set1_ml = (float*)s_set1 - 512;
+  float* s_set1_ml = (float*)(s_set1 + 4 * TILE);
 
   // ---- unshared stage: every beam's own u decode tokens, through the same MFMA path.
   // The 32 query columns of a wave belong to a handful of beams (32/g of them when g divides 32).

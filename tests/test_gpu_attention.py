@@ -345,3 +345,16 @@ def test_partials_of_blocks_that_are_not_full(gr, oracle_lib, d, W, Hq, Hkv):
         _check(gr, oracle_lib, a, float(np.float32(1 / np.sqrt(d))))
     finally:
         gr.gr_diag_attn_plan(0, 0)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("rows,copies", [(128, 1), (128, 12), (256, 1)])      # two sets of wavefronts, workgroups of 4, of 8
+def test_prompts_of_every_number_of_tiles(gr, oracle_lib, d, rows, copies):
+    # tiles ahead are asked for in places that come round after two or three tiles: prompts of 1 to 8 tiles, whole and not
+    lens = (1, 64, 65, 128, 129, 192, 193, 256, 257, 320, 321, 449) * copies
+    a = rand_attn_case(d + rows, len(lens), 3, 4, 2, d, 3, 2, lens)
+    gr.gr_diag_attn_plan(rows, 1)
+    try:
+        _check(gr, oracle_lib, a, float(np.float32(1 / np.sqrt(d))))
+    finally:
+        gr.gr_diag_attn_plan(0, 0)
