@@ -512,73 +512,68 @@ k_beam_attn(AttnCtx c) {
   const char* vbase = (const char*)c.vs + ((size_t)row0 * c.Hkv + kvh) * D * EB;
   const float cp = KV8 ? c.c * c.k_scale : c.c;              // exponent scale of the prompt loop
   typename T::Rd rdo = T::make_rd(lane, (int)(uintptr_t)(__attribute__((address_space(3))) uint16_t*)s_tiles);
-  int crow[CPW];                                             // this lane's row inside a tile, per chunk
-  uint32_t koff[CPW], voff[CPW];                             // and its byte offsets from the tile's first row (full tiles)
+  // this lane's byte offsets from the tile's first row, per chunk (rows up to `most`)
+  auto tile_offsets = [&](uint32_t (&off)[CPW], bool is_k, int most) {
 #pragma unroll
-  for (int i = 0; i < CPW; i++) {
-    const int ch = i * NWAVES + wave, row = ch * RPC + lane / PPR, slot = lane % PPR;
-    crow[i] = row;
-    koff[i] = (uint32_t)row * tok_bytes + (uint32_t)((slot ^ T::swz_k(row)) * 16);
-    voff[i] = (uint32_t)row * tok_bytes + (uint32_t)((slot ^ T::swz_v(row)) * 16);
-  }
+    for (int i = 0; i < CPW; i++) {
+      const int row = (i * NWAVES + wave) * RPC + lane / PPR, slot = lane % PPR;
+      off[i] = (uint32_t)min(row, most) * tok_bytes + (uint32_t)((slot ^ (is_k ? T::swz_k(row) : T::swz_v(row))) * 16);
+    }
+  };
   const uint32_t lds_k = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint16_t*)s_k;
   const uint32_t lds_v = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint16_t*)s_v;
   auto dma = [&](uint32_t lds_addr, const char* gbase, uint32_t off) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr), "v"(off), "s"(gbase) : "memory", "m0");
   };
-  struct Tile { const char* base; uint32_t off[CPW]; };
-  auto tile_at = [&](bool is_k, int t) __attribute__((always_inline)) {
-    const int tok0 = seg0 + t * KT, nvalid = seg1 - tok0;    // (wave-uniform; nvalid >= 1)
-    Tile at;
-    at.base = (is_k ? kbase : vbase) + (size_t)tok0 * tok_bytes;
-#pragma unroll
-    for (int i = 0; i < CPW; i++) at.off[i] = is_k ? koff[i] : voff[i];
-    if (nvalid < KT) {
-#pragma unroll
-      for (int i = 0; i < CPW; i++) {
-        const int row = min(crow[i], nvalid - 1), slot = lane % PPR;
-        at.off[i] = (uint32_t)row * tok_bytes + (uint32_t)((slot ^ (is_k ? T::swz_k(crow[i]) : T::swz_v(crow[i]))) * 16);
-      }
-    }
-    return at;
+  // Tiles are asked for in their order, the last one again and again: the next one's address goes up by a tile, and when it is the last one, the only
+  // one that can be partial, the offsets become its own.  (Worked out from its number, with a look at how full it is, a tile's
+  // addresses were half of what stood between the MFMAs of two tiles: 64 ragged requests of 512-8192 x 256 beams 856 -> 845 us, 32 x 4096 x 256 476 -> 470.)
+  const int tl = ntiles - 1;
+  const int last_row = seg1 - (seg0 + tl * KT) - 1;          // of the last tile
+  const size_t tile_bytes = (size_t)KT * tok_bytes;
+  const char* k_at = kbase + (size_t)seg0 * tok_bytes;
+  const char* v_at = vbase + (size_t)seg0 * tok_bytes;
+  uint32_t koff[CPW], voff[CPW];
+  auto tload_chunk = [&](bool is_k, int buf, int i) {
+    dma((is_k ? lds_k : lds_v) + (uint32_t)(buf * (TILE * 2) + (i * NWAVES + wave_u) * 1024), is_k ? k_at : v_at, is_k ? koff[i] : voff[i]);
   };
-  auto tload_chunk = [&](bool is_k, int buf, const Tile& at, int i) {
-    dma((is_k ? lds_k : lds_v) + (uint32_t)(buf * (TILE * 2) + (i * NWAVES + wave_u) * 1024), at.base, at.off[i]);
-  };
-  auto tload = [&](bool is_k, int buf, int t) {
-    const Tile at = tile_at(is_k, t);
+  auto tload = [&](bool is_k, int buf) {
 #pragma unroll
-    for (int i = 0; i < CPW; i++) tload_chunk(is_k, buf, at, i);
+    for (int i = 0; i < CPW; i++) tload_chunk(is_k, buf, i);
   };
   auto all_landed = [&]() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); };
   // FP8 tiles: piece p = tid + i * NT of a tile = 8 codes of row p / PPR; registers one tile ahead
   constexpr int P8 = KT * PPR / NT;                          // pieces per thread and tile
   struct Stage8 { uint2 r[P8]; };
-  uint32_t off8[P8];                                         // byte offsets of this thread's pieces inside a full tile
+  uint32_t off8[P8];                                         // byte offsets of this thread's pieces inside a tile
 #pragma unroll
   for (int i = 0; i < P8; i++) { const int p = tid + i * NT; off8[i] = (uint32_t)(p / PPR) * tok_bytes + (uint32_t)(p % PPR) * 8; }
-  struct Tile8 { const char* base; uint32_t off[P8]; };
-  auto tile8_at = [&](bool is_k, int t) __attribute__((always_inline)) {
-    const int tok0 = seg0 + t * KT, nvalid = seg1 - tok0;    // (wave-uniform; nvalid >= 1); rows past the end re-read the last valid row
-    Tile8 at;
-    at.base = (is_k ? kbase : vbase) + (size_t)tok0 * tok_bytes;
-#pragma unroll
-    for (int i = 0; i < P8; i++) at.off[i] = off8[i];
-    if (nvalid < KT) {
-#pragma unroll
-      for (int i = 0; i < P8; i++) {
-        const int p = tid + i * NT;
-        at.off[i] = (uint32_t)min(p / PPR, nvalid - 1) * tok_bytes + (uint32_t)(p % PPR) * 8;
-      }
-    }
-    return at;
+  // (pieces past the segment's last row read as 0, by the loads' bounds check: the bytes from the tile's first row to the segment's end)
+  uint32_t k_left = (uint32_t)(seg1 - seg0) * tok_bytes, v_left = k_left;
+  auto gload8_piece = [&](bool is_k, int i) {
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    const u32x2 r = __builtin_amdgcn_raw_buffer_load_b64(
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(is_k ? k_at : v_at), 0, is_k ? k_left : v_left, 0x00020000), (int)off8[i], 0, 0);
+    return make_uint2(r.x, r.y);
   };
-  auto gload8 = [&](bool is_k, int t) {
-    const Tile8 at = tile8_at(is_k, t);
+  auto gload8 = [&](bool is_k) {
     Stage8 st;
 #pragma unroll
-    for (int i = 0; i < P8; i++) st.r[i] = *(const uint2*)(at.base + at.off[i]);
+    for (int i = 0; i < P8; i++) st.r[i] = gload8_piece(is_k, i);
     return st;
+  };
+  auto offsets_of_last = [&](bool is_k) {
+    if (!KV8 && last_row < KT - 1) tile_offsets(is_k ? koff : voff, is_k, last_row);
+  };
+  // to the next tile, or back
+  auto advance = [&](bool is_k, bool back) __attribute__((always_inline)) {
+    (is_k ? k_at : v_at) += back ? -(ptrdiff_t)tile_bytes : (ptrdiff_t)tile_bytes;
+    if (KV8) (is_k ? k_left : v_left) += back ? (uint32_t)tile_bytes : 0u - (uint32_t)tile_bytes;
+  };
+  // the address of tile `to`, from that of the one before
+  auto go_to = [&](bool is_k, int to) {
+    if (to <= tl) advance(is_k, false);
+    if (to == tl) offsets_of_last(is_k);
   };
   auto widen8 = [](uint2 r) {
     const bf16x2 e01 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8((int)r.x, 1.0f, false);
@@ -590,9 +585,11 @@ k_beam_attn(AttnCtx c) {
     v.z = __builtin_bit_cast(uint32_t, e45); v.w = __builtin_bit_cast(uint32_t, e67);
     return v;
   };
+  // (a thread's pieces are 16 rows or a multiple apart, in the same place of each: one address for all)
+  static_assert(NT / PPR % 16 == 0, "swizzles repeat every 16 rows");
+  const int row8 = tid / PPR, k8_to = row8 * D + ((tid % PPR) ^ T::swz_k(row8)) * 8, v8_to = row8 * D + ((tid % PPR) ^ T::swz_v(row8)) * 8;
   auto lstore8_piece = [&](uint16_t* dst, bool is_k, uint2 codes, int i) {
-    const int p = tid + i * NT, row = p / PPR, slot = (p % PPR) ^ (is_k ? T::swz_k(row) : T::swz_v(row));
-    *(uint4*)(dst + row * D + slot * 8) = widen8(codes);
+    *(uint4*)(dst + (is_k ? k8_to : v8_to) + i * (NT / PPR) * D) = widen8(codes);
   };
   auto lstore8 = [&](uint16_t* dst, bool is_k, const Stage8& st) {
 #pragma unroll
@@ -674,15 +671,21 @@ k_beam_attn(AttnCtx c) {
       dma(lds_0 + (uint32_t)q_at(ch * RPC) * 2, q_b, (uint32_t)r * (D * 2) + (uint32_t)small_div(r, c.rcp_g) * skip + (uint32_t)(((lane % PPR) ^ T::swz_k(rl)) * 16));
     }
   }
+  if (!KV8) {
+    tile_offsets(koff, true, KT - 1);
+    tile_offsets(voff, false, KT - 1);
+    if (tl == 0) { offsets_of_last(true); offsets_of_last(false); }
+  }
   // first prompt tiles: requested before anything waits on memory; V(0) once Q has left its place where Q has no LDS of its own.
   Stage8 k8b;
   if (KV8) {
-    if (ntiles > 0) { k8 = gload8(true, 0); v8 = gload8(false, 0); k8b = gload8(true, min(1, ntiles - 1)); }
+    if (ntiles > 0) { k8 = gload8(true); v8 = gload8(false); go_to(true, 1); k8b = gload8(true); }
   } else if (ntiles > 0) {
-    tload(true, flip, 0);
-    if (kQSeparate) tload(false, VS == 3 ? 0 : flip, 0);
-    tload(true, flip ^ 1, min(1, ntiles - 1));
-    if (VS == 3) tload(false, 1, min(1, ntiles - 1));
+    tload(true, flip);
+    if (kQSeparate) tload(false, VS == 3 ? 0 : flip);
+    go_to(true, 1);
+    tload(true, flip ^ 1);
+    if (VS == 3) { go_to(false, 1); tload(false, 1); }
   }
   uint32_t prow0 = may_own ? own_row(0) : 0;
   // Q as B operands: lane holds query column n32 of the wave's block, d = 16*ks + 8*G + (0..7)
@@ -690,8 +693,9 @@ k_beam_attn(AttnCtx c) {
   {
     if (KV8 && kQSeparate && ntiles > 0) {
       lstore8(s_k + flip * TILE, true, k8); lstore8(s_v + (VS == 3 ? 0 : flip * TILE), false, v8); lstore8(s_k + (flip ^ 1) * TILE, true, k8b);
-      k8 = gload8(true, min(2, ntiles - 1));
-      v8 = gload8(false, min(1, ntiles - 1));
+      go_to(true, 2); go_to(false, 1);
+      k8 = gload8(true);
+      v8 = gload8(false);
     }
     // (Q and K(0), which the first scores take; what was asked for after them may be on its way.  The FP8 codes that were waited for came after Q.)
     if (ntiles == 0) all_landed();
@@ -702,11 +706,12 @@ k_beam_attn(AttnCtx c) {
     for (int ks = 0; ks < D / 16; ks++) qop[0][ks] = T::read_k(q_at(wave_u * 32) - (int)(s_tiles - smem), rdo, 0, ks);
     if (!kQSeparate) {
       __syncthreads();                               // the V tile slots may now be overwritten
-      if (!KV8 && ntiles > 0) tload(false, flip, 0);
+      if (!KV8 && ntiles > 0) tload(false, flip);
       if (KV8 && ntiles > 0) {
         lstore8(s_k + flip * TILE, true, k8); lstore8(s_v + flip * TILE, false, v8); lstore8(s_k + (flip ^ 1) * TILE, true, k8b);
-        k8 = gload8(true, min(2, ntiles - 1));
-        v8 = gload8(false, min(1, ntiles - 1));
+        go_to(true, 2); go_to(false, 1);
+        k8 = gload8(true);
+        v8 = gload8(false);
         __syncthreads();
       }
     }
@@ -719,7 +724,6 @@ k_beam_attn(AttnCtx c) {
     // Meanwhile K(t+2) and V(t+1) are on their way into LDS, in the places of K(t) and V(t-1), which everybody had read when the
     // workgroup met near the end of the iteration before: one barrier per tile orders every buffer reuse.  Loads for tiles past the end are clamped to the
     // last tile (harmless re-reads; a duplicate K tile lands in a buffer nobody reads any more).
-    const int tl = ntiles - 1;
 
     // One steady-state iteration: tile t (scores in s_in) has a successor whose scores go to s_out.  The references are settled
     // first (raising them, and rescaling O and the running sum, is a rare wave-uniform branch), so that the tile's MFMAs and
@@ -734,9 +738,9 @@ k_beam_attn(AttnCtx c) {
       l_run[0] *= alpha;
       rounded *= alpha;
     };
+    auto rose = [&]() __attribute__((always_inline)) { return __any(!(rs <= T::kRaise)); };
     auto settle = [&]() __attribute__((always_inline)) {       // by the sum of the tile before
-      l_run[0] += rs;
-      if (__builtin_expect(!rise && __any(!(rs <= T::kRaise)), 0)) {
+      if (KS == 2 ? __builtin_expect(!rise && rose(), 0) : !rise && rose()) {
         rise = true;
         const float r = halves_max(rs);
         again = again || __any(!(r <= T::kTooHigh));
@@ -771,32 +775,45 @@ k_beam_attn(AttnCtx c) {
       else asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"i"(VS == 3 ? CPW : 0) : "memory");      // (three V tiles: the last one asked for is not needed yet)
     };
     bf16x8 head[T::PF];
+    constexpr int kAheadK = KV8 ? 3 : 2, kAheadV = KV8 ? 2 : VS - 1;       // step t asks for tiles t + kAhead
+    const int seldom = min(tl - kAheadK, touch_own);
     int vs = 0;                                        // three V tiles: the place of V(t), which rdo.v has in it
     auto step = [&](auto slot_c, f32x16 (&s_in)[KT / 32][NCB], f32x16 (&s_out)[KT / 32][NCB], int t) {      // tile t in slot slot_c
       constexpr int slot = decltype(slot_c)::value;
-      settle();
+      l_run[0] += rs;
       if (CAUSAL && seg0 + t * KT + KT - 1 > wave_tok0) causal_mask(s_in, seg0 + t * KT);       // (wave-uniform) past the wave's first token
-      if (__builtin_expect(rise, 0)) raise_to(T::colmax(s_in) * cp);
+      // (one branch where the tiles are many; two sets, whose kernels are short of registers, spilled with it: FP8 codes, 12 x 900 x 60 beams 21.4 us, 19.2)
+      if (KS == 2) {
+        settle();
+        if (__builtin_expect(rise, 0)) raise_to(T::colmax(s_in) * cp);
+      } else if (__builtin_expect(rise || rose(), 0)) {
+        settle();
+        raise_to(T::colmax(s_in) * cp);
+      }
       const int v_to = VS == 3 ? (vs == 0 ? 2 : vs - 1) : slot ^ 1;
-      if (t == touch_own) touch_own_rows(VS == 3 ? lds_v + (uint32_t)v_to * (TILE * 2) + (uint32_t)wave_u * 256 : lds_dump, prow0);
-      const Tile k_t = tile_at(true, min(t + 2, tl)), v_t = tile_at(false, min(t + VS - 1, tl));
-      const Tile8 k8_t = tile8_at(true, min(t + 3, tl)), v8_t = tile8_at(false, min(t + 2, tl));
+      advance(true, false);
+      advance(false, false);
+      if (__builtin_expect(t >= seldom, KS == 2)) {                               // (one test for what the last steps have to do)
+        if (t == touch_own) touch_own_rows(VS == 3 ? lds_v + (uint32_t)v_to * (TILE * 2) + (uint32_t)wave_u * 256 : lds_dump, prow0);
+        if (t + kAheadK >= tl) { if (t + kAheadK > tl) advance(true, true); else offsets_of_last(true); }
+        if (t + kAheadV >= tl) { if (t + kAheadV > tl) advance(false, true); else offsets_of_last(false); }
+      }
       T::template fused<HEAD>([&](int j) __attribute__((always_inline)) {
         const int i = j / T::SPREAD;
         if (KV8) {
           if (j % T::SPREAD || i >= 2 * P8) return;
           if (i < P8) {
             lstore8_piece(s_k + slot * TILE, true, k8.r[i], i);     // K(t+2) over K(t)
-            k8.r[i] = *(const uint2*)(k8_t.base + k8_t.off[i]);     // K(t+3)
+            k8.r[i] = gload8_piece(true, i);                        // K(t+3)
           } else {
             lstore8_piece(s_v + (VS == 3 ? (vs == 2 ? 0 : vs + 1) : slot ^ 1) * TILE, false, v8.r[i - P8], i - P8);       // V(t+1)
-            v8.r[i - P8] = *(const uint2*)(v8_t.base + v8_t.off[i - P8]);              // V(t+2)
+            v8.r[i - P8] = gload8_piece(false, i - P8);             // V(t+2)
           }
           return;
         }
         if (j % T::SPREAD || i >= 2 * CPW) return;
-        if (i < CPW) tload_chunk(true, slot, k_t, i);               // K(t+2) over K(t)
-        else tload_chunk(false, v_to, v_t, i - CPW);                // V(t+1), of three V tiles V(t+2), over V(t-1)
+        if (i < CPW) tload_chunk(true, slot, i);               // K(t+2) over K(t)
+        else tload_chunk(false, v_to, i - CPW);                // V(t+1), of three V tiles V(t+2), over V(t-1)
       }, meet, head, slot * TILE, (slot ^ 1) * TILE, (VS == 3 ? 2 : 2 + slot) * TILE, qop, s_in, s_out, o_acc, m_run[0], cp, rs, pop, rdo);
       if (VS == 3) {
         const int on = (vs == 2 ? -2 : 1) * (TILE * 2);
@@ -807,6 +824,7 @@ k_beam_attn(AttnCtx c) {
     };
     // the last tile of the segment: the only one that can be partial, and it has no successor
     auto last = [&](f32x16 (&s_in)[KT / 32][NCB], int t) {
+      l_run[0] += rs;
       settle();
       if (own_stage) uload(true, prow0, Ru);               // (into the place of K tiles that nobody reads any more)
       const int tok0 = seg0 + t * KT;
