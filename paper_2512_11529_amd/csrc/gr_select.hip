@@ -36,6 +36,7 @@ constexpr int kSelThreads = 1024;
 constexpr int kListCap = 8192;      // survivors that fit in LDS
 constexpr int kChunkCap = 4096;     // keys whose candidates are looked at again by the fast path
 constexpr int kUnitCap = 8192;      // units of four candidates that are
+constexpr int kFewMax = 192;        // candidates that are counted against each other
 constexpr int kDirectQuads = 512;   // quads of scores of short gathered rows that are all taken at once
 constexpr int kHistBins = 2048;
 constexpr int kMaxMaskWords = 1024; // V <= 32768
@@ -252,6 +253,20 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
   return v;
 }
 
+// lanes of the mask in front of this one
+__device__ __forceinline__ uint32_t rank_below(uint64_t mask) {
+  return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0));
+}
+
+// sum over aligned groups of 1 << sh lanes, sh = 2 to 4
+__device__ __forceinline__ int lanes_sum(int v, int sh) {
+  v += __builtin_amdgcn_update_dpp(0, v, kXor1, 0xf, 0xf, true);
+  v += __builtin_amdgcn_update_dpp(0, v, kXor2, 0xf, 0xf, true);
+  if (sh > 2) v += __builtin_amdgcn_update_dpp(0, v, kHalfMirror, 0xf, 0xf, true);
+  if (sh > 3) v += __builtin_amdgcn_update_dpp(0, v, kMirror, 0xf, 0xf, true);
+  return v;
+}
+
 // Workgroup reductions with ONE barrier each: the per-wavefront partials go to one of two slot sets, used
 // alternately (every thread makes the same sequence of calls: `par` counts them), so a wavefront that is
 // already writing the next reduction's partials cannot disturb a slower one that still reads this one's; the
@@ -409,8 +424,8 @@ struct PickLds {
   uint64_t list[kPickCap], tmp[kPickCap];
   uint32_t hist[kHistBins];
   uint32_t red[2 * 8];
-  float low[2][8];                     // per wavefront: the logit down to which the threshold is looked for
-  uint32_t others[2][8];               // and whether it saw another live row of the request
+  float top[8], low[8];                // per wavefront: the best logit, the logit down to which the threshold is looked for
+  uint32_t others[8];                  // and whether it saw another live row of the request
   uint32_t n, crowded;
   int thr;
 };
@@ -437,71 +452,18 @@ __device__ __forceinline__ float key16_low(float best, uint32_t key) { return be
 
 __device__ __forceinline__ void mark_dead(const SelCtx& c, int row) { c.row_info[row] = ROW_DEAD; }
 
-// The W best of one row's candidates, which the workgroup holds in registers (thread t: tokens 4 (t + NT i) + j), written as the
-// request's new beams; lo = a score that few lie below (none where all fit in the list).  False where they are too many for it (thousands of
-// scores as good as equal), or the W-th lies below lo; nothing is written then.
-template <int NT>
-__device__ __forceinline__ bool row_pick(const SelCtx& c, const MaskView& mv, PickLds& P, int row, const float (&xv)[kBlockV / NT], float bias, float hi, float lo) {
-  int tid = threadIdx.x;
-  asm volatile("" : "+v"(tid));                              // (what follows from it is not made ahead of the loop over rows and spilled)
-  int par = 0;
-  // threshold that W candidates reach
-  const Bins bins = make_bins(hi, hi - lo);
-#pragma unroll
-  for (int e = 0; e < kBlockV / NT; e++)
-    if (xv[e] > -INFINITY) atomicAdd(&P.hist[bins.of(__fadd_rn(bias, xv[e]))], 1u);
-  __syncthreads();
-  const uint32_t total = hist_threshold_all<NT>(P.hist, (uint32_t)c.W, &P.thr, P.red, par);
-  __syncthreads();
-  const float T = bins.floor_of(P.thr);
-  if (T == kNoThreshold && total >= (uint32_t)c.W) return false;
-  // what reaches it (all of fewer than W), in bins of one width
-  const float end = T == kNoThreshold ? lo : T, scale = hi > end ? fminf((float)(kHistBins - 1) / (hi - end), 1e30f) : 0.f;
-#pragma unroll
-  for (int e = 0; e < kBlockV / NT; e++) {
-    const float score = __fadd_rn(bias, xv[e]);
-    if (!(score >= T)) continue;
-    atomicAdd(&P.hist[key_bin(hi, scale, score)], 1u);
-    const uint32_t pos = atomicAdd(&P.n, 1u);
-    if (pos < (uint32_t)kPickCap) P.list[pos] = composite(score, (uint32_t)(4 * (tid + NT * (e / 4)) + (e & 3)));
-  }
-  __syncthreads();
-  const int n = (int)P.n;
-  bool fits = n <= kPickCap;
-  if (fits) {
-    if (hist_prefix<NT>(P.hist, (uint32_t)c.W, &P.thr, P.red, par) > 128u) P.crowded = 1u;
-    __syncthreads();
-    fits = !P.crowded;
-  }
-  if (!fits) {
-    __syncthreads();                                         // (the next row clears what this was seen by)
-    return false;
-  }
-  const int cut = P.thr, m = cut < kHistBins - 1 ? (int)P.hist[cut + 1] : n;
-  __syncthreads();                                           // (the bin after the cut is read before any counter moves)
-  order_by_bins<NT>(P.list, P.tmp, P.hist, n, m, cut, hi, scale);
-  const LateArgs late = late_args();
-  for (int j = tid; j < late->W; j += NT) {
-    const size_t o = (size_t)row + j;
-    int32_t* po = late->prefix_out + o * late->depth;
-    int token = -1, r_lo = 0, r_hi = 0;
-    float score = -INFINITY;
-    if (j < m) {
-      const uint64_t key = P.list[j];
-      token = (int)(0xffffffffu - (uint32_t)key);
-      score = gr_ordkey_inv((uint32_t)(key >> 32));
-      if (late->blob) { r_lo = mv.off1[token]; r_hi = mv.off1[token + 1]; }
-    }
-    late->parent_out[o] = j < m ? 0 : -1;
-    late->token_out[o] = token;
-    late->scores_out[o] = score;
-    po[0] = token;
-    for (int k = 1; k < late->depth; k++) po[k] = -1;
-    late->range_out[2 * o] = r_lo;
-    late->range_out[2 * o + 1] = r_hi;
-    if (late->item_index_out) late->item_index_out[o] = -1;
-  }
-  return true;
+// What a streamed row leaves, by one wavefront; keys: the best logit of every line.
+__device__ __forceinline__ void row_leaves(const SelCtx& c, int row, float bias, float best, const float* keys) {
+  const int tid = threadIdx.x & 63;
+  if (tid == 0) { c.row_bias[row] = bias; c.row_info[row] = ROW_DENSE; }
+  const float4 kl = *(const float4*)&keys[4 * tid];
+  const float k0 = __fadd_rn(bias, kl.x), k1 = __fadd_rn(bias, kl.y), k2 = __fadd_rn(bias, kl.z), k3 = __fadd_rn(bias, kl.w);      // (bias is finite)
+  uint2 packed;
+  packed.x = key16(best, k0) | (key16(best, k1) << 16);
+  packed.y = key16(best, k2) | (key16(best, k3) << 16);
+  *(uint2*)(c.row_data + (size_t)row * kRowFloats + 2 * tid) = packed;
+  const float group = quad_max(max_raw(max_raw(k0, k1), max_raw(k2, k3)));
+  if ((tid & 3) == 0) c.row_group[(size_t)row * kGroups + (tid >> 2)] = group;
 }
 
 // Bound: HBM and, close behind, the fp64 exponentials: 8192 rows of 8192 logits take 53 us = 5.1 TB/s, of which the vector
@@ -511,13 +473,8 @@ __device__ __forceinline__ bool row_pick(const SelCtx& c, const MaskView& mv, Pi
 // `row` is live; t1 = first token of its prefix (level 1), [start, start + n_list) = its children where they were looked up
 // (all wave-uniform).  Every wavefront works relative to its own maximum and the workgroup meets once: the first wavefront then joins
 // the (max, sum) pairs and writes the row's results, while the others are free for the next row (or gone).
-//
-// PICK (level 0): the row is its request's first.  Where `rivals`, the scores of the request's other rows, are all dead, the workgroup, which
-// holds all of the request's candidates in registers, selects the W best too.  k_select then only finds that it is done: a level-0
-// step of 8 x 128 beams over 8192 tokens 18.0 -> 12.9 us, of 128 x 256 18.8 -> 13.6, of one x 16 over 256 13.4 -> 10.1.
-template <int NT, bool PICK>
-__device__ __forceinline__ void row_dense(const SelCtx& c, const MaskView& mv, RowLds<NT>& L, int row, float s_in, int t1, int start, int n_list, int set,
-                                          PickLds* P = nullptr, float2 rivals = {0.f, 0.f}) {
+template <int NT>
+__device__ __forceinline__ void row_dense(const SelCtx& c, const MaskView& mv, RowLds<NT>& L, int row, float s_in, int t1, int start, int n_list, int set) {
   constexpr int NV4 = kBlockV / 4 / NT, NWV = NT / 64;        // float4 per thread; wavefronts
   const int tid = threadIdx.x, wave = tid >> 6, V = c.V;
   const float* x = c.logits + (size_t)row * V;
@@ -667,29 +624,9 @@ __device__ __forceinline__ void row_dense(const SelCtx& c, const MaskView& mv, R
       if (!b1) key[2 * b2 + b0] = r;
     }
   }
-  if constexpr (PICK) {
-    // down to where the threshold is looked for: the worst of all where they fit in the list (W may be most of them: 163 beams over 256
-    // tokens gave up with the best of every four, 17.9 us instead of 11.2), else the worst of the threads' best of a load
-    float low = INFINITY;
-    static_assert(kPickCap == 4 * NT, "a list of one load");
-    if (V <= kPickCap) {
-#pragma unroll
-      for (int j = 0; j < 4; j++) low = fminf(low, xv[j] > -INFINITY ? xv[j] : INFINITY);
-    } else {
-#pragma unroll
-      for (int i = 0; i < NV4; i++) low = fminf(low, lmax[i] > -INFINITY ? lmax[i] : INFINITY);
-    }
-    low = -wave_max(-low);
-    const bool any = __any(rivals.x > -INFINITY || rivals.y > -INFINITY);
-    if ((tid & 63) == 0) { P->low[set][wave] = low; P->others[set][wave] = any; }
-    for (int i = tid; i < kHistBins; i += NT) P->hist[i] = 0;
-    if (tid == 0) { P->n = 0; P->crowded = 0; }
-  }
   __syncthreads();
+  if (wave != 0) return;
   const int lane = tid & 63;
-  bool pick = false;
-  if (PICK) pick = !__any(lane < NWV && P->others[set][lane & (NWV - 1)]);       // (the same for all wavefronts)
-  if (wave != 0 && !pick) return;
   m = (lane < NWV) ? L.m[set][lane] : -INFINITY;
   S = (lane < NWV) ? L.s[set][lane] : 0.0;
   const float M = wave_max(m);
@@ -701,25 +638,262 @@ __device__ __forceinline__ void row_dense(const SelCtx& c, const MaskView& mv, R
   const float lse = (float)((double)M + log(T));
   const float bias = __fsub_rn(s_in, lse);
   const float best = __fadd_rn(bias, M);
-  if constexpr (PICK) {
-    if (pick) {
-      const float low = -wave_max(lane < NWV ? -P->low[set][lane & (NWV - 1)] : -INFINITY);
-      if (row_pick<NT>(c, mv, *P, row, xv, bias, best, __fadd_rn(bias, low))) {
-        if (tid == 0) c.row_info[row] = ROW_DONE;
-        return;
-      }
-      if (wave != 0) return;
+  row_leaves(c, row, bias, best, L.key[set]);
+}
+
+// Level 0, where as a rule one row of a request is live, its first: this is that row.  Where the request's other rows are all dead, the workgroup, which holds
+// all of the request's candidates in registers, selects the W best too, and k_select then only finds that it is done: a level-0
+// step of 8 x 128 beams over 8192 tokens 18.0 -> 12.9 us, of 128 x 256 18.8 -> 13.6, of one x 16 over 256 13.4 -> 10.1.
+//
+// Bound: the chain of steps in one workgroup.  So the row's logits are asked for before it is known to be live; the threshold that W candidates
+// reach is looked for among the logits, beside the exponentials (rounding a sum is monotone: what reaches a logit reaches its score); it is
+// found among the best of every four where they are enough; candidates get their places a wavefront at a time, and few of them
+// are counted against each other.  A call without and with these, us: one request x 16 beams over 256 tokens 10.1, 9.5; one x 128 over 8192 12.5, 11.4; 8 x 128
+// 13.3, 12.2.
+constexpr int kPickFew = 128;          // candidates that are counted against each other
+template <int NT>
+__device__ __forceinline__ void row_first(const SelCtx& c, const MaskView& mv, RowLds<NT>& L, PickLds& P, int row) {
+  constexpr int NV4 = kBlockV / 4 / NT, NWV = NT / 64;        // float4 per thread; wavefronts
+  static_assert(NV4 == 4 && NWV == 8 && kPickW <= 2 * NT && kPickCap == 4 * NT, "a list of one load, two other rows to a thread");
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));                              // (what follows from it is not made ahead of the loop over rows and spilled)
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), V = c.V, words = (V + 31) >> 5;
+  const float* x = c.logits + (size_t)row * V;
+  const bool all_valid = !c.blob;
+  const __amdgpu_buffer_rsrc_t rx = buffer_of(x, (uint32_t)(V & ~3) * 4);
+  u32x4 xr[NV4];
+  uint32_t mw[NV4];
+#pragma unroll
+  for (int i = 0; i < NV4; i++) xr[i] = __builtin_amdgcn_raw_buffer_load_b128(rx, 16 * tid + i * (NT * 16), 0, 0);
+  const float s_in = c.scores_in[row];
+  float rival0 = -INFINITY, rival1 = -INFINITY;
+  if (1 + tid < c.W) rival0 = c.scores_in[row + 1 + tid];
+  if (1 + tid + NT < c.W) rival1 = c.scores_in[row + 1 + tid + NT];
+  if (!all_valid && !mv.ok) {
+    if (tid == 0) mark_dead(c, row);
+    return;
+  }
+  if (!all_valid) {
+    const __amdgpu_buffer_rsrc_t rm = buffer_of(mv.l0, (uint32_t)words * 4);
+#pragma unroll
+    for (int i = 0; i < NV4; i++) mw[i] = __builtin_amdgcn_raw_buffer_load_b32(rm, (tid >> 3) * 4 + i * (NT / 2), 0, 0);
+  }
+  fill_exp_tab(L.tab, NT);
+  for (int i = tid; i < kHistBins; i += NT) P.hist[i] = 0;
+  if (tid == 0) { P.n = 0; P.crowded = 0; }
+  if (!(s_in > -INFINITY)) {
+    if (tid == 0) mark_dead(c, row);
+    return;
+  }
+  // validity bits and the row's tail as in row_dense
+  uint32_t vbits = 0xffffu;
+  const bool whole = all_valid && V == kBlockV;
+  if (!whole) {
+    vbits = 0;
+#pragma unroll
+    for (int i = 0; i < NV4; i++) {
+      const int left = V - 4 * (tid + i * NT);
+      const uint32_t w = !all_valid ? mw[i] >> (4 * (tid & 7)) : left >= 4 ? 0xfu : left > 0 ? (1u << left) - 1u : 0u;
+      vbits |= (w & 0xfu) << (4 * i);
     }
   }
-  if (tid == 0) { c.row_bias[row] = bias; c.row_info[row] = ROW_DENSE; }
-  const float4 kl = *(const float4*)&L.key[set][4 * tid];
-  const float k0 = __fadd_rn(bias, kl.x), k1 = __fadd_rn(bias, kl.y), k2 = __fadd_rn(bias, kl.z), k3 = __fadd_rn(bias, kl.w);      // (bias is finite)
-  uint2 packed;
-  packed.x = key16(best, k0) | (key16(best, k1) << 16);
-  packed.y = key16(best, k2) | (key16(best, k3) << 16);
-  *(uint2*)(c.row_data + (size_t)row * kRowFloats + 2 * tid) = packed;
-  const float group = quad_max(max_raw(max_raw(k0, k1), max_raw(k2, k3)));
-  if ((tid & 3) == 0) c.row_group[(size_t)row * kGroups + (tid >> 2)] = group;
+  const int tail = V >> 2;
+  if ((V & 3) && (tail & (NT - 1)) == tid) {
+    u32x4 t = {0, 0, 0, 0};
+    const float* xt = x + (V & ~3);
+    t.x = __float_as_uint(xt[0]);
+    if ((V & 3) > 1) t.y = __float_as_uint(xt[1]);
+    if ((V & 3) > 2) t.z = __float_as_uint(xt[2]);
+#pragma unroll
+    for (int i = 0; i < NV4; i++) if (i == tail / NT) xr[i] = t;
+  }
+  float xv[4 * NV4], best4[NV4];                             // best4: of each load
+#pragma unroll
+  for (int i = 0; i < NV4; i++) {
+    xv[4 * i] = __uint_as_float(xr[i].x); xv[4 * i + 1] = __uint_as_float(xr[i].y);
+    xv[4 * i + 2] = __uint_as_float(xr[i].z); xv[4 * i + 3] = __uint_as_float(xr[i].w);
+  }
+  if (!whole) {
+#pragma unroll
+    for (int e = 0; e < 4 * NV4; e++) xv[e] = keep_if_bit(xv[e], vbits, e);
+  }
+#pragma unroll
+  for (int i = 0; i < NV4; i++) best4[i] = max_raw(max_raw(xv[4 * i], xv[4 * i + 1]), max_raw(xv[4 * i + 2], xv[4 * i + 3]));
+  const float mb = wave_max(max_raw(max_raw(best4[0], best4[1]), max_raw(best4[2], best4[3])));
+  // down to where the threshold is looked for: the worst of all where they fit in the list (W may be most of them: 163 beams over 256
+  // tokens gave up with the best of every four, 17.9 us instead of 11.2), else the worst of the threads' best of a load
+  float low = INFINITY;
+  if (V <= kPickCap) {
+#pragma unroll
+    for (int j = 0; j < 4; j++) low = fminf(low, xv[j] > -INFINITY ? xv[j] : INFINITY);
+  } else {
+#pragma unroll
+    for (int i = 0; i < NV4; i++) low = fminf(low, best4[i] > -INFINITY ? best4[i] : INFINITY);
+  }
+  low = -wave_max(-low);
+  const bool any = __any(rival0 > -INFINITY || rival1 > -INFINITY);
+  if (lane == 0) { P.top[wave] = mb; P.low[wave] = low; P.others[wave] = any; }
+  __syncthreads();                                           // (publishes the table and the empty histogram too)
+  const float hi = wave_max(lane < NWV ? P.top[lane & (NWV - 1)] : -INFINITY), lo = -wave_max(lane < NWV ? -P.low[lane & (NWV - 1)] : -INFINITY);
+  const bool pick = !__any(lane < NWV && P.others[lane & (NWV - 1)]);
+  if (!(hi > -INFINITY)) {
+    if (tid == 0) mark_dead(c, row);
+    return;
+  }
+  const Bins bins = make_bins(hi, hi - lo);
+  const bool by_load = 4 * c.W <= V;
+  if (pick) {
+    if (by_load) {
+#pragma unroll
+      for (int i = 0; i < NV4; i++)
+        if (best4[i] > -INFINITY) atomicAdd(&P.hist[bins.of(best4[i])], 1u);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4 * NV4; e++)
+        if (xv[e] > -INFINITY) atomicAdd(&P.hist[bins.of(xv[e])], 1u);
+    }
+  }
+  // the wavefront's sum relative to its own maximum, as in row_dense
+  const ExpK ek = exp_consts();
+  double S = 0.0;
+  if (mb > -INFINITY) {
+    const double rc = -(double)mb * ek.c;
+    const float cap = mb - 600.f;
+    bool packed = false;
+    if (!whole) {
+      const uint32_t mine = (uint32_t)__popc(vbits), incl = wave_incl_scan(mine);
+      const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+      packed = total <= (uint32_t)(kBlockV / NWV / 4);
+      if (packed) {
+        float* q = L.q[wave];
+        uint32_t pos = incl - mine;
+#pragma unroll
+        for (int e = 0; e < 4 * NV4; e++)
+          if ((vbits >> e) & 1u) q[pos++] = xv[e];
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll 1
+        for (uint32_t i = lane; i < total; i += 64) S = exp_add(S, max_raw(q[i], cap), rc, L.tab, ek);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      }
+    }
+    if (!packed) {
+#pragma unroll
+      for (int i = 0; i < NV4; i++) {
+        if (4 * NT * i < V) {                      // (uniform)
+#pragma unroll
+          for (int j = 0; j < 4; j++) S = exp_add(S, max_raw(xv[4 * i + j], cap), rc, L.tab, ek);
+        }
+        asm volatile("" : "+v"(S)::"memory");
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  }
+  S = wave_sum(S);
+  if (lane == 0) { L.m[0][wave] = mb; L.s[0][wave] = S; }
+  __syncthreads();
+  const float m_w = (lane < NWV) ? L.m[0][lane & (NWV - 1)] : -INFINITY;
+  const double Sw = (lane < NWV) ? L.s[0][lane & (NWV - 1)] : 0.0;
+  const double total_S = wave_sum(Sw * exp_rel(max_raw(m_w, hi - 600.f), -(double)hi * ek.c, L.tab, ek));
+  const float lse = (float)((double)hi + log(total_S));
+  const float bias = __fsub_rn(s_in, lse), best = __fadd_rn(bias, hi);
+  // what the row leaves for k_select where it does not select
+  auto leave = [&]() {
+    {
+      const bool b2 = tid & 4, b0 = tid & 1, b1 = tid & 2;
+      float v[2];
+#pragma unroll
+      for (int i = 0; i < 2; i++) v[i] = half_max<kHalfMirror>(best4[i], best4[i + 2], b2);
+      float r = half_max<kXor1>(v[0], v[1], b0);
+      r = max_raw(r, dpp_f32<kXor2>(r));
+      if (!b1) L.key[0][(tid >> 3) * NV4 + 2 * b2 + b0] = r;
+    }
+    __syncthreads();
+    if (wave == 0) row_leaves(c, row, bias, best, L.key[0]);
+  };
+  if (!pick) { leave(); return; }
+  int par = 0;
+  uint32_t total = hist_threshold_all<NT>(P.hist, (uint32_t)c.W, &P.thr, P.red, par);
+  __syncthreads();
+  float T = bins.floor_of(P.thr);
+  if (by_load && (T == kNoThreshold || total < (uint32_t)c.W)) {        // (too few of them, or the W-th is among the lowest: all candidates)
+#pragma unroll
+    for (int e = 0; e < 4 * NV4; e++)
+      if (xv[e] > -INFINITY) atomicAdd(&P.hist[bins.of(xv[e])], 1u);
+    __syncthreads();
+    total = hist_threshold_all<NT>(P.hist, (uint32_t)c.W, &P.thr, P.red, par);
+    __syncthreads();
+    T = bins.floor_of(P.thr);
+  }
+  if (T == kNoThreshold && total >= (uint32_t)c.W) { leave(); return; }        // (the W-th lies below lo)
+  // what reaches it (all of fewer than W), in bins of one width
+  if (T > kNoThreshold) T = __fadd_rn(bias, T);
+  const float end = T == kNoThreshold ? __fadd_rn(bias, lo) : T, scale = best > end ? fminf((float)(kHistBins - 1) / (best - end), 1e30f) : 0.f;
+  uint32_t in = 0;
+#pragma unroll
+  for (int e = 0; e < 4 * NV4; e++) {
+    xv[e] = __fadd_rn(bias, xv[e]);                          // (scores from here on)
+    in |= (xv[e] >= T ? 1u : 0u) << e;
+  }
+  const uint32_t count = (uint32_t)__popc(in), incl = wave_incl_scan(count);
+  uint32_t at = 0;
+  if (lane == 63) at = atomicAdd(&P.n, incl);
+  at = (uint32_t)__builtin_amdgcn_readlane((int)at, 63) + incl - count;
+#pragma unroll
+  for (int e = 0; e < 4 * NV4; e++) {
+    if (!((in >> e) & 1u)) continue;
+    atomicAdd(&P.hist[key_bin(best, scale, xv[e])], 1u);
+    if (at < (uint32_t)kPickCap) P.list[at] = composite(xv[e], (uint32_t)(4 * (tid + NT * (e / 4)) + (e & 3)));
+    at++;
+  }
+  __syncthreads();
+  const int n = (int)P.n;
+  const LateArgs late = late_args();
+  auto emit = [&](int j, bool some, uint64_t key) {
+    const size_t o = (size_t)row + j;
+    int32_t* po = late->prefix_out + o * late->depth;
+    int token = -1, r_lo = 0, r_hi = 0;
+    float score = -INFINITY;
+    if (some) {
+      token = (int)(0xffffffffu - (uint32_t)key);
+      score = gr_ordkey_inv((uint32_t)(key >> 32));
+      if (late->blob) { r_lo = mv.off1[token]; r_hi = mv.off1[token + 1]; }
+    }
+    late->parent_out[o] = some ? 0 : -1;
+    late->token_out[o] = token;
+    late->scores_out[o] = score;
+    po[0] = token;
+    for (int k = 1; k < late->depth; k++) po[k] = -1;
+    late->range_out[2 * o] = r_lo;
+    late->range_out[2 * o + 1] = r_hi;
+    if (late->item_index_out) late->item_index_out[o] = -1;
+  };
+  if (tid == 0) c.row_info[row] = ROW_DONE;
+  if (n <= kPickFew) {
+    const int sh = n <= 32 ? 4 : n <= 64 ? 3 : 2, i = tid >> sh;
+    uint64_t key = 0;
+    int better = 0;
+    if (i < n) {
+      key = P.list[i];
+#pragma unroll 4
+      for (int j = tid & ((1 << sh) - 1); j < n; j += 1 << sh) better += P.list[j] > key;
+    }
+    better = lanes_sum(better, sh);
+    const bool mine = i < n && (tid & ((1 << sh) - 1)) == 0;
+    if (mine && better < late->W) emit(better, true, key);
+    for (int j = n + tid; j < late->W; j += NT) emit(j, false, 0);
+    return;
+  }
+  bool fits = n <= kPickCap;
+  if (fits) {
+    if (hist_prefix<NT>(P.hist, (uint32_t)c.W, &P.thr, P.red, par) > 128u) P.crowded = 1u;
+    __syncthreads();
+    fits = !P.crowded;
+  }
+  if (!fits) { leave(); return; }
+  const int cut = P.thr, m = cut < kHistBins - 1 ? (int)P.hist[cut + 1] : n;
+  __syncthreads();                                           // (the bin after the cut is read before any counter moves)
+  order_by_bins<NT>(P.list, P.tmp, P.hist, n, m, cut, best, scale);
+  for (int j = tid; j < late->W; j += NT) emit(j, j < m, j < m ? P.list[j] : 0);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -959,11 +1133,20 @@ __global__ void __launch_bounds__(NT, STRIDE ? 4 : 6) k_rows(SelCtx c) {
     int start = 0, n = 0;
     if (c.blob && c.step == 2) row_children(c, mv, row, &start, &n);
     __syncthreads();
-    row_dense<NT, false>(c, mv, L, row, s_in, t1, start, n, 0);
+    row_dense<NT>(c, mv, L, row, s_in, t1, start, n, 0);
   } else {
     c.step = 0;                                              // (no other level comes here: what those need of row_dense is left out)
-    fill_exp_tab(L.tab, NT);
     if (c.blob) mv = mask_view(c.blob, c.V, c.depth);
+    bool filled = false;
+    if constexpr (PICK) {
+#pragma unroll 1
+      for (int b = blockIdx.x; b < c.B; b += gridDim.x) {
+        if (filled) __syncthreads();                         // (everybody is done with what the row before left in LDS)
+        row_first<NT>(c, mv, L, P, b * c.W);
+        filled = true;
+      }
+    }
+    if (!filled) fill_exp_tab(L.tab, NT);
     __syncthreads();
     // the requests' first rows come first, then all others
     auto row_at = [&](int64_t at) {
@@ -974,26 +1157,14 @@ __global__ void __launch_bounds__(NT, STRIDE ? 4 : 6) k_rows(SelCtx c) {
     int set = 0;
     for (int64_t base = blockIdx.x; base < rows; base += (int64_t)gridDim.x * 64) {
       const int64_t at = base + (int64_t)lane * gridDim.x;
-      const int r = at < rows ? row_at(at) : 0;
-      const float s = at < rows ? c.scores_in[r] : -INFINITY;
-      if (tid < 64 && at < rows && !(s > -INFINITY)) mark_dead(c, r);
+      const bool mine = at < rows && !(PICK && at < c.B);
+      const int r = mine ? row_at(at) : 0;
+      const float s = mine ? c.scores_in[r] : -INFINITY;
+      if (tid < 64 && mine && !(s > -INFINITY)) mark_dead(c, r);
       uint64_t live = __ballot(s > -INFINITY);
-      if constexpr (PICK) {
-        uint64_t firsts = live & __ballot(at < c.B);
-        live &= ~firsts;
-        for (; firsts; firsts &= firsts - 1) {
-          const int l = __ffsll((unsigned long long)firsts) - 1, row = __builtin_amdgcn_readlane(r, l);
-          float2 rivals = {-INFINITY, -INFINITY};            // (asked for here, looked at when the row's logits have been)
-          static_assert(kPickW <= 2 * NT, "two other rows to a thread");
-          if (1 + tid < c.W) rivals.x = c.scores_in[row + 1 + tid];
-          if (1 + tid + NT < c.W) rivals.y = c.scores_in[row + 1 + tid + NT];
-          row_dense<NT, true>(c, mv, L, row, lane_f32(s, l), -1, 0, 0, set, &P, rivals);
-          set ^= 1;
-        }
-      }
       for (; live; live &= live - 1) {
         const int l = __ffsll((unsigned long long)live) - 1, row = __builtin_amdgcn_readlane(r, l);
-        row_dense<NT, false>(c, mv, L, row, lane_f32(s, l), -1, 0, 0, set);
+        row_dense<NT>(c, mv, L, row, lane_f32(s, l), -1, 0, 0, set);
         set ^= 1;
       }
     }
@@ -1234,6 +1405,9 @@ __global__ void __launch_bounds__(kSelThreads) k_select(SelCtx c) {
   block_max_min<NW>(hi, lo, s_redf, parf);                   // (its barrier publishes the row table and the groups)
 
   int n = 0;
+  int place = -1;                                            // few candidates: this thread's one is the request's beam of that number
+  uint64_t own_key = 0;
+  bool few = false;
   if (hi > -INFINITY) {
     // Few scores of short gathered rows (the last level, as a rule): all of them are candidates, and the worst of the groups, which as many as
     // there are rows reach, is the threshold.  (Up to kDirectQuads: scores as good as equal are ranked one by one further down.  The
@@ -1261,12 +1435,25 @@ __global__ void __launch_bounds__(kSelThreads) k_select(SelCtx c) {
     auto take = [&](int w, int q, const float4& f) {         // the candidates of a short gathered row's quad
       const float v[4] = {f.x, f.y, f.z, f.w};
       const int left = (s_rinfo[w] >> 2) - 4 * q;            // (past the row's last wavefront of children nothing was written)
+      // (places for the wavefront's candidates of all four at once: an atomic is waited for some 0.1 us)
+      uint64_t in[4];
+      uint32_t total = 0;
+#pragma unroll
+      for (int j = 0; j < 4; j++) { in[j] = __ballot(j < left && v[j] >= T); total += (uint32_t)__popcll(in[j]); }
+      if (total == 0) return;
+      const uint64_t here = __ballot(1);
+      const int first = __ffsll((unsigned long long)here) - 1;
+      uint32_t at = 0;
+      if (gr_lane() == first) at = atomicAdd(&s_n, total);
+      at = (uint32_t)__builtin_amdgcn_readlane((int)at, first);
 #pragma unroll
       for (int j = 0; j < 4; j++) {
-        if (j >= left || !(v[j] >= T)) continue;
-        atomicAdd(&s_hist[key_bin(hi, scale, v[j])], 1u);
-        const uint32_t pos = atomicAdd(&s_n, 1u);
-        if (pos < (uint32_t)kListCap) s_list[pos] = composite(v[j], (uint32_t)w * (uint32_t)c.V + (uint32_t)(4 * q + j));
+        if (j < left && v[j] >= T) {
+          atomicAdd(&s_hist[key_bin(hi, scale, v[j])], 1u);
+          const uint32_t pos = at + rank_below(in[j]);
+          if (pos < (uint32_t)kListCap) s_list[pos] = composite(v[j], (uint32_t)w * (uint32_t)c.V + (uint32_t)(4 * q + j));
+        }
+        at += (uint32_t)__popcll(in[j]);
       }
     };
     auto quarter = [&](int i) { return ((int)s_units[i >> ssh] << ssh) + (i & ((1 << ssh) - 1)); };      // row << 6 | quarter of the row's 16 groups
@@ -1350,6 +1537,21 @@ __global__ void __launch_bounds__(kSelThreads) k_select(SelCtx c) {
     int nd = (int)s_nd, ns = (int)s_ns;
     n = (int)s_n;
     const bool taken = short_rows && !fallback && n <= kListCap && ns <= kChunkCap;    // the list is complete
+    // Few candidates count those that are better, several threads to one, and their threads write the beams: no bins, and no barrier any more (16 beams, V = 256
+    // 8.9 -> 7.9 us at level 1, 8.6 -> 7.3 at level 2; 128 beams, V = 8192, at level 2 10.4 -> 9.9).  The work grows with the square of their number: at 192 some
+    // 0.8 us, as long as the bins.
+    few = taken && n <= kFewMax;
+    if (few) {
+      const int sh = n <= 64 ? 4 : n <= 128 ? 3 : 2, i = tid >> sh;
+      if (i < n) own_key = s_list[i];
+      int better = 0;
+      if (i < n) {
+#pragma unroll 4
+        for (int j = tid & ((1 << sh) - 1); j < n; j += 1 << sh) better += s_list[j] > own_key;
+      }
+      better = lanes_sum(better, sh);
+      if (i < n && (tid & ((1 << sh) - 1)) == 0) place = better;
+    } else {
     if (!taken) {
     if (__builtin_expect(n > 0, 0)) {
       __syncthreads();
@@ -1657,6 +1859,7 @@ __global__ void __launch_bounds__(kSelThreads) k_select(SelCtx c) {
         }
       }
     }
+    }
   }
 
   // ---- level 1: which pair a survivor of a streamed row is = the valid tokens before it in its mask row, counted by four
@@ -1690,14 +1893,18 @@ __global__ void __launch_bounds__(kSelThreads) k_select(SelCtx c) {
 
   // ---- write the new beam state, best first.  (The arguments are read again here: held from the start on, the scalar registers they
   // take are spilled and reloaded all through the kernel.)
+  // Few candidates: their threads first, then (if fewer than W) the beams behind them.
   const LateArgs late = late_args();
-  for (int j = tid; j < late->W; j += kSelThreads) {
+#pragma unroll 1
+  for (int j = few ? (place >= 0 ? place : kMaxW) : tid, round = 0; round == 0 || !few || (round == 1 && n < late->W); j = few ? n + tid : j + kSelThreads, round++) {
+    if (!few && j - tid >= late->W) break;
+    if (j >= late->W) continue;
     const size_t o = (size_t)b * late->W + j;
     int32_t* po = late->prefix_out + o * late->depth;
     for (int k = 0; k < late->depth; k++) po[k] = -1;
     int r_lo = 0, r_hi = 0, item = -1;
     if (j < n) {
-      const uint64_t key = s_list[j];
+      const uint64_t key = few ? own_key : s_list[j];
       const uint32_t flat = 0xffffffffu - (uint32_t)key;
       const int parent = (int)(flat / (uint32_t)late->V), place = (int)(flat % (uint32_t)late->V);
       constexpr bool gathered = LISTED;

@@ -426,3 +426,24 @@ def test_level_0_with_about_as_many_beams_as_first_tokens(gr, oracle_lib, V, W, 
         mask = gr.gr_item_mask_build(to_dev(items), V)
     want = oracle_lib.beam_select(items, logits, sc, pf, 0)
     assert_select_equal(run_select(gr, mask, logits, sc, pf, rg, 0), want)
+
+
+@pytest.mark.parametrize("W", [1, 31, 32, 33, 63, 64, 65, 127, 128, 129, 150, 151, 191, 192, 193])
+@pytest.mark.parametrize("masked", [False, True])
+@pytest.mark.parametrize("step_size", [0.0, 0.25])
+def test_few_candidates_counted_against_each_other(gr, oracle_lib, W, masked, step_size):  # noqa: F811
+    # as many candidates as a lane's share of the counting changes at, with and without scores that are equal; 600 tokens: the best of every four are as
+    # many as 150 beams, and a row ends inside a load
+    V, B = 602, 2
+    rng = np.random.default_rng(W)
+    pairs = np.stack([rng.integers(0, V, 4000), rng.integers(0, V, 4000), rng.integers(0, V, 4000)], axis=1)
+    items = np.unique(pairs, axis=0).astype(np.int32)
+    mask = gr.gr_item_mask_build(to_dev(items), V) if masked else None
+    sc, pf, rg = gr_synth.initial_beam_state(B, W, 3)
+    for step in range(3 if masked else 1):
+        logits = (2.0 * rng.standard_normal((B, W, V))).astype(np.float32)
+        if step_size:
+            logits = (np.round(logits / step_size) * step_size).astype(np.float32)
+        want = oracle_lib.beam_select(items if masked else None, logits, sc, pf, step)
+        assert_select_equal(run_select(gr, mask, logits, sc, pf, rg, step), want, f"step {step}")
+        sc, pf, rg = want["scores"], want["prefix"], want["range"]
