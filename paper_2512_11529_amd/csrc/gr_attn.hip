@@ -222,13 +222,15 @@ struct AttnTile {
   // One steady-state tile with the matrix and vector pipes kept busy together.  The wave issues, in this order,
   // the MFMAs of S(t+1) = K(t+1).Q^T and then those of O += V(t).P(t); between consecutive MFMAs it
   // exponentiates a fixed share of tile t's scores (their reference m2 is already decided), so that
-  // the 32 quarter-rate exponentials per lane run in the shadow of the 32 MFMAs instead of after them.  P(t) is
-  // complete before the second half of the PV MFMAs starts.  Instruction order is pinned chunk by chunk.
+  // the 32 quarter-rate exponentials per lane run in the shadow of the 32 MFMAs instead of after them.  P(t)'s quarters are
+  // complete when the PV MFMAs come to them.  Instruction order is pinned chunk by chunk.
   // Measured at 32 x 4096 tokens x 256 beams, two wavefronts per SIMD: 507 us with the exponentials staged over three chunks, 515
   // with each finished in one; 8 x 2048 x 128 (one wavefront per SIMD, 1.1 us a tile): 40.1 against 41.4 us.  Operand reads 5 or 6
   // MFMAs ahead: no change.
   static constexpr int NQK = (KT / 32) * (D / 16), NPV = (KT / 16) * (D / 32), NMF = NQK + NPV;
-  static constexpr int EXP_BY = NQK + NPV / 2;            // all 32 exponentials are issued after this many MFMAs
+  // All 32 exponentials are issued after this many MFMAs: as late as the last quarter of the probabilities, packed two chunks later, allows.  us with NPV / 2
+  // and with this: 32 x 4096 x 256 beams 477.9, 472.6; 64 ragged requests of 512-8192 853, 845; 8 causal prompts of 1024-8192 1184, 1173.
+  static constexpr int EXP_BY = NQK + NPV * 11 / 16;
   static constexpr int exps_after(int j) {                // exponentials finished once MFMA j's chunk has been issued
     const int t = (32 * (j + 1) + EXP_BY - 1) / EXP_BY;
     return j < 0 ? 0 : (t > 32 ? 32 : t);
