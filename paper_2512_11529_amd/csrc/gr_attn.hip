@@ -1191,6 +1191,9 @@ __global__ void __launch_bounds__(256) k_attn_order(const int32_t* cu, int B, in
 // above the best number on average (3.4 % without the rounds and with 4 TB/s): 2 requests of 8000 tokens x 200
 // beams, 8 query and 2 KV heads of 64: 29.2 us with 9 segments, whose 36 pairs put 35 workgroups on some XCDs, 20.5 with 8; 4 x 2048 x 128 of 8
 // heads of 64 20.9 with 8, 15.9 with 4; one of 800 x 128 of these 13.9, 13.7, 12.5, 11.5, 12.8 with 1 to 5.
+// Up to two workgroups per CU are looked at: with one at most, long prompts whose pairs and row blocks are somewhat more than half of 256, or a third, left
+// places empty: 9 of 2860-4376 x 195 beams of 16 query and 4 KV heads 97.4 us, now 74.4; 7 x 12959 x 66 178.7, 145.6; 12 of 1504-2443 x 39, 8 heads
+// of 64, 23.2, 21.0; of 180 shapes none is more than 2 % slower.
 //
 // With 256 workgroups of 256 rows or more, 128 rows win nevertheless, us with 128 and 256 rows:
 //   where they waste fewer rows of the last block (more than 5 %; 8 % for FP8 codes, which every workgroup widens for itself): 128 requests of
@@ -1221,7 +1224,7 @@ AttnPlan plan_attn(const gr_attn_params* p, bool kv8) {
   const int64_t units = (int64_t)p->B * p->Hkv * ((M + plan.mwg - 1) / plan.mwg);
   plan.nsplit = 1;
   if (units < 256 && p->max_L > 4 * KT) {
-    const int64_t want = (256 + units / 2) / units, cap = p->max_L / ((p->d == 64 ? 3 : 4) * KT);      // about one workgroup per CU; at least so many tiles per segment
+    const int64_t want = (512 + units / 2) / units, cap = p->max_L / ((p->d == 64 ? 3 : 4) * KT);      // about two workgroups per CU; at least so many tiles per segment
     const int most = (int)(want < cap ? (want < 16 ? want : 16) : (cap < 16 ? cap : 16));
     const int tiles = (p->max_L + KT - 1) / KT;
     const double partial_us = 2.0 * p->B * p->W * p->Hq * p->d * 4 / (p->d == 64 ? 3.5e6 : 3e6);             // of one segment

@@ -358,3 +358,13 @@ def test_prompts_of_every_number_of_tiles(gr, oracle_lib, d, rows, copies):
         _check(gr, oracle_lib, a, float(np.float32(1 / np.sqrt(d))))
     finally:
         gr.gr_diag_attn_plan(0, 0)
+
+
+@pytest.mark.parametrize("uniform", [True, False])
+def test_segments_for_two_workgroups_per_cu(gr, oracle_lib, uniform):
+    # 96 (request, KV head) pairs of one row block: split so that more workgroups run than there are CUs, in the order of their lengths where these differ
+    B = 12
+    lens = (1700,) * B if uniform else tuple(int(n) for n in np.random.default_rng(2).integers(1400, 1900, B))
+    a = rand_attn_case(B, B, 20, 8, 8, 64, 3, 2, lens)
+    assert gr.attn_workspace_bytes(B, 20, 8, 8, 64, max(lens), sum(lens)) >= 3 * B * 20 * 8 * (64 + 2) * 4       # (three segments or more: 288 workgroups)
+    _check(gr, oracle_lib, a, 0.125)
