@@ -878,9 +878,9 @@ __device__ __forceinline__ void row_first(const SelCtx& c, const MaskView& mv, R
       for (int j = tid & ((1 << sh) - 1); j < n; j += 1 << sh) better += P.list[j] > key;
     }
     better = lanes_sum(better, sh);
-    const bool mine = i < n && (tid & ((1 << sh) - 1)) == 0;
-    if (mine && better < late->W) emit(better, true, key);
-    for (int j = n + tid; j < late->W; j += NT) emit(j, false, 0);
+    if (i < n && (tid & ((1 << sh) - 1)) == 0) P.tmp[better] = key;
+    __syncthreads();
+    for (int j = tid; j < late->W; j += NT) emit(j, j < n, j < n ? P.tmp[j] : 0);
     return;
   }
   bool fits = n <= kPickCap;
@@ -1405,8 +1405,6 @@ __global__ void __launch_bounds__(kSelThreads) k_select(SelCtx c) {
   block_max_min<NW>(hi, lo, s_redf, parf);                   // (its barrier publishes the row table and the groups)
 
   int n = 0;
-  int place = -1;                                            // few candidates: this thread's one is the request's beam of that number
-  uint64_t own_key = 0;
   bool few = false;
   if (hi > -INFINITY) {
     // Few scores of short gathered rows (the last level, as a rule): all of them are candidates, and the worst of the groups, which as many as
@@ -1537,12 +1535,13 @@ __global__ void __launch_bounds__(kSelThreads) k_select(SelCtx c) {
     int nd = (int)s_nd, ns = (int)s_ns;
     n = (int)s_n;
     const bool taken = short_rows && !fallback && n <= kListCap && ns <= kChunkCap;    // the list is complete
-    // Few candidates count those that are better, several threads to one, and their threads write the beams: no bins, and no barrier any more (16 beams, V = 256
-    // 8.9 -> 7.9 us at level 1, 8.6 -> 7.3 at level 2; 128 beams, V = 8192, at level 2 10.4 -> 9.9).  The work grows with the square of their number: at 192 some
+    // Few candidates count those that are better, several threads to one: no bins (16 beams, V = 256 9.1 -> 7.6 us at level 1; one request of 128 beams,
+    // V = 8192, at level 2 10.6 -> 9.7, 30 of 40 beams 11.3 -> 10.0).  The work grows with the square of their number: at 192 some
     // 0.8 us, as long as the bins.
     few = taken && n <= kFewMax;
     if (few) {
       const int sh = n <= 64 ? 4 : n <= 128 ? 3 : 2, i = tid >> sh;
+      uint64_t own_key = 0;
       if (i < n) own_key = s_list[i];
       int better = 0;
       if (i < n) {
@@ -1550,7 +1549,8 @@ __global__ void __launch_bounds__(kSelThreads) k_select(SelCtx c) {
         for (int j = tid & ((1 << sh) - 1); j < n; j += 1 << sh) better += s_list[j] > own_key;
       }
       better = lanes_sum(better, sh);
-      if (i < n && (tid & ((1 << sh) - 1)) == 0) place = better;
+      if (i < n && (tid & ((1 << sh) - 1)) == 0) s_tmp[better] = own_key;
+      __syncthreads();
     } else {
     if (!taken) {
     if (__builtin_expect(n > 0, 0)) {
@@ -1893,18 +1893,15 @@ __global__ void __launch_bounds__(kSelThreads) k_select(SelCtx c) {
 
   // ---- write the new beam state, best first.  (The arguments are read again here: held from the start on, the scalar registers they
   // take are spilled and reloaded all through the kernel.)
-  // Few candidates: their threads first, then (if fewer than W) the beams behind them.
   const LateArgs late = late_args();
-#pragma unroll 1
-  for (int j = few ? (place >= 0 ? place : kMaxW) : tid, round = 0; round == 0 || !few || (round == 1 && n < late->W); j = few ? n + tid : j + kSelThreads, round++) {
-    if (!few && j - tid >= late->W) break;
-    if (j >= late->W) continue;
+  const uint64_t* best = few ? s_tmp : s_list;
+  for (int j = tid; j < late->W; j += kSelThreads) {
     const size_t o = (size_t)b * late->W + j;
     int32_t* po = late->prefix_out + o * late->depth;
     for (int k = 0; k < late->depth; k++) po[k] = -1;
     int r_lo = 0, r_hi = 0, item = -1;
     if (j < n) {
-      const uint64_t key = few ? own_key : s_list[j];
+      const uint64_t key = best[j];
       const uint32_t flat = 0xffffffffu - (uint32_t)key;
       const int parent = (int)(flat / (uint32_t)late->V), place = (int)(flat % (uint32_t)late->V);
       constexpr bool gathered = LISTED;
