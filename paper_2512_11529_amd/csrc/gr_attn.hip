@@ -65,6 +65,14 @@ struct AttnCtx {
   const int32_t* slot;    // [B, W, ND] row of the request's own-token block that holds (beam, token), or nullptr (= w * ND + t)
 };
 
+// The kernel's arguments, read where this stands and not before: what only rare or late code needs takes no scalar registers through the prompt loop.
+typedef const __attribute__((address_space(4))) AttnCtx* LateArgs;
+__device__ __forceinline__ LateArgs late_args() {
+  LateArgs a = (LateArgs)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(a));
+  return a;
+}
+
 __device__ __forceinline__ float bf16_bits_to_float(uint32_t h) { return __uint_as_float(h << 16); }
 
 __device__ __forceinline__ bf16x8 as_bf16x8(uint4 v) { return __builtin_bit_cast(bf16x8, v); }
@@ -454,9 +462,10 @@ k_beam_attn(AttnCtx c) {
   const unsigned gq = CAUSAL ? (unsigned)group : div_by((unsigned)group, (unsigned)c.nsplit, c.inv_split);
   const int sp = CAUSAL ? 0 : (int)((unsigned)group - gq * (unsigned)c.nsplit);
   const int bi = (int)div_by(gq, (unsigned)c.Hkv, c.inv_hkv);
-  const int kvh = (int)(gq - (unsigned)bi * (unsigned)c.Hkv);
+  const unsigned kvh = gq - (unsigned)bi * (unsigned)c.Hkv;
   int b = c.order ? c.order[bi] : bi;
   if constexpr (!CAUSAL && FIND) b = request_by_length(c.cu, c.B, bi, lane, &row0_l, &len_l);
+  const unsigned bu = (unsigned)b;                             // (for offsets: no sign to extend, which takes scalar registers)
   const int row0 = FIND ? row0_l : c.cu[b];
   const int Lb = FIND ? len_l : c.cu[b + 1] - row0;
   const int Mb = CAUSAL ? Lb * c.g : c.M;                      // query rows of this (request, KV head)
@@ -510,8 +519,6 @@ k_beam_attn(AttnCtx c) {
   // wave's loads, and the barrier that follows publishes every wave's.
   constexpr int EB = KV8 ? 1 : 2;                            // bytes per stored K/V element
   const uint32_t tok_bytes = (uint32_t)c.Hkv * D * EB;      // bytes between consecutive tokens
-  const char* kbase = (const char*)c.ks + ((size_t)row0 * c.Hkv + kvh) * D * EB;
-  const char* vbase = (const char*)c.vs + ((size_t)row0 * c.Hkv + kvh) * D * EB;
   const float cp = KV8 ? c.c * c.k_scale : c.c;              // exponent scale of the prompt loop
   typename T::Rd rdo = T::make_rd(lane, (int)(uintptr_t)(__attribute__((address_space(3))) uint16_t*)s_tiles);
   // this lane's byte offsets from the tile's first row, per chunk (rows up to `most`)
@@ -532,9 +539,10 @@ k_beam_attn(AttnCtx c) {
   // addresses were half of what stood between the MFMAs of two tiles: 64 ragged requests of 512-8192 x 256 beams 856 -> 845 us, 32 x 4096 x 256 476 -> 470.)
   const int tl = ntiles - 1;
   const int last_row = seg1 - (seg0 + tl * KT) - 1;          // of the last tile
-  const size_t tile_bytes = (size_t)KT * tok_bytes;
-  const char* k_at = kbase + (size_t)seg0 * tok_bytes;
-  const char* v_at = vbase + (size_t)seg0 * tok_bytes;
+  const uint32_t tile_bytes = KT * tok_bytes;                // (a prompt of more than one tile: below 2^32)
+  const size_t first_byte = ((size_t)(unsigned)(row0 + seg0) * (unsigned)c.Hkv + kvh) * D * EB;
+  const char* k_at = (const char*)c.ks + first_byte;
+  const char* v_at = (const char*)c.vs + first_byte;
   uint32_t koff[CPW], voff[CPW];
   auto tload_chunk = [&](bool is_k, int buf, int i) {
     dma((is_k ? lds_k : lds_v) + (uint32_t)(buf * (TILE * 2) + (i * NWAVES + wave_u) * 1024), is_k ? k_at : v_at, is_k ? koff[i] : voff[i]);
@@ -565,12 +573,18 @@ k_beam_attn(AttnCtx c) {
     return st;
   };
   auto offsets_of_last = [&](bool is_k) {
-    if (!KV8 && last_row < KT - 1) tile_offsets(is_k ? koff : voff, is_k, last_row);
+    if (KV8) return;
+    int most = last_row;
+    // (decode: worked out when they are needed; ahead of the loop they took registers through it, and something was spilled.  The causal kernels have
+    // those registers, and a call of 16 short prompts was 0.4 % slower so.)
+    if (CAUSAL && most == KT - 1) return;
+    if (!CAUSAL) asm volatile("" : "+v"(most));
+    tile_offsets(is_k ? koff : voff, is_k, most);
   };
   // to the next tile, or back
   auto advance = [&](bool is_k, bool back) __attribute__((always_inline)) {
     (is_k ? k_at : v_at) += back ? -(ptrdiff_t)tile_bytes : (ptrdiff_t)tile_bytes;
-    if (KV8) (is_k ? k_left : v_left) += back ? (uint32_t)tile_bytes : 0u - (uint32_t)tile_bytes;
+    if (KV8) (is_k ? k_left : v_left) += back ? tile_bytes : 0u - tile_bytes;
   };
   // the address of tile `to`, from that of the one before
   auto go_to = [&](bool is_k, int to) {
@@ -626,13 +640,13 @@ k_beam_attn(AttnCtx c) {
     divmod_small(rho < Ru ? rho : 0, c.u, c.rcp_u, &bl, &tok);
     int prow = (beam0 + bl) * c.ND + tok;
     if (c.slot && Ru > 0) {                                // (an entry outside the block falls back to the beam's own row)
-      const int sl = c.slot[(size_t)b * c.W * c.ND + prow];
+      const int sl = c.slot[(size_t)bu * (unsigned)(c.W * c.ND) + (unsigned)prow];
       prow = ((unsigned)sl < (unsigned)(c.W * c.ND)) ? sl : prow;
     }
     return (uint32_t)prow * own_bytes;
   };
-  const char* ku_b = (const char*)(c.ku + (size_t)b * c.W * c.ND * c.Hkv * D + (size_t)kvh * D);        // this request's own-token caches
-  const char* vu_b = (const char*)(c.vu + (size_t)b * c.W * c.ND * c.Hkv * D + (size_t)kvh * D);
+  const char* ku_b = (const char*)(c.ku + ((size_t)bu * (unsigned)(c.W * c.ND) * (unsigned)c.Hkv + kvh) * D);        // this request's own-token caches
+  const char* vu_b = (const char*)(c.vu + ((size_t)bu * (unsigned)(c.W * c.ND) * (unsigned)c.Hkv + kvh) * D);
   // element offsets from s_tiles of the wave's mini-tiles: K in place of the K tiles, which the last tile's step no longer reads, or of Q
   const int own_k = (NWAVES == 8 ? 4 * TILE : 0) + wave_u * UR * D, own_v = (NWAVES == 8 ? 0 : 2 * TILE) + wave_u * UR * D;
   auto uload = [&](bool is_k, uint32_t row_off, int rows) {               // the first `rows` rows of a mini-tile, and what else is in their 1 KiB chunks
@@ -646,13 +660,15 @@ k_beam_attn(AttnCtx c) {
 
   // The own-token rows are what the end of a unit waits for: they are asked for three tiles before the last one, one 4-byte load
   // per 128-byte line into LDS that nobody reads, so that the loads into registers (which have no room earlier) find them in L2.
-  const uint32_t lds_dump = KS == 2 ? lds_k + 4 * TILE * 2 + (uint32_t)wave_u * 256 : lds_k + attn_lds_used(D, MWG) + (uint32_t)wave_u * 256;
   auto touch = [&](uint32_t dump, const void* gbase, uint32_t off) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(dump), "v"(off), "s"(gbase) : "memory", "m0");
   };
   // (with three V tiles: one tile before the last one, when the place of the V tile after that is free)
   const int touch_own = own_stage && Ru > 0 ? max(0, ntiles - (VS == 3 ? 2 : 4)) : 0x7fffffff;
-  auto touch_own_rows = [&](uint32_t dump, uint32_t row_off) {
+  auto touch_own_rows = [&](int v_free, uint32_t row_off) {      // v_free: place of a V tile that nobody reads, of three
+    uint32_t w = (uint32_t)wave_u;
+    asm volatile("" : "+s"(w));                            // (worked out here, not kept in a register from the start on)
+    const uint32_t dump = (VS == 3 ? lds_v + (uint32_t)v_free * (TILE * 2) : lds_k + (KS == 2 ? 4 * TILE * 2 : attn_lds_used(D, MWG))) + w * 256;
     const uint32_t off = row_off + (D == 128 ? 128 * G : 0);
     touch(dump, ku_b, off);
     touch(dump, vu_b, off);
@@ -663,7 +679,7 @@ k_beam_attn(AttnCtx c) {
   {
     constexpr int NWG = NWAVES * KS, QPW = MWG / RPC / NWG;    // 1 KiB chunks per wave
     // this request's queries (decode: its W beams; prefill: its own tokens); offsets inside it fit 32 bits
-    const char* q_b = (const char*)(c.q + ((CAUSAL ? (size_t)row0 : (size_t)b * c.W) * c.Hq + kvh * c.g) * D);
+    const char* q_b = (const char*)(c.q + ((CAUSAL ? (size_t)(unsigned)row0 : (size_t)bu * (unsigned)c.W) * (unsigned)c.Hq + kvh * (unsigned)c.g) * D);
     const int wg_wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const uint32_t lds_0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint16_t*)smem;
     const uint32_t skip = (uint32_t)(c.Hq - c.g) * D * 2;      // from a beam's last row of this KV head to the next beam's first
@@ -796,7 +812,7 @@ k_beam_attn(AttnCtx c) {
       advance(true, false);
       advance(false, false);
       if (__builtin_expect(t >= seldom, KS == 2)) {                               // (one test for what the last steps have to do)
-        if (t == touch_own) touch_own_rows(VS == 3 ? lds_v + (uint32_t)v_to * (TILE * 2) + (uint32_t)wave_u * 256 : lds_dump, prow0);
+        if (t == touch_own) touch_own_rows(v_to, prow0);
         if (t + kAheadK >= tl) { if (t + kAheadK > tl) advance(true, true); else offsets_of_last(true); }
         if (t + kAheadV >= tl) { if (t + kAheadV > tl) advance(false, true); else offsets_of_last(false); }
       }
@@ -956,6 +972,10 @@ k_beam_attn(AttnCtx c) {
     uint16_t* k32 = s_tiles + own_k;
     uint16_t* v32 = s_tiles + own_v;
     all_landed();                                          // (the own tokens' K, which is written over)
+    const LateArgs late = late_args();
+    const size_t first_byte = ((size_t)(unsigned)row0 * (unsigned)late->Hkv + kvh) * D * EB;
+    const char* kbase = (const char*)late->ks + first_byte;
+    const char* vbase = (const char*)late->vs + first_byte;
     m_run[0] = -INFINITY; l_run[0] = 0.f;
 #pragma unroll
     for (int db = 0; db < D / 32; db++)
@@ -1020,7 +1040,10 @@ k_beam_attn(AttnCtx c) {
     *(f32x2*)(s_set1_ml + (wave * 64 + lane) * 2) = ml;
   }
   if (own_stage) {
-    if (ntiles == 0) uload(true, prow0, Ru);
+    int tiles = ntiles;
+    // (compared again in the kernels that have no scalar registers to keep the result of the comparison at the start of the unit in)
+    if (!KV8 && NWAVES * KS == 4) asm volatile("" : "+s"(tiles));
+    if (tiles == 0) uload(true, prow0, Ru);
     uint32_t row_off = prow0;
     for (int pass = 0; pass * UR < Ru; pass++) {
       const int used = Ru - pass * UR;                     // (V: whole halves of 16 rows, whose probabilities are 0 past the last one)
@@ -1074,7 +1097,7 @@ k_beam_attn(AttnCtx c) {
           st.y = __builtin_bit_cast(uint32_t, hb);
           *(uint2*)(&s_o[n32 * D + ((4 * db + q4) ^ (n32 & (PPR - 1))) * 8 + 4 * G]) = st;
         }
-      uint16_t* out_b = c.out + ((CAUSAL ? (size_t)row0 : (size_t)b * c.W) * c.Hq + kvh * c.g) * D;
+      uint16_t* out_b = c.out + ((CAUSAL ? (size_t)(unsigned)row0 : (size_t)bu * (unsigned)c.W) * (unsigned)c.Hq + kvh * (unsigned)c.g) * D;
 #pragma unroll
       for (int i = 0; i < 32 * PPR / 64; i++) {
         const int p = lane + 64 * i, rl = p / PPR, piece = p % PPR, rr = row_w + rl;
@@ -1082,12 +1105,12 @@ k_beam_attn(AttnCtx c) {
         if (rr < Mb) *(uint4*)(out_b + (uint32_t)((rr + small_div(rr, c.rcp_g) * (c.Hq - c.g)) * D + piece * 8)) = v;
       }
       if (c.lse && G == 0 && r >= 0)
-        c.lse[((CAUSAL ? (size_t)row0 : (size_t)b * c.W) + beam_q) * c.Hq + kvh * c.g + (r - beam_q * c.g)] = (l_tot > 0.f) ? (m + __builtin_amdgcn_logf(l_tot)) * kLn2 : -INFINITY;
+        c.lse[((CAUSAL ? (size_t)(unsigned)row0 : (size_t)bu * (unsigned)c.W) + (unsigned)beam_q) * (unsigned)c.Hq + kvh * (unsigned)c.g + (unsigned)(r - beam_q * c.g)] = (l_tot > 0.f) ? (m + __builtin_amdgcn_logf(l_tot)) * kLn2 : -INFINITY;
     } else {
       // this segment's unnormalised fp32 partial O and (max, sum), as the lanes hold them (see k_attn_merge): every store is a run of whole lines.
       // (Staged through LDS into rows of D floats they took 2.1 us of a unit's 13.5.)
       const int first = mbi * MWG + wave_u * 32, left = min(32, Mb - first);       // the wave's rows
-      const size_t row_p = (((size_t)b * c.nsplit + sp) * c.Hkv + kvh) * c.M + first;
+      const size_t row_p = (((size_t)bu * (unsigned)c.nsplit + (unsigned)sp) * (unsigned)c.Hkv + kvh) * (unsigned)c.M + (unsigned)first;
       if (r >= 0) {
         f32x4* part = (f32x4*)(c.part_o + row_p * D) + G * left + n32;
 #pragma unroll
