@@ -73,10 +73,6 @@ __device__ __forceinline__ LateArgs late_args() {
   return a;
 }
 
-__device__ __forceinline__ float bf16_bits_to_float(uint32_t h) { return __uint_as_float(h << 16); }
-
-__device__ __forceinline__ bf16x8 as_bf16x8(uint4 v) { return __builtin_bit_cast(bf16x8, v); }
-
 // n / d and n % d for 0 <= n < 2^22 and a small runtime divisor, through a float reciprocal and one
 // correction step (a handful of instructions where the generic 32-bit division takes dozens).
 __device__ __forceinline__ void divmod_small(int n, int d, float rcp_d, int* q, int* r) {
@@ -400,9 +396,9 @@ k_beam_attn(AttnCtx c) {
   constexpr int CPW = NCHUNK / NWAVES;           // chunks per wave and tile
   constexpr int RPC = 1024 / (D * 2);            // rows per chunk
   static_assert(NCHUNK % NWAVES == 0, "tile must divide over the waves");
-  // double-buffered tiles: K(j) in s_k[slot], V(j) in s_v[slot], slot = (j + flip) % 2 (flip is chosen below so that the last
-  // tile is in slot 0: the main loop then names its slots at compile time); then (8-wave workgroups only: they own the CU's LDS
-  // anyway) a separate region for the Q hand-over, so that the first tiles can be in flight while Q is staged; of 4 waves, K's only
+  // Tiles in LDS: K(j) in s_k[slot], V(j) in s_v[slot], slot = (j + flip) % 2 (flip is chosen below so that the last tile is in slot 0: the main loop
+  // then names its slots at compile time); where there are three V tiles (VS), V(j) in s_v[j % 3].  Then, for workgroups of 8 waves, which own the
+  // CU's LDS anyway, a region of its own for the Q hand-over, so that the first tiles can be in flight while Q is staged; of 4 waves, K's only
   extern __shared__ __attribute__((aligned(1024))) uint16_t smem[];
   const int set = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x / NT);
   // V tiles in LDS.  Two sets of a large head have three and ask for V two tiles ahead: their units are few, so that memory's latency is waited for, and with the
@@ -659,11 +655,11 @@ k_beam_attn(AttnCtx c) {
   };
 
   // The own-token rows are what the end of a unit waits for: they are asked for three tiles before the last one, one 4-byte load
-  // per 128-byte line into LDS that nobody reads, so that the loads into registers (which have no room earlier) find them in L2.
+  // per 128-byte line into LDS that nobody reads, so that the loads into their places, which are free with the last tile only, find them in L2.
   auto touch = [&](uint32_t dump, const void* gbase, uint32_t off) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(dump), "v"(off), "s"(gbase) : "memory", "m0");
   };
-  // (with three V tiles: one tile before the last one, when the place of the V tile after that is free)
+  // (with three V tiles, two sets of head size 128: one tile before the last one, when the place of the V tile after that is free)
   const int touch_own = own_stage && Ru > 0 ? max(0, ntiles - (VS == 3 ? 2 : 4)) : 0x7fffffff;
   auto touch_own_rows = [&](int v_free, uint32_t row_off) {      // v_free: place of a V tile that nobody reads, of three
     uint32_t w = (uint32_t)wave_u;
@@ -906,14 +902,7 @@ k_beam_attn(AttnCtx c) {
   auto set1_o = [&](int e) { return (f32x4*)(s_set1 + (e < D / 16 ? own_k : own_v) + (e % (D / 16)) * 512) + lane; };
   float* s_set1_ml = (float*)(s_set1 + 4 * TILE);
 
-  // ---- unshared stage: every beam's own u decode tokens, through the same MFMA path.
-  // The 32 query columns of a wave belong to a handful of beams (32/g of them when g divides 32).
-  // Their K rows (then V rows) are laid out as private 32-row mini-tiles, row rho = beam_local * u +
-  // token, loaded with coalesced 16-byte pieces into the wave's own slice of the (now idle) tile
-  // memory; S^T = K_u . Q^T is a full 32 x 32 block of which a column keeps only its own beam's u
-  // rows (the rest are masked to -inf), and O^T += V_u^T . P^T follows.  Compared with per-lane dot
-  // products this reads each beam's rows once instead of once per query head and replaces ~1000
-  // VALU operations per lane by 16 MFMAs per wave.
+  // ---- unshared stage (see its geometry above)
   if (KS == 2 && set == 1)
     for (int i = 0; i < set1_idle; i++) __syncthreads();
   if (KS == 2 || own_stage || ntiles > 0) __syncthreads(); // every wave is done with the prompt tiles
@@ -1321,7 +1310,7 @@ gr_status attn_run(const gr_attn_params* p, const int32_t* slot, bool kv8, float
   if (p->total_L >= ((int64_t)1 << 31)) return GR_ERR_UNSUPPORTED;
   if ((int64_t)p->max_L * p->Hkv * p->d * 2 >= ((int64_t)1 << 32)) return GR_ERR_UNSUPPORTED;   // one request's K (or V) must fit a buffer descriptor
   const int g = p->Hq / p->Hkv;
-  if ((int64_t)p->W * g >= ((int64_t)1 << 22)) return GR_ERR_UNSUPPORTED;      // row indices go through divmod_small
+  if ((int64_t)p->W * g >= ((int64_t)1 << 22)) return GR_ERR_UNSUPPORTED;      // row indices go through small_div, whose bound is 2^22
   if ((int64_t)p->W * p->Hq * p->d >= ((int64_t)1 << 31) || (int64_t)p->W * p->ND * p->Hkv * p->d >= ((int64_t)1 << 31))
     return GR_ERR_UNSUPPORTED;                                                   // offsets inside one request fit 32 bits
 
@@ -1425,7 +1414,7 @@ extern "C" gr_status gr_prefill_attn(const gr_prefill_params* p, void* stream_) 
   if (p->total_L >= ((int64_t)1 << 31)) return GR_ERR_UNSUPPORTED;
   if ((int64_t)p->max_L * p->Hkv * p->d * 2 >= ((int64_t)1 << 32)) return GR_ERR_UNSUPPORTED;   // one request's K (or V) must fit a buffer descriptor
   const int g = p->Hq / p->Hkv;
-  if ((int64_t)p->max_L * g >= ((int64_t)1 << 22)) return GR_ERR_UNSUPPORTED;                   // row indices go through divmod_small
+  if ((int64_t)p->max_L * g >= ((int64_t)1 << 22)) return GR_ERR_UNSUPPORTED;                   // row indices go through small_div, whose bound is 2^22
   if ((int64_t)p->max_L * p->Hq * p->d >= ((int64_t)1 << 31)) return GR_ERR_UNSUPPORTED;        // offsets inside one request fit 32 bits
   if (p->total_L == 0 || p->max_L == 0) return GR_OK;
 
