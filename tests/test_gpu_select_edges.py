@@ -447,3 +447,36 @@ def test_few_candidates_counted_against_each_other(gr, oracle_lib, W, masked, st
         want = oracle_lib.beam_select(items if masked else None, logits, sc, pf, step)
         assert_select_equal(run_select(gr, mask, logits, sc, pf, rg, step), want, f"step {step}")
         sc, pf, rg = want["scores"], want["prefix"], want["range"]
+
+
+@pytest.mark.parametrize("masked", [False, True])
+@pytest.mark.parametrize("V", [64, 602])
+def test_level_0_of_more_requests_than_workgroups(gr, oracle_lib, V, masked):  # noqa: F811
+    """512 workgroups select from three requests each, one after the other, in the same LDS: every way a request can end (dead; other live rows; no
+    finite logit; too many equal scores; few candidates; more than are counted against each other) is followed by every other."""
+    rng = np.random.default_rng(V)
+    B, W, grid = 1100, 20, 512
+    logits = (2.0 * rng.standard_normal((B, W, V))).astype(np.float32)
+    sc = np.full((B, W), -np.inf, np.float32)
+    sc[:, 0] = -3.0 * rng.random(B)
+    for b in range(B):
+        kind = b % grid // 6 ** (b // grid) % 6
+        if kind == 0:
+            sc[b] = -np.inf
+        elif kind == 1:
+            sc[b, 1 + b % (W - 1)] = -1.5
+        elif kind == 2:
+            logits[b, 0] = -np.inf
+        elif kind == 3:
+            logits[b, 0] = 0.75
+        elif kind == 5:                                        # fewer than W far ahead of many in one bin of the threshold, of several bins of the order
+            logits[b, 0] = -100.0 + 0.4 * rng.random(V)
+            logits[b, 0, rng.choice(V, W - 4, replace=False)] = 5.0 * rng.random(W - 4)
+    pf, rg = np.full((B, W, 3), -1, np.int32), np.zeros((B, W, 2), np.int32)
+    items = mask = None
+    if masked:
+        t1 = np.sort(rng.choice(V, V * 3 // 4, replace=False))
+        items = np.stack([t1, t1 // 2, t1 // 3], axis=1).astype(np.int32)
+        mask = gr.gr_item_mask_build(to_dev(items), V)
+    want = oracle_lib.beam_select(items, logits, sc, pf, 0)
+    assert_select_equal(run_select(gr, mask, logits, sc, pf, rg, 0), want)
