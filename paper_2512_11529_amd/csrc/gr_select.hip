@@ -418,7 +418,7 @@ struct RowLds {
 };
 
 // What the workgroup of a request's only live row needs to select as well.
-constexpr int kPickCap = 2048;         // candidates that reach the threshold
+constexpr int kPickCap = 2432;         // candidates that reach the threshold
 constexpr int kPickW = 1024;
 struct PickLds {
   uint64_t list[kPickCap], tmp[kPickCap];
@@ -648,13 +648,20 @@ __device__ __forceinline__ void row_dense(const SelCtx& c, const MaskView& mv, R
 // Bound: the chain of steps in one workgroup.  So the row's logits are asked for before it is known to be live; the threshold that W candidates
 // reach is looked for among the logits, beside the exponentials (rounding a sum is monotone: what reaches a logit reaches its score); it is
 // found among the best of every four where they are enough; candidates get their places a wavefront at a time, and few of them
-// are counted against each other.  A call without and with these, us: one request x 16 beams over 256 tokens 10.1, 9.5; one x 128 over 8192 12.5, 11.4; 8 x 128
-// 13.3, 12.2.
-constexpr int kPickFew = 128;          // candidates that are counted against each other
+// are counted against each other.  A call without and with these, us: one request x 16 beams over 256 tokens 10.1, 9.6; one x 128 over 8192 12.3, 11.3; 8 x 128
+// with a mask 13.8, 12.6.
+//
+// The best of every four (by_load) for up to a sixth of the tokens: beyond that the threshold among them lets through many more than are wanted.  us by all
+// candidates and by fours: 256 tokens x 64 beams 9.9, 10.4; 1024 x 256 11.0, 11.0; 4096 x 600 13.0, 12.6; 4096 x 512 12.3, 11.9; 8192 x 512 13.9, 12.6; but 4096 x 1024,
+// where they did not fit the list and the request was left to k_select, 14.1, 23.8.  And only where four candidates for every beam, and some, fit the
+// list, so that it holds them however alike the four are: 8192 x 1024 with the logits of a four as good as equal 16.0, 26.3
+// (all different 15.3, 14.6), 8192 x 512, which four times fit, 13.9 (15.2 by all).
+constexpr int kPickFew = 96;           // candidates that are counted against each other: 128 take as long as by bins or longer (300 tokens x 128 beams 10.9 us, 10.6 by bins)
 template <int NT>
 __device__ __forceinline__ void row_first(const SelCtx& c, const MaskView& mv, RowLds<NT>& L, PickLds& P, int row) {
   constexpr int NV4 = kBlockV / 4 / NT, NWV = NT / 64;        // float4 per thread; wavefronts
-  static_assert(NV4 == 4 && NWV == 8 && kPickW <= 2 * NT && kPickCap == 4 * NT, "a list of one load, two other rows to a thread");
+  static_assert(NV4 == 4 && NWV == 8 && kPickW <= 2 * NT && 4 * NT <= kPickCap, "a list of one load at least, two other rows to a thread");
+  static_assert(kPickFew <= NT / 4, "four threads to a candidate that is counted");
   int tid = threadIdx.x;
   asm volatile("" : "+v"(tid));                              // (what follows from it is not made ahead of the loop over rows and spilled)
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), V = c.V, words = (V + 31) >> 5;
@@ -669,7 +676,7 @@ __device__ __forceinline__ void row_first(const SelCtx& c, const MaskView& mv, R
   float rival0 = -INFINITY, rival1 = -INFINITY;
   if (1 + tid < c.W) rival0 = c.scores_in[row + 1 + tid];
   if (1 + tid + NT < c.W) rival1 = c.scores_in[row + 1 + tid + NT];
-  if (!all_valid && !mv.ok) {
+  if (__builtin_expect(!all_valid && !mv.ok, 0)) {
     if (tid == 0) mark_dead(c, row);
     return;
   }
@@ -681,10 +688,12 @@ __device__ __forceinline__ void row_first(const SelCtx& c, const MaskView& mv, R
   fill_exp_tab(L.tab, NT);
   for (int i = tid; i < kHistBins; i += NT) P.hist[i] = 0;
   if (tid == 0) { P.n = 0; P.crowded = 0; }
-  if (!(s_in > -INFINITY)) {
+  if (__builtin_expect(!(s_in > -INFINITY), 0)) {
     if (tid == 0) mark_dead(c, row);
     return;
   }
+  const bool by_load = 6 * c.W <= V && 4 * c.W + 256 <= kPickCap;
+  if (!by_load) __syncthreads();                             // (publishes the table and the empty histogram, while the logits are on their way)
   // validity bits and the row's tail as in row_dense
   uint32_t vbits = 0xffffu;
   const bool whole = all_valid && V == kBlockV;
@@ -720,10 +729,10 @@ __device__ __forceinline__ void row_first(const SelCtx& c, const MaskView& mv, R
 #pragma unroll
   for (int i = 0; i < NV4; i++) best4[i] = max_raw(max_raw(xv[4 * i], xv[4 * i + 1]), max_raw(xv[4 * i + 2], xv[4 * i + 3]));
   const float mb = wave_max(max_raw(max_raw(best4[0], best4[1]), max_raw(best4[2], best4[3])));
-  // down to where the threshold is looked for: the worst of all where they fit in the list (W may be most of them: 163 beams over 256
+  // down to where the threshold is looked for: the worst of all where one load holds them (W may be most of them: 163 beams over 256
   // tokens gave up with the best of every four, 17.9 us instead of 11.2), else the worst of the threads' best of a load
   float low = INFINITY;
-  if (V <= kPickCap) {
+  if (V <= 4 * NT) {
 #pragma unroll
     for (int j = 0; j < 4; j++) low = fminf(low, xv[j] > -INFINITY ? xv[j] : INFINITY);
   } else {
@@ -733,24 +742,26 @@ __device__ __forceinline__ void row_first(const SelCtx& c, const MaskView& mv, R
   low = -wave_max(-low);
   const bool any = __any(rival0 > -INFINITY || rival1 > -INFINITY);
   if (lane == 0) { P.top[wave] = mb; P.low[wave] = low; P.others[wave] = any; }
-  __syncthreads();                                           // (publishes the table and the empty histogram too)
-  const float hi = wave_max(lane < NWV ? P.top[lane & (NWV - 1)] : -INFINITY), lo = -wave_max(lane < NWV ? -P.low[lane & (NWV - 1)] : -INFINITY);
-  const bool pick = !__any(lane < NWV && P.others[lane & (NWV - 1)]);
-  if (!(hi > -INFINITY)) {
-    if (tid == 0) mark_dead(c, row);
-    return;
-  }
-  const Bins bins = make_bins(hi, hi - lo);
-  const bool by_load = 4 * c.W <= V;
-  if (pick) {
-    if (by_load) {
+  float hi = 0.f, lo = 0.f;
+  bool pick = true;
+  Bins bins = {0.f, 0};
+  auto look = [&]() __attribute__((always_inline)) {
+    hi = wave_max(lane < NWV ? P.top[lane & (NWV - 1)] : -INFINITY);
+    lo = -wave_max(lane < NWV ? -P.low[lane & (NWV - 1)] : -INFINITY);
+    pick = !__any(lane < NWV && P.others[lane & (NWV - 1)]);
+    bins = make_bins(hi, hi - lo);
+  };
+  if (by_load) {
+    __syncthreads();                                         // (publishes the table and the empty histogram too)
+    look();
+    if (__builtin_expect(!(hi > -INFINITY), 0)) {
+      if (tid == 0) mark_dead(c, row);
+      return;
+    }
+    if (pick) {
 #pragma unroll
       for (int i = 0; i < NV4; i++)
         if (best4[i] > -INFINITY) atomicAdd(&P.hist[bins.of(best4[i])], 1u);
-    } else {
-#pragma unroll
-      for (int e = 0; e < 4 * NV4; e++)
-        if (xv[e] > -INFINITY) atomicAdd(&P.hist[bins.of(xv[e])], 1u);
     }
   }
   // the wavefront's sum relative to its own maximum, as in row_dense
@@ -791,6 +802,18 @@ __device__ __forceinline__ void row_first(const SelCtx& c, const MaskView& mv, R
   S = wave_sum(S);
   if (lane == 0) { L.m[0][wave] = mb; L.s[0][wave] = S; }
   __syncthreads();
+  if (!by_load) {
+    look();
+    if (__builtin_expect(!(hi > -INFINITY), 0)) {
+      if (tid == 0) mark_dead(c, row);
+      return;
+    }
+    if (pick) {
+#pragma unroll
+      for (int e = 0; e < 4 * NV4; e++)
+        if (xv[e] > -INFINITY) atomicAdd(&P.hist[bins.of(xv[e])], 1u);
+    }
+  }
   const float m_w = (lane < NWV) ? L.m[0][lane & (NWV - 1)] : -INFINITY;
   const double Sw = (lane < NWV) ? L.s[0][lane & (NWV - 1)] : 0.0;
   const double total_S = wave_sum(Sw * exp_rel(max_raw(m_w, hi - 600.f), -(double)hi * ek.c, L.tab, ek));
@@ -810,12 +833,13 @@ __device__ __forceinline__ void row_first(const SelCtx& c, const MaskView& mv, R
     __syncthreads();
     if (wave == 0) row_leaves(c, row, bias, best, L.key[0]);
   };
-  if (!pick) { leave(); return; }
+  if (__builtin_expect(!pick, 0)) { leave(); return; }
   int par = 0;
+  if (!by_load) __syncthreads();
   uint32_t total = hist_threshold_all<NT>(P.hist, (uint32_t)c.W, &P.thr, P.red, par);
   __syncthreads();
   float T = bins.floor_of(P.thr);
-  if (by_load && (T == kNoThreshold || total < (uint32_t)c.W)) {        // (too few of them, or the W-th is among the lowest: all candidates)
+  if (__builtin_expect(by_load && (T == kNoThreshold || total < (uint32_t)c.W), 0)) {        // (too few of them, or the W-th is among the lowest: all candidates)
 #pragma unroll
     for (int e = 0; e < 4 * NV4; e++)
       if (xv[e] > -INFINITY) atomicAdd(&P.hist[bins.of(xv[e])], 1u);
@@ -824,7 +848,7 @@ __device__ __forceinline__ void row_first(const SelCtx& c, const MaskView& mv, R
     __syncthreads();
     T = bins.floor_of(P.thr);
   }
-  if (T == kNoThreshold && total >= (uint32_t)c.W) { leave(); return; }        // (the W-th lies below lo)
+  if (__builtin_expect(T == kNoThreshold && total >= (uint32_t)c.W, 0)) { leave(); return; }        // (the W-th lies below lo)
   // what reaches it (all of fewer than W), in bins of one width
   if (T > kNoThreshold) T = __fadd_rn(bias, T);
   const float end = T == kNoThreshold ? __fadd_rn(bias, lo) : T, scale = best > end ? fminf((float)(kHistBins - 1) / (best - end), 1e30f) : 0.f;
@@ -884,12 +908,12 @@ __device__ __forceinline__ void row_first(const SelCtx& c, const MaskView& mv, R
     return;
   }
   bool fits = n <= kPickCap;
-  if (fits) {
+  if (__builtin_expect(fits, 1)) {
     if (hist_prefix<NT>(P.hist, (uint32_t)c.W, &P.thr, P.red, par) > 128u) P.crowded = 1u;
     __syncthreads();
     fits = !P.crowded;
   }
-  if (!fits) { leave(); return; }
+  if (__builtin_expect(!fits, 0)) { leave(); return; }
   const int cut = P.thr, m = cut < kHistBins - 1 ? (int)P.hist[cut + 1] : n;
   __syncthreads();                                           // (the bin after the cut is read before any counter moves)
   order_by_bins<NT>(P.list, P.tmp, P.hist, n, m, cut, best, scale);
@@ -1108,9 +1132,8 @@ __device__ __forceinline__ void gather_rows(const SelCtx& c, const MaskView& mv,
 //   cost 16 us to dispatch; the live rows of 8 requests spread over 1021 workgroups 3 us more than at the front of 512, which is
 //   two to a CU).  With so few rows at work a row is dealt to twice as many threads.
 //   PICK: first rows may select as well.  They have a loop of their own: what the selection keeps in registers slows other rows down.  us where
-//   all rows are live, with one loop, with two and in the kernel without PICK: 32 x 256 beams over 8192 tokens 79.6, 77.2, 76.5; 8 x 128
-//   21.9, 21.6, 21.3; 64 x 128 over 1000 63.4, 60.1, 58.5; 185 x 485 over 500 564, 535 (507 before there was a selection here: many short
-//   rows are what still loses by it).
+//   all rows are live, here and in the kernel without PICK: 32 x 256 beams over 8192 tokens 72.0, 73.0; 8 x 128 21.7, 21.3; 64 x 128 over 1000
+//   59.6, 58.8; 185 x 485 over 500 512, 507 (short rows that are many lose by the code beside them).
 constexpr size_t kStrideGrid = 512;
 template <bool STRIDE, int NT, bool PICK>
 __global__ void __launch_bounds__(NT, STRIDE ? 4 : 6) k_rows(SelCtx c) {

@@ -480,3 +480,23 @@ def test_level_0_of_more_requests_than_workgroups(gr, oracle_lib, V, masked):  #
         mask = gr.gr_item_mask_build(to_dev(items), V)
     want = oracle_lib.beam_select(items, logits, sc, pf, 0)
     assert_select_equal(run_select(gr, mask, logits, sc, pf, rg, 0), want)
+
+
+@pytest.mark.parametrize("V,W", [(8192, 96), (8192, 544), (8192, 545), (8192, 1024), (4096, 544), (4096, 1024), (3264, 544), (3263, 544), (602, 100), (602, 101), (256, 97)])
+@pytest.mark.parametrize("alike", [False, True])
+def test_level_0_selects_beside_its_rows(gr, oracle_lib, V, W, alike):  # noqa: F811
+    """Around the numbers of beams up to which the threshold is looked for among the best of every four logits: the workgroup's list holds what
+    reaches it, also where the logits of a four are as good as equal, and the request is not left to the second kernel."""
+    rng = np.random.default_rng(V + W)
+    B = 3
+    logits = (3.0 * rng.standard_normal((B, W, V))).astype(np.float32)
+    if alike:
+        logits = np.repeat(logits[:, :, ::4], 4, axis=2)[:, :, :V] + (1e-3 * rng.standard_normal((B, W, V))).astype(np.float32)
+    sc, pf, rg = gr_synth.initial_beam_state(B, W, 3)
+    workspace = torch.zeros(gr.select_workspace_bytes(B, W, V, 3), dtype=torch.uint8, device="cuda:0")
+    r = gr.gr_beam_select(None, to_dev(logits), to_dev(sc), to_dev(pf), to_dev(rg), 0, workspace=workspace)
+    torch.cuda.synchronize()
+    assert_select_equal({k: v.cpu().numpy() for k, v in r.items()}, oracle_lib.beam_select(None, logits, sc, pf, 0))
+    words = (4 * B * W + 255) // 256 * 64                      # (the rows' modes lie behind their biases)
+    modes = workspace.view(torch.int32)[words:words + B * W].view(B, W)[:, 0].cpu() & 3
+    assert (modes == 3).all()
