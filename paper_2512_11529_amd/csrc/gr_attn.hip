@@ -412,6 +412,11 @@ k_beam_attn(AttnCtx c) {
   // (workgroups of 4 waves meet between tiles: another one on the CU computes meanwhile, and waits for memory are longer the earlier a tile's loads have to
   // have landed; 16 prompts of 60-700 tokens 36.2 us with 3, 35.6)
   constexpr int HEAD = NWAVES * KS == 4 ? 0 : D == 128 ? 3 : 2;
+  // K loads of a tile that go out before the references are settled and the first operands read.  Tiles of head size 64 are short: where long prompts are streamed
+  // by about a workgroup per CU, every tile waits for the way from the meeting to its loads.  us with none and with these: 60 x 16384 tokens x 56 beams, 8
+  // query and 2 KV heads, 180, 171; 128 x 8000 x 30 109, 105; 40 of 4000-12000 x 120, 8 heads, 207, 202.  64 x 8000 x 100, 8 heads, where a CU's two workgroups
+  // compute in turn, 200, 202 (with all of K's 205).  Head size 128: 80 of 12768-18396 x 150, 2 heads, 400, 393, but 160 x 8000 x 120 256, 261: none there.
+  constexpr int EARLY = !KV8 && !CAUSAL && D == 64 ? (KS == 2 ? CPW : 1) : 0;
   // Q's rows: behind the tiles, of two sets half of them behind either's; of 4 waves, in place of the V tiles
   static_assert(NWAVES == 8 || MWG * D == 2 * TILE, "Q fits the V tiles' place");
   auto q_at = [&](int row) { return KS == 2 ? 4 * TILE + row * D + (row >= MWG / 2 ? 5 * TILE - TILE : 0) : (kQSeparate ? 4 : 2) * TILE + row * D; };
@@ -797,6 +802,20 @@ k_beam_attn(AttnCtx c) {
     int vs = 0;                                        // three V tiles: the place of V(t), which rdo.v has in it
     auto step = [&](auto slot_c, f32x16 (&s_in)[KT / 32][NCB], f32x16 (&s_out)[KT / 32][NCB], int t) {      // tile t in slot slot_c
       constexpr int slot = decltype(slot_c)::value;
+      int v_to;
+      auto ask = [&]() __attribute__((always_inline)) {
+        v_to = VS == 3 ? (vs == 0 ? 2 : vs - 1) : slot ^ 1;
+        advance(true, false);
+        advance(false, false);
+        if (__builtin_expect(t >= seldom, KS == 2)) {                               // (one test for what the last steps have to do)
+          if (t == touch_own) touch_own_rows(v_to, prow0);
+          if (t + kAheadK >= tl) { if (t + kAheadK > tl) advance(true, true); else offsets_of_last(true); }
+          if (t + kAheadV >= tl) { if (t + kAheadV > tl) advance(false, true); else offsets_of_last(false); }
+        }
+#pragma unroll
+        for (int i = 0; i < EARLY; i++) tload_chunk(true, slot, i);
+      };
+      if (EARLY > 0) ask();
       l_run[0] += rs;
       if (CAUSAL && seg0 + t * KT + KT - 1 > wave_tok0) causal_mask(s_in, seg0 + t * KT);       // (wave-uniform) past the wave's first token
       // (one branch where the tiles are many; two sets, whose kernels are short of registers, spilled with it: FP8 codes, 12 x 900 x 60 beams 21.4 us, 19.2)
@@ -807,16 +826,9 @@ k_beam_attn(AttnCtx c) {
         settle();
         raise_to(T::colmax(s_in) * cp);
       }
-      const int v_to = VS == 3 ? (vs == 0 ? 2 : vs - 1) : slot ^ 1;
-      advance(true, false);
-      advance(false, false);
-      if (__builtin_expect(t >= seldom, KS == 2)) {                               // (one test for what the last steps have to do)
-        if (t == touch_own) touch_own_rows(v_to, prow0);
-        if (t + kAheadK >= tl) { if (t + kAheadK > tl) advance(true, true); else offsets_of_last(true); }
-        if (t + kAheadV >= tl) { if (t + kAheadV > tl) advance(false, true); else offsets_of_last(false); }
-      }
+      if (EARLY == 0) ask();
       T::template fused<HEAD>([&](int j) __attribute__((always_inline)) {
-        const int i = j / T::SPREAD;
+        const int i = j / T::SPREAD + EARLY;
         if (KV8) {
           if (j % T::SPREAD || i >= 2 * P8) return;
           if (i < P8) {
